@@ -8,7 +8,7 @@
 // The addition's carry runs through the whole row, so a row is not updated at once: lane l holds word l
 // and works on row t - l in step t, taking the carry that lane l - 1 produced for the same row one step
 // earlier (all carries of a wavefront are one 64-bit lane mask, so handing them on is one scalar shift).
-// A wavefront covers a strip of 4,096 columns; a longer cur takes one workgroup per strip, each reading
+// A wavefront covers a strip of 2,048 columns; a longer cur takes one workgroup per strip, each reading
 // the carries out of the strip before it.  The rows stay where they were written, one step after the
 // other, and the alignment is read back from (n, m): equal operators pair, otherwise left if bit j-1 of
 // V_i is set (L[i][j-1] = L[i][j]), else up; on the host for short sequences, on the GPU for long ones.
@@ -22,7 +22,7 @@ namespace {
 
 typedef unsigned long long u64;
 
-constexpr uint32_t kAlignLenLimit = 1u << 16;          // at most 16 strips
+constexpr uint32_t kAlignLenLimit = 1u << 16;          // at most 32 strips
 constexpr size_t kAlignRowBytesLimit = 1ull << 30;     // rows kept for the walk back
 constexpr uint32_t kBlock = 32;                        // steps between two looks at the neighbouring strip
 constexpr uint32_t kGroup = 8;                         // steps whose masks are looked up together
@@ -122,7 +122,7 @@ struct RowsArgs {
 // All rows of one strip.  my_ids: entry t is the id of this lane's row in step t; table: this lane's word of an LDS
 // mask row of key 0 (inverted).  carry[strip][block]: bit u = carry out of the strip's last lane in step 32 * block + u,
 // bit 32 = the word is there (the value and its arrival are one store, so no fence is needed); cleared before the
-// launch.  A strip waits only for the strip before it, which was started before it and waits for no later one.
+// launch.  A strip waits only for the strip before it, which waits for no later one, and not for ever (kPollLimit).
 template <class Id, bool TAKES, bool GIVES>
 __device__ __forceinline__ void strip_rows(const RowsArgs &a, const Id *my_ids, const uint8_t *table) {
   constexpr bool kLds = sizeof(Id) == 2;

@@ -3,14 +3,22 @@
 // swap policy induces, compute the memory in use at every operator, its peak, and the
 // memory reduction entries (excess over the budget per operator).
 //
-// One workgroup of 1024 lanes handles one scan: per-operator class sums are gathered
-// with 64-bit integer atomics (order-independent, hence deterministic), a chunked
-// workgroup prefix scan over the operators gives the amount held on entry to each
-// operator, and, if the per-event timeline is wanted, a second chunked scan over each
-// event list places every event at its canonical position.  At the sizes of a training
-// iteration (thousands of operators, up to 10^5 events) the work is latency-bound;
-// keeping one scan inside one workgroup makes a batch of scans (one per candidate
-// policy) a single launch.
+// Event lists come in operator order, so everything follows from running sums along each list: the sums of the
+// positive and of the negative deltas and the count of the positive ones, taken at the first event of every
+// operator (OpAt).  With P and N these sums over both lists at operator t, the memory of t is
+//     base + P[t + 1] + N[t],
+// and an event's place and total in the canonical order are its own list's running values plus differences of
+// OpAt entries at t and t + 1.  No accumulator is cleared and nothing is added atomically.
+//
+// Short traces: one workgroup keeps the events in registers and the OpAt table in LDS, one launch.  Long ones: three
+// launches over tiles of events (sums per tile; running sums and OpAt; operators and timeline).  A list that
+// turns out not to be in operator order is gathered per operator with 64-bit integer atomics instead
+// (order-independent, hence deterministic); it has no timeline.
+//
+// Bound by latency: barriers and dependent loads in a short trace (124 + 24 events, 66 operators: 6.3 us in one
+// workgroup; with sums gathered by atomics, fences and running values in device memory 31 us), launches and one pass
+// each over the events in a long one (100,000 + 40,000 events with a timeline: 4.0 + 8.8 + 4.1 us; with operators
+// and timeline left to one workgroup 1,084 us; 1,048,574 + 20,014 events, 65,536 operators: 58 us, was 221).
 #include <algorithm>
 #include <cstring>
 
@@ -21,375 +29,675 @@ namespace {
 constexpr int kThreads = 1024;
 constexpr int kWaves = kThreads / 64;
 
+// running values of one list before the first event of an operator
+struct OpAt { int64_t sp, sn; uint32_t f, cp; };       // sums of positive / negative deltas, events, positive events
+struct TileSum { int64_t sp, sn; uint32_t cp, flags; };
+struct Best { int64_t val; uint32_t idx, over; };
+
 struct ScanArgs {
   const ss_event_t *ev;    uint64_t n_ev;
   const ss_event_t *pev;   uint64_t n_pe;
   uint32_t n_ops;          int want_timeline;
   int64_t base, budget;
-  // scratch
-  int64_t *csum;    // [4][n_ops] sum of deltas per (class, operator)
-  uint32_t *ccnt;   // [4][n_ops] number of events per (class, operator)
-  int64_t *before;  // [n_ops] total held on entry to the operator, without base
-  uint32_t *evstart;// [n_ops] canonical position of the operator's first event
-  int64_t *segsum;  // [4][n_ops] running class sum of the own list at the operator's first event
-  uint32_t *segcnt; // [4][n_ops]
-  int64_t *sumx;    // [n_ev + n_pe] exclusive running sum of the event's own class in its list
-  uint32_t *cntx;   // [n_ev + n_pe]
+  // scratch (device memory; a short trace needs none)
+  OpAt *at;           // [2][n_ops + 1]
+  int64_t *pos, *net; // [n_ops] per-operator sums of a list out of order
+  int64_t *sumx;      // [n_ev + n_pe] inclusive running sum of the event's own class in its list
+  uint32_t *cntx;     // [n_ev + n_pe] events of its own class before it in its list
+  TileSum *tiles;     // [tiles of both lists]
+  Best *best;         // [blocks of operators]
+  uint32_t *ctl;      // [0] operator blocks done, [1] flags
+  uint64_t tile;      // events per tile
+  uint32_t tiles0, tiles1;
   // outputs
   int64_t *per_op, *mre, *timeline;
-  ss_scan_result_t *res;
-  uint32_t *flags;  // bit 0: event names an operator >= n_ops; bit 1: a list is not in operator order
-  int res_flags;    // also report the flags in res->reserved (for callers that read nothing but res)
+  ss_scan_result_t *res;    // the flags go to res->reserved (bit 0: an event names an operator >= n_ops, nothing
+                            // else is meaningful; bit 1: a list is not in operator order)
 };
 
-__device__ inline int64_t shfl_up_i64(int64_t v, int d) {
-  int lo = __shfl_up((int)(uint32_t)(uint64_t)v, d, 64);
-  int hi = __shfl_up((int)(uint32_t)((uint64_t)v >> 32), d, 64);
+// ---- wavefront and workgroup sums -------------------------------------------------------------------------------
+
+// v of another lane by one data-parallel move, 0 where there is none
+template <int kCtrl, int kRows>
+__device__ __forceinline__ int64_t dpp_i64(int64_t v) {
+  const int lo = __builtin_amdgcn_update_dpp(0, (int)(uint32_t)(uint64_t)v, kCtrl, kRows, 0xF, false);
+  const int hi = __builtin_amdgcn_update_dpp(0, (int)((uint64_t)v >> 32), kCtrl, kRows, 0xF, false);
   return (int64_t)(((uint64_t)(uint32_t)hi << 32) | (uint32_t)lo);
 }
 
-// Inclusive prefix sum over the workgroup (lane order = threadIdx.x); returns the
-// inclusive value and the workgroup total.  `wsum` holds one entry per wavefront.
-__device__ inline int64_t block_scan_i64(int64_t v, int64_t *wsum, int64_t &total) {
-  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-#pragma unroll
-  for (int d = 1; d < 64; d <<= 1) {
-    int64_t o = shfl_up_i64(v, d);
-    if (lane >= d) v += o;
-  }
-  __syncthreads();               // wsum may still be read from the previous call
-  if (lane == 63) wsum[w] = v;
-  __syncthreads();
-  int64_t add = 0, tot = 0;
-#pragma unroll
-  for (int i = 0; i < kWaves; ++i) {
-    int64_t x = wsum[i];
-    if (i < w) add += x;
-    tot += x;
-  }
-  total = tot;
-  return v + add;
+// inclusive prefix sum over the 64 lanes: within rows of 16, then the rows' last lanes handed on
+__device__ __forceinline__ int64_t wave_scan(int64_t v) {
+  v += dpp_i64<0x111, 0xF>(v);
+  v += dpp_i64<0x112, 0xF>(v);
+  v += dpp_i64<0x114, 0xF>(v);
+  v += dpp_i64<0x118, 0xF>(v);
+  v += dpp_i64<0x142, 0xA>(v);
+  v += dpp_i64<0x143, 0xC>(v);
+  return v;
+}
+
+__device__ __forceinline__ int64_t lane_i64(int64_t v, int lane) {
+  return (int64_t)(((uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)((uint64_t)v >> 32), lane) << 32) |
+                   (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(uint64_t)v, lane));
+}
+
+// operator of the event before lane 0's, else of the lane before
+__device__ __forceinline__ uint32_t prev_lane(uint32_t v, uint32_t before) {
+  return (uint32_t)__builtin_amdgcn_update_dpp((int)before, (int)v, 0x138, 0xF, 0xF, false);
 }
 
 __device__ inline void add_i64(int64_t *p, int64_t v) {
   atomicAdd(reinterpret_cast<unsigned long long *>(p), (unsigned long long)v);
 }
 
-// class of an event: 0 policy alloc, 1 trace alloc, 2 trace release, 3 policy release
-__device__ inline int event_class(bool policy, int64_t delta) {
-  return policy ? (delta >= 0 ? 0 : 3) : (delta >= 0 ? 1 : 2);
+__device__ __forceinline__ void better(Best &a, const Best &b) {
+  if (b.val > a.val || (b.val == a.val && b.idx < a.idx)) { a.val = b.val; a.idx = b.idx; }
+  a.over += b.over;
 }
 
-// phase 1: gather class sums and counts per operator (integer atomics: any order, same result).
-// Neighbouring events mostly belong to the same operator, and 64 lanes adding to one address are
-// served one after the other: so each wavefront first folds every run of equal operators among its
-// 64 consecutive events (two wavefront prefix sums, two ballots) and only the first lane of a run
-// adds the run's totals.  Workgroup `wg` of `n_wg` takes every n_wg-th stretch of events; the
-// accumulators must have been cleared before any workgroup starts.  Returns this lane's share of the
-// flags (bit 0: operator out of range, bit 1: list not in operator order).
-__device__ __forceinline__ uint32_t gather_events(const ScanArgs &a, uint32_t wg, uint32_t n_wg) {
-  const uint32_t tid = threadIdx.x;
-  const uint32_t n = a.n_ops;
-  uint32_t bad = 0;
-  const int lane = tid & 63;
-  const uint64_t below = lane ? (~0ull >> (64 - lane)) : 0ull;           // bits of the lanes before this one
-  for (int list = 0; list < 2; ++list) {
-    const ss_event_t *L = list ? a.pev : a.ev;
-    const uint64_t cnt = list ? a.n_pe : a.n_ev;
-    const int cpos = list ? 0 : 1, cneg = list ? 3 : 2;
-    constexpr int kAhead = 4;            // events in flight per lane: the loop is bound by load latency
-    for (uint64_t g0 = (uint64_t)wg * kAhead * kThreads; g0 < cnt; g0 += (uint64_t)n_wg * kAhead * kThreads) {
-      ss_event_t xs[kAhead];
-      uint32_t before0[kAhead];          // lane 0 only: operator of the event before the wavefront's first
+__device__ __forceinline__ Best wave_best(Best b) {
 #pragma unroll
-      for (int u = 0; u < kAhead; ++u) {
-        const uint64_t e = g0 + (uint64_t)u * kThreads + tid;
-        xs[u] = ss_event_t{0xFFFFFFFFu, 0, 0};
-        before0[u] = 0;
-        if (e < cnt) {
-          xs[u] = L[e];
-          if (lane == 0 && e > 0) before0[u] = L[e - 1].op_idx;
-        }
-      }
+  for (int d = 32; d >= 1; d >>= 1) {
+    Best o;
+    o.val = (int64_t)(((uint64_t)(uint32_t)__shfl_xor((int)((uint64_t)b.val >> 32), d, 64) << 32) |
+                      (uint32_t)__shfl_xor((int)(uint32_t)(uint64_t)b.val, d, 64));
+    o.idx = (uint32_t)__shfl_xor((int)b.idx, d, 64);
+    o.over = (uint32_t)__shfl_xor((int)b.over, d, 64);
+    better(b, o);
+  }
+  return b;
+}
+
+constexpr uint32_t kNoOp = 0xFFFFFFFFu;
+
+__device__ __forceinline__ Best no_best() { return Best{INT64_MIN, kNoOp, 0}; }
+
+__device__ __forceinline__ void write_result(const ScanArgs &a, const Best &b, int64_t final_total, uint32_t flags) {
+  ss_scan_result_t r;
+  if (flags & 1u) {
+    r = ss_scan_result_t{a.base, a.base, -1, 0, 0, flags};
+  } else {
+    r.peak = a.n_ops ? b.val : a.base;
+    r.final_total = final_total;
+    r.argpeak_op = a.n_ops ? (int32_t)b.idx : -1;
+    r.n_over = b.over;
+    r.sorted = (flags & 2u) ? 0u : 1u;
+    r.reserved = flags;
+  }
+  *a.res = r;
+}
+
+// memory at operator t; writes the per-operator outputs
+__device__ __forceinline__ void put_op(const ScanArgs &a, uint32_t t, int64_t p, Best &b) {
+  if (a.per_op) a.per_op[t] = p;
+  const int64_t ex = p > a.budget ? p - a.budget : 0;
+  if (a.mre) a.mre[t] = ex;
+  better(b, Best{p, t, ex > 0 ? 1u : 0u});
+}
+
+// canonical place and total of an event: class 0 policy alloc, 1 trace alloc, 2 trace release, 3 policy release.
+// sum: inclusive running sum of its class in its list, cnt: events of its class before it there
+__device__ __forceinline__ void put_event(const ScanArgs &a, bool policy, bool positive, int64_t sum, uint32_t cnt,
+                                          const OpAt &e0, const OpAt &e1, const OpAt &p0, const OpAt &p1) {
+  uint32_t q = e0.f + p0.f;                        // events of earlier operators
+  int64_t v;
+  const uint32_t n0 = p1.cp - p0.cp, n1 = e1.cp - e0.cp;
+  if (policy && positive) {
+    q += cnt - p0.cp;
+    v = e0.sp + e0.sn + p0.sn + sum;
+  } else if (positive) {
+    q += n0 + cnt - e0.cp;
+    v = e0.sn + p0.sn + p1.sp + sum;
+  } else if (!policy) {
+    q += n0 + n1 + cnt - (e0.f - e0.cp);
+    v = p0.sn + p1.sp + e1.sp + sum;
+  } else {
+    q += n0 + (e1.f - e0.f) + cnt - (p0.f - p0.cp);
+    v = e1.sn + e1.sp + p1.sp + sum;
+  }
+  a.timeline[q] = a.base + v;
+}
+
+// OpAt entries of operators (prev, op] take the values before the event that starts op.  A lane fills a short gap by
+// itself; the wavefront fills a long one together.
+__device__ __forceinline__ void fill_gap(OpAt *at, bool has, uint32_t from, uint32_t to, const OpAt &x) {
+  constexpr uint32_t kAlone = 4;
+  const uint32_t len = has ? to - from : 0;
+  if (len && len <= kAlone)
+    for (uint32_t t = from; t < to; ++t) at[t] = x;
+  uint64_t wide = __ballot(len > kAlone);
+  const uint32_t lane = threadIdx.x & 63;
+  while (wide) {
+    const int src = __builtin_ctzll(wide);
+    wide &= wide - 1;
+    OpAt y;
+    y.sp = lane_i64(x.sp, src);
+    y.sn = lane_i64(x.sn, src);
+    y.f = (uint32_t)__builtin_amdgcn_readlane((int)x.f, src);
+    y.cp = (uint32_t)__builtin_amdgcn_readlane((int)x.cp, src);
+    const uint32_t lo = (uint32_t)__builtin_amdgcn_readlane((int)from, src), hi = (uint32_t)__builtin_amdgcn_readlane((int)to, src);
+    for (uint32_t t = lo + lane; t < hi; t += 64) at[t] = y;
+  }
+}
+
+// ---- running sums over a stretch of elements ---------------------------------------------------------------------
+
+// Totals of the wavefronts' stretches, then what comes before each, and the totals after them.
+struct SumShared {
+  int64_t sp[64], sn[64], tot_sp, tot_sn;
+  uint32_t cp[64], tot_cp;
+};
+
+// T * K consecutive elements, K per thread, element k * T + thread; dead ones have delta 0 and pos false.  Out: the sums
+// of the positive and of the negative deltas and the count of the positive events before each element, carries
+// included.  One barrier after the totals are written and one after they are summed; the caller puts one between calls.
+template <int T, int K>
+__device__ __forceinline__ void wg_sums(SumShared &sh, const int64_t *delta, const bool *pos, int64_t carry_sp,
+                                        int64_t carry_sn, uint32_t carry_cp, int64_t *xsp, int64_t *xsn, uint32_t *xcp) {
+  constexpr int W = T / 64, S = W * K;
+  static_assert(S <= 64, "the stretches' totals are summed by one wavefront");
+  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+  const uint64_t below = lane ? (~0ull >> (64 - lane)) : 0ull;
 #pragma unroll
-      for (int u = 0; u < kAhead; ++u) {
-        const uint64_t e0 = g0 + (uint64_t)u * kThreads;
-        if (e0 >= cnt) break;                                            // uniform: shuffles inside
-        const uint64_t e = e0 + tid;
-        const bool in = e < cnt;
-        const ss_event_t x = xs[u];
-        const bool live = in && x.op_idx < n;
-        if (in && !live) bad |= 1u;
-        uint32_t prev = (uint32_t)__shfl_up((int)x.op_idx, 1, 64);
-        if (lane == 0) prev = before0[u];
-        if (in && e > 0 && prev > x.op_idx) bad |= 2u;
-        const bool head = lane == 0 || prev != x.op_idx;
-        const bool is_pos = x.delta >= 0;
-        const uint64_t H = __ballot(head);
-        const uint64_t P = __ballot(live && is_pos), N = __ballot(live && !is_pos);
-        // inclusive wavefront prefix sums of the positive and of the negative deltas
-        int64_t ip = live && is_pos ? x.delta : 0, ineg = live && !is_pos ? x.delta : 0;
-#pragma unroll
-        for (int d = 1; d < 64; d <<= 1) {
-          const int64_t op_ = shfl_up_i64(ip, d), on_ = shfl_up_i64(ineg, d);
-          if (lane >= d) { ip += op_; ineg += on_; }
-        }
-        const uint64_t later_heads = H & ~below & ~(1ull << lane);
-        const int end = later_heads ? __ffsll((unsigned long long)later_heads) - 1 : 64;   // one past the run's last lane
-        int64_t bp = shfl_up_i64(ip, 1), bn = shfl_up_i64(ineg, 1);      // totals before this lane
-        if (lane == 0) { bp = 0; bn = 0; }
-        const int last = end - 1;
-        const int64_t ep = (int64_t)(((uint64_t)(uint32_t)__shfl((int)(uint32_t)((uint64_t)ip >> 32), last, 64) << 32) |
-                                     (uint32_t)__shfl((int)(uint32_t)(uint64_t)ip, last, 64));
-        const int64_t en = (int64_t)(((uint64_t)(uint32_t)__shfl((int)(uint32_t)((uint64_t)ineg >> 32), last, 64) << 32) |
-                                     (uint32_t)__shfl((int)(uint32_t)(uint64_t)ineg, last, 64));
-        if (head && live) {
-          const uint64_t run = (end == 64 ? ~0ull : ((1ull << end) - 1)) & ~below;
-          const uint32_t np = (uint32_t)__popcll(P & run), nn = (uint32_t)__popcll(N & run);
-          if (np) {
-            add_i64(a.csum + (uint64_t)cpos * n + x.op_idx, ep - bp);
-            atomicAdd(a.ccnt + (uint64_t)cpos * n + x.op_idx, np);
-          }
-          if (nn) {
-            add_i64(a.csum + (uint64_t)cneg * n + x.op_idx, en - bn);
-            atomicAdd(a.ccnt + (uint64_t)cneg * n + x.op_idx, nn);
-          }
-        }
-      }
+  for (int k = 0; k < K; ++k) {
+    const int64_t p = pos[k] ? delta[k] : 0, q = delta[k] - p;
+    const int64_t ip = wave_scan(p), iq = wave_scan(q);
+    const uint64_t b = __ballot(pos[k]);
+    xsp[k] = ip - p;
+    xsn[k] = iq - q;
+    xcp[k] = (uint32_t)__popcll(b & below);
+    if (lane == 63) {
+      sh.sp[k * W + w] = ip;
+      sh.sn[k * W + w] = iq;
+      sh.cp[k * W + w] = (uint32_t)__popcll(b);
     }
   }
-  return bad;
+  __syncthreads();
+  if (w == 0) {
+    const int64_t p = lane < S ? sh.sp[lane] : 0, q = lane < S ? sh.sn[lane] : 0, c = lane < S ? sh.cp[lane] : 0;
+    const int64_t ip = wave_scan(p), iq = wave_scan(q), ic = wave_scan(c);
+    if (lane < S) {
+      sh.sp[lane] = carry_sp + ip - p;
+      sh.sn[lane] = carry_sn + iq - q;
+      sh.cp[lane] = carry_cp + (uint32_t)(ic - c);
+    }
+    if (lane == 63) {
+      sh.tot_sp = carry_sp + ip;
+      sh.tot_sn = carry_sn + iq;
+      sh.tot_cp = carry_cp + (uint32_t)ic;
+    }
+  }
+  __syncthreads();
+#pragma unroll
+  for (int k = 0; k < K; ++k) {
+    xsp[k] += sh.sp[k * W + w];
+    xsn[k] += sh.sn[k * W + w];
+    xcp[k] += sh.cp[k * W + w];
+  }
 }
 
-// `gathered`: phases 0 and 1 have been done by launches before this one (a.flags holds their flags)
-__device__ __forceinline__ void scan_body(const ScanArgs &a, bool gathered) {
-  __shared__ int64_t wsum[kWaves];
-  __shared__ int64_t red_val[kWaves];
-  __shared__ uint32_t red_idx[kWaves];
-  __shared__ uint32_t red_cnt[kWaves];
-  __shared__ uint32_t s_flags;
-  const uint32_t tid = threadIdx.x;
-  const uint32_t n = a.n_ops;
-  if (tid == 0) s_flags = gathered ? *a.flags : 0;
-  if (!gathered) {
-    // phase 0: clear the per-operator accumulators
-    for (uint64_t i = tid; i < 4ull * n; i += kThreads) {
-      a.csum[i] = 0;
-      a.ccnt[i] = 0;
+// An event as a lane holds it: `prev` is the operator of the event before it in its list (its own for the first).
+struct Elem {
+  uint32_t op, prev;
+  int64_t delta;
+  bool live, pos, first, last;
+};
+
+// Elements first .. first + T * K of one list, or (both) of the two lists back to back, all loads in flight at once;
+// returns the flags.
+template <int T, int K>
+__device__ __forceinline__ uint32_t load_events(const ss_event_t *L0, uint64_t n0, const ss_event_t *L1, uint64_t n1,
+                                                uint64_t first, uint64_t end, uint32_t n_ops, Elem *x) {
+  ss_event_t raw[K];
+  uint32_t before[K], flags = 0;
+#pragma unroll
+  for (int k = 0; k < K; ++k) {
+    const uint64_t i = first + (uint64_t)k * T + threadIdx.x;
+    x[k].live = i < end;
+    const bool second = i >= n0;
+    const ss_event_t *L = second ? L1 : L0;
+    const uint64_t e = second ? i - n0 : i;
+    raw[k] = ss_event_t{kNoOp, 0, 0};
+    before[k] = kNoOp;
+    x[k].first = e == 0;
+    x[k].last = e + 1 == (second ? n1 : n0);
+    if (x[k].live) {
+      raw[k] = L[e];
+      if ((threadIdx.x & 63) == 0 && e) before[k] = L[e - 1].op_idx;
+    }
+  }
+#pragma unroll
+  for (int k = 0; k < K; ++k) {
+    Elem &y = x[k];
+    y.op = raw[k].op_idx;
+    y.delta = y.live ? raw[k].delta : 0;
+    y.pos = y.live && raw[k].delta >= 0;
+    y.prev = prev_lane(y.op, before[k]);
+    if (y.first) y.prev = y.op;
+    y.last = y.last && y.live;
+    if (y.live && y.op >= n_ops) flags |= 1u;
+    if (y.live && y.prev > y.op) flags |= 2u;
+  }
+  return flags;
+}
+
+// OpAt entries that this element decides: those of the operators after the previous event's up to its own, and after
+// the list's last event those up to n_ops.
+__device__ __forceinline__ void fill_from(OpAt *at, const Elem &y, uint32_t e, int64_t sp, int64_t sn, uint32_t cp,
+                                          uint32_t n_ops) {
+  const bool ok = y.live && y.op < n_ops && y.prev <= y.op;
+  fill_gap(at, ok && (y.first || y.prev != y.op), y.first ? 0 : y.prev + 1, y.op + 1, OpAt{sp, sn, e, cp});
+  if (__ballot(ok && y.last))
+    fill_gap(at, ok && y.last, y.op + 1, n_ops + 1,
+             OpAt{sp + (y.pos ? y.delta : 0), sn + (y.pos ? 0 : y.delta), e + 1, cp + (y.pos ? 1 : 0)});
+}
+
+// A list out of order: per-operator sums by integer atomics.  Neighbouring events mostly belong to the same operator,
+// and 64 lanes adding to one address are served one after the other: so each run of equal operators among a
+// wavefront's events is folded first and only its first lane adds.
+__device__ __forceinline__ void gather_run(int64_t *pos, int64_t *net, const Elem &y, uint32_t n_ops) {
+  const int lane = threadIdx.x & 63;
+  const bool live = y.live && y.op < n_ops, head = lane == 0 || y.first || y.prev != y.op;
+  const int64_t p = live && y.pos ? y.delta : 0, d = live ? y.delta : 0;
+  const int64_t ip = wave_scan(p), id = wave_scan(d);
+  const uint64_t heads = __ballot(head);
+  const uint64_t above = lane == 63 ? 0 : heads >> (lane + 1);
+  const int last = above ? lane + __builtin_ctzll(above) : 63;
+  const int64_t ep = (int64_t)(((uint64_t)(uint32_t)__shfl((int)((uint64_t)ip >> 32), last, 64) << 32) |
+                               (uint32_t)__shfl((int)(uint32_t)(uint64_t)ip, last, 64));
+  const int64_t ed = (int64_t)(((uint64_t)(uint32_t)__shfl((int)((uint64_t)id >> 32), last, 64) << 32) |
+                               (uint32_t)__shfl((int)(uint32_t)(uint64_t)id, last, 64));
+  if (head && live) {
+    const int64_t tp = ep - (ip - p), td = ed - (id - d);
+    if (tp) add_i64(pos + y.op, tp);
+    if (td) add_i64(net + y.op, td);
+  }
+}
+
+// Operators from the gathered sums: a chunked prefix scan of one workgroup.  Leaves the total in sh.tot_sp.
+template <int T>
+__device__ __forceinline__ Best ops_of_sums(const ScanArgs &a, const int64_t *pos, const int64_t *net, SumShared &sh) {
+  Best b = no_best();
+  int64_t carry = 0;
+  for (uint32_t c0 = 0; c0 < a.n_ops; c0 += T) {
+    const uint32_t t = c0 + threadIdx.x;
+    const int64_t d[1] = {t < a.n_ops ? net[t] : 0};
+    const bool all[1] = {true};
+    int64_t x[1], none[1];
+    uint32_t cnt[1];
+    wg_sums<T, 1>(sh, d, all, carry, 0, 0, x, none, cnt);
+    if (t < a.n_ops) put_op(a, t, a.base + x[0] + pos[t], b);
+    carry = sh.tot_sp;
+    __syncthreads();
+  }
+  if (threadIdx.x == 0) sh.tot_sp = carry;
+  return b;
+}
+
+// ---- one workgroup: short traces, candidates of a batch ------------------------------------------------------------
+
+struct WgShared {
+  SumShared sums;
+  int64_t ev_sp, ev_sn;                    // totals of the first list
+  uint32_t ev_cp, flags;
+  Best best[kWaves];
+};
+
+template <int T>
+__device__ __forceinline__ Best wg_best(Best b, Best *part) {
+  b = wave_best(b);
+  if ((threadIdx.x & 63) == 0) part[threadIdx.x >> 6] = b;
+  __syncthreads();
+  b = no_best();
+  for (int i = 0; i < T / 64; ++i) better(b, part[i]);
+  return b;
+}
+
+// at: 2 * (n_ops + 1) entries; pos, net: n_ops entries, may lie in `at`.  A timeline only if the trace fits one pass.
+template <int T, int K>
+__device__ __forceinline__ void scan_wg(const ScanArgs &a, OpAt *at, int64_t *pos, int64_t *net, WgShared &sh) {
+  const uint32_t n = a.n_ops, tid = threadIdx.x;
+  OpAt *const at_ev = at, *const at_pe = at + n + 1;
+  const uint64_t total = a.n_ev + a.n_pe;
+  if (tid == 0) {
+    sh.flags = 0;
+    sh.ev_sp = sh.ev_sn = 0;
+    sh.ev_cp = 0;
+  }
+  if (!a.n_ev)
+    for (uint32_t t = tid; t <= n; t += T) at_ev[t] = OpAt{0, 0, 0, 0};
+  if (!a.n_pe)
+    for (uint32_t t = tid; t <= n; t += T) at_pe[t] = OpAt{0, 0, 0, 0};
+  __syncthreads();
+  Elem x[K];
+  int64_t delta[K], sp[K], sn[K], carry_sp = 0, carry_sn = 0;
+  uint32_t cp[K], carry_cp = 0;
+  bool pos_of[K];
+  for (uint64_t first = 0; first < total; first += (uint64_t)T * K) {
+    const uint32_t bad = load_events<T, K>(a.ev, a.n_ev, a.pev, a.n_pe, first, total, n, x);
+    if (bad) atomicOr(&sh.flags, bad);
+#pragma unroll
+    for (int k = 0; k < K; ++k) { delta[k] = x[k].delta; pos_of[k] = x[k].pos; }
+    wg_sums<T, K>(sh.sums, delta, pos_of, carry_sp, carry_sn, carry_cp, sp, sn, cp);
+    carry_sp = sh.sums.tot_sp; carry_sn = sh.sums.tot_sn; carry_cp = sh.sums.tot_cp;
+    if (a.n_pe && first + (uint64_t)T * K > a.n_ev) {        // the second list starts from its own zero
+#pragma unroll
+      for (int k = 0; k < K; ++k)
+        if (first + (uint64_t)k * T + tid == a.n_ev) { sh.ev_sp = sp[k]; sh.ev_sn = sn[k]; sh.ev_cp = cp[k]; }
+      __syncthreads();
+#pragma unroll
+      for (int k = 0; k < K; ++k)
+        if (first + (uint64_t)k * T + tid >= a.n_ev) { sp[k] -= sh.ev_sp; sn[k] -= sh.ev_sn; cp[k] -= sh.ev_cp; }
+    }
+    // a wavefront's elements of one k may belong to both lists: each list's are filled in turn
+#pragma unroll
+    for (int k = 0; k < K; ++k) {
+      const uint64_t i = first + (uint64_t)k * T + tid;
+      Elem y = x[k];
+      y.live = x[k].live && i < a.n_ev;
+      y.last = x[k].last && y.live;
+      if (__ballot(y.live)) fill_from(at_ev, y, (uint32_t)i, sp[k], sn[k], cp[k], n);
+      y.live = x[k].live && i >= a.n_ev;
+      y.last = x[k].last && y.live;
+      if (__ballot(y.live)) fill_from(at_pe, y, (uint32_t)(i - a.n_ev), sp[k], sn[k], cp[k], n);
+    }
+    __syncthreads();                                         // the shared totals are written again in the next pass
+  }
+  __syncthreads();
+  const uint32_t flags = sh.flags;
+  Best b = no_best();
+  int64_t final_total = a.base;
+  if (flags & 1u) {
+    if (tid == 0) write_result(a, b, 0, flags);
+    return;
+  }
+  if (flags & 2u) {
+    for (uint32_t t = tid; t < n; t += T) pos[t] = net[t] = 0;
+    __threadfence();
+    __syncthreads();
+    for (uint64_t first = 0; first < total; first += (uint64_t)T * K) {
+      load_events<T, K>(a.ev, a.n_ev, a.pev, a.n_pe, first, total, n, x);
+#pragma unroll
+      for (int k = 0; k < K; ++k) gather_run(pos, net, x[k], n);
     }
     __threadfence();
     __syncthreads();
-    const uint32_t bad = gather_events(a, 0, 1);
-    if (bad) atomicOr(&s_flags, bad);
-  }
-  __threadfence();
-  __syncthreads();
-  const uint32_t flags = s_flags;
-  if (flags & 1u) {                       // an operator index out of range: nothing else is meaningful
-    if (tid == 0) {
-      *a.flags = flags;
-      if (a.res_flags) {
-        ss_scan_result_t r = {a.base, a.base, -1, 0, 0, flags};
-        *a.res = r;
-      }
-    }
-    return;
-  }
-
-  // phase 2: prefix scan over operators
-  int64_t carry = 0;                      // deltas of all operators before this chunk
-  uint32_t carry_cnt = 0;
-  int64_t best = INT64_MIN;
-  uint32_t best_t = 0xFFFFFFFFu, over = 0;
-  for (uint32_t c0 = 0; c0 < n; c0 += kThreads) {
-    const uint32_t t = c0 + tid;
-    int64_t pos = 0, net = 0;
-    uint32_t cnt = 0;
-    if (t < n) {
-      const int64_t s0 = a.csum[t], s1 = a.csum[(uint64_t)n + t], s2 = a.csum[2ull * n + t],
-                    s3 = a.csum[3ull * n + t];
-      pos = s0 + s1;
-      net = pos + s2 + s3;
-      cnt = a.ccnt[t] + a.ccnt[(uint64_t)n + t] + a.ccnt[2ull * n + t] + a.ccnt[3ull * n + t];
-    }
-    int64_t tot, tot_cnt;
-    const int64_t inc = block_scan_i64(net, wsum, tot);
-    const int64_t inc_cnt = block_scan_i64((int64_t)cnt, wsum, tot_cnt);
-    if (t < n) {
-      const int64_t entry = carry + inc - net;            // held on entry to t (without base)
-      const int64_t p = a.base + entry + pos;             // entry + everything t allocates
-      a.before[t] = entry;
-      a.evstart[t] = carry_cnt + (uint32_t)(inc_cnt - cnt);
-      if (a.per_op) a.per_op[t] = p;
-      const int64_t ex = p > a.budget ? p - a.budget : 0;
-      if (a.mre) a.mre[t] = ex;
-      over += ex > 0;
-      if (p > best) { best = p; best_t = t; }             // ascending t per lane: first maximum kept
-    }
-    carry += tot;
-    carry_cnt += (uint32_t)tot_cnt;
-  }
-  // workgroup reduction: maximum, its first operator, number of over-budget operators
-  {
-    const int lane = tid & 63, w = tid >> 6;
-#pragma unroll
-    for (int d = 32; d >= 1; d >>= 1) {
-      const int64_t ob = (int64_t)(((uint64_t)(uint32_t)__shfl_down((int)(uint32_t)((uint64_t)best >> 32), d, 64) << 32) |
-                                   (uint32_t)__shfl_down((int)(uint32_t)(uint64_t)best, d, 64));
-      const uint32_t ot = (uint32_t)__shfl_down((int)best_t, d, 64);
-      const uint32_t oo = (uint32_t)__shfl_down((int)over, d, 64);
-      if (lane + d < 64) {
-        if (ob > best || (ob == best && ot < best_t)) { best = ob; best_t = ot; }
-        over += oo;
-      }
-    }
-    if (lane == 0) { red_val[w] = best; red_idx[w] = best_t; red_cnt[w] = over; }
+    b = ops_of_sums<T>(a, pos, net, sh.sums);
     __syncthreads();
-    if (tid == 0) {
-      int64_t b = INT64_MIN; uint32_t bt = 0xFFFFFFFFu, oc = 0;
-      for (int i = 0; i < kWaves; ++i) {
-        if (red_val[i] > b || (red_val[i] == b && red_idx[i] < bt)) { b = red_val[i]; bt = red_idx[i]; }
-        oc += red_cnt[i];
+    final_total += n ? sh.sums.tot_sp : 0;
+  } else {
+    for (uint32_t t = tid; t < n; t += T)
+      put_op(a, t, a.base + at_ev[t + 1].sp + at_pe[t + 1].sp + at_ev[t].sn + at_pe[t].sn, b);
+    final_total += at_ev[n].sp + at_ev[n].sn + at_pe[n].sp + at_pe[n].sn;
+    if (a.want_timeline) {
+#pragma unroll
+      for (int k = 0; k < K; ++k) {
+        const Elem &y = x[k];
+        const uint64_t i = (uint64_t)k * T + tid;
+        if (i >= total || !y.live) continue;
+        const bool policy = i >= a.n_ev;
+        const uint32_t e = (uint32_t)(policy ? i - a.n_ev : i);
+        put_event(a, policy, y.pos, (y.pos ? sp[k] : sn[k]) + y.delta, y.pos ? cp[k] : e - cp[k], at_ev[y.op],
+                  at_ev[y.op + 1], at_pe[y.op], at_pe[y.op + 1]);
       }
-      ss_scan_result_t r;
-      r.peak = n ? b : a.base;
-      r.final_total = a.base + carry;
-      r.argpeak_op = n ? (int32_t)bt : -1;
-      r.n_over = oc;
-      r.sorted = (flags & 2u) ? 0u : 1u;
-      r.reserved = a.res_flags ? flags : 0;
-      *a.res = r;
-      *a.flags = flags;
     }
   }
-  if (!a.want_timeline || (flags & 2u)) return;
-  __threadfence();
-  __syncthreads();
-
-  // phase 3a: running sum and count of each event's own class along its list; remember
-  // them at the first event of every operator
-  for (int list = 0; list < 2; ++list) {
-    const ss_event_t *L = list ? a.pev : a.ev;
-    const uint64_t cnt = list ? a.n_pe : a.n_ev;
-    const uint64_t out0 = list ? a.n_ev : 0;
-    const int cpos = list ? 0 : 1, cneg = list ? 3 : 2;
-    int64_t cs_pos = 0, cs_neg = 0, cc_pos = 0, cc_neg = 0;      // carries
-    for (uint64_t e0 = 0; e0 < cnt; e0 += kThreads) {
-      const uint64_t e = e0 + tid;
-      ss_event_t x = {0, 0, 0};
-      bool live = e < cnt, is_pos = false;
-      if (live) { x = L[e]; is_pos = x.delta >= 0; }
-      int64_t t_sp, t_sn, t_cp, t_cn;
-      const int64_t i_sp = block_scan_i64(live && is_pos ? x.delta : 0, wsum, t_sp);
-      const int64_t i_sn = block_scan_i64(live && !is_pos ? x.delta : 0, wsum, t_sn);
-      const int64_t i_cp = block_scan_i64(live && is_pos ? 1 : 0, wsum, t_cp);
-      const int64_t i_cn = block_scan_i64(live && !is_pos ? 1 : 0, wsum, t_cn);
-      if (live) {
-        // exclusive values at e
-        const int64_t xsp = cs_pos + i_sp - (is_pos ? x.delta : 0);
-        const int64_t xsn = cs_neg + i_sn - (!is_pos ? x.delta : 0);
-        const uint32_t xcp = (uint32_t)(cc_pos + i_cp - (is_pos ? 1 : 0));
-        const uint32_t xcn = (uint32_t)(cc_neg + i_cn - (!is_pos ? 1 : 0));
-        a.sumx[out0 + e] = is_pos ? xsp : xsn;
-        a.cntx[out0 + e] = is_pos ? xcp : xcn;
-        if (e == 0 || L[e - 1].op_idx != x.op_idx) {
-          a.segsum[(uint64_t)cpos * n + x.op_idx] = xsp;
-          a.segsum[(uint64_t)cneg * n + x.op_idx] = xsn;
-          a.segcnt[(uint64_t)cpos * n + x.op_idx] = xcp;
-          a.segcnt[(uint64_t)cneg * n + x.op_idx] = xcn;
-        }
-      }
-      cs_pos += t_sp; cs_neg += t_sn; cc_pos += t_cp; cc_neg += t_cn;
-    }
-  }
-  __threadfence();
-  __syncthreads();
-
-  // phase 3b: canonical position and running total of every event
-  for (int list = 0; list < 2; ++list) {
-    const ss_event_t *L = list ? a.pev : a.ev;
-    const uint64_t cnt = list ? a.n_pe : a.n_ev;
-    const uint64_t out0 = list ? a.n_ev : 0;
-    for (uint64_t e = tid; e < cnt; e += kThreads) {
-      const ss_event_t x = L[e];
-      const uint32_t t = x.op_idx;
-      const int c = event_class(list != 0, x.delta);
-      uint32_t q = a.evstart[t];
-      int64_t v = a.base + a.before[t];
-      for (int c2 = 0; c2 < c; ++c2) {
-        q += a.ccnt[(uint64_t)c2 * n + t];
-        v += a.csum[(uint64_t)c2 * n + t];
-      }
-      q += a.cntx[out0 + e] - a.segcnt[(uint64_t)c * n + t];
-      v += a.sumx[out0 + e] - a.segsum[(uint64_t)c * n + t] + x.delta;
-      a.timeline[q] = v;
-    }
-  }
+  b = wg_best<T>(b, sh.best);
+  if (tid == 0) write_result(a, b, final_total, flags);
 }
 
-__global__ __launch_bounds__(kThreads) void ss_scan_kernel(ScanArgs a) { scan_body(a, false); }
+// One workgroup takes a trace whose events fit its registers (four a lane) and whose two OpAt tables fit LDS (24 bytes
+// an entry).  Up to there it is the faster form: 6 to 12 us, the three launches of the other take 15 at least.
+constexpr uint32_t kLdsOps = 2900;
+constexpr uint64_t kSmallEvents = 4096;
+
+static size_t lds_at(uint32_t n_ops) { return 2 * ((size_t)n_ops + 1) * sizeof(OpAt); }
+
+template <int T>
+__global__ __launch_bounds__(T) void ss_scan_small_kernel(ScanArgs a) {
+  __shared__ WgShared sh;
+  extern __shared__ OpAt lds[];
+  int64_t *const sums = reinterpret_cast<int64_t *>(lds);
+  scan_wg<T, 4>(a, lds, sums, sums + a.n_ops, sh);
+}
 
 // one workgroup per scan: candidate policies against the same trace in a single launch
+template <bool LDS>
 __global__ __launch_bounds__(kThreads) void ss_scan_batch_kernel(const ScanArgs *__restrict__ args) {
+  __shared__ WgShared sh;
+  extern __shared__ OpAt lds[];
   const ScanArgs a = args[blockIdx.x];
-  scan_body(a, false);
-}
-
-// Long traces: the gather is the part that grows with the number of events (one workgroup takes 1.6 us per
-// thousand events), and it is the part that splits: the accumulators are cleared by one launch, gathered
-// into by a launch of many workgroups, and the rest (the scan over the operators, the timeline) runs in one
-// workgroup as before.
-__global__ __launch_bounds__(kThreads) void ss_scan_clear_kernel(ScanArgs a) {
-  const uint64_t total = 4ull * a.n_ops;
-  for (uint64_t i = (uint64_t)blockIdx.x * kThreads + threadIdx.x; i < total; i += (uint64_t)gridDim.x * kThreads) {
-    a.csum[i] = 0;
-    a.ccnt[i] = 0;
+  if (LDS) {
+    int64_t *const sums = reinterpret_cast<int64_t *>(lds);
+    scan_wg<kThreads, 4>(a, lds, sums, sums + a.n_ops, sh);
+  } else {
+    scan_wg<kThreads, 4>(a, a.at, a.pos, a.net, sh);
   }
-  if (blockIdx.x == 0 && threadIdx.x == 0) *a.flags = 0;
 }
 
-__global__ __launch_bounds__(kThreads) void ss_scan_gather_kernel(ScanArgs a) {
-  const uint32_t bad = gather_events(a, blockIdx.x, gridDim.x);
-  if (bad) atomicOr(a.flags, bad);
+// ---- long traces: three launches over tiles of events ---------------------------------------------------------------
+
+constexpr int kTileThreads = 256, kTileK = 8;
+constexpr uint64_t kTileEvents = (uint64_t)kTileThreads * kTileK;
+constexpr uint64_t kMaxTiles = 1024;                  // per list: every workgroup reads all tiles' sums
+
+// the tile of a workgroup: first the tiles of ev, then those of pev (at least one each)
+struct Tile {
+  bool policy;
+  const ss_event_t *L;
+  uint64_t cnt, lo, hi, out0;        // events of its list; its events [lo, hi) there; where its list starts in sumx
+  uint32_t first, index;             // its list's first tile; its own
+  __device__ explicit Tile(const ScanArgs &a) {
+    index = blockIdx.x;
+    policy = index >= a.tiles0;
+    first = policy ? a.tiles0 : 0;
+    L = policy ? a.pev : a.ev;
+    cnt = policy ? a.n_pe : a.n_ev;
+    out0 = policy ? a.n_ev : 0;
+    lo = (uint64_t)(index - first) * a.tile;
+    hi = lo + a.tile < cnt ? lo + a.tile : cnt;
+  }
+};
+
+// Sums of a tile; also clears what a list out of order would be gathered into.
+__global__ __launch_bounds__(kTileThreads) void ss_scan_tiles_kernel(ScanArgs a) {
+  __shared__ TileSum part[kTileThreads / 64];
+  const Tile tl(a);
+  for (uint64_t i = (uint64_t)blockIdx.x * kTileThreads + threadIdx.x; i < a.n_ops; i += (uint64_t)gridDim.x * kTileThreads)
+    a.pos[i] = a.net[i] = 0;
+  if (blockIdx.x == 0 && threadIdx.x == 0) a.ctl[0] = 0;
+  int64_t sp = 0, sn = 0;
+  uint32_t cp = 0, flags = 0;
+  for (uint64_t lo = tl.lo; lo < tl.hi; lo += kTileEvents) {
+    Elem x[kTileK];
+    flags |= load_events<kTileThreads, kTileK>(tl.L, tl.cnt, nullptr, 0, lo, tl.hi, a.n_ops, x);
+#pragma unroll
+    for (int k = 0; k < kTileK; ++k) {
+      sp += x[k].pos ? x[k].delta : 0;
+      sn += x[k].pos ? 0 : x[k].delta;
+      cp += x[k].pos;
+    }
+  }
+  sp = lane_i64(wave_scan(sp), 63);
+  sn = lane_i64(wave_scan(sn), 63);
+  const int64_t c = lane_i64(wave_scan((int64_t)cp), 63);
+  flags = (__ballot(flags & 1u) ? 1u : 0u) | (__ballot(flags & 2u) ? 2u : 0u);
+  if ((threadIdx.x & 63) == 0) part[threadIdx.x >> 6] = TileSum{sp, sn, (uint32_t)c, flags};
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    TileSum s = part[0];
+    for (int i = 1; i < kTileThreads / 64; ++i) {
+      s.sp += part[i].sp; s.sn += part[i].sn; s.cp += part[i].cp; s.flags |= part[i].flags;
+    }
+    a.tiles[tl.index] = s;
+  }
 }
 
-__global__ __launch_bounds__(kThreads) void ss_scan_finish_kernel(ScanArgs a) { scan_body(a, true); }
+// Running sums along each list: OpAt, and for a timeline each event's own.
+__global__ __launch_bounds__(kTileThreads) void ss_scan_running_kernel(ScanArgs a) {
+  __shared__ SumShared sh;
+  __shared__ TileSum part[kTileThreads / 64];
+  const Tile tl(a);
+  OpAt *const at = a.at + (tl.policy ? (size_t)a.n_ops + 1 : 0);
+  int64_t sp = 0, sn = 0;
+  uint32_t cp = 0, flags = 0;
+  for (uint32_t i = threadIdx.x; i < a.tiles0 + a.tiles1; i += kTileThreads) {
+    const TileSum s = a.tiles[i];
+    flags |= s.flags;
+    if (i >= tl.first && i < tl.index) { sp += s.sp; sn += s.sn; cp += s.cp; }
+  }
+  sp = lane_i64(wave_scan(sp), 63);
+  sn = lane_i64(wave_scan(sn), 63);
+  const int64_t c = lane_i64(wave_scan((int64_t)cp), 63);
+  flags = (__ballot(flags & 1u) ? 1u : 0u) | (__ballot(flags & 2u) ? 2u : 0u);
+  if ((threadIdx.x & 63) == 0) part[threadIdx.x >> 6] = TileSum{sp, sn, (uint32_t)c, flags};
+  __syncthreads();
+  TileSum before = part[0];
+  for (int i = 1; i < kTileThreads / 64; ++i) {
+    before.sp += part[i].sp; before.sn += part[i].sn; before.cp += part[i].cp; before.flags |= part[i].flags;
+  }
+  if (blockIdx.x == 0 && threadIdx.x == 0) a.ctl[1] = before.flags;
+  if (before.flags & 1u) return;
+  if (!tl.cnt)
+    for (uint32_t t = threadIdx.x; t <= a.n_ops; t += kTileThreads) at[t] = OpAt{0, 0, 0, 0};
+  for (uint64_t lo = tl.lo; lo < tl.hi; lo += kTileEvents) {
+    Elem x[kTileK];
+    load_events<kTileThreads, kTileK>(tl.L, tl.cnt, nullptr, 0, lo, tl.hi, a.n_ops, x);
+    if (before.flags & 2u) {
+#pragma unroll
+      for (int k = 0; k < kTileK; ++k) gather_run(a.pos, a.net, x[k], a.n_ops);
+      continue;
+    }
+    int64_t delta[kTileK], xsp[kTileK], xsn[kTileK];
+    uint32_t xcp[kTileK];
+    bool pos[kTileK];
+#pragma unroll
+    for (int k = 0; k < kTileK; ++k) { delta[k] = x[k].delta; pos[k] = x[k].pos; }
+    wg_sums<kTileThreads, kTileK>(sh, delta, pos, before.sp, before.sn, before.cp, xsp, xsn, xcp);
+    before.sp = sh.tot_sp; before.sn = sh.tot_sn; before.cp = sh.tot_cp;
+#pragma unroll
+    for (int k = 0; k < kTileK; ++k) {
+      const uint64_t e = lo + (uint64_t)k * kTileThreads + threadIdx.x;
+      if (a.want_timeline && x[k].live) {
+        a.sumx[tl.out0 + e] = (pos[k] ? xsp[k] : xsn[k]) + delta[k];
+        a.cntx[tl.out0 + e] = pos[k] ? xcp[k] : (uint32_t)e - xcp[k];
+      }
+      fill_from(at, x[k], (uint32_t)e, xsp[k], xsn[k], xcp[k], a.n_ops);
+    }
+    __syncthreads();                                         // sh is written again in the next pass
+  }
+}
 
-constexpr uint64_t kSplitFromEvents = 32768;     // below this one workgroup is as fast as three launches
-
-void launch_scan(hipStream_t s, const ScanArgs &a) {
-  const uint64_t E = a.n_ev + a.n_pe;
-  if (E < kSplitFromEvents) {
-    hipLaunchKernelGGL(ss_scan_kernel, dim3(1), dim3(kThreads), 0, s, a);
+// Operators (workgroups [0, op_wgs)) and, for a timeline, events (the rest).  The last operator workgroup to end folds
+// all their maxima.
+__global__ __launch_bounds__(kThreads) void ss_scan_finish_kernel(ScanArgs a, uint32_t op_wgs) {
+  __shared__ Best part[kWaves];
+  __shared__ SumShared sh;
+  __shared__ uint32_t s_last;
+  const uint32_t n = a.n_ops, tid = threadIdx.x, flags = a.ctl[1];
+  const OpAt *const at_ev = a.at, *const at_pe = a.at + n + 1;
+  if (flags) {
+    if (blockIdx.x) return;
+    Best b = no_best();
+    if (!(flags & 1u)) {
+      b = ops_of_sums<kThreads>(a, a.pos, a.net, sh);
+      b = wg_best<kThreads>(b, part);
+    }
+    if (tid == 0) write_result(a, b, a.base + (n && !(flags & 1u) ? sh.tot_sp : 0), flags);
     return;
   }
-  const uint64_t per_wg = 4ull * kThreads;         // one pass of the gather loop per workgroup
-  const uint32_t g_clear = (uint32_t)std::min<uint64_t>(256, (4ull * a.n_ops + kThreads - 1) / kThreads + 1);
-  const uint32_t g_gather = (uint32_t)std::min<uint64_t>(512, (std::max(a.n_ev, a.n_pe) + per_wg - 1) / per_wg);
-  hipLaunchKernelGGL(ss_scan_clear_kernel, dim3(g_clear), dim3(kThreads), 0, s, a);
-  hipLaunchKernelGGL(ss_scan_gather_kernel, dim3(g_gather), dim3(kThreads), 0, s, a);
-  hipLaunchKernelGGL(ss_scan_finish_kernel, dim3(1), dim3(kThreads), 0, s, a);
+  if (blockIdx.x >= op_wgs) {
+    const uint64_t total = a.n_ev + a.n_pe;
+    for (uint64_t i = (uint64_t)(blockIdx.x - op_wgs) * kThreads + tid; i < total; i += (uint64_t)(gridDim.x - op_wgs) * kThreads) {
+      const bool policy = i >= a.n_ev;
+      const ss_event_t x = policy ? a.pev[i - a.n_ev] : a.ev[i];
+      put_event(a, policy, x.delta >= 0, a.sumx[i], a.cntx[i], at_ev[x.op_idx], at_ev[x.op_idx + 1], at_pe[x.op_idx],
+                at_pe[x.op_idx + 1]);
+    }
+    return;
+  }
+  Best b = no_best();
+  for (uint32_t t = blockIdx.x * kThreads + tid; t < n; t += op_wgs * kThreads)
+    put_op(a, t, a.base + at_ev[t + 1].sp + at_pe[t + 1].sp + at_ev[t].sn + at_pe[t].sn, b);
+  b = wg_best<kThreads>(b, part);
+  const int64_t final_total = a.base + at_ev[n].sp + at_ev[n].sn + at_pe[n].sp + at_pe[n].sn;
+  if (op_wgs > 1) {
+    if (tid == 0) {
+      a.best[blockIdx.x] = b;
+      __threadfence();
+      s_last = atomicAdd(a.ctl, 1u) + 1 == op_wgs;
+    }
+    __syncthreads();
+    if (!s_last) return;
+    __threadfence();
+    b = no_best();
+    for (uint32_t i = tid; i < op_wgs; i += kThreads) better(b, a.best[i]);
+    __syncthreads();
+    b = wg_best<kThreads>(b, part);
+  }
+  if (tid == 0) write_result(a, b, final_total, 0);
+}
+
+constexpr uint32_t kMaxOpWgs = 256;
+
+uint64_t tile_events(uint64_t n_ev, uint64_t n_pe) {
+  return std::max(kTileEvents, ss_align_up((std::max(n_ev, n_pe) + kMaxTiles - 1) / kMaxTiles, kTileEvents));
+}
+
+bool is_short(uint64_t n_ev, uint64_t n_pe, uint32_t n_ops) { return n_ev + n_pe <= kSmallEvents && n_ops <= kLdsOps; }
+
+// Scratch of a long trace from `d` on; returns its size (nothing is assigned where `a` is null).
+size_t scan_scratch(ScanArgs *a, uint8_t *d, uint64_t n_ev, uint64_t n_pe, uint64_t n_ops, bool timeline) {
+  size_t off = 0;
+  auto take = [&](size_t bytes) { uint8_t *p = d + off; off += ss_align_up(bytes, 256); return p; };
+  const uint64_t E = timeline ? n_ev + n_pe : 0;
+  uint8_t *at = take(2 * (n_ops + 1) * sizeof(OpAt)), *pos = take(n_ops * 8), *net = take(n_ops * 8);
+  uint8_t *sumx = take(E * 8), *cntx = take(E * 4), *tiles = take((2 * kMaxTiles + 2) * sizeof(TileSum));
+  uint8_t *best = take(kMaxOpWgs * sizeof(Best)), *ctl = take(8);
+  if (a) {
+    a->at = (OpAt *)at;
+    a->pos = (int64_t *)pos;
+    a->net = (int64_t *)net;
+    a->sumx = (int64_t *)sumx;
+    a->cntx = (uint32_t *)cntx;
+    a->tiles = (TileSum *)tiles;
+    a->best = (Best *)best;
+    a->ctl = (uint32_t *)ctl;
+  }
+  return off;
+}
+
+void launch_scan(hipStream_t s, ScanArgs &a) {
+  if (is_short(a.n_ev, a.n_pe, a.n_ops)) {
+    if (a.n_ev + a.n_pe <= 1024)
+      hipLaunchKernelGGL(ss_scan_small_kernel<256>, dim3(1), dim3(256), lds_at(a.n_ops), s, a);
+    else
+      hipLaunchKernelGGL(ss_scan_small_kernel<kThreads>, dim3(1), dim3(kThreads), lds_at(a.n_ops), s, a);
+    return;
+  }
+  a.tile = tile_events(a.n_ev, a.n_pe);
+  a.tiles0 = (uint32_t)std::max<uint64_t>(1, (a.n_ev + a.tile - 1) / a.tile);
+  a.tiles1 = (uint32_t)std::max<uint64_t>(1, (a.n_pe + a.tile - 1) / a.tile);
+  const uint32_t tiles = a.tiles0 + a.tiles1;
+  const uint32_t op_wgs = (uint32_t)std::min<uint64_t>(kMaxOpWgs, std::max<uint64_t>(1, ((uint64_t)a.n_ops + kThreads - 1) / kThreads));
+  const uint32_t ev_wgs = a.want_timeline ? (uint32_t)std::min<uint64_t>(2048, (a.n_ev + a.n_pe + kThreads - 1) / kThreads) : 0;
+  hipLaunchKernelGGL(ss_scan_tiles_kernel, dim3(tiles), dim3(kTileThreads), 0, s, a);
+  hipLaunchKernelGGL(ss_scan_running_kernel, dim3(tiles), dim3(kTileThreads), 0, s, a);
+  hipLaunchKernelGGL(ss_scan_finish_kernel, dim3(op_wgs + ev_wgs), dim3(kThreads), 0, s, a, op_wgs);
 }
 
 }  // namespace
 
 // ---- the scan for callers that cannot allocate ------------------------------------------------
 //
-// Same kernel, but its scratch (per-operator class sums and counts, entry totals, event
-// positions, per-event class prefixes) lives in a static device array instead of memory the
-// library allocates, and inputs and outputs are the caller's device arrays: the call only
-// enqueues the scan's kernels (one, or three for a long trace) on the caller's stream.
+// Same kernels, but their scratch lies in a static device array instead of memory the library allocates, and inputs
+// and outputs are the caller's device arrays: the call only enqueues the scan's kernels (one, or three for a long
+// trace) on the caller's stream.
 
 constexpr uint32_t kStaticMaxOps = 65536;
 constexpr uint64_t kStaticMaxEvents = 262144;
-constexpr size_t kStaticBytes =
-    2 * (4ull * kStaticMaxOps * 8)        // csum, segsum
-    + 1ull * kStaticMaxOps * 8            // before
-    + 2 * (4ull * kStaticMaxOps * 4)      // ccnt, segcnt
-    + 1ull * kStaticMaxOps * 4            // evstart
-    + kStaticMaxEvents * 8                // sumx
-    + kStaticMaxEvents * 4                // cntx
-    + 256;                                // flags
+constexpr size_t kStaticBytes = 2 * (kStaticMaxOps + 1) * sizeof(OpAt) + 2 * kStaticMaxOps * 8 + kStaticMaxEvents * 12 +
+                                (2 * kMaxTiles + 2) * sizeof(TileSum) + kMaxOpWgs * sizeof(Best) + 8 * 256;
 static __device__ __align__(256) uint8_t scratch[kStaticBytes];
 
 // Address of `scratch` on each device (the name itself is only a host-side handle): resolved once
@@ -436,26 +744,14 @@ extern "C" int ss_timeline_scan_static(ss_ctx *ctx, void *stream, const ss_event
   const int rc = static_scratch_ptr(dev, &d, &e);
   if (rc == SS_E_HIP) SS_HIP(e);
   if (rc != SS_OK) return rc;
-  const uint64_t n = kStaticMaxOps, E = kStaticMaxEvents;    // fixed layout: every piece at its maximum
-  size_t off = 0;
-  auto take = [&](size_t bytes) { size_t o = off; off += bytes; return o; };
-  ScanArgs a;
+  ScanArgs a = {};
   a.ev = d_ev; a.n_ev = n_ev;
   a.pev = d_pev; a.n_pe = n_pe;
   a.n_ops = n_ops; a.want_timeline = d_timeline != nullptr;
   a.base = base; a.budget = budget;
-  a.csum = (int64_t *)(d + take(4 * n * 8));
-  a.segsum = (int64_t *)(d + take(4 * n * 8));
-  a.before = (int64_t *)(d + take(n * 8));
-  a.sumx = (int64_t *)(d + take(E * 8));
-  a.ccnt = (uint32_t *)(d + take(4 * n * 4));
-  a.segcnt = (uint32_t *)(d + take(4 * n * 4));
-  a.evstart = (uint32_t *)(d + take(n * 4));
-  a.cntx = (uint32_t *)(d + take(E * 4));
-  a.flags = (uint32_t *)(d + take(256));
+  scan_scratch(&a, d, n_ev, n_pe, n_ops, true);              // at most kStaticBytes
   a.per_op = d_per_op; a.mre = d_mre; a.timeline = d_timeline;
   a.res = d_res;
-  a.res_flags = 1;
   launch_scan((hipStream_t)stream, a);
   SS_HIP(hipGetLastError());
   return SS_OK;
@@ -473,59 +769,51 @@ extern "C" int ss_timeline_scan_batch(ss_ctx *ctx, const ss_event_t *ev, uint64_
       if (pe_start[c] > pe_start[c + 1]) return SS_E_INVAL;
     if (pe_start[0] != 0 || (n_pe && !pev) || n_ev + n_pe >= (1ull << 31)) return SS_E_INVAL;
     const uint64_t n = n_ops;
+    const bool lds = n_ops <= kLdsOps;                 // the OpAt tables fit LDS
     size_t off = 0;
     auto take = [&](size_t bytes) { size_t o = off; off += ss_align_up(bytes, 256); return o; };
     const size_t o_ev = take(n_ev * sizeof(ss_event_t)), o_pev = take(n_pe * sizeof(ss_event_t));
-    const size_t o_args = take((size_t)k * sizeof(ScanArgs)), o_res = take((size_t)k * sizeof(ss_scan_result_t));
-    const size_t o_flags = take((size_t)k * 4);
-    const size_t per_scan = ss_align_up(4 * n * 8, 256) + 3 * ss_align_up(n * 8, 256) + ss_align_up(4 * n * 4, 256) +
-                            ss_align_up(n * 4, 256);
-    const size_t o_work = take((size_t)k * per_scan);
-    const size_t host_bytes = (size_t)k * (sizeof(ScanArgs) + sizeof(ss_scan_result_t) + 4) + 1024;
-    int rc = ss_scratch_reserve(ctx, off, host_bytes);
+    const size_t per_scan = lds ? 0 : ss_align_up(2 * (n + 1) * sizeof(OpAt), 256) + 2 * ss_align_up(n * 8, 256);
+    const size_t o_work = take((size_t)k * per_scan), o_per_op = take(per_op ? (size_t)k * n * 8 : 0);
+    const size_t args_bytes = ss_align_up((size_t)k * sizeof(ScanArgs), 256);
+    int rc = ss_scratch_reserve(ctx, off, args_bytes + (size_t)k * sizeof(ss_scan_result_t));
     if (rc != SS_OK) return rc;
-    uint8_t *d = (uint8_t *)ctx->d_scratch, *h = (uint8_t *)ctx->h_scratch;
+    uint8_t *d = (uint8_t *)ctx->d_scratch, *h = (uint8_t *)ctx->h_scratch, *hd = nullptr;
+    SS_HIP(hipHostGetDevicePointer((void **)&hd, h, 0));
     hipStream_t s = ctx->s_aux;
     if (n_ev) SS_HIP(hipMemcpyAsync(d + o_ev, ev, n_ev * sizeof(ss_event_t), hipMemcpyHostToDevice, s));
     if (n_pe) SS_HIP(hipMemcpyAsync(d + o_pev, pev, n_pe * sizeof(ss_event_t), hipMemcpyHostToDevice, s));
-    ScanArgs *ha = (ScanArgs *)h;                       // pinned: argument blocks, then results and flags
+    ScanArgs *ha = (ScanArgs *)h;                       // pinned, read and written by the kernel: arguments, results
     for (uint32_t c = 0; c < k; ++c) {
       uint8_t *w = d + o_work + (size_t)c * per_scan;
-      size_t wo = 0;
-      auto wtake = [&](size_t bytes) { uint8_t *p = w + wo; wo += ss_align_up(bytes, 256); return p; };
-      ScanArgs a;
-      std::memset(&a, 0, sizeof(a));
+      ScanArgs a = {};
       a.ev = (const ss_event_t *)(d + o_ev); a.n_ev = n_ev;
       a.pev = (const ss_event_t *)(d + o_pev) + pe_start[c]; a.n_pe = pe_start[c + 1] - pe_start[c];
-      a.n_ops = n_ops; a.want_timeline = 0;
+      a.n_ops = n_ops;
       a.base = base; a.budget = budget;
-      a.csum = (int64_t *)wtake(4 * n * 8);
-      a.before = (int64_t *)wtake(n * 8);
-      a.per_op = (int64_t *)wtake(n * 8);
-      a.mre = (int64_t *)wtake(n * 8);
-      a.ccnt = (uint32_t *)wtake(4 * n * 4);
-      a.evstart = (uint32_t *)wtake(n * 4);
-      a.res = (ss_scan_result_t *)(d + o_res) + c;
-      a.flags = (uint32_t *)(d + o_flags) + c;
+      if (!lds) {
+        a.at = (OpAt *)w;
+        a.pos = (int64_t *)(w + ss_align_up(2 * (n + 1) * sizeof(OpAt), 256));
+        a.net = a.pos + ss_align_up(n * 8, 256) / 8;
+      }
+      if (per_op) a.per_op = (int64_t *)(d + o_per_op) + (size_t)c * n;
+      a.res = (ss_scan_result_t *)(hd + args_bytes) + c;
       ha[c] = a;
     }
-    SS_HIP(hipMemcpyAsync(d + o_args, ha, (size_t)k * sizeof(ScanArgs), hipMemcpyHostToDevice, s));
-    hipLaunchKernelGGL(ss_scan_batch_kernel, dim3(k), dim3(kThreads), 0, s, (const ScanArgs *)(d + o_args));
+    const ScanArgs *dargs = (const ScanArgs *)hd;
+    if (lds) hipLaunchKernelGGL(ss_scan_batch_kernel<true>, dim3(k), dim3(kThreads), lds_at(n_ops), s, dargs);
+    else hipLaunchKernelGGL(ss_scan_batch_kernel<false>, dim3(k), dim3(kThreads), 0, s, dargs);
     SS_HIP(hipGetLastError());
-    uint8_t *hres = h + ss_align_up((size_t)k * sizeof(ScanArgs), 256);
-    uint8_t *hflags = hres + (size_t)k * sizeof(ss_scan_result_t);
-    SS_HIP(hipMemcpyAsync(hres, d + o_res, (size_t)k * sizeof(ss_scan_result_t), hipMemcpyDeviceToHost, s));
-    SS_HIP(hipMemcpyAsync(hflags, d + o_flags, (size_t)k * 4, hipMemcpyDeviceToHost, s));
     SS_HIP(hipStreamSynchronize(s));
+    const ss_scan_result_t *hres = (const ss_scan_result_t *)(h + args_bytes);
+    for (uint32_t c = 0; c < k; ++c)
+      if (hres[c].reserved & 1u) return SS_E_INVAL;
     for (uint32_t c = 0; c < k; ++c) {
-      uint32_t fl;
-      std::memcpy(&fl, hflags + 4 * (size_t)c, 4);
-      if (fl & 1u) return SS_E_INVAL;
+      res[c] = hres[c];
+      res[c].reserved = 0;
     }
-    std::memcpy(res, hres, (size_t)k * sizeof(ss_scan_result_t));
     if (per_op && n) {
-      for (uint32_t c = 0; c < k; ++c)
-        SS_HIP(hipMemcpyAsync(per_op + (size_t)c * n, ha[c].per_op, n * 8, hipMemcpyDeviceToHost, s));
+      SS_HIP(hipMemcpyAsync(per_op, d + o_per_op, (size_t)k * n * 8, hipMemcpyDeviceToHost, s));
       SS_HIP(hipStreamSynchronize(s));
     }
     return SS_OK;
@@ -538,50 +826,61 @@ extern "C" int ss_timeline_scan(ss_ctx *ctx, const ss_event_t *ev, uint64_t n_ev
   return ss_guard([&]() -> int {
     if (!ctx || !res || (n_ev && !ev) || (n_pe && !pev)) return SS_E_INVAL;
     if (n_ops > (1u << 23) || n_ev + n_pe >= (1ull << 31)) return SS_E_INVAL;
-    const uint64_t E = n_ev + n_pe;
-    const uint64_t n = n_ops;
-    // device layout (8-byte aligned pieces first)
-    size_t off = 0;
-    auto take = [&](size_t bytes) { size_t o = off; off += ss_align_up(bytes, 256); return o; };
-    const size_t o_ev = take(n_ev * sizeof(ss_event_t)), o_pev = take(n_pe * sizeof(ss_event_t));
-    const size_t o_csum = take(4 * n * 8), o_before = take(n * 8), o_segsum = take(4 * n * 8);
-    const size_t o_sumx = take(E * 8), o_perop = take(n * 8), o_mre = take(n * 8), o_tl = take(E * 8);
-    const size_t o_ccnt = take(4 * n * 4), o_evstart = take(n * 4), o_segcnt = take(4 * n * 4);
-    const size_t o_cntx = take(E * 4), o_res = take(sizeof(ss_scan_result_t)), o_flags = take(4);
-    int rc = ss_scratch_reserve(ctx, off, 512);
-    if (rc != SS_OK) return rc;
-    uint8_t *d = (uint8_t *)ctx->d_scratch;
+    const uint64_t E = n_ev + n_pe, n = n_ops;
     hipStream_t s = ctx->s_aux;
-    if (n_ev) SS_HIP(hipMemcpyAsync(d + o_ev, ev, n_ev * sizeof(ss_event_t), hipMemcpyHostToDevice, s));
-    if (n_pe) SS_HIP(hipMemcpyAsync(d + o_pev, pev, n_pe * sizeof(ss_event_t), hipMemcpyHostToDevice, s));
-    ScanArgs a;
-    a.res_flags = 0;
-    a.ev = (const ss_event_t *)(d + o_ev); a.n_ev = n_ev;
-    a.pev = (const ss_event_t *)(d + o_pev); a.n_pe = n_pe;
+    ScanArgs a = {};
+    a.n_ev = n_ev; a.n_pe = n_pe;
     a.n_ops = n_ops; a.want_timeline = timeline != nullptr;
     a.base = base; a.budget = budget;
-    a.csum = (int64_t *)(d + o_csum); a.ccnt = (uint32_t *)(d + o_ccnt);
-    a.before = (int64_t *)(d + o_before); a.evstart = (uint32_t *)(d + o_evstart);
-    a.segsum = (int64_t *)(d + o_segsum); a.segcnt = (uint32_t *)(d + o_segcnt);
-    a.sumx = (int64_t *)(d + o_sumx); a.cntx = (uint32_t *)(d + o_cntx);
-    a.per_op = (int64_t *)(d + o_perop); a.mre = (int64_t *)(d + o_mre);
-    a.timeline = (int64_t *)(d + o_tl);
-    a.res = (ss_scan_result_t *)(d + o_res); a.flags = (uint32_t *)(d + o_flags);
+    // A short trace: the kernel reads the events out of pinned host memory and writes every result there (they are
+    // touched once, and a copy each way would cost a launch more than the kernel); else the events go by copy.
+    const bool mapped = is_short(n_ev, n_pe, n_ops);
+    size_t off = 0, hoff = 0;
+    auto take = [](size_t &o, size_t bytes) { size_t at = o; o += ss_align_up(bytes, 256); return at; };
+    size_t &io = mapped ? hoff : off;
+    const size_t o_ev = take(io, n_ev * sizeof(ss_event_t)), o_pev = take(io, n_pe * sizeof(ss_event_t));
+    const size_t o_perop = take(io, per_op ? n * 8 : 0), o_mre = take(io, mre ? n * 8 : 0);
+    const size_t o_tl = take(io, timeline ? E * 8 : 0), o_res = take(hoff, sizeof(ss_scan_result_t));
+    const size_t o_scratch = take(off, mapped ? 0 : scan_scratch(nullptr, nullptr, n_ev, n_pe, n, timeline != nullptr));
+    int rc = ss_scratch_reserve(ctx, off, hoff);
+    if (rc != SS_OK) return rc;
+    uint8_t *d = (uint8_t *)ctx->d_scratch, *h = (uint8_t *)ctx->h_scratch, *hd = nullptr;
+    SS_HIP(hipHostGetDevicePointer((void **)&hd, h, 0));
+    uint8_t *const at = mapped ? hd : d;
+    if (mapped) {
+      if (n_ev) std::memcpy(h + o_ev, ev, n_ev * sizeof(ss_event_t));
+      if (n_pe) std::memcpy(h + o_pev, pev, n_pe * sizeof(ss_event_t));
+    } else {
+      if (n_ev) SS_HIP(hipMemcpyAsync(d + o_ev, ev, n_ev * sizeof(ss_event_t), hipMemcpyHostToDevice, s));
+      if (n_pe) SS_HIP(hipMemcpyAsync(d + o_pev, pev, n_pe * sizeof(ss_event_t), hipMemcpyHostToDevice, s));
+      scan_scratch(&a, d + o_scratch, n_ev, n_pe, n, timeline != nullptr);
+    }
+    a.ev = (const ss_event_t *)(at + o_ev);
+    a.pev = (const ss_event_t *)(at + o_pev);
+    a.per_op = per_op ? (int64_t *)(at + o_perop) : nullptr;
+    a.mre = mre ? (int64_t *)(at + o_mre) : nullptr;
+    a.timeline = timeline ? (int64_t *)(at + o_tl) : nullptr;
+    a.res = (ss_scan_result_t *)(hd + o_res);
     launch_scan(s, a);
     SS_HIP(hipGetLastError());
-    uint8_t *h = (uint8_t *)ctx->h_scratch;            // pinned: result + flags
-    SS_HIP(hipMemcpyAsync(h, d + o_res, sizeof(ss_scan_result_t), hipMemcpyDeviceToHost, s));
-    SS_HIP(hipMemcpyAsync(h + 256, d + o_flags, 4, hipMemcpyDeviceToHost, s));
     SS_HIP(hipStreamSynchronize(s));
-    uint32_t flags;
-    std::memcpy(&flags, h + 256, 4);
+    ss_scan_result_t r;
+    std::memcpy(&r, h + o_res, sizeof(r));
+    const uint32_t flags = r.reserved;
     if (flags & 1u) return SS_E_INVAL;
-    std::memcpy(res, h, sizeof(*res));
-    if (per_op && n) SS_HIP(hipMemcpyAsync(per_op, d + o_perop, n * 8, hipMemcpyDeviceToHost, s));
-    if (mre && n) SS_HIP(hipMemcpyAsync(mre, d + o_mre, n * 8, hipMemcpyDeviceToHost, s));
+    r.reserved = 0;
+    *res = r;
     const bool tl_ok = timeline && !(flags & 2u);
-    if (tl_ok && E) SS_HIP(hipMemcpyAsync(timeline, d + o_tl, E * 8, hipMemcpyDeviceToHost, s));
-    SS_HIP(hipStreamSynchronize(s));
+    if (mapped) {
+      if (per_op && n) std::memcpy(per_op, h + o_perop, n * 8);
+      if (mre && n) std::memcpy(mre, h + o_mre, n * 8);
+      if (tl_ok && E) std::memcpy(timeline, h + o_tl, E * 8);
+    } else {
+      if (per_op && n) SS_HIP(hipMemcpyAsync(per_op, d + o_perop, n * 8, hipMemcpyDeviceToHost, s));
+      if (mre && n) SS_HIP(hipMemcpyAsync(mre, d + o_mre, n * 8, hipMemcpyDeviceToHost, s));
+      if (tl_ok && E) SS_HIP(hipMemcpyAsync(timeline, d + o_tl, E * 8, hipMemcpyDeviceToHost, s));
+      SS_HIP(hipStreamSynchronize(s));
+    }
     if (timeline && !tl_ok) return SS_E_ORDER;
     return SS_OK;
   });

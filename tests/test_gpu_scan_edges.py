@@ -1,0 +1,95 @@
+"""GPU parity of the timeline scan where its kernels change form: one workgroup with its tables in LDS (256 or 1,024
+lanes), tiles over three launches, lists in and out of operator order, operators without events, empty lists, deltas of
+zero.  Exact comparison with the oracle."""
+import numpy as np
+import pytest
+
+import oracle
+import workloads as W
+from test_gpu_trace_scan_match import P, ctx, assert_scan_equal          # noqa: F401  (fixtures)
+from test_zz_no_alloc import static_scan
+
+pytestmark = pytest.mark.gpu
+
+
+def events(rng, n_ev, n_ops, runs=False):
+    """n_ev events in operator order; a few deltas are zero; with `runs` most belong to a few operators"""
+    op = rng.integers(0, n_ops, n_ev)
+    if runs and n_ev:
+        few = op[:1 + n_ev // 500]
+        op = np.where(rng.random(n_ev) < 0.9, few[rng.integers(0, len(few), n_ev)], op)
+    ev = np.zeros(n_ev, dtype=W.EVENT_DT)
+    ev["op_idx"] = np.sort(op)
+    ev["tensor_id"] = np.arange(n_ev)
+    ev["delta"] = rng.integers(-(1 << 40), 1 << 40, n_ev) * (rng.random(n_ev) > 0.05)
+    return ev
+
+
+def both_ways(P, ctx, ev, pe, n_ops, base, budget):               # noqa: F811
+    import torch
+    ora = oracle.timeline_scan(ev, pe, n_ops, base, budget)
+    assert_scan_equal(P.ss_timeline_scan(ctx, ev, pe, n_ops, base, budget, want_timeline=True), ora)
+    if len(ev) + len(pe) <= 262144 and n_ops <= 65536:
+        got = static_scan(P, torch, ctx, ev, pe, n_ops, base, budget)
+        assert got["flags"] == 0
+        assert_scan_equal(got, ora)
+    return ora
+
+
+@pytest.mark.parametrize("n_ev,n_pe,n_ops", [
+    (1, 0, 1), (0, 1, 3), (63, 1, 5), (64, 64, 64), (1000, 24, 66), (1000, 25, 66),          # 256 lanes | 1,024 lanes
+    (255, 257, 2900), (255, 257, 2901),                                                      # LDS tables | device tables
+    (4096, 0, 700), (4000, 97, 700), (0, 4097, 700), (2048, 2049, 3000),                     # one launch | three
+    (2047, 3000, 40), (6144, 2048, 9000), (40, 7, 60001), (30000, 20000, 1),
+])
+def test_edges_of_the_forms(P, ctx, n_ev, n_pe, n_ops):           # noqa: F811
+    rng = np.random.default_rng([n_ev, n_pe, n_ops])
+    ev, pe = events(rng, n_ev, n_ops), events(rng, n_pe, n_ops, runs=True)
+    both_ways(P, ctx, ev, pe, n_ops, -7, 1 << 41)
+
+
+def test_operators_without_events_and_events_of_one_operator(P, ctx):       # noqa: F811
+    rng = np.random.default_rng(5)
+    for n_ops, at in ((2000, [0, 1999]), (2000, [777]), (40000, [39999]), (40000, [0, 20000])):
+        ev = events(rng, 300, len(at))
+        ev["op_idx"] = np.asarray(at)[ev["op_idx"]]
+        pe = events(rng, 5000 if n_ops > 2900 else 50, 1)
+        pe["op_idx"] = at[0]
+        both_ways(P, ctx, ev, pe, n_ops, 1 << 45, 0)
+
+
+@pytest.mark.parametrize("n_ev,n_pe,n_ops", [(700, 200, 66), (3000, 100, 700), (300, 20, 5000), (9000, 4000, 700), (70000, 50, 9000)])
+def test_lists_out_of_order_give_the_same_operators(P, ctx, n_ev, n_pe, n_ops):      # noqa: F811
+    import torch
+    rng = np.random.default_rng([n_ev, n_pe, n_ops, 1])
+    ev, pe = events(rng, n_ev, n_ops, runs=True), events(rng, n_pe, n_ops)
+    ora = oracle.timeline_scan(ev, pe, n_ops, 11, 1 << 40)
+    for a, b in ((ev[rng.permutation(n_ev)], pe), (ev, pe[::-1].copy()), (np.roll(ev, 1), pe)):
+        lib = P.ss_timeline_scan(ctx, a, b, n_ops, 11, 1 << 40)
+        assert_scan_equal(lib, ora, timeline=False)
+        assert lib["sorted"] == 0
+        got = static_scan(P, torch, ctx, a, b, n_ops, 11, 1 << 40)
+        assert got["flags"] == 2
+        assert_scan_equal(got, ora, timeline=False)
+        with pytest.raises(P.SsError) as e:
+            P.ss_timeline_scan(ctx, a, b, n_ops, 11, 1 << 40, want_timeline=True)
+        assert e.value.code == P.SS_E_ORDER
+        one = P.ss_timeline_scan_batch(ctx, a, [b, None], n_ops, 11, 1 << 40, want_per_op=True)
+        assert one[0]["peak"] == ora["peak"] and np.array_equal(one[0]["per_op"], ora["per_op"])
+        bad = a.copy()
+        bad["op_idx"][n_ev // 2] = n_ops
+        with pytest.raises(P.SsError) as e:
+            P.ss_timeline_scan(ctx, bad, b, n_ops, 11, 1 << 40)
+        assert e.value.code == P.SS_E_INVAL
+
+
+@pytest.mark.parametrize("n_ev,n_ops", [(500, 66), (9000, 2900), (9000, 2901), (40, 40000)])
+def test_batch_with_tables_in_lds_and_in_device_memory(P, ctx, n_ev, n_ops):         # noqa: F811
+    rng = np.random.default_rng([n_ev, n_ops])
+    ev = events(rng, n_ev, n_ops)
+    cands = [None, events(rng, 1, n_ops), events(rng, 4100, n_ops), events(rng, 64, n_ops, runs=True)]
+    lib = P.ss_timeline_scan_batch(ctx, ev, cands, n_ops, 3, 1 << 40, want_per_op=True)
+    for r, c in zip(lib, cands):
+        ora = oracle.timeline_scan(ev, c, n_ops, 3, 1 << 40)
+        assert (r["peak"], r["argpeak_op"], r["n_over"], r["final"]) == (ora["peak"], ora["argpeak_op"], ora["n_over"], ora["final"])
+        assert np.array_equal(r["per_op"], ora["per_op"])
