@@ -6,11 +6,12 @@
 //     on the host in 128-bit integer arithmetic.
 // (ii) Re-anchoring of policy items in the current sequence (Sec. 5.1: multi-feature
 //     matching on operator name, call stack and data type with integer comparisons
-//     only).  One wavefront serves one anchor: it counts, with per-lane compares and a
-//     wavefront reduction, how many earlier operators of the reference share the anchor's
-//     key at each of three relaxation levels, then walks the current sequence 64
-//     operators at a time, using ballots and population counts to find the operator of
-//     that ordinal.
+//     only): an anchor's ordinal among the reference's operators with its key, at each of three
+//     relaxation levels, and the operator of that ordinal in the current sequence.  Few anchors or
+//     short sequences: one workgroup per anchor counts and searches.  Many: the layers of a model
+//     share their keys, so the anchors' distinct keys are collected first, one workgroup per key
+//     lists the places where it occurs, and an anchor looks its ordinal up.
+#include <algorithm>
 #include <cstring>
 
 #include "ss_internal.h"
@@ -30,67 +31,93 @@ __device__ inline uint64_t wave_sum_u64(uint64_t v) {
   return v;
 }
 
-// sums[0] = dot, sums[1] = na (current), sums[2] = nb (reference), flags bit 0: token too large
-__global__ __launch_bounds__(256) void ss_cosine_kernel(const ss_op_t *__restrict__ ref, uint32_t n,
-                                                        const ss_op_t *__restrict__ cur, uint32_t m,
-                                                        unsigned long long *sums, uint32_t *flags) {
-  __shared__ uint64_t part[3][4];
-  const uint32_t len = n > m ? n : m;
-  uint64_t dot = 0, na = 0, nb = 0;
-  uint32_t bad = 0;
-  for (uint32_t i = blockIdx.x * blockDim.x + threadIdx.x; i < len; i += gridDim.x * blockDim.x) {
-    const uint64_t a = i < m ? cur[i].op_token : 0;     // the shorter sequence is padded with token 0
-    const uint64_t b = i < n ? ref[i].op_token : 0;
-    if (a >= kTokenLimit || b >= kTokenLimit) bad = 1;
-    dot += a * b;
-    na += a * a;
-    nb += b * b;
-  }
+// What one workgroup adds to the cosine's three sums (na: current, nb: reference); bad: a token is too large.
+struct CosinePart { uint64_t dot, na, nb, bad; };
+
+constexpr uint32_t kMaxParts = 1024;
+
+__device__ __forceinline__ void put_part(CosinePart *out, uint64_t dot, uint64_t na, uint64_t nb, uint32_t bad) {
+  __shared__ CosinePart part[4];
   dot = wave_sum_u64(dot); na = wave_sum_u64(na); nb = wave_sum_u64(nb);
-  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-  if (lane == 0) { part[0][w] = dot; part[1][w] = na; part[2][w] = nb; }
+  const uint64_t any = __ballot(bad != 0);
+  if ((threadIdx.x & 63) == 0) part[threadIdx.x >> 6] = CosinePart{dot, na, nb, any ? 1ull : 0ull};
   __syncthreads();
-  if (threadIdx.x < 3) {
-    uint64_t s = part[threadIdx.x][0] + part[threadIdx.x][1] + part[threadIdx.x][2] + part[threadIdx.x][3];
-    if (s) atomicAdd(sums + threadIdx.x, (unsigned long long)s);
-  }
-  if (bad) atomicOr(flags, 1u);
+  if (threadIdx.x) return;
+  CosinePart s = part[0];
+  for (int w = 1; w < 4; ++w) { s.dot += part[w].dot; s.na += part[w].na; s.nb += part[w].nb; s.bad |= part[w].bad; }
+  out[blockIdx.x] = s;
 }
 
-// occurrence counts per token of both sequences (token 0 never counts)
+// Everything that has to be done before anchors can be looked for, in one pass: the sequences (and anchors) are copied
+// from pinned host memory to device memory if dref / dcur / danc are given, the sums of the cosine taken on the way
+// (unless counted: histograms), and the words of `clear` set (tables of the kernels that follow).
+struct PrepArgs {
+  const ss_op_t *ref, *cur;  const ss_anchor_t *anchors;
+  ss_op_t *dref, *dcur;      ss_anchor_t *danc;
+  uint32_t n, m, k, cosine;
+  uint4 *ones, *zeros;       uint32_t n_ones, n_zeros;       // in 16-byte words
+  CosinePart *part;          // one per workgroup
+};
+
+__global__ __launch_bounds__(256) void ss_prep_kernel(PrepArgs a) {
+  const uint32_t stride = gridDim.x * 256, first = blockIdx.x * 256 + threadIdx.x, len = a.n > a.m ? a.n : a.m;
+  uint64_t dot = 0, na = 0, nb = 0;
+  uint32_t bad = 0;
+  for (uint32_t i = first; i < len; i += stride) {
+    ss_op_t c = {0, 0, 0, 0}, r = {0, 0, 0, 0};         // the shorter sequence is padded with token 0
+    if (i < a.m) c = a.cur[i];
+    if (i < a.n) r = a.ref[i];
+    if (a.dcur && i < a.m) a.dcur[i] = c;
+    if (a.dref && i < a.n) a.dref[i] = r;
+    const uint64_t x = c.op_token, y = r.op_token;
+    if (x >= kTokenLimit || y >= kTokenLimit) bad = 1;
+    dot += x * y;
+    na += x * x;
+    nb += y * y;
+  }
+  if (a.danc)
+    for (uint32_t i = first; i < a.k; i += stride) a.danc[i] = a.anchors[i];
+  for (uint32_t i = first; i < a.n_ones; i += stride) a.ones[i] = uint4{~0u, ~0u, ~0u, ~0u};
+  for (uint32_t i = first; i < a.n_zeros; i += stride) a.zeros[i] = uint4{0, 0, 0, 0};
+  if (a.cosine) put_part(a.part, dot, na, nb, bad);
+}
+
+// occurrence counts per token of both sequences (token 0 never counts).  A model has few operator names, so most
+// additions would meet at a few addresses: each workgroup counts the low tokens in LDS first.
+constexpr uint32_t kLdsTokens = 1024;
+
 __global__ __launch_bounds__(256) void ss_histogram_kernel(const ss_op_t *__restrict__ ref, uint32_t n,
                                                            const ss_op_t *__restrict__ cur, uint32_t m,
                                                            uint32_t *h_ref, uint32_t *h_cur, uint32_t *flags) {
+  __shared__ uint32_t low[2][kLdsTokens];
+  for (uint32_t t = threadIdx.x; t < 2 * kLdsTokens; t += 256) low[0][t] = 0;
+  __syncthreads();
   const uint32_t len = n > m ? n : m;
+  auto add = [&](uint32_t t, uint32_t *mine, uint32_t *all) {
+    if (t >= kTokenLimit) atomicOr(flags, 1u);
+    else if (t >= kLdsTokens) atomicAdd(all + t, 1u);
+    else if (t) atomicAdd(mine + t, 1u);
+  };
   for (uint32_t i = blockIdx.x * blockDim.x + threadIdx.x; i < len; i += gridDim.x * blockDim.x) {
-    if (i < m) {
-      const uint32_t a = cur[i].op_token;
-      if (a >= kTokenLimit) atomicOr(flags, 1u); else if (a) atomicAdd(h_cur + a, 1u);
-    }
-    if (i < n) {
-      const uint32_t b = ref[i].op_token;
-      if (b >= kTokenLimit) atomicOr(flags, 1u); else if (b) atomicAdd(h_ref + b, 1u);
-    }
+    if (i < m) add(cur[i].op_token, low[0], h_cur);
+    if (i < n) add(ref[i].op_token, low[1], h_ref);
+  }
+  __syncthreads();
+  for (uint32_t t = threadIdx.x; t < kLdsTokens; t += 256) {
+    if (low[0][t]) atomicAdd(h_cur + t, low[0][t]);
+    if (low[1][t]) atomicAdd(h_ref + t, low[1][t]);
   }
 }
 
 __global__ __launch_bounds__(256) void ss_histdot_kernel(const uint32_t *__restrict__ h_ref,
                                                          const uint32_t *__restrict__ h_cur, uint32_t vocab,
-                                                         unsigned long long *sums) {
-  __shared__ uint64_t part[3][4];
+                                                         const uint32_t *__restrict__ flags, CosinePart *part) {
   uint64_t dot = 0, na = 0, nb = 0;
   for (uint32_t i = blockIdx.x * blockDim.x + threadIdx.x; i < vocab; i += gridDim.x * blockDim.x) {
     const uint64_t a = h_cur[i], b = h_ref[i];
     dot += a * b; na += a * a; nb += b * b;
   }
-  dot = wave_sum_u64(dot); na = wave_sum_u64(na); nb = wave_sum_u64(nb);
-  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-  if (lane == 0) { part[0][w] = dot; part[1][w] = na; part[2][w] = nb; }
-  __syncthreads();
-  if (threadIdx.x < 3) {
-    uint64_t s = part[threadIdx.x][0] + part[threadIdx.x][1] + part[threadIdx.x][2] + part[threadIdx.x][3];
-    if (s) atomicAdd(sums + threadIdx.x, (unsigned long long)s);
-  }
+  put_part(part, dot, na, nb, *flags);
 }
 
 __device__ inline uint32_t wave_sum_u32(uint32_t v) {
@@ -107,57 +134,24 @@ __device__ inline int nth_set_bit(uint64_t mask, uint32_t need, int lane) {
   return __ffsll((long long)sel) - 1;
 }
 
-// One wavefront per anchor.  land[a] = operator index in cur (or -1), lvl[a] = level (or 255).
-__global__ __launch_bounds__(256) void ss_anchor_kernel(const ss_op_t *__restrict__ ref, uint32_t n,
-                                                        const ss_op_t *__restrict__ cur, uint32_t m,
-                                                        const ss_anchor_t *__restrict__ anchors, uint32_t k,
-                                                        int32_t *land, uint8_t *lvl) {
-  const int lane = threadIdx.x & 63;
-  const uint32_t a = (blockIdx.x * blockDim.x + threadIdx.x) >> 6;
-  if (a >= k) return;                                   // uniform per wavefront
-  const uint32_t i = anchors[a].ref_op, s = anchors[a].out_slot;
-  int32_t result = -1;
-  uint8_t level = 255;
-  if (i < n && ref[i].op_token != 0) {
-    const ss_op_t R = ref[i];
-    // ordinal of ref[i] among the earlier operators with the same key, per level
-    uint32_t r0 = 0, r1 = 0, r2 = 0;
-    for (uint32_t j = lane; j < i; j += 64) {
-      const ss_op_t o = ref[j];
-      const bool e2 = o.op_token == R.op_token;
-      const bool e1 = e2 && o.sig == R.sig;
-      const bool e0 = e1 && o.stack_hash == R.stack_hash;
-      r2 += e2; r1 += e1; r0 += e0;
-    }
-    r0 = wave_sum_u32(r0); r1 = wave_sum_u32(r1); r2 = wave_sum_u32(r2);
-    // operator of that ordinal in cur, per level
-    int32_t f0 = -1, f1 = -1, f2 = -1;
-    uint32_t c0 = 0, c1 = 0, c2 = 0;                    // matches seen so far (uniform)
-    for (uint32_t base = 0; base < m; base += 64) {
-      const uint32_t j = base + lane;
-      bool e0 = false, e1 = false, e2 = false;
-      if (j < m) {
-        const ss_op_t o = cur[j];
-        e2 = o.op_token == R.op_token;
-        e1 = e2 && o.sig == R.sig;
-        e0 = e1 && o.stack_hash == R.stack_hash;
-      }
-      const uint64_t b0 = __ballot(e0), b1 = __ballot(e1), b2 = __ballot(e2);
-      if (f0 < 0) { const uint32_t pc = __popcll(b0); if (c0 + pc > r0) f0 = (int32_t)base + nth_set_bit(b0, r0 - c0, lane); else c0 += pc; }
-      if (f1 < 0) { const uint32_t pc = __popcll(b1); if (c1 + pc > r1) f1 = (int32_t)base + nth_set_bit(b1, r1 - c1, lane); else c1 += pc; }
-      if (f2 < 0) { const uint32_t pc = __popcll(b2); if (c2 + pc > r2) f2 = (int32_t)base + nth_set_bit(b2, r2 - c2, lane); else c2 += pc; }
-      if (f0 >= 0 && f1 >= 0 && f2 >= 0) break;
-    }
-    const int32_t f[3] = {f0, f1, f2};
-    const uint32_t want = R.sig & 0xFFu;
+// Equality of two operators at each relaxation level: (token, stack, sig), (token, sig), (token).
+__device__ __forceinline__ void same_key(const ss_op_t &x, const ss_op_t &y, bool &e0, bool &e1, bool &e2) {
+  e2 = x.op_token == y.op_token;
+  e1 = e2 && x.sig == y.sig;
+  e0 = e1 && x.stack_hash == y.stack_hash;
+}
+
+// The first level whose landing place has the slot and the data type; f[L] < 0: none at level L.
+__device__ __forceinline__ int32_t choose_landing(const ss_op_t *cur, const ss_op_t &R, uint32_t slot, const int32_t f[3],
+                                                  uint8_t &level) {
 #pragma unroll
-    for (int L = 0; L < 3; ++L) {
-      if (result >= 0 || f[L] < 0) continue;
-      const ss_op_t o = cur[f[L]];
-      if (s < o.n_out && (o.sig & 0xFFu) == want) { result = f[L]; level = (uint8_t)L; }
-    }
+  for (int L = 0; L < 3; ++L) {
+    if (f[L] < 0) continue;
+    const ss_op_t o = cur[f[L]];
+    if (slot < o.n_out && (o.sig & 0xFFu) == (R.sig & 0xFFu)) { level = (uint8_t)L; return f[L]; }
   }
-  if (lane == 0) { land[a] = result; lvl[a] = level; }
+  level = 255;
+  return -1;
 }
 
 // Among anchors landing on the same (operator, slot) only the lowest anchor index keeps it.
@@ -168,46 +162,301 @@ __global__ __launch_bounds__(256) void ss_anchor_kernel(const ss_op_t *__restric
 // by one took 2 ms).
 constexpr unsigned long long kEmptyKey = ~0ull;
 
-__global__ __launch_bounds__(256) void ss_claim_kernel(const ss_anchor_t *__restrict__ anchors, uint32_t k,
-                                                       const int32_t *__restrict__ land,
-                                                       unsigned long long *keys, uint32_t *owner,
-                                                       uint32_t *__restrict__ slot_of, uint32_t mask,
-                                                       uint32_t shift) {
-  const uint32_t a = blockIdx.x * blockDim.x + threadIdx.x;
-  if (a >= k) return;
-  const int32_t j = land[a];
-  if (j < 0) return;
-  const unsigned long long key = ((unsigned long long)(uint32_t)j << 32) | anchors[a].out_slot;   // j < 2^31: never kEmptyKey
-  uint32_t h = (uint32_t)((key * 0x9E3779B97F4A7C15ull) >> shift);
+struct ClaimTable {
+  unsigned long long *keys;    // all kEmptyKey before the first claim
+  uint32_t *owner;             // all ones
+  uint32_t mask, shift;
+};
+
+__device__ __forceinline__ uint32_t claim(const ClaimTable &t, int32_t j, uint32_t slot, uint32_t a) {
+  const unsigned long long key = ((unsigned long long)(uint32_t)j << 32) | slot;     // j < 2^31: never kEmptyKey
+  uint32_t h = (uint32_t)((key * 0x9E3779B97F4A7C15ull) >> t.shift);
   // at most k distinct keys in more than 2k slots: a free or matching slot is met within mask + 1 probes
-  for (uint32_t probe = 0; probe <= mask; ++probe) {
-    const unsigned long long seen = atomicCAS(keys + h, kEmptyKey, key);
+  for (uint32_t probe = 0; probe <= t.mask; ++probe) {
+    const unsigned long long seen = atomicCAS(t.keys + h, kEmptyKey, key);
     if (seen == kEmptyKey || seen == key) {
-      atomicMin(owner + h, a);
-      slot_of[a] = h;
-      return;
+      atomicMin(t.owner + h, a);
+      return h;
     }
-    h = (h + 1) & mask;
+    h = (h + 1) & t.mask;
+  }
+  return 0;
+}
+
+struct AnchorArgs {
+  const ss_op_t *ref, *cur;
+  const ss_anchor_t *anchors;
+  uint32_t n, m, k;
+  int32_t *land;               // operator index in cur, or -1
+  uint8_t *lvl;                // its level, or 255
+  uint32_t *slot_of;           // its slot of the claim table
+  ClaimTable table;
+};
+
+// One workgroup per anchor.  Each wavefront counts, over its quarter of the reference up to the anchor and its quarter of
+// the current sequence, the operators with the anchor's key at each level; the ordinal's quarter is then known and its
+// wavefront walks it 64 operators at a time (ballots and population counts find the operator).  Bound by the latency of
+// these walks: 480 anchors of 1,154 operators 8.7 us, claims included; a wavefront per anchor, all of both sequences in
+// one walk, took 13.0 us and the claims 3.1 us in a launch of their own.
+__global__ __launch_bounds__(256) void ss_anchor_kernel(AnchorArgs g) {
+  __shared__ uint32_t in_ref[4][3], in_cur[4][3];
+  __shared__ int32_t found[3];
+  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+  const uint32_t a = blockIdx.x, i = g.anchors[a].ref_op, slot = g.anchors[a].out_slot;
+  if (i >= g.n || g.ref[i].op_token == 0) {              // uniform
+    if (threadIdx.x == 0) { g.land[a] = -1; g.lvl[a] = 255; }
+    return;
+  }
+  const ss_op_t R = g.ref[i];
+  const uint32_t rq = (i + 255) / 256 * 64, cq = (g.m + 255) / 256 * 64;       // quarters, whole strips of 64
+  const uint32_t r_lo = w * rq, r_hi = min(i, r_lo + rq), c_lo = w * cq, c_hi = min(g.m, c_lo + cq);
+  uint32_t r[3] = {0, 0, 0}, c[3] = {0, 0, 0};
+  auto count = [&](const ss_op_t *seq, uint32_t lo, uint32_t hi, uint32_t *out) {
+    constexpr uint32_t kAhead = 4;
+    for (uint32_t j0 = lo + lane; j0 < hi; j0 += 64 * kAhead) {
+      ss_op_t o[kAhead];
+#pragma unroll
+      for (uint32_t u = 0; u < kAhead; ++u) {
+        o[u].op_token = 0;                               // padding: never the anchor's token
+        if (j0 + 64 * u < hi) o[u] = seq[j0 + 64 * u];
+      }
+#pragma unroll
+      for (uint32_t u = 0; u < kAhead; ++u) {
+        bool e0, e1, e2;
+        same_key(o[u], R, e0, e1, e2);
+        out[0] += e0; out[1] += e1; out[2] += e2;
+      }
+    }
+#pragma unroll
+    for (int L = 0; L < 3; ++L) out[L] = wave_sum_u32(out[L]);
+  };
+  count(g.ref, r_lo, r_hi, r);
+  count(g.cur, c_lo, c_hi, c);
+  if (lane < 3) {
+    in_ref[w][lane] = lane == 0 ? r[0] : lane == 1 ? r[1] : r[2];
+    in_cur[w][lane] = lane == 0 ? c[0] : lane == 1 ? c[1] : c[2];
+  }
+  if (threadIdx.x < 3) found[threadIdx.x] = -1;
+  __syncthreads();
+  // this wavefront's levels: the ordinal lies in its quarter
+  uint32_t need[3];
+  bool open[3];
+#pragma unroll
+  for (int L = 0; L < 3; ++L) {
+    uint32_t ord = in_ref[0][L] + in_ref[1][L] + in_ref[2][L] + in_ref[3][L], before = 0;
+    for (int v = 0; v < w; ++v) before += in_cur[v][L];
+    open[L] = ord >= before && ord < before + in_cur[w][L];
+    need[L] = ord - before;
+  }
+  for (uint32_t base = c_lo; (open[0] || open[1] || open[2]) && base < c_hi; base += 64) {
+    const uint32_t j = base + lane;
+    bool e[3] = {false, false, false};
+    if (j < c_hi) same_key(g.cur[j], R, e[0], e[1], e[2]);
+#pragma unroll
+    for (int L = 0; L < 3; ++L) {
+      const uint64_t b = __ballot(e[L]);
+      if (!open[L]) continue;
+      const uint32_t pc = __popcll(b);
+      if (need[L] < pc) {
+        const int at = nth_set_bit(b, need[L], lane);
+        if (lane == 0) found[L] = (int32_t)base + at;
+        open[L] = false;
+      } else {
+        need[L] -= pc;
+      }
+    }
+  }
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    const int32_t f[3] = {found[0], found[1], found[2]};
+    uint8_t level;
+    const int32_t j = choose_landing(g.cur, R, slot, f, level);
+    g.land[a] = j;
+    g.lvl[a] = level;
+    if (j >= 0) g.slot_of[a] = claim(g.table, j, slot, a);
   }
 }
 
-__global__ __launch_bounds__(256) void ss_injective_kernel(uint32_t k, const int32_t *__restrict__ land,
-                                                           const uint8_t *__restrict__ lvl,
-                                                           const uint32_t *__restrict__ slot_of,
-                                                           const uint32_t *__restrict__ owner, int32_t *new_idx,
-                                                           uint8_t *level, uint32_t *n_unmatched) {
-  const uint32_t a = blockIdx.x * blockDim.x + threadIdx.x;
+// ---- many anchors: the distinct keys first ------------------------------------------------------------------------
+//
+// 8,001 anchors over 18,464 + 18,467 operators: comparing every anchor with every operator is bound by the issue of 300
+// million compares (186 us).  With some forty distinct keys the three launches below take 22 us for the lists (bound by
+// the passes of a workgroup over both sequences, one of them twice), 10 for the keys and 7 for the anchors.
+
+// Per level: an open-addressing table of at least 2k slots holding 1 + the anchor that stands for a key, the slots in
+// use, and for each of them where its places in the current sequence are listed and how many there are.
+struct KeyLists {
+  uint32_t *rep[3], *used[3], *start[3], *count[3];
+  uint32_t *n_used;            // [3]; [3..5]: places listed so far
+  uint32_t *key_of[3];         // anchor -> slot
+  uint32_t *rank[3];           // reference operator -> its ordinal, where its key is an anchor's
+  uint32_t *place[3];          // places, key after key
+  uint32_t mask, shift, max_lists;
+};
+
+// More distinct keys (of all levels) than this, or than half the anchors, and a workgroup per key costs more than a
+// wavefront per anchor.
+constexpr uint32_t kMaxLists = 4096;
+
+__device__ __forceinline__ bool same_at(const ss_op_t &x, const ss_op_t &y, int L) {
+  return x.op_token == y.op_token && (L == 2 || x.sig == y.sig) && (L != 0 || x.stack_hash == y.stack_hash);
+}
+
+// workgroup (x, L): the anchors' keys of level L
+__global__ __launch_bounds__(256) void ss_keys_kernel(AnchorArgs g, KeyLists q) {
+  const uint32_t a = blockIdx.x * 256 + threadIdx.x;
+  const int L = blockIdx.y;
+  if (a >= g.k) return;
+  const uint32_t i = g.anchors[a].ref_op;
+  if (i >= g.n) return;
+  const ss_op_t R = g.ref[i];
+  if (R.op_token == 0) return;
+  unsigned long long x = R.op_token;
+  if (L < 2) x |= (unsigned long long)R.sig << 32;
+  if (L < 1) x ^= (unsigned long long)R.stack_hash << 18;
+  uint32_t h = (uint32_t)((x * 0x9E3779B97F4A7C15ull) >> q.shift);
+  for (uint32_t probe = 0; probe <= q.mask; ++probe) {         // at most k keys in more than 2k slots
+    uint32_t seen = __hip_atomic_load(q.rep[L] + h, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if (!seen) {
+      seen = atomicCAS(q.rep[L] + h, 0u, a + 1);
+      if (!seen) {
+        q.used[L][atomicAdd(q.n_used + L, 1u)] = h;
+        break;
+      }
+    }
+    if (same_at(g.ref[g.anchors[seen - 1].ref_op], R, L)) break;
+    h = (h + 1) & q.mask;
+  }
+  q.key_of[L][a] = h;
+}
+
+__global__ __launch_bounds__(1024) void ss_lists_kernel(AnchorArgs g, KeyLists q) {
+  __shared__ uint32_t wave_cnt[2][16], s_start;
+  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+  const uint64_t below = lane ? (~0ull >> (64 - lane)) : 0ull;
+  const uint32_t n0 = q.n_used[0], n1 = q.n_used[1], n2 = q.n_used[2];
+  if (n0 + n1 + n2 > q.max_lists) return;
+  for (uint32_t it = blockIdx.x; it < n0 + n1 + n2; it += gridDim.x) {
+    const int L = it < n0 ? 0 : it < n0 + n1 ? 1 : 2;
+    const uint32_t h = q.used[L][it - (L == 0 ? 0 : L == 1 ? n0 : n0 + n1)];
+    const ss_op_t R = g.ref[g.anchors[q.rep[L][h] - 1].ref_op];
+    // every occurrence in seq, in order: put(position, ordinal); returns how many there are.  A wavefront takes 256
+    // consecutive operators a pass, four loads in flight; one barrier a pass (the counts alternate between two sets).
+    auto each = [&](const ss_op_t *seq, uint32_t len, auto put) -> uint32_t {
+      uint32_t seen = 0;
+      int set = 0;
+      for (uint32_t base = 0; base < len; base += 4096, set ^= 1) {
+        const uint32_t j0 = base + w * 256 + lane;
+        ss_op_t o[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+          o[u].op_token = 0;
+          if (j0 + 64 * u < len) o[u] = seq[j0 + 64 * u];
+        }
+        uint64_t hit[4];
+        uint32_t mine = 0;
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+          hit[u] = __ballot(same_at(o[u], R, L));
+          mine += __popcll(hit[u]);
+        }
+        if (lane == 0) wave_cnt[set][w] = mine;
+        __syncthreads();
+        uint32_t ord = seen, all = 0;
+        for (int v = 0; v < 16; ++v) {
+          const uint32_t x = wave_cnt[set][v];
+          if (v < w) ord += x;
+          all += x;
+        }
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+          if ((hit[u] >> lane) & 1ull) put(j0 + 64 * u, ord + (uint32_t)__popcll(hit[u] & below));
+          ord += __popcll(hit[u]);
+        }
+        seen += all;
+      }
+      __syncthreads();
+      return seen;
+    };
+    each(g.ref, g.n, [&](uint32_t j, uint32_t ord) { q.rank[L][j] = ord; });
+    const uint32_t cnt = each(g.cur, g.m, [](uint32_t, uint32_t) {});
+    if (threadIdx.x == 0) {
+      s_start = atomicAdd(q.n_used + 3 + L, cnt);            // the keys of a level share no place: m entries suffice
+      q.start[L][h] = s_start;
+      q.count[L][h] = cnt;
+    }
+    __syncthreads();
+    uint32_t *const out = q.place[L] + s_start;
+    each(g.cur, g.m, [&](uint32_t j, uint32_t ord) { out[ord] = j; });
+  }
+}
+
+// One wavefront per anchor: looks its ordinal up, or, with too many distinct keys, counts and searches by itself.
+__global__ __launch_bounds__(256) void ss_lookup_kernel(AnchorArgs g, KeyLists q) {
+  const int lane = threadIdx.x & 63;
+  const uint32_t a = (blockIdx.x * 256 + threadIdx.x) >> 6;
+  if (a >= g.k) return;                                      // uniform per wavefront
+  const uint32_t i = g.anchors[a].ref_op, slot = g.anchors[a].out_slot;
+  int32_t f[3] = {-1, -1, -1}, result = -1;
+  uint8_t level = 255;
+  if (i < g.n && g.ref[i].op_token != 0) {
+    const ss_op_t R = g.ref[i];
+    if (q.n_used[0] + q.n_used[1] + q.n_used[2] <= q.max_lists) {
+#pragma unroll
+      for (int L = 0; L < 3; ++L) {
+        const uint32_t h = q.key_of[L][a], ord = q.rank[L][i];
+        if (ord < q.count[L][h]) f[L] = (int32_t)q.place[L][q.start[L][h] + ord];
+      }
+    } else {
+      uint32_t r[3] = {0, 0, 0};
+      for (uint32_t j = lane; j < i; j += 64) {
+        bool e0, e1, e2;
+        same_key(g.ref[j], R, e0, e1, e2);
+        r[0] += e0; r[1] += e1; r[2] += e2;
+      }
+#pragma unroll
+      for (int L = 0; L < 3; ++L) r[L] = wave_sum_u32(r[L]);
+      for (uint32_t base = 0; base < g.m; base += 64) {
+        const uint32_t j = base + lane;
+        bool e[3] = {false, false, false};
+        if (j < g.m) same_key(g.cur[j], R, e[0], e[1], e[2]);
+#pragma unroll
+        for (int L = 0; L < 3; ++L) {
+          const uint64_t b = __ballot(e[L]);
+          if (f[L] >= 0) continue;
+          const uint32_t pc = __popcll(b);
+          if (r[L] < pc) f[L] = (int32_t)base + nth_set_bit(b, r[L], lane);
+          else r[L] -= pc;
+        }
+        if (f[0] >= 0 && f[1] >= 0 && f[2] >= 0) break;
+      }
+    }
+    result = choose_landing(g.cur, R, slot, f, level);
+  }
+  if (lane == 0) {
+    g.land[a] = result;
+    g.lvl[a] = level;
+    if (result >= 0) g.slot_of[a] = claim(g.table, result, slot, a);
+  }
+}
+
+__global__ __launch_bounds__(256) void ss_injective_kernel(AnchorArgs g, int32_t *new_idx, uint8_t *level,
+                                                           uint32_t *lost_of_wg) {
+  __shared__ uint32_t lost_of[4];
+  const uint32_t a = blockIdx.x * 256 + threadIdx.x;
   bool lost = false;
-  if (a < k) {
-    int32_t j = land[a];
-    uint8_t L = lvl[a];
-    if (j >= 0 && owner[slot_of[a]] != a) { j = -1; L = 255; }
+  if (a < g.k) {
+    int32_t j = g.land[a];
+    uint8_t L = g.lvl[a];
+    if (j >= 0 && g.table.owner[g.slot_of[a]] != a) { j = -1; L = 255; }
     new_idx[a] = j;
     level[a] = L;
     lost = j < 0;
   }
-  const uint64_t m = __ballot(lost);
-  if ((threadIdx.x & 63) == 0 && m) atomicAdd(n_unmatched, (uint32_t)__popcll(m));
+  const uint64_t b = __ballot(lost);
+  if ((threadIdx.x & 63) == 0) lost_of[threadIdx.x >> 6] = (uint32_t)__popcll(b);
+  __syncthreads();
+  if (threadIdx.x == 0) lost_of_wg[blockIdx.x] = lost_of[0] + lost_of[1] + lost_of[2] + lost_of[3];
 }
 
 }  // namespace
@@ -298,73 +547,136 @@ extern "C" int ss_match_sequence(ss_ctx *ctx, const ss_op_t *ref, uint32_t n, co
       finish(sm, unm);
       return SS_OK;
     }
-    size_t off = 0;
-    auto take = [&](size_t bytes) { size_t o = off; off += ss_align_up(bytes, 256); return o; };
-    const size_t o_ref = take((size_t)n * sizeof(ss_op_t)), o_cur = take((size_t)m * sizeof(ss_op_t));
-    const size_t o_anc = take((size_t)k * sizeof(ss_anchor_t));
-    const size_t o_land = take((size_t)k * 4), o_idx = take((size_t)k * 4);
-    const size_t o_lvl = take(k), o_level = take(k);
-    const size_t o_small = take(64);                       // 3 x u64 sums, flags, n_unmatched
-    const size_t o_hist = take(hist ? 2 * (size_t)kTokenLimit * 4 : 0);
-    // table of the injectivity pass: a power of two of at least 2k slots; keys, then owners, back to back
+    const bool search = k && !aligned;
+    const size_t op_bytes = sizeof(ss_op_t), in_bytes = ((size_t)n + m) * op_bytes + (size_t)k * sizeof(ss_anchor_t);
+    // Inputs up to this size go through pinned memory that the first kernel reads (and copies on the way) and the last
+    // one writes: a copy call for each array costs more than the kernels.  Beyond it the copy engine is as fast and
+    // nothing that large is kept pinned.
+    const bool mapped = in_bytes <= (4u << 20);
+    const uint64_t pairs = (uint64_t)k * ((uint64_t)n + m);
+    const bool listed = search && pairs > (1ull << 24);        // 12 us of comparing; the lists take 25 us
+    const uint32_t len = n > m ? n : m, wgs = std::min(256u, std::max(1u, (len + 255) / 256));
+    const uint32_t out_wgs = (k + 255) / 256;
+    // table of the injectivity pass: a power of two of at least 2k slots
     uint32_t bits = 6;
     while ((1ull << bits) < 2ull * k) ++bits;
     const size_t slots = (size_t)1 << bits;
-    const size_t o_keys = take(k ? slots * 8 : 0), o_owner = take(k ? slots * 4 : 0), o_slot = take((size_t)k * 4);
-    int rc = ss_scratch_reserve(ctx, off, 512);
+    size_t off = 0, hoff = 0;
+    auto take = [&](size_t bytes) { size_t o = off; off += ss_align_up(bytes, 256); return o; };
+    auto htake = [&](size_t bytes) { size_t o = hoff; hoff += ss_align_up(bytes, 256); return o; };
+    const size_t o_ref = take((size_t)n * op_bytes), o_cur = take((size_t)m * op_bytes), o_anc = take((size_t)k * sizeof(ss_anchor_t));
+    const size_t o_land = take((size_t)k * 4), o_lvl = take(k), o_slot = take((size_t)k * 4);
+    const size_t o_idx = take(mapped ? 0 : (size_t)k * 4), o_level = take(mapped ? 0 : k);
+    const size_t o_ones = take(search ? slots * 8 : 0), o_owner = take(search ? slots * 4 : 0), ones_end = off;
+    const size_t o_hist = take(hist ? 2 * (size_t)kTokenLimit * 4 + 256 : 0);
+    size_t o_rep[3];
+    for (size_t &o : o_rep) o = take(listed ? slots * 4 : 0);
+    const size_t o_n_used = take(listed ? 6 * 4 : 0), zeros_end = off;
+    size_t o_used[3], o_start[3], o_count[3], o_key[3], o_rank[3], o_place[3];
+    for (int L = 0; L < 3; ++L) {
+      o_used[L] = take(listed ? (size_t)k * 4 : 0);
+      o_start[L] = take(listed ? slots * 4 : 0);
+      o_count[L] = take(listed ? slots * 4 : 0);
+      o_key[L] = take(listed ? (size_t)k * 4 : 0);
+      o_rank[L] = take(listed ? (size_t)n * 4 : 0);
+      o_place[L] = take(listed ? (size_t)m * 4 : 0);
+    }
+    const size_t ho_ref = htake(mapped ? (size_t)n * op_bytes : 0), ho_cur = htake(mapped ? (size_t)m * op_bytes : 0);
+    const size_t ho_anc = htake(mapped ? (size_t)k * sizeof(ss_anchor_t) : 0);
+    const size_t ho_idx = htake(mapped ? (size_t)k * 4 : 0), ho_level = htake(mapped ? k : 0);
+    const size_t ho_part = htake(kMaxParts * sizeof(CosinePart)), ho_lost = htake((size_t)out_wgs * 4);
+    int rc = ss_scratch_reserve(ctx, off, hoff);
     if (rc != SS_OK) return rc;
-    uint8_t *d = (uint8_t *)ctx->d_scratch;
+    uint8_t *d = (uint8_t *)ctx->d_scratch, *h = (uint8_t *)ctx->h_scratch, *hd = nullptr;
+    SS_HIP(hipHostGetDevicePointer((void **)&hd, h, 0));
     hipStream_t s = ctx->s_aux;
-    if (n) SS_HIP(hipMemcpyAsync(d + o_ref, ref, (size_t)n * sizeof(ss_op_t), hipMemcpyHostToDevice, s));
-    if (m) SS_HIP(hipMemcpyAsync(d + o_cur, cur, (size_t)m * sizeof(ss_op_t), hipMemcpyHostToDevice, s));
-    if (k) SS_HIP(hipMemcpyAsync(d + o_anc, anchors, (size_t)k * sizeof(ss_anchor_t), hipMemcpyHostToDevice, s));
-    // zero the small counters (and histograms) with a fill kernel: safe under graph capture too
-    ss_launch_fill(s, d + o_small, 64, 0);
-    if (hist) ss_launch_fill(s, d + o_hist, 2 * (size_t)kTokenLimit * 4, 0);
-    SS_HIP(hipGetLastError());
-    unsigned long long *sums = (unsigned long long *)(d + o_small);
-    uint32_t *dflags = (uint32_t *)(d + o_small + 32), *d_unm = (uint32_t *)(d + o_small + 40);
+    CosinePart *dpart = (CosinePart *)(hd + ho_part);
+    PrepArgs p = {};
+    p.n = n; p.m = m; p.k = search ? k : 0;
+    p.cosine = !hist;
+    p.ones = (uint4 *)(d + o_ones);
+    p.n_ones = (uint32_t)((ones_end - o_ones) / 16);
+    p.zeros = (uint4 *)(d + o_hist);
+    p.n_zeros = (uint32_t)((zeros_end - o_hist) / 16);
+    p.part = dpart;
+    if (mapped) {
+      if (n) std::memcpy(h + ho_ref, ref, (size_t)n * op_bytes);
+      if (m) std::memcpy(h + ho_cur, cur, (size_t)m * op_bytes);
+      if (k) std::memcpy(h + ho_anc, anchors, (size_t)k * sizeof(ss_anchor_t));
+      p.ref = (const ss_op_t *)(hd + ho_ref); p.dref = (ss_op_t *)(d + o_ref);
+      p.cur = (const ss_op_t *)(hd + ho_cur); p.dcur = (ss_op_t *)(d + o_cur);
+      p.anchors = (const ss_anchor_t *)(hd + ho_anc);
+      if (search) p.danc = (ss_anchor_t *)(d + o_anc);
+    } else {
+      if (n) SS_HIP(hipMemcpyAsync(d + o_ref, ref, (size_t)n * op_bytes, hipMemcpyHostToDevice, s));
+      if (m) SS_HIP(hipMemcpyAsync(d + o_cur, cur, (size_t)m * op_bytes, hipMemcpyHostToDevice, s));
+      if (k) SS_HIP(hipMemcpyAsync(d + o_anc, anchors, (size_t)k * sizeof(ss_anchor_t), hipMemcpyHostToDevice, s));
+      p.ref = (const ss_op_t *)(d + o_ref);
+      p.cur = (const ss_op_t *)(d + o_cur);
+    }
+    const uint32_t clears = std::max(p.n_ones, p.n_zeros);
+    const uint32_t prep_wgs = std::max(wgs, std::min(kMaxParts, clears / 2048));
+    hipLaunchKernelGGL(ss_prep_kernel, dim3(prep_wgs), dim3(256), 0, s, p);
+    const uint32_t parts = hist ? 256 : prep_wgs;
     const ss_op_t *dref = (const ss_op_t *)(d + o_ref), *dcur = (const ss_op_t *)(d + o_cur);
-    const uint32_t len = n > m ? n : m;
-    if (len) {
-      uint32_t grid = (len + 255) / 256;
-      if (grid > 256) grid = 256;
-      if (!hist) {
-        hipLaunchKernelGGL(ss_cosine_kernel, dim3(grid), dim3(256), 0, s, dref, n, dcur, m, sums, dflags);
+    if (hist) {
+      uint32_t *h_ref = (uint32_t *)(d + o_hist), *h_cur = h_ref + kTokenLimit, *bad = h_cur + kTokenLimit;
+      hipLaunchKernelGGL(ss_histogram_kernel, dim3(wgs), dim3(256), 0, s, dref, n, dcur, m, h_ref, h_cur, bad);
+      hipLaunchKernelGGL(ss_histdot_kernel, dim3(256), dim3(256), 0, s, h_ref, h_cur, kTokenLimit, bad, dpart);
+    }
+    SS_HIP(hipGetLastError());
+    if (search) {
+      AnchorArgs g = {dref, dcur, (const ss_anchor_t *)(d + o_anc), n, m, k, (int32_t *)(d + o_land), d + o_lvl,
+                      (uint32_t *)(d + o_slot),
+                      {(unsigned long long *)(d + o_ones), (uint32_t *)(d + o_owner), (uint32_t)(slots - 1), 64u - bits}};
+      if (listed) {
+        KeyLists q = {};
+        for (int L = 0; L < 3; ++L) {
+          q.rep[L] = (uint32_t *)(d + o_rep[L]);
+          q.used[L] = (uint32_t *)(d + o_used[L]);
+          q.start[L] = (uint32_t *)(d + o_start[L]);
+          q.count[L] = (uint32_t *)(d + o_count[L]);
+          q.key_of[L] = (uint32_t *)(d + o_key[L]);
+          q.rank[L] = (uint32_t *)(d + o_rank[L]);
+          q.place[L] = (uint32_t *)(d + o_place[L]);
+        }
+        q.n_used = (uint32_t *)(d + o_n_used);
+        q.mask = (uint32_t)(slots - 1);
+        q.shift = 64u - bits;
+        q.max_lists = std::min(kMaxLists, k / 2);
+        hipLaunchKernelGGL(ss_keys_kernel, dim3((k + 255) / 256, 3), dim3(256), 0, s, g, q);
+        hipLaunchKernelGGL(ss_lists_kernel, dim3(512), dim3(1024), 0, s, g, q);
+        hipLaunchKernelGGL(ss_lookup_kernel, dim3((k + 3) / 4), dim3(256), 0, s, g, q);
       } else {
-        uint32_t *h_ref = (uint32_t *)(d + o_hist), *h_cur = h_ref + kTokenLimit;
-        hipLaunchKernelGGL(ss_histogram_kernel, dim3(grid), dim3(256), 0, s, dref, n, dcur, m, h_ref, h_cur, dflags);
-        hipLaunchKernelGGL(ss_histdot_kernel, dim3(256), dim3(256), 0, s, h_ref, h_cur, kTokenLimit, sums);
+        hipLaunchKernelGGL(ss_anchor_kernel, dim3(k), dim3(256), 0, s, g);
       }
+      hipLaunchKernelGGL(ss_injective_kernel, dim3(out_wgs), dim3(256), 0, s, g,
+                         (int32_t *)(mapped ? hd + ho_idx : d + o_idx), mapped ? hd + ho_level : d + o_level,
+                         (uint32_t *)(hd + ho_lost));
       SS_HIP(hipGetLastError());
-    }
-    if (k && !aligned) {
-      const uint32_t grid = (k + 3) / 4;                    // 4 wavefronts (anchors) per workgroup
-      hipLaunchKernelGGL(ss_anchor_kernel, dim3(grid), dim3(256), 0, s, dref, n, dcur, m,
-                         (const ss_anchor_t *)(d + o_anc), k, (int32_t *)(d + o_land), d + o_lvl);
-      ss_launch_fill(s, d + o_keys, slots * 12, 0xFF);      // every key empty, every owner "nobody" (slots * 8 is a multiple of 256)
-      hipLaunchKernelGGL(ss_claim_kernel, dim3((k + 255) / 256), dim3(256), 0, s, (const ss_anchor_t *)(d + o_anc), k,
-                         (const int32_t *)(d + o_land), (unsigned long long *)(d + o_keys), (uint32_t *)(d + o_owner),
-                         (uint32_t *)(d + o_slot), (uint32_t)(slots - 1), 64u - bits);
-      hipLaunchKernelGGL(ss_injective_kernel, dim3((k + 255) / 256), dim3(256), 0, s, k, (const int32_t *)(d + o_land),
-                         d + o_lvl, (const uint32_t *)(d + o_slot), (const uint32_t *)(d + o_owner),
-                         (int32_t *)(d + o_idx), d + o_level, d_unm);
-      SS_HIP(hipGetLastError());
-    }
-    uint8_t *h = (uint8_t *)ctx->h_scratch;
-    SS_HIP(hipMemcpyAsync(h, d + o_small, 64, hipMemcpyDeviceToHost, s));
-    if (k && !aligned) {
-      SS_HIP(hipMemcpyAsync(new_idx, d + o_idx, (size_t)k * 4, hipMemcpyDeviceToHost, s));
-      SS_HIP(hipMemcpyAsync(level, d + o_level, k, hipMemcpyDeviceToHost, s));
+      if (!mapped) {
+        SS_HIP(hipMemcpyAsync(new_idx, d + o_idx, (size_t)k * 4, hipMemcpyDeviceToHost, s));
+        SS_HIP(hipMemcpyAsync(level, d + o_level, k, hipMemcpyDeviceToHost, s));
+      }
     }
     SS_HIP(hipStreamSynchronize(s));
-    uint64_t sm[3];
-    uint32_t fl, unm;
-    std::memcpy(sm, h, 24);
-    std::memcpy(&fl, h + 32, 4);
-    std::memcpy(&unm, h + 40, 4);
-    if (fl & 1u) return SS_E_INVAL;                          // a token beyond 2^18
-    uint32_t n_unm = (k && !aligned) ? unm : 0;
+    uint64_t sm[3] = {0, 0, 0}, too_large = 0;
+    const CosinePart *part = (const CosinePart *)(h + ho_part);
+    for (uint32_t w = 0; w < parts; ++w) {
+      sm[0] += part[w].dot;
+      sm[1] += part[w].na;
+      sm[2] += part[w].nb;
+      too_large |= part[w].bad;
+    }
+    if (too_large) return SS_E_INVAL;                        // a token beyond 2^18
+    uint32_t n_unm = 0;
+    if (search) {
+      if (mapped) {
+        std::memcpy(new_idx, h + ho_idx, (size_t)k * 4);
+        std::memcpy(level, h + ho_level, k);
+      }
+      for (uint32_t w = 0; w < out_wgs; ++w) n_unm += ((const uint32_t *)(h + ho_lost))[w];
+    }
     if (k && aligned) {                                      // the scratch is free again: the stream is idle
       std::vector<int32_t> ref_to_cur(n);
       uint32_t lcs = 0;
