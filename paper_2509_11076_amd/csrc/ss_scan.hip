@@ -49,6 +49,9 @@ struct ScanArgs {
   uint32_t *ctl;      // [0] operator blocks done, [1] flags
   uint64_t tile;      // events per tile
   uint32_t tiles0, tiles1;
+  // the tile sums read the events from here, if given, and copy them to ev / pev (without the tensor ids, which no
+  // kernel looks at)
+  const ss_event_t *src_ev, *src_pev;
   // outputs
   int64_t *per_op, *mre, *timeline;
   ss_scan_result_t *res;    // the flags go to res->reserved (bit 0: an event names an operator >= n_ops, nothing
@@ -484,7 +487,7 @@ constexpr uint64_t kMaxTiles = 1024;                  // per list: every workgro
 // the tile of a workgroup: first the tiles of ev, then those of pev (at least one each)
 struct Tile {
   bool policy;
-  const ss_event_t *L;
+  const ss_event_t *L, *src;
   uint64_t cnt, lo, hi, out0;        // events of its list; its events [lo, hi) there; where its list starts in sumx
   uint32_t first, index;             // its list's first tile; its own
   __device__ explicit Tile(const ScanArgs &a) {
@@ -492,6 +495,7 @@ struct Tile {
     policy = index >= a.tiles0;
     first = policy ? a.tiles0 : 0;
     L = policy ? a.pev : a.ev;
+    src = policy ? a.src_pev : a.src_ev;
     cnt = policy ? a.n_pe : a.n_ev;
     out0 = policy ? a.n_ev : 0;
     lo = (uint64_t)(index - first) * a.tile;
@@ -510,9 +514,11 @@ __global__ __launch_bounds__(kTileThreads) void ss_scan_tiles_kernel(ScanArgs a)
   uint32_t cp = 0, flags = 0;
   for (uint64_t lo = tl.lo; lo < tl.hi; lo += kTileEvents) {
     Elem x[kTileK];
-    flags |= load_events<kTileThreads, kTileK>(tl.L, tl.cnt, nullptr, 0, lo, tl.hi, a.n_ops, x);
+    flags |= load_events<kTileThreads, kTileK>(tl.src ? tl.src : tl.L, tl.cnt, nullptr, 0, lo, tl.hi, a.n_ops, x);
 #pragma unroll
     for (int k = 0; k < kTileK; ++k) {
+      if (tl.src && x[k].live)
+        const_cast<ss_event_t *>(tl.L)[lo + (uint64_t)k * kTileThreads + threadIdx.x] = ss_event_t{x[k].op, 0, x[k].delta};
       sp += x[k].pos ? x[k].delta : 0;
       sn += x[k].pos ? 0 : x[k].delta;
       cp += x[k].pos;
@@ -646,6 +652,11 @@ uint64_t tile_events(uint64_t n_ev, uint64_t n_pe) {
 
 bool is_short(uint64_t n_ev, uint64_t n_pe, uint32_t n_ops) { return n_ev + n_pe <= kSmallEvents && n_ops <= kLdsOps; }
 
+// Host calls: up to this much goes through the context's pinned scratch (which starts at 1 MiB), read and written by the
+// kernels themselves; a copy call for pageable memory costs 19 to 33 us at 16 to 64 KiB and a copy from pinned memory a
+// launch, the link's time is the same.  Beyond it the copy engine keeps up with the link and the call's cost is small.
+constexpr size_t kMappedBytes = 768 * 1024;
+
 // Scratch of a long trace from `d` on; returns its size (nothing is assigned where `a` is null).
 size_t scan_scratch(ScanArgs *a, uint8_t *d, uint64_t n_ev, uint64_t n_pe, uint64_t n_ops, bool timeline) {
   size_t off = 0;
@@ -770,25 +781,35 @@ extern "C" int ss_timeline_scan_batch(ss_ctx *ctx, const ss_event_t *ev, uint64_
     if (pe_start[0] != 0 || (n_pe && !pev) || n_ev + n_pe >= (1ull << 31)) return SS_E_INVAL;
     const uint64_t n = n_ops;
     const bool lds = n_ops <= kLdsOps;                 // the OpAt tables fit LDS
-    size_t off = 0;
-    auto take = [&](size_t bytes) { size_t o = off; off += ss_align_up(bytes, 256); return o; };
-    const size_t o_ev = take(n_ev * sizeof(ss_event_t)), o_pev = take(n_pe * sizeof(ss_event_t));
-    const size_t per_scan = lds ? 0 : ss_align_up(2 * (n + 1) * sizeof(OpAt), 256) + 2 * ss_align_up(n * 8, 256);
-    const size_t o_work = take((size_t)k * per_scan), o_per_op = take(per_op ? (size_t)k * n * 8 : 0);
+    const size_t ev_bytes = n_ev * sizeof(ss_event_t), pe_bytes = n_pe * sizeof(ss_event_t);
+    // every scan reads the trace once: over the link while that takes no longer than the two copies' calls (about 40 us)
+    const bool mapped = ev_bytes + pe_bytes <= kMappedBytes / 2 && k * (uint64_t)ev_bytes <= (1u << 20);
+    size_t off = 0, hoff = 0;
+    auto take = [](size_t &o, size_t bytes) { size_t at = o; o += ss_align_up(bytes, 256); return at; };
     const size_t args_bytes = ss_align_up((size_t)k * sizeof(ScanArgs), 256);
-    int rc = ss_scratch_reserve(ctx, off, args_bytes + (size_t)k * sizeof(ss_scan_result_t));
+    take(hoff, args_bytes + (size_t)k * sizeof(ss_scan_result_t));
+    const size_t o_ev = take(mapped ? hoff : off, ev_bytes), o_pev = take(mapped ? hoff : off, pe_bytes);
+    const size_t per_scan = lds ? 0 : ss_align_up(2 * (n + 1) * sizeof(OpAt), 256) + 2 * ss_align_up(n * 8, 256);
+    const size_t o_work = take(off, (size_t)k * per_scan), o_per_op = take(off, per_op ? (size_t)k * n * 8 : 0);
+    int rc = ss_scratch_reserve(ctx, off, hoff);
     if (rc != SS_OK) return rc;
     uint8_t *d = (uint8_t *)ctx->d_scratch, *h = (uint8_t *)ctx->h_scratch, *hd = nullptr;
     SS_HIP(hipHostGetDevicePointer((void **)&hd, h, 0));
     hipStream_t s = ctx->s_aux;
-    if (n_ev) SS_HIP(hipMemcpyAsync(d + o_ev, ev, n_ev * sizeof(ss_event_t), hipMemcpyHostToDevice, s));
-    if (n_pe) SS_HIP(hipMemcpyAsync(d + o_pev, pev, n_pe * sizeof(ss_event_t), hipMemcpyHostToDevice, s));
+    if (mapped) {
+      if (n_ev) std::memcpy(h + o_ev, ev, ev_bytes);
+      if (n_pe) std::memcpy(h + o_pev, pev, pe_bytes);
+    } else {
+      if (n_ev) SS_HIP(hipMemcpyAsync(d + o_ev, ev, ev_bytes, hipMemcpyHostToDevice, s));
+      if (n_pe) SS_HIP(hipMemcpyAsync(d + o_pev, pev, pe_bytes, hipMemcpyHostToDevice, s));
+    }
+    const uint8_t *const in = mapped ? hd : d;
     ScanArgs *ha = (ScanArgs *)h;                       // pinned, read and written by the kernel: arguments, results
     for (uint32_t c = 0; c < k; ++c) {
       uint8_t *w = d + o_work + (size_t)c * per_scan;
       ScanArgs a = {};
-      a.ev = (const ss_event_t *)(d + o_ev); a.n_ev = n_ev;
-      a.pev = (const ss_event_t *)(d + o_pev) + pe_start[c]; a.n_pe = pe_start[c + 1] - pe_start[c];
+      a.ev = (const ss_event_t *)(in + o_ev); a.n_ev = n_ev;
+      a.pev = (const ss_event_t *)(in + o_pev) + pe_start[c]; a.n_pe = pe_start[c + 1] - pe_start[c];
       a.n_ops = n_ops;
       a.base = base; a.budget = budget;
       if (!lds) {
@@ -832,34 +853,43 @@ extern "C" int ss_timeline_scan(ss_ctx *ctx, const ss_event_t *ev, uint64_t n_ev
     a.n_ev = n_ev; a.n_pe = n_pe;
     a.n_ops = n_ops; a.want_timeline = timeline != nullptr;
     a.base = base; a.budget = budget;
-    // A short trace: the kernel reads the events out of pinned host memory and writes every result there (they are
-    // touched once, and a copy each way would cost a launch more than the kernel); else the events go by copy.
-    const bool mapped = is_short(n_ev, n_pe, n_ops);
+    const size_t ev_bytes = n_ev * sizeof(ss_event_t), pe_bytes = n_pe * sizeof(ss_event_t);
+    const size_t out_bytes = (per_op ? n * 8 : 0) + (mre ? n * 8 : 0) + (timeline ? E * 8 : 0);
+    // Short traces: the one kernel reads the events out of pinned memory.  Longer ones: the first kernel does, and copies
+    // them on the way for the other two.  Results are written to pinned memory in both cases.
+    const bool is_small = is_short(n_ev, n_pe, n_ops);
+    const bool in_mapped = is_small || ev_bytes + pe_bytes <= kMappedBytes;
+    const bool out_mapped = is_small || (in_mapped ? ev_bytes + pe_bytes : 0) + out_bytes <= kMappedBytes;
     size_t off = 0, hoff = 0;
     auto take = [](size_t &o, size_t bytes) { size_t at = o; o += ss_align_up(bytes, 256); return at; };
-    size_t &io = mapped ? hoff : off;
-    const size_t o_ev = take(io, n_ev * sizeof(ss_event_t)), o_pev = take(io, n_pe * sizeof(ss_event_t));
-    const size_t o_perop = take(io, per_op ? n * 8 : 0), o_mre = take(io, mre ? n * 8 : 0);
-    const size_t o_tl = take(io, timeline ? E * 8 : 0), o_res = take(hoff, sizeof(ss_scan_result_t));
-    const size_t o_scratch = take(off, mapped ? 0 : scan_scratch(nullptr, nullptr, n_ev, n_pe, n, timeline != nullptr));
+    const size_t ho_ev = take(hoff, in_mapped ? ev_bytes : 0), ho_pev = take(hoff, in_mapped ? pe_bytes : 0);
+    const size_t o_ev = take(off, is_small ? 0 : ev_bytes), o_pev = take(off, is_small ? 0 : pe_bytes);
+    size_t &oo = out_mapped ? hoff : off;
+    const size_t o_perop = take(oo, per_op ? n * 8 : 0), o_mre = take(oo, mre ? n * 8 : 0);
+    const size_t o_tl = take(oo, timeline ? E * 8 : 0), o_res = take(hoff, sizeof(ss_scan_result_t));
+    const size_t o_scratch = take(off, is_small ? 0 : scan_scratch(nullptr, nullptr, n_ev, n_pe, n, timeline != nullptr));
     int rc = ss_scratch_reserve(ctx, off, hoff);
     if (rc != SS_OK) return rc;
     uint8_t *d = (uint8_t *)ctx->d_scratch, *h = (uint8_t *)ctx->h_scratch, *hd = nullptr;
     SS_HIP(hipHostGetDevicePointer((void **)&hd, h, 0));
-    uint8_t *const at = mapped ? hd : d;
-    if (mapped) {
-      if (n_ev) std::memcpy(h + o_ev, ev, n_ev * sizeof(ss_event_t));
-      if (n_pe) std::memcpy(h + o_pev, pev, n_pe * sizeof(ss_event_t));
+    uint8_t *const out = out_mapped ? hd : d;
+    a.ev = (const ss_event_t *)(is_small ? hd + ho_ev : d + o_ev);
+    a.pev = (const ss_event_t *)(is_small ? hd + ho_pev : d + o_pev);
+    if (in_mapped) {
+      if (n_ev) std::memcpy(h + ho_ev, ev, ev_bytes);
+      if (n_pe) std::memcpy(h + ho_pev, pev, pe_bytes);
+      if (!is_small) {
+        a.src_ev = (const ss_event_t *)(hd + ho_ev);
+        a.src_pev = (const ss_event_t *)(hd + ho_pev);
+      }
     } else {
-      if (n_ev) SS_HIP(hipMemcpyAsync(d + o_ev, ev, n_ev * sizeof(ss_event_t), hipMemcpyHostToDevice, s));
-      if (n_pe) SS_HIP(hipMemcpyAsync(d + o_pev, pev, n_pe * sizeof(ss_event_t), hipMemcpyHostToDevice, s));
-      scan_scratch(&a, d + o_scratch, n_ev, n_pe, n, timeline != nullptr);
+      if (n_ev) SS_HIP(hipMemcpyAsync(d + o_ev, ev, ev_bytes, hipMemcpyHostToDevice, s));
+      if (n_pe) SS_HIP(hipMemcpyAsync(d + o_pev, pev, pe_bytes, hipMemcpyHostToDevice, s));
     }
-    a.ev = (const ss_event_t *)(at + o_ev);
-    a.pev = (const ss_event_t *)(at + o_pev);
-    a.per_op = per_op ? (int64_t *)(at + o_perop) : nullptr;
-    a.mre = mre ? (int64_t *)(at + o_mre) : nullptr;
-    a.timeline = timeline ? (int64_t *)(at + o_tl) : nullptr;
+    if (!is_small) scan_scratch(&a, d + o_scratch, n_ev, n_pe, n, timeline != nullptr);
+    a.per_op = per_op ? (int64_t *)(out + o_perop) : nullptr;
+    a.mre = mre ? (int64_t *)(out + o_mre) : nullptr;
+    a.timeline = timeline ? (int64_t *)(out + o_tl) : nullptr;
     a.res = (ss_scan_result_t *)(hd + o_res);
     launch_scan(s, a);
     SS_HIP(hipGetLastError());
@@ -871,7 +901,7 @@ extern "C" int ss_timeline_scan(ss_ctx *ctx, const ss_event_t *ev, uint64_t n_ev
     r.reserved = 0;
     *res = r;
     const bool tl_ok = timeline && !(flags & 2u);
-    if (mapped) {
+    if (out_mapped) {
       if (per_op && n) std::memcpy(per_op, h + o_perop, n * 8);
       if (mre && n) std::memcpy(mre, h + o_mre, n * 8);
       if (tl_ok && E) std::memcpy(timeline, h + o_tl, E * 8);
