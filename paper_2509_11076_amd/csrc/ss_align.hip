@@ -14,7 +14,6 @@
 // V_i is set (L[i][j-1] = L[i][j]), else up; on the host for short sequences, on the GPU for long ones.
 #include <algorithm>
 #include <cstring>
-#include <unordered_map>
 
 #include "ss_internal.h"
 
@@ -50,10 +49,185 @@ static inline __host__ __device__ size_t row_word(uint32_t r, uint32_t w, uint32
 
 // A key id as it is stored: 16 bits, already multiplied by the 256 bytes of an LDS mask row, where the mask rows fit
 // LDS; else 32 bits as it is.
-static inline __host__ __device__ uint32_t key_of(uint16_t id) { return id >> 8; }
-static inline __host__ __device__ uint32_t key_of(uint32_t id) { return id; }
-static inline void set_key(uint16_t *id, uint32_t key) { *id = (uint16_t)(key << 8); }
-static inline void set_key(uint32_t *id, uint32_t key) { *id = key; }
+static __device__ __forceinline__ uint32_t key_of(uint16_t id) { return id >> 8; }
+static __device__ __forceinline__ uint32_t key_of(uint32_t id) { return id; }
+
+// ---- key ids ---------------------------------------------------------------------------------------------------
+//
+// The distinct (op_token, stack_hash, sig) of cur get dense ids through an open-addressing table whose slots hold
+// 1 + the operator that stands for a key; which key gets which id does not matter.  Operators of ref whose key cur does
+// not hold share the id n_keys, whose mask row is empty.  Ids are written in the form the rows kernel reads (key_of):
+// 16 bits if there are few enough keys, 32 bits otherwise.  2,310 operators: one workgroup, 6.4 us; 64,609: three
+// launches, 33 us, of which 23 bring the operators over the link.  An unordered map on the host took about 23 and 260 us.
+
+struct KeyArgs {
+  const ss_op_t *ref, *cur;
+  uint32_t n, m, n_steps;
+  uint32_t few;                // up to this many keys the ids take 16 bits
+  void *ref_id, *cur_id;       // id_length(n_steps) entries, padded; m entries
+  uint32_t *n_keys;            // device: distinct keys so far
+  uint32_t *n_keys_out;        // pinned: how many there are
+  // long sequences
+  uint32_t *rep, *id;          // per slot
+  uint32_t *slot;              // per operator of cur
+  uint32_t mask, shift;
+};
+
+__device__ __forceinline__ uint32_t key_hash(uint32_t token, uint32_t stack, uint32_t sig, uint32_t shift) {
+  const u64 x = (((u64)token << 32) | stack) * 0x9E3779B97F4A7C15ull ^ (u64)sig * 0xC2B2AE3D27D4EB4Full;
+  return (uint32_t)((x ^ (x >> 29)) * 0x9E3779B97F4A7C15ull >> shift);
+}
+
+__device__ __forceinline__ void put_id(void *ids, size_t at, uint32_t key, bool few) {
+  if (few) static_cast<uint16_t *>(ids)[at] = (uint16_t)(key << 8);
+  else static_cast<uint32_t *>(ids)[at] = key;
+}
+
+// Both sequences in one workgroup, keys and table in LDS, ops read from pinned host memory.
+constexpr uint32_t kWgOps = 4096, kWgSlots = 8192, kWgThreads = 1024, kWgPer = kWgOps / kWgThreads;
+
+__global__ __launch_bounds__(kWgThreads) void ss_align_keys_kernel(KeyArgs a) {
+  extern __shared__ uint32_t lds[];
+  uint32_t *const rep = lds, *const id = rep + kWgSlots, *const tok = id + kWgSlots, *const stk = tok + kWgOps, *const sig = stk + kWgOps;
+  __shared__ uint32_t n_keys;
+  constexpr uint32_t kShift = 64 - 13;
+  static_assert(kWgSlots == 1u << 13, "hash bits");
+  const uint32_t tid = threadIdx.x, total = a.m + a.n;       // cur first
+  ss_op_t o[kWgPer];
+#pragma unroll
+  for (uint32_t u = 0; u < kWgPer; ++u) {
+    const uint32_t i = u * kWgThreads + tid;
+    if (i < total) o[u] = i < a.m ? a.cur[i] : a.ref[i - a.m];
+  }
+  for (uint32_t i = tid; i < kWgSlots; i += kWgThreads) rep[i] = 0;
+  if (tid == 0) n_keys = 0;
+  uint32_t slot[kWgPer];
+#pragma unroll
+  for (uint32_t u = 0; u < kWgPer; ++u) {
+    const uint32_t i = u * kWgThreads + tid;
+    if (i < total) { tok[i] = o[u].op_token; stk[i] = o[u].stack_hash; sig[i] = o[u].sig; }
+  }
+  __syncthreads();
+  // at most m <= kWgSlots / 2 keys: a free or matching slot is met
+  auto find = [&](uint32_t u, bool insert) -> uint32_t {
+    const uint32_t i = u * kWgThreads + tid;
+    uint32_t h = key_hash(o[u].op_token, o[u].stack_hash, o[u].sig, kShift);
+    for (uint32_t probe = 0; probe < kWgSlots; ++probe) {
+      uint32_t seen = *(volatile uint32_t *)(rep + h);
+      if (!seen) {
+        if (!insert) return kWgSlots;
+        seen = atomicCAS(rep + h, 0u, i + 1);
+        if (!seen) {
+          id[h] = atomicAdd(&n_keys, 1u);
+          return h;
+        }
+      }
+      const uint32_t r = seen - 1;
+      if (tok[r] == o[u].op_token && stk[r] == o[u].stack_hash && sig[r] == o[u].sig) return h;
+      h = (h + 1) % kWgSlots;
+    }
+    return kWgSlots;
+  };
+#pragma unroll
+  for (uint32_t u = 0; u < kWgPer; ++u)
+    if (u * kWgThreads + tid < a.m) slot[u] = find(u, true);
+  __syncthreads();
+  const uint32_t keys = n_keys;
+  const bool few = keys <= a.few;
+  if (tid == 0) { *a.n_keys = keys; *a.n_keys_out = keys; }
+#pragma unroll
+  for (uint32_t u = 0; u < kWgPer; ++u) {
+    const uint32_t i = u * kWgThreads + tid;
+    if (i < a.m) {
+      put_id(a.cur_id, i, id[slot[u]], few);
+    } else if (i < total) {
+      const uint32_t h = find(u, false);
+      put_id(a.ref_id, kIdPad + i - a.m, h < kWgSlots ? id[h] : keys, few);
+    }
+  }
+  for (uint32_t i = tid; i < id_length(a.n_steps); i += kWgThreads)
+    if (i < kIdPad || i >= kIdPad + a.n) put_id(a.ref_id, i, keys, few);
+}
+
+// Long sequences: ops copied from pinned host memory and the table cleared; keys of cur inserted; ids of both.
+__global__ __launch_bounds__(256) void ss_align_fetch_kernel(const ss_op_t *__restrict__ ref, ss_op_t *__restrict__ dref,
+                                                             uint32_t n, const ss_op_t *__restrict__ cur,
+                                                             ss_op_t *__restrict__ dcur, uint32_t m, uint32_t *rep,
+                                                             uint32_t slots, uint32_t *n_keys) {
+  const uint32_t first = blockIdx.x * 256 + threadIdx.x, stride = gridDim.x * 256;
+  for (uint32_t i = first; i < n; i += stride) dref[i] = ref[i];
+  for (uint32_t i = first; i < m; i += stride) dcur[i] = cur[i];
+  for (uint32_t i = first; i < slots; i += stride) rep[i] = 0;
+  if (first == 0) *n_keys = 0;
+}
+
+__device__ __forceinline__ bool same_key(const ss_op_t &x, const ss_op_t &y) {
+  return x.op_token == y.op_token && x.stack_hash == y.stack_hash && x.sig == y.sig;
+}
+
+// A workgroup's operators share few keys, and every one of them would go for the same few slots: the first of each key
+// within the workgroup (found through a table in LDS) goes, the others take over its slot.
+__global__ __launch_bounds__(256) void ss_align_insert_kernel(KeyArgs a) {
+  constexpr uint32_t kSlots = 512, kShift = 64 - 9;
+  __shared__ uint32_t first[kSlots], slot_of[kSlots];
+  __shared__ ss_op_t ops[256];
+  const uint32_t j = blockIdx.x * 256 + threadIdx.x;
+  const bool live = j < a.m;
+  ss_op_t o = {0, 0, 0, 0};
+  if (live) o = a.cur[j];
+  ops[threadIdx.x] = o;
+  for (uint32_t i = threadIdx.x; i < kSlots; i += 256) first[i] = 0;
+  __syncthreads();
+  uint32_t l = key_hash(o.op_token, o.stack_hash, o.sig, kShift);
+  bool goes = false;
+  for (uint32_t probe = 0; live && probe < kSlots; ++probe) {  // at most 256 keys in 512 slots
+    uint32_t seen = *(volatile uint32_t *)(first + l);
+    if (!seen) {
+      seen = atomicCAS(first + l, 0u, threadIdx.x + 1);
+      if (!seen) { goes = true; break; }
+    }
+    if (same_key(ops[seen - 1], o)) break;
+    l = (l + 1) % kSlots;
+  }
+  if (goes) {
+    uint32_t h = key_hash(o.op_token, o.stack_hash, o.sig, a.shift);
+    for (uint32_t probe = 0; probe <= a.mask; ++probe) {       // at most m keys in at least 2m slots
+      uint32_t seen = __hip_atomic_load(a.rep + h, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      if (!seen) {
+        seen = atomicCAS(a.rep + h, 0u, j + 1);
+        if (!seen) {
+          a.id[h] = atomicAdd(a.n_keys, 1u);
+          break;
+        }
+      }
+      if (same_key(a.cur[seen - 1], o)) break;
+      h = (h + 1) & a.mask;
+    }
+    slot_of[l] = h;
+  }
+  __syncthreads();
+  if (live) a.slot[j] = slot_of[l];
+}
+
+__global__ __launch_bounds__(256) void ss_align_ids_kernel(KeyArgs a) {
+  const uint32_t i = blockIdx.x * 256 + threadIdx.x, keys = *a.n_keys;
+  const bool few = keys <= a.few;
+  if (i == 0) *a.n_keys_out = keys;
+  if (i < a.m) put_id(a.cur_id, i, a.id[a.slot[i]], few);
+  if (i >= id_length(a.n_steps)) return;
+  uint32_t key = keys;
+  if (i >= kIdPad && i < kIdPad + a.n) {
+    const ss_op_t o = a.ref[i - kIdPad];
+    uint32_t h = key_hash(o.op_token, o.stack_hash, o.sig, a.shift);
+    for (uint32_t probe = 0; probe <= a.mask; ++probe) {
+      const uint32_t seen = a.rep[h];
+      if (!seen) break;
+      if (same_key(a.cur[seen - 1], o)) { key = a.id[h]; break; }
+      h = (h + 1) & a.mask;
+    }
+  }
+  put_id(a.ref_id, i, key, few);
+}
 
 template <class Id>
 __global__ void ss_align_masks_kernel(const Id *__restrict__ cur_id, uint32_t m, uint32_t *__restrict__ masks,
@@ -212,19 +386,22 @@ __device__ __forceinline__ void strip_rows(const RowsArgs &a, const Id *my_ids, 
 // instruction; masks are looked up one block of steps ahead, a carry word one block before it is needed).  18.9 ns a
 // row for one strip, 30 ns for sixteen that hand carries on.  Updating a whole row at once in one wavefront, its
 // carries crossing lanes by two ballots and scalar arithmetic, took 128 ns a row at 1,156 columns and 755 ns at
-// 32,300: 1,154 x 1,156 operators 149 -> 35 us, 32,312 x 32,297 operators 24.5 -> 1.03 ms.
+// 32,300: 1,154 x 1,156 operators 149 -> 30 us, 32,312 x 32,297 operators 24.5 -> 1.0 ms.
 template <class Id>
 __global__ __launch_bounds__(64) void ss_align_rows_kernel(const Id *__restrict__ ref_id,
                                                            const Id *__restrict__ cur_id, uint32_t m, RowsArgs a,
-                                                           uint32_t n_mask_rows) {
+                                                           const uint32_t *__restrict__ n_keys) {
   constexpr bool kLds = sizeof(Id) == 2;
   extern __shared__ uint32_t lds[];
   const uint32_t lane = threadIdx.x, strip = blockIdx.x;
   const uint32_t w0 = strip * kStripWords;
   const uint32_t lanes = min(kStripWords, a.W - w0);
+  const uint32_t n_mask_rows = *n_keys + 1;
+  if (kLds && n_mask_rows > kLdsKeys) return;                // launched before the number was known, and the ids are wide
   Id *const lds_ids = reinterpret_cast<Id *>(lds + n_mask_rows * kStripWords);
   if constexpr (kLds) {
-    for (uint32_t i = lane; i < n_mask_rows * kStripWords; i += 64) lds[i] = ~0u;
+    uint4 *const table4 = reinterpret_cast<uint4 *>(lds);
+    for (uint32_t i = lane; i < n_mask_rows * (kStripWords / 4); i += 64) table4[i] = uint4{~0u, ~0u, ~0u, ~0u};
     const uint4 *src = reinterpret_cast<const uint4 *>(ref_id);
     uint4 *dst = reinterpret_cast<uint4 *>(lds_ids);
     const uint32_t n16 = id_length(a.n_steps) * sizeof(Id) / 16;
@@ -271,7 +448,8 @@ __global__ __launch_bounds__(64) void ss_align_rows_kernel(const Id *__restrict_
 // the end (ss_align_chain_kernel), and with every block's entry known the blocks are walked again side by side to
 // write the pairs (ss_align_pairs_kernel).  A block whose entry lies outside its window, or whose path leaves the tile
 // to the left, is walked in place by a wavefront of the chain.
-// 32,312 rows: 63 us for the tables, 145 us for the chain (two dependent LDS reads a block), 24 us for the pairs; single
+// 32,312 rows: 62 us for the tables, 90 us for the chain (an LDS read and its way through the scalar unit per block; with
+// the window's start read from LDS too 145), 24 us for the pairs; single
 // steps in one wavefront took 97 ns a row (3.1 ms), the rows over the host link (130 MB) 2.3 ms and a walk there.
 constexpr uint32_t kWalkRows = 64;
 constexpr uint32_t kWindow = 2048;                     // entry columns tabulated per block of rows
@@ -423,7 +601,6 @@ __global__ __launch_bounds__(kChainThreads) void ss_align_chain_kernel(const Id 
                                                                        int32_t *__restrict__ entry,
                                                                        int32_t *__restrict__ ref_to_cur) {
   __shared__ uint4 tabs[kChainBlocks * kWindow / 8];
-  __shared__ uint32_t start[kChainBlocks];
   constexpr uint32_t kPer = kChainBlocks * kWindow / 8 / kChainThreads;
   const uint32_t K = (n + kWalkRows - 1) / kWalkRows;
   const uint4 *src = reinterpret_cast<const uint4 *>(table);
@@ -441,25 +618,29 @@ __global__ __launch_bounds__(kChainThreads) void ss_align_chain_kernel(const Id 
   for (uint32_t k0 = 0; k0 < K; k0 += kChainBlocks) {
 #pragma unroll
     for (uint32_t i = 0; i < kPer; ++i) tabs[i * kChainThreads + threadIdx.x] = next[i];
-    if (threadIdx.x < kChainBlocks && k0 + threadIdx.x < K) start[threadIdx.x] = window_start(k0 + threadIdx.x, n, m);
     __syncthreads();
     fetch(k0 + kChainBlocks);
     if (threadIdx.x < 64) {
       const uint16_t *t = reinterpret_cast<const uint16_t *>(tabs);
-      const uint32_t k1 = min(K, k0 + kChainBlocks);
-      for (uint32_t k = k0; k < k1; ++k) {
-        const uint32_t at = j - start[k - k0];               // before the window: wraps to a large number
-        uint32_t d = at < kWindow ? t[(k - k0) * kWindow + at] : kNoEntry;
-        d = __builtin_amdgcn_readfirstlane(d);
-        if (d != kNoEntry) {
-          if (threadIdx.x == 0) entry[k] = (int32_t)j;
-          j -= d;
-        } else {
-          if (threadIdx.x == 0) entry[k] = -1;
-          j = __builtin_amdgcn_readfirstlane(
-              walk_in_place(ref_id, masks, rows, W, n_steps, RowBlock(k, n), j, ref_to_cur));
+      const uint32_t mine = min(k0 + (threadIdx.x & (kChainBlocks - 1)), K - 1);
+      const uint32_t starts = window_start(mine, n, m);      // lane u: block k0 + u's
+      int32_t entries = 0;                                   // likewise
+#pragma unroll
+      for (uint32_t u = 0; u < kChainBlocks; ++u) {
+        const uint32_t k = k0 + u;
+        if (k < K) {
+          const uint32_t at = j - (uint32_t)__builtin_amdgcn_readlane((int)starts, u);       // before the window: wraps to a large number
+          const uint32_t d = at < kWindow ? __builtin_amdgcn_readfirstlane((uint32_t)t[u * kWindow + at]) : kNoEntry;
+          if (threadIdx.x == u) entries = d != kNoEntry ? (int32_t)j : -1;
+          if (__builtin_expect(d != kNoEntry, 1)) {
+            j -= d;
+          } else {
+            j = __builtin_amdgcn_readfirstlane(
+                walk_in_place(ref_id, masks, rows, W, n_steps, RowBlock(k, n), j, ref_to_cur));
+          }
         }
       }
+      if (threadIdx.x < kChainBlocks && k0 + threadIdx.x < K) entry[k0 + threadIdx.x] = entries;
     }
     __syncthreads();
   }
@@ -486,110 +667,97 @@ __global__ __launch_bounds__(64) void ss_align_pairs_kernel(const Id *__restrict
   if (threadIdx.x < blk.hi - blk.lo) ref_to_cur[blk.hi - 1 - threadIdx.x] = paired[threadIdx.x];
 }
 
-struct KeyHash {
-  size_t operator()(const std::pair<uint64_t, uint32_t> &k) const {
-    uint64_t x = k.first * 0x9E3779B97F4A7C15ull ^ ((uint64_t)k.second * 0xC2B2AE3D27D4EB4Full);
-    x ^= x >> 29;
-    return (size_t)x;
-  }
-};
-
 // LDS of the rows kernel with 16-bit ids: mask rows and all ids of the reference
 size_t lds_need(uint32_t n_keys, uint32_t n) {
   return (size_t)(n_keys + 1) * kStripWords * 4 + (size_t)id_length(steps_of(n)) * 2;
 }
 
-// ref_to_cur (host, all -1 on entry) from the ids of both sequences
-template <class Id>
-int align_ids(ss_ctx *ctx, const std::vector<uint32_t> &ref_id, const std::vector<uint32_t> &cur_id, uint32_t n_keys,
-              int32_t *ref_to_cur, uint32_t *lcs) {
-  const uint32_t n = (uint32_t)ref_id.size(), m = (uint32_t)cur_id.size();
-  constexpr bool kLds = sizeof(Id) == 2;
-  const uint32_t W = (m + 31) / 32;                      // 32-bit words of a row
-  const uint32_t strips = (W + kStripWords - 1) / kStripWords;
-  const uint32_t n_steps = steps_of(n), n_blocks = n_steps / kBlock;
-  const size_t row_bytes = (size_t)strips * n_steps * kStripWords * 4;
-  const size_t id_len = id_length(n_steps);
-  // short: the kernel writes the rows to pinned host memory and the host walks them; else they stay in device memory
-  // and are walked there
-  const bool short_rows = row_bytes <= kHostRowBytes;
-  const bool ids_mapped = kLds && short_rows;            // each id is read once: straight from host memory
-  const bool masks_needed = !kLds || !short_rows;
-  size_t off = 0, hoff = 0;
-  auto take = [&](size_t bytes) { size_t o = off; off += ss_align_up(bytes, 256); return o; };
-  auto htake = [&](size_t bytes) { size_t o = hoff; hoff += ss_align_up(bytes, 256); return o; };
-  const size_t ho_ref = htake(id_len * sizeof(Id)), ho_cur = htake((size_t)m * sizeof(Id)), ids_end = hoff;
-  const size_t ho_flag = htake(4), ho_out = htake(short_rows ? row_bytes : (size_t)n * 4);
-  const size_t o_ids = take(ids_mapped ? 0 : ids_end);
-  const size_t o_mask = take(masks_needed ? (size_t)(n_keys + 1) * W * 4 : 0);   // mask table, then the carry words:
-  const size_t o_carry = take((size_t)(strips - 1) * (n_blocks + kCarryPad) * 8), o_end = off; // cleared in one go
-  const size_t o_rows = take(short_rows ? 0 : row_bytes), o_pair = take(short_rows ? 0 : (size_t)n * 4);
-  const uint32_t walk_blocks = (n + kWalkRows - 1) / kWalkRows;
-  const size_t o_table = take(short_rows ? 0 : (size_t)walk_blocks * kWindow * 2);
-  const size_t o_entry = take(short_rows ? 0 : (size_t)walk_blocks * 4);
-  const int rc = ss_scratch_reserve(ctx, off, hoff);
-  if (rc != SS_OK) return rc;
-  uint8_t *d = (uint8_t *)ctx->d_scratch, *h = (uint8_t *)ctx->h_scratch, *hd = nullptr;
-  SS_HIP(hipHostGetDevicePointer((void **)&hd, h, 0));
-  hipStream_t s = ctx->s_aux;
-  Id *h_ref = (Id *)(h + ho_ref), *h_cur = (Id *)(h + ho_cur);
-  for (uint32_t i = 0; i < kIdPad; ++i) set_key(h_ref + i, n_keys);
-  for (uint32_t i = 0; i < n; ++i) set_key(h_ref + kIdPad + i, ref_id[i]);
-  for (size_t i = kIdPad + n; i < id_len; ++i) set_key(h_ref + i, n_keys);
-  for (uint32_t j = 0; j < m; ++j) set_key(h_cur + j, cur_id[j]);
-  volatile uint32_t *h_flag = (volatile uint32_t *)(h + ho_flag);
-  *h_flag = 0;
-  uint8_t *const ids_at = ids_mapped ? hd : d + o_ids;
-  const Id *dref = (const Id *)(ids_at + ho_ref), *dcur = (const Id *)(ids_at + ho_cur);
-  if (!ids_mapped) SS_HIP(hipMemcpyAsync(ids_at, h, ids_end, hipMemcpyHostToDevice, s));
-  uint32_t *masks = (uint32_t *)(d + o_mask), *rows = (uint32_t *)(short_rows ? hd + ho_out : d + o_rows);
-  if (o_end > o_mask) ss_launch_fill(s, d + o_mask, o_end - o_mask, 0);
-  if (masks_needed)
-    hipLaunchKernelGGL(ss_align_masks_kernel<Id>, dim3((m + 255) / 256), dim3(256), 0, s, dcur, m, masks, W);
-  const RowsArgs args = {masks, (u64 *)(d + o_carry), rows, (uint32_t *)(hd + ho_flag), W, n_steps};
-  hipLaunchKernelGGL(ss_align_rows_kernel<Id>, dim3(strips), dim3(64), kLds ? lds_need(n_keys, n) : 0, s, dref, dcur, m, args,
-                     n_keys + 1);
-  SS_HIP(hipGetLastError());
-  uint32_t pairs = 0;
-  if (!short_rows) {
-    int32_t *dpair = (int32_t *)(d + o_pair);
-    uint16_t *table = (uint16_t *)(d + o_table);
-    int32_t *entry = (int32_t *)(d + o_entry);
-    const uint32_t *cmasks = masks, *crows = rows;
-    hipLaunchKernelGGL(ss_align_tab_kernel<Id>, dim3(walk_blocks, kWindow / kEntries), dim3(kEntries), 0, s, dref, n, cmasks,
-                       m, W, n_steps, crows, table);
-    hipLaunchKernelGGL(ss_align_chain_kernel<Id>, dim3(1), dim3(kChainThreads), 0, s, dref, n, cmasks, m, W, n_steps, crows,
-                       (const uint16_t *)table, entry, dpair);
-    hipLaunchKernelGGL(ss_align_pairs_kernel<Id>, dim3(walk_blocks), dim3(64), 0, s, dref, n, cmasks, W, n_steps, crows,
-                       (const int32_t *)entry, dpair);
-    SS_HIP(hipGetLastError());
-    SS_HIP(hipMemcpyAsync(h + ho_out, dpair, (size_t)n * 4, hipMemcpyDeviceToHost, s));
-    SS_HIP(hipStreamSynchronize(s));
-    if (*h_flag) return SS_E_TIMEOUT;
-    std::memcpy(ref_to_cur, h + ho_out, (size_t)n * 4);
-    for (uint32_t i = 0; i < n; ++i) pairs += ref_to_cur[i] >= 0;
-    *lcs = pairs;
-    return SS_OK;
-  }
-  SS_HIP(hipStreamSynchronize(s));
-  if (*h_flag) return SS_E_TIMEOUT;
+// the most keys with which it can run
+uint32_t most_few(uint32_t n) {
+  const size_t ids = lds_need(0, n);
+  return ids > kLdsBytes ? 0 : (uint32_t)std::min<size_t>(kLdsKeys - 1, (kLdsBytes - ids) / (kStripWords * 4));
+}
 
-  // walk back from (n, m)
-  const uint32_t *hr = (const uint32_t *)(h + ho_out);
-  uint32_t i = n, j = m;
-  while (i > 0 && j > 0) {
-    if (ref_id[i - 1] == cur_id[j - 1]) {
-      ref_to_cur[i - 1] = (int32_t)(j - 1);
-      ++pairs;
-      --i;
-      --j;
-    } else if ((hr[row_word(i - 1, (j - 1) >> 5, n_steps)] >> ((j - 1) & 31)) & 1u) {
-      --j;
-    } else {
-      --i;
-    }
+// Where everything lies.  `d` device scratch, `h` pinned scratch.
+struct Layout {
+  size_t h_ref, h_cur, h_flag, h_n_keys, h_out, h_end;
+  size_t ref, cur, ref_id, cur_id, n_keys, rep, id, slot, carry, rows, pair, table, entry, masks, end;
+  uint32_t n, m, W, strips, n_steps, n_blocks, walk_blocks, slots, bits;
+  bool one_wg, short_rows;
+
+  Layout(uint32_t n_, uint32_t m_) : n(n_), m(m_) {
+    W = (m + 31) / 32;                                     // 32-bit words of a row
+    strips = (W + kStripWords - 1) / kStripWords;
+    n_steps = steps_of(n);
+    n_blocks = n_steps / kBlock;
+    walk_blocks = (n + kWalkRows - 1) / kWalkRows;
+    const size_t row_bytes = (size_t)strips * n_steps * kStripWords * 4;
+    one_wg = n + m <= kWgOps;
+    // the kernel writes the rows to pinned host memory and the host walks them; else they stay in device memory and
+    // are walked there
+    short_rows = row_bytes <= kHostRowBytes;
+    bits = 13;
+    while ((1u << bits) < 2 * m) ++bits;
+    slots = 1u << bits;
+    size_t o = 0;
+    auto take = [&](size_t bytes) { size_t at = o; o += ss_align_up(bytes, 256); return at; };
+    h_ref = take((size_t)n * sizeof(ss_op_t));
+    h_cur = take((size_t)m * sizeof(ss_op_t));
+    h_flag = take(4);
+    h_n_keys = take(4);
+    h_out = take(short_rows ? row_bytes : (size_t)n * 4);
+    h_end = o;
+    o = 0;
+    ref = take(one_wg ? 0 : (size_t)n * sizeof(ss_op_t));
+    cur = take(one_wg ? 0 : (size_t)m * sizeof(ss_op_t));
+    ref_id = take((size_t)id_length(n_steps) * 4);
+    cur_id = take((size_t)m * 4);
+    n_keys = take(4);
+    rep = take(one_wg ? 0 : (size_t)slots * 4);
+    id = take(one_wg ? 0 : (size_t)slots * 4);
+    slot = take(one_wg ? 0 : (size_t)m * 4);
+    rows = take(short_rows ? 0 : row_bytes);
+    pair = take(short_rows ? 0 : (size_t)n * 4);
+    table = take(short_rows ? 0 : (size_t)walk_blocks * kWindow * 2);
+    entry = take(short_rows ? 0 : (size_t)walk_blocks * 4);
+    carry = take((size_t)(strips - 1) * (n_blocks + kCarryPad) * 8);
+    masks = o;                                             // last: its size needs the number of keys
+    end = o;
   }
-  *lcs = pairs;
+  size_t with_masks(uint32_t keys) const { return end + (size_t)(keys + 1) * W * 4; }
+};
+
+// Rows (and, long ones, the walk) for ids of the given form.  The masks are needed where the rows kernel does not keep its
+// own in LDS, and by the walk.
+template <class Id>
+int launch_rows(ss_ctx *ctx, const Layout &y, uint8_t *d, uint8_t *hd, uint32_t keys) {
+  constexpr bool kLds = sizeof(Id) == 2;
+  hipStream_t s = ctx->s_aux;
+  const Id *ref_id = (const Id *)(d + y.ref_id), *cur_id = (const Id *)(d + y.cur_id);
+  uint32_t *masks = (uint32_t *)(d + y.masks), *rows = (uint32_t *)(y.short_rows ? hd + y.h_out : d + y.rows);
+  const bool masks_needed = !kLds || !y.short_rows;
+  const size_t clear = (masks_needed ? y.with_masks(keys) : y.end) - y.carry;          // carry words, then masks
+  if (clear) ss_launch_fill(s, d + y.carry, clear, 0);
+  if (masks_needed)
+    hipLaunchKernelGGL(ss_align_masks_kernel<Id>, dim3((y.m + 255) / 256), dim3(256), 0, s, cur_id, y.m, masks, y.W);
+  const RowsArgs args = {masks, (u64 *)(d + y.carry), rows, (uint32_t *)(hd + y.h_flag), y.W, y.n_steps};
+  const uint32_t *n_keys = (const uint32_t *)(d + y.n_keys);
+  hipLaunchKernelGGL(ss_align_rows_kernel<Id>, dim3(y.strips), dim3(64), kLds ? lds_need(keys, y.n) : 0, s, ref_id, cur_id,
+                     y.m, args, n_keys);
+  if (!y.short_rows) {
+    const uint32_t *cmasks = masks, *crows = rows;
+    uint16_t *table = (uint16_t *)(d + y.table);
+    int32_t *entry = (int32_t *)(d + y.entry), *pair = (int32_t *)(d + y.pair);
+    hipLaunchKernelGGL(ss_align_tab_kernel<Id>, dim3(y.walk_blocks, kWindow / kEntries), dim3(kEntries), 0, s, ref_id, y.n,
+                       cmasks, y.m, y.W, y.n_steps, crows, table);
+    hipLaunchKernelGGL(ss_align_chain_kernel<Id>, dim3(1), dim3(kChainThreads), 0, s, ref_id, y.n, cmasks, y.m, y.W,
+                       y.n_steps, crows, (const uint16_t *)table, entry, pair);
+    hipLaunchKernelGGL(ss_align_pairs_kernel<Id>, dim3(y.walk_blocks), dim3(64), 0, s, ref_id, y.n, cmasks, y.W, y.n_steps,
+                       crows, (const int32_t *)entry, pair);
+    SS_HIP(hipGetLastError());
+    SS_HIP(hipMemcpyAsync((uint8_t *)ctx->h_scratch + y.h_out, pair, (size_t)y.n * 4, hipMemcpyDeviceToHost, s));
+  }
+  SS_HIP(hipGetLastError());
   return SS_OK;
 }
 
@@ -604,30 +772,106 @@ int ss_align_core(ss_ctx *ctx, const ss_op_t *ref, uint32_t n, const ss_op_t *cu
   *lcs = 0;
   if (n_keys_out) *n_keys_out = 0;
   if (n == 0 || m == 0) return SS_OK;
+  // (with both lengths at their limit the rows take 0.5 GiB, and so does the mask table with every key distinct)
+  static_assert((uint64_t)kAlignLenLimit * (kAlignLenLimit / 64) * 8 <= kAlignRowBytesLimit, "rows and masks fit");
 
-  // dense key ids: the keys of cur in first-seen order; reference operators whose key cur does not
-  // hold share the id n_keys, whose mask row stays zero
-  std::unordered_map<std::pair<uint64_t, uint32_t>, uint32_t, KeyHash> ids;
-  ids.reserve(256);
-  std::vector<uint32_t> cur_id(m), ref_id(n);
-  for (uint32_t j = 0; j < m; ++j) {
-    const std::pair<uint64_t, uint32_t> key{((uint64_t)cur[j].op_token << 32) | cur[j].stack_hash, cur[j].sig};
-    auto it = ids.find(key);
-    if (it == ids.end()) it = ids.emplace(key, (uint32_t)ids.size()).first;
-    cur_id[j] = it->second;
+  const Layout y(n, m);
+  const uint32_t few = most_few(n);
+  hipStream_t s = ctx->s_aux;
+  uint8_t *d = nullptr, *h = nullptr, *hd = nullptr;
+  volatile uint32_t *h_flag = nullptr, *h_n_keys = nullptr;
+  // key ids; again if the mask table then turns out not to fit (the first call with that many keys)
+  auto make_ids = [&](size_t dev_bytes) -> int {
+    const int rc = ss_scratch_reserve(ctx, dev_bytes, y.h_end);
+    if (rc != SS_OK) return rc;
+    d = (uint8_t *)ctx->d_scratch;
+    h = (uint8_t *)ctx->h_scratch;
+    SS_HIP(hipHostGetDevicePointer((void **)&hd, h, 0));
+    std::memcpy(h + y.h_ref, ref, (size_t)n * sizeof(ss_op_t));
+    std::memcpy(h + y.h_cur, cur, (size_t)m * sizeof(ss_op_t));
+    h_flag = (volatile uint32_t *)(h + y.h_flag);
+    h_n_keys = (volatile uint32_t *)(h + y.h_n_keys);
+    *h_flag = 0;
+    KeyArgs a = {};
+    a.n = n; a.m = m; a.n_steps = y.n_steps;
+    a.few = few;
+    a.ref_id = d + y.ref_id;
+    a.cur_id = d + y.cur_id;
+    a.n_keys = (uint32_t *)(d + y.n_keys);
+    a.n_keys_out = (uint32_t *)(hd + y.h_n_keys);
+    const ss_op_t *mref = (const ss_op_t *)(hd + y.h_ref), *mcur = (const ss_op_t *)(hd + y.h_cur);
+    if (y.one_wg) {
+      a.ref = mref;
+      a.cur = mcur;
+      hipLaunchKernelGGL(ss_align_keys_kernel, dim3(1), dim3(kWgThreads), (2 * kWgSlots + 3 * kWgOps) * 4, s, a);
+    } else {
+      ss_op_t *dref = (ss_op_t *)(d + y.ref), *dcur = (ss_op_t *)(d + y.cur);
+      a.ref = dref;
+      a.cur = dcur;
+      a.rep = (uint32_t *)(d + y.rep);
+      a.id = (uint32_t *)(d + y.id);
+      a.slot = (uint32_t *)(d + y.slot);
+      a.mask = y.slots - 1;
+      a.shift = 64 - y.bits;
+      const uint32_t wgs = std::min(256u, (std::max(n, m) + 255) / 256), len = std::max(m, id_length(y.n_steps));
+      hipLaunchKernelGGL(ss_align_fetch_kernel, dim3(wgs), dim3(256), 0, s, mref, dref, n, mcur, dcur, m, a.rep, y.slots, a.n_keys);
+      hipLaunchKernelGGL(ss_align_insert_kernel, dim3((m + 255) / 256), dim3(256), 0, s, a);
+      hipLaunchKernelGGL(ss_align_ids_kernel, dim3((len + 255) / 256), dim3(256), 0, s, a);
+    }
+    SS_HIP(hipGetLastError());
+    return SS_OK;
+  };
+  int rc = make_ids(y.with_masks(kLdsKeys));
+  if (rc != SS_OK) return rc;
+  uint32_t keys = kLdsKeys - 1;
+  bool done = false;
+  if (y.one_wg) {                       // rows at once, as if there were few keys (the kernel looks again): one wait less
+    if ((rc = launch_rows<uint16_t>(ctx, y, d, hd, keys)) != SS_OK) return rc;
+    SS_HIP(hipStreamSynchronize(s));
+    keys = *h_n_keys;
+    done = keys <= few;
+  } else {
+    SS_HIP(hipStreamSynchronize(s));
+    keys = *h_n_keys;
   }
-  const uint32_t n_keys = (uint32_t)ids.size();
-  for (uint32_t i = 0; i < n; ++i) {
-    const std::pair<uint64_t, uint32_t> key{((uint64_t)ref[i].op_token << 32) | ref[i].stack_hash, ref[i].sig};
-    auto it = ids.find(key);
-    ref_id[i] = it == ids.end() ? n_keys : it->second;
+  if (!done) {
+    if (y.with_masks(keys) > ctx->d_scratch_bytes) {
+      if ((rc = make_ids(y.with_masks(keys))) != SS_OK) return rc;
+    }
+    rc = keys <= few ? launch_rows<uint16_t>(ctx, y, d, hd, keys) : launch_rows<uint32_t>(ctx, y, d, hd, keys);
+    if (rc != SS_OK) return rc;
+    SS_HIP(hipStreamSynchronize(s));
   }
-  if (n_keys_out) *n_keys_out = n_keys;
-  const uint64_t W64 = (m + 63) / 64;
-  if (n * W64 * 8 > kAlignRowBytesLimit || (n_keys + 1) * W64 * 8 > kAlignRowBytesLimit) return SS_E_CAPACITY;
-  return n_keys + 1 <= kLdsKeys && lds_need(n_keys, n) <= kLdsBytes
-             ? align_ids<uint16_t>(ctx, ref_id, cur_id, n_keys, ref_to_cur, lcs)
-             : align_ids<uint32_t>(ctx, ref_id, cur_id, n_keys, ref_to_cur, lcs);
+  if (*h_flag) return SS_E_TIMEOUT;
+  if (n_keys_out) *n_keys_out = keys;
+  uint32_t pairs = 0;
+  if (!y.short_rows) {
+    std::memcpy(ref_to_cur, h + y.h_out, (size_t)n * 4);
+    for (uint32_t i = 0; i < n; ++i) pairs += ref_to_cur[i] >= 0;
+    *lcs = pairs;
+    return SS_OK;
+  }
+  // walk back from (n, m)
+  const uint32_t *hr = (const uint32_t *)(h + y.h_out);
+  constexpr uint32_t kAhead = 24;
+  uint32_t i = n, j = m;
+  while (i > 0 && j > 0) {
+    // the rows came over the link: none is in a cache, and the path's next rows lie near the diagonal
+    if (i > kAhead && j > kAhead) __builtin_prefetch(hr + row_word(i - 1 - kAhead, (j - 1 - kAhead) >> 5, y.n_steps));
+    const ss_op_t &a = ref[i - 1], &b = cur[j - 1];
+    if (a.op_token == b.op_token && a.stack_hash == b.stack_hash && a.sig == b.sig) {
+      ref_to_cur[i - 1] = (int32_t)(j - 1);
+      ++pairs;
+      --i;
+      --j;
+    } else if ((hr[row_word(i - 1, (j - 1) >> 5, y.n_steps)] >> ((j - 1) & 31)) & 1u) {
+      --j;
+    } else {
+      --i;
+    }
+  }
+  *lcs = pairs;
+  return SS_OK;
 }
 
 void ss_align_anchors(const ss_op_t *ref, uint32_t n, const ss_op_t *cur, const int32_t *ref_to_cur,
