@@ -6,12 +6,14 @@
 // L[i][j+1] = L[i][j] + 1, V_0 is all ones, and one reference operator advances the row by
 //     V' = (V + (V & M)) | (V & ~M),     M = positions of cur holding that operator's key.
 // The addition's carry runs through the whole row, so a row is not updated at once: lane l holds word l
-// and works on row t - l in step t, taking the carry that lane l - 1 produced for the same row one step
-// earlier (all carries of a wavefront are one 64-bit lane mask, so handing them on is one scalar shift).
-// A wavefront covers a strip of 2,048 columns; a longer cur takes one workgroup per strip, each reading
-// the carries out of the strip before it.  The rows stay where they were written, one step after the
-// other, and the alignment is read back from (n, m): equal operators pair, otherwise left if bit j-1 of
-// V_i is set (L[i][j-1] = L[i][j]), else up; on the host for short sequences, on the GPU for long ones.
+// and works on row t - 2 l in step t, taking the carry that lane l - 1 produced for the same row two steps
+// earlier (all carries of a wavefront are one 64-bit lane mask, so handing them on is one scalar shift;
+// with one step in between, the way through the scalar unit and back was the longest chain).
+// A wavefront covers a strip of 2,048 columns; a longer cur takes one workgroup per strip of 1,984, each
+// reading the carries out of the strip before it.  The rows stay where they were written, four steps of a
+// lane together, and the alignment is read back from (n, m): equal operators pair, otherwise left if bit
+// j-1 of V_i is set (L[i][j-1] = L[i][j]), else up; on the host for short sequences, on the GPU for long
+// ones.
 #include <algorithm>
 #include <cstring>
 
@@ -20,31 +22,40 @@
 namespace {
 
 typedef unsigned long long u64;
+typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 
-constexpr uint32_t kAlignLenLimit = 1u << 16;          // at most 32 strips
+constexpr uint32_t kAlignLenLimit = 1u << 16;          // at most 34 strips
 constexpr size_t kAlignRowBytesLimit = 1ull << 30;     // rows kept for the walk back
 constexpr uint32_t kBlock = 32;                        // steps between two looks at the neighbouring strip
 constexpr uint32_t kGroup = 8;                         // steps whose masks are looked up together
-constexpr uint32_t kStripWords = 64;                   // 32-bit words of a row, one per lane
+constexpr uint32_t kStripWords = 64;                   // 32-bit words of a row, one per lane, in a single strip
+constexpr uint32_t kInnerWords = 62;                   // the same where there are several strips: lanes 1 to 62
 constexpr uint32_t kLdsKeys = 256;                     // mask rows (with the empty one) a strip keeps in LDS at most, 256 bytes each
-constexpr size_t kLdsBytes = 160 * 1024;               // for these and the reference's ids
-constexpr uint32_t kIdPad = 64;                        // entries before the first id (lanes whose row has not begun)
+constexpr size_t kLdsBytes = 160 * 1024;               // for these, the reference's ids and the ring below
+constexpr uint32_t kRingBytes = 4096;
+constexpr uint32_t kSkew = 2;                          // steps that a lane is behind the one before it
+constexpr uint32_t kIdPad = 64 * kSkew;                // entries before the first id (lanes whose row has not begun)
 // Rows up to this many bytes go straight to host memory and are walked there: beside the kernel's pace they cost the
 // link nothing up to about 13 GB/s, and the walk on the GPU takes four more launches and two copies.
 constexpr size_t kHostRowBytes = 4u << 20;
-constexpr uint32_t kCarryPad = 4;                      // carry words a strip may look at beyond its neighbour's last
+constexpr uint32_t kCarryPad = 8;                      // carry words a strip may look at beyond its neighbour's last
 constexpr uint32_t kPollLimit = 1u << 24;              // looks at a carry word before a strip gives up
 
 // steps a strip takes for n rows, whole blocks of them
-static inline uint32_t steps_of(uint32_t n) { return (n + kStripWords - 1 + kBlock - 1) / kBlock * kBlock; }
+static inline uint32_t steps_of(uint32_t n) { return (n + kSkew * (kStripWords - 1) + kBlock - 1) / kBlock * kBlock; }
 
 // entries of a padded id array, a multiple of 16 bytes
-static inline __host__ __device__ uint32_t id_length(uint32_t n_steps) { return kIdPad + n_steps + 2 * kBlock; }
+static inline __host__ __device__ uint32_t id_length(uint32_t n_steps) { return kIdPad + n_steps + 3 * kBlock; }
 
-// word w of row r: lane w % 64 of strip w / 64 wrote it in step r + w % 64
-static inline __host__ __device__ size_t row_word(uint32_t r, uint32_t w, uint32_t steps) {
-  const uint32_t l = w % kStripWords;
-  return ((size_t)(w / kStripWords) * steps + r + l) * kStripWords + l;
+static inline __host__ __device__ uint32_t strips_of(uint32_t W) {
+  return W <= kStripWords ? 1 : (W + kInnerWords - 1) / kInnerWords;
+}
+
+// Word w (of W) of row r: lane l of its strip wrote it in step r + 2 l, four steps of a lane to a 16-byte store.
+static inline __host__ __device__ size_t row_word(uint32_t r, uint32_t w, uint32_t W, uint32_t steps) {
+  const bool one = W <= kStripWords;
+  const uint32_t strip = one ? 0 : w / kInnerWords, l = one ? w : w % kInnerWords + 1, t = r + kSkew * l;
+  return (size_t)strip * steps * kStripWords + ((size_t)(t / 4) * kStripWords + l) * 4 + t % 4;
 }
 
 // A key id as it is stored: 16 bits, already multiplied by the 256 bytes of an LDS mask row, where the mask rows fit
@@ -236,55 +247,24 @@ __global__ void ss_align_masks_kernel(const Id *__restrict__ cur_id, uint32_t m,
   if (j < m) atomicOr(&masks[(size_t)key_of(cur_id[j]) * W + (j >> 5)], 1u << (j & 31));
 }
 
-// One row step of a word, N = ~M: V' = (V + (V & M) + carry in) | (V & ~M); the carries in and out are lane masks.
-// Written out because the compiler turns a carry that leaves as a lane mask into a select and a compare.
-__device__ __forceinline__ u64 row_step(uint32_t &V, uint32_t N, u64 cin) {
+// Two row steps of a word: V' = (V + (V & M) + carry in) | (V & ~M); the carries in and out are lane masks, `even` and
+// `odd` those out of the two steps before.
+// Written out because the compiler turns a carry that leaves as a lane mask into a select and a compare, and for the order.
+// (bitop3's number is its truth table, S0 = 0xF0, S1 = 0xCC, S2 = 0xAA: (S0 & ~S1) | S2.)
+__device__ __forceinline__ void row_steps(uint32_t V, uint32_t M0, uint32_t M1, u64 &even, u64 &odd, uint32_t &V0, uint32_t &V1) {
   uint32_t a;
-  u64 cout;
-  asm("v_bfi_b32 %[a], %[n], 0, %[v]\n\t"
-      "v_addc_co_u32_e64 %[a], %[co], %[v], %[a], %[ci]\n\t"
-      "v_and_or_b32 %[v], %[v], %[n], %[a]"
-      : [v] "+v"(V), [a] "=&v"(a), [co] "=&s"(cout)
-      : [n] "v"(N), [ci] "s"(cin));
-  return cout;
+  asm("v_and_b32_e32 %[a], %[m0], %[v]\n\t"
+      "s_lshl_b64 %[c0], %[c0], 1\n\t"
+      "s_lshl_b64 %[c1], %[c1], 1\n\t"
+      "v_addc_co_u32_e64 %[a], %[c0], %[v], %[a], %[c0]\n\t"
+      "v_bitop3_b32 %[v0], %[v], %[m0], %[a] bitop3:0xba\n\t"
+      "v_and_b32_e32 %[a], %[m1], %[v0]\n\t"
+      "v_addc_co_u32_e64 %[a], %[c1], %[v0], %[a], %[c1]\n\t"
+      "v_bitop3_b32 %[v1], %[v0], %[m1], %[a] bitop3:0xba"
+      : [v0] "=&v"(V0), [v1] "=v"(V1), [a] "=&v"(a), [c0] "+s"(even), [c1] "+s"(odd)
+      : [v] "v"(V), [m0] "v"(M0), [m1] "v"(M1)
+      : "scc");
 }
-
-// The same, and hist = 2 * hist + this lane's bit of `before`, the carries out of the previous step (written long
-// enough ago: a carry mask may be read again two instructions after it was written at the earliest).
-__device__ __forceinline__ u64 row_step_kept(uint32_t &V, uint32_t N, u64 cin, uint32_t &hist, u64 before) {
-  uint32_t a;
-  u64 cout;
-  asm("v_bfi_b32 %[a], %[n], 0, %[v]\n\t"
-      "v_addc_co_u32_e64 %[a], %[co], %[v], %[a], %[ci]\n\t"
-      "v_addc_co_u32_e64 %[h], vcc, %[h], %[h], %[be]\n\t"
-      "v_and_or_b32 %[v], %[v], %[n], %[a]"
-      : [v] "+v"(V), [a] "=&v"(a), [co] "=&s"(cout), [h] "+v"(hist)
-      : [n] "v"(N), [ci] "s"(cin), [be] "s"(before)
-      : "vcc");
-  return cout;
-}
-
-// The ids of kGroup consecutive steps; 16-bit ids stay packed until they are used, so that reading them is one load
-// that nothing waits for.
-template <class Id>
-struct IdGroup {
-  Id v[kGroup];
-  __device__ __forceinline__ void load(const Id *p) {
-#pragma unroll
-    for (uint32_t u = 0; u < kGroup; ++u) v[u] = p[u];
-  }
-  __device__ __forceinline__ uint32_t operator[](uint32_t u) const { return v[u]; }
-};
-template <>
-struct IdGroup<uint16_t> {
-  uint4 v;
-  __device__ __forceinline__ void load(const uint16_t *p) { __builtin_memcpy(&v, p, 16); }
-  __device__ __forceinline__ uint32_t operator[](uint32_t u) const {
-    const uint32_t x = u < 2 ? v.x : u < 4 ? v.y : u < 6 ? v.z : v.w;
-    return u & 1 ? x >> 16 : x & 0xFFFFu;
-  }
-};
-static_assert(kGroup == 8, "a group of 16-bit ids is one 16-byte word");
 
 struct RowsArgs {
   const uint32_t *masks;     // wide ids only
@@ -293,22 +273,102 @@ struct RowsArgs {
   uint32_t W, n_steps;
 };
 
-// All rows of one strip.  my_ids: entry t is the id of this lane's row in step t; table: this lane's word of an LDS
-// mask row of key 0 (inverted).  carry[strip][block]: bit u = carry out of the strip's last lane in step 32 * block + u,
-// bit 32 = the word is there (the value and its arrival are one store, so no fence is needed); cleared before the
-// launch.  A strip waits only for the strip before it, which waits for no later one, and not for ever (kPollLimit).
-template <class Id, bool TAKES, bool GIVES>
-__device__ __forceinline__ void strip_rows(const RowsArgs &a, const Id *my_ids, const uint8_t *table) {
-  constexpr bool kLds = sizeof(Id) == 2;
+static __device__ const uint32_t all_ones = ~0u;
+
+// Mask words of the steps of this lane, looked up a group at a time for the block after the one at work.
+// Wide ids: masks and ids from device memory; a lane that holds no word of the row has W = 0 and `word` = &all_ones.
+// The ids are read a block before they are used, since waiting for them waits for everything read before them too (read
+// one group before: 2,000 x 2,000 operators with 1,000 keys 176 us a call against 120, 60,000 x 60,000 with 500 keys
+// 5.9 ms against 4.4).
+template <class Id>
+struct Masks {
+  const __attribute__((address_space(1))) uint32_t *word;      // this lane's word of the mask row of key 0
+  const uint32_t *ids;       // entry t is the id of this lane's row in step t
+  uint32_t W, id[kBlock];
+  __device__ __forceinline__ void begin() { prime(0); }
+  __device__ __forceinline__ void first(uint32_t) {}
+  __device__ __forceinline__ void prime(uint32_t b) {
+#pragma unroll
+    for (uint32_t u = 0; u < kBlock; ++u) id[u] = ids[b * kBlock + u];
+  }
+  __device__ __forceinline__ uint32_t look_up(uint32_t u) const { return word[(size_t)id[u] * W]; }
+  __device__ __forceinline__ void refill(uint32_t b, uint32_t g) {
+#pragma unroll
+    for (uint32_t u = 0; u < kGroup; ++u) id[g + u] = ids[(b + 2) * kBlock + g + u];
+  }
+  __device__ __forceinline__ void block_begins() {}
+  __device__ __forceinline__ void block_ends() {}
+};
+
+// 16-bit ids: masks and ids in LDS.  Lane l needs eight ids from entry t - 2 l on, and a 16-byte LDS read that isn't
+// aligned in every lane keeps the LDS for 72 cycles (up to 3.7 ns a step).  So the ids next needed lie in a ring a second
+// time, once for each of the shifts 2 l % 8: piece c of position i holds entries 8 i - 2 c to 8 i - 2 c + 7, and a
+// lane's read is an aligned 16 bytes.  A block of steps uses up four positions; the next four are copied by one 4-byte
+// read and write of every lane.  The ring's 32 positions are there twice, so that five in a row never wrap.
+template <>
+struct Masks<uint16_t> {
+  static constexpr uint32_t kPosition = 64, kHalf = kRingBytes / 2, kAdvance = kBlock / kGroup * kPosition;
+  const uint8_t *table;      // this lane's word of the LDS mask row of key 0
+  const uint16_t *ids;       // all of them, padded
+  uint8_t *ring;
+  uint32_t lane, read_at, write_at, moving;
+  const uint32_t *from;
+  uint4 id;
+
+  __device__ __forceinline__ void store(uint32_t x) {
+    *reinterpret_cast<uint32_t *>(ring + write_at) = x;
+    *reinterpret_cast<uint32_t *>(ring + write_at + kHalf) = x;
+    write_at = (write_at + kAdvance) % kHalf;
+    from += kBlock / 2;
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");   // read by other lanes; LDS accesses of a wavefront are in order
+    __builtin_amdgcn_wave_barrier();
+  }
+  // positions 1 to 24: from the last lane's first to as far as the first block of steps reads
+  __device__ __forceinline__ void begin() {
+    const uint32_t position = 1 + lane / 16, shift = lane % 16 / 4 * 2, part = lane % 4;
+    from = reinterpret_cast<const uint32_t *>(ids + position * kGroup - shift + 2 * part);
+    write_at = kPosition + lane * 4;
+#pragma unroll 1
+    for (uint32_t i = 0; i < 6; ++i) store(*from);
+    read_at = (kIdPad / kGroup - lane / 4) * kPosition + lane % 4 * 16;
+  }
+  // ids of the group of steps that is `positions` after where read_at stands, at most four
+  __device__ __forceinline__ void read_ids(uint32_t positions) {
+    id = *reinterpret_cast<const uint4 *>(ring + read_at + positions * kPosition);
+  }
+  __device__ __forceinline__ void first(uint32_t g) { read_ids(g / kGroup); }
+  __device__ __forceinline__ void prime(uint32_t) {
+    read_ids(kBlock / kGroup);
+    read_at = (read_at + kAdvance) % kHalf;
+  }
+  __device__ __forceinline__ void refill(uint32_t, uint32_t g) { read_ids(g / kGroup + 1); }
+  __device__ __forceinline__ uint32_t look_up(uint32_t step) const {
+    const uint32_t u = step % kGroup, x = u < 2 ? id.x : u < 4 ? id.y : u < 6 ? id.z : id.w;
+    return *reinterpret_cast<const uint32_t *>(table + (u & 1 ? x >> 16 : x & 0xFFFFu));
+  }
+  __device__ __forceinline__ void block_begins() { moving = *from; }
+  __device__ __forceinline__ void block_ends() {
+    store(moving);
+    read_at = (read_at + kAdvance) % kHalf;
+  }
+};
+static_assert(kSkew == 2 && kGroup == 8 && kBlock == 32 && kIdPad == 128, "positions of the ring");
+
+// All rows of one strip.  Where there are several (kMany), lanes 0 and 63 hold no word: their M is all ones, which
+// makes a step V' = 2 V + carry in with V's top bit as the carry out.  So lane 63 collects what lane 62 hands on, one bit
+// a step, first step highest, and lane 0 hands on what it was given as a word, likewise: strips exchange carries without
+// an instruction in any step (a history kept beside the row and bits put into the lane mask took 3.7 of 11.1 instructions).
+// carry[strip][block]: lane 63's word after step 32 * block + 31, bit 32 = the word is there (the value and its arrival
+// are one store, so no fence is needed); cleared before the launch.  A strip waits only for the strip before it,
+// which waits for no later one, and not for ever (kPollLimit).
+template <class Id, bool kMany>
+__device__ __forceinline__ void strip_rows(const RowsArgs &a, Masks<Id> masks, bool stored) {
   const uint32_t lane = threadIdx.x, strip = blockIdx.x, n_blocks = a.n_steps / kBlock;
-  auto mask_of = [&](uint32_t id) -> uint32_t {              // inverted
-    if constexpr (kLds) return *reinterpret_cast<const uint32_t *>(table + id);
-    return ~a.masks[(size_t)id * a.W + strip * kStripWords + lane];
-  };
-  const u64 *const cin_words = a.carry + (size_t)(strip - (TAKES ? 1 : 0)) * (n_blocks + kCarryPad);
+  const bool takes = kMany && strip != 0, gives = kMany && strip + 1 < gridDim.x;
+  const u64 *const cin_words = a.carry + (size_t)(strip - (takes ? 1 : 0)) * (n_blocks + kCarryPad);
   u64 *const cout_words = a.carry + (size_t)strip * (n_blocks + kCarryPad);
   auto peek = [&](uint32_t block) { return __hip_atomic_load(cin_words + block, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); };
-  // x: what a peek saw earlier; the result is uniform, as it takes part in lane masks
+  // x: what a peek saw earlier
   auto carry_word = [&](uint32_t block, u64 x) -> uint32_t {
     uint32_t word = __builtin_amdgcn_readfirstlane((uint32_t)x);
     if (__builtin_expect(__builtin_amdgcn_readfirstlane((uint32_t)(x >> 32)) != 0, 1)) return word;
@@ -323,53 +383,62 @@ __device__ __forceinline__ void strip_rows(const RowsArgs &a, const Id *my_ids, 
     return 0;
   };
 
-  uint32_t V = ~0u, hist = 0;
-  u64 cmask = 0;
-  uint32_t N[kBlock];
-  IdGroup<Id> ids;
+  uint32_t V = ~0u;
+  u64 even = 0, odd = 0;
+  uint32_t M[kBlock];
+  masks.begin();
 #pragma unroll
   for (uint32_t g = 0; g < kBlock; g += kGroup) {
-    ids.load(my_ids + g);
+    masks.first(g);
 #pragma unroll
-    for (uint32_t u = 0; u < kGroup; ++u) N[g + u] = mask_of(ids[u]);
+    for (uint32_t u = g; u < g + kGroup; ++u) M[u] = masks.look_up(u);
   }
-  ids.load(my_ids + kBlock);
+  masks.prime(1);
   uint32_t prev_word = 0;
   u64 ahead = 0;                      // a carry word, looked at one block before it is needed
-  if constexpr (TAKES) {
-    prev_word = n_blocks > 1 ? carry_word(1, peek(1)) : 0;
-    ahead = peek(2);
-    asm volatile("" : "+v"(ahead));   // arrived: inside the loop the wait for it then leaves that block's stores in flight
+  if (takes) {
+    prev_word = n_blocks > 3 ? carry_word(3, peek(3)) : 0;
+    ahead = peek(4);
   }
-  uint32_t *out = a.rows + (size_t)strip * a.n_steps * kStripWords;        // uniform: lane l of a step is word l
+  asm volatile("" : "+v"(ahead));     // arrived: inside the loop the wait for it then leaves that block's stores in flight
+  // A lane whose word nobody reads stores beyond the end of the buffer, which drops it: all lanes stay in step, and
+  // no store needs a lane mask of its own.
+  const __amdgpu_buffer_rsrc_t out = __builtin_amdgcn_make_buffer_rsrc(
+      a.rows + (size_t)strip * a.n_steps * kStripWords, 0, (int)(a.n_steps * kStripWords * 4), 0x00027000);
+  uint32_t at = stored ? lane * 16 : 0x80000000u;
   for (uint32_t b = 0; b < n_blocks; ++b) {
-    // lane 0's row in step t is row t; its carry left the strip before in that strip's step t + 63
-    uint32_t in = 0;
-    if constexpr (TAKES) {
-      const uint32_t next_word = b + 2 < n_blocks ? carry_word(b + 2, ahead) : 0;
-      in = __builtin_amdgcn_readfirstlane((prev_word >> 31) | (next_word << 1));
-      prev_word = next_word;
-      ahead = peek(b + 3);
+    masks.block_begins();
+    if constexpr (kMany) {
+      // lane 0 hands row t on in step t; lane 63 of the strip before received that carry in step t + 126
+      uint32_t in = 0;
+      if (takes) {
+        const uint32_t next_word = b + 4 < n_blocks ? carry_word(b + 4, ahead) : 0;
+        in = (prev_word << 30) | (next_word >> 2);
+        prev_word = next_word;
+        ahead = peek(b + 5);
+      }
+      V = lane ? V : in;
     }
-    const Id *const ids_at = my_ids + (b + 1) * kBlock;
 #pragma unroll
     for (uint32_t g = 0; g < kBlock; g += kGroup) {
 #pragma unroll
-      for (uint32_t u = g; u < g + kGroup; ++u) {
-        const u64 cin = TAKES ? (cmask << 1) | ((in >> u) & 1u) : cmask << 1;
-        cmask = GIVES ? row_step_kept(V, N[u], cin, hist, cmask) : row_step(V, N[u], cin);
-        out[u * kStripWords + lane] = V;
+      for (uint32_t u = g; u < g + kGroup; u += 4) {
+        uint32_t v0, v1, v2;
+        row_steps(V, M[u], M[u + 1], even, odd, v0, v1);
+        row_steps(v1, M[u + 2], M[u + 3], even, odd, v2, V);
+        const u32x4 v = {v0, v1, v2, V};
+        __builtin_amdgcn_raw_buffer_store_b128(v, out, at, u * kStripWords * 4, 0);
       }
 #pragma unroll
-      for (uint32_t u = 0; u < kGroup; ++u) N[g + u] = mask_of(ids[u]);  // the same steps of the next block
-      ids.load(ids_at + g + kGroup);
+      for (uint32_t u = g; u < g + kGroup; ++u) M[u] = masks.look_up(u);  // the same steps of the next block
+      masks.refill(b, g);
       // kept in this order: a refill moved up needs a second register, and the copy back waits for the load
       __builtin_amdgcn_sched_barrier(0);
     }
-    out += kBlock * kStripWords;
-    if constexpr (GIVES) {            // the last lane's carries, first step lowest; hist is one step behind
-      const uint32_t h = __builtin_amdgcn_readlane((int)hist, 63);
-      const uint32_t word = __builtin_bitreverse32((h << 1) | (uint32_t)(cmask >> 63));
+    at += kBlock * kStripWords * 4;
+    masks.block_ends();
+    if (gives) {
+      const uint32_t word = __builtin_amdgcn_readlane((int)V, 63);
       if (lane == 0)
         __hip_atomic_store(cout_words + b, (1ull << 32) | word, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
@@ -381,12 +450,18 @@ __device__ __forceinline__ void strip_rows(const RowsArgs &a, const Id *my_ids, 
 // the strip builds its own mask table in LDS from cur_id and keeps all the reference's ids there too; wider ids (more
 // keys or operators than fit): masks and ids come from device memory.
 //
-// Bound by the issue of one wavefront's instructions from one step to the next, seven of them for a single strip
-// (words of 32 bits, since a wider word puts a second addition into the chain; the table holds ~M, which saves an
-// instruction; masks are looked up one block of steps ahead, a carry word one block before it is needed).  18.9 ns a
-// row for one strip, 30 ns for sixteen that hand carries on.  Updating a whole row at once in one wavefront, its
-// carries crossing lanes by two ballots and scalar arithmetic, took 128 ns a row at 1,156 columns and 755 ns at
-// 32,300: 1,154 x 1,156 operators 149 -> 30 us, 32,312 x 32,297 operators 24.5 -> 1.0 ms.
+// Bound by the issue of one wavefront's instructions from one step to the next, seven of them (words of 32 bits, since
+// a wider word puts a second addition into the chain; masks are looked up one block of steps ahead, a carry word one
+// block before it is needed).  A scalar instruction that comes soon after a vector instruction that wrote a lane mask
+// waits for it, whichever mask it reads: so lanes are two steps apart and the shifts of two steps' carries stand
+// together, as far from the additions as they can.  Single strip, a row: 18.8 ns with a shift in every step, 17.3 with lanes
+// two steps apart and still one shift a step, 15.5 as it is; sixteen strips that hand carries on: 24.7, 22.1, 20.1.
+// (The parts of V that the next row needs worked out together with V, one operation less in the chain and one more
+// to issue: 18.6 and 21.8.)  Rows stored one word at a time, carries exchanged by two more instructions a step and ids
+// read unaligned: 18.9 and 29.4.  Updating a whole row at once in one wavefront, its carries crossing lanes by two ballots and
+// scalar arithmetic, took 128 ns a row at 1,156 columns and 755 ns at 32,300: 1,154 x 1,156 operators 149 -> 27 us, 32,312 x
+// 32,297 operators 24.5 -> 0.65 ms.  Two steps between lanes and the two lanes without a word cost a strip
+// about 70 steps more until the next one has its first carry: 500 x 30,000 operators take 252 us a call, 214 without.
 template <class Id>
 __global__ __launch_bounds__(64) void ss_align_rows_kernel(const Id *__restrict__ ref_id,
                                                            const Id *__restrict__ cur_id, uint32_t m, RowsArgs a,
@@ -394,14 +469,22 @@ __global__ __launch_bounds__(64) void ss_align_rows_kernel(const Id *__restrict_
   constexpr bool kLds = sizeof(Id) == 2;
   extern __shared__ uint32_t lds[];
   const uint32_t lane = threadIdx.x, strip = blockIdx.x;
-  const uint32_t w0 = strip * kStripWords;
-  const uint32_t lanes = min(kStripWords, a.W - w0);
+  const bool many = gridDim.x > 1;
+  const uint32_t first = many ? 1 : 0;                       // lane of the strip's first word
+  const uint32_t w0 = strip * kInnerWords;
+  const uint32_t words = min(many ? kInnerWords : kStripWords, a.W - w0);
+  const bool stored = lane >= first && lane < first + words;
   const uint32_t n_mask_rows = *n_keys + 1;
   if (kLds && n_mask_rows > kLdsKeys) return;                // launched before the number was known, and the ids are wide
-  Id *const lds_ids = reinterpret_cast<Id *>(lds + n_mask_rows * kStripWords);
+  Masks<Id> masks;
   if constexpr (kLds) {
+    uint8_t *const ring = reinterpret_cast<uint8_t *>(lds + n_mask_rows * kStripWords);
+    Id *const lds_ids = reinterpret_cast<Id *>(ring + kRingBytes);
     uint4 *const table4 = reinterpret_cast<uint4 *>(lds);
-    for (uint32_t i = lane; i < n_mask_rows * (kStripWords / 4); i += 64) table4[i] = uint4{~0u, ~0u, ~0u, ~0u};
+    for (uint32_t i = lane; i < n_mask_rows * (kStripWords / 4); i += 64) {
+      const uint32_t part = i % (kStripWords / 4);
+      table4[i] = uint4{many && part == 0 ? ~0u : 0, 0, 0, many && part == kStripWords / 4 - 1 ? ~0u : 0};
+    }
     const uint4 *src = reinterpret_cast<const uint4 *>(ref_id);
     uint4 *dst = reinterpret_cast<uint4 *>(lds_ids);
     const uint32_t n16 = id_length(a.n_steps) * sizeof(Id) / 16;
@@ -416,28 +499,31 @@ __global__ __launch_bounds__(64) void ss_align_rows_kernel(const Id *__restrict_
     }
     __syncthreads();
     // two words' columns a pass, sixteen passes of ids in flight
-    for (uint32_t g = 0; g < lanes; g += 32) {
+    for (uint32_t g = 0; g < words; g += 32) {
       uint32_t id[16];
 #pragma unroll
       for (uint32_t u = 0; u < 16; ++u) {
-        const uint32_t j = (w0 + g + 2 * u) * 32 + lane;
-        id[u] = j < m ? cur_id[j] : 0xFFFFFFFFu;
+        const uint32_t w = g + 2 * u + (lane >> 5), j = (w0 + w) * 32 + (lane & 31);
+        id[u] = w < words && j < m ? cur_id[j] : 0xFFFFFFFFu;
       }
 #pragma unroll
       for (uint32_t u = 0; u < 16; ++u)
         if (id[u] != 0xFFFFFFFFu)
-          atomicAnd(&lds[key_of((uint16_t)id[u]) * kStripWords + g + 2 * u + (lane >> 5)], ~(1u << (lane & 31)));
+          atomicOr(&lds[key_of((uint16_t)id[u]) * kStripWords + first + g + 2 * u + (lane >> 5)], 1u << (lane & 31));
     }
     __syncthreads();
+    masks.table = reinterpret_cast<const uint8_t *>(lds + lane);
+    masks.ids = lds_ids;
+    masks.ring = ring;
+    masks.lane = lane;
+  } else {
+    using Global = const __attribute__((address_space(1))) uint32_t *;
+    masks.word = stored ? (Global)(a.masks + w0 + lane - first) : (Global)&all_ones;
+    masks.ids = ref_id + kIdPad - kSkew * lane;
+    masks.W = stored ? a.W : 0;
   }
-  if (lane >= lanes) return;                                 // beyond the last word: the rest has no barrier
-  const Id *const my_ids = (kLds ? lds_ids : ref_id) + kIdPad - lane;
-  const uint8_t *const table = reinterpret_cast<const uint8_t *>(lds + lane);
-  const bool takes = strip != 0, gives = strip + 1 < gridDim.x;
-  if (takes && gives) strip_rows<Id, true, true>(a, my_ids, table);
-  else if (takes) strip_rows<Id, true, false>(a, my_ids, table);
-  else if (gives) strip_rows<Id, false, true>(a, my_ids, table);
-  else strip_rows<Id, false, false>(a, my_ids, table);
+  if (many) strip_rows<Id, true>(a, masks, stored);
+  else strip_rows<Id, false>(a, masks, stored);
 }
 
 // ---- the walk back on the GPU ----------------------------------------------------------------------------------
@@ -478,15 +564,15 @@ __device__ __forceinline__ void load_tile(const Id *ref_id, const uint32_t *mask
                                           uint32_t n_steps, RowBlock blk, int w0, uint32_t (*M)[kTileStride],
                                           uint32_t (*X)[kTileStride]) {
   const uint32_t n_rows = blk.hi - blk.lo;
-  for (uint32_t i = threadIdx.x; i < (kWalkRows + kTileWords) * kTileWords; i += blockDim.x) {
-    const uint32_t l = i % kTileWords, t = i / kTileWords;             // row lo + t - l
-    if (t < l || t - l >= n_rows) continue;
-    const uint32_t r = blk.lo + t - l, q = blk.hi - 1 - r;             // q: how far from the block's last row
+  for (uint32_t i = threadIdx.x; i < (kWalkRows + kSkew * kTileWords) * kTileWords; i += blockDim.x) {
+    const uint32_t l = i % kTileWords, t = i / kTileWords, back = kSkew * l;       // row lo + t - back
+    if (t < back || t - back >= n_rows) continue;
+    const uint32_t r = blk.lo + t - back, q = blk.hi - 1 - r;          // q: how far from the block's last row
     const int w = w0 + (int)l;
     uint32_t mm = 0, x = 0;
     if (w >= 0 && (uint32_t)w < W) {
       mm = masks[(size_t)key_of(ref_id[kIdPad + r]) * W + w];
-      x = mm | ~rows[row_word(r, (uint32_t)w, n_steps)];
+      x = mm | ~rows[row_word(r, (uint32_t)w, W, n_steps)];
     }
     M[q][l] = mm;
     X[q][l] = x;
@@ -548,7 +634,7 @@ __device__ uint32_t walk_in_place(const Id *ref_id, const uint32_t *masks, const
     if (w >= 0 && mine_is_row) {
       const uint32_t a = 2 * (uint32_t)w, b = min(a + 1, W - 1);       // an odd last word: its upper half is never reached
       x.M = ((u64)masks[(size_t)id * W + b] << 32) | masks[(size_t)id * W + a];
-      x.V = ((u64)rows[row_word((uint32_t)r, b, n_steps)] << 32) | rows[row_word((uint32_t)r, a, n_steps)];
+      x.V = ((u64)rows[row_word((uint32_t)r, b, W, n_steps)] << 32) | rows[row_word((uint32_t)r, a, W, n_steps)];
     }
     return x;
   };
@@ -667,9 +753,9 @@ __global__ __launch_bounds__(64) void ss_align_pairs_kernel(const Id *__restrict
   if (threadIdx.x < blk.hi - blk.lo) ref_to_cur[blk.hi - 1 - threadIdx.x] = paired[threadIdx.x];
 }
 
-// LDS of the rows kernel with 16-bit ids: mask rows and all ids of the reference
+// LDS of the rows kernel with 16-bit ids: mask rows, ring and all ids of the reference
 size_t lds_need(uint32_t n_keys, uint32_t n) {
-  return (size_t)(n_keys + 1) * kStripWords * 4 + (size_t)id_length(steps_of(n)) * 2;
+  return (size_t)(n_keys + 1) * kStripWords * 4 + kRingBytes + (size_t)id_length(steps_of(n)) * 2;
 }
 
 // the most keys with which it can run
@@ -687,7 +773,7 @@ struct Layout {
 
   Layout(uint32_t n_, uint32_t m_) : n(n_), m(m_) {
     W = (m + 31) / 32;                                     // 32-bit words of a row
-    strips = (W + kStripWords - 1) / kStripWords;
+    strips = strips_of(W);
     n_steps = steps_of(n);
     n_blocks = n_steps / kBlock;
     walk_blocks = (n + kWalkRows - 1) / kWalkRows;
@@ -857,14 +943,14 @@ int ss_align_core(ss_ctx *ctx, const ss_op_t *ref, uint32_t n, const ss_op_t *cu
   uint32_t i = n, j = m;
   while (i > 0 && j > 0) {
     // the rows came over the link: none is in a cache, and the path's next rows lie near the diagonal
-    if (i > kAhead && j > kAhead) __builtin_prefetch(hr + row_word(i - 1 - kAhead, (j - 1 - kAhead) >> 5, y.n_steps));
+    if (i > kAhead && j > kAhead) __builtin_prefetch(hr + row_word(i - 1 - kAhead, (j - 1 - kAhead) >> 5, y.W, y.n_steps));
     const ss_op_t &a = ref[i - 1], &b = cur[j - 1];
     if (a.op_token == b.op_token && a.stack_hash == b.stack_hash && a.sig == b.sig) {
       ref_to_cur[i - 1] = (int32_t)(j - 1);
       ++pairs;
       --i;
       --j;
-    } else if ((hr[row_word(i - 1, (j - 1) >> 5, y.n_steps)] >> ((j - 1) & 31)) & 1u) {
+    } else if ((hr[row_word(i - 1, (j - 1) >> 5, y.W, y.n_steps)] >> ((j - 1) & 31)) & 1u) {
       --j;
     } else {
       --i;

@@ -1,4 +1,4 @@
-"""GPU parity of the sequence aligner where its kernels change form: strips of 2,048 columns, blocks of 32 steps, rows
+"""GPU parity of the sequence aligner where its kernels change form: one strip of 2,048 columns or several of 1,984, blocks of 32 steps, rows
 walked on the host or on the GPU, mask tables in LDS or in device memory, paths that leave the tabulated window.
 The whole pairing is compared exactly with the recurrence in Python integers, which is itself checked against the
 oracle's textbook dynamic programme."""
@@ -55,6 +55,7 @@ def test_the_reference_here_is_the_oracles(P):                    # noqa: F811
 
 @pytest.mark.parametrize("n,m,alpha", [
     (1, 2048, 3), (31, 2049, 5), (33, 2047, 5), (64, 4096, 40), (97, 4097, 7), (400, 6145, 250),     # strip and block edges
+    (30, 1984, 5), (65, 3968, 7), (96, 3969, 300), (1, 5953, 3),
     (8191, 4000, 30), (8193, 4097, 30), (16300, 1900, 12), (16500, 1900, 12),                         # host walk, GPU walk
     (9000, 9001, 254), (9000, 9001, 255), (9000, 9001, 256), (9000, 9001, 3000),                      # LDS masks, masks in memory
     (65536, 600, 200), (700, 40000, 60), (40000, 700, 60),                                            # ids beyond LDS, steep and flat
