@@ -280,8 +280,9 @@ __global__ __launch_bounds__(256) void ss_anchor_kernel(AnchorArgs g) {
 // ---- many anchors: the distinct keys first ------------------------------------------------------------------------
 //
 // 8,001 anchors over 18,464 + 18,467 operators: comparing every anchor with every operator is bound by the issue of 300
-// million compares (186 us).  With some forty distinct keys the three launches below take 22 us for the lists (bound by
-// the passes of a workgroup over both sequences, one of them twice), 10 for the keys and 7 for the anchors.
+// million compares (186 us).  With some forty distinct keys the three launches below take 4 us for the keys (20 with
+// every anchor at the table), 17 for the lists (bound by the turns of a workgroup over both sequences; 22 with one sequence
+// after the other and cur twice; loading a turn ahead gains nothing) and 7 for the anchors.
 
 // Per level: an open-addressing table of at least 2k slots holding 1 + the anchor that stands for a key, the slots in
 // use, and for each of them where its places in the current sequence are listed and how many there are.
@@ -302,36 +303,68 @@ __device__ __forceinline__ bool same_at(const ss_op_t &x, const ss_op_t &y, int 
   return x.op_token == y.op_token && (L == 2 || x.sig == y.sig) && (L != 0 || x.stack_hash == y.stack_hash);
 }
 
-// workgroup (x, L): the anchors' keys of level L
+// workgroup (x, L): the anchors' keys of level L.  They are few, and every anchor would go for the same few slots: the
+// first of each key within the workgroup (found through a table in LDS) goes, the others take over its slot.
 __global__ __launch_bounds__(256) void ss_keys_kernel(AnchorArgs g, KeyLists q) {
+  constexpr uint32_t kSlots = 512, kShift = 64 - 9;
+  __shared__ uint32_t first[kSlots], slot_of[kSlots];
+  __shared__ ss_op_t ops[256];
   const uint32_t a = blockIdx.x * 256 + threadIdx.x;
   const int L = blockIdx.y;
-  if (a >= g.k) return;
-  const uint32_t i = g.anchors[a].ref_op;
-  if (i >= g.n) return;
-  const ss_op_t R = g.ref[i];
-  if (R.op_token == 0) return;
+  ss_op_t R = {0, 0, 0, 0};
+  if (a < g.k) {
+    const uint32_t i = g.anchors[a].ref_op;
+    if (i < g.n) R = g.ref[i];
+  }
+  const bool live = R.op_token != 0;
+  ops[threadIdx.x] = R;
+  for (uint32_t i = threadIdx.x; i < kSlots; i += 256) first[i] = 0;
+  __syncthreads();
   unsigned long long x = R.op_token;
   if (L < 2) x |= (unsigned long long)R.sig << 32;
   if (L < 1) x ^= (unsigned long long)R.stack_hash << 18;
-  uint32_t h = (uint32_t)((x * 0x9E3779B97F4A7C15ull) >> q.shift);
-  for (uint32_t probe = 0; probe <= q.mask; ++probe) {         // at most k keys in more than 2k slots
-    uint32_t seen = __hip_atomic_load(q.rep[L] + h, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  x *= 0x9E3779B97F4A7C15ull;
+  uint32_t l = (uint32_t)(x >> kShift);
+  bool goes = false;
+  for (uint32_t probe = 0; live && probe < kSlots; ++probe) {  // at most 256 keys in 512 slots
+    uint32_t seen = *(volatile uint32_t *)(first + l);
     if (!seen) {
-      seen = atomicCAS(q.rep[L] + h, 0u, a + 1);
-      if (!seen) {
-        q.used[L][atomicAdd(q.n_used + L, 1u)] = h;
-        break;
-      }
+      seen = atomicCAS(first + l, 0u, threadIdx.x + 1);
+      if (!seen) { goes = true; break; }
     }
-    if (same_at(g.ref[g.anchors[seen - 1].ref_op], R, L)) break;
-    h = (h + 1) & q.mask;
+    if (same_at(ops[seen - 1], R, L)) break;
+    l = (l + 1) % kSlots;
   }
-  q.key_of[L][a] = h;
+  if (goes) {
+    uint32_t h = (uint32_t)(x >> q.shift);
+    for (uint32_t probe = 0; probe <= q.mask; ++probe) {       // at most k keys in more than 2k slots
+      uint32_t seen = __hip_atomic_load(q.rep[L] + h, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      if (!seen) {
+        seen = atomicCAS(q.rep[L] + h, 0u, a + 1);
+        if (!seen) {
+          q.used[L][atomicAdd(q.n_used + L, 1u)] = h;
+          break;
+        }
+      }
+      if (same_at(g.ref[g.anchors[seen - 1].ref_op], R, L)) break;
+      h = (h + 1) & q.mask;
+    }
+    slot_of[l] = h;
+  }
+  __syncthreads();
+  if (live) q.key_of[L][a] = slot_of[l];
 }
 
+constexpr uint32_t kHitWords = 4096;                   // groups of 64 operators of cur whose hits are kept in LDS
+
+// One workgroup per key: ordinals of its occurrences in ref, and the list of those in cur.  Both sequences are gone through
+// together, a wavefront taking 256 consecutive operators of each a turn, all loads in flight, one barrier a turn (the
+// counts alternate between two sets).  The list's place is known only after that, so the hits in cur are kept and
+// the list is written from them, where cur has more than kHitWords * 64 operators by going through it again.
 __global__ __launch_bounds__(1024) void ss_lists_kernel(AnchorArgs g, KeyLists q) {
-  __shared__ uint32_t wave_cnt[2][16], s_start;
+  constexpr uint32_t kTurn = 4096;
+  __shared__ uint32_t wave_cnt[2][2][16], s_start, at[kHitWords];
+  __shared__ uint64_t hits[kHitWords];
   const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
   const uint64_t below = lane ? (~0ull >> (64 - lane)) : 0ull;
   const uint32_t n0 = q.n_used[0], n1 = q.n_used[1], n2 = q.n_used[2];
@@ -340,54 +373,88 @@ __global__ __launch_bounds__(1024) void ss_lists_kernel(AnchorArgs g, KeyLists q
     const int L = it < n0 ? 0 : it < n0 + n1 ? 1 : 2;
     const uint32_t h = q.used[L][it - (L == 0 ? 0 : L == 1 ? n0 : n0 + n1)];
     const ss_op_t R = g.ref[g.anchors[q.rep[L][h] - 1].ref_op];
-    // every occurrence in seq, in order: put(position, ordinal); returns how many there are.  A wavefront takes 256
-    // consecutive operators a pass, four loads in flight; one barrier a pass (the counts alternate between two sets).
-    auto each = [&](const ss_op_t *seq, uint32_t len, auto put) -> uint32_t {
-      uint32_t seen = 0;
-      int set = 0;
-      for (uint32_t base = 0; base < len; base += 4096, set ^= 1) {
-        const uint32_t j0 = base + w * 256 + lane;
-        ss_op_t o[4];
+    struct Turn { uint64_t hit[4]; uint32_t ord, all; };
+    auto load = [&](const ss_op_t *seq, uint32_t len, uint32_t j0, ss_op_t *o) {
 #pragma unroll
-        for (int u = 0; u < 4; ++u) {
-          o[u].op_token = 0;
-          if (j0 + 64 * u < len) o[u] = seq[j0 + 64 * u];
-        }
-        uint64_t hit[4];
-        uint32_t mine = 0;
-#pragma unroll
-        for (int u = 0; u < 4; ++u) {
-          hit[u] = __ballot(same_at(o[u], R, L));
-          mine += __popcll(hit[u]);
-        }
-        if (lane == 0) wave_cnt[set][w] = mine;
-        __syncthreads();
-        uint32_t ord = seen, all = 0;
-        for (int v = 0; v < 16; ++v) {
-          const uint32_t x = wave_cnt[set][v];
-          if (v < w) ord += x;
-          all += x;
-        }
-#pragma unroll
-        for (int u = 0; u < 4; ++u) {
-          if ((hit[u] >> lane) & 1ull) put(j0 + 64 * u, ord + (uint32_t)__popcll(hit[u] & below));
-          ord += __popcll(hit[u]);
-        }
-        seen += all;
+      for (int u = 0; u < 4; ++u) {
+        o[u].op_token = 0;
+        if (j0 + 64 * u < len) o[u] = seq[j0 + 64 * u];
       }
-      __syncthreads();
-      return seen;
     };
-    each(g.ref, g.n, [&](uint32_t j, uint32_t ord) { q.rank[L][j] = ord; });
-    const uint32_t cnt = each(g.cur, g.m, [](uint32_t, uint32_t) {});
+    auto test = [&](const ss_op_t *o, Turn &t, uint32_t *cnt) {
+      uint32_t mine = 0;
+#pragma unroll
+      for (int u = 0; u < 4; ++u) {
+        t.hit[u] = __ballot(same_at(o[u], R, L));
+        mine += __popcll(t.hit[u]);
+      }
+      if (lane == 0) cnt[w] = mine;
+    };
+    auto count = [&](Turn &t, const uint32_t *cnt) {           // hits before this wavefront's, and of all of them
+      t.ord = t.all = 0;
+      for (int v = 0; v < 16; ++v) {
+        const uint32_t x = cnt[v];
+        if (v < w) t.ord += x;
+        t.all += x;
+      }
+    };
+    uint32_t seen_r = 0, seen_c = 0;
+    int set = 0;
+    for (uint32_t base = 0; base < max(g.n, g.m); base += kTurn, set ^= 1) {
+      const uint32_t j0 = base + w * 256 + lane;
+      ss_op_t r[4], c[4];
+      load(g.ref, g.n, j0, r);
+      load(g.cur, g.m, j0, c);
+      Turn tr, tc;
+      test(r, tr, wave_cnt[set][0]);
+      test(c, tc, wave_cnt[set][1]);
+      __syncthreads();
+      count(tr, wave_cnt[set][0]);
+      count(tc, wave_cnt[set][1]);
+      uint32_t ord_r = seen_r + tr.ord, ord_c = seen_c + tc.ord;
+#pragma unroll
+      for (int u = 0; u < 4; ++u) {
+        if ((tr.hit[u] >> lane) & 1ull) q.rank[L][j0 + 64 * u] = ord_r + (uint32_t)__popcll(tr.hit[u] & below);
+        const uint32_t word = base / 64 + w * 4 + u;
+        if (lane == 0 && word < kHitWords) { hits[word] = tc.hit[u]; at[word] = ord_c; }
+        ord_r += __popcll(tr.hit[u]);
+        ord_c += __popcll(tc.hit[u]);
+      }
+      seen_r += tr.all;
+      seen_c += tc.all;
+    }
     if (threadIdx.x == 0) {
-      s_start = atomicAdd(q.n_used + 3 + L, cnt);            // the keys of a level share no place: m entries suffice
+      s_start = atomicAdd(q.n_used + 3 + L, seen_c);         // the keys of a level share no place: m entries suffice
       q.start[L][h] = s_start;
-      q.count[L][h] = cnt;
+      q.count[L][h] = seen_c;
     }
     __syncthreads();
     uint32_t *const out = q.place[L] + s_start;
-    each(g.cur, g.m, [&](uint32_t j, uint32_t ord) { out[ord] = j; });
+    const uint32_t words = min((g.m + 63) / 64, kHitWords);
+    for (uint32_t word = w; word < words; word += 16) {
+      const uint64_t hit = hits[word];
+      if ((hit >> lane) & 1ull) out[at[word] + (uint32_t)__popcll(hit & below)] = word * 64 + lane;
+    }
+    if (g.m > kHitWords * 64) {
+      uint32_t seen = at[kHitWords - 1] + (uint32_t)__popcll(hits[kHitWords - 1]);
+      for (uint32_t base = kHitWords * 64; base < g.m; base += kTurn, set ^= 1) {
+        const uint32_t j0 = base + w * 256 + lane;
+        ss_op_t c[4];
+        load(g.cur, g.m, j0, c);
+        Turn t;
+        test(c, t, wave_cnt[set][0]);
+        __syncthreads();
+        count(t, wave_cnt[set][0]);
+        uint32_t ord = seen + t.ord;
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+          if ((t.hit[u] >> lane) & 1ull) out[ord + (uint32_t)__popcll(t.hit[u] & below)] = j0 + 64 * u;
+          ord += __popcll(t.hit[u]);
+        }
+        seen += t.all;
+      }
+    }
+    __syncthreads();                                         // the next key's counts and hits
   }
 }
 
@@ -554,7 +621,7 @@ extern "C" int ss_match_sequence(ss_ctx *ctx, const ss_op_t *ref, uint32_t n, co
     // nothing that large is kept pinned.
     const bool mapped = in_bytes <= (4u << 20);
     const uint64_t pairs = (uint64_t)k * ((uint64_t)n + m);
-    const bool listed = search && pairs > (1ull << 24);        // 12 us of comparing; the lists take 25 us
+    const bool listed = search && pairs > (1ull << 24);        // 10 us of comparing; the lists take 20 us
     const uint32_t len = n > m ? n : m, wgs = std::min(256u, std::max(1u, (len + 255) / 256));
     const uint32_t out_wgs = (k + 255) / 256;
     // table of the injectivity pass: a power of two of at least 2k slots
