@@ -530,13 +530,14 @@ __global__ __launch_bounds__(64) void ss_align_rows_kernel(const Id *__restrict_
 //
 // The walk is one chain of n rows, but what 64 rows do to it is a function of one number: how many columns are left
 // when it enters them.  So that function is tabulated for every block of 64 rows at once, one thread per entry
-// column of a window around the diagonal (ss_align_tab_kernel); one workgroup then follows the blocks' tables from
-// the end (ss_align_chain_kernel), and with every block's entry known the blocks are walked again side by side to
-// write the pairs (ss_align_pairs_kernel).  A block whose entry lies outside its window, or whose path leaves the tile
-// to the left, is walked in place by a wavefront of the chain.
-// 32,312 rows: 62 us for the tables, 90 us for the chain (an LDS read and its way through the scalar unit per block; with
-// the window's start read from LDS too 145), 24 us for the pairs; single
-// steps in one wavefront took 97 ns a row (3.1 ms), the rows over the host link (130 MB) 2.3 ms and a walk there.
+// column of a window around the diagonal (ss_align_tab_kernel), and eight blocks' tables are put together to one
+// (ss_align_compose_kernel); one workgroup then follows these from the end (ss_align_chain_kernel), and with every
+// group's entry known the blocks are walked again side by side to write the pairs (ss_align_pairs_kernel).  Where a group's
+// table has no entry the chain follows its blocks' own, and a block whose entry lies outside its window, or whose path
+// leaves the tile to the left, is walked in place by a wavefront of the chain.
+// 32,312 rows: 64 us for the tables, 5 us for the groups' and 17 us for the chain (an LDS read and its way through the
+// scalar unit per group; 90 us block by block), 30 us for the pairs; single steps in one wavefront took 97 ns a row (3.1
+// ms), the rows over the host link (130 MB) 2.3 ms and a walk there.
 constexpr uint32_t kWalkRows = 64;
 constexpr uint32_t kWindow = 2048;                     // entry columns tabulated per block of rows
 constexpr uint32_t kEntries = 256;                     // of these, per workgroup
@@ -674,59 +675,88 @@ __device__ uint32_t walk_in_place(const Id *ref_id, const uint32_t *masks, const
   return w < 0 ? 0 : (uint32_t)(64 * w + p + 1);
 }
 
-constexpr uint32_t kChainBlocks = 16;                  // tables in LDS at a time
+constexpr uint32_t kGroupBlocks = 8;                   // blocks whose tables are put together
+constexpr uint32_t kChainGroups = 16;                  // tables in LDS at a time
 constexpr uint32_t kChainThreads = 256;
 
-// entry[k]: columns left when the walk enters block k, or -1 if the block has been walked here
+// columns that block k takes off j, or kNoEntry
+__device__ __forceinline__ uint32_t taken(const uint16_t *table, uint32_t k, uint32_t n, uint32_t m, uint32_t j) {
+  const uint32_t at = j - window_start(k, n, m);             // before the window: wraps to a large number
+  return at < kWindow ? table[(size_t)k * kWindow + at] : kNoEntry;
+}
+
+// the table of a group of blocks, for the window of its first: at most 8 * (kEntries + kMargin) columns
+__global__ __launch_bounds__(256) void ss_align_compose_kernel(const uint16_t *__restrict__ table, uint32_t n, uint32_t m,
+                                                               uint32_t K, uint16_t *__restrict__ groups) {
+  const uint32_t k0 = blockIdx.x * kGroupBlocks, i = blockIdx.y * 256 + threadIdx.x, entry = window_start(k0, n, m) + i;
+  uint32_t j = entry;
+  bool known = j <= m;
+  for (uint32_t k = k0; known && k < min(k0 + kGroupBlocks, K); ++k) {
+    const uint32_t d = taken(table, k, n, m, j);
+    known = d != kNoEntry;
+    if (known) j -= d;
+  }
+  groups[(size_t)blockIdx.x * kWindow + i] = known ? (uint16_t)(entry - j) : kNoEntry;
+}
+
+// group_entry[g]: columns left when the walk enters group g, or -1 if its blocks have been followed one by one here;
+// then entry[k] is that of block k, or -1 if the block has been walked here
 template <class Id>
 __global__ __launch_bounds__(kChainThreads) void ss_align_chain_kernel(const Id *__restrict__ ref_id, uint32_t n,
                                                                        const uint32_t *__restrict__ masks, uint32_t m,
                                                                        uint32_t W, uint32_t n_steps,
                                                                        const uint32_t *__restrict__ rows,
                                                                        const uint16_t *__restrict__ table,
+                                                                       const uint16_t *__restrict__ groups,
                                                                        int32_t *__restrict__ entry,
+                                                                       int32_t *__restrict__ group_entry,
                                                                        int32_t *__restrict__ ref_to_cur) {
-  __shared__ uint4 tabs[kChainBlocks * kWindow / 8];
-  constexpr uint32_t kPer = kChainBlocks * kWindow / 8 / kChainThreads;
-  const uint32_t K = (n + kWalkRows - 1) / kWalkRows;
-  const uint4 *src = reinterpret_cast<const uint4 *>(table);
-  const size_t total = (size_t)K * kWindow / 8;
+  __shared__ uint4 tabs[kChainGroups * kWindow / 8];
+  constexpr uint32_t kPer = kChainGroups * kWindow / 8 / kChainThreads;
+  const uint32_t K = (n + kWalkRows - 1) / kWalkRows, G = (K + kGroupBlocks - 1) / kGroupBlocks;
+  const uint4 *src = reinterpret_cast<const uint4 *>(groups);
+  const size_t total = (size_t)G * kWindow / 8;
   uint4 next[kPer];
-  auto fetch = [&](uint32_t k0) {
+  auto fetch = [&](uint32_t g0) {
 #pragma unroll
     for (uint32_t i = 0; i < kPer; ++i) {
-      const size_t at = (size_t)k0 * kWindow / 8 + i * kChainThreads + threadIdx.x;
+      const size_t at = (size_t)g0 * kWindow / 8 + i * kChainThreads + threadIdx.x;
       next[i] = at < total ? src[at] : uint4{0, 0, 0, 0};
     }
   };
   fetch(0);
   uint32_t j = m;                                            // wavefront 0's own
-  for (uint32_t k0 = 0; k0 < K; k0 += kChainBlocks) {
+  for (uint32_t g0 = 0; g0 < G; g0 += kChainGroups) {
 #pragma unroll
     for (uint32_t i = 0; i < kPer; ++i) tabs[i * kChainThreads + threadIdx.x] = next[i];
     __syncthreads();
-    fetch(k0 + kChainBlocks);
+    fetch(g0 + kChainGroups);
     if (threadIdx.x < 64) {
       const uint16_t *t = reinterpret_cast<const uint16_t *>(tabs);
-      const uint32_t mine = min(k0 + (threadIdx.x & (kChainBlocks - 1)), K - 1);
-      const uint32_t starts = window_start(mine, n, m);      // lane u: block k0 + u's
+      const uint32_t mine = min(g0 + (threadIdx.x & (kChainGroups - 1)), G - 1);
+      const uint32_t starts = window_start(mine * kGroupBlocks, n, m);      // lane u: group g0 + u's
       int32_t entries = 0;                                   // likewise
-#pragma unroll
-      for (uint32_t u = 0; u < kChainBlocks; ++u) {
-        const uint32_t k = k0 + u;
-        if (k < K) {
-          const uint32_t at = j - (uint32_t)__builtin_amdgcn_readlane((int)starts, u);       // before the window: wraps to a large number
-          const uint32_t d = at < kWindow ? __builtin_amdgcn_readfirstlane((uint32_t)t[u * kWindow + at]) : kNoEntry;
-          if (threadIdx.x == u) entries = d != kNoEntry ? (int32_t)j : -1;
-          if (__builtin_expect(d != kNoEntry, 1)) {
-            j -= d;
-          } else {
+#pragma unroll 1
+      for (uint32_t u = 0; u < kChainGroups && g0 + u < G; ++u) {
+        const uint32_t at = j - (uint32_t)__builtin_amdgcn_readlane((int)starts, u);       // before the window: wraps to a large number
+        const uint32_t d = at < kWindow ? __builtin_amdgcn_readfirstlane((uint32_t)t[u * kWindow + at]) : kNoEntry;
+        if (threadIdx.x == u) entries = d != kNoEntry ? (int32_t)j : -1;
+        if (__builtin_expect(d != kNoEntry, 1)) {
+          j -= d;
+          continue;
+        }
+        const uint32_t k0 = (g0 + u) * kGroupBlocks;
+        for (uint32_t k = k0; k < min(k0 + kGroupBlocks, K); ++k) {
+          const uint32_t e = __builtin_amdgcn_readfirstlane(taken(table, k, n, m, j));
+          if (threadIdx.x == 0) entry[k] = e != kNoEntry ? (int32_t)j : -1;
+          if (e != kNoEntry)
+            j -= e;
+          else
             j = __builtin_amdgcn_readfirstlane(
                 walk_in_place(ref_id, masks, rows, W, n_steps, RowBlock(k, n), j, ref_to_cur));
-          }
         }
       }
-      if (threadIdx.x < kChainBlocks && k0 + threadIdx.x < K) entry[k0 + threadIdx.x] = entries;
+      if (threadIdx.x < kChainGroups && g0 + threadIdx.x < G) group_entry[g0 + threadIdx.x] = entries;
     }
     __syncthreads();
   }
@@ -734,14 +764,21 @@ __global__ __launch_bounds__(kChainThreads) void ss_align_chain_kernel(const Id 
 
 template <class Id>
 __global__ __launch_bounds__(64) void ss_align_pairs_kernel(const Id *__restrict__ ref_id, uint32_t n,
-                                                            const uint32_t *__restrict__ masks, uint32_t W,
+                                                            const uint32_t *__restrict__ masks, uint32_t m, uint32_t W,
                                                             uint32_t n_steps, const uint32_t *__restrict__ rows,
+                                                            const uint16_t *__restrict__ table,
                                                             const int32_t *__restrict__ entry,
+                                                            const int32_t *__restrict__ group_entry,
                                                             int32_t *__restrict__ ref_to_cur) {
   __shared__ uint32_t M[kWalkRows][kTileStride], X[kWalkRows][kTileStride];
   __shared__ int32_t paired[kWalkRows];
-  const uint32_t k = blockIdx.x;
-  const int j = entry[k];
+  const uint32_t k = blockIdx.x, k0 = k / kGroupBlocks * kGroupBlocks;
+  int j = group_entry[k / kGroupBlocks];
+  if (j >= 0) {
+    for (uint32_t b = k0; b < k; ++b) j -= (int)taken(table, b, n, m, (uint32_t)j);       // known: the group's table is
+  } else {
+    j = entry[k];
+  }
   if (j < 0) return;
   const RowBlock blk(k, n);
   const int w0 = j / (int)kEntries * (int)(kEntries / 32) - (int)(kMargin / 32);     // the tile the table came from
@@ -767,8 +804,8 @@ uint32_t most_few(uint32_t n) {
 // Where everything lies.  `d` device scratch, `h` pinned scratch.
 struct Layout {
   size_t h_ref, h_cur, h_flag, h_n_keys, h_out, h_end;
-  size_t ref, cur, ref_id, cur_id, n_keys, rep, id, slot, carry, rows, pair, table, entry, masks, end;
-  uint32_t n, m, W, strips, n_steps, n_blocks, walk_blocks, slots, bits;
+  size_t ref, cur, ref_id, cur_id, n_keys, rep, id, slot, carry, rows, pair, table, entry, groups, group_entry, masks, end;
+  uint32_t n, m, W, strips, n_steps, n_blocks, walk_blocks, walk_groups, slots, bits;
   bool one_wg, short_rows;
 
   Layout(uint32_t n_, uint32_t m_) : n(n_), m(m_) {
@@ -777,6 +814,7 @@ struct Layout {
     n_steps = steps_of(n);
     n_blocks = n_steps / kBlock;
     walk_blocks = (n + kWalkRows - 1) / kWalkRows;
+    walk_groups = (walk_blocks + kGroupBlocks - 1) / kGroupBlocks;
     const size_t row_bytes = (size_t)strips * n_steps * kStripWords * 4;
     one_wg = n + m <= kWgOps;
     // the kernel writes the rows to pinned host memory and the host walks them; else they stay in device memory and
@@ -806,6 +844,8 @@ struct Layout {
     pair = take(short_rows ? 0 : (size_t)n * 4);
     table = take(short_rows ? 0 : (size_t)walk_blocks * kWindow * 2);
     entry = take(short_rows ? 0 : (size_t)walk_blocks * 4);
+    groups = take(short_rows ? 0 : (size_t)walk_groups * kWindow * 2);
+    group_entry = take(short_rows ? 0 : (size_t)walk_groups * 4);
     carry = take((size_t)(strips - 1) * (n_blocks + kCarryPad) * 8);
     masks = o;                                             // last: its size needs the number of keys
     end = o;
@@ -832,14 +872,16 @@ int launch_rows(ss_ctx *ctx, const Layout &y, uint8_t *d, uint8_t *hd, uint32_t 
                      y.m, args, n_keys);
   if (!y.short_rows) {
     const uint32_t *cmasks = masks, *crows = rows;
-    uint16_t *table = (uint16_t *)(d + y.table);
-    int32_t *entry = (int32_t *)(d + y.entry), *pair = (int32_t *)(d + y.pair);
+    uint16_t *table = (uint16_t *)(d + y.table), *groups = (uint16_t *)(d + y.groups);
+    int32_t *entry = (int32_t *)(d + y.entry), *group_entry = (int32_t *)(d + y.group_entry), *pair = (int32_t *)(d + y.pair);
     hipLaunchKernelGGL(ss_align_tab_kernel<Id>, dim3(y.walk_blocks, kWindow / kEntries), dim3(kEntries), 0, s, ref_id, y.n,
                        cmasks, y.m, y.W, y.n_steps, crows, table);
+    hipLaunchKernelGGL(ss_align_compose_kernel, dim3(y.walk_groups, kWindow / 256), dim3(256), 0, s, table, y.n, y.m,
+                       y.walk_blocks, groups);
     hipLaunchKernelGGL(ss_align_chain_kernel<Id>, dim3(1), dim3(kChainThreads), 0, s, ref_id, y.n, cmasks, y.m, y.W,
-                       y.n_steps, crows, (const uint16_t *)table, entry, pair);
-    hipLaunchKernelGGL(ss_align_pairs_kernel<Id>, dim3(y.walk_blocks), dim3(64), 0, s, ref_id, y.n, cmasks, y.W, y.n_steps,
-                       crows, (const int32_t *)entry, pair);
+                       y.n_steps, crows, table, groups, entry, group_entry, pair);
+    hipLaunchKernelGGL(ss_align_pairs_kernel<Id>, dim3(y.walk_blocks), dim3(64), 0, s, ref_id, y.n, cmasks, y.m, y.W, y.n_steps,
+                       crows, table, entry, group_entry, pair);
     SS_HIP(hipGetLastError());
     SS_HIP(hipMemcpyAsync((uint8_t *)ctx->h_scratch + y.h_out, pair, (size_t)y.n * 4, hipMemcpyDeviceToHost, s));
   }

@@ -58,6 +58,7 @@ def test_the_reference_here_is_the_oracles(P):                    # noqa: F811
     (30, 1984, 5), (65, 3968, 7), (96, 3969, 300), (1, 5953, 3),
     (8191, 4000, 30), (8193, 4097, 30), (16300, 1900, 12), (16500, 1900, 12),                         # host walk, GPU walk
     (9000, 9001, 254), (9000, 9001, 255), (9000, 9001, 256), (9000, 9001, 3000),                      # LDS masks, masks in memory
+    (8704, 9000, 40), (8705, 9000, 40),                                                               # groups of blocks walked back
     (65536, 600, 200), (700, 40000, 60), (40000, 700, 60),                                            # ids beyond LDS, steep and flat
 ])
 def test_random_and_perturbed_at_the_edges(P, ctx, n, m, alpha):  # noqa: F811
