@@ -18,7 +18,7 @@
 // Bound by latency: barriers and dependent loads in a short trace (124 + 24 events, 66 operators: 6.3 us in one
 // workgroup; with sums gathered by atomics, fences and running values in device memory 31 us), launches and one pass
 // each over the events in a long one (100,000 + 40,000 events with a timeline: 4.0 + 8.8 + 4.1 us; with operators
-// and timeline left to one workgroup 1,084 us; 1,048,574 + 20,014 events, 65,536 operators: 58 us, was 221).
+// and timeline left to one workgroup 1,084 us; 1,048,574 + 20,014 events, 65,536 operators: 46 us, was 221).
 #include <algorithm>
 #include <cstring>
 
@@ -47,7 +47,7 @@ struct ScanArgs {
   TileSum *tiles;     // [tiles of both lists]
   Best *best;         // [blocks of operators]
   uint32_t *ctl;      // [0] operator blocks done, [1] flags
-  uint64_t tile;      // events per tile
+  uint32_t tile[2];   // events per tile of ev, of pev
   uint32_t tiles0, tiles1;
   // the tile sums read the events from here, if given, and copy them to ev / pev (without the tensor ids, which no
   // kernel looks at)
@@ -162,9 +162,11 @@ __device__ __forceinline__ void put_event(const ScanArgs &a, bool policy, bool p
 }
 
 // OpAt entries of operators (prev, op] take the values before the event that starts op.  A lane fills a short gap by
-// itself; the wavefront fills a long one together.
+// itself; the wavefront fills a long one (more than kAlone operators) together, about 0.1 us for each.  A workgroup that
+// does the whole scan has few long gaps in a wavefront: 4.  A tile may have many: 16 (the running sums of 20,014 events
+// over 65,536 operators 30 us, with 4 37).
+template <uint32_t kAlone>
 __device__ __forceinline__ void fill_gap(OpAt *at, bool has, uint32_t from, uint32_t to, const OpAt &x) {
-  constexpr uint32_t kAlone = 4;
   const uint32_t len = has ? to - from : 0;
   if (len && len <= kAlone)
     for (uint32_t t = from; t < to; ++t) at[t] = x;
@@ -286,12 +288,13 @@ __device__ __forceinline__ uint32_t load_events(const ss_event_t *L0, uint64_t n
 
 // OpAt entries that this element decides: those of the operators after the previous event's up to its own, and after
 // the list's last event those up to n_ops.
+template <uint32_t kAlone = 4>
 __device__ __forceinline__ void fill_from(OpAt *at, const Elem &y, uint32_t e, int64_t sp, int64_t sn, uint32_t cp,
                                           uint32_t n_ops) {
   const bool ok = y.live && y.op < n_ops && y.prev <= y.op;
-  fill_gap(at, ok && (y.first || y.prev != y.op), y.first ? 0 : y.prev + 1, y.op + 1, OpAt{sp, sn, e, cp});
+  fill_gap<kAlone>(at, ok && (y.first || y.prev != y.op), y.first ? 0 : y.prev + 1, y.op + 1, OpAt{sp, sn, e, cp});
   if (__ballot(ok && y.last))
-    fill_gap(at, ok && y.last, y.op + 1, n_ops + 1,
+    fill_gap<kAlone>(at, ok && y.last, y.op + 1, n_ops + 1,
              OpAt{sp + (y.pos ? y.delta : 0), sn + (y.pos ? 0 : y.delta), e + 1, cp + (y.pos ? 1 : 0)});
 }
 
@@ -498,8 +501,8 @@ struct Tile {
     src = policy ? a.src_pev : a.src_ev;
     cnt = policy ? a.n_pe : a.n_ev;
     out0 = policy ? a.n_ev : 0;
-    lo = (uint64_t)(index - first) * a.tile;
-    hi = lo + a.tile < cnt ? lo + a.tile : cnt;
+    lo = (uint64_t)(index - first) * a.tile[policy];
+    hi = lo + a.tile[policy] < cnt ? lo + a.tile[policy] : cnt;
   }
 };
 
@@ -588,7 +591,7 @@ __global__ __launch_bounds__(kTileThreads) void ss_scan_running_kernel(ScanArgs 
         a.sumx[tl.out0 + e] = (pos[k] ? xsp[k] : xsn[k]) + delta[k];
         a.cntx[tl.out0 + e] = pos[k] ? xcp[k] : (uint32_t)e - xcp[k];
       }
-      fill_from(at, x[k], (uint32_t)e, xsp[k], xsn[k], xcp[k], a.n_ops);
+      fill_from<16>(at, x[k], (uint32_t)e, xsp[k], xsn[k], xcp[k], a.n_ops);
     }
     __syncthreads();                                         // sh is written again in the next pass
   }
@@ -646,8 +649,14 @@ __global__ __launch_bounds__(kThreads) void ss_scan_finish_kernel(ScanArgs a, ui
 
 constexpr uint32_t kMaxOpWgs = 256;
 
-uint64_t tile_events(uint64_t n_ev, uint64_t n_pe) {
-  return std::max(kTileEvents, ss_align_up((std::max(n_ev, n_pe) + kMaxTiles - 1) / kMaxTiles, kTileEvents));
+// Events of a tile: as many as a workgroup takes in a pass, or more to stay within kMaxTiles (256 to a tile and so eight
+// times as many sums for every workgroup to read: the running sums of 140,000 events 13.9 us against 9.1).  But where
+// operators outnumber the events, filling the gaps between them is the work (a wavefront fills gaps above kAlone one
+// after the other), and few events to a tile spread it: 60,000 operators with 40,000 events and 2,000 of the policy
+// 82 -> 40 us, with 6,000 and 200 66 -> 41.
+uint32_t tile_events(uint64_t n, uint32_t n_ops) {
+  if (n_ops > 2 * n) return (uint32_t)std::max<uint64_t>(8, ss_align_up((n + 255) / 256, 8));
+  return (uint32_t)std::max(kTileEvents, ss_align_up((n + kMaxTiles - 1) / kMaxTiles, kTileEvents));
 }
 
 bool is_short(uint64_t n_ev, uint64_t n_pe, uint32_t n_ops) { return n_ev + n_pe <= kSmallEvents && n_ops <= kLdsOps; }
@@ -686,9 +695,10 @@ void launch_scan(hipStream_t s, ScanArgs &a) {
       hipLaunchKernelGGL(ss_scan_small_kernel<kThreads>, dim3(1), dim3(kThreads), lds_at(a.n_ops), s, a);
     return;
   }
-  a.tile = tile_events(a.n_ev, a.n_pe);
-  a.tiles0 = (uint32_t)std::max<uint64_t>(1, (a.n_ev + a.tile - 1) / a.tile);
-  a.tiles1 = (uint32_t)std::max<uint64_t>(1, (a.n_pe + a.tile - 1) / a.tile);
+  a.tile[0] = tile_events(a.n_ev, a.n_ops);
+  a.tile[1] = tile_events(a.n_pe, a.n_ops);
+  a.tiles0 = (uint32_t)std::max<uint64_t>(1, (a.n_ev + a.tile[0] - 1) / a.tile[0]);
+  a.tiles1 = (uint32_t)std::max<uint64_t>(1, (a.n_pe + a.tile[1] - 1) / a.tile[1]);
   const uint32_t tiles = a.tiles0 + a.tiles1;
   const uint32_t op_wgs = (uint32_t)std::min<uint64_t>(kMaxOpWgs, std::max<uint64_t>(1, ((uint64_t)a.n_ops + kThreads - 1) / kThreads));
   const uint32_t ev_wgs = a.want_timeline ? (uint32_t)std::min<uint64_t>(2048, (a.n_ev + a.n_pe + kThreads - 1) / kThreads) : 0;

@@ -41,6 +41,7 @@ def both_ways(P, ctx, ev, pe, n_ops, base, budget):               # noqa: F811
     (255, 257, 2900), (255, 257, 2901),                                                      # LDS tables | device tables
     (4096, 0, 700), (4000, 97, 700), (0, 4097, 700), (2048, 2049, 3000),                     # one launch | three
     (2047, 3000, 40), (6144, 2048, 9000), (40, 7, 60001), (30000, 20000, 1),
+    (3000, 2050, 6000), (3000, 2050, 6001), (2049, 2048, 40000), (20000, 3, 65536),          # small tiles where gaps are wide
 ])
 def test_edges_of_the_forms(P, ctx, n_ev, n_pe, n_ops):           # noqa: F811
     rng = np.random.default_rng([n_ev, n_pe, n_ops])
