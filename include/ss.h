@@ -48,8 +48,7 @@ enum {
   SS_E_STATE = -8,      /* call out of sequence (e.g. swap before a schedule is loaded) */
   SS_E_CAPACITY = -9,   /* a caller-provided output array or a configured maximum is too small */
   SS_E_TIMEOUT = -10    /* SS_CFG_BARE_RING: a stream gave up waiting for a ring transfer (flag_wait_ms); the
-                           bytes moved in this iteration are not to be trusted.  ss_align_sequence: a part of the
-                           kernel gave up waiting for another (seconds; no result) */
+                           bytes moved in this iteration are not to be trusted */
 };
 
 /* ---- records (all little-endian, naturally aligned, no padding) ---------- */

@@ -39,7 +39,6 @@ constexpr uint32_t kIdPad = 64 * kSkew;                // entries before the fir
 // link nothing up to about 13 GB/s, and the walk on the GPU takes four more launches and two copies.
 constexpr size_t kHostRowBytes = 4u << 20;
 constexpr uint32_t kCarryPad = 8;                      // carry words a strip may look at beyond its neighbour's last
-constexpr uint32_t kPollLimit = 1u << 24;              // looks at a carry word before a strip gives up
 
 // steps a strip takes for n rows, whole blocks of them
 static inline uint32_t steps_of(uint32_t n) { return (n + kSkew * (kStripWords - 1) + kBlock - 1) / kBlock * kBlock; }
@@ -269,8 +268,11 @@ __device__ __forceinline__ void row_steps(uint32_t V, uint32_t M0, uint32_t M1, 
 struct RowsArgs {
   const uint32_t *masks;     // wide ids only
   u64 *carry;
-  uint32_t *rows, *gave_up;
-  uint32_t W, n_steps;
+  uint32_t *rows;
+  uint32_t *gave_up;         // device, cleared before the launch (several strips only): a strip has given up
+  uint32_t *gave_up_host;    // pinned: the same
+  uint32_t W, n_steps, strips, strip0;       // strips of a row; the one of workgroup 0
+  uint32_t wait_looks;       // looks at a carry word before a strip gives up
 };
 
 static __device__ const uint32_t all_ones = ~0u;
@@ -360,26 +362,35 @@ static_assert(kSkew == 2 && kGroup == 8 && kBlock == 32 && kIdPad == 128, "posit
 // an instruction in any step (a history kept beside the row and bits put into the lane mask took 3.7 of 11.1 instructions).
 // carry[strip][block]: lane 63's word after step 32 * block + 31, bit 32 = the word is there (the value and its arrival
 // are one store, so no fence is needed); cleared before the launch.  A strip waits only for the strip before it,
-// which waits for no later one, and not for ever (kPollLimit).
+// which waits for no later one.  That one may not be running, though (compute units held by others), so a wait ends
+// after a.wait_looks; whoever gives up says so and goes on with zeros, and so does every strip that waits or comes to
+// wait, after one look: a word that never comes costs one limit, not one per block and strip.  The host then starts the
+// strips one by one.
 template <class Id, bool kMany>
 __device__ __forceinline__ void strip_rows(const RowsArgs &a, Masks<Id> masks, bool stored) {
-  const uint32_t lane = threadIdx.x, strip = blockIdx.x, n_blocks = a.n_steps / kBlock;
-  const bool takes = kMany && strip != 0, gives = kMany && strip + 1 < gridDim.x;
+  const uint32_t lane = threadIdx.x, strip = a.strip0 + blockIdx.x, n_blocks = a.n_steps / kBlock;
+  const bool takes = kMany && strip != 0, gives = kMany && strip + 1 < a.strips;
   const u64 *const cin_words = a.carry + (size_t)(strip - (takes ? 1 : 0)) * (n_blocks + kCarryPad);
   u64 *const cout_words = a.carry + (size_t)strip * (n_blocks + kCarryPad);
   auto peek = [&](uint32_t block) { return __hip_atomic_load(cin_words + block, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); };
-  // x: what a peek saw earlier
+  // x: what a peek saw earlier.  (A way out of the blocks' loop on giving up makes every block wait for its stores: 34 ns a
+  // row in place of 20.)
   auto carry_word = [&](uint32_t block, u64 x) -> uint32_t {
     uint32_t word = __builtin_amdgcn_readfirstlane((uint32_t)x);
     if (__builtin_expect(__builtin_amdgcn_readfirstlane((uint32_t)(x >> 32)) != 0, 1)) return word;
 #pragma unroll 1
-    for (uint32_t tries = 0; tries < kPollLimit; ++tries) {
+    for (uint32_t looks = 0; looks <= a.wait_looks; ++looks) {
       __builtin_amdgcn_s_sleep(1);
       const u64 y = peek(block);
+      const uint32_t over = __hip_atomic_load(a.gave_up, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
       word = __builtin_amdgcn_readfirstlane((uint32_t)y);
       if (__builtin_amdgcn_readfirstlane((uint32_t)(y >> 32))) return word;
+      if (__builtin_amdgcn_readfirstlane(over)) break;
     }
-    if (lane == 0) __hip_atomic_store(a.gave_up, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+    if (lane == 0) {
+      __hip_atomic_store(a.gave_up, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      __hip_atomic_store(a.gave_up_host, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+    }
     return 0;
   };
 
@@ -445,7 +456,7 @@ __device__ __forceinline__ void strip_rows(const RowsArgs &a, Masks<Id> masks, b
   }
 }
 
-// One wavefront per workgroup, workgroup = strip.  ref_id: n ids with kIdPad entries of the empty mask row before them
+// One wavefront per workgroup, workgroup = strip (all of them, or one to a launch).  ref_id: n ids with kIdPad entries of the empty mask row before them
 // and id_length() - kIdPad - n after them, so that a lane whose row has not begun or is over adds nothing.  16-bit ids:
 // the strip builds its own mask table in LDS from cur_id and keeps all the reference's ids there too; wider ids (more
 // keys or operators than fit): masks and ids come from device memory.
@@ -468,8 +479,8 @@ __global__ __launch_bounds__(64) void ss_align_rows_kernel(const Id *__restrict_
                                                            const uint32_t *__restrict__ n_keys) {
   constexpr bool kLds = sizeof(Id) == 2;
   extern __shared__ uint32_t lds[];
-  const uint32_t lane = threadIdx.x, strip = blockIdx.x;
-  const bool many = gridDim.x > 1;
+  const uint32_t lane = threadIdx.x, strip = a.strip0 + blockIdx.x;
+  const bool many = a.strips > 1;
   const uint32_t first = many ? 1 : 0;                       // lane of the strip's first word
   const uint32_t w0 = strip * kInnerWords;
   const uint32_t words = min(many ? kInnerWords : kStripWords, a.W - w0);
@@ -804,7 +815,7 @@ uint32_t most_few(uint32_t n) {
 // Where everything lies.  `d` device scratch, `h` pinned scratch.
 struct Layout {
   size_t h_ref, h_cur, h_flag, h_n_keys, h_out, h_end;
-  size_t ref, cur, ref_id, cur_id, n_keys, rep, id, slot, carry, rows, pair, table, entry, groups, group_entry, masks, end;
+  size_t ref, cur, ref_id, cur_id, n_keys, rep, id, slot, carry, gave_up, rows, pair, table, entry, groups, group_entry, masks, end;
   uint32_t n, m, W, strips, n_steps, n_blocks, walk_blocks, walk_groups, slots, bits;
   bool one_wg, short_rows;
 
@@ -847,6 +858,7 @@ struct Layout {
     groups = take(short_rows ? 0 : (size_t)walk_groups * kWindow * 2);
     group_entry = take(short_rows ? 0 : (size_t)walk_groups * 4);
     carry = take((size_t)(strips - 1) * (n_blocks + kCarryPad) * 8);
+    gave_up = take(strips > 1 ? 4 : 0);
     masks = o;                                             // last: its size needs the number of keys
     end = o;
   }
@@ -856,7 +868,7 @@ struct Layout {
 // Rows (and, long ones, the walk) for ids of the given form.  The masks are needed where the rows kernel does not keep its
 // own in LDS, and by the walk.
 template <class Id>
-int launch_rows(ss_ctx *ctx, const Layout &y, uint8_t *d, uint8_t *hd, uint32_t keys) {
+int launch_rows(ss_ctx *ctx, const Layout &y, uint8_t *d, uint8_t *hd, uint32_t keys, bool one_by_one = false) {
   constexpr bool kLds = sizeof(Id) == 2;
   hipStream_t s = ctx->s_aux;
   const Id *ref_id = (const Id *)(d + y.ref_id), *cur_id = (const Id *)(d + y.cur_id);
@@ -866,10 +878,13 @@ int launch_rows(ss_ctx *ctx, const Layout &y, uint8_t *d, uint8_t *hd, uint32_t 
   if (clear) ss_launch_fill(s, d + y.carry, clear, 0);
   if (masks_needed)
     hipLaunchKernelGGL(ss_align_masks_kernel<Id>, dim3((y.m + 255) / 256), dim3(256), 0, s, cur_id, y.m, masks, y.W);
-  const RowsArgs args = {masks, (u64 *)(d + y.carry), rows, (uint32_t *)(hd + y.h_flag), y.W, y.n_steps};
+  RowsArgs args = {masks, (u64 *)(d + y.carry), rows, (uint32_t *)(d + y.gave_up), (uint32_t *)(hd + y.h_flag),
+                   y.W, y.n_steps, y.strips, 0, ctx->align_wait_looks};
   const uint32_t *n_keys = (const uint32_t *)(d + y.n_keys);
-  hipLaunchKernelGGL(ss_align_rows_kernel<Id>, dim3(y.strips), dim3(64), kLds ? lds_need(keys, y.n) : 0, s, ref_id, cur_id,
-                     y.m, args, n_keys);
+  const uint32_t per_launch = one_by_one ? 1 : y.strips;
+  for (; args.strip0 < y.strips; args.strip0 += per_launch)
+    hipLaunchKernelGGL(ss_align_rows_kernel<Id>, dim3(per_launch), dim3(64), kLds ? lds_need(keys, y.n) : 0, s, ref_id,
+                       cur_id, y.m, args, n_keys);
   if (!y.short_rows) {
     const uint32_t *cmasks = masks, *crows = rows;
     uint16_t *table = (uint16_t *)(d + y.table), *groups = (uint16_t *)(d + y.groups);
@@ -970,7 +985,12 @@ int ss_align_core(ss_ctx *ctx, const ss_op_t *ref, uint32_t n, const ss_op_t *cu
     if (rc != SS_OK) return rc;
     SS_HIP(hipStreamSynchronize(s));
   }
-  if (*h_flag) return SS_E_TIMEOUT;
+  if (*h_flag) {                        // a strip gave up: each after the one before it, then every word is there and none waits
+    ctx->align_one_by_one += 1;
+    rc = keys <= few ? launch_rows<uint16_t>(ctx, y, d, hd, keys, true) : launch_rows<uint32_t>(ctx, y, d, hd, keys, true);
+    if (rc != SS_OK) return rc;
+    SS_HIP(hipStreamSynchronize(s));
+  }
   if (n_keys_out) *n_keys_out = keys;
   uint32_t pairs = 0;
   if (!y.short_rows) {
@@ -1000,6 +1020,13 @@ int ss_align_core(ss_ctx *ctx, const ss_op_t *ref, uint32_t n, const ss_op_t *cu
   }
   *lcs = pairs;
   return SS_OK;
+}
+
+// For tests: the context's limit of a strip's wait, in looks at the word; returns how many of its calls have started the
+// strips one by one so far.
+extern "C" uint32_t ss_align_wait_limit(ss_ctx *ctx, uint32_t looks) {
+  ctx->align_wait_looks = looks;
+  return ctx->align_one_by_one;
 }
 
 void ss_align_anchors(const ss_op_t *ref, uint32_t n, const ss_op_t *cur, const int32_t *ref_to_cur,

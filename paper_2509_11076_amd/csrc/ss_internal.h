@@ -163,6 +163,10 @@ struct ss_ctx {
   size_t d_scratch_bytes = 0;
   void *h_scratch = nullptr;        // pinned
   size_t h_scratch_bytes = 0;
+  // aligner: looks of a strip at a word of the one before it until it gives up (about a second); calls that then ran
+  // strip after strip
+  uint32_t align_wait_looks = 1u << 20;
+  uint32_t align_one_by_one = 0;
   ss_sched sched;
   ss_stats_t stats;
 };

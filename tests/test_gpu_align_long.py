@@ -2,6 +2,8 @@
 walked on the host or on the GPU, mask tables in LDS or in device memory, paths that leave the tabulated window.
 The whole pairing is compared exactly with the recurrence in Python integers, which is itself checked against the
 oracle's textbook dynamic programme."""
+import ctypes
+
 import numpy as np
 import pytest
 
@@ -82,3 +84,34 @@ def test_long_gaps_leave_the_window(P, ctx, n):                   # noqa: F811
                 np.concatenate([30 + rng.integers(0, 3, 400), ref[n // 3:], 30 + rng.integers(0, 3, 5000)])):
         lib = P.ss_align_sequence(ctx, ops_arr(ref), ops_arr(cur))
         assert np.array_equal(lib["ref_to_cur"], pairing(ref.tolist(), cur.tolist()))
+
+
+@pytest.mark.parametrize("n,m,alpha", [
+    (500, 6145, 250), (700, 40000, 60), (9000, 9001, 254), (9000, 9001, 3000),       # walked on the host, on the GPU, wide ids
+    (1154, 1156, 40),                                                                # one strip: nothing to wait for
+])
+def test_strips_that_give_up_waiting_are_started_one_by_one(P, ctx, n, m, alpha):    # noqa: F811
+    """a limit of zero: a strip that finds its neighbour's first word missing leaves at once, the kernel ends, and the call
+    still gives the pairing; so does the next one under the usual limit"""
+    lib = ctypes.CDLL(P.LIB_PATH)
+    lib.ss_align_wait_limit.argtypes, lib.ss_align_wait_limit.restype = [ctypes.c_void_p, ctypes.c_uint32], ctypes.c_uint32
+    rng = np.random.default_rng([n, m, alpha, 1])
+    ref = rng.integers(0, alpha, n)
+    ref[:min(n, alpha)] = np.arange(min(n, alpha))
+    cur = rng.integers(0, alpha, m)
+    want = pairing(ref.tolist(), cur.tolist())
+    x, y = ops_arr(ref), ops_arr(cur)
+    anc = np.zeros(50, dtype=P.ANCHOR_DT)
+    anc["ref_op"] = rng.integers(0, n, 50)
+    usual, many = 1 << 20, m > 2048
+    before = lib.ss_align_wait_limit(ctx, 0)
+    try:
+        assert np.array_equal(P.ss_align_sequence(ctx, x, y)["ref_to_cur"], want)
+        got = P.ss_match_sequence(ctx, x, y, anc, flags=P.SS_MATCH_ALIGN)
+    finally:
+        after = lib.ss_align_wait_limit(ctx, usual)
+    assert after - before == (2 if many else 0)
+    again = P.ss_match_sequence(ctx, x, y, anc, flags=P.SS_MATCH_ALIGN)
+    assert np.array_equal(got["new_idx"], again["new_idx"]) and np.array_equal(got["level"], again["level"])
+    assert np.array_equal(P.ss_align_sequence(ctx, x, y)["ref_to_cur"], want)
+    assert lib.ss_align_wait_limit(ctx, usual) == after
