@@ -25,7 +25,6 @@ typedef unsigned long long u64;
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 
 constexpr uint32_t kAlignLenLimit = 1u << 16;          // at most 34 strips
-constexpr size_t kAlignRowBytesLimit = 1ull << 30;     // rows kept for the walk back
 constexpr uint32_t kBlock = 32;                        // steps between two looks at the neighbouring strip
 constexpr uint32_t kGroup = 8;                         // steps whose masks are looked up together
 constexpr uint32_t kStripWords = 64;                   // 32-bit words of a row, one per lane, in a single strip
@@ -41,12 +40,12 @@ constexpr size_t kHostRowBytes = 4u << 20;
 constexpr uint32_t kCarryPad = 8;                      // carry words a strip may look at beyond its neighbour's last
 
 // steps a strip takes for n rows, whole blocks of them
-static inline uint32_t steps_of(uint32_t n) { return (n + kSkew * (kStripWords - 1) + kBlock - 1) / kBlock * kBlock; }
+static constexpr uint32_t steps_of(uint32_t n) { return (n + kSkew * (kStripWords - 1) + kBlock - 1) / kBlock * kBlock; }
 
 // entries of a padded id array, a multiple of 16 bytes
 static inline __host__ __device__ uint32_t id_length(uint32_t n_steps) { return kIdPad + n_steps + 3 * kBlock; }
 
-static inline __host__ __device__ uint32_t strips_of(uint32_t W) {
+static constexpr __host__ __device__ uint32_t strips_of(uint32_t W) {
   return W <= kStripWords ? 1 : (W + kInnerWords - 1) / kInnerWords;
 }
 
@@ -864,6 +863,11 @@ struct Layout {
   }
   size_t with_masks(uint32_t keys) const { return end + (size_t)(keys + 1) * W * 4; }
 };
+// With both lengths at their limit the rows take 545 MiB, a strip 16 MiB (the kernel's buffer offsets have 31 bits), and the
+// masks, with every key distinct, 512 MiB.
+static_assert((uint64_t)steps_of(kAlignLenLimit) * kStripWords * 4 * strips_of(kAlignLenLimit / 32) <= 1ull << 30, "rows");
+static_assert((uint64_t)steps_of(kAlignLenLimit) * kStripWords * 4 < 1ull << 31, "a strip's rows");
+static_assert(((uint64_t)kAlignLenLimit + 1) * (kAlignLenLimit / 32) * 4 <= 1ull << 30, "masks");
 
 // Rows (and, long ones, the walk) for ids of the given form.  The masks are needed where the rows kernel does not keep its
 // own in LDS, and by the walk.
@@ -915,9 +919,6 @@ int ss_align_core(ss_ctx *ctx, const ss_op_t *ref, uint32_t n, const ss_op_t *cu
   *lcs = 0;
   if (n_keys_out) *n_keys_out = 0;
   if (n == 0 || m == 0) return SS_OK;
-  // (with both lengths at their limit the rows take 0.5 GiB, and so does the mask table with every key distinct)
-  static_assert((uint64_t)kAlignLenLimit * (kAlignLenLimit / 64) * 8 <= kAlignRowBytesLimit, "rows and masks fit");
-
   const Layout y(n, m);
   const uint32_t few = most_few(n);
   hipStream_t s = ctx->s_aux;
