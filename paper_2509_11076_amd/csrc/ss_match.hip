@@ -196,16 +196,18 @@ struct AnchorArgs {
   ClaimTable table;
 };
 
-// One workgroup per anchor.  Each wavefront counts, over its quarter of the reference up to the anchor and its quarter of
-// the current sequence, the operators with the anchor's key at each level; the ordinal's quarter is then known and its
-// wavefront walks it 64 operators at a time (ballots and population counts find the operator).  Bound by the latency of
-// these walks: 480 anchors of 1,154 operators 8.7 us, claims included; a wavefront per anchor, all of both sequences in
-// one walk, took 13.0 us and the claims 3.1 us in a launch of their own.
-__global__ __launch_bounds__(256) void ss_anchor_kernel(AnchorArgs g) {
-  __shared__ uint32_t in_ref[4][3], in_cur[4][3];
-  __shared__ int32_t found[3];
+struct AnchorShared {
+  uint32_t in_ref[4][3], in_cur[4][3];
+  int32_t found[3];
+};
+
+// The landing of anchor a, found by the whole workgroup.  Each wavefront counts, over its quarter of the reference up to
+// the anchor and its quarter of the current sequence, the operators with the anchor's key at each level; the ordinal's
+// quarter is then known and its wavefront walks it 64 operators at a time (ballots and population counts find the
+// operator).
+__device__ __forceinline__ void search_anchor(const AnchorArgs &g, uint32_t a, AnchorShared &sh) {
   const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-  const uint32_t a = blockIdx.x, i = g.anchors[a].ref_op, slot = g.anchors[a].out_slot;
+  const uint32_t i = g.anchors[a].ref_op, slot = g.anchors[a].out_slot;
   if (i >= g.n || g.ref[i].op_token == 0) {              // uniform
     if (threadIdx.x == 0) { g.land[a] = -1; g.lvl[a] = 255; }
     return;
@@ -236,19 +238,19 @@ __global__ __launch_bounds__(256) void ss_anchor_kernel(AnchorArgs g) {
   count(g.ref, r_lo, r_hi, r);
   count(g.cur, c_lo, c_hi, c);
   if (lane < 3) {
-    in_ref[w][lane] = lane == 0 ? r[0] : lane == 1 ? r[1] : r[2];
-    in_cur[w][lane] = lane == 0 ? c[0] : lane == 1 ? c[1] : c[2];
+    sh.in_ref[w][lane] = lane == 0 ? r[0] : lane == 1 ? r[1] : r[2];
+    sh.in_cur[w][lane] = lane == 0 ? c[0] : lane == 1 ? c[1] : c[2];
   }
-  if (threadIdx.x < 3) found[threadIdx.x] = -1;
+  if (threadIdx.x < 3) sh.found[threadIdx.x] = -1;
   __syncthreads();
   // this wavefront's levels: the ordinal lies in its quarter
   uint32_t need[3];
   bool open[3];
 #pragma unroll
   for (int L = 0; L < 3; ++L) {
-    uint32_t ord = in_ref[0][L] + in_ref[1][L] + in_ref[2][L] + in_ref[3][L], before = 0;
-    for (int v = 0; v < w; ++v) before += in_cur[v][L];
-    open[L] = ord >= before && ord < before + in_cur[w][L];
+    uint32_t ord = sh.in_ref[0][L] + sh.in_ref[1][L] + sh.in_ref[2][L] + sh.in_ref[3][L], before = 0;
+    for (int v = 0; v < w; ++v) before += sh.in_cur[v][L];
+    open[L] = ord >= before && ord < before + sh.in_cur[w][L];
     need[L] = ord - before;
   }
   for (uint32_t base = c_lo; (open[0] || open[1] || open[2]) && base < c_hi; base += 64) {
@@ -262,7 +264,7 @@ __global__ __launch_bounds__(256) void ss_anchor_kernel(AnchorArgs g) {
       const uint32_t pc = __popcll(b);
       if (need[L] < pc) {
         const int at = nth_set_bit(b, need[L], lane);
-        if (lane == 0) found[L] = (int32_t)base + at;
+        if (lane == 0) sh.found[L] = (int32_t)base + at;
         open[L] = false;
       } else {
         need[L] -= pc;
@@ -271,13 +273,49 @@ __global__ __launch_bounds__(256) void ss_anchor_kernel(AnchorArgs g) {
   }
   __syncthreads();
   if (threadIdx.x == 0) {
-    const int32_t f[3] = {found[0], found[1], found[2]};
+    const int32_t f[3] = {sh.found[0], sh.found[1], sh.found[2]};
     uint8_t level;
     const int32_t j = choose_landing(g.cur, R, slot, f, level);
     g.land[a] = j;
     g.lvl[a] = level;
     if (j >= 0) g.slot_of[a] = claim(g.table, j, slot, a);
   }
+}
+
+// One workgroup per anchor.  Bound by the latency of the walks: 480 anchors of 1,154 operators 8.7 us, claims included; a
+// wavefront per anchor, all of both sequences in one walk, took 13.0 us and the claims 3.1 us in a launch of their own.
+__global__ __launch_bounds__(256) void ss_anchor_kernel(AnchorArgs g) {
+  __shared__ AnchorShared sh;
+  search_anchor(g, blockIdx.x, sh);
+}
+
+// The landing of anchor a, found by one wavefront: all of both sequences in one walk.
+__device__ __forceinline__ int32_t search_alone(const AnchorArgs &g, const ss_op_t &R, uint32_t i, uint32_t slot, uint8_t &level) {
+  const int lane = threadIdx.x & 63;
+  int32_t f[3] = {-1, -1, -1};
+  uint32_t r[3] = {0, 0, 0};
+  for (uint32_t j = lane; j < i; j += 64) {
+    bool e0, e1, e2;
+    same_key(g.ref[j], R, e0, e1, e2);
+    r[0] += e0; r[1] += e1; r[2] += e2;
+  }
+#pragma unroll
+  for (int L = 0; L < 3; ++L) r[L] = wave_sum_u32(r[L]);
+  for (uint32_t base = 0; base < g.m; base += 64) {
+    const uint32_t j = base + lane;
+    bool e[3] = {false, false, false};
+    if (j < g.m) same_key(g.cur[j], R, e[0], e[1], e[2]);
+#pragma unroll
+    for (int L = 0; L < 3; ++L) {
+      const uint64_t b = __ballot(e[L]);
+      if (f[L] >= 0) continue;
+      const uint32_t pc = __popcll(b);
+      if (r[L] < pc) f[L] = (int32_t)base + nth_set_bit(b, r[L], lane);
+      else r[L] -= pc;
+    }
+    if (f[0] >= 0 && f[1] >= 0 && f[2] >= 0) break;
+  }
+  return choose_landing(g.cur, R, slot, f, level);
 }
 
 // ---- many anchors: the distinct keys first ------------------------------------------------------------------------
@@ -298,8 +336,8 @@ struct KeyLists {
   uint32_t mask, shift, max_lists;
 };
 
-// More distinct keys (of all levels) than this, or than half the anchors, and a workgroup per key costs more than a
-// wavefront per anchor.
+// More distinct keys (of all levels) than this, or than half the anchors, and a workgroup per key costs more than one
+// per anchor.
 constexpr uint32_t kMaxLists = 4096;
 
 __device__ __forceinline__ bool same_at(const ss_op_t &x, const ss_op_t &y, int L) {
@@ -461,49 +499,39 @@ __global__ __launch_bounds__(1024) void ss_lists_kernel(AnchorArgs g, KeyLists q
   }
 }
 
-// One wavefront per anchor: looks its ordinal up, or, with too many distinct keys, counts and searches by itself.
-__global__ __launch_bounds__(256) void ss_lookup_kernel(AnchorArgs g, KeyLists q) {
-  const int lane = threadIdx.x & 63;
-  const uint32_t a = (blockIdx.x * 256 + threadIdx.x) >> 6;
-  if (a >= g.k) return;                                      // uniform per wavefront
+// A wavefront per anchor looks its ordinal up, four to a workgroup or, up to kOneEach anchors, one.  With too many distinct
+// keys for lists an anchor is searched for by itself: by its workgroup where that has no other, else by its wavefront.
+// 1,000 anchors over 65,536 operators 302 us a call with a workgroup each, 711 with a wavefront each; 4,000 over 18,464
+// operators 180 and 255, 8,001 260 and 296, 20,000 488 and 478.  Where there are lists a workgroup each costs its launch:
+// 8,001 anchors 227 us against 222, 2,048 nothing to be seen.
+constexpr uint32_t kOneEach = 4096;
+
+__global__ __launch_bounds__(256) void ss_lookup_kernel(AnchorArgs g, KeyLists q, uint32_t per) {
+  __shared__ AnchorShared sh;
+  const bool listed = q.n_used[0] + q.n_used[1] + q.n_used[2] <= q.max_lists;
+  if (!listed && per == 1) {
+    search_anchor(g, blockIdx.x, sh);
+    return;
+  }
+  const uint32_t w = threadIdx.x >> 6, a = blockIdx.x * per + w;
+  if (w >= per || a >= g.k) return;                          // uniform per wavefront
   const uint32_t i = g.anchors[a].ref_op, slot = g.anchors[a].out_slot;
   int32_t f[3] = {-1, -1, -1}, result = -1;
   uint8_t level = 255;
   if (i < g.n && g.ref[i].op_token != 0) {
     const ss_op_t R = g.ref[i];
-    if (q.n_used[0] + q.n_used[1] + q.n_used[2] <= q.max_lists) {
+    if (listed) {
 #pragma unroll
       for (int L = 0; L < 3; ++L) {
         const uint32_t h = q.key_of[L][a], ord = q.rank[L][i];
         if (ord < q.count[L][h]) f[L] = (int32_t)q.place[L][q.start[L][h] + ord];
       }
+      result = choose_landing(g.cur, R, slot, f, level);
     } else {
-      uint32_t r[3] = {0, 0, 0};
-      for (uint32_t j = lane; j < i; j += 64) {
-        bool e0, e1, e2;
-        same_key(g.ref[j], R, e0, e1, e2);
-        r[0] += e0; r[1] += e1; r[2] += e2;
-      }
-#pragma unroll
-      for (int L = 0; L < 3; ++L) r[L] = wave_sum_u32(r[L]);
-      for (uint32_t base = 0; base < g.m; base += 64) {
-        const uint32_t j = base + lane;
-        bool e[3] = {false, false, false};
-        if (j < g.m) same_key(g.cur[j], R, e[0], e[1], e[2]);
-#pragma unroll
-        for (int L = 0; L < 3; ++L) {
-          const uint64_t b = __ballot(e[L]);
-          if (f[L] >= 0) continue;
-          const uint32_t pc = __popcll(b);
-          if (r[L] < pc) f[L] = (int32_t)base + nth_set_bit(b, r[L], lane);
-          else r[L] -= pc;
-        }
-        if (f[0] >= 0 && f[1] >= 0 && f[2] >= 0) break;
-      }
+      result = search_alone(g, R, i, slot, level);
     }
-    result = choose_landing(g.cur, R, slot, f, level);
   }
-  if (lane == 0) {
+  if ((threadIdx.x & 63) == 0) {
     g.land[a] = result;
     g.lvl[a] = level;
     if (result >= 0) g.slot_of[a] = claim(g.table, result, slot, a);
@@ -716,7 +744,8 @@ extern "C" int ss_match_sequence(ss_ctx *ctx, const ss_op_t *ref, uint32_t n, co
         q.max_lists = std::min(kMaxLists, k / 2);
         hipLaunchKernelGGL(ss_keys_kernel, dim3((k + 255) / 256, 3), dim3(256), 0, s, g, q);
         hipLaunchKernelGGL(ss_lists_kernel, dim3(512), dim3(1024), 0, s, g, q);
-        hipLaunchKernelGGL(ss_lookup_kernel, dim3((k + 3) / 4), dim3(256), 0, s, g, q);
+        const uint32_t per = k <= kOneEach ? 1 : 4;
+        hipLaunchKernelGGL(ss_lookup_kernel, dim3((k + per - 1) / per), dim3(256), 0, s, g, q, per);
       } else {
         hipLaunchKernelGGL(ss_anchor_kernel, dim3(k), dim3(256), 0, s, g);
       }

@@ -98,6 +98,7 @@ def test_the_definition_here_is_the_oracles(P):                   # noqa: F811
     (140000, 100, 40, 30), (140000, 300, 40, 30),                                            # inputs by copy
     (8192, 2100, 3, 2), (300000, 100, 3, 2),                                                 # whole turns, hits beyond LDS
     (4097, 65537, 12, 9), (9001, 65537, 200, 1 << 30),                                       # many anchors, with lists and without
+    (30000, 300, 40, 1 << 30), (9001, 4096, 200, 1 << 30), (9001, 4097, 200, 1 << 30),       # no lists: a workgroup, a wavefront each
 ])
 def test_forms(P, ctx, n, k, tokens, stacks):                     # noqa: F811
     rng = np.random.default_rng([n, k, tokens])
