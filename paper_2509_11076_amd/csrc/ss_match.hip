@@ -8,7 +8,7 @@
 //     matching on operator name, call stack and data type with integer comparisons
 //     only): an anchor's ordinal among the reference's operators with its key, at each of three
 //     relaxation levels, and the operator of that ordinal in the current sequence.  Few anchors or
-//     short sequences: one workgroup per anchor counts and searches.  Many: the layers of a model
+//     short sequences: one workgroup or wavefront per anchor counts and searches.  Many: the layers of a model
 //     share their keys, so the anchors' distinct keys are collected first, one workgroup per key
 //     lists the places where it occurs, and an anchor looks its ordinal up.
 #include <algorithm>
@@ -316,6 +316,26 @@ __device__ __forceinline__ int32_t search_alone(const AnchorArgs &g, const ss_op
     if (f[0] >= 0 && f[1] >= 0 && f[2] >= 0) break;
   }
   return choose_landing(g.cur, R, slot, f, level);
+}
+
+// One wavefront per anchor, for kAloneAnchors and more that are at least twice the operators: then a workgroup's barriers
+// and launch cost more than its four wavefronts gain.  20,000 anchors over 60 + 60 operators 56 us a call against 85, 2,000
+// over 500 + 500 43.2 against 43.9, 8,000 over 1,000 + 1,000 62 against 72, but 2,000 over these 45.1 against 42.9.  The
+// rule also keeps the other kernel's launch within 2^32 work-items (2^24 anchors may come with one operator).
+constexpr uint32_t kAloneAnchors = 2048;
+
+__global__ __launch_bounds__(256) void ss_anchor_short_kernel(AnchorArgs g) {
+  const uint32_t a = (blockIdx.x * 256 + threadIdx.x) >> 6;
+  if (a >= g.k) return;                                      // uniform per wavefront
+  const uint32_t i = g.anchors[a].ref_op, slot = g.anchors[a].out_slot;
+  int32_t result = -1;
+  uint8_t level = 255;
+  if (i < g.n && g.ref[i].op_token != 0) result = search_alone(g, g.ref[i], i, slot, level);
+  if ((threadIdx.x & 63) == 0) {
+    g.land[a] = result;
+    g.lvl[a] = level;
+    if (result >= 0) g.slot_of[a] = claim(g.table, result, slot, a);
+  }
 }
 
 // ---- many anchors: the distinct keys first ------------------------------------------------------------------------
@@ -747,7 +767,8 @@ extern "C" int ss_match_sequence(ss_ctx *ctx, const ss_op_t *ref, uint32_t n, co
         const uint32_t per = k <= kOneEach ? 1 : 4;
         hipLaunchKernelGGL(ss_lookup_kernel, dim3((k + per - 1) / per), dim3(256), 0, s, g, q, per);
       } else {
-        hipLaunchKernelGGL(ss_anchor_kernel, dim3(k), dim3(256), 0, s, g);
+        if (k >= kAloneAnchors && k >= 2 * (n + m)) hipLaunchKernelGGL(ss_anchor_short_kernel, dim3((k + 3) / 4), dim3(256), 0, s, g);
+        else hipLaunchKernelGGL(ss_anchor_kernel, dim3(k), dim3(256), 0, s, g);
       }
       hipLaunchKernelGGL(ss_injective_kernel, dim3(out_wgs), dim3(256), 0, s, g,
                          (int32_t *)(mapped ? hd + ho_idx : d + o_idx), mapped ? hd + ho_level : d + o_level,

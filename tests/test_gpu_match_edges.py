@@ -99,6 +99,7 @@ def test_the_definition_here_is_the_oracles(P):                   # noqa: F811
     (8192, 2100, 3, 2), (300000, 100, 3, 2),                                                 # whole turns, hits beyond LDS
     (4097, 65537, 12, 9), (9001, 65537, 200, 1 << 30),                                       # many anchors, with lists and without
     (30000, 300, 40, 1 << 30), (9001, 4096, 200, 1 << 30), (9001, 4097, 200, 1 << 30),       # no lists: a workgroup, a wavefront each
+    (500, 2047, 12, 9), (500, 2048, 12, 9), (600, 2048, 12, 9), (63, 70000, 9, 3),           # short, many anchors: a wavefront each
 ])
 def test_forms(P, ctx, n, k, tokens, stacks):                     # noqa: F811
     rng = np.random.default_rng([n, k, tokens])
@@ -106,6 +107,19 @@ def test_forms(P, ctx, n, k, tokens, stacks):                     # noqa: F811
     check(P, ctx, ref, perturbed(rng, ref), anchors(rng, n, k))
     check(P, ctx, ref, ref[:0], anchors(rng, n, k))
     check(P, ctx, perturbed(rng, ref), ref, anchors(rng, n, 7))
+
+
+@pytest.mark.parametrize("m", [0, 1])
+def test_the_most_anchors_over_the_fewest_operators(P, ctx, m):   # noqa: F811
+    """2^24 anchors on one operator: the lowest keeps its counterpart, if there is one, and no launch is too large"""
+    ref = sequence(np.random.default_rng(1), 1, 1, 1)
+    ref["op_token"], ref["n_out"] = 1, 1
+    cur = ref[:m].copy()
+    cur["stack_hash"] += 1
+    anc = np.zeros(1 << 24, dtype=W.ANCHOR_DT)
+    r = P.ss_match_sequence(ctx, ref, cur, anc)
+    assert (r["n_unmatched"], r["new_idx"][0], r["level"][0]) == (len(anc) - m, m - 1, 1 if m else 255)
+    assert np.all(r["new_idx"][1:] == -1) and np.all(r["level"][1:] == 255)
 
 
 @pytest.mark.parametrize("n,tokens", [(300, 7), (5000, 1500), (70000, 40), (20000, (1 << 18) - 1)])
