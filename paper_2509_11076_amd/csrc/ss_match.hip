@@ -63,17 +63,28 @@ __global__ __launch_bounds__(256) void ss_prep_kernel(PrepArgs a) {
   const uint32_t stride = gridDim.x * 256, first = blockIdx.x * 256 + threadIdx.x, len = a.n > a.m ? a.n : a.m;
   uint64_t dot = 0, na = 0, nb = 0;
   uint32_t bad = 0;
-  for (uint32_t i = first; i < len; i += stride) {
-    ss_op_t c = {0, 0, 0, 0}, r = {0, 0, 0, 0};         // the shorter sequence is padded with token 0
-    if (i < a.m) c = a.cur[i];
-    if (i < a.n) r = a.ref[i];
-    if (a.dcur && i < a.m) a.dcur[i] = c;
-    if (a.dref && i < a.n) a.dref[i] = r;
-    const uint64_t x = c.op_token, y = r.op_token;
-    if (x >= kTokenLimit || y >= kTokenLimit) bad = 1;
-    dot += x * y;
-    na += x * x;
-    nb += y * y;
+  // operators of each sequence that a thread reads together (one by one 500,000 operators of each take 25 us in place of 6)
+  constexpr uint32_t kAhead = 4;
+  for (uint32_t i0 = first; i0 < len; i0 += kAhead * stride) {
+    ss_op_t c[kAhead], r[kAhead];                        // the shorter sequence is padded with token 0
+#pragma unroll
+    for (uint32_t u = 0; u < kAhead; ++u) {
+      const uint32_t i = i0 + u * stride;
+      c[u] = r[u] = ss_op_t{0, 0, 0, 0};
+      if (i < a.m) c[u] = a.cur[i];
+      if (i < a.n) r[u] = a.ref[i];
+    }
+#pragma unroll
+    for (uint32_t u = 0; u < kAhead; ++u) {
+      const uint32_t i = i0 + u * stride;
+      if (a.dcur && i < a.m) a.dcur[i] = c[u];
+      if (a.dref && i < a.n) a.dref[i] = r[u];
+      const uint64_t x = c[u].op_token, y = r[u].op_token;
+      if (x >= kTokenLimit || y >= kTokenLimit) bad = 1;
+      dot += x * y;
+      na += x * x;
+      nb += y * y;
+    }
   }
   if (a.danc)
     for (uint32_t i = first; i < a.k; i += stride) a.danc[i] = a.anchors[i];
