@@ -13,7 +13,8 @@
 // Short traces: one workgroup keeps the events in registers and the OpAt table in LDS, one launch.  Long ones: three
 // launches over tiles of events (sums per tile; running sums and OpAt; operators and timeline).  A list that
 // turns out not to be in operator order is gathered per operator with 64-bit integer atomics instead
-// (order-independent, hence deterministic); it has no timeline.
+// (order-independent, hence deterministic); it has no timeline.  So are the longer ones of a batch, one workgroup a scan,
+// in any order.
 //
 // Bound by latency: barriers and dependent loads in a short trace (124 + 24 events, 66 operators: 6.3 us in one
 // workgroup; with sums gathered by atomics, fences and running values in device memory 31 us), launches and one pass
@@ -379,12 +380,23 @@ __device__ __forceinline__ void scan_wg(const ScanArgs &a, OpAt *at, int64_t *po
   int64_t delta[K], sp[K], sn[K], carry_sp = 0, carry_sn = 0;
   uint32_t cp[K], carry_cp = 0;
   bool pos_of[K];
-  for (uint64_t first = 0; first < total; first += (uint64_t)T * K) {
+  // Running sums where the events take one pass or two.  A list out of order needs none: they end as soon as it shows, and
+  // the events are gathered by operator, whatever their order; more events than that (of a batch: it has no timeline) are
+  // gathered at once.  (Running sums always, and gathered after them where the order was wrong: six scans of 100,000 + 20
+  // events over 400 operators 249 us in order and 343 out of order, gathered at once 212 and 213; of 10,000 + 2,000 over 700
+  // 134 and 164 against 133 and 137; of 8,000 + 100, two passes, 67 and 90 against 67 and 76 to 83.)
+  const bool in_sums = total <= 2 * (uint64_t)T * K;
+  for (uint64_t first = 0; in_sums && first < total; first += (uint64_t)T * K) {
     const uint32_t bad = load_events<T, K>(a.ev, a.n_ev, a.pev, a.n_pe, first, total, n, x);
     if (bad) atomicOr(&sh.flags, bad);
+    // A wavefront with events out of order fills nothing: in random order nearly every gap would be a long one (4,000 + 90
+    // events over 700 operators 104 us, 24 without; six scans of 20,000 + 2,000 over 65,536 71 ms).  Known without a look at
+    // LDS, which would cost an ordered trace 0.3 us.
+    const bool tidy = !__ballot(bad != 0);
 #pragma unroll
     for (int k = 0; k < K; ++k) { delta[k] = x[k].delta; pos_of[k] = x[k].pos; }
     wg_sums<T, K>(sh.sums, delta, pos_of, carry_sp, carry_sn, carry_cp, sp, sn, cp);
+    if (total > (uint64_t)T * K && sh.flags) break;
     carry_sp = sh.sums.tot_sp; carry_sn = sh.sums.tot_sn; carry_cp = sh.sums.tot_cp;
     if (a.n_pe && first + (uint64_t)T * K > a.n_ev) {        // the second list starts from its own zero
 #pragma unroll
@@ -397,7 +409,7 @@ __device__ __forceinline__ void scan_wg(const ScanArgs &a, OpAt *at, int64_t *po
     }
     // a wavefront's elements of one k may belong to both lists: each list's are filled in turn
 #pragma unroll
-    for (int k = 0; k < K; ++k) {
+    for (int k = 0; tidy && k < K; ++k) {
       const uint64_t i = first + (uint64_t)k * T + tid;
       Elem y = x[k];
       y.live = x[k].live && i < a.n_ev;
@@ -410,24 +422,29 @@ __device__ __forceinline__ void scan_wg(const ScanArgs &a, OpAt *at, int64_t *po
     __syncthreads();                                         // the shared totals are written again in the next pass
   }
   __syncthreads();
-  const uint32_t flags = sh.flags;
+  uint32_t flags = sh.flags;
   Best b = no_best();
   int64_t final_total = a.base;
-  if (flags & 1u) {
-    if (tid == 0) write_result(a, b, 0, flags);
-    return;
-  }
-  if (flags & 2u) {
+  const bool gathered = !in_sums || (flags & 3u) == 2u;
+  if (gathered) {
     for (uint32_t t = tid; t < n; t += T) pos[t] = net[t] = 0;
     __threadfence();
     __syncthreads();
     for (uint64_t first = 0; first < total; first += (uint64_t)T * K) {
-      load_events<T, K>(a.ev, a.n_ev, a.pev, a.n_pe, first, total, n, x);
+      const uint32_t bad = load_events<T, K>(a.ev, a.n_ev, a.pev, a.n_pe, first, total, n, x);
+      if (bad) atomicOr(&sh.flags, bad);
 #pragma unroll
       for (int k = 0; k < K; ++k) gather_run(pos, net, x[k], n);
     }
     __threadfence();
     __syncthreads();
+    flags = sh.flags;
+  }
+  if (flags & 1u) {
+    if (tid == 0) write_result(a, b, 0, flags);
+    return;
+  }
+  if (gathered) {
     b = ops_of_sums<T>(a, pos, net, sh.sums);
     __syncthreads();
     final_total += n ? sh.sums.tot_sp : 0;

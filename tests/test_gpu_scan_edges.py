@@ -94,3 +94,27 @@ def test_batch_with_tables_in_lds_and_in_device_memory(P, ctx, n_ev, n_ops):    
         ora = oracle.timeline_scan(ev, c, n_ops, 3, 1 << 40)
         assert (r["peak"], r["argpeak_op"], r["n_over"], r["final"]) == (ora["peak"], ora["argpeak_op"], ora["n_over"], ora["final"])
         assert np.array_equal(r["per_op"], ora["per_op"])
+
+
+@pytest.mark.parametrize("n_ops", [700, 5000])
+def test_batch_lists_out_of_order_from_the_start_or_late(P, ctx, n_ops):             # noqa: F811
+    """several passes over the events: what is out of order shows in the first, at an edge or in the last; an operator out
+    of range behind it is still found"""
+    rng = np.random.default_rng([n_ops, 7])
+    ev, pe = events(rng, 9000, n_ops), events(rng, 4200, n_ops)
+    ora = oracle.timeline_scan(ev, pe, n_ops, 11, 1 << 40)
+    none = oracle.timeline_scan(ev, None, n_ops, 11, 1 << 40)
+
+    def moved(x, where):
+        rest = x[:-1] if where < len(x) // 2 else x[1:]
+        return np.insert(rest, where, x[-1] if where < len(x) // 2 else x[0])
+    for a, b in [(moved(ev, w), pe) for w in (0, 4095, 4096, 8999)] + [(ev, moved(pe, w)) for w in (0, 4199)]:
+        lib = P.ss_timeline_scan_batch(ctx, a, [b, None, b], n_ops, 11, 1 << 40, want_per_op=True)
+        for r, o in zip(lib, (ora, none, ora)):
+            assert (r["peak"], r["argpeak_op"], r["n_over"], r["final"]) == (o["peak"], o["argpeak_op"], o["n_over"], o["final"])
+            assert np.array_equal(r["per_op"], o["per_op"])
+        for late in (a.copy(), a), (b.copy(), b):
+            late[0]["op_idx"][-2] = n_ops
+            with pytest.raises(P.SsError) as e:
+                P.ss_timeline_scan_batch(ctx, late[0] if late[1] is a else a, [None, late[0] if late[1] is b else b], n_ops, 11, 1 << 40)
+            assert e.value.code == P.SS_E_INVAL
