@@ -123,6 +123,30 @@ def test_tiny_traces_limits_links_and_layer_counts(P, seed):
     assert None in seen and 0 in seen and len(seen) >= 4   # infeasible, nothing to do, real policies
 
 
+@pytest.mark.parametrize("n_tensors", [1, 9, 11, 40])
+def test_short_spans_in_a_long_trace(P, n_tensors):
+    """tensors away for 6 operators at most: the spans together shorter than the trace, longer, and shorter once some tensors
+    are taken"""
+    rng = np.random.default_rng(n_tensors)
+    n_ops = 48
+    phases = [0] * 24 + [1] * 24
+    last = np.sort(rng.integers(1, 36, n_tensors)).tolist()
+    rows = [(a - 1, a, b, b, int(rng.integers(100, 400))) for a, b in ((a, a + int(rng.integers(6, 9))) for a in last)]
+    rows += [(a + 3, a + 3, W.NONE_OP, a + 4, 300) for a in last[::2]]       # temporaries while the tensors are away
+    tab = table(rows)
+    ev = W.transformer.events_of(tab)
+    peak = int(oracle.timeline_scan(ev, None, n_ops, 0, 0)["per_op"].max())
+    found = 0
+    for bpo in (1 << 30, 300):
+        c = make_ctx(P, staging_bytes=4096, link_bytes_per_op=bpo)
+        try:
+            for limit in (peak - 1, peak - 90, peak * 3 // 4, peak * 5 // 8, peak // 2):
+                found += bool(check_against_oracle(P, c, ops_with_phases(phases), phases, tab, ev, n_ops, limit, bpo, 24, 24))
+        finally:
+            P.ss_destroy(c)
+    assert found >= 2
+
+
 def test_edge_cases(P):
     c = make_ctx(P, staging_bytes=4096, link_bytes_per_op=1000)
     try:
