@@ -742,6 +742,7 @@ extern "C" int ss_match_sequence(ss_ctx *ctx, const ss_op_t *ref, uint32_t n, co
       if (k) SS_HIP(hipMemcpyAsync(d + o_anc, anchors, (size_t)k * sizeof(ss_anchor_t), hipMemcpyHostToDevice, s));
       p.ref = (const ss_op_t *)(d + o_ref);
       p.cur = (const ss_op_t *)(d + o_cur);
+      if (hist) p.n = p.m = 0;                               // nothing to read them for
     }
     const uint32_t clears = std::max(p.n_ones, p.n_zeros);
     const uint32_t prep_wgs = std::max(wgs, std::min(kMaxParts, clears / 2048));
