@@ -59,31 +59,46 @@ struct PrepArgs {
   CosinePart *part;          // one per workgroup
 };
 
+// kTogether: a thread reads four operators of each sequence together.  From device memory (500,000 of each one by one take
+// 25 us, together 6) and for short sequences from pinned memory, where the link's latency is what it takes (1,154 of each
+// 22.4 us a call, together 20.1; 8,000 27 to 29 and 25.5).  Long ones come over the link faster one by one (18,464 38.5 and
+// 38.0, 30,000 52.0 and 52.6, 65,536 96 and 105).
+constexpr uint32_t kTogetherMapped = 16384;
+
+template <bool kTogether>
 __global__ __launch_bounds__(256) void ss_prep_kernel(PrepArgs a) {
   const uint32_t stride = gridDim.x * 256, first = blockIdx.x * 256 + threadIdx.x, len = a.n > a.m ? a.n : a.m;
   uint64_t dot = 0, na = 0, nb = 0;
   uint32_t bad = 0;
-  // operators of each sequence that a thread reads together (one by one 500,000 operators of each take 25 us in place of 6)
-  constexpr uint32_t kAhead = 4;
-  for (uint32_t i0 = first; i0 < len; i0 += kAhead * stride) {
-    ss_op_t c[kAhead], r[kAhead];                        // the shorter sequence is padded with token 0
+  auto take = [&](uint32_t i, const ss_op_t &c, const ss_op_t &r) {
+    if (a.dcur && i < a.m) a.dcur[i] = c;
+    if (a.dref && i < a.n) a.dref[i] = r;
+    const uint64_t x = c.op_token, y = r.op_token;
+    if (x >= kTokenLimit || y >= kTokenLimit) bad = 1;
+    dot += x * y;
+    na += x * x;
+    nb += y * y;
+  };
+  if constexpr (kTogether) {
+    constexpr uint32_t kAhead = 4;
+    for (uint32_t i0 = first; i0 < len; i0 += kAhead * stride) {
+      ss_op_t c[kAhead], r[kAhead];                      // the shorter sequence is padded with token 0
 #pragma unroll
-    for (uint32_t u = 0; u < kAhead; ++u) {
-      const uint32_t i = i0 + u * stride;
-      c[u] = r[u] = ss_op_t{0, 0, 0, 0};
-      if (i < a.m) c[u] = a.cur[i];
-      if (i < a.n) r[u] = a.ref[i];
+      for (uint32_t u = 0; u < kAhead; ++u) {
+        const uint32_t i = i0 + u * stride;
+        c[u] = r[u] = ss_op_t{0, 0, 0, 0};
+        if (i < a.m) c[u] = a.cur[i];
+        if (i < a.n) r[u] = a.ref[i];
+      }
+#pragma unroll
+      for (uint32_t u = 0; u < kAhead; ++u) take(i0 + u * stride, c[u], r[u]);
     }
-#pragma unroll
-    for (uint32_t u = 0; u < kAhead; ++u) {
-      const uint32_t i = i0 + u * stride;
-      if (a.dcur && i < a.m) a.dcur[i] = c[u];
-      if (a.dref && i < a.n) a.dref[i] = r[u];
-      const uint64_t x = c[u].op_token, y = r[u].op_token;
-      if (x >= kTokenLimit || y >= kTokenLimit) bad = 1;
-      dot += x * y;
-      na += x * x;
-      nb += y * y;
+  } else {
+    for (uint32_t i = first; i < len; i += stride) {
+      ss_op_t c = {0, 0, 0, 0}, r = {0, 0, 0, 0};
+      if (i < a.m) c = a.cur[i];
+      if (i < a.n) r = a.ref[i];
+      take(i, c, r);
     }
   }
   if (a.danc)
@@ -746,7 +761,8 @@ extern "C" int ss_match_sequence(ss_ctx *ctx, const ss_op_t *ref, uint32_t n, co
     }
     const uint32_t clears = std::max(p.n_ones, p.n_zeros);
     const uint32_t prep_wgs = std::max(wgs, std::min(kMaxParts, clears / 2048));
-    hipLaunchKernelGGL(ss_prep_kernel, dim3(prep_wgs), dim3(256), 0, s, p);
+    if (mapped && len > kTogetherMapped) hipLaunchKernelGGL(ss_prep_kernel<false>, dim3(prep_wgs), dim3(256), 0, s, p);
+    else hipLaunchKernelGGL(ss_prep_kernel<true>, dim3(prep_wgs), dim3(256), 0, s, p);
     const uint32_t parts = hist ? 256 : prep_wgs;
     const ss_op_t *dref = (const ss_op_t *)(d + o_ref), *dcur = (const ss_op_t *)(d + o_cur);
     if (hist) {
