@@ -308,7 +308,7 @@ __device__ __forceinline__ void search_anchor(const AnchorArgs &g, uint32_t a, A
   }
 }
 
-// One workgroup per anchor.  Bound by the latency of the walks: 480 anchors of 1,154 operators 8.7 us, claims included; a
+// One workgroup per anchor.  Bound by the latency of the walks: 480 anchors of 1,154 operators 8.3 us, claims included; a
 // wavefront per anchor, all of both sequences in one walk, took 13.0 us and the claims 3.1 us in a launch of their own.
 __global__ __launch_bounds__(256) void ss_anchor_kernel(AnchorArgs g) {
   __shared__ AnchorShared sh;
