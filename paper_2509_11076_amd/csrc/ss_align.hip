@@ -1026,6 +1026,7 @@ int ss_align_core(ss_ctx *ctx, const ss_op_t *ref, uint32_t n, const ss_op_t *cu
 // For tests: the context's limit of a strip's wait, in looks at the word; returns how many of its calls have started the
 // strips one by one so far.
 extern "C" uint32_t ss_align_wait_limit(ss_ctx *ctx, uint32_t looks) {
+  if (!ctx) return 0;
   ctx->align_wait_looks = looks;
   return ctx->align_one_by_one;
 }
