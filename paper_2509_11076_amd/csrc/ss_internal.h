@@ -158,6 +158,8 @@ struct ss_ctx {
   std::unordered_map<std::string, uint32_t> stacks;
   // stage machine (Algo. 1)
   uint32_t stage = SS_STAGE_WARMUP, stable_step = 0;
+  void *d_board = nullptr;          // what the workgroups of a long scan tell each other (ss_scan.hip)
+  uint32_t scan_wait_ticks = 0;     // limit of their waits, 0 = the usual one
   // scratch for scan / match (device + pinned mirrors), grown on demand
   void *d_scratch = nullptr;
   size_t d_scratch_bytes = 0;
@@ -189,8 +191,9 @@ static inline uint64_t ss_align_up(uint64_t x, uint64_t a) { return (x + a - 1) 
 
 // scratch management (ss_runtime.hip)
 int ss_scratch_reserve(ss_ctx *ctx, size_t dev_bytes, size_t host_bytes);
-// address of the static scratch array of ss_timeline_scan_static on the context's device (ss_scan.hip)
-int ss_scan_static_init(ss_ctx *ctx);
+// address of the static scratch array of ss_timeline_scan_static on the context's device, and the context's own board
+// (ss_scan.hip)
+int ss_scan_init(ss_ctx *ctx);
 
 // internal entry used by the greedy generator: timing + schedule without loading it
 struct ss_applied {

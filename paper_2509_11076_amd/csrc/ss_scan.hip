@@ -10,16 +10,16 @@
 // and an event's place and total in the canonical order are its own list's running values plus differences of
 // OpAt entries at t and t + 1.  No accumulator is cleared and nothing is added atomically.
 //
-// Short traces: one workgroup keeps the events in registers and the OpAt table in LDS, one launch.  Long ones: three
-// launches over tiles of events (sums per tile; running sums and OpAt; operators and timeline).  A list that
+// Short traces: one workgroup keeps the events in registers and the OpAt table in LDS, one launch.  Long ones: two
+// launches over tiles of events (running sums and OpAt; operators and timeline).  A list that
 // turns out not to be in operator order is gathered per operator with 64-bit integer atomics instead
 // (order-independent, hence deterministic); it has no timeline.  So are the longer ones of a batch, one workgroup a scan,
 // in any order.
 //
 // Bound by latency: barriers and dependent loads in a short trace (124 + 24 events, 66 operators: 6.3 us in one
 // workgroup; with sums gathered by atomics, fences and running values in device memory 31 us), launches and one pass
-// each over the events in a long one (100,000 + 40,000 events with a timeline: 4.0 + 8.8 + 4.1 us; with operators
-// and timeline left to one workgroup 1,084 us; 1,048,574 + 20,014 events, 65,536 operators: 46 us, was 221).
+// each over the events in a long one (100,000 + 40,000 events with a timeline: 7.6 + 4.6 us; with operators
+// and timeline left to one workgroup 1,084 us; 1,048,574 + 20,014 events, 65,536 operators: 44 us, was 221).
 #include <algorithm>
 #include <cstring>
 
@@ -35,6 +35,20 @@ struct OpAt { int64_t sp, sn; uint32_t f, cp; };       // sums of positive / neg
 struct TileSum { int64_t sp, sn; uint32_t cp, flags; };
 struct Best { int64_t val; uint32_t idx, over; };
 
+constexpr uint64_t kMaxTiles = 1024;       // per list: a workgroup reads the sums of all tiles before its own
+constexpr uint32_t kMaxOpWgs = 256;
+
+// What the workgroups of a long trace tell each other.  A tile's sums are five words and a maximum is four, each with the
+// number of the scan in its upper half, so that a reader knows each word by itself for this scan's and neither side needs a
+// fence.  `scan` is the last one's number (the second launch sets it); nothing is ever cleared, and what an earlier
+// scan left, finished or not, is not taken for this one's.
+struct TileBoard {
+  uint32_t scan;
+  uint32_t done;              // workgroups of the second launch that have ended; the first sets it to 0
+  uint64_t tile[5][2 * kMaxTiles + 2];
+  uint64_t best[4][kMaxOpWgs];
+};
+
 struct ScanArgs {
   const ss_event_t *ev;    uint64_t n_ev;
   const ss_event_t *pev;   uint64_t n_pe;
@@ -45,13 +59,12 @@ struct ScanArgs {
   int64_t *pos, *net; // [n_ops] per-operator sums of a list out of order
   int64_t *sumx;      // [n_ev + n_pe] inclusive running sum of the event's own class in its list
   uint32_t *cntx;     // [n_ev + n_pe] events of its own class before it in its list
-  TileSum *tiles;     // [tiles of both lists]
-  Best *best;         // [blocks of operators]
-  uint32_t *ctl;      // [0] operator blocks done, [1] flags
+  TileBoard *board;
+  uint32_t wait_ticks;
   uint32_t tile[2];   // events per tile of ev, of pev
   uint32_t tiles0, tiles1;
-  // the tile sums read the events from here, if given, and copy them to ev / pev (without the tensor ids, which no
-  // kernel looks at)
+  // the first launch reads the events from here, if given, and copies them to ev / pev for the second (without the tensor
+  // ids, which no kernel looks at)
   const ss_event_t *src_ev, *src_pev;
   // outputs
   int64_t *per_op, *mre, *timeline;
@@ -471,7 +484,8 @@ __device__ __forceinline__ void scan_wg(const ScanArgs &a, OpAt *at, int64_t *po
 }
 
 // One workgroup takes a trace whose events fit its registers (four a lane) and whose two OpAt tables fit LDS (24 bytes
-// an entry).  Up to there it is the faster form: 6 to 12 us, the three launches of the other take 15 at least.
+// an entry).  Mostly it is the faster form: 6 to 12 us, the two launches of the other take 11 at least (4,090 events over 700
+// operators 15 and 11).
 constexpr uint32_t kLdsOps = 2900;
 constexpr uint64_t kSmallEvents = 4096;
 
@@ -499,11 +513,9 @@ __global__ __launch_bounds__(kThreads) void ss_scan_batch_kernel(const ScanArgs 
   }
 }
 
-// ---- long traces: three launches over tiles of events ---------------------------------------------------------------
+// ---- long traces: two launches over tiles of events -----------------------------------------------------------------
 
-constexpr int kTileThreads = 256, kTileK = 8;
-constexpr uint64_t kTileEvents = (uint64_t)kTileThreads * kTileK;
-constexpr uint64_t kMaxTiles = 1024;                  // per list: every workgroup reads all tiles' sums
+constexpr int kTileThreads = 256;
 
 // the tile of a workgroup: first the tiles of ev, then those of pev (at least one each)
 struct Tile {
@@ -524,87 +536,157 @@ struct Tile {
   }
 };
 
-// Sums of a tile; also clears what a list out of order would be gathered into.
-__global__ __launch_bounds__(kTileThreads) void ss_scan_tiles_kernel(ScanArgs a) {
-  __shared__ TileSum part[kTileThreads / 64];
-  const Tile tl(a);
-  for (uint64_t i = (uint64_t)blockIdx.x * kTileThreads + threadIdx.x; i < a.n_ops; i += (uint64_t)gridDim.x * kTileThreads)
-    a.pos[i] = a.net[i] = 0;
-  if (blockIdx.x == 0 && threadIdx.x == 0) a.ctl[0] = 0;
+// N words of entry `at`, 32 bits of content each
+template <int N, size_t L>
+__device__ __forceinline__ void tell(uint64_t (*words)[L], uint32_t at, uint32_t scan, const uint32_t (&x)[N]) {
+#pragma unroll
+  for (int w = 0; w < N; ++w)
+    __hip_atomic_store(&words[w][at], (uint64_t)scan << 32 | x[w], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
+// false: not all there yet
+template <int N, size_t L>
+__device__ __forceinline__ bool hear(const uint64_t (*words)[L], uint32_t at, uint32_t scan, uint32_t (&x)[N]) {
+  uint64_t y[N];
+#pragma unroll
+  for (int w = 0; w < N; ++w) y[w] = __hip_atomic_load(&words[w][at], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  bool all = true;
+#pragma unroll
+  for (int w = 0; w < N; ++w) {
+    x[w] = (uint32_t)y[w];
+    all &= (uint32_t)(y[w] >> 32) == scan;
+  }
+  return all;
+}
+
+__device__ __forceinline__ int64_t both_halves(uint32_t lo, uint32_t hi) { return (int64_t)((uint64_t)hi << 32 | lo); }
+__device__ __forceinline__ uint32_t low_half(int64_t v) { return (uint32_t)(uint64_t)v; }
+__device__ __forceinline__ uint32_t high_half(int64_t v) { return (uint32_t)((uint64_t)v >> 32); }
+
+__device__ __forceinline__ void put_tile(TileBoard *b, uint32_t tile, uint32_t scan, const TileSum &s) {
+  const uint32_t x[5] = {low_half(s.sp), high_half(s.sp), low_half(s.sn), high_half(s.sn), s.flags << 30 | s.cp};   // cp < 2^22
+  tell(b->tile, tile, scan, x);
+}
+
+__device__ __forceinline__ bool get_tile(const TileBoard *b, uint32_t tile, uint32_t scan, TileSum &s) {
+  uint32_t x[5];
+  const bool there = hear(b->tile, tile, scan, x);
+  s = TileSum{both_halves(x[0], x[1]), both_halves(x[2], x[3]), x[4] & 0x3FFFFFFFu, x[4] >> 30};
+  return there;
+}
+
+// sums over the workgroup, given in every thread
+__device__ __forceinline__ TileSum wg_total(int64_t sp, int64_t sn, uint32_t cp, uint32_t flags, TileSum *part) {
+  sp = lane_i64(wave_scan(sp), 63);
+  sn = lane_i64(wave_scan(sn), 63);
+  const int64_t c = lane_i64(wave_scan((int64_t)cp), 63);
+  flags = (__ballot(flags & 1u) ? 1u : 0u) | (__ballot(flags & 2u) ? 2u : 0u);
+  if ((threadIdx.x & 63) == 0) part[threadIdx.x >> 6] = TileSum{sp, sn, (uint32_t)c, flags};
+  __syncthreads();
+  TileSum s = part[0];
+  for (int i = 1; i < kTileThreads / 64; ++i) {
+    s.sp += part[i].sp; s.sn += part[i].sn; s.cp += part[i].cp; s.flags |= part[i].flags;
+  }
+  __syncthreads();                                           // part may be written again
+  return s;
+}
+
+// Sums over events [lo, hi) of the workgroup's list; `copy`: also to where the second launch reads them.
+template <int K>
+__device__ __forceinline__ TileSum sum_events(const ScanArgs &a, const Tile &tl, uint64_t lo, uint64_t hi, bool copy, TileSum *part) {
   int64_t sp = 0, sn = 0;
   uint32_t cp = 0, flags = 0;
-  for (uint64_t lo = tl.lo; lo < tl.hi; lo += kTileEvents) {
-    Elem x[kTileK];
-    flags |= load_events<kTileThreads, kTileK>(tl.src ? tl.src : tl.L, tl.cnt, nullptr, 0, lo, tl.hi, a.n_ops, x);
+  for (; lo < hi; lo += (uint64_t)kTileThreads * K) {
+    Elem x[K];
+    flags |= load_events<kTileThreads, K>(tl.src ? tl.src : tl.L, tl.cnt, nullptr, 0, lo, hi, a.n_ops, x);
 #pragma unroll
-    for (int k = 0; k < kTileK; ++k) {
-      if (tl.src && x[k].live)
+    for (int k = 0; k < K; ++k) {
+      if (copy && x[k].live)
         const_cast<ss_event_t *>(tl.L)[lo + (uint64_t)k * kTileThreads + threadIdx.x] = ss_event_t{x[k].op, 0, x[k].delta};
       sp += x[k].pos ? x[k].delta : 0;
       sn += x[k].pos ? 0 : x[k].delta;
       cp += x[k].pos;
     }
   }
-  sp = lane_i64(wave_scan(sp), 63);
-  sn = lane_i64(wave_scan(sn), 63);
-  const int64_t c = lane_i64(wave_scan((int64_t)cp), 63);
-  flags = (__ballot(flags & 1u) ? 1u : 0u) | (__ballot(flags & 2u) ? 2u : 0u);
-  if ((threadIdx.x & 63) == 0) part[threadIdx.x >> 6] = TileSum{sp, sn, (uint32_t)c, flags};
-  __syncthreads();
-  if (threadIdx.x == 0) {
-    TileSum s = part[0];
-    for (int i = 1; i < kTileThreads / 64; ++i) {
-      s.sp += part[i].sp; s.sn += part[i].sn; s.cp += part[i].cp; s.flags |= part[i].flags;
-    }
-    a.tiles[tl.index] = s;
-  }
+  return wg_total(sp, sn, cp, flags, part);
 }
 
-// Running sums along each list: OpAt, and for a timeline each event's own.
+// How long a workgroup waits for the sums of the tiles before its own (10 ns each).  They belong to workgroups that are
+// started before it and wait for no later one, so it sees them within a few us; should one of them not run all the same,
+// it adds up their events itself, and no wait depends on another workgroup's progress.
+constexpr uint32_t kTileWaitTicks = 10000;
+
+// Running sums along each list: OpAt, and for a timeline each event's own.  Also clears what a list out of order is
+// gathered into.  A workgroup works out its tile, tells its sums, and takes up those of the tiles before it: one launch and
+// one pass over the events where the sums had a launch of their own (100,000 + 40,000 events with a timeline 7.6 us in
+// place of 4.1 + 9.1, a launch of about 2.5 and the second loading of the events; 1,048,574 + 20,014 events 30.4 in place of
+// 7.4 + 25.5, the filling of gaps being the most of it).
+template <int K, bool kOnce>
 __global__ __launch_bounds__(kTileThreads) void ss_scan_running_kernel(ScanArgs a) {
   __shared__ SumShared sh;
   __shared__ TileSum part[kTileThreads / 64];
   const Tile tl(a);
+  const uint32_t scan = a.board->scan + 1, tid = threadIdx.x;
   OpAt *const at = a.at + (tl.policy ? (size_t)a.n_ops + 1 : 0);
-  int64_t sp = 0, sn = 0;
-  uint32_t cp = 0, flags = 0;
-  for (uint32_t i = threadIdx.x; i < a.tiles0 + a.tiles1; i += kTileThreads) {
-    const TileSum s = a.tiles[i];
-    flags |= s.flags;
-    if (i >= tl.first && i < tl.index) { sp += s.sp; sn += s.sn; cp += s.cp; }
+  Elem x[K];
+  int64_t delta[K], xsp[K], xsn[K];
+  uint32_t xcp[K];
+  bool pos[K];
+  TileSum mine;
+  auto sums = [&](int64_t sp, int64_t sn, uint32_t cp) {
+#pragma unroll
+    for (int k = 0; k < K; ++k) { delta[k] = x[k].delta; pos[k] = x[k].pos; }
+    wg_sums<kTileThreads, K>(sh, delta, pos, sp, sn, cp, xsp, xsn, xcp);
+  };
+  if constexpr (kOnce) {
+    const uint32_t f = load_events<kTileThreads, K>(tl.src ? tl.src : tl.L, tl.cnt, nullptr, 0, tl.lo, tl.hi, a.n_ops, x);
+    const uint32_t flags = (__ballot(f & 1u) ? 1u : 0u) | (__ballot(f & 2u) ? 2u : 0u);
+    if ((tid & 63) == 0) part[tid >> 6].flags = flags;
+    sums(0, 0, 0);
+    mine = TileSum{sh.tot_sp, sh.tot_sn, sh.tot_cp, 0};
+    for (int i = 0; i < kTileThreads / 64; ++i) mine.flags |= part[i].flags;
+  } else {
+    mine = sum_events<K>(a, tl, tl.lo, tl.hi, tl.src != nullptr, part);
   }
-  sp = lane_i64(wave_scan(sp), 63);
-  sn = lane_i64(wave_scan(sn), 63);
-  const int64_t c = lane_i64(wave_scan((int64_t)cp), 63);
-  flags = (__ballot(flags & 1u) ? 1u : 0u) | (__ballot(flags & 2u) ? 2u : 0u);
-  if ((threadIdx.x & 63) == 0) part[threadIdx.x >> 6] = TileSum{sp, sn, (uint32_t)c, flags};
-  __syncthreads();
-  TileSum before = part[0];
-  for (int i = 1; i < kTileThreads / 64; ++i) {
-    before.sp += part[i].sp; before.sn += part[i].sn; before.cp += part[i].cp; before.flags |= part[i].flags;
-  }
-  if (blockIdx.x == 0 && threadIdx.x == 0) a.ctl[1] = before.flags;
-  if (before.flags & 1u) return;
+  if (tid == 0) put_tile(a.board, tl.index, scan, mine);
+  if (blockIdx.x == 0 && tid == 0) a.board->done = 0;
+  for (uint64_t i = (uint64_t)blockIdx.x * kTileThreads + tid; i < a.n_ops; i += (uint64_t)gridDim.x * kTileThreads)
+    a.pos[i] = a.net[i] = 0;
   if (!tl.cnt)
-    for (uint32_t t = threadIdx.x; t <= a.n_ops; t += kTileThreads) at[t] = OpAt{0, 0, 0, 0};
-  for (uint64_t lo = tl.lo; lo < tl.hi; lo += kTileEvents) {
-    Elem x[kTileK];
-    load_events<kTileThreads, kTileK>(tl.L, tl.cnt, nullptr, 0, lo, tl.hi, a.n_ops, x);
-    if (before.flags & 2u) {
+    for (uint32_t t = tid; t <= a.n_ops; t += kTileThreads) at[t] = OpAt{0, 0, 0, 0};
+  if (kOnce && tl.src) {
 #pragma unroll
-      for (int k = 0; k < kTileK; ++k) gather_run(a.pos, a.net, x[k], a.n_ops);
-      continue;
+    for (int k = 0; k < K; ++k)
+      if (x[k].live) const_cast<ss_event_t *>(tl.L)[tl.lo + (uint64_t)k * kTileThreads + tid] = ss_event_t{x[k].op, 0, x[k].delta};
+  }
+  if (mine.flags) return;                                    // an operator out of range, or to be gathered
+  TileSum before = {0, 0, 0, 0};
+  if (tl.index != tl.first) {
+    bool there = true;
+    const uint64_t since = wall_clock64();
+    for (uint32_t i = tl.first + tid; there && i < tl.index; i += kTileThreads) {
+      TileSum s;
+      while (!get_tile(a.board, i, scan, s))
+        if (wall_clock64() - since > a.wait_ticks) { there = false; break; }
+      before.sp += s.sp; before.sn += s.sn; before.cp += s.cp; before.flags |= s.flags;
     }
-    int64_t delta[kTileK], xsp[kTileK], xsn[kTileK];
-    uint32_t xcp[kTileK];
-    bool pos[kTileK];
+    __syncthreads();                                         // everyone has read its part
+    before = wg_total(before.sp, before.sn, before.cp, before.flags, part);
+    if (__syncthreads_or(!there)) before = sum_events<K>(a, tl, 0, tl.lo, false, part);
+  }
+  if (before.flags) return;
+  for (uint64_t lo = tl.lo; lo < tl.hi; lo += (uint64_t)kTileThreads * K) {
+    if constexpr (kOnce) {
 #pragma unroll
-    for (int k = 0; k < kTileK; ++k) { delta[k] = x[k].delta; pos[k] = x[k].pos; }
-    wg_sums<kTileThreads, kTileK>(sh, delta, pos, before.sp, before.sn, before.cp, xsp, xsn, xcp);
-    before.sp = sh.tot_sp; before.sn = sh.tot_sn; before.cp = sh.tot_cp;
+      for (int k = 0; k < K; ++k) { xsp[k] += before.sp; xsn[k] += before.sn; xcp[k] += before.cp; }
+    } else {
+      load_events<kTileThreads, K>(tl.L, tl.cnt, nullptr, 0, lo, tl.hi, a.n_ops, x);
+      sums(before.sp, before.sn, before.cp);
+      before.sp = sh.tot_sp; before.sn = sh.tot_sn; before.cp = sh.tot_cp;
+    }
 #pragma unroll
-    for (int k = 0; k < kTileK; ++k) {
-      const uint64_t e = lo + (uint64_t)k * kTileThreads + threadIdx.x;
+    for (int k = 0; k < K; ++k) {
+      const uint64_t e = lo + (uint64_t)k * kTileThreads + tid;
       if (a.want_timeline && x[k].live) {
         a.sumx[tl.out0 + e] = (pos[k] ? xsp[k] : xsn[k]) + delta[k];
         a.cntx[tl.out0 + e] = pos[k] ? xcp[k] : (uint32_t)e - xcp[k];
@@ -615,26 +697,61 @@ __global__ __launch_bounds__(kTileThreads) void ss_scan_running_kernel(ScanArgs 
   }
 }
 
-// Operators (workgroups [0, op_wgs)) and, for a timeline, events (the rest).  The last operator workgroup to end folds
-// all their maxima.
+constexpr int kGatherK = 1;
+
+// true in the workgroup that ends last of `wgs` that call this; what the others wrote before is visible to it
+__device__ __forceinline__ bool ends_last(TileBoard *b, uint32_t wgs, uint32_t *s_last) {
+  __builtin_amdgcn_s_waitcnt(0x0F70);                        // vmcnt(0): this wavefront's stores and atomics are complete
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    __threadfence();                                         // for the workgroup (one fence each: 64 workgroups' 1,024 took 14 us)
+    *s_last = atomicAdd(&b->done, 1u) + 1 == wgs;
+  }
+  __syncthreads();
+  if (!*s_last) return false;
+  __threadfence();
+  return true;
+}
+
+// Operators (workgroups [0, op_wgs)) and, for a timeline, events (those from op_wgs on).  The first operator workgroup folds
+// all their maxima; it waits for each as the tiles do, and goes through the operators of one that doesn't come itself.
+// (With a fence and a counter, the last one folding: two operator workgroups 6 us more than one.)  Lists out of order are
+// gathered by all workgroups, and the last one to end does the operators.
 __global__ __launch_bounds__(kThreads) void ss_scan_finish_kernel(ScanArgs a, uint32_t op_wgs) {
   __shared__ Best part[kWaves];
   __shared__ SumShared sh;
-  __shared__ uint32_t s_last;
-  const uint32_t n = a.n_ops, tid = threadIdx.x, flags = a.ctl[1];
+  __shared__ uint32_t s_last, s_flags[kWaves];
+  const uint32_t n = a.n_ops, tid = threadIdx.x;
+  const uint32_t scan = (uint32_t)(a.board->tile[4][0] >> 32);      // this scan's number, as the first launch used it
+  if (blockIdx.x == 0 && tid == 0) a.board->scan = scan;
+  const uint64_t total = a.n_ev + a.n_pe;
   const OpAt *const at_ev = a.at, *const at_pe = a.at + n + 1;
+  uint32_t flags = 0;
+  for (uint32_t i = tid; i < a.tiles0 + a.tiles1; i += kThreads) flags |= (uint32_t)a.board->tile[4][i] >> 30;
+  flags = (__ballot(flags & 1u) ? 1u : 0u) | (__ballot(flags & 2u) ? 2u : 0u);
+  if ((tid & 63) == 0) s_flags[tid >> 6] = flags;
+  __syncthreads();
+  flags = 0;
+  for (int i = 0; i < kWaves; ++i) flags |= s_flags[i];
+  if (flags & 1u) {
+    if (blockIdx.x == 0 && tid == 0) write_result(a, no_best(), a.base, flags);
+    return;
+  }
   if (flags) {
-    if (blockIdx.x) return;
-    Best b = no_best();
-    if (!(flags & 1u)) {
-      b = ops_of_sums<kThreads>(a, a.pos, a.net, sh);
-      b = wg_best<kThreads>(b, part);
+    for (uint64_t first = (uint64_t)blockIdx.x * kThreads * kGatherK; first < total; first += (uint64_t)gridDim.x * kThreads * kGatherK) {
+      Elem x[kGatherK];
+      load_events<kThreads, kGatherK>(a.ev, a.n_ev, a.pev, a.n_pe, first, total, n, x);
+#pragma unroll
+      for (int k = 0; k < kGatherK; ++k) gather_run(a.pos, a.net, x[k], n);
     }
-    if (tid == 0) write_result(a, b, a.base + (n && !(flags & 1u) ? sh.tot_sp : 0), flags);
+    if (!ends_last(a.board, gridDim.x, &s_last)) return;
+    Best b = ops_of_sums<kThreads>(a, a.pos, a.net, sh);
+    b = wg_best<kThreads>(b, part);
+    if (tid == 0) write_result(a, b, a.base + (n ? sh.tot_sp : 0), flags);
     return;
   }
   if (blockIdx.x >= op_wgs) {
-    const uint64_t total = a.n_ev + a.n_pe;
+    if (!a.want_timeline) return;
     for (uint64_t i = (uint64_t)(blockIdx.x - op_wgs) * kThreads + tid; i < total; i += (uint64_t)(gridDim.x - op_wgs) * kThreads) {
       const bool policy = i >= a.n_ev;
       const ss_event_t x = policy ? a.pev[i - a.n_ev] : a.ev[i];
@@ -643,38 +760,48 @@ __global__ __launch_bounds__(kThreads) void ss_scan_finish_kernel(ScanArgs a, ui
     }
     return;
   }
-  Best b = no_best();
-  for (uint32_t t = blockIdx.x * kThreads + tid; t < n; t += op_wgs * kThreads)
-    put_op(a, t, a.base + at_ev[t + 1].sp + at_pe[t + 1].sp + at_ev[t].sn + at_pe[t].sn, b);
-  b = wg_best<kThreads>(b, part);
-  const int64_t final_total = a.base + at_ev[n].sp + at_ev[n].sn + at_pe[n].sp + at_pe[n].sn;
-  if (op_wgs > 1) {
-    if (tid == 0) {
-      a.best[blockIdx.x] = b;
-      __threadfence();
-      s_last = atomicAdd(a.ctl, 1u) + 1 == op_wgs;
-    }
-    __syncthreads();
-    if (!s_last) return;
-    __threadfence();
-    b = no_best();
-    for (uint32_t i = tid; i < op_wgs; i += kThreads) better(b, a.best[i]);
-    __syncthreads();
-    b = wg_best<kThreads>(b, part);
+  auto operators = [&](uint32_t first, uint32_t step) {
+    Best b = no_best();
+    for (uint32_t t = first; t < n; t += step)
+      put_op(a, t, a.base + at_ev[t + 1].sp + at_pe[t + 1].sp + at_ev[t].sn + at_pe[t].sn, b);
+    return b;
+  };
+  Best b = wg_best<kThreads>(operators(blockIdx.x * kThreads + tid, op_wgs * kThreads), part);
+  if (blockIdx.x) {
+    const uint32_t x[4] = {low_half(b.val), high_half(b.val), b.idx, b.over};
+    if (tid == 0) tell(a.board->best, blockIdx.x, scan, x);
+    return;
   }
-  if (tid == 0) write_result(a, b, final_total, 0);
+  if (op_wgs > 1) {
+    Best other = tid == 0 ? b : no_best();
+    bool there = true;
+    if (tid && tid < op_wgs) {
+      const uint64_t since = wall_clock64();
+      uint32_t x[4];
+      while (!hear(a.board->best, tid, scan, x))
+        if (wall_clock64() - since > a.wait_ticks) { there = false; break; }
+      other = Best{both_halves(x[0], x[1]), x[2], x[3]};
+    }
+    if (__syncthreads_or(!there)) other = operators(tid, kThreads);
+    b = wg_best<kThreads>(other, part);
+  }
+  if (tid == 0) write_result(a, b, a.base + at_ev[n].sp + at_ev[n].sn + at_pe[n].sp + at_pe[n].sn, 0);
 }
 
-constexpr uint32_t kMaxOpWgs = 256;
-
-// Events of a tile: as many as a workgroup takes in a pass, or more to stay within kMaxTiles (256 to a tile and so eight
-// times as many sums for every workgroup to read: the running sums of 140,000 events 13.9 us against 9.1).  But where
-// operators outnumber the events, filling the gaps between them is the work (a wavefront fills gaps above kAlone one
+// Events of a tile.  Few to a lane is the faster form as long as there are no more tiles than a workgroup may read (the
+// two launches of 140,000 events: two to a lane 12.2 us, four 13.1, eight 15.8; the first of 1,068,588 events: two, in two
+// passes, 30.4 us, four 32.1, eight 42.9), so a lane gets two, or four, and beyond that a tile takes several passes of eight.
+// Where operators outnumber the events, filling the gaps between them is the work (a wavefront fills gaps above kAlone one
 // after the other), and few events to a tile spread it: 60,000 operators with 40,000 events and 2,000 of the policy
 // 82 -> 40 us, with 6,000 and 200 66 -> 41.
-uint32_t tile_events(uint64_t n, uint32_t n_ops) {
+int events_per_lane(uint64_t n) {
+  return n <= kMaxTiles * kTileThreads * 2 ? 2 : n <= kMaxTiles * kTileThreads * 4 ? 4 : 8;
+}
+
+uint32_t tile_events(uint64_t n, uint32_t n_ops, int per_lane) {
   if (n_ops > 2 * n) return (uint32_t)std::max<uint64_t>(8, ss_align_up((n + 255) / 256, 8));
-  return (uint32_t)std::max(kTileEvents, ss_align_up((n + kMaxTiles - 1) / kMaxTiles, kTileEvents));
+  const uint64_t pass = (uint64_t)kTileThreads * per_lane;
+  return (uint32_t)std::max(pass, ss_align_up((n + kMaxTiles - 1) / kMaxTiles, pass));
 }
 
 bool is_short(uint64_t n_ev, uint64_t n_pe, uint32_t n_ops) { return n_ev + n_pe <= kSmallEvents && n_ops <= kLdsOps; }
@@ -690,17 +817,13 @@ size_t scan_scratch(ScanArgs *a, uint8_t *d, uint64_t n_ev, uint64_t n_pe, uint6
   auto take = [&](size_t bytes) { uint8_t *p = d + off; off += ss_align_up(bytes, 256); return p; };
   const uint64_t E = timeline ? n_ev + n_pe : 0;
   uint8_t *at = take(2 * (n_ops + 1) * sizeof(OpAt)), *pos = take(n_ops * 8), *net = take(n_ops * 8);
-  uint8_t *sumx = take(E * 8), *cntx = take(E * 4), *tiles = take((2 * kMaxTiles + 2) * sizeof(TileSum));
-  uint8_t *best = take(kMaxOpWgs * sizeof(Best)), *ctl = take(8);
+  uint8_t *sumx = take(E * 8), *cntx = take(E * 4);
   if (a) {
     a->at = (OpAt *)at;
     a->pos = (int64_t *)pos;
     a->net = (int64_t *)net;
     a->sumx = (int64_t *)sumx;
     a->cntx = (uint32_t *)cntx;
-    a->tiles = (TileSum *)tiles;
-    a->best = (Best *)best;
-    a->ctl = (uint32_t *)ctl;
   }
   return off;
 }
@@ -713,15 +836,20 @@ void launch_scan(hipStream_t s, ScanArgs &a) {
       hipLaunchKernelGGL(ss_scan_small_kernel<kThreads>, dim3(1), dim3(kThreads), lds_at(a.n_ops), s, a);
     return;
   }
-  a.tile[0] = tile_events(a.n_ev, a.n_ops);
-  a.tile[1] = tile_events(a.n_pe, a.n_ops);
+  const int per_lane = events_per_lane(std::max(a.n_ev, a.n_pe));
+  a.tile[0] = tile_events(a.n_ev, a.n_ops, per_lane);
+  a.tile[1] = tile_events(a.n_pe, a.n_ops, per_lane);
+  if (!a.wait_ticks) a.wait_ticks = kTileWaitTicks;
   a.tiles0 = (uint32_t)std::max<uint64_t>(1, (a.n_ev + a.tile[0] - 1) / a.tile[0]);
   a.tiles1 = (uint32_t)std::max<uint64_t>(1, (a.n_pe + a.tile[1] - 1) / a.tile[1]);
   const uint32_t tiles = a.tiles0 + a.tiles1;
   const uint32_t op_wgs = (uint32_t)std::min<uint64_t>(kMaxOpWgs, std::max<uint64_t>(1, ((uint64_t)a.n_ops + kThreads - 1) / kThreads));
-  const uint32_t ev_wgs = a.want_timeline ? (uint32_t)std::min<uint64_t>(2048, (a.n_ev + a.n_pe + kThreads - 1) / kThreads) : 0;
-  hipLaunchKernelGGL(ss_scan_tiles_kernel, dim3(tiles), dim3(kTileThreads), 0, s, a);
-  hipLaunchKernelGGL(ss_scan_running_kernel, dim3(tiles), dim3(kTileThreads), 0, s, a);
+  // without a timeline these are there for lists out of order only, and end at once where there are none
+  const uint64_t per_wg = a.want_timeline ? kThreads : kGatherK * kThreads;
+  const uint32_t ev_wgs = (uint32_t)std::min<uint64_t>(2048, (a.n_ev + a.n_pe + per_wg - 1) / per_wg);
+  if (per_lane == 2) hipLaunchKernelGGL((ss_scan_running_kernel<2, true>), dim3(tiles), dim3(kTileThreads), 0, s, a);
+  else if (per_lane == 4) hipLaunchKernelGGL((ss_scan_running_kernel<4, true>), dim3(tiles), dim3(kTileThreads), 0, s, a);
+  else hipLaunchKernelGGL((ss_scan_running_kernel<8, false>), dim3(tiles), dim3(kTileThreads), 0, s, a);
   hipLaunchKernelGGL(ss_scan_finish_kernel, dim3(op_wgs + ev_wgs), dim3(kThreads), 0, s, a, op_wgs);
 }
 
@@ -730,14 +858,15 @@ void launch_scan(hipStream_t s, ScanArgs &a) {
 // ---- the scan for callers that cannot allocate ------------------------------------------------
 //
 // Same kernels, but their scratch lies in a static device array instead of memory the library allocates, and inputs
-// and outputs are the caller's device arrays: the call only enqueues the scan's kernels (one, or three for a long
+// and outputs are the caller's device arrays: the call only enqueues the scan's kernels (one, or two for a long
 // trace) on the caller's stream.
 
 constexpr uint32_t kStaticMaxOps = 65536;
 constexpr uint64_t kStaticMaxEvents = 262144;
-constexpr size_t kStaticBytes = 2 * (kStaticMaxOps + 1) * sizeof(OpAt) + 2 * kStaticMaxOps * 8 + kStaticMaxEvents * 12 +
-                                (2 * kMaxTiles + 2) * sizeof(TileSum) + kMaxOpWgs * sizeof(Best) + 8 * 256;
-static __device__ __align__(256) uint8_t scratch[kStaticBytes];
+constexpr size_t kBoardBytes = (sizeof(TileBoard) + 255) / 256 * 256;
+constexpr size_t kStaticBytes = kBoardBytes + 2 * (kStaticMaxOps + 1) * sizeof(OpAt) + 2 * kStaticMaxOps * 8 +
+                                kStaticMaxEvents * 12 + 8 * 256;
+static __device__ __align__(256) uint8_t scratch[kStaticBytes];          // starts as zeros: so does the board at its front
 
 // Address of `scratch` on each device (the name itself is only a host-side handle): resolved once
 // per device, with that device current.
@@ -760,12 +889,16 @@ static int static_scratch_ptr(int device, uint8_t **out, hipError_t *err) {
   return SS_OK;
 }
 
-int ss_scan_static_init(ss_ctx *ctx) {
+int ss_scan_init(ss_ctx *ctx) {
   uint8_t *p;
   hipError_t e;
   const int rc = static_scratch_ptr(ctx->device, &p, &e);
   if (rc == SS_E_HIP) SS_HIP(e);
-  return rc;
+  if (rc != SS_OK) return rc;
+  SS_HIP(hipMalloc(&ctx->d_board, sizeof(TileBoard)));
+  SS_HIP(hipMemset(ctx->d_board, 0, sizeof(TileBoard)));
+  SS_HIP(hipStreamSynchronize(nullptr));
+  return SS_OK;
 }
 
 extern "C" int ss_timeline_scan_static(ss_ctx *ctx, void *stream, const ss_event_t *d_ev, uint64_t n_ev,
@@ -788,7 +921,8 @@ extern "C" int ss_timeline_scan_static(ss_ctx *ctx, void *stream, const ss_event
   a.pev = d_pev; a.n_pe = n_pe;
   a.n_ops = n_ops; a.want_timeline = d_timeline != nullptr;
   a.base = base; a.budget = budget;
-  scan_scratch(&a, d, n_ev, n_pe, n_ops, true);              // at most kStaticBytes
+  a.board = (TileBoard *)d;
+  scan_scratch(&a, d + kBoardBytes, n_ev, n_pe, n_ops, true);          // at most kStaticBytes
   a.per_op = d_per_op; a.mre = d_mre; a.timeline = d_timeline;
   a.res = d_res;
   launch_scan((hipStream_t)stream, a);
@@ -914,7 +1048,11 @@ extern "C" int ss_timeline_scan(ss_ctx *ctx, const ss_event_t *ev, uint64_t n_ev
       if (n_ev) SS_HIP(hipMemcpyAsync(d + o_ev, ev, ev_bytes, hipMemcpyHostToDevice, s));
       if (n_pe) SS_HIP(hipMemcpyAsync(d + o_pev, pev, pe_bytes, hipMemcpyHostToDevice, s));
     }
-    if (!is_small) scan_scratch(&a, d + o_scratch, n_ev, n_pe, n, timeline != nullptr);
+    if (!is_small) {
+      scan_scratch(&a, d + o_scratch, n_ev, n_pe, n, timeline != nullptr);
+      a.board = (TileBoard *)ctx->d_board;
+      a.wait_ticks = ctx->scan_wait_ticks;
+    }
     a.per_op = per_op ? (int64_t *)(out + o_perop) : nullptr;
     a.mre = mre ? (int64_t *)(out + o_mre) : nullptr;
     a.timeline = timeline ? (int64_t *)(out + o_tl) : nullptr;
@@ -942,4 +1080,9 @@ extern "C" int ss_timeline_scan(ss_ctx *ctx, const ss_event_t *ev, uint64_t n_ev
     if (timeline && !tl_ok) return SS_E_ORDER;
     return SS_OK;
   });
+}
+
+// For tests: how long a workgroup of the context's long scans waits for a tile's sums (10 ns each; 0 = the usual time).
+extern "C" void ss_scan_wait_limit(ss_ctx *ctx, uint32_t ticks) {
+  if (ctx) ctx->scan_wait_ticks = ticks;
 }

@@ -1,5 +1,5 @@
 """GPU parity of the timeline scan where its kernels change form: one workgroup with its tables in LDS (256 or 1,024
-lanes), tiles over three launches, lists in and out of operator order, operators without events, empty lists, deltas of
+lanes), tiles over two launches, lists in and out of operator order, operators without events, empty lists, deltas of
 zero.  Exact comparison with the oracle."""
 import numpy as np
 import pytest
@@ -39,7 +39,7 @@ def both_ways(P, ctx, ev, pe, n_ops, base, budget):               # noqa: F811
 @pytest.mark.parametrize("n_ev,n_pe,n_ops", [
     (1, 0, 1), (0, 1, 3), (63, 1, 5), (64, 64, 64), (1000, 24, 66), (1000, 25, 66),          # 256 lanes | 1,024 lanes
     (255, 257, 2900), (255, 257, 2901),                                                      # LDS tables | device tables
-    (4096, 0, 700), (4000, 97, 700), (0, 4097, 700), (2048, 2049, 3000),                     # one launch | three
+    (4096, 0, 700), (4000, 97, 700), (0, 4097, 700), (2048, 2049, 3000),                     # one launch | two
     (2047, 3000, 40), (6144, 2048, 9000), (40, 7, 60001), (30000, 20000, 1),
     (3000, 2050, 6000), (3000, 2050, 6001), (2049, 2048, 40000), (20000, 3, 65536),          # small tiles where gaps are wide
 ])
@@ -118,3 +118,19 @@ def test_batch_lists_out_of_order_from_the_start_or_late(P, ctx, n_ops):        
             with pytest.raises(P.SsError) as e:
                 P.ss_timeline_scan_batch(ctx, late[0] if late[1] is a else a, [None, late[0] if late[1] is b else b], n_ops, 11, 1 << 40)
             assert e.value.code == P.SS_E_INVAL
+
+
+@pytest.mark.parametrize("n_ev,n_pe,n_ops", [
+    (4096, 513, 700), (4607, 512, 700), (5121, 0, 9),                                # tiles of 512 events and their edges
+    (524288, 512, 500), (524289, 1025, 500), (1048576, 0, 40), (1048577, 3, 40),     # two a lane | four | passes of eight
+])
+def test_tiles_take_up_the_sums_before_them(P, ctx, n_ev, n_pe, n_ops):              # noqa: F811
+    """each form with the usual wait for the tiles before, and with none: then a workgroup adds up their events itself"""
+    import ctypes
+    lib = P._lib
+    lib.ss_scan_wait_limit.argtypes, lib.ss_scan_wait_limit.restype = [ctypes.c_void_p, ctypes.c_uint32], None
+    rng = np.random.default_rng([n_ev, n_pe, n_ops, 3])
+    ev, pe = events(rng, n_ev, n_ops), events(rng, n_pe, n_ops, runs=True)
+    ora = both_ways(P, ctx, ev, pe, n_ops, 5, 1 << 41)
+    lib.ss_scan_wait_limit(ctx, 1)
+    assert_scan_equal(P.ss_timeline_scan(ctx, ev, pe, n_ops, 5, 1 << 41, want_timeline=True), ora)
