@@ -16,7 +16,7 @@
 // (order-independent, hence deterministic); it has no timeline.  So are the longer ones of a batch, one workgroup a scan,
 // in any order.
 //
-// Bound by latency: barriers and dependent loads in a short trace (124 + 24 events, 66 operators: 6.3 us in one
+// Bound by latency: barriers and dependent loads in a short trace (124 + 24 events, 66 operators: 4.3 us in one
 // workgroup; with sums gathered by atomics, fences and running values in device memory 31 us), launches and one pass
 // each over the events in a long one (100,000 + 40,000 events with a timeline: 7.6 + 4.6 us; with operators
 // and timeline left to one workgroup 1,084 us; 1,048,574 + 20,014 events, 65,536 operators: 44 us, was 221).
@@ -82,7 +82,23 @@ __device__ __forceinline__ int64_t dpp_i64(int64_t v) {
   return (int64_t)(((uint64_t)(uint32_t)hi << 32) | (uint32_t)lo);
 }
 
+// the same over 32 bits, `none` where there is no such lane
+template <int kCtrl, int kRows>
+__device__ __forceinline__ uint32_t dpp_u32(uint32_t v, uint32_t none) {
+  return (uint32_t)__builtin_amdgcn_update_dpp((int)none, (int)v, kCtrl, kRows, 0xF, false);
+}
+
 // inclusive prefix sum over the 64 lanes: within rows of 16, then the rows' last lanes handed on
+__device__ __forceinline__ uint32_t wave_scan_u32(uint32_t v) {
+  v += dpp_u32<0x111, 0xF>(v, 0);
+  v += dpp_u32<0x112, 0xF>(v, 0);
+  v += dpp_u32<0x114, 0xF>(v, 0);
+  v += dpp_u32<0x118, 0xF>(v, 0);
+  v += dpp_u32<0x142, 0xA>(v, 0);
+  v += dpp_u32<0x143, 0xC>(v, 0);
+  return v;
+}
+
 __device__ __forceinline__ int64_t wave_scan(int64_t v) {
   v += dpp_i64<0x111, 0xF>(v);
   v += dpp_i64<0x112, 0xF>(v);
@@ -112,22 +128,39 @@ __device__ __forceinline__ void better(Best &a, const Best &b) {
   a.over += b.over;
 }
 
-__device__ __forceinline__ Best wave_best(Best b) {
-#pragma unroll
-  for (int d = 32; d >= 1; d >>= 1) {
-    Best o;
-    o.val = (int64_t)(((uint64_t)(uint32_t)__shfl_xor((int)((uint64_t)b.val >> 32), d, 64) << 32) |
-                      (uint32_t)__shfl_xor((int)(uint32_t)(uint64_t)b.val, d, 64));
-    o.idx = (uint32_t)__shfl_xor((int)b.idx, d, 64);
-    o.over = (uint32_t)__shfl_xor((int)b.over, d, 64);
-    better(b, o);
-  }
-  return b;
-}
-
 constexpr uint32_t kNoOp = 0xFFFFFFFFu;
 
 __device__ __forceinline__ Best no_best() { return Best{INT64_MIN, kNoOp, 0}; }
+
+template <int kCtrl, int kRows>
+__device__ __forceinline__ int64_t max_step(int64_t v) {
+  const uint32_t lo = dpp_u32<kCtrl, kRows>((uint32_t)(uint64_t)v, 0), hi = dpp_u32<kCtrl, kRows>((uint32_t)((uint64_t)v >> 32), 0x80000000u);
+  const int64_t o = (int64_t)((uint64_t)hi << 32 | lo);
+  return o > v ? o : v;
+}
+
+template <int kCtrl, int kRows>
+__device__ __forceinline__ uint32_t min_step(uint32_t v) { return min(v, dpp_u32<kCtrl, kRows>(v, ~0u)); }
+
+// over the wavefront, given in every lane: the largest value, its lowest index, the sum of `over`
+__device__ __forceinline__ Best wave_best(Best b) {
+  int64_t v = b.val;
+  v = max_step<0x111, 0xF>(v);
+  v = max_step<0x112, 0xF>(v);
+  v = max_step<0x114, 0xF>(v);
+  v = max_step<0x118, 0xF>(v);
+  v = max_step<0x142, 0xA>(v);
+  v = max_step<0x143, 0xC>(v);
+  v = lane_i64(v, 63);
+  uint32_t i = b.val == v ? b.idx : ~0u;
+  i = min_step<0x111, 0xF>(i);
+  i = min_step<0x112, 0xF>(i);
+  i = min_step<0x114, 0xF>(i);
+  i = min_step<0x118, 0xF>(i);
+  i = min_step<0x142, 0xA>(i);
+  i = min_step<0x143, 0xC>(i);
+  return Best{v, (uint32_t)__builtin_amdgcn_readlane((int)i, 63), (uint32_t)__builtin_amdgcn_readlane((int)wave_scan_u32(b.over), 63)};
+}
 
 __device__ __forceinline__ void write_result(const ScanArgs &a, const Best &b, int64_t final_total, uint32_t flags) {
   ss_scan_result_t r;
@@ -154,7 +187,7 @@ __device__ __forceinline__ void put_op(const ScanArgs &a, uint32_t t, int64_t p,
 
 // canonical place and total of an event: class 0 policy alloc, 1 trace alloc, 2 trace release, 3 policy release.
 // sum: inclusive running sum of its class in its list, cnt: events of its class before it there
-__device__ __forceinline__ void put_event(const ScanArgs &a, bool policy, bool positive, int64_t sum, uint32_t cnt,
+__device__ __forceinline__ void put_event(const ScanArgs &a, int64_t *timeline, bool policy, bool positive, int64_t sum, uint32_t cnt,
                                           const OpAt &e0, const OpAt &e1, const OpAt &p0, const OpAt &p1) {
   uint32_t q = e0.f + p0.f;                        // events of earlier operators
   int64_t v;
@@ -172,7 +205,7 @@ __device__ __forceinline__ void put_event(const ScanArgs &a, bool policy, bool p
     q += n0 + (e1.f - e0.f) + cnt - (p0.f - p0.cp);
     v = e1.sn + e1.sp + p1.sp + sum;
   }
-  a.timeline[q] = a.base + v;
+  timeline[q] = a.base + v;
 }
 
 // OpAt entries of operators (prev, op] take the values before the event that starts op.  A lane fills a short gap by
@@ -364,14 +397,14 @@ struct WgShared {
   Best best[kWaves];
 };
 
+// over the workgroup, given in the first wavefront
 template <int T>
 __device__ __forceinline__ Best wg_best(Best b, Best *part) {
   b = wave_best(b);
   if ((threadIdx.x & 63) == 0) part[threadIdx.x >> 6] = b;
   __syncthreads();
-  b = no_best();
-  for (int i = 0; i < T / 64; ++i) better(b, part[i]);
-  return b;
+  if (threadIdx.x >= 64) return no_best();
+  return wave_best(threadIdx.x < T / 64 ? part[threadIdx.x] : no_best());
 }
 
 // at: 2 * (n_ops + 1) entries; pos, net: n_ops entries, may lie in `at`.  A timeline only if the trace fits one pass.
@@ -474,7 +507,7 @@ __device__ __forceinline__ void scan_wg(const ScanArgs &a, OpAt *at, int64_t *po
         if (i >= total || !y.live) continue;
         const bool policy = i >= a.n_ev;
         const uint32_t e = (uint32_t)(policy ? i - a.n_ev : i);
-        put_event(a, policy, y.pos, (y.pos ? sp[k] : sn[k]) + y.delta, y.pos ? cp[k] : e - cp[k], at_ev[y.op],
+        put_event(a, a.timeline, policy, y.pos, (y.pos ? sp[k] : sn[k]) + y.delta, y.pos ? cp[k] : e - cp[k], at_ev[y.op],
                   at_ev[y.op + 1], at_pe[y.op], at_pe[y.op + 1]);
       }
     }
@@ -483,21 +516,224 @@ __device__ __forceinline__ void scan_wg(const ScanArgs &a, OpAt *at, int64_t *po
   if (tid == 0) write_result(a, b, final_total, flags);
 }
 
-// One workgroup takes a trace whose events fit its registers (four a lane) and whose two OpAt tables fit LDS (24 bytes
-// an entry).  Mostly it is the faster form: 6 to 12 us, the two launches of the other take 11 at least (4,090 events over 700
-// operators 15 and 11).
-constexpr uint32_t kLdsOps = 2900;
-constexpr uint64_t kSmallEvents = 4096;
+// ---- one workgroup, short traces -------------------------------------------------------------------------------------
+//
+// The events lie in registers, K consecutive ones to a lane, each list from a wavefront's first lane on, so that a
+// wavefront adds up a list's running sums with one prefix sum of each kind (a wavefront issues an instruction in some five
+// cycles, and with the events dealt out lane by lane and a prefix sum for every 64 the sums took 1.3 us for 148 events
+// and 3 for 1,734).  An operator's OpAt entry is written by the event that starts it; those of operators without events
+// are copied from the next operator that has some, found in a bit map (each gap filled by the wavefront that met it: 1.6
+// and 2.5 us, 7 with 90 events over 700 operators).  The timeline is put together in LDS, so that it leaves in whole lines.
+// 124 + 24 events over 66 operators: 4.3 us, before 6.0; 1,398 + 336 over 700 from and to pinned memory 8.7, before 12.1.
 
-static size_t lds_at(uint32_t n_ops) { return 2 * ((size_t)n_ops + 1) * sizeof(OpAt); }
+constexpr uint32_t kLdsOps = 2900;                       // OpAt tables of more don't fit LDS
+constexpr uint32_t kHeadWords = (kLdsOps + 1 + 31) / 32;
+constexpr uint64_t kSmallEvents = 4096;
+constexpr size_t kShortLds = 150 * 1024;
 
 template <int T>
-__global__ __launch_bounds__(T) void ss_scan_small_kernel(ScanArgs a) {
-  __shared__ WgShared sh;
-  extern __shared__ OpAt lds[];
-  int64_t *const sums = reinterpret_cast<int64_t *>(lds);
-  scan_wg<T, 4>(a, lds, sums, sums + a.n_ops, sh);
+struct ShortShared {
+  int64_t sp[T / 64], sn[T / 64];
+  uint32_t cp[T / 64], flags;
+  uint32_t head[2][kHeadWords];                          // operators whose entry an event has written
+  Best best[T / 64];
+  SumShared sums;                                        // lists out of order
+};
+
+static __host__ __device__ constexpr uint32_t round_up(uint32_t x, uint32_t to) { return (x + to - 1) / to * to; }
+
+// LDS beyond ShortShared: the events on their way to their lanes, then the OpAt tables (or the sums of lists out of order);
+// the timeline
+static size_t short_tables(int T, int K, uint32_t n_ops) {
+  return ss_align_up(std::max((size_t)T * K * 12, 2 * ((size_t)n_ops + 1) * sizeof(OpAt)), 16);
 }
+
+static size_t short_lds(int T, int K, uint32_t n_ops, uint64_t events, bool timeline) {
+  return short_tables(T, K, n_ops) + (timeline ? events * 8 : 0);
+}
+
+template <int T, int K>
+__device__ __forceinline__ void scan_short(const ScanArgs &a, uint8_t *lds, uint32_t tl_at, ShortShared<T> &sh) {
+  constexpr uint32_t W = T / 64, kChunk = 64 * K;
+  const uint32_t n = a.n_ops, tid = threadIdx.x, lane = tid & 63, w = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const uint32_t w1 = round_up((uint32_t)a.n_ev, kChunk) / kChunk;     // the second list's first wavefront
+  const bool policy = w >= w1;
+  const ss_event_t *const L = policy ? a.pev : a.ev;
+  const uint32_t cnt = (uint32_t)(policy ? a.n_pe : a.n_ev), c0 = (policy ? w - w1 : w) * kChunk;
+  OpAt *const tables = reinterpret_cast<OpAt *>(lds), *const at = tables + (policy ? n + 1 : 0);
+  const OpAt *const at_ev = tables, *const at_pe = tables + n + 1;
+  int64_t *const tl = reinterpret_cast<int64_t *>(lds + tl_at);
+  uint32_t op[K];
+  int64_t delta[K];
+  uint32_t before = kNoOp;                               // operator of the event before the wavefront's first
+  {
+    ss_event_t raw[K];
+#pragma unroll
+    for (int k = 0; k < K; ++k) {
+      const uint32_t e = c0 + k * 64 + lane;
+      raw[k] = ss_event_t{kNoOp, 0, 0};
+      if (e < cnt) raw[k] = L[e];
+    }
+    if (lane == 0 && c0 && c0 < cnt) before = L[c0 - 1].op_idx;
+    for (uint32_t i = tid; i < 2 * kHeadWords; i += T) sh.head[0][i] = 0;
+    if (tid == 0) sh.flags = 0;
+    if constexpr (K == 1) {
+      op[0] = raw[0].op_idx;
+      delta[0] = raw[0].delta;
+    } else {
+      int64_t *const mine = reinterpret_cast<int64_t *>(lds) + w * kChunk;
+      uint32_t *const mine_op = reinterpret_cast<uint32_t *>(lds + (size_t)T * K * 8) + w * kChunk;
+#pragma unroll
+      for (int k = 0; k < K; ++k) { mine[k * 64 + lane] = raw[k].delta; mine_op[k * 64 + lane] = raw[k].op_idx; }
+      __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");           // LDS accesses of a wavefront are in order
+      __builtin_amdgcn_wave_barrier();
+#pragma unroll
+      for (int k = 0; k < K; ++k) { delta[k] = mine[lane * K + k]; op[k] = mine_op[lane * K + k]; }
+    }
+  }
+  const uint32_t e0 = c0 + lane * K;
+  int64_t sp[K], sn[K], tsp = 0, tsn = 0;                // before the event; of the lane
+  uint32_t cp[K], tcp = 0, flags = 0;
+  bool pos[K], starts[K];
+  uint32_t prev = prev_lane(op[K - 1], before);
+#pragma unroll
+  for (int k = 0; k < K; ++k) {
+    const bool live = e0 + k < cnt;
+    pos[k] = live && delta[k] >= 0;
+    starts[k] = live && (e0 + k == 0 || prev != op[k]);
+    if (live && op[k] >= n) flags |= 1u;
+    if (live && e0 + k && prev > op[k]) flags |= 2u;
+    prev = op[k];
+    sp[k] = tsp; sn[k] = tsn; cp[k] = tcp;
+    tsp += pos[k] ? delta[k] : 0;
+    tsn += pos[k] ? 0 : delta[k];
+    tcp += pos[k];
+  }
+  const int64_t isp = wave_scan(tsp), isn = wave_scan(tsn);
+  const uint32_t icp = wave_scan_u32(tcp);
+  if (lane == 63) { sh.sp[w] = isp; sh.sn[w] = isn; sh.cp[w] = icp; }
+  __syncthreads();
+  const uint64_t wrong = __ballot(flags != 0);
+  if (wrong) {
+    flags = (__ballot(flags & 1u) ? 1u : 0u) | (__ballot(flags & 2u) ? 2u : 0u);
+    if (lane == 0) atomicOr(&sh.flags, flags);
+  }
+  {
+    // what the wavefronts of the same list before this one add up to
+    const bool counts = lane < w && lane >= (policy ? w1 : 0);
+    const int64_t x = wave_scan(counts ? sh.sp[lane % W] : 0), y = wave_scan(counts ? sh.sn[lane % W] : 0);
+    const uint32_t z = wave_scan_u32(counts ? sh.cp[lane % W] : 0);
+    const int64_t bsp = lane_i64(x, 63) + isp - tsp, bsn = lane_i64(y, 63) + isn - tsn;
+    const uint32_t bcp = (uint32_t)__builtin_amdgcn_readlane((int)z, 63) + icp - tcp;
+#pragma unroll
+    for (int k = 0; k < K; ++k) {
+      sp[k] += bsp; sn[k] += bsn; cp[k] += bcp;
+      if (starts[k] && op[k] < n) {
+        at[op[k]] = OpAt{sp[k], sn[k], e0 + k, cp[k]};
+        atomicOr(&sh.head[policy][op[k] / 32], 1u << (op[k] % 32));
+      }
+      if (e0 + k + 1 == cnt) {
+        at[n] = OpAt{sp[k] + (pos[k] ? delta[k] : 0), sn[k] + (pos[k] ? 0 : delta[k]), cnt, cp[k] + (pos[k] ? 1 : 0)};
+        atomicOr(&sh.head[policy][n / 32], 1u << (n % 32));
+      }
+    }
+  }
+  if (tid < 2 && !(tid ? a.n_pe : a.n_ev)) {             // an empty list
+    tables[tid * (n + 1) + n] = OpAt{0, 0, 0, 0};
+    atomicOr(&sh.head[tid][n / 32], 1u << (n % 32));
+  }
+  __syncthreads();
+  flags = sh.flags;
+  Best b = no_best();
+  int64_t final_total = a.base;
+  if (flags & 1u) {
+    if (tid == 0) write_result(a, b, 0, flags);
+    return;
+  }
+  if (flags) {
+    int64_t *const gpos = reinterpret_cast<int64_t *>(lds), *const gnet = gpos + n;
+    const uint64_t total = a.n_ev + a.n_pe;
+    for (uint32_t t = tid; t < n; t += T) gpos[t] = gnet[t] = 0;
+    __syncthreads();
+    for (uint64_t first = 0; first < total; first += (uint64_t)T * K) {
+      Elem x[K];
+      load_events<T, K>(a.ev, a.n_ev, a.pev, a.n_pe, first, total, n, x);
+#pragma unroll
+      for (int k = 0; k < K; ++k) gather_run(gpos, gnet, x[k], n);
+    }
+    __syncthreads();
+    b = ops_of_sums<T>(a, gpos, gnet, sh.sums);
+    __syncthreads();
+    final_total += n ? sh.sums.tot_sp : 0;
+  } else {
+    for (uint32_t i = tid; i < 2 * n; i += T) {
+      const uint32_t l = i >= n, t = i - (l ? n : 0);
+      uint32_t word = t / 32, bits = sh.head[l][word] >> (t % 32);
+      if (bits & 1u) continue;
+      uint32_t next = t;
+      if (!bits) {
+        do bits = sh.head[l][++word]; while (!bits);     // the entry of n is always there
+        next = word * 32;
+      }
+      next += (uint32_t)__builtin_ctz(bits);
+      tables[l * (n + 1) + t] = tables[l * (n + 1) + next];
+    }
+    __syncthreads();
+    for (uint32_t t = tid; t < n; t += T)
+      put_op(a, t, a.base + at_ev[t + 1].sp + at_pe[t + 1].sp + at_ev[t].sn + at_pe[t].sn, b);
+    final_total += at_ev[n].sp + at_ev[n].sn + at_pe[n].sp + at_pe[n].sn;
+    if (a.want_timeline) {
+#pragma unroll
+      for (int k = 0; k < K; ++k)
+        if (e0 + k < cnt)
+          put_event(a, tl, policy, pos[k], (pos[k] ? sp[k] : sn[k]) + delta[k], pos[k] ? cp[k] : e0 + k - cp[k], at_ev[op[k]],
+                    at_ev[op[k] + 1], at_pe[op[k]], at_pe[op[k] + 1]);
+    }
+  }
+  b = wg_best<T>(b, sh.best);                            // its barrier is the timeline's too
+  if (a.want_timeline && !flags)
+    for (uint32_t i = tid; i < (uint32_t)(a.n_ev + a.n_pe); i += T) a.timeline[i] = tl[i];
+  if (tid == 0) write_result(a, b, final_total, flags);
+}
+
+template <int T, int K>
+__global__ __launch_bounds__(T) void ss_scan_short_kernel(ScanArgs a, uint32_t tl_at) {
+  __shared__ ShortShared<T> sh;
+  extern __shared__ __align__(16) uint8_t short_mem[];
+  scan_short<T, K>(a, short_mem, tl_at, sh);
+}
+
+// candidate policies against the same trace
+template <int T, int K>
+__global__ __launch_bounds__(T) void ss_scan_short_batch_kernel(const ScanArgs *__restrict__ args) {
+  __shared__ ShortShared<T> sh;
+  extern __shared__ __align__(16) uint8_t short_mem[];
+  const ScanArgs a = args[blockIdx.x];
+  scan_short<T, K>(a, short_mem, 0, sh);
+}
+
+// lanes and events to a lane for two lists of that many
+struct ShortForm { int T, K; };
+
+static ShortForm short_form(uint64_t n_ev, uint64_t n_pe) {
+  auto fits = [&](uint64_t T, uint64_t K) { return ss_align_up(n_ev, 64 * K) + ss_align_up(n_pe, 64 * K) <= T * K; };
+  if (fits(256, 1)) return {256, 1};
+  if (fits(256, 4)) return {256, 4};
+  if (fits(512, 4)) return {512, 4};
+  if (fits(1024, 4)) return {1024, 4};
+  return {0, 0};
+}
+
+#define SS_SHORT_FORM(f, LAUNCH)                                    \
+  do {                                                              \
+    if ((f).T == 256 && (f).K == 1) LAUNCH(256, 1);                 \
+    else if ((f).T == 256) LAUNCH(256, 4);                          \
+    else if ((f).T == 512) LAUNCH(512, 4);                          \
+    else LAUNCH(1024, 4);                                           \
+  } while (0)
+
+// The OpAt tables of a batch's scans lie in LDS up to this many operators (24 bytes an entry).
+static size_t lds_at(uint32_t n_ops) { return 2 * ((size_t)n_ops + 1) * sizeof(OpAt); }
 
 // one workgroup per scan: candidate policies against the same trace in a single launch
 template <bool LDS>
@@ -755,7 +991,7 @@ __global__ __launch_bounds__(kThreads) void ss_scan_finish_kernel(ScanArgs a, ui
     for (uint64_t i = (uint64_t)(blockIdx.x - op_wgs) * kThreads + tid; i < total; i += (uint64_t)(gridDim.x - op_wgs) * kThreads) {
       const bool policy = i >= a.n_ev;
       const ss_event_t x = policy ? a.pev[i - a.n_ev] : a.ev[i];
-      put_event(a, policy, x.delta >= 0, a.sumx[i], a.cntx[i], at_ev[x.op_idx], at_ev[x.op_idx + 1], at_pe[x.op_idx],
+      put_event(a, a.timeline, policy, x.delta >= 0, a.sumx[i], a.cntx[i], at_ev[x.op_idx], at_ev[x.op_idx + 1], at_pe[x.op_idx],
                 at_pe[x.op_idx + 1]);
     }
     return;
@@ -804,7 +1040,13 @@ uint32_t tile_events(uint64_t n, uint32_t n_ops, int per_lane) {
   return (uint32_t)std::max(pass, ss_align_up((n + kMaxTiles - 1) / kMaxTiles, pass));
 }
 
-bool is_short(uint64_t n_ev, uint64_t n_pe, uint32_t n_ops) { return n_ev + n_pe <= kSmallEvents && n_ops <= kLdsOps; }
+// One workgroup takes a trace whose events fit its registers and whose tables fit LDS.  Up to there it is the faster form: a
+// call for 3,500 + 500 events over 2,500 operators 9.3 us, with a timeline 11.0, the two launches of the other 11 at least.
+bool is_short(uint64_t n_ev, uint64_t n_pe, uint32_t n_ops, bool timeline) {
+  if (n_ev + n_pe > kSmallEvents || n_ops > kLdsOps) return false;
+  const ShortForm f = short_form(n_ev, n_pe);
+  return f.T && short_lds(f.T, f.K, n_ops, n_ev + n_pe, timeline) <= kShortLds;
+}
 
 // Host calls: up to this much goes through the context's pinned scratch (which starts at 1 MiB), read and written by the
 // kernels themselves; a copy call for pageable memory costs 19 to 33 us at 16 to 64 KiB and a copy from pinned memory a
@@ -829,11 +1071,13 @@ size_t scan_scratch(ScanArgs *a, uint8_t *d, uint64_t n_ev, uint64_t n_pe, uint6
 }
 
 void launch_scan(hipStream_t s, ScanArgs &a) {
-  if (is_short(a.n_ev, a.n_pe, a.n_ops)) {
-    if (a.n_ev + a.n_pe <= 1024)
-      hipLaunchKernelGGL(ss_scan_small_kernel<256>, dim3(1), dim3(256), lds_at(a.n_ops), s, a);
-    else
-      hipLaunchKernelGGL(ss_scan_small_kernel<kThreads>, dim3(1), dim3(kThreads), lds_at(a.n_ops), s, a);
+  if (is_short(a.n_ev, a.n_pe, a.n_ops, a.want_timeline)) {
+    const ShortForm f = short_form(a.n_ev, a.n_pe);
+    const size_t bytes = short_lds(f.T, f.K, a.n_ops, a.n_ev + a.n_pe, a.want_timeline);
+    const uint32_t tl_at = (uint32_t)short_tables(f.T, f.K, a.n_ops);
+#define SS_LAUNCH(T, K) hipLaunchKernelGGL((ss_scan_short_kernel<T, K>), dim3(1), dim3(T), bytes, s, a, tl_at)
+    SS_SHORT_FORM(f, SS_LAUNCH);
+#undef SS_LAUNCH
     return;
   }
   const int per_lane = events_per_lane(std::max(a.n_ev, a.n_pe));
@@ -984,7 +1228,19 @@ extern "C" int ss_timeline_scan_batch(ss_ctx *ctx, const ss_event_t *ev, uint64_
       ha[c] = a;
     }
     const ScanArgs *dargs = (const ScanArgs *)hd;
-    if (lds) hipLaunchKernelGGL(ss_scan_batch_kernel<true>, dim3(k), dim3(kThreads), lds_at(n_ops), s, dargs);
+    ShortForm f = {0, 0};                               // one for all
+    bool all_short = lds;
+    for (uint32_t c = 0; c < k && all_short; ++c) {
+      const ShortForm g = short_form(n_ev, ha[c].n_pe);
+      all_short = g.T && n_ev + ha[c].n_pe <= kSmallEvents && short_lds(g.T, g.K, n_ops, 0, false) <= kShortLds;
+      if (g.T * g.K > f.T * f.K) f = g;
+    }
+    if (all_short) {
+#define SS_LAUNCH(T, K) \
+  hipLaunchKernelGGL((ss_scan_short_batch_kernel<T, K>), dim3(k), dim3(T), short_lds(T, K, n_ops, 0, false), s, dargs)
+      SS_SHORT_FORM(f, SS_LAUNCH);
+#undef SS_LAUNCH
+    } else if (lds) hipLaunchKernelGGL(ss_scan_batch_kernel<true>, dim3(k), dim3(kThreads), lds_at(n_ops), s, dargs);
     else hipLaunchKernelGGL(ss_scan_batch_kernel<false>, dim3(k), dim3(kThreads), 0, s, dargs);
     SS_HIP(hipGetLastError());
     SS_HIP(hipStreamSynchronize(s));
@@ -1019,7 +1275,7 @@ extern "C" int ss_timeline_scan(ss_ctx *ctx, const ss_event_t *ev, uint64_t n_ev
     const size_t out_bytes = (per_op ? n * 8 : 0) + (mre ? n * 8 : 0) + (timeline ? E * 8 : 0);
     // Short traces: the one kernel reads the events out of pinned memory.  Longer ones: the first kernel does, and copies
     // them on the way for the other two.  Results are written to pinned memory in both cases.
-    const bool is_small = is_short(n_ev, n_pe, n_ops);
+    const bool is_small = is_short(n_ev, n_pe, n_ops, timeline != nullptr);
     const bool in_mapped = is_small || ev_bytes + pe_bytes <= kMappedBytes;
     const bool out_mapped = is_small || (in_mapped ? ev_bytes + pe_bytes : 0) + out_bytes <= kMappedBytes;
     size_t off = 0, hoff = 0;

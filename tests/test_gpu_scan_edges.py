@@ -121,6 +121,30 @@ def test_batch_lists_out_of_order_from_the_start_or_late(P, ctx, n_ops):        
 
 
 @pytest.mark.parametrize("n_ev,n_pe,n_ops", [
+    (256, 0, 66), (192, 64, 700), (193, 64, 700), (0, 257, 31), (1024, 0, 32), (768, 256, 33),     # lanes and events to a lane
+    (769, 256, 1000), (1792, 255, 90), (1793, 256, 2899), (3840, 256, 2000), (3841, 255, 2000),    # one workgroup | two launches
+    (2048, 2048, 2560), (2048, 2048, 2561), (2048, 2048, 2600), (5, 3, 2900), (4090, 1, 2900),     # tables and timeline in LDS
+])
+def test_one_workgroup_forms(P, ctx, n_ev, n_pe, n_ops):          # noqa: F811
+    rng = np.random.default_rng([n_ev, n_pe, n_ops, 4])
+    ev, pe = events(rng, n_ev, n_ops), events(rng, n_pe, n_ops, runs=True)
+    ora = both_ways(P, ctx, ev, pe, n_ops, 1 << 44, 9)
+    for r, c in zip(P.ss_timeline_scan_batch(ctx, ev, [pe, None, pe[:7]], n_ops, 1 << 44, 9, want_per_op=True), (pe, None, pe[:7])):
+        o = ora if c is pe else oracle.timeline_scan(ev, c, n_ops, 1 << 44, 9)
+        assert (r["peak"], r["argpeak_op"], r["n_over"], r["final"]) == (o["peak"], o["argpeak_op"], o["n_over"], o["final"])
+        assert np.array_equal(r["per_op"], o["per_op"])
+
+
+def test_every_operator_alike_and_the_lowest_of_equal_peaks(P, ctx):                 # noqa: F811
+    for n_ops in (65, 2900, 9000):
+        ev = np.zeros(2 * n_ops if n_ops < 2000 else 2000, dtype=W.EVENT_DT)
+        ev["op_idx"] = np.arange(len(ev)) % n_ops
+        ev["delta"] = np.where(np.arange(len(ev)) % 2 == 0, 7, -7)
+        ev = ev[np.argsort(ev["op_idx"], kind="stable")]
+        both_ways(P, ctx, ev, np.zeros(0, dtype=W.EVENT_DT), n_ops, -(1 << 62), -(1 << 62) + 3)
+
+
+@pytest.mark.parametrize("n_ev,n_pe,n_ops", [
     (4096, 513, 700), (4607, 512, 700), (5121, 0, 9),                                # tiles of 512 events and their edges
     (524288, 512, 500), (524289, 1025, 500), (1048576, 0, 40), (1048577, 3, 40),     # two a lane | four | passes of eight
 ])
