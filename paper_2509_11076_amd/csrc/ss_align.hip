@@ -76,6 +76,7 @@ struct KeyArgs {
   void *ref_id, *cur_id;       // id_length(n_steps) entries, padded; m entries
   uint32_t *n_keys;            // device: distinct keys so far
   uint32_t *n_keys_out;        // pinned: how many there are
+  ss_done done;                // long sequences: the host waits for them
   // long sequences
   uint32_t *rep, *id;          // per slot
   uint32_t *slot;              // per operator of cur
@@ -218,7 +219,7 @@ __global__ __launch_bounds__(256) void ss_align_insert_kernel(KeyArgs a) {
   if (live) a.slot[j] = slot_of[l];
 }
 
-__global__ __launch_bounds__(256) void ss_align_ids_kernel(KeyArgs a) {
+__device__ __forceinline__ void operator_ids(const KeyArgs &a) {
   const uint32_t i = blockIdx.x * 256 + threadIdx.x, keys = *a.n_keys;
   const bool few = keys <= a.few;
   if (i == 0) *a.n_keys_out = keys;
@@ -236,6 +237,11 @@ __global__ __launch_bounds__(256) void ss_align_ids_kernel(KeyArgs a) {
     }
   }
   put_id(a.ref_id, i, key, few);
+}
+
+__global__ __launch_bounds__(256) void ss_align_ids_kernel(KeyArgs a) {
+  operator_ids(a);
+  ss_tell_host(a.done);
 }
 
 template <class Id>
@@ -272,6 +278,7 @@ struct RowsArgs {
   uint32_t *gave_up_host;    // pinned: the same
   uint32_t W, n_steps, strips, strip0;       // strips of a row; the one of workgroup 0
   uint32_t wait_looks;       // looks at a carry word before a strip gives up
+  ss_done done;              // where the host walks the rows
 };
 
 static __device__ const uint32_t all_ones = ~0u;
@@ -485,7 +492,10 @@ __global__ __launch_bounds__(64) void ss_align_rows_kernel(const Id *__restrict_
   const uint32_t words = min(many ? kInnerWords : kStripWords, a.W - w0);
   const bool stored = lane >= first && lane < first + words;
   const uint32_t n_mask_rows = *n_keys + 1;
-  if (kLds && n_mask_rows > kLdsKeys) return;                // launched before the number was known, and the ids are wide
+  if (kLds && n_mask_rows > kLdsKeys) {                      // launched before the number was known, and the ids are wide
+    ss_tell_host(a.done);
+    return;
+  }
   Masks<Id> masks;
   if constexpr (kLds) {
     uint8_t *const ring = reinterpret_cast<uint8_t *>(lds + n_mask_rows * kStripWords);
@@ -534,6 +544,7 @@ __global__ __launch_bounds__(64) void ss_align_rows_kernel(const Id *__restrict_
   }
   if (many) strip_rows<Id, true>(a, masks, stored);
   else strip_rows<Id, false>(a, masks, stored);
+  ss_tell_host(a.done);
 }
 
 // ---- the walk back on the GPU ----------------------------------------------------------------------------------
@@ -779,7 +790,7 @@ __global__ __launch_bounds__(64) void ss_align_pairs_kernel(const Id *__restrict
                                                             const uint16_t *__restrict__ table,
                                                             const int32_t *__restrict__ entry,
                                                             const int32_t *__restrict__ group_entry,
-                                                            int32_t *__restrict__ ref_to_cur) {
+                                                            int32_t *__restrict__ ref_to_cur, ss_done done) {
   __shared__ uint32_t M[kWalkRows][kTileStride], X[kWalkRows][kTileStride];
   __shared__ int32_t paired[kWalkRows];
   const uint32_t k = blockIdx.x, k0 = k / kGroupBlocks * kGroupBlocks;
@@ -789,7 +800,10 @@ __global__ __launch_bounds__(64) void ss_align_pairs_kernel(const Id *__restrict
   } else {
     j = entry[k];
   }
-  if (j < 0) return;
+  if (j < 0) {                                               // the chain has walked it
+    ss_tell_host(done);
+    return;
+  }
   const RowBlock blk(k, n);
   const int w0 = j / (int)kEntries * (int)(kEntries / 32) - (int)(kMargin / 32);     // the tile the table came from
   paired[threadIdx.x] = -1;
@@ -798,6 +812,7 @@ __global__ __launch_bounds__(64) void ss_align_pairs_kernel(const Id *__restrict
   if (threadIdx.x == 0) walk_tile(blk.hi - blk.lo, w0, j, M, X, [&](uint32_t q, int c) { paired[q] = c; });
   __syncthreads();
   if (threadIdx.x < blk.hi - blk.lo) ref_to_cur[blk.hi - 1 - threadIdx.x] = paired[threadIdx.x];
+  ss_tell_host(done);
 }
 
 // LDS of the rows kernel with 16-bit ids: mask rows, ring and all ids of the reference
@@ -814,7 +829,7 @@ uint32_t most_few(uint32_t n) {
 // Where everything lies.  `d` device scratch, `h` pinned scratch.
 struct Layout {
   size_t h_ref, h_cur, h_flag, h_n_keys, h_out, h_end;
-  size_t ref, cur, ref_id, cur_id, n_keys, rep, id, slot, carry, gave_up, rows, pair, table, entry, groups, group_entry, masks, end;
+  size_t ref, cur, ref_id, cur_id, n_keys, rep, id, slot, carry, gave_up, rows, table, entry, groups, group_entry, masks, end;
   uint32_t n, m, W, strips, n_steps, n_blocks, walk_blocks, walk_groups, slots, bits;
   bool one_wg, short_rows;
 
@@ -851,7 +866,6 @@ struct Layout {
     id = take(one_wg ? 0 : (size_t)slots * 4);
     slot = take(one_wg ? 0 : (size_t)m * 4);
     rows = take(short_rows ? 0 : row_bytes);
-    pair = take(short_rows ? 0 : (size_t)n * 4);
     table = take(short_rows ? 0 : (size_t)walk_blocks * kWindow * 2);
     entry = take(short_rows ? 0 : (size_t)walk_blocks * 4);
     groups = take(short_rows ? 0 : (size_t)walk_groups * kWindow * 2);
@@ -872,7 +886,7 @@ static_assert(((uint64_t)kAlignLenLimit + 1) * (kAlignLenLimit / 32) * 4 <= 1ull
 // Rows (and, long ones, the walk) for ids of the given form.  The masks are needed where the rows kernel does not keep its
 // own in LDS, and by the walk.
 template <class Id>
-int launch_rows(ss_ctx *ctx, const Layout &y, uint8_t *d, uint8_t *hd, uint32_t keys, bool one_by_one = false) {
+int launch_rows(ss_ctx *ctx, const Layout &y, uint8_t *d, uint8_t *hd, uint32_t keys, ss_done &done, bool one_by_one = false) {
   constexpr bool kLds = sizeof(Id) == 2;
   hipStream_t s = ctx->s_aux;
   const Id *ref_id = (const Id *)(d + y.ref_id), *cur_id = (const Id *)(d + y.cur_id);
@@ -883,16 +897,19 @@ int launch_rows(ss_ctx *ctx, const Layout &y, uint8_t *d, uint8_t *hd, uint32_t 
   if (masks_needed)
     hipLaunchKernelGGL(ss_align_masks_kernel<Id>, dim3((y.m + 255) / 256), dim3(256), 0, s, cur_id, y.m, masks, y.W);
   RowsArgs args = {masks, (u64 *)(d + y.carry), rows, (uint32_t *)(d + y.gave_up), (uint32_t *)(hd + y.h_flag),
-                   y.W, y.n_steps, y.strips, 0, ctx->align_wait_looks};
+                   y.W, y.n_steps, y.strips, 0, ctx->align_wait_looks, {}};
   const uint32_t *n_keys = (const uint32_t *)(d + y.n_keys);
   const uint32_t per_launch = one_by_one ? 1 : y.strips;
+  done = ss_next_done(ctx);
+  done.wgs = y.short_rows ? y.strips : y.walk_blocks;
+  if (y.short_rows) args.done = done;
   for (; args.strip0 < y.strips; args.strip0 += per_launch)
     hipLaunchKernelGGL(ss_align_rows_kernel<Id>, dim3(per_launch), dim3(64), kLds ? lds_need(keys, y.n) : 0, s, ref_id,
                        cur_id, y.m, args, n_keys);
   if (!y.short_rows) {
     const uint32_t *cmasks = masks, *crows = rows;
     uint16_t *table = (uint16_t *)(d + y.table), *groups = (uint16_t *)(d + y.groups);
-    int32_t *entry = (int32_t *)(d + y.entry), *group_entry = (int32_t *)(d + y.group_entry), *pair = (int32_t *)(d + y.pair);
+    int32_t *entry = (int32_t *)(d + y.entry), *group_entry = (int32_t *)(d + y.group_entry), *pair = (int32_t *)(hd + y.h_out);
     hipLaunchKernelGGL(ss_align_tab_kernel<Id>, dim3(y.walk_blocks, kWindow / kEntries), dim3(kEntries), 0, s, ref_id, y.n,
                        cmasks, y.m, y.W, y.n_steps, crows, table);
     hipLaunchKernelGGL(ss_align_compose_kernel, dim3(y.walk_groups, kWindow / 256), dim3(256), 0, s, table, y.n, y.m,
@@ -900,9 +917,7 @@ int launch_rows(ss_ctx *ctx, const Layout &y, uint8_t *d, uint8_t *hd, uint32_t 
     hipLaunchKernelGGL(ss_align_chain_kernel<Id>, dim3(1), dim3(kChainThreads), 0, s, ref_id, y.n, cmasks, y.m, y.W,
                        y.n_steps, crows, table, groups, entry, group_entry, pair);
     hipLaunchKernelGGL(ss_align_pairs_kernel<Id>, dim3(y.walk_blocks), dim3(64), 0, s, ref_id, y.n, cmasks, y.m, y.W, y.n_steps,
-                       crows, table, entry, group_entry, pair);
-    SS_HIP(hipGetLastError());
-    SS_HIP(hipMemcpyAsync((uint8_t *)ctx->h_scratch + y.h_out, pair, (size_t)y.n * 4, hipMemcpyDeviceToHost, s));
+                       crows, table, entry, group_entry, pair, done);
   }
   SS_HIP(hipGetLastError());
   return SS_OK;
@@ -924,6 +939,7 @@ int ss_align_core(ss_ctx *ctx, const ss_op_t *ref, uint32_t n, const ss_op_t *cu
   hipStream_t s = ctx->s_aux;
   uint8_t *d = nullptr, *h = nullptr, *hd = nullptr;
   volatile uint32_t *h_flag = nullptr, *h_n_keys = nullptr;
+  ss_done keys_known = {}, done = {};
   // key ids; again if the mask table then turns out not to fit (the first call with that many keys)
   auto make_ids = [&](size_t dev_bytes) -> int {
     const int rc = ss_scratch_reserve(ctx, dev_bytes, y.h_end);
@@ -960,7 +976,9 @@ int ss_align_core(ss_ctx *ctx, const ss_op_t *ref, uint32_t n, const ss_op_t *cu
       const uint32_t wgs = std::min(256u, (std::max(n, m) + 255) / 256), len = std::max(m, id_length(y.n_steps));
       hipLaunchKernelGGL(ss_align_fetch_kernel, dim3(wgs), dim3(256), 0, s, mref, dref, n, mcur, dcur, m, a.rep, y.slots, a.n_keys);
       hipLaunchKernelGGL(ss_align_insert_kernel, dim3((m + 255) / 256), dim3(256), 0, s, a);
-      hipLaunchKernelGGL(ss_align_ids_kernel, dim3((len + 255) / 256), dim3(256), 0, s, a);
+      keys_known = a.done = ss_next_done(ctx);
+      a.done.wgs = (len + 255) / 256;
+      hipLaunchKernelGGL(ss_align_ids_kernel, dim3(a.done.wgs), dim3(256), 0, s, a);
     }
     SS_HIP(hipGetLastError());
     return SS_OK;
@@ -968,29 +986,30 @@ int ss_align_core(ss_ctx *ctx, const ss_op_t *ref, uint32_t n, const ss_op_t *cu
   int rc = make_ids(y.with_masks(kLdsKeys));
   if (rc != SS_OK) return rc;
   uint32_t keys = kLdsKeys - 1;
-  bool done = false;
+  bool done_rows = false;
+  auto rows = [&](bool one_by_one) -> int {
+    int r = keys <= few ? launch_rows<uint16_t>(ctx, y, d, hd, keys, done, one_by_one)
+                        : launch_rows<uint32_t>(ctx, y, d, hd, keys, done, one_by_one);
+    return r != SS_OK ? r : ss_wait_done(ctx, done);
+  };
   if (y.one_wg) {                       // rows at once, as if there were few keys (the kernel looks again): one wait less
-    if ((rc = launch_rows<uint16_t>(ctx, y, d, hd, keys)) != SS_OK) return rc;
-    SS_HIP(hipStreamSynchronize(s));
+    if ((rc = launch_rows<uint16_t>(ctx, y, d, hd, keys, done)) != SS_OK) return rc;
+    if ((rc = ss_wait_done(ctx, done)) != SS_OK) return rc;
     keys = *h_n_keys;
-    done = keys <= few;
+    done_rows = keys <= few;
   } else {
-    SS_HIP(hipStreamSynchronize(s));
+    if ((rc = ss_wait_done(ctx, keys_known)) != SS_OK) return rc;
     keys = *h_n_keys;
   }
-  if (!done) {
+  if (!done_rows) {
     if (y.with_masks(keys) > ctx->d_scratch_bytes) {
       if ((rc = make_ids(y.with_masks(keys))) != SS_OK) return rc;
     }
-    rc = keys <= few ? launch_rows<uint16_t>(ctx, y, d, hd, keys) : launch_rows<uint32_t>(ctx, y, d, hd, keys);
-    if (rc != SS_OK) return rc;
-    SS_HIP(hipStreamSynchronize(s));
+    if ((rc = rows(false)) != SS_OK) return rc;
   }
   if (*h_flag) {                        // a strip gave up: each after the one before it, then every word is there and none waits
     ctx->align_one_by_one += 1;
-    rc = keys <= few ? launch_rows<uint16_t>(ctx, y, d, hd, keys, true) : launch_rows<uint32_t>(ctx, y, d, hd, keys, true);
-    if (rc != SS_OK) return rc;
-    SS_HIP(hipStreamSynchronize(s));
+    if ((rc = rows(true)) != SS_OK) return rc;
   }
   if (n_keys_out) *n_keys_out = keys;
   uint32_t pairs = 0;

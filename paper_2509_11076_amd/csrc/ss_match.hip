@@ -57,6 +57,7 @@ struct PrepArgs {
   uint32_t n, m, k, cosine;
   uint4 *ones, *zeros;       uint32_t n_ones, n_zeros;       // in 16-byte words
   CosinePart *part;          // one per workgroup
+  ss_done done;              // if this is the call's last kernel
 };
 
 // kTogether: a thread reads four operators of each sequence together.  From device memory (500,000 of each one by one take
@@ -106,6 +107,7 @@ __global__ __launch_bounds__(256) void ss_prep_kernel(PrepArgs a) {
   for (uint32_t i = first; i < a.n_ones; i += stride) a.ones[i] = uint4{~0u, ~0u, ~0u, ~0u};
   for (uint32_t i = first; i < a.n_zeros; i += stride) a.zeros[i] = uint4{0, 0, 0, 0};
   if (a.cosine) put_part(a.part, dot, na, nb, bad);
+  ss_tell_host(a.done);
 }
 
 // occurrence counts per token of both sequences (token 0 never counts).  A model has few operator names, so most
@@ -137,13 +139,14 @@ __global__ __launch_bounds__(256) void ss_histogram_kernel(const ss_op_t *__rest
 
 __global__ __launch_bounds__(256) void ss_histdot_kernel(const uint32_t *__restrict__ h_ref,
                                                          const uint32_t *__restrict__ h_cur, uint32_t vocab,
-                                                         const uint32_t *__restrict__ flags, CosinePart *part) {
+                                                         const uint32_t *__restrict__ flags, CosinePart *part, ss_done done) {
   uint64_t dot = 0, na = 0, nb = 0;
   for (uint32_t i = blockIdx.x * blockDim.x + threadIdx.x; i < vocab; i += gridDim.x * blockDim.x) {
     const uint64_t a = h_cur[i], b = h_ref[i];
     dot += a * b; na += a * a; nb += b * b;
   }
   put_part(part, dot, na, nb, *flags);
+  ss_tell_host(done);
 }
 
 __device__ inline uint32_t wave_sum_u32(uint32_t v) {
@@ -585,7 +588,7 @@ __global__ __launch_bounds__(256) void ss_lookup_kernel(AnchorArgs g, KeyLists q
 }
 
 __global__ __launch_bounds__(256) void ss_injective_kernel(AnchorArgs g, int32_t *new_idx, uint8_t *level,
-                                                           uint32_t *lost_of_wg) {
+                                                           uint32_t *lost_of_wg, ss_done done) {
   __shared__ uint32_t lost_of[4];
   const uint32_t a = blockIdx.x * 256 + threadIdx.x;
   bool lost = false;
@@ -601,6 +604,7 @@ __global__ __launch_bounds__(256) void ss_injective_kernel(AnchorArgs g, int32_t
   if ((threadIdx.x & 63) == 0) lost_of[threadIdx.x >> 6] = (uint32_t)__popcll(b);
   __syncthreads();
   if (threadIdx.x == 0) lost_of_wg[blockIdx.x] = lost_of[0] + lost_of[1] + lost_of[2] + lost_of[3];
+  ss_tell_host(done);
 }
 
 }  // namespace
@@ -761,6 +765,10 @@ extern "C" int ss_match_sequence(ss_ctx *ctx, const ss_op_t *ref, uint32_t n, co
     }
     const uint32_t clears = std::max(p.n_ones, p.n_zeros);
     const uint32_t prep_wgs = std::max(wgs, std::min(kMaxParts, clears / 2048));
+    // the call's last kernel tells the host, unless copies follow it
+    ss_done done = search && !mapped ? ss_done{} : ss_next_done(ctx);
+    done.wgs = search ? out_wgs : hist ? 256 : prep_wgs;
+    if (!search && !hist) p.done = done;
     if (mapped && len > kTogetherMapped) hipLaunchKernelGGL(ss_prep_kernel<false>, dim3(prep_wgs), dim3(256), 0, s, p);
     else hipLaunchKernelGGL(ss_prep_kernel<true>, dim3(prep_wgs), dim3(256), 0, s, p);
     const uint32_t parts = hist ? 256 : prep_wgs;
@@ -768,7 +776,8 @@ extern "C" int ss_match_sequence(ss_ctx *ctx, const ss_op_t *ref, uint32_t n, co
     if (hist) {
       uint32_t *h_ref = (uint32_t *)(d + o_hist), *h_cur = h_ref + kTokenLimit, *bad = h_cur + kTokenLimit;
       hipLaunchKernelGGL(ss_histogram_kernel, dim3(wgs), dim3(256), 0, s, dref, n, dcur, m, h_ref, h_cur, bad);
-      hipLaunchKernelGGL(ss_histdot_kernel, dim3(256), dim3(256), 0, s, h_ref, h_cur, kTokenLimit, bad, dpart);
+      hipLaunchKernelGGL(ss_histdot_kernel, dim3(256), dim3(256), 0, s, h_ref, h_cur, kTokenLimit, bad, dpart,
+                         search ? ss_done{} : done);
     }
     SS_HIP(hipGetLastError());
     if (search) {
@@ -800,14 +809,15 @@ extern "C" int ss_match_sequence(ss_ctx *ctx, const ss_op_t *ref, uint32_t n, co
       }
       hipLaunchKernelGGL(ss_injective_kernel, dim3(out_wgs), dim3(256), 0, s, g,
                          (int32_t *)(mapped ? hd + ho_idx : d + o_idx), mapped ? hd + ho_level : d + o_level,
-                         (uint32_t *)(hd + ho_lost));
+                         (uint32_t *)(hd + ho_lost), done);
       SS_HIP(hipGetLastError());
       if (!mapped) {
         SS_HIP(hipMemcpyAsync(new_idx, d + o_idx, (size_t)k * 4, hipMemcpyDeviceToHost, s));
         SS_HIP(hipMemcpyAsync(level, d + o_level, k, hipMemcpyDeviceToHost, s));
       }
     }
-    SS_HIP(hipStreamSynchronize(s));
+    if (!done.flag) SS_HIP(hipStreamSynchronize(s));
+    else if ((rc = ss_wait_done(ctx, done)) != SS_OK) return rc;
     uint64_t sm[3] = {0, 0, 0}, too_large = 0;
     const CosinePart *part = (const CosinePart *)(h + ho_part);
     for (uint32_t w = 0; w < parts; ++w) {
@@ -825,7 +835,7 @@ extern "C" int ss_match_sequence(ss_ctx *ctx, const ss_op_t *ref, uint32_t n, co
       }
       for (uint32_t w = 0; w < out_wgs; ++w) n_unm += ((const uint32_t *)(h + ho_lost))[w];
     }
-    if (k && aligned) {                                      // the scratch is free again: the stream is idle
+    if (k && aligned) {                                      // the scratch is free again
       std::vector<int32_t> ref_to_cur(n);
       uint32_t lcs = 0;
       rc = ss_align_core(ctx, ref, n, cur, m, ref_to_cur.data(), &lcs, nullptr);

@@ -563,7 +563,8 @@ extern "C" int ss_destroy(ss_ctx *ctx) {
   if (ctx->staging) (void)hipHostFree(ctx->staging);
   if (ctx->ops) (void)hipHostFree(ctx->ops);
   if (ctx->events) (void)hipHostFree(ctx->events);
-  if (ctx->d_board) (void)hipFree(ctx->d_board);
+  if (ctx->d_told) (void)hipFree(ctx->d_told);
+  if (ctx->h_done) (void)hipHostFree(ctx->h_done);
   if (ctx->d_scratch) (void)hipFree(ctx->d_scratch);
   if (ctx->h_scratch) (void)hipHostFree(ctx->h_scratch);
   delete ctx;
@@ -582,7 +583,27 @@ extern "C" int ss_bind(ss_ctx *ctx, void *arena, uint64_t arena_bytes, void *com
   return SS_OK;
 }
 
+ss_done ss_next_done(ss_ctx *ctx) {
+  if (++ctx->done_count == 0) ctx->done_count = 1;          // the word starts at 0
+  return ss_done{ctx->d_told, ctx->d_done, ctx->done_count, 1};
+}
+
+// A look takes a few ns; after a millisecond, with the GPU busy with other work, the thread leaves the core to others.
+int ss_wait_done(ss_ctx *ctx, const ss_done &d) {
+  const auto until = std::chrono::steady_clock::now() + std::chrono::milliseconds(1);
+  do {
+    for (int i = 0; i < 64; ++i) {
+      if (__atomic_load_n(ctx->h_done, __ATOMIC_ACQUIRE) == d.value) return SS_OK;
+      __builtin_ia32_pause();
+    }
+  } while (std::chrono::steady_clock::now() < until);
+  SS_HIP(hipStreamSynchronize(ctx->s_aux));
+  return SS_OK;
+}
+
 int ss_scratch_reserve(ss_ctx *ctx, size_t dev_bytes, size_t host_bytes) {
+  // the kernel of a call that has returned may still be on its way to its end
+  if (dev_bytes > ctx->d_scratch_bytes || host_bytes > ctx->h_scratch_bytes) SS_HIP(hipStreamSynchronize(ctx->s_aux));
   if (dev_bytes > ctx->d_scratch_bytes) {
     if (ctx->d_scratch) SS_HIP(hipFree(ctx->d_scratch));
     ctx->d_scratch = nullptr;
@@ -602,7 +623,7 @@ int ss_scratch_reserve(ss_ctx *ctx, size_t dev_bytes, size_t host_bytes) {
     ctx->h_scratch = nullptr;
     ctx->h_scratch_bytes = 0;
     size_t want = ss_align_up(host_bytes + host_bytes / 4, 1 << 20);
-    hipError_t e = hipHostMalloc(&ctx->h_scratch, want, hipHostMallocDefault);
+    hipError_t e = hipHostMalloc(&ctx->h_scratch, want, hipHostMallocMapped | hipHostMallocCoherent);
     if (e != hipSuccess) {
       ctx->stats.last_hip_error = (int32_t)e;
       ss_note_hip_error((int)e, __FILE__, __LINE__);

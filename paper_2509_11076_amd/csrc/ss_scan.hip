@@ -68,6 +68,7 @@ struct ScanArgs {
   const ss_event_t *src_ev, *src_pev;
   // outputs
   int64_t *per_op, *mre, *timeline;
+  ss_done done;             // host calls
   ss_scan_result_t *res;    // the flags go to res->reserved (bit 0: an event names an operator >= n_ops, nothing
                             // else is meaningful; bit 1: a list is not in operator order)
 };
@@ -701,6 +702,7 @@ __global__ __launch_bounds__(T) void ss_scan_short_kernel(ScanArgs a, uint32_t t
   __shared__ ShortShared<T> sh;
   extern __shared__ __align__(16) uint8_t short_mem[];
   scan_short<T, K>(a, short_mem, tl_at, sh);
+  ss_tell_host(a.done);
 }
 
 // candidate policies against the same trace
@@ -710,6 +712,7 @@ __global__ __launch_bounds__(T) void ss_scan_short_batch_kernel(const ScanArgs *
   extern __shared__ __align__(16) uint8_t short_mem[];
   const ScanArgs a = args[blockIdx.x];
   scan_short<T, K>(a, short_mem, 0, sh);
+  ss_tell_host(a.done);
 }
 
 // lanes and events to a lane for two lists of that many
@@ -747,6 +750,7 @@ __global__ __launch_bounds__(kThreads) void ss_scan_batch_kernel(const ScanArgs 
   } else {
     scan_wg<kThreads, 4>(a, a.at, a.pos, a.net, sh);
   }
+  ss_tell_host(a.done);
 }
 
 // ---- long traces: two launches over tiles of events -----------------------------------------------------------------
@@ -953,10 +957,13 @@ __device__ __forceinline__ bool ends_last(TileBoard *b, uint32_t wgs, uint32_t *
 // all their maxima; it waits for each as the tiles do, and goes through the operators of one that doesn't come itself.
 // (With a fence and a counter, the last one folding: two operator workgroups 6 us more than one.)  Lists out of order are
 // gathered by all workgroups, and the last one to end does the operators.
-__global__ __launch_bounds__(kThreads) void ss_scan_finish_kernel(ScanArgs a, uint32_t op_wgs) {
-  __shared__ Best part[kWaves];
-  __shared__ SumShared sh;
-  __shared__ uint32_t s_last, s_flags[kWaves];
+struct FinishShared {
+  Best part[kWaves];
+  SumShared sums;
+  uint32_t last, flags[kWaves];
+};
+
+__device__ __forceinline__ void scan_finish(const ScanArgs &a, uint32_t op_wgs, FinishShared &sh) {
   const uint32_t n = a.n_ops, tid = threadIdx.x;
   const uint32_t scan = (uint32_t)(a.board->tile[4][0] >> 32);      // this scan's number, as the first launch used it
   if (blockIdx.x == 0 && tid == 0) a.board->scan = scan;
@@ -965,10 +972,10 @@ __global__ __launch_bounds__(kThreads) void ss_scan_finish_kernel(ScanArgs a, ui
   uint32_t flags = 0;
   for (uint32_t i = tid; i < a.tiles0 + a.tiles1; i += kThreads) flags |= (uint32_t)a.board->tile[4][i] >> 30;
   flags = (__ballot(flags & 1u) ? 1u : 0u) | (__ballot(flags & 2u) ? 2u : 0u);
-  if ((tid & 63) == 0) s_flags[tid >> 6] = flags;
+  if ((tid & 63) == 0) sh.flags[tid >> 6] = flags;
   __syncthreads();
   flags = 0;
-  for (int i = 0; i < kWaves; ++i) flags |= s_flags[i];
+  for (int i = 0; i < kWaves; ++i) flags |= sh.flags[i];
   if (flags & 1u) {
     if (blockIdx.x == 0 && tid == 0) write_result(a, no_best(), a.base, flags);
     return;
@@ -980,10 +987,10 @@ __global__ __launch_bounds__(kThreads) void ss_scan_finish_kernel(ScanArgs a, ui
 #pragma unroll
       for (int k = 0; k < kGatherK; ++k) gather_run(a.pos, a.net, x[k], n);
     }
-    if (!ends_last(a.board, gridDim.x, &s_last)) return;
-    Best b = ops_of_sums<kThreads>(a, a.pos, a.net, sh);
-    b = wg_best<kThreads>(b, part);
-    if (tid == 0) write_result(a, b, a.base + (n ? sh.tot_sp : 0), flags);
+    if (!ends_last(a.board, gridDim.x, &sh.last)) return;
+    Best b = ops_of_sums<kThreads>(a, a.pos, a.net, sh.sums);
+    b = wg_best<kThreads>(b, sh.part);
+    if (tid == 0) write_result(a, b, a.base + (n ? sh.sums.tot_sp : 0), flags);
     return;
   }
   if (blockIdx.x >= op_wgs) {
@@ -1002,7 +1009,7 @@ __global__ __launch_bounds__(kThreads) void ss_scan_finish_kernel(ScanArgs a, ui
       put_op(a, t, a.base + at_ev[t + 1].sp + at_pe[t + 1].sp + at_ev[t].sn + at_pe[t].sn, b);
     return b;
   };
-  Best b = wg_best<kThreads>(operators(blockIdx.x * kThreads + tid, op_wgs * kThreads), part);
+  Best b = wg_best<kThreads>(operators(blockIdx.x * kThreads + tid, op_wgs * kThreads), sh.part);
   if (blockIdx.x) {
     const uint32_t x[4] = {low_half(b.val), high_half(b.val), b.idx, b.over};
     if (tid == 0) tell(a.board->best, blockIdx.x, scan, x);
@@ -1019,9 +1026,15 @@ __global__ __launch_bounds__(kThreads) void ss_scan_finish_kernel(ScanArgs a, ui
       other = Best{both_halves(x[0], x[1]), x[2], x[3]};
     }
     if (__syncthreads_or(!there)) other = operators(tid, kThreads);
-    b = wg_best<kThreads>(other, part);
+    b = wg_best<kThreads>(other, sh.part);
   }
   if (tid == 0) write_result(a, b, a.base + at_ev[n].sp + at_ev[n].sn + at_pe[n].sp + at_pe[n].sn, 0);
+}
+
+__global__ __launch_bounds__(kThreads) void ss_scan_finish_kernel(ScanArgs a, uint32_t op_wgs) {
+  __shared__ FinishShared sh;
+  scan_finish(a, op_wgs, sh);
+  ss_tell_host(a.done);
 }
 
 // Events of a tile.  Few to a lane is the faster form as long as there are no more tiles than a workgroup may read (the
@@ -1094,6 +1107,7 @@ void launch_scan(hipStream_t s, ScanArgs &a) {
   if (per_lane == 2) hipLaunchKernelGGL((ss_scan_running_kernel<2, true>), dim3(tiles), dim3(kTileThreads), 0, s, a);
   else if (per_lane == 4) hipLaunchKernelGGL((ss_scan_running_kernel<4, true>), dim3(tiles), dim3(kTileThreads), 0, s, a);
   else hipLaunchKernelGGL((ss_scan_running_kernel<8, false>), dim3(tiles), dim3(kTileThreads), 0, s, a);
+  a.done.wgs = op_wgs + ev_wgs;
   hipLaunchKernelGGL(ss_scan_finish_kernel, dim3(op_wgs + ev_wgs), dim3(kThreads), 0, s, a, op_wgs);
 }
 
@@ -1139,9 +1153,14 @@ int ss_scan_init(ss_ctx *ctx) {
   const int rc = static_scratch_ptr(ctx->device, &p, &e);
   if (rc == SS_E_HIP) SS_HIP(e);
   if (rc != SS_OK) return rc;
-  SS_HIP(hipMalloc(&ctx->d_board, sizeof(TileBoard)));
-  SS_HIP(hipMemset(ctx->d_board, 0, sizeof(TileBoard)));
+  constexpr size_t kBoardAt = 256;
+  SS_HIP(hipMalloc((void **)&ctx->d_told, kBoardAt + sizeof(TileBoard)));
+  SS_HIP(hipMemset(ctx->d_told, 0, kBoardAt + sizeof(TileBoard)));
   SS_HIP(hipStreamSynchronize(nullptr));
+  ctx->d_board = (uint8_t *)ctx->d_told + kBoardAt;
+  SS_HIP(hipHostMalloc((void **)&ctx->h_done, 256, hipHostMallocMapped | hipHostMallocCoherent));
+  *ctx->h_done = 0;
+  SS_HIP(hipHostGetDevicePointer((void **)&ctx->d_done, ctx->h_done, 0));
   return SS_OK;
 }
 
@@ -1210,6 +1229,8 @@ extern "C" int ss_timeline_scan_batch(ss_ctx *ctx, const ss_event_t *ev, uint64_
       if (n_pe) SS_HIP(hipMemcpyAsync(d + o_pev, pev, pe_bytes, hipMemcpyHostToDevice, s));
     }
     const uint8_t *const in = mapped ? hd : d;
+    ss_done done = ss_next_done(ctx);
+    done.wgs = k;
     ScanArgs *ha = (ScanArgs *)h;                       // pinned, read and written by the kernel: arguments, results
     for (uint32_t c = 0; c < k; ++c) {
       uint8_t *w = d + o_work + (size_t)c * per_scan;
@@ -1223,6 +1244,7 @@ extern "C" int ss_timeline_scan_batch(ss_ctx *ctx, const ss_event_t *ev, uint64_
         a.pos = (int64_t *)(w + ss_align_up(2 * (n + 1) * sizeof(OpAt), 256));
         a.net = a.pos + ss_align_up(n * 8, 256) / 8;
       }
+      a.done = done;
       if (per_op) a.per_op = (int64_t *)(d + o_per_op) + (size_t)c * n;
       a.res = (ss_scan_result_t *)(hd + args_bytes) + c;
       ha[c] = a;
@@ -1243,7 +1265,7 @@ extern "C" int ss_timeline_scan_batch(ss_ctx *ctx, const ss_event_t *ev, uint64_
     } else if (lds) hipLaunchKernelGGL(ss_scan_batch_kernel<true>, dim3(k), dim3(kThreads), lds_at(n_ops), s, dargs);
     else hipLaunchKernelGGL(ss_scan_batch_kernel<false>, dim3(k), dim3(kThreads), 0, s, dargs);
     SS_HIP(hipGetLastError());
-    SS_HIP(hipStreamSynchronize(s));
+    if ((rc = ss_wait_done(ctx, done)) != SS_OK) return rc;
     const ss_scan_result_t *hres = (const ss_scan_result_t *)(h + args_bytes);
     for (uint32_t c = 0; c < k; ++c)
       if (hres[c].reserved & 1u) return SS_E_INVAL;
@@ -1313,9 +1335,10 @@ extern "C" int ss_timeline_scan(ss_ctx *ctx, const ss_event_t *ev, uint64_t n_ev
     a.mre = mre ? (int64_t *)(out + o_mre) : nullptr;
     a.timeline = timeline ? (int64_t *)(out + o_tl) : nullptr;
     a.res = (ss_scan_result_t *)(hd + o_res);
+    a.done = ss_next_done(ctx);
     launch_scan(s, a);
     SS_HIP(hipGetLastError());
-    SS_HIP(hipStreamSynchronize(s));
+    if ((rc = ss_wait_done(ctx, a.done)) != SS_OK) return rc;
     ss_scan_result_t r;
     std::memcpy(&r, h + o_res, sizeof(r));
     const uint32_t flags = r.reserved;

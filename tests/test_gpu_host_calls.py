@@ -1,0 +1,49 @@
+"""Host calls return once their last kernel has told the host, or, where that takes long, once the stream is idle: the same
+results on an idle GPU and beside products that hold every compute unit, many calls in a row, buffers growing in between."""
+import numpy as np
+import pytest
+
+from test_gpu_trace_scan_match import P, ctx          # noqa: F401  (fixtures)
+from test_gpu_scan_edges import events
+
+pytestmark = pytest.mark.gpu
+
+
+def operators(P, rng, n):                              # noqa: F811
+    ops = np.zeros(n, dtype=P.OP_DT)
+    ops["op_token"], ops["stack_hash"], ops["n_out"] = rng.integers(1, 9, n), rng.integers(1, 5, n), 1
+    ops["sig"] = 1 | (1 << 8)
+    return ops
+
+
+def test_results_beside_work_on_the_compute_stream(P, ctx):                          # noqa: F811
+    import torch
+    rng = np.random.default_rng(11)
+    calls = []
+    for n_ev, n_ops in ((100, 66), (9000, 3000), (60000, 9000), (300, 200)):
+        ev, pe = events(rng, n_ev, n_ops), events(rng, n_ev // 4, n_ops)
+        calls.append(lambda ev=ev, pe=pe, n=n_ops: P.ss_timeline_scan(ctx, ev, pe, n, 5, 1 << 40, want_timeline=True))
+        calls.append(lambda ev=ev, pe=pe, n=n_ops: P.ss_timeline_scan_batch(ctx, ev, [pe, None, pe[:50]], n, 5, 9, want_per_op=True))
+    for n, k in ((90, 30), (1500, 400), (7000, 5000)):
+        ref, cur = operators(P, rng, n), operators(P, rng, n + 7)
+        anchors = np.zeros(k, dtype=P.ANCHOR_DT)
+        anchors["ref_op"] = np.sort(rng.choice(n, k, replace=False))
+        for flags in (0, P.SS_MATCH_HISTOGRAM, P.SS_MATCH_ALIGN):
+            calls.append(lambda r=ref, c=cur, a=anchors, f=flags: P.ss_match_sequence(ctx, r, c, a, flags=f))
+        calls.append(lambda r=ref, c=cur: P.ss_match_sequence(ctx, r, c, None))
+        calls.append(lambda r=ref, c=cur, a=anchors: P.ss_align_sequence(ctx, r, c, a))
+
+    def same(x, y):
+        if isinstance(x, list):
+            return len(x) == len(y) and all(same(p, q) for p, q in zip(x, y))
+        return x.keys() == y.keys() and all(np.array_equal(x[k], y[k]) for k in x)
+    idle = [f() for f in calls]
+    m = torch.ones(8192, 8192, dtype=torch.bfloat16, device="cuda")
+    for _ in range(2):
+        for f, want in zip(calls, idle):
+            for _ in range(3):
+                m @ m                                  # about a millisecond each
+            assert same(f(), want)
+        torch.cuda.synchronize()
+        for f, want in zip(calls, idle):
+            assert all(same(f(), want) for _ in range(5))
