@@ -205,18 +205,21 @@ ss_done ss_next_done(ss_ctx *ctx);                 // for the next kernel on s_a
 int ss_wait_done(ss_ctx *ctx, const ss_done &d);   // the stream itself is waited for where the word doesn't come soon
 
 #ifdef __HIPCC__
-// The last thing that every thread of each of the workgroups calls.  Pinned memory is coherent here, so a wavefront's stores
-// have arrived once its store counter is zero.
+// The last thing that every thread of each of the workgroups calls.  Results written to pinned memory may still be in the
+// L2 of the workgroup's die when its stores have completed: every workgroup releases its own to the system before it counts
+// (the last one's release writes back its own die's only; beside products on the compute stream the host then saw the word
+// before other dies' results).
 __device__ __forceinline__ void ss_tell_host(const ss_done &d) {
   if (!d.flag) return;
-  __builtin_amdgcn_s_waitcnt(0x0F70);              // vmcnt(0)
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
   __syncthreads();
   if (threadIdx.x) return;
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "");
   if (d.wgs > 1) {
-    if (atomicAdd(d.told, 1u) + 1 != d.wgs) return;
+    if (__hip_atomic_fetch_add(d.told, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) + 1 != d.wgs) return;
     __hip_atomic_store(d.told, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   }
-  __hip_atomic_store(d.flag, d.value, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
+  __hip_atomic_store(d.flag, d.value, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
 }
 #endif
 

@@ -941,7 +941,7 @@ constexpr int kGatherK = 1;
 
 // true in the workgroup that ends last of `wgs` that call this; what the others wrote before is visible to it
 __device__ __forceinline__ bool ends_last(TileBoard *b, uint32_t wgs, uint32_t *s_last) {
-  __builtin_amdgcn_s_waitcnt(0x0F70);                        // vmcnt(0): this wavefront's stores and atomics are complete
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");           // this wavefront's stores and atomics are complete
   __syncthreads();
   if (threadIdx.x == 0) {
     __threadfence();                                         // for the workgroup (one fence each: 64 workgroups' 1,024 took 14 us)

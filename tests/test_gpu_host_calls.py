@@ -47,3 +47,27 @@ def test_results_beside_work_on_the_compute_stream(P, ctx):                     
         torch.cuda.synchronize()
         for f, want in zip(calls, idle):
             assert all(same(f(), want) for _ in range(5))
+
+
+@pytest.mark.parametrize("n_ev,n_ops", [(60000, 9000), (20000, 3000)])
+def test_the_word_comes_after_every_result(P, ctx, n_ev, n_ops):                     # noqa: F811
+    """two inputs in turn, so that a result that is late is the other input's; beside short products and beside kernels that
+    keep the caches full of their own stores (a word that did not wait for other dies' results: 2 to 4 % of the calls)"""
+    import torch
+    rng = np.random.default_rng([n_ev, n_ops])
+    inputs = [(events(rng, n_ev, n_ops), events(rng, n_ev // 4, n_ops), 5 + 1000003 * i) for i in (1, 2)]
+
+    def call(i):
+        ev, pe, base = inputs[i]
+        return P.ss_timeline_scan(ctx, ev, pe, n_ops, base, 1 << 40, want_timeline=True)
+    want = [call(0), call(1)]
+    m = torch.ones(4096, 4096, dtype=torch.bfloat16, device="cuda")
+    full = torch.zeros(1 << 28, dtype=torch.uint8, device="cuda")
+    for work in (lambda: m @ m, lambda: full.add_(1)):
+        for _ in range(250):
+            for _ in range(6):
+                work()
+            for i in (0, 1):
+                got = call(i)
+                assert all(np.array_equal(got[k], want[i][k]) for k in got)
+        torch.cuda.synchronize()
