@@ -267,7 +267,7 @@ typedef struct {
 typedef struct {
   uint64_t bytes_out, bytes_in;         /* since ss_create                                  */
   uint64_t kernel_batches, engine_batches;
-  uint64_t free_waits, in_waits;        /* device-side stream waits issued for FREE / WAIT_IN */
+  uint64_t free_waits, in_waits;        /* batches the compute stream was put behind by FREE / WAIT_IN */
   uint64_t ops_recorded, events_recorded;
   int32_t last_hip_error;               /* hipError_t of the last failing HIP call, 0 if none */
   uint32_t engine_batches_out;          /* of engine_batches, the swap-out ones             */
@@ -552,7 +552,10 @@ int ss_generate_policy_best(ss_ctx *ctx, const ss_op_t *ops, uint32_t n_ops, con
 /* Enqueue swap-out batch `batch`: the swap-out stream waits (on the device) for
  * everything enqueued so far on the compute stream, copies each tensor of the
  * batch to its staging slot and records the batch's done-event.  Returns at
- * once. */
+ * once.  A copy-kernel batch of at most 256 KiB is copied on the compute stream itself, by both calls, while
+ * no batch on a swap stream is outstanding (issued, and neither released / waited for nor drained): that delays
+ * the compute stream by less than the events between two streams.  Not with SS_CFG_MEMORY_MARKERS, copy_cus, an
+ * HBM ring, or addresses given with the call. */
 int ss_swap_out(ss_ctx *ctx, uint32_t batch);
 
 /* Enqueue swap-in batch `batch`: the swap-in stream waits for everything
@@ -585,7 +588,8 @@ int ss_swap_in_to(ss_ctx *ctx, uint32_t batch, void *const *dev_dst /* host arra
 enum { SS_SYNC_FREE = 0,    /* id = tensor: compute stream waits (device-side) for that tensor's
                                swap-out; after this call its block may be given to later operators */
        SS_SYNC_WAIT_IN = 1, /* id = tensor: compute stream waits (device-side) for its swap-in     */
-       SS_SYNC_DRAIN = 2,   /* host waits for both swap streams; surfaces asynchronous errors      */
+       SS_SYNC_DRAIN = 2,   /* host waits for both swap streams and for the batches copied on the compute
+                               stream (not for what follows them there); surfaces asynchronous errors */
        SS_SYNC_ITERATION_END = 3 };
                             /* ends the iteration like SS_SYNC_DRAIN (batches may be issued again, the
                                other set of events is used) without making the host wait for it: the swap

@@ -25,6 +25,8 @@
 // training step running on the compute stream.
 #include "ss_internal.h"
 
+#include <hip/hip_ext.h>
+
 namespace {
 
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
@@ -245,21 +247,21 @@ void ss_launch_wait_flag(hipStream_t s, const uint64_t *flag, uint64_t want, uin
 void ss_launch_copy(hipStream_t s, uint32_t workgroups, uint32_t unroll, bool to_host, uint8_t *arena,
                     uint8_t *staging, const ss_desc_t *d_descs, const uint32_t *d_chunk0,
                     const uint32_t *d_chunk_desc, uint32_t n_chunks, uint32_t chunk_shift, uint32_t n_desc,
-                    bool lds_lookup) {
+                    bool lds_lookup, hipEvent_t done) {
   if (n_chunks == 0) return;
   const dim3 grid(workgroups < n_chunks ? workgroups : n_chunks), block(SS_COPY_THREADS);
   if (lds_lookup && n_desc != 0 && n_desc + 1 <= kLdsPrefixMax) {      // a batch too long for LDS takes the table
     if (to_host)
-      hipLaunchKernelGGL((ss_copy_kernel<true, 8, true>), grid, block, 0, s, arena, staging, d_descs, d_chunk0,
-                         d_chunk_desc, n_chunks, chunk_shift, n_desc);
+      hipExtLaunchKernelGGL((ss_copy_kernel<true, 8, true>), grid, block, 0, s, nullptr, done, 0, arena, staging, d_descs,
+                            d_chunk0, d_chunk_desc, n_chunks, chunk_shift, n_desc);
     else
-      hipLaunchKernelGGL((ss_copy_kernel<false, 8, true>), grid, block, 0, s, arena, staging, d_descs, d_chunk0,
-                         d_chunk_desc, n_chunks, chunk_shift, n_desc);
+      hipExtLaunchKernelGGL((ss_copy_kernel<false, 8, true>), grid, block, 0, s, nullptr, done, 0, arena, staging, d_descs,
+                            d_chunk0, d_chunk_desc, n_chunks, chunk_shift, n_desc);
     return;
   }
 #define SS_LAUNCH(TH, U)                                                                                  \
-  hipLaunchKernelGGL((ss_copy_kernel<TH, U, false>), grid, block, 0, s, arena, staging, d_descs, d_chunk0, \
-                     d_chunk_desc, n_chunks, chunk_shift, n_desc)
+  hipExtLaunchKernelGGL((ss_copy_kernel<TH, U, false>), grid, block, 0, s, nullptr, done, 0, arena, staging, d_descs, \
+                        d_chunk0, d_chunk_desc, n_chunks, chunk_shift, n_desc)
   if (to_host) {
     if (unroll <= 2) SS_LAUNCH(true, 2); else if (unroll <= 4) SS_LAUNCH(true, 4); else SS_LAUNCH(true, 8);
   } else {

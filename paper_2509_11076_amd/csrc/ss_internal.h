@@ -36,6 +36,10 @@ struct ss_sched {
   std::unordered_map<uint32_t, uint32_t> out_of_tensor, in_of_tensor;  // tensor id -> descriptor index
   std::vector<uint32_t> out_batch_of, in_batch_of;                      // descriptor index -> batch
   std::vector<uint8_t> out_waited, in_waited, out_issued, in_issued;    // per batch, this iteration
+  std::vector<uint8_t> out_inline, in_inline;                           // per batch, this iteration: copied on the compute stream
+  hipEvent_t last_inline = nullptr;               // done-event of the latest of these since the streams were last joined
+  bool any_inline = false;                        // this iteration has some
+  uint32_t unsettled = 0;                         // batches on streams of their own that the compute stream doesn't wait for yet
   // Per-batch events exist twice: iterations alternate between the two sets (`phase`, switched by the
   // drain), so that the timing of the iteration drained last stays readable while the next one runs.
   std::vector<hipEvent_t> ev_out_done[2], ev_in_done[2], ev_out_start[2], ev_in_start[2];
@@ -141,8 +145,10 @@ struct ss_ctx {
   uint32_t *h_mark_timeouts = nullptr, *d_mark_timeouts = nullptr;   // pinned word and its device address
   uint64_t mark_limit_ticks = 0;
   // SS_SYNC_ITERATION_END: end-of-iteration events of the swap streams, two sets used in turn (out streams 0..3,
-  // in streams 4..7, ring-transfer stream 8); at most one iteration is outstanding behind the one being issued
-  hipEvent_t ev_iter[2][9] = {};
+  // in streams 4..7, ring-transfer stream 8, compute stream 9); at most one iteration is outstanding behind the one being
+  // issued
+  static constexpr int kIterEvents = 10;
+  hipEvent_t ev_iter[2][kIterEvents] = {};
   bool iter_pending[2] = {false, false};
   uint64_t iter_last_seq[2] = {0, 0};
   int iter_set = 0;
@@ -249,7 +255,7 @@ constexpr uint32_t SS_COPY_THREADS = 256;
 void ss_launch_copy(hipStream_t s, uint32_t workgroups, uint32_t unroll, bool to_host, uint8_t *arena,
                     uint8_t *staging, const ss_desc_t *d_descs, const uint32_t *d_chunk0,
                     const uint32_t *d_chunk_desc, uint32_t n_chunks, uint32_t chunk_shift, uint32_t n_desc,
-                    bool lds_lookup);
+                    bool lds_lookup, hipEvent_t done = nullptr /* recorded with the kernel's end, if there is one */);
 // one tensor by its two addresses, no descriptor table (16-byte aligned on both sides)
 void ss_launch_copy_flat(hipStream_t s, uint32_t workgroups, const uint8_t *src, uint8_t *dst, uint64_t nbytes);
 void ss_launch_fill(hipStream_t s, uint8_t *dst, uint64_t nbytes, uint8_t value);

@@ -506,11 +506,20 @@ static void free_events(std::vector<hipEvent_t> &v) {
 // host joins every swap stream of both directions
 static int sync_swap_streams(ss_ctx *ctx) {
   eq_wait_idle(ctx);                  // the ring transfers pushed so far are on their stream
+  if (ctx->sched.last_inline) {       // copies on the compute stream: up to the latest, not what the program put behind it
+    const hipEvent_t last = ctx->sched.last_inline;
+    ctx->sched.last_inline = nullptr;
+    if (hipStreamWaitEvent(ctx->s_in[0], last, 0) != hipSuccess) {     // recorded into a graph that the program captured
+      (void)hipGetLastError();
+      SS_HIP(hipStreamSynchronize(ctx->compute));
+    }
+  }
   for (uint32_t i = 0; i < ctx->n_s_out; ++i)
     if (ctx->s_out[i]) SS_HIP(hipStreamSynchronize(ctx->s_out[i]));
   for (uint32_t i = 0; i < ctx->n_s_in; ++i)
     if (ctx->s_in[i]) SS_HIP(hipStreamSynchronize(ctx->s_in[i]));
   if (ctx->s_flush) SS_HIP(hipStreamSynchronize(ctx->s_flush));
+  ctx->sched.unsettled = 0;
   return SS_OK;
 }
 
@@ -548,7 +557,7 @@ extern "C" int ss_destroy(ss_ctx *ctx) {
   sched_release(ctx->sched);
   for (hipEvent_t ev : ctx->ev_ring) (void)hipEventDestroy(ev);
   for (int p = 0; p < 2; ++p)
-    for (int k = 0; k < 9; ++k)
+    for (int k = 0; k < ss_ctx::kIterEvents; ++k)
       if (ctx->ev_iter[p][k]) (void)hipEventDestroy(ctx->ev_iter[p][k]);
   for (int i = 0; i < ss_ctx::kMaxSwapStreams; ++i) {       // joined above: nothing is pending on them
     if (ctx->s_out[i]) ctx->pooled_streams ? pool_give(ctx->device, kRoleOut + i, ctx->s_out[i]) : (void)hipStreamDestroy(ctx->s_out[i]);
@@ -639,6 +648,9 @@ int ss_scratch_reserve(ss_ctx *ctx, size_t dev_bytes, size_t host_bytes) {
 
 // per-iteration state of the staged swap-out path
 static void ring_reset(ss_sched &s, uint32_t n_slots) {
+  std::fill(s.out_inline.begin(), s.out_inline.end(), 0);
+  std::fill(s.in_inline.begin(), s.in_inline.end(), 0);
+  s.any_inline = false;
   std::fill(s.done_ev_of.begin(), s.done_ev_of.end(), -1);
   std::fill(s.ring_state.begin(), s.ring_state.end(), 0);
   for (size_t g = 0; g < s.groups.size(); ++g) {
@@ -810,8 +822,10 @@ extern "C" int ss_load_schedule(ss_ctx *ctx, const ss_desc_t *descs_out, uint32_
         s.in_of_tensor[s.in[i].tensor_id] = i;
       }
     s.out_waited.assign(n_out_batches, 0);
+    s.out_inline.assign(n_out_batches, 0);
     s.out_issued.assign(n_out_batches, 0);
     s.in_waited.assign(n_in_batches, 0);
+    s.in_inline.assign(n_in_batches, 0);
     s.in_issued.assign(n_in_batches, 0);
     s.last_engine_out = -1;
     // staged swap-out: group consecutive batches whose staging slots form one gap-free range (every size
@@ -1295,6 +1309,36 @@ extern "C" int ss_swap_in_to(ss_ctx *ctx, uint32_t batch, void *const *dev_dst) 
   return rc;
 }
 
+// Small batches are copied by a kernel on the compute stream itself.  On a stream of its own a batch takes an event in each
+// direction between the two streams, which costs the host five calls instead of two and the compute stream more than the copy
+// does.  24 batches of one tensor beside compute kernels of 30 us each, waited for three operators later (us for all):
+// 16 KiB 888 on a stream of their own and 849 on the compute stream, 64 KiB 890 and 868, 128 KiB 891 and 897, 256 KiB 886
+// and 960; beside kernels of 6 us 580 and 237, 589 and 249, 642 and 277, 635 and 333; of 63 us 1,720 and 1,634 ... 1,724 and
+// 1,748; waited for at once 1,236 and 849 ... 1,315 and 960.  (Without any copy 767, 137 and 1,554.)  So up to 256 KiB it is
+// the faster form or 2 to 8 % of such a step slower, and beyond it a copy that may overlap should.
+// Only while no batch on a stream of its own is on its way as far as the compute stream knows: beside one the copy would
+// queue for the link with the compute stream behind it, and the orders below (a swap-in after the swap-outs of its tensors, a
+// staging slot written again) follow from the compute stream's own.
+constexpr uint64_t kInlineBytes = 256u << 10;
+
+static bool copies_inline(const ss_ctx *ctx, bool engine, uint64_t bytes) {
+  const ss_sched &s = ctx->sched;
+  return !engine && bytes <= kInlineBytes && s.unsettled == 0 && !s.flat_next && !ctx->d_mark && !ctx->cfg.copy_cus &&
+         !ctx->ring && !ctx->ring_in;
+}
+
+// The done-event of a batch copied on the compute stream goes with the kernel's launch: 24 of them 125 us, recorded by calls of
+// their own 147.  Where batches are timed all events are recorded alike.
+static hipEvent_t with_kernel(const ss_ctx *ctx, bool in_line, hipEvent_t done) {
+  return in_line && !(ctx->cfg.flags & (SS_CFG_TIMING | SS_CFG_STALL_TIMING)) ? done : nullptr;
+}
+
+static uint64_t batch_bytes(const std::vector<ss_desc_t> &d, uint32_t lo, uint32_t hi) {
+  uint64_t bytes = 0;
+  for (uint32_t i = lo; i < hi; ++i) bytes += d[i].nbytes;
+  return bytes;
+}
+
 static int swap_out_batch(ss_ctx *ctx, uint32_t batch) {
   ss_sched &s = ctx->sched;
   if (!s.loaded || !ctx->bound) return SS_E_STATE;
@@ -1317,27 +1361,29 @@ static int swap_out_batch(ss_ctx *ctx, uint32_t batch) {
   const bool engine = ctx->eq ? false
                     : s.flat_next ? ctx->cfg.copy_path != SS_PATH_KERNEL
                                   : use_engine(ctx, ctx->cfg.copy_path, true, s.out, lo, hi);
+  const uint64_t bytes = batch_bytes(s.out, lo, hi);
+  const bool in_line = copies_inline(ctx, engine, bytes);
+  const hipEvent_t done = with_kernel(ctx, in_line, s.ev_out_done[s.phase][batch]);
+  bool recorded = false;
   // copy-kernel batches take the swap-out streams in turn; copy-engine batches stay on the first
-  hipStream_t so = engine ? ctx->s_out[0] : ctx->s_out[batch % ctx->n_s_out];
+  hipStream_t so = in_line ? ctx->compute : engine ? ctx->s_out[0] : ctx->s_out[batch % ctx->n_s_out];
   // the tensors' last forward use is already enqueued on the compute stream: order after it
   ss_marker mark;
   if (s.group_of[batch] >= 0) {
     const int rc = swap_out_staged(ctx, batch, mark);
     if (rc < 0) return rc;
     if (rc == 1) {
-      uint64_t moved = 0;
-      for (uint32_t i = lo; i < hi; ++i) moved += s.out[i].nbytes;
-      ctx->stats.bytes_out += moved;
+      ctx->stats.bytes_out += bytes;
       return SS_OK;
     }
   }
-  {
+  if (!in_line) {
     const int rm = wait_for_compute(ctx, mark, so, !engine);
     if (rm != SS_OK) return rm;
+  } else if (ctx->cfg.flags & SS_CFG_STALL_TIMING) {         // the compute stream stands still for the copy
+    SS_HIP(hipEventRecord(s.ev_free_at[batch], so));
   }
   if (ctx->cfg.flags & SS_CFG_TIMING) SS_HIP(hipEventRecord(s.ev_out_start[s.phase][batch], so));
-  uint64_t bytes = 0;
-  for (uint32_t i = lo; i < hi; ++i) bytes += s.out[i].nbytes;
   if (engine) {
     if (ctx->cfg.engine_window_out && s.engine_out_issued.size() >= ctx->cfg.engine_window_out) {   // see swap_in_batch
       const uint32_t old = s.engine_out_issued[s.engine_out_issued.size() - ctx->cfg.engine_window_out];
@@ -1362,17 +1408,25 @@ static int swap_out_batch(ss_ctx *ctx, uint32_t batch) {
     const uint32_t *c0 = s.d_out_chunk0 + lo + batch;
     const uint32_t n_chunks = s.out_chunk0[(size_t)hi + batch];
     ss_launch_copy(so, ctx->cfg.copy_workgroups_out, ctx->cfg.copy_unroll, true, ctx->arena, ctx->staging_dev, s.d_out + lo, c0,
-                   s.d_out_cdesc + s.out_cbase[batch], n_chunks, s.out_shift[batch], hi - lo, ctx->cfg.copy_desc_lookup == 1);
+                   s.d_out_cdesc + s.out_cbase[batch], n_chunks, s.out_shift[batch], hi - lo, ctx->cfg.copy_desc_lookup == 1, done);
     SS_HIP(hipGetLastError());
     ctx->stats.kernel_batches++;
+    recorded = done && n_chunks;
   }
-  SS_HIP(hipEventRecord(s.ev_out_done[s.phase][batch], so));
+  if (!recorded) SS_HIP(hipEventRecord(s.ev_out_done[s.phase][batch], so));
   s.done_ev_of[batch] = (int32_t)batch;
   s.out_issued[batch] = 1;
   s.last_direct_out = batch;
   if ((int64_t)batch < s.max_out_issued) s.out_of_order = true;
   else s.max_out_issued = batch;
-  s.last_out_on[engine ? 0 : batch % ctx->n_s_out] = batch;
+  if (in_line) {
+    s.out_inline[batch] = 1;
+    s.any_inline = true;
+    s.last_inline = s.ev_out_done[s.phase][batch];
+  } else {
+    s.last_out_on[engine ? 0 : batch % ctx->n_s_out] = batch;
+    s.unsettled++;
+  }
   ctx->stats.bytes_out += bytes;
   return SS_OK;
 }
@@ -1480,27 +1534,33 @@ static int swap_in_batch(ss_ctx *ctx, uint32_t batch) {
   const bool engine = ctx->eq ? false                                                // see swap_out_batch
                     : s.flat_next ? ctx->cfg.copy_path_in != SS_PATH_KERNEL
                                   : use_engine(ctx, ctx->cfg.copy_path_in, false, s.in, lo, hi);
-  hipStream_t si = engine ? ctx->s_in[0] : ctx->s_in[batch % ctx->n_s_in];
+  const uint64_t bytes = batch_bytes(s.in, lo, hi);
+  const bool in_line = copies_inline(ctx, engine, bytes);
+  const hipEvent_t done = with_kernel(ctx, in_line, s.ev_in_done[s.phase][batch]);
+  bool recorded = false;
+  hipStream_t si = in_line ? ctx->compute : engine ? ctx->s_in[0] : ctx->s_in[batch % ctx->n_s_in];
   // destination blocks are free once the compute stream reaches this point
   ss_marker mark;
   if (hi > lo && s.in_group_of[batch] >= 0) {
     const int rc = swap_in_staged(ctx, batch, mark);
     if (rc < 0) return rc;
     if (rc == 1) {
-      uint64_t moved = 0;
-      for (uint32_t i = lo; i < hi; ++i) moved += s.in[i].nbytes;
-      ctx->stats.bytes_in += moved;
+      ctx->stats.bytes_in += bytes;
       return SS_OK;
     }
   }
-  {
+  if (!in_line) {
     const int rm = wait_for_compute(ctx, mark, si, !engine);
     if (rm != SS_OK) return rm;
+  } else if (ctx->cfg.flags & SS_CFG_STALL_TIMING) {
+    SS_HIP(hipEventRecord(s.ev_wait_at[batch], si));
   }
   // staging slots must be completely written: the batch's tensors left in swap-out batches up to in_dep;
   // with the swap-out batches spread over n streams, the last n of them up to in_dep cover every stream
   // (each stream runs its own batches in order)
-  if (hi > lo && s.groups.empty() && s.out_of_order) {
+  if (in_line) {
+    // every swap-out so far is behind the compute stream or on it
+  } else if (hi > lo && s.groups.empty() && s.out_of_order) {
     // swap-outs were not issued in index order: "up to in_dep" says nothing about what ran before what, so the
     // batch waits for the one issued most recently on every swap-out stream (everything issued so far)
     for (uint32_t k = 0; k < ctx->n_s_out; ++k)
@@ -1526,11 +1586,9 @@ static int swap_in_batch(ss_ctx *ctx, uint32_t batch) {
   }
   // a copy-engine swap-out collapses to a quarter of the link rate as soon as anything flows the
   // other way: no swap-in starts before the engine swap-outs issued so far have finished
-  if (s.last_engine_out >= 0 && (hi <= lo || (int64_t)s.in_dep[batch] < s.last_engine_out))
+  if (!in_line && s.last_engine_out >= 0 && (hi <= lo || (int64_t)s.in_dep[batch] < s.last_engine_out))
     SS_HIP(hipStreamWaitEvent(si, s.ev_out_done[s.phase][(size_t)s.last_engine_out], 0));
   if (ctx->cfg.flags & SS_CFG_TIMING) SS_HIP(hipEventRecord(s.ev_in_start[s.phase][batch], si));
-  uint64_t bytes = 0;
-  for (uint32_t i = lo; i < hi; ++i) bytes += s.in[i].nbytes;
   if (engine) {
     // Flow control: copy-engine transfers queued behind more than a few others run at a fraction of the link
     // rate, so with engine_window_in = w the call does not return before the engine swap-in batch issued w
@@ -1557,12 +1615,20 @@ static int swap_in_batch(ss_ctx *ctx, uint32_t batch) {
     const uint32_t *c0 = s.d_in_chunk0 + lo + batch;
     const uint32_t n_chunks = s.in_chunk0[(size_t)hi + batch];
     ss_launch_copy(si, ctx->cfg.copy_workgroups, ctx->cfg.copy_unroll, false, ctx->arena, ctx->staging_dev, s.d_in + lo, c0,
-                   s.d_in_cdesc + s.in_cbase[batch], n_chunks, s.in_shift[batch], hi - lo, ctx->cfg.copy_desc_lookup == 1);
+                   s.d_in_cdesc + s.in_cbase[batch], n_chunks, s.in_shift[batch], hi - lo, ctx->cfg.copy_desc_lookup == 1, done);
     SS_HIP(hipGetLastError());
     ctx->stats.kernel_batches++;
+    recorded = done && n_chunks;
   }
-  SS_HIP(hipEventRecord(s.ev_in_done[s.phase][batch], si));
+  if (!recorded) SS_HIP(hipEventRecord(s.ev_in_done[s.phase][batch], si));
   s.in_issued[batch] = 1;
+  if (in_line) {
+    s.in_inline[batch] = 1;
+    s.any_inline = true;
+    s.last_inline = s.ev_in_done[s.phase][batch];
+  } else {
+    s.unsettled++;
+  }
   ctx->stats.bytes_in += bytes;
   return SS_OK;
 }
@@ -1617,10 +1683,13 @@ extern "C" int ss_sync(ss_ctx *ctx, uint32_t what, uint32_t id) {
       const uint32_t b = s.out_batch_of[it->second];
       if (!s.out_issued[b]) return SS_E_STATE;   // releasing a block whose swap-out was never issued
       if (!s.out_waited[b]) {
-        if (ctx->cfg.flags & SS_CFG_STALL_TIMING) SS_HIP(hipEventRecord(s.ev_free_at[b], ctx->compute));
         // device-side: later compute-stream work starts only after the batch has left its blocks (for the
-        // staging area, or, staged, for the ring)
-        SS_HIP(hipStreamWaitEvent(ctx->compute, s.out_staged[b] ? s.ev_gathered[s.phase][b] : s.ev_out_done[s.phase][b], 0));
+        // staging area, or, staged, for the ring); one copied on the compute stream has by then
+        if (!s.out_inline[b]) {
+          if (ctx->cfg.flags & SS_CFG_STALL_TIMING) SS_HIP(hipEventRecord(s.ev_free_at[b], ctx->compute));
+          SS_HIP(hipStreamWaitEvent(ctx->compute, s.out_staged[b] ? s.ev_gathered[s.phase][b] : s.ev_out_done[s.phase][b], 0));
+          if (s.unsettled) s.unsettled--;
+        }
         s.out_waited[b] = 1;
         ctx->stats.free_waits++;
       }
@@ -1638,8 +1707,11 @@ extern "C" int ss_sync(ss_ctx *ctx, uint32_t what, uint32_t id) {
       const uint32_t b = s.in_batch_of[it->second];
       if (!s.in_issued[b]) return SS_E_STATE;    // waiting for a swap-in that was never issued
       if (!s.in_waited[b]) {
-        if (ctx->cfg.flags & SS_CFG_STALL_TIMING) SS_HIP(hipEventRecord(s.ev_wait_at[b], ctx->compute));
-        SS_HIP(hipStreamWaitEvent(ctx->compute, s.ev_in_done[s.phase][b], 0));
+        if (!s.in_inline[b]) {
+          if (ctx->cfg.flags & SS_CFG_STALL_TIMING) SS_HIP(hipEventRecord(s.ev_wait_at[b], ctx->compute));
+          SS_HIP(hipStreamWaitEvent(ctx->compute, s.ev_in_done[s.phase][b], 0));
+          if (s.unsettled) s.unsettled--;
+        }
         s.in_waited[b] = 1;
         ctx->stats.in_waits++;
       }
@@ -1654,7 +1726,7 @@ extern "C" int ss_sync(ss_ctx *ctx, uint32_t what, uint32_t id) {
       const int cur = ctx->iter_set, prev = cur ^ 1;
       // the iteration before this one has to be over: the next one records into its set of events
       if (ctx->iter_pending[prev]) {
-        for (int k = 0; k < 9; ++k)
+        for (int k = 0; k < ss_ctx::kIterEvents; ++k)
           if (ctx->ev_iter[prev][k]) SS_HIP(hipEventSynchronize(ctx->ev_iter[prev][k]));
         eq_wait_enqueued(ctx, ctx->iter_last_seq[prev]);
         ctx->iter_pending[prev] = false;
@@ -1684,6 +1756,7 @@ extern "C" int ss_sync(ss_ctx *ctx, uint32_t what, uint32_t id) {
       for (uint32_t i = 0; i < ctx->n_s_in; ++i)
         if ((rc = end_of(4 + (int)i, ctx->s_in[i])) != SS_OK) return rc;
       if (ctx->s_flush && !ctx->eq && (rc = end_of(8, ctx->s_flush)) != SS_OK) return rc;
+      if (s.any_inline && (rc = end_of(9, ctx->compute)) != SS_OK) return rc;
       // The next iteration's swap-outs write staging slots and ring slots that this iteration's swap-ins and ring
       // transfers still read: every swap-out stream goes on only after the swap-in streams and the ring transfers of
       // this iteration; the ring transfers of the next iteration (into slots this iteration's scatters read) only

@@ -1,0 +1,127 @@
+"""Copy-kernel batches of at most 256 KiB are copied on the compute stream while no other batch is outstanding: batches at
+and beyond that size mixed, released at once or late, swap-outs in either order, several iterations that end with and without
+a host wait, the compute stream lagging behind the calls; bytes exact in staging and arena."""
+import numpy as np
+import pytest
+
+import oracle
+import workloads as W
+
+pytestmark = pytest.mark.gpu
+K = 1 << 10
+
+
+@pytest.fixture(scope="module")
+def P():
+    import paper_2509_11076_amd.binding as B
+    return B
+
+
+@pytest.mark.parametrize("flags_name", [None, "SS_CFG_TIMING", "SS_CFG_STALL_TIMING", "SS_CFG_MEMORY_MARKERS"])
+@pytest.mark.parametrize("release", ["at once", "late", "reversed"])
+@pytest.mark.parametrize("end", ["drain", "no wait"])
+def test_small_and_large_batches_mixed(P, flags_name, release, end):
+    import torch
+    groups = [[1], [256 * K], [256 * K + 1], [16], [64 * K, 100 * K + 3], [1024 * K], [], [255 * K, K], [128 * K, 128 * K + 1],
+              [300 * K], [5] * 9]
+    sizes = [n for g in groups for n in g]
+    start = np.cumsum([0] + [len(g) for g in groups]).astype(np.uint32)
+    slot = [(n + 255) // 256 * 256 for n in sizes]
+    span, n = sum(slot), len(sizes)
+    d_out, d_in = np.zeros(n, dtype=W.DESC_DT), np.zeros(n, dtype=W.DESC_DT)
+    rng = np.random.default_rng(8)
+    src, dst = np.zeros(n, dtype=np.int64), np.zeros(n, dtype=np.int64)
+    for off in (src, dst):
+        order = rng.permutation(n)
+        off[order] = np.cumsum(np.array(slot)[order]) - np.array(slot)[order]
+    h = np.cumsum(slot) - slot
+    for i in range(n):
+        d_out[i] = (src[i], h[i], sizes[i], i, 0)
+        d_in[i] = (span + dst[i], h[i], sizes[i], i, 0)
+    g = torch.Generator(device="cuda")
+    g.manual_seed(9)
+    srcs = [torch.randint(0, 256, (span,), dtype=torch.uint8, device="cuda", generator=g) for _ in range(4)]
+    arena = torch.zeros(2 * span, dtype=torch.uint8, device="cuda")
+    torch.cuda.synchronize()
+    cfg = P.ss_config_default()
+    cfg.staging_bytes = span
+    cfg.copy_path = cfg.copy_path_in = P.SS_PATH_KERNEL
+    cfg.flags = getattr(P, flags_name) if flags_name else 0
+    ctx = P.ss_create(cfg)
+    stream = torch.cuda.Stream()
+    try:
+        with torch.cuda.stream(stream):
+            P.ss_bind(ctx, arena.data_ptr(), 2 * span, stream.cuda_stream)
+            P.ss_staging_fill(ctx, 0)
+            P.ss_load_schedule(ctx, d_out, start, d_in, start)
+            got = []
+            for it, s in enumerate(srcs):
+                torch.cuda._sleep(2000000)                   # a millisecond or so behind the calls
+                arena[:span].copy_(s)
+                batches = list(range(len(groups)))
+                for b in batches[::-1] if release == "reversed" else batches:
+                    P.ss_swap_out(ctx, b)
+                    if release == "at once":
+                        for t in range(start[b], start[b + 1]):
+                            P.ss_sync(ctx, P.SS_SYNC_FREE, t)
+                for t in range(n):
+                    P.ss_sync(ctx, P.SS_SYNC_FREE, t)
+                arena.fill_(0x3C)
+                for b in batches[::-1]:
+                    P.ss_swap_in(ctx, b)
+                    if b % 2:
+                        for t in range(start[b], start[b + 1]):
+                            P.ss_sync(ctx, P.SS_SYNC_WAIT_IN, t)
+                for t in range(n):
+                    P.ss_sync(ctx, P.SS_SYNC_WAIT_IN, t)
+                got.append(arena.clone())
+                last = it + 1 == len(srcs)
+                torch.cuda._sleep(200000)                    # what follows the last batch there
+                P.ss_sync(ctx, P.SS_SYNC_DRAIN if last or end == "drain" else P.SS_SYNC_ITERATION_END)
+                if last or end == "drain":
+                    want = np.zeros(span, dtype=np.uint8)
+                    oracle.swap_out(s.cpu().numpy(), want, [tuple(int(x) for x in r) for r in d_out.tolist()])
+                    assert np.array_equal(P.ss_host_peek(ctx, 0, span), want)
+            torch.cuda.synchronize()
+        for s, a in zip(srcs, got):
+            staging, want = np.zeros(span, dtype=np.uint8), np.full(2 * span, 0x3C, dtype=np.uint8)
+            oracle.swap_out(s.cpu().numpy(), staging, [tuple(int(x) for x in r) for r in d_out.tolist()])
+            oracle.swap_in(want, staging, [tuple(int(x) for x in r) for r in d_in.tolist()])
+            assert np.array_equal(a.cpu().numpy(), want)
+        st = P.ss_get_stats(ctx)
+        waits = 4 * sum(1 for x in groups if x)
+        assert st["free_waits"] == waits and st["in_waits"] == waits and st["bytes_out"] == 4 * sum(sizes)
+        if flags_name == "SS_CFG_TIMING":
+            for dr in (0, 1):
+                assert all(P.ss_batch_ms(ctx, dr, b)[0] >= 0 for b in range(len(groups)))
+    finally:
+        P.ss_destroy(ctx)
+
+
+def test_a_batch_is_done_before_what_follows_it_on_the_compute_stream(P):
+    import time
+    import torch
+    n = 64 * K
+    arena = torch.randint(0, 256, (2 * n,), dtype=torch.uint8, device="cuda")
+    want = arena[:n].cpu().numpy()
+    d_out, d_in = np.zeros(1, dtype=W.DESC_DT), np.zeros(1, dtype=W.DESC_DT)
+    d_out[0], d_in[0] = (0, 0, n, 0, 0), (n, 0, n, 0, 0)
+    start = np.array([0, 1], dtype=np.uint32)
+    cfg = P.ss_config_default()
+    cfg.staging_bytes = n
+    ctx = P.ss_create(cfg)
+    try:
+        P.ss_bind(ctx, arena.data_ptr(), 2 * n, torch.cuda.current_stream().cuda_stream)
+        P.ss_load_schedule(ctx, d_out, start, d_in, start)
+        torch.cuda.synchronize()
+        P.ss_swap_out(ctx, 0)
+        torch.cuda._sleep(1 << 30)                           # half a second
+        t = time.time()
+        while not P.ss_batch_done(ctx, 0, 0):
+            assert time.time() - t < 0.2
+        assert np.array_equal(P.ss_host_peek(ctx, 0, n), want)
+        P.ss_sync(ctx, P.SS_SYNC_DRAIN)                      # waits for the batch alone
+        assert time.time() - t < 0.2
+        torch.cuda.synchronize()
+    finally:
+        P.ss_destroy(ctx)
