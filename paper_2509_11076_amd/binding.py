@@ -217,8 +217,18 @@ def _arr(a, dt):
     return a
 
 
+_view = C.c_char.from_buffer
+
+
 def _ptr(a):
-    return None if a is None or a.size == 0 else a.ctypes.data_as(_P)
+    """Address of an array's first element.  By way of the buffer protocol it takes 0.4 us, by `a.ctypes.data_as` 2.7, which
+    for the five or six arrays of a call was more than the rest of its marshalling; read-only arrays have no such view."""
+    if a is None or a.size == 0:
+        return None
+    try:
+        return C.addressof(_view(a))
+    except (TypeError, ValueError, BufferError):
+        return a.ctypes.data
 
 
 def ss_config_default():
@@ -311,12 +321,12 @@ def ss_timeline_scan(ctx, events, policy_events, n_ops, base, budget, want_timel
     pe = _arr(policy_events, EVENT_DT)
     n_ev = 0 if ev is None else len(ev)
     n_pe = 0 if pe is None else len(pe)
-    tl = np.zeros(n_ev + n_pe, dtype=np.int64) if want_timeline else None
-    per_op = np.zeros(n_ops, dtype=np.int64) if want_per_op else None
-    mre = np.zeros(n_ops, dtype=np.int64) if want_per_op else None
+    tl = np.empty(n_ev + n_pe, dtype=np.int64) if want_timeline else None       # all of each is written
+    per_op = np.empty(n_ops, dtype=np.int64) if want_per_op else None
+    mre = np.empty(n_ops, dtype=np.int64) if want_per_op else None
     res = ss_scan_result_t()
     # an empty output array still needs a non-null pointer to be "wanted"
-    tlp = None if tl is None else tl.ctypes.data_as(_P)
+    tlp = None if tl is None else _ptr(tl) or tl.ctypes.data
     _ck(_lib.ss_timeline_scan(ctx, _ptr(ev), n_ev, _ptr(pe), n_pe, int(n_ops), int(base), int(budget),
                               tlp, _ptr(per_op), _ptr(mre), C.byref(res)), "ss_timeline_scan")
     return dict(timeline=tl, per_op=per_op, mre=mre, peak=res.peak, argpeak_op=res.argpeak_op,
@@ -326,11 +336,11 @@ def ss_timeline_scan(ctx, events, policy_events, n_ops, base, budget, want_timel
 def ss_timeline_scan_static(ctx, stream, d_ev, n_ev, d_pev, n_pe, n_ops, base, budget, d_timeline, d_per_op, d_mre,
                             d_res):
     """every d_* is a device address (int, 0 = NULL); only enqueues: synchronise the stream before reading"""
-    def p(x):
-        return _P(int(x)) if x else None
-    _ck(_lib.ss_timeline_scan_static(ctx, p(stream), p(d_ev), int(n_ev), p(d_pev), int(n_pe), int(n_ops), int(base),
-                                     int(budget), p(d_timeline), p(d_per_op), p(d_mre), p(d_res)),
-        "ss_timeline_scan_static")
+    rc = _lib.ss_timeline_scan_static(ctx, int(stream or 0), int(d_ev or 0), int(n_ev), int(d_pev or 0), int(n_pe), int(n_ops),
+                                      int(base), int(budget), int(d_timeline or 0), int(d_per_op or 0), int(d_mre or 0),
+                                      int(d_res or 0))
+    if rc != SS_OK:
+        raise SsError(rc, "ss_timeline_scan_static")
 
 
 def ss_timeline_scan_batch(ctx, events, policy_event_lists, n_ops, base, budget, want_per_op=False):
@@ -343,9 +353,9 @@ def ss_timeline_scan_batch(ctx, events, policy_event_lists, n_ops, base, budget,
     pev = np.concatenate(lists) if k and int(start[-1]) else np.zeros(0, EVENT_DT)
     res = (ss_scan_result_t * max(1, k))()
     per_op = np.zeros((k, n_ops), dtype=np.int64) if want_per_op else None
-    pp = None if per_op is None or per_op.size == 0 else per_op.ctypes.data_as(_P)
+    pp = _ptr(per_op)
     _ck(_lib.ss_timeline_scan_batch(ctx, _ptr(ev), 0 if ev is None else len(ev), _ptr(pev), _ptr(start), k, int(n_ops),
-                                    int(base), int(budget), pp, C.cast(res, _P)), "ss_timeline_scan_batch")
+                                    int(base), int(budget), pp, res), "ss_timeline_scan_batch")
     out = []
     for c in range(k):
         r = res[c]
@@ -359,8 +369,8 @@ def ss_match_sequence(ctx, ref, cur, anchors, flags=0):
     cur = _arr(cur, OP_DT)
     anc = _arr(anchors, ANCHOR_DT)
     k = 0 if anc is None else len(anc)
-    new_idx = np.full(k, -1, dtype=np.int32)
-    level = np.full(k, 255, dtype=np.uint8)
+    new_idx = np.empty(k, dtype=np.int32)                  # all of each is written
+    level = np.empty(k, dtype=np.uint8)
     res = ss_match_result_t()
     _ck(_lib.ss_match_sequence(ctx, _ptr(ref), len(ref), _ptr(cur), len(cur), _ptr(anc), k, int(flags),
                                _ptr(new_idx), _ptr(level), C.byref(res)), "ss_match_sequence")
@@ -375,9 +385,9 @@ def ss_align_sequence(ctx, ref, cur, anchors=None):
     k = 0 if anc is None else len(anc)
     n = 0 if ref is None else len(ref)
     m = 0 if cur is None else len(cur)
-    ref_to_cur = np.full(n, -2, dtype=np.int32)
-    new_idx = np.full(k, -1, dtype=np.int32)
-    level = np.full(k, 255, dtype=np.uint8)
+    ref_to_cur = np.empty(n, dtype=np.int32)               # all of each is written
+    new_idx = np.empty(k, dtype=np.int32)
+    level = np.empty(k, dtype=np.uint8)
     res = ss_align_result_t()
     _ck(_lib.ss_align_sequence(ctx, _ptr(ref), n, _ptr(cur), m, _ptr(anc), k, _ptr(ref_to_cur), _ptr(new_idx),
                                _ptr(level), C.byref(res)), "ss_align_sequence")
@@ -479,7 +489,7 @@ def ss_generate_policy_best(ctx, ops, tensors, events, base, limit, param_sets):
     n, chosen = C.c_uint32(len(out)), C.c_uint32(0)
     res = ss_gen_result_t()
     _ck(_lib.ss_generate_policy_best(ctx, _ptr(ops), len(ops), _ptr(tab), len(tab), _ptr(ev), len(ev), int(base),
-                                     int(limit), C.cast(prm, _P), len(param_sets), _ptr(out), C.byref(n),
+                                     int(limit), prm, len(param_sets), _ptr(out), C.byref(n),
                                      C.byref(chosen), C.byref(res)), "ss_generate_policy_best")
     return out[:n.value], {f: getattr(res, f) for f, _ in ss_gen_result_t._fields_}, chosen.value
 
@@ -494,7 +504,7 @@ def ss_swap_in(ctx, batch):
 
 def _addr_array(addrs):
     a = np.ascontiguousarray(addrs, dtype=np.uint64)
-    return a, (a.ctypes.data_as(_P) if len(a) else None)
+    return a, _ptr(a)
 
 
 def ss_swap_out_from(ctx, batch, dev_src):
