@@ -165,7 +165,7 @@ struct ss_ctx {
   // stage machine (Algo. 1)
   uint32_t stage = SS_STAGE_WARMUP, stable_step = 0;
   void *d_board = nullptr;          // what the workgroups of a long scan tell each other (ss_scan.hip)
-  uint32_t *h_done = nullptr, *d_done = nullptr;            // pinned word and its device address (ss_done)
+  uint32_t *h_done = nullptr, *d_done = nullptr;            // pinned word (behind ops) and its device address (ss_done)
   uint32_t *d_told = nullptr;       // device (in front of d_board)
   uint32_t done_count = 0;
   uint32_t scan_wait_ticks = 0;     // limit of their waits, 0 = the usual one
@@ -231,9 +231,10 @@ __device__ __forceinline__ void ss_tell_host(const ss_done &d) {
 
 // scratch management (ss_runtime.hip)
 int ss_scratch_reserve(ss_ctx *ctx, size_t dev_bytes, size_t host_bytes);
-// address of the static scratch array of ss_timeline_scan_static on the context's device, and the context's own board
-// (ss_scan.hip)
-int ss_scan_init(ss_ctx *ctx);
+// address of the static scratch array of ss_timeline_scan_static on the context's device; the context's own board, once s_aux
+// is there (ss_scan.hip)
+int ss_scan_static_init(ss_ctx *ctx);
+int ss_scan_board_init(ss_ctx *ctx);
 
 // internal entry used by the greedy generator: timing + schedule without loading it
 struct ss_applied {

@@ -413,15 +413,22 @@ extern "C" int ss_create(ss_ctx **out, const ss_config_t *cfg_in) {
 #define fail(code, e) fail_at(code, e, __LINE__)
     hipError_t e;
     if ((e = hipGetDevice(&ctx->device)) != hipSuccess) fail(SS_E_HIP, e);
-    if (rc == SS_OK) rc = ss_scan_init(ctx);
+    if (rc == SS_OK) rc = ss_scan_static_init(ctx);
     if (rc == SS_OK && cfg.staging_bytes) {
       e = hipHostMalloc((void **)&ctx->staging, cfg.staging_bytes, hipHostMallocMapped | hipHostMallocPortable);
       if (e != hipSuccess) fail(SS_E_NOMEM, e);
       else if ((e = hipHostGetDevicePointer((void **)&ctx->staging_dev, ctx->staging, 0)) != hipSuccess)
         fail(SS_E_HIP, e);
     }
-    if (rc == SS_OK && (e = hipHostMalloc((void **)&ctx->ops, (size_t)cfg.max_ops * sizeof(ss_op_t),
-                                          hipHostMallocMapped)) != hipSuccess) fail(SS_E_NOMEM, e);
+    // the word that kernels tell the host through has a cache line of its own behind the operators
+    const size_t done_at = ss_align_up((uint64_t)cfg.max_ops * sizeof(ss_op_t), 256);
+    if (rc == SS_OK && (e = hipHostMalloc((void **)&ctx->ops, done_at + 256, hipHostMallocMapped | hipHostMallocCoherent)) != hipSuccess)
+      fail(SS_E_NOMEM, e);
+    if (rc == SS_OK) {
+      ctx->h_done = (uint32_t *)((uint8_t *)ctx->ops + done_at);
+      *ctx->h_done = 0;
+      if ((e = hipHostGetDevicePointer((void **)&ctx->d_done, ctx->h_done, 0)) != hipSuccess) fail(SS_E_HIP, e);
+    }
     if (rc == SS_OK && (e = hipHostMalloc((void **)&ctx->events, (size_t)cfg.max_events * sizeof(ss_event_t),
                                           hipHostMallocMapped)) != hipSuccess) fail(SS_E_NOMEM, e);
     // all streams at the default priority
@@ -457,6 +464,7 @@ extern "C" int ss_create(ss_ctx **out, const ss_config_t *cfg_in) {
     // queues (4 per process here) with another - a stream that shares its queue with the stream of the
     // copy-engine transfers stands still for the length of every transfer.
     ctx->s_aux = ctx->s_in[0];
+    if (rc == SS_OK) rc = ss_scan_board_init(ctx);
     if (rc == SS_OK && (cfg.copy_path == SS_PATH_STAGED || cfg.copy_path_in == SS_PATH_STAGED)) {
       // gathers / scatters and direct batches of a direction share that direction's one stream; the copy-engine
       // transfers out of and into the rings share a third
@@ -573,7 +581,6 @@ extern "C" int ss_destroy(ss_ctx *ctx) {
   if (ctx->ops) (void)hipHostFree(ctx->ops);
   if (ctx->events) (void)hipHostFree(ctx->events);
   if (ctx->d_told) (void)hipFree(ctx->d_told);
-  if (ctx->h_done) (void)hipHostFree(ctx->h_done);
   if (ctx->d_scratch) (void)hipFree(ctx->d_scratch);
   if (ctx->h_scratch) (void)hipHostFree(ctx->h_scratch);
   delete ctx;

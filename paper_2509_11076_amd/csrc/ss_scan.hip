@@ -1147,20 +1147,20 @@ static int static_scratch_ptr(int device, uint8_t **out, hipError_t *err) {
   return SS_OK;
 }
 
-int ss_scan_init(ss_ctx *ctx) {
+int ss_scan_static_init(ss_ctx *ctx) {
   uint8_t *p;
   hipError_t e;
   const int rc = static_scratch_ptr(ctx->device, &p, &e);
   if (rc == SS_E_HIP) SS_HIP(e);
-  if (rc != SS_OK) return rc;
+  return rc;
+}
+
+int ss_scan_board_init(ss_ctx *ctx) {
   constexpr size_t kBoardAt = 256;
   SS_HIP(hipMalloc((void **)&ctx->d_told, kBoardAt + sizeof(TileBoard)));
-  SS_HIP(hipMemset(ctx->d_told, 0, kBoardAt + sizeof(TileBoard)));
-  SS_HIP(hipStreamSynchronize(nullptr));
   ctx->d_board = (uint8_t *)ctx->d_told + kBoardAt;
-  SS_HIP(hipHostMalloc((void **)&ctx->h_done, 256, hipHostMallocMapped | hipHostMallocCoherent));
-  *ctx->h_done = 0;
-  SS_HIP(hipHostGetDevicePointer((void **)&ctx->d_done, ctx->h_done, 0));
+  ss_launch_fill(ctx->s_aux, (uint8_t *)ctx->d_told, kBoardAt + sizeof(TileBoard), 0);     // their kernels run there too
+  SS_HIP(hipGetLastError());
   return SS_OK;
 }
 
