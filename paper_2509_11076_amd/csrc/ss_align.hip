@@ -26,24 +26,24 @@ typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 
 constexpr uint32_t kAlignLenLimit = 1u << 16;          // at most 34 strips
 constexpr uint32_t kBlock = 32;                        // steps between two looks at the neighbouring strip
-constexpr uint32_t kGroup = 8;                         // steps whose masks are looked up together
 constexpr uint32_t kStripWords = 64;                   // 32-bit words of a row, one per lane, in a single strip
 constexpr uint32_t kInnerWords = 62;                   // the same where there are several strips: lanes 1 to 62
 constexpr uint32_t kLdsKeys = 256;                     // mask rows (with the empty one) a strip keeps in LDS at most, 256 bytes each
-constexpr size_t kLdsBytes = 160 * 1024;               // for these, the reference's ids and the ring below
-constexpr uint32_t kRingBytes = 4096;
+constexpr uint32_t kFeeds = 4;                         // blocks of steps whose masks lie in LDS, and carries
+constexpr uint32_t kFeedWords = kBlock * kStripWords;
+constexpr uint32_t kRowsThreads = 320;
 constexpr uint32_t kSkew = 2;                          // steps that a lane is behind the one before it
 constexpr uint32_t kIdPad = 64 * kSkew;                // entries before the first id (lanes whose row has not begun)
 // Rows up to this many bytes go straight to host memory and are walked there: beside the kernel's pace they cost the
 // link nothing up to about 13 GB/s, and the walk on the GPU takes four more launches and two copies.
 constexpr size_t kHostRowBytes = 4u << 20;
-constexpr uint32_t kCarryPad = 8;                      // carry words a strip may look at beyond its neighbour's last
+constexpr uint32_t kCarryPad = 8;                      // carry words beyond a strip's last (the first of them is looked at)
 
 // steps a strip takes for n rows, whole blocks of them
 static constexpr uint32_t steps_of(uint32_t n) { return (n + kSkew * (kStripWords - 1) + kBlock - 1) / kBlock * kBlock; }
 
 // entries of a padded id array, a multiple of 16 bytes
-static inline __host__ __device__ uint32_t id_length(uint32_t n_steps) { return kIdPad + n_steps + 3 * kBlock; }
+static inline __host__ __device__ uint32_t id_length(uint32_t n_steps) { return kIdPad + n_steps + 6 * kBlock; }
 
 static constexpr __host__ __device__ uint32_t strips_of(uint32_t W) {
   return W <= kStripWords ? 1 : (W + kInnerWords - 1) / kInnerWords;
@@ -251,12 +251,12 @@ __global__ void ss_align_masks_kernel(const Id *__restrict__ cur_id, uint32_t m,
   if (j < m) atomicOr(&masks[(size_t)key_of(cur_id[j]) * W + (j >> 5)], 1u << (j & 31));
 }
 
-// Two row steps of a word: V' = (V + (V & M) + carry in) | (V & ~M); the carries in and out are lane masks, `even` and
+// Four row steps of a word: V' = (V + (V & M) + carry in) | (V & ~M); the carries in and out are lane masks, `even` and
 // `odd` those out of the two steps before.
 // Written out because the compiler turns a carry that leaves as a lane mask into a select and a compare, and for the order.
 // (bitop3's number is its truth table, S0 = 0xF0, S1 = 0xCC, S2 = 0xAA: (S0 & ~S1) | S2.)
-__device__ __forceinline__ void row_steps(uint32_t V, uint32_t M0, uint32_t M1, u64 &even, u64 &odd, uint32_t &V0, uint32_t &V1) {
-  uint32_t a;
+__device__ __forceinline__ void row_steps(uint32_t V, const u32x4 &M, u64 &even, u64 &odd, u32x4 &rows) {
+  uint32_t a, v0, v1, v2, v3;
   asm("v_and_b32_e32 %[a], %[m0], %[v]\n\t"
       "s_lshl_b64 %[c0], %[c0], 1\n\t"
       "s_lshl_b64 %[c1], %[c1], 1\n\t"
@@ -264,10 +264,19 @@ __device__ __forceinline__ void row_steps(uint32_t V, uint32_t M0, uint32_t M1, 
       "v_bitop3_b32 %[v0], %[v], %[m0], %[a] bitop3:0xba\n\t"
       "v_and_b32_e32 %[a], %[m1], %[v0]\n\t"
       "v_addc_co_u32_e64 %[a], %[c1], %[v0], %[a], %[c1]\n\t"
-      "v_bitop3_b32 %[v1], %[v0], %[m1], %[a] bitop3:0xba"
-      : [v0] "=&v"(V0), [v1] "=v"(V1), [a] "=&v"(a), [c0] "+s"(even), [c1] "+s"(odd)
-      : [v] "v"(V), [m0] "v"(M0), [m1] "v"(M1)
+      "v_bitop3_b32 %[v1], %[v0], %[m1], %[a] bitop3:0xba\n\t"
+      "v_and_b32_e32 %[a], %[m2], %[v1]\n\t"
+      "s_lshl_b64 %[c0], %[c0], 1\n\t"
+      "s_lshl_b64 %[c1], %[c1], 1\n\t"
+      "v_addc_co_u32_e64 %[a], %[c0], %[v1], %[a], %[c0]\n\t"
+      "v_bitop3_b32 %[v2], %[v1], %[m2], %[a] bitop3:0xba\n\t"
+      "v_and_b32_e32 %[a], %[m3], %[v2]\n\t"
+      "v_addc_co_u32_e64 %[a], %[c1], %[v2], %[a], %[c1]\n\t"
+      "v_bitop3_b32 %[v3], %[v2], %[m3], %[a] bitop3:0xba"
+      : [v0] "=&v"(v0), [v1] "=&v"(v1), [v2] "=&v"(v2), [v3] "=v"(v3), [a] "=&v"(a), [c0] "+s"(even), [c1] "+s"(odd)
+      : [v] "v"(V), [m0] "v"(M.x), [m1] "v"(M.y), [m2] "v"(M.z), [m3] "v"(M.w)
       : "scc");
+  rows = u32x4{v0, v1, v2, v3};
 }
 
 struct RowsArgs {
@@ -283,114 +292,118 @@ struct RowsArgs {
 
 static __device__ const uint32_t all_ones = ~0u;
 
-// Mask words of the steps of this lane, looked up a group at a time for the block after the one at work.
-// Wide ids: masks and ids from device memory; a lane that holds no word of the row has W = 0 and `word` = &all_ones.
-// The ids are read a block before they are used, since waiting for them waits for everything read before them too (read
-// one group before: 2,000 x 2,000 operators with 1,000 keys 176 us a call against 120, 60,000 x 60,000 with 500 keys
-// 5.9 ms against 4.4).
+// Mask words of a block of steps of this lane.  The ids are read from device memory as 16 bytes (a row's distance between
+// lanes keeps them aligned to 4), long before they are used.
+typedef uint32_t ids16 __attribute__((ext_vector_type(4), aligned(4)));
+
+// Wide ids: masks from device memory; a lane that holds no word of the row has W = 0 and `word` = &all_ones.
 template <class Id>
 struct Masks {
   const __attribute__((address_space(1))) uint32_t *word;      // this lane's word of the mask row of key 0
   const uint32_t *ids;       // entry t is the id of this lane's row in step t
-  uint32_t W, id[kBlock];
-  __device__ __forceinline__ void begin() { prime(0); }
-  __device__ __forceinline__ void first(uint32_t) {}
-  __device__ __forceinline__ void prime(uint32_t b) {
+  uint32_t W;
+  ids16 id[kBlock / 4];
+  __device__ __forceinline__ void load(uint32_t b) {
 #pragma unroll
-    for (uint32_t u = 0; u < kBlock; ++u) id[u] = ids[b * kBlock + u];
+    for (uint32_t u = 0; u < kBlock / 4; ++u) id[u] = *reinterpret_cast<const ids16 *>(ids + b * kBlock + 4 * u);
   }
-  __device__ __forceinline__ uint32_t look_up(uint32_t u) const { return word[(size_t)id[u] * W]; }
-  __device__ __forceinline__ void refill(uint32_t b, uint32_t g) {
-#pragma unroll
-    for (uint32_t u = 0; u < kGroup; ++u) id[g + u] = ids[(b + 2) * kBlock + g + u];
-  }
-  __device__ __forceinline__ void block_begins() {}
-  __device__ __forceinline__ void block_ends() {}
+  __device__ __forceinline__ uint32_t look_up(uint32_t step) const { return word[(size_t)id[step / 4][step % 4] * W]; }
 };
 
-// 16-bit ids: masks and ids in LDS.  Lane l needs eight ids from entry t - 2 l on, and a 16-byte LDS read that isn't
-// aligned in every lane keeps the LDS for 72 cycles (up to 3.7 ns a step).  So the ids next needed lie in a ring a second
-// time, once for each of the shifts 2 l % 8: piece c of position i holds entries 8 i - 2 c to 8 i - 2 c + 7, and a
-// lane's read is an aligned 16 bytes.  A block of steps uses up four positions; the next four are copied by one 4-byte
-// read and write of every lane.  The ring's 32 positions are there twice, so that five in a row never wrap.
+// 16-bit ids: masks in LDS.
 template <>
 struct Masks<uint16_t> {
-  static constexpr uint32_t kPosition = 64, kHalf = kRingBytes / 2, kAdvance = kBlock / kGroup * kPosition;
   const uint8_t *table;      // this lane's word of the LDS mask row of key 0
-  const uint16_t *ids;       // all of them, padded
-  uint8_t *ring;
-  uint32_t lane, read_at, write_at, moving;
-  const uint32_t *from;
-  uint4 id;
-
-  __device__ __forceinline__ void store(uint32_t x) {
-    *reinterpret_cast<uint32_t *>(ring + write_at) = x;
-    *reinterpret_cast<uint32_t *>(ring + write_at + kHalf) = x;
-    write_at = (write_at + kAdvance) % kHalf;
-    from += kBlock / 2;
-    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");   // read by other lanes; LDS accesses of a wavefront are in order
-    __builtin_amdgcn_wave_barrier();
+  const uint16_t *ids;
+  ids16 id[kBlock / 8];
+  __device__ __forceinline__ void load(uint32_t b) {
+#pragma unroll
+    for (uint32_t u = 0; u < kBlock / 8; ++u) id[u] = *reinterpret_cast<const ids16 *>(ids + b * kBlock + 8 * u);
   }
-  // positions 1 to 24: from the last lane's first to as far as the first block of steps reads
-  __device__ __forceinline__ void begin() {
-    const uint32_t position = 1 + lane / 16, shift = lane % 16 / 4 * 2, part = lane % 4;
-    from = reinterpret_cast<const uint32_t *>(ids + position * kGroup - shift + 2 * part);
-    write_at = kPosition + lane * 4;
-#pragma unroll 1
-    for (uint32_t i = 0; i < 6; ++i) store(*from);
-    read_at = (kIdPad / kGroup - lane / 4) * kPosition + lane % 4 * 16;
-  }
-  // ids of the group of steps that is `positions` after where read_at stands, at most four
-  __device__ __forceinline__ void read_ids(uint32_t positions) {
-    id = *reinterpret_cast<const uint4 *>(ring + read_at + positions * kPosition);
-  }
-  __device__ __forceinline__ void first(uint32_t g) { read_ids(g / kGroup); }
-  __device__ __forceinline__ void prime(uint32_t) {
-    read_ids(kBlock / kGroup);
-    read_at = (read_at + kAdvance) % kHalf;
-  }
-  __device__ __forceinline__ void refill(uint32_t, uint32_t g) { read_ids(g / kGroup + 1); }
   __device__ __forceinline__ uint32_t look_up(uint32_t step) const {
-    const uint32_t u = step % kGroup, x = u < 2 ? id.x : u < 4 ? id.y : u < 6 ? id.z : id.w;
-    return *reinterpret_cast<const uint32_t *>(table + (u & 1 ? x >> 16 : x & 0xFFFFu));
-  }
-  __device__ __forceinline__ void block_begins() { moving = *from; }
-  __device__ __forceinline__ void block_ends() {
-    store(moving);
-    read_at = (read_at + kAdvance) % kHalf;
+    const uint32_t x = id[step / 8][step / 2 % 4];
+    return *reinterpret_cast<const uint32_t *>(table + (step & 1 ? x >> 16 : x & 0xFFFFu));
   }
 };
-static_assert(kSkew == 2 && kGroup == 8 && kBlock == 32 && kIdPad == 128, "positions of the ring");
 
-// All rows of one strip.  Where there are several (kMany), lanes 0 and 63 hold no word: their M is all ones, which
-// makes a step V' = 2 V + carry in with V's top bit as the carry out.  So lane 63 collects what lane 62 hands on, one bit
-// a step, first step highest, and lane 0 hands on what it was given as a word, likewise: strips exchange carries without
-// an instruction in any step (a history kept beside the row and bits put into the lane mask took 3.7 of 11.1 instructions).
-// carry[strip][block]: lane 63's word after step 32 * block + 31, bit 32 = the word is there (the value and its arrival
-// are one store, so no fence is needed); cleared before the launch.  A strip waits only for the strip before it,
-// which waits for no later one.  That one may not be running, though (compute units held by others), so a wait ends
-// after a.wait_looks; whoever gives up says so and goes on with zeros, and so does every strip that waits or comes to
-// wait, after one look: a word that never comes costs one limit, not one per block and strip.  The host then starts the
-// strips one by one.
-template <class Id, bool kMany>
-__device__ __forceinline__ void strip_rows(const RowsArgs &a, Masks<Id> masks, bool stored) {
-  const uint32_t lane = threadIdx.x, strip = a.strip0 + blockIdx.x, n_blocks = a.n_steps / kBlock;
-  const bool takes = kMany && strip != 0, gives = kMany && strip + 1 < a.strips;
-  const u64 *const cin_words = a.carry + (size_t)(strip - (takes ? 1 : 0)) * (n_blocks + kCarryPad);
-  u64 *const cout_words = a.carry + (size_t)strip * (n_blocks + kCarryPad);
-  auto peek = [&](uint32_t block) { return __hip_atomic_load(cin_words + block, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); };
-  // x: what a peek saw earlier.  (A way out of the blocks' loop on giving up makes every block wait for its stores: 34 ns a
-  // row in place of 20.)
-  auto carry_word = [&](uint32_t block, u64 x) -> uint32_t {
-    uint32_t word = __builtin_amdgcn_readfirstlane((uint32_t)x);
-    if (__builtin_expect(__builtin_amdgcn_readfirstlane((uint32_t)(x >> 32)) != 0, 1)) return word;
+struct RowsShared {
+  uint32_t feed[kFeeds][kFeedWords];     // masks of a block of steps, four steps of a lane together
+  uint32_t in[kFeeds];                   // what lane 0 hands on during a block
+  uint32_t out[kFeeds][kStripWords];     // V after a block; lane 63's is what the strip hands on
+};
+
+// The wavefronts of a strip meet after every block of steps.  Those that write LDS have done so by then; the first one
+// only reads, what it reads is not written again before it has used it (kFeeds), and it waits for none of its reads here.
+__device__ __forceinline__ void meet() { asm volatile("s_barrier" ::: "memory"); }
+__device__ __forceinline__ void meet_written() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
+
+// Masks for the first wavefront: two feeders take the blocks in turn.  Block c lies in LDS when the first one enters block
+// c - 1 (it reads ahead by a block); its masks are looked up one block of steps before they are written there.
+template <class Id>
+__device__ __forceinline__ void feed_masks(RowsShared &sh, Masks<Id> masks, uint32_t feeder, uint32_t n_blocks) {
+  const uint32_t lane = threadIdx.x & 63;
+  uint32_t M[kBlock];
+  auto look = [&]() {
+#pragma unroll
+    for (uint32_t u = 0; u < kBlock; ++u) M[u] = masks.look_up(u);
+  };
+  auto put = [&](uint32_t block) {
+    u32x4 *const out = reinterpret_cast<u32x4 *>(sh.feed[block % kFeeds]) + lane;
+#pragma unroll
+    for (uint32_t u = 0; u < kBlock; u += 4) out[u / 4 * kStripWords] = u32x4{M[u], M[u + 1], M[u + 2], M[u + 3]};
+  };
+  masks.load(feeder);
+  look();
+  put(feeder);
+  masks.load(feeder + 2);
+  if (!feeder) {
+    look();                            // block 2
+    masks.load(4);
+  }
+  meet_written();
+#pragma unroll 1
+  for (uint32_t b = 0; b < n_blocks; ++b) {
+    if ((b ^ feeder) & 1) {
+      look();                          // block b + 3
+      masks.load(b + 5);
+    } else {
+      put(b + 2);
+    }
+    meet_written();
+  }
+  meet_written();
+}
+
+// What strips tell each other.  carry[strip][block]: lane 63's word after step 32 * block + 31 of that strip, bit 32 = the
+// word is there (the value and its arrival are one store, so no fence is needed); cleared before the launch.  Lane 0 hands
+// row t on in step t, and lane 63 of the strip before received that carry in step t + 126: block b needs words b + 3 and
+// b + 4.  A word takes about a us from one strip to the other, three blocks of steps, so several looks are on their way at a
+// time, one begun in every block, each at the 64 words from the one needed on; the oldest that shows the word will do.  (One
+// look at each word, begun four blocks before it is needed, finds it only if the strip before is that much further ahead:
+// 32,312 x 32,297 operators 523 us against 515.)
+// A strip waits only for the strip before it, which waits for no later one.  That one may not be running, though (compute
+// units held by others), so a wait ends after a.wait_looks; whoever gives up says so and goes on with zeros, and so does
+// every strip that waits or comes to wait, after one look: a word that never comes costs one limit, not one per block and
+// strip.  The host then starts the strips one by one.
+__device__ __forceinline__ void take_carries(RowsShared &sh, const RowsArgs &a, bool takes) {
+  constexpr uint32_t kLooks = 4;
+  const uint32_t lane = threadIdx.x & 63, strip = a.strip0 + blockIdx.x, n_blocks = a.n_steps / kBlock;
+  const u64 *const words = a.carry + (size_t)(strip - (takes ? 1 : 0)) * (n_blocks + kCarryPad);
+  auto look = [&](uint32_t from) {                             // lane l: word from + l
+    return __hip_atomic_load(words + min(from + lane, n_blocks), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  };
+  // the word that `seen` shows in lane l; false: it was not there
+  auto found = [&](u64 seen, uint32_t l, uint32_t &word) {
+    word = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)seen, l);
+    return __builtin_amdgcn_readlane((int)(uint32_t)(seen >> 32), l) != 0;
+  };
+  auto wait_for = [&](uint32_t block) -> uint32_t {
+    uint32_t word;
 #pragma unroll 1
     for (uint32_t looks = 0; looks <= a.wait_looks; ++looks) {
-      __builtin_amdgcn_s_sleep(1);
-      const u64 y = peek(block);
+      const u64 y = look(block);
       const uint32_t over = __hip_atomic_load(a.gave_up, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-      word = __builtin_amdgcn_readfirstlane((uint32_t)y);
-      if (__builtin_amdgcn_readfirstlane((uint32_t)(y >> 32))) return word;
+      if (found(y, 0, word)) return word;
       if (__builtin_amdgcn_readfirstlane(over)) break;
     }
     if (lane == 0) {
@@ -399,151 +412,184 @@ __device__ __forceinline__ void strip_rows(const RowsArgs &a, Masks<Id> masks, b
     }
     return 0;
   };
+  uint32_t prev = 0;
+  u64 x[kLooks];
+  auto give = [&](uint32_t block, uint32_t word) {             // the input of `block`, with word block + 4
+    if (lane == 0) sh.in[block % kFeeds] = (prev << 30) | (word >> 2);
+    prev = word;
+  };
+  if (takes) {
+    prev = 3 < n_blocks ? wait_for(3) : 0;
+    give(0, 4 < n_blocks ? wait_for(4) : 0);
+    give(1, 5 < n_blocks ? wait_for(5) : 0);
+#pragma unroll
+    for (uint32_t u = 0; u < kLooks; ++u) x[u] = look(u + 2);
+  } else if (lane < kFeeds) {
+    sh.in[lane] = 0;
+  }
+  meet_written();
+  // kLooks blocks a turn, so that what is on its way stays in its register
+#pragma unroll 1
+  for (uint32_t b = 0; b < n_blocks; b += kLooks) {
+#pragma unroll
+    for (uint32_t u = 0; u < kLooks; ++u) {
+      if (b + u >= n_blocks) break;
+      if (takes) {
+        const uint32_t need = b + u + 6;                       // the looks were begun at need - 4, ... need - 1
+        uint32_t word = 0;
+        if (need < n_blocks && !found(x[u], 4, word) && !found(x[(u + 1) % kLooks], 3, word) &&
+            !found(x[(u + 2) % kLooks], 2, word) && !found(x[(u + 3) % kLooks], 1, word))
+          word = wait_for(need);
+        give(need - 4, word);
+        x[u] = look(need);
+      }
+      meet_written();
+    }
+  }
+  meet_written();
+}
 
+// The first wavefront leaves its words in LDS (a store of its own, by one lane, took it 70 cycles a block) and doesn't wait
+// for that: they are there a block later.  Taking and giving are two wavefronts' work: behind its own stores the one that
+// looks at the other strip's words waits for them too (32,312 x 32,297 operators 623 us against 500).
+__device__ __forceinline__ void give_carries(const RowsShared &sh, const RowsArgs &a, bool gives) {
+  const uint32_t lane = threadIdx.x & 63, strip = a.strip0 + blockIdx.x, n_blocks = a.n_steps / kBlock;
+  u64 *const own = a.carry + (size_t)strip * (n_blocks + kCarryPad);
+  auto hand_on = [&](uint32_t block) {
+    const uint32_t word = sh.out[block % kFeeds][kStripWords - 1];
+    if (lane == 0) __hip_atomic_store(own + block, (1ull << 32) | word, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  };
+  meet_written();
+#pragma unroll 1
+  for (uint32_t b = 0; b < n_blocks; ++b) {
+    if (gives && b >= 2) hand_on(b - 2);
+    meet_written();
+  }
+  meet_written();
+  if (gives)
+    for (uint32_t b = max(n_blocks, 2u) - 2; b < n_blocks; ++b) hand_on(b);
+}
+
+// All rows of one strip.  Where there are several (kMany), lanes 0 and 63 hold no word: their M is all ones, which
+// makes a step V' = 2 V + carry in with V's top bit as the carry out.  So lane 63 collects what lane 62 hands on, one bit
+// a step, first step highest, and lane 0 hands on what it was given as a word, likewise: strips exchange carries without
+// an instruction in any step (a history kept beside the row and bits put into the lane mask took 3.7 of 11.1 instructions).
+template <bool kMany>
+__device__ __forceinline__ void strip_rows(RowsShared &sh, const RowsArgs &a, bool stored) {
+  const uint32_t lane = threadIdx.x & 63, strip = a.strip0 + blockIdx.x, n_blocks = a.n_steps / kBlock;
   uint32_t V = ~0u;
   u64 even = 0, odd = 0;
-  uint32_t M[kBlock];
-  masks.begin();
-#pragma unroll
-  for (uint32_t g = 0; g < kBlock; g += kGroup) {
-    masks.first(g);
-#pragma unroll
-    for (uint32_t u = g; u < g + kGroup; ++u) M[u] = masks.look_up(u);
-  }
-  masks.prime(1);
-  uint32_t prev_word = 0;
-  u64 ahead = 0;                      // a carry word, looked at one block before it is needed
-  if (takes) {
-    prev_word = n_blocks > 3 ? carry_word(3, peek(3)) : 0;
-    ahead = peek(4);
-  }
-  asm volatile("" : "+v"(ahead));     // arrived: inside the loop the wait for it then leaves that block's stores in flight
+  u32x4 M[kBlock / 4];
   // A lane whose word nobody reads stores beyond the end of the buffer, which drops it: all lanes stay in step, and
   // no store needs a lane mask of its own.
   const __amdgpu_buffer_rsrc_t out = __builtin_amdgcn_make_buffer_rsrc(
       a.rows + (size_t)strip * a.n_steps * kStripWords, 0, (int)(a.n_steps * kStripWords * 4), 0x00027000);
   uint32_t at = stored ? lane * 16 : 0x80000000u;
+  meet();
+  auto feed = [&](uint32_t block) { return reinterpret_cast<const u32x4 *>(sh.feed[block % kFeeds]) + lane; };
+  uint32_t in = sh.in[0];              // read in the same order as in the loop, whose waits then count the reads that are later
+  __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+  for (uint32_t q = 0; q < kBlock / 4; ++q) {
+    M[q] = feed(0)[q * kStripWords];
+    __builtin_amdgcn_sched_barrier(0);
+  }
+#pragma unroll 1
   for (uint32_t b = 0; b < n_blocks; ++b) {
-    masks.block_begins();
+    const u32x4 *const ahead = feed(b + 1);
     if constexpr (kMany) {
-      // lane 0 hands row t on in step t; lane 63 of the strip before received that carry in step t + 126
-      uint32_t in = 0;
-      if (takes) {
-        const uint32_t next_word = b + 4 < n_blocks ? carry_word(b + 4, ahead) : 0;
-        in = (prev_word << 30) | (next_word >> 2);
-        prev_word = next_word;
-        ahead = peek(b + 5);
-      }
       V = lane ? V : in;
+      in = sh.in[(b + 1) % kFeeds];
+      __builtin_amdgcn_sched_barrier(0);
     }
 #pragma unroll
-    for (uint32_t g = 0; g < kBlock; g += kGroup) {
-#pragma unroll
-      for (uint32_t u = g; u < g + kGroup; u += 4) {
-        uint32_t v0, v1, v2;
-        row_steps(V, M[u], M[u + 1], even, odd, v0, v1);
-        row_steps(v1, M[u + 2], M[u + 3], even, odd, v2, V);
-        const u32x4 v = {v0, v1, v2, V};
-        __builtin_amdgcn_raw_buffer_store_b128(v, out, at, u * kStripWords * 4, 0);
-      }
-#pragma unroll
-      for (uint32_t u = g; u < g + kGroup; ++u) M[u] = masks.look_up(u);  // the same steps of the next block
-      masks.refill(b, g);
-      // kept in this order: a refill moved up needs a second register, and the copy back waits for the load
+    for (uint32_t q = 0; q < kBlock / 4; ++q) {
+      u32x4 v;
+      row_steps(V, M[q], even, odd, v);
+      V = v.w;
+      __builtin_amdgcn_raw_buffer_store_b128(v, out, at, q * kStripWords * 16, 0);
+      M[q] = ahead[q * kStripWords];
       __builtin_amdgcn_sched_barrier(0);
     }
     at += kBlock * kStripWords * 4;
-    masks.block_ends();
-    if (gives) {
-      const uint32_t word = __builtin_amdgcn_readlane((int)V, 63);
-      if (lane == 0)
-        __hip_atomic_store(cout_words + b, (1ull << 32) | word, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    }
+    if constexpr (kMany) sh.out[b % kFeeds][lane] = V;
+    meet();
   }
+  meet_written();
 }
 
-// One wavefront per workgroup, workgroup = strip (all of them, or one to a launch).  ref_id: n ids with kIdPad entries of the empty mask row before them
-// and id_length() - kIdPad - n after them, so that a lane whose row has not begun or is over adds nothing.  16-bit ids:
-// the strip builds its own mask table in LDS from cur_id and keeps all the reference's ids there too; wider ids (more
-// keys or operators than fit): masks and ids come from device memory.
+// A workgroup per strip (all of them, or one to a launch): the first wavefront does the rows, two look its masks up for it,
+// and two take and give carries where there are several strips.  ref_id: n ids with kIdPad entries of the empty mask row before them
+// and id_length() - kIdPad - n after them, so that a lane whose row has not begun or is over adds nothing.  16-bit ids: the
+// strip builds its own mask table in LDS from cur_id; wider ids (more keys than fit): masks come from device memory.
 //
-// Bound by the issue of one wavefront's instructions from one step to the next, seven of them (words of 32 bits, since
-// a wider word puts a second addition into the chain; masks are looked up one block of steps ahead, a carry word one
-// block before it is needed).  A scalar instruction that comes soon after a vector instruction that wrote a lane mask
-// waits for it, whichever mask it reads: so lanes are two steps apart and the shifts of two steps' carries stand
-// together, as far from the additions as they can.  Single strip, a row: 18.8 ns with a shift in every step, 17.3 with lanes
-// two steps apart and still one shift a step, 15.5 as it is; sixteen strips that hand carries on: 24.7, 22.1, 20.1.
-// (The parts of V that the next row needs worked out together with V, one operation less in the chain and one more
-// to issue: 18.6 and 21.8.)  Rows stored one word at a time, carries exchanged by two more instructions a step and ids
-// read unaligned: 18.9 and 29.4.  Updating a whole row at once in one wavefront, its carries crossing lanes by two ballots and
-// scalar arithmetic, took 128 ns a row at 1,156 columns and 755 ns at 32,300: 1,154 x 1,156 operators 149 -> 27 us, 32,312 x
-// 32,297 operators 24.5 -> 0.65 ms.  Two steps between lanes and the two lanes without a word cost a strip
-// about 70 steps more until the next one has its first carry: 500 x 30,000 operators take 252 us a call, 214 without.
+// Bound by the issue of the first wavefront's instructions from one step to the next: three vector instructions in a chain
+// and a shift of the carries, with a half of one for the masks' coming and the row's going (words of 32 bits, since a wider
+// word puts a second addition into the chain).  A scalar instruction that comes soon after a vector instruction that wrote a
+// lane mask waits for it, whichever mask it reads: so lanes are two steps apart and the shifts of two steps' carries stand
+// together, as far from the additions as they can.  A loop of nothing but these steps, reads and stores takes 24.8 cycles a
+// step, without the shifts 18.8; with a shift in every step 28.8, with the parts of V that the next row needs worked out
+// beside V, one operation less in the chain and one more to issue, 28.3, with the carries in vector registers 34.8.
+// One wavefront that also looked up its masks and exchanged carries took seven instructions a step and 15.5 ns (20.1 in
+// several strips): 1,154 x 1,156 operators 27.0 us, now 23.0; 32,312 x 32,297 in 17 strips 650 us, now 500, of which some 80
+// are the strips' start one after the other.  Updating a whole row at once in one wavefront, its carries crossing lanes by
+// two ballots and scalar arithmetic, took 149 us and 24.5 ms.
 template <class Id>
-__global__ __launch_bounds__(64) void ss_align_rows_kernel(const Id *__restrict__ ref_id,
-                                                           const Id *__restrict__ cur_id, uint32_t m, RowsArgs a,
-                                                           const uint32_t *__restrict__ n_keys) {
+__global__ __launch_bounds__(kRowsThreads) void ss_align_rows_kernel(const Id *__restrict__ ref_id,
+                                                                     const Id *__restrict__ cur_id, uint32_t m, RowsArgs a,
+                                                                     const uint32_t *__restrict__ n_keys) {
   constexpr bool kLds = sizeof(Id) == 2;
+  __shared__ RowsShared sh;
   extern __shared__ uint32_t lds[];
-  const uint32_t lane = threadIdx.x, strip = a.strip0 + blockIdx.x;
+  const uint32_t tid = threadIdx.x, lane = tid & 63, role = __builtin_amdgcn_readfirstlane(tid >> 6), strip = a.strip0 + blockIdx.x;
   const bool many = a.strips > 1;
   const uint32_t first = many ? 1 : 0;                       // lane of the strip's first word
   const uint32_t w0 = strip * kInnerWords;
   const uint32_t words = min(many ? kInnerWords : kStripWords, a.W - w0);
   const bool stored = lane >= first && lane < first + words;
-  const uint32_t n_mask_rows = *n_keys + 1;
+  const uint32_t n_mask_rows = *n_keys + 1, n_blocks = a.n_steps / kBlock;
   if (kLds && n_mask_rows > kLdsKeys) {                      // launched before the number was known, and the ids are wide
     ss_tell_host(a.done);
     return;
   }
   Masks<Id> masks;
   if constexpr (kLds) {
-    uint8_t *const ring = reinterpret_cast<uint8_t *>(lds + n_mask_rows * kStripWords);
-    Id *const lds_ids = reinterpret_cast<Id *>(ring + kRingBytes);
     uint4 *const table4 = reinterpret_cast<uint4 *>(lds);
-    for (uint32_t i = lane; i < n_mask_rows * (kStripWords / 4); i += 64) {
+    for (uint32_t i = tid; i < n_mask_rows * (kStripWords / 4); i += kRowsThreads) {
       const uint32_t part = i % (kStripWords / 4);
       table4[i] = uint4{many && part == 0 ? ~0u : 0, 0, 0, many && part == kStripWords / 4 - 1 ? ~0u : 0};
     }
-    const uint4 *src = reinterpret_cast<const uint4 *>(ref_id);
-    uint4 *dst = reinterpret_cast<uint4 *>(lds_ids);
-    const uint32_t n16 = id_length(a.n_steps) * sizeof(Id) / 16;
-    for (uint32_t i0 = lane; i0 < n16; i0 += 8 * 64) {
-      uint4 x[8];
+    // ten words' columns at a time, all of them in flight
+    constexpr uint32_t kPer = (kStripWords * 32 + kRowsThreads - 1) / kRowsThreads;
+    uint32_t id[kPer];
 #pragma unroll
-      for (uint32_t u = 0; u < 8; ++u)
-        if (i0 + 64 * u < n16) x[u] = src[i0 + 64 * u];
-#pragma unroll
-      for (uint32_t u = 0; u < 8; ++u)
-        if (i0 + 64 * u < n16) dst[i0 + 64 * u] = x[u];
+    for (uint32_t u = 0; u < kPer; ++u) {
+      const uint32_t w = u * (kRowsThreads / 32) + (tid >> 5), j = (w0 + w) * 32 + (tid & 31);
+      id[u] = w < words && j < m ? cur_id[j] : 0xFFFFFFFFu;
     }
     __syncthreads();
-    // two words' columns a pass, sixteen passes of ids in flight
-    for (uint32_t g = 0; g < words; g += 32) {
-      uint32_t id[16];
 #pragma unroll
-      for (uint32_t u = 0; u < 16; ++u) {
-        const uint32_t w = g + 2 * u + (lane >> 5), j = (w0 + w) * 32 + (lane & 31);
-        id[u] = w < words && j < m ? cur_id[j] : 0xFFFFFFFFu;
-      }
-#pragma unroll
-      for (uint32_t u = 0; u < 16; ++u)
-        if (id[u] != 0xFFFFFFFFu)
-          atomicOr(&lds[key_of((uint16_t)id[u]) * kStripWords + first + g + 2 * u + (lane >> 5)], 1u << (lane & 31));
-    }
+    for (uint32_t u = 0; u < kPer; ++u)
+      if (id[u] != 0xFFFFFFFFu)
+        atomicOr(&lds[key_of((uint16_t)id[u]) * kStripWords + first + u * (kRowsThreads / 32) + (tid >> 5)], 1u << (tid & 31));
     __syncthreads();
     masks.table = reinterpret_cast<const uint8_t *>(lds + lane);
-    masks.ids = lds_ids;
-    masks.ring = ring;
-    masks.lane = lane;
   } else {
     using Global = const __attribute__((address_space(1))) uint32_t *;
     masks.word = stored ? (Global)(a.masks + w0 + lane - first) : (Global)&all_ones;
-    masks.ids = ref_id + kIdPad - kSkew * lane;
     masks.W = stored ? a.W : 0;
   }
-  if (many) strip_rows<Id, true>(a, masks, stored);
-  else strip_rows<Id, false>(a, masks, stored);
+  masks.ids = ref_id + kIdPad - kSkew * lane;
+  if (role == 0) {
+    if (many) strip_rows<true>(sh, a, stored);
+    else strip_rows<false>(sh, a, stored);
+  } else if (role < 3) {
+    feed_masks(sh, masks, role - 1, n_blocks);
+  } else if (role == 3) {
+    take_carries(sh, a, many && strip != 0);
+  } else {
+    give_carries(sh, a, many && strip + 1 < a.strips);
+  }
   ss_tell_host(a.done);
 }
 
@@ -783,8 +829,11 @@ __global__ __launch_bounds__(kChainThreads) void ss_align_chain_kernel(const Id 
   }
 }
 
+// One thread walks, all of them load its tile.  32,312 rows: 25 us; with 64 threads, which load it in 24 turns, 36.
+constexpr uint32_t kPairThreads = 256;
+
 template <class Id>
-__global__ __launch_bounds__(64) void ss_align_pairs_kernel(const Id *__restrict__ ref_id, uint32_t n,
+__global__ __launch_bounds__(kPairThreads) void ss_align_pairs_kernel(const Id *__restrict__ ref_id, uint32_t n,
                                                             const uint32_t *__restrict__ masks, uint32_t m, uint32_t W,
                                                             uint32_t n_steps, const uint32_t *__restrict__ rows,
                                                             const uint16_t *__restrict__ table,
@@ -806,7 +855,7 @@ __global__ __launch_bounds__(64) void ss_align_pairs_kernel(const Id *__restrict
   }
   const RowBlock blk(k, n);
   const int w0 = j / (int)kEntries * (int)(kEntries / 32) - (int)(kMargin / 32);     // the tile the table came from
-  paired[threadIdx.x] = -1;
+  if (threadIdx.x < kWalkRows) paired[threadIdx.x] = -1;
   load_tile(ref_id, masks, rows, W, n_steps, blk, w0, M, X);
   __syncthreads();
   if (threadIdx.x == 0) walk_tile(blk.hi - blk.lo, w0, j, M, X, [&](uint32_t q, int c) { paired[q] = c; });
@@ -815,16 +864,8 @@ __global__ __launch_bounds__(64) void ss_align_pairs_kernel(const Id *__restrict
   ss_tell_host(done);
 }
 
-// LDS of the rows kernel with 16-bit ids: mask rows, ring and all ids of the reference
-size_t lds_need(uint32_t n_keys, uint32_t n) {
-  return (size_t)(n_keys + 1) * kStripWords * 4 + kRingBytes + (size_t)id_length(steps_of(n)) * 2;
-}
-
-// the most keys with which it can run
-uint32_t most_few(uint32_t n) {
-  const size_t ids = lds_need(0, n);
-  return ids > kLdsBytes ? 0 : (uint32_t)std::min<size_t>(kLdsKeys - 1, (kLdsBytes - ids) / (kStripWords * 4));
-}
+// LDS of the rows kernel with 16-bit ids, beside what it always has: its mask rows
+size_t lds_need(uint32_t n_keys) { return (size_t)(n_keys + 1) * kStripWords * 4; }
 
 // Where everything lies.  `d` device scratch, `h` pinned scratch.
 struct Layout {
@@ -904,7 +945,7 @@ int launch_rows(ss_ctx *ctx, const Layout &y, uint8_t *d, uint8_t *hd, uint32_t 
   done.wgs = y.short_rows ? y.strips : y.walk_blocks;
   if (y.short_rows) args.done = done;
   for (; args.strip0 < y.strips; args.strip0 += per_launch)
-    hipLaunchKernelGGL(ss_align_rows_kernel<Id>, dim3(per_launch), dim3(64), kLds ? lds_need(keys, y.n) : 0, s, ref_id,
+    hipLaunchKernelGGL(ss_align_rows_kernel<Id>, dim3(per_launch), dim3(kRowsThreads), kLds ? lds_need(keys) : 0, s, ref_id,
                        cur_id, y.m, args, n_keys);
   if (!y.short_rows) {
     const uint32_t *cmasks = masks, *crows = rows;
@@ -916,8 +957,8 @@ int launch_rows(ss_ctx *ctx, const Layout &y, uint8_t *d, uint8_t *hd, uint32_t 
                        y.walk_blocks, groups);
     hipLaunchKernelGGL(ss_align_chain_kernel<Id>, dim3(1), dim3(kChainThreads), 0, s, ref_id, y.n, cmasks, y.m, y.W,
                        y.n_steps, crows, table, groups, entry, group_entry, pair);
-    hipLaunchKernelGGL(ss_align_pairs_kernel<Id>, dim3(y.walk_blocks), dim3(64), 0, s, ref_id, y.n, cmasks, y.m, y.W, y.n_steps,
-                       crows, table, entry, group_entry, pair, done);
+    hipLaunchKernelGGL(ss_align_pairs_kernel<Id>, dim3(y.walk_blocks), dim3(kPairThreads), 0, s, ref_id, y.n, cmasks, y.m, y.W,
+                       y.n_steps, crows, table, entry, group_entry, pair, done);
   }
   SS_HIP(hipGetLastError());
   return SS_OK;
@@ -935,7 +976,7 @@ int ss_align_core(ss_ctx *ctx, const ss_op_t *ref, uint32_t n, const ss_op_t *cu
   if (n_keys_out) *n_keys_out = 0;
   if (n == 0 || m == 0) return SS_OK;
   const Layout y(n, m);
-  const uint32_t few = most_few(n);
+  const uint32_t few = kLdsKeys - 1;
   hipStream_t s = ctx->s_aux;
   uint8_t *d = nullptr, *h = nullptr, *hd = nullptr;
   volatile uint32_t *h_flag = nullptr, *h_n_keys = nullptr;
