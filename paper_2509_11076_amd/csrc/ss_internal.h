@@ -211,6 +211,23 @@ ss_done ss_next_done(ss_ctx *ctx);                 // for the next kernel on s_a
 int ss_wait_done(ss_ctx *ctx, const ss_done &d);   // the stream itself is waited for where the word doesn't come soon
 
 #ifdef __HIPCC__
+// v of another lane by one data-parallel move, `none` where there is no such lane
+template <int kCtrl, int kRows>
+__device__ __forceinline__ uint32_t dpp_u32(uint32_t v, uint32_t none) {
+  return (uint32_t)__builtin_amdgcn_update_dpp((int)none, (int)v, kCtrl, kRows, 0xF, false);
+}
+
+// inclusive prefix sum over the 64 lanes: within rows of 16, then the rows' last lanes handed on
+__device__ __forceinline__ uint32_t wave_scan_u32(uint32_t v) {
+  v += dpp_u32<0x111, 0xF>(v, 0);
+  v += dpp_u32<0x112, 0xF>(v, 0);
+  v += dpp_u32<0x114, 0xF>(v, 0);
+  v += dpp_u32<0x118, 0xF>(v, 0);
+  v += dpp_u32<0x142, 0xA>(v, 0);
+  v += dpp_u32<0x143, 0xC>(v, 0);
+  return v;
+}
+
 // The last thing that every thread of each of the workgroups calls.  Results written to pinned memory may still be in the
 // L2 of the workgroup's die when its stores have completed: every workgroup releases its own to the system before it counts
 // (the last one's release writes back its own die's only; beside products on the compute stream the host then saw the word

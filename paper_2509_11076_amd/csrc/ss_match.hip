@@ -9,8 +9,8 @@
 //     only): an anchor's ordinal among the reference's operators with its key, at each of three
 //     relaxation levels, and the operator of that ordinal in the current sequence.  Few anchors or
 //     short sequences: one workgroup or wavefront per anchor counts and searches.  Many: the layers of a model
-//     share their keys, so the anchors' distinct keys are collected first, one workgroup per key
-//     lists the places where it occurs, and an anchor looks its ordinal up.
+//     share their keys, so the anchors' distinct keys are collected first, both sequences are gone through once, chunk by
+//     chunk, to number the occurrences of each key, and an anchor looks its ordinal up.
 #include <algorithm>
 #include <cstring>
 
@@ -65,6 +65,11 @@ struct PrepArgs {
 // 22.4 us a call, together 20.1; 8,000 27 to 29 and 25.5).  Long ones come over the link faster one by one (18,464 38.5 and
 // 38.0, 30,000 52.0 and 52.6, 65,536 96 and 105).
 constexpr uint32_t kTogetherMapped = 16384;
+
+// Sequences of this many bytes each take two such passes: the reference comes over the link while the host copies the other
+// one to pinned memory (about 30 GB/s, half the link's rate).  The cosine of 65,536 operators 105 us a call in one pass and
+// 90 in two, of 50,000 68.1 and 66.6, of 24,000 39.4 and 38.9, of 9,000 20.2 and 21.8.
+constexpr size_t kSplitBytes = 768 * 1024;
 
 template <bool kTogether>
 __global__ __launch_bounds__(256) void ss_prep_kernel(PrepArgs a) {
@@ -370,34 +375,51 @@ __global__ __launch_bounds__(256) void ss_anchor_short_kernel(AnchorArgs g) {
 // ---- many anchors: the distinct keys first ------------------------------------------------------------------------
 //
 // 8,001 anchors over 18,464 + 18,467 operators: comparing every anchor with every operator is bound by the issue of 300
-// million compares (186 us).  With some forty distinct keys the three launches below take 4 us for the keys (20 with
-// every anchor at the table), 17 for the lists (bound by the turns of a workgroup over both sequences; 22 with one sequence
-// after the other and cur twice; loading a turn ahead gains nothing) and 7 for the anchors.
+// million compares (186 us).  With some forty distinct keys the three launches below take 3.9 us for the keys, 4.1 to number
+// their occurrences and 8.8 for the anchors.  (A workgroup per key that went through both sequences and listed its places took
+// 16.5 us, bound by the turns of one workgroup, and the anchors 7.8.)
 
-// Per level: an open-addressing table of at least 2k slots holding 1 + the anchor that stands for a key, the slots in
-// use, and for each of them where its places in the current sequence are listed and how many there are.
-struct KeyLists {
-  uint32_t *rep[3], *used[3], *start[3], *count[3];
-  uint32_t *n_used;            // [3]; [3..5]: places listed so far
-  uint32_t *key_of[3];         // anchor -> slot
-  uint32_t *rank[3];           // reference operator -> its ordinal, where its key is an anchor's
-  uint32_t *place[3];          // places, key after key
-  uint32_t mask, shift, max_lists;
+// Per level: an open-addressing table of at least 2k slots holding the anchor that stands for a key, and beside it the
+// key itself with its number; and for every operator of both sequences the number of its key and how many with that key come
+// before it in its chunk.
+struct KeyTable {
+  uint32_t *rep[3];
+  uint4 *key[3];               // {1 + number, token, stack, sig}; zeros: no key
+  uint32_t *n_used;            // [3]: distinct keys
+  uint32_t *info[2][3];        // [0] ref, [1] cur: number << kRankBits | rank in the chunk, or kNoKey; whole chunks
+  uint32_t *count[2];          // [level][chunk][number]: occurrences in the chunk, n_used of the level to a chunk
+  uint32_t mask, shift, max_keys;
+  uint32_t chunk_bits[2], chunks[2];         // operators of a chunk (a power of two), chunks
 };
+// They take the calls of that many comparisons of an anchor with an operator (10 us of comparing), and those where a single
+// search goes through that many operators, whatever the number of anchors: 500 anchors over 6,100 + 6,100 operators 38.6 us a
+// call with some forty keys and 47.6 with a key each, a search each 43.8 and 45.9; 300 over 18,464 53.7 and 56.6 against 94.9
+// and 90.4; 20 over 65,536 105 against 279; but 500 over 5,000 38.3 and 51 against 41.7 and 40.
+constexpr uint64_t kManyPairs = 1ull << 24, kLongSearch = 12000;
+constexpr uint32_t kRankBits = 20, kNoKey = 0xFFFFFFFFu;
+constexpr uint32_t kChunkThreads = 512, kMaxChunks = 256;
+static_assert((1u << 23) / kMaxChunks < 1u << kRankBits, "a rank fits its bits");
 
-// More distinct keys (of all levels) than this, or than half the anchors, and a workgroup per key costs more than one
-// per anchor.
-constexpr uint32_t kMaxLists = 4096;
+// More distinct keys (of all levels) than this, and an anchor is searched for by itself.
+constexpr uint32_t kMaxKeys = 4096;
+static_assert(kMaxKeys <= 1u << (32 - kRankBits), "a key's number fits its bits");
 
 __device__ __forceinline__ bool same_at(const ss_op_t &x, const ss_op_t &y, int L) {
   return (x.op_token == y.op_token) & ((L == 2) | (x.sig == y.sig)) & ((L != 0) | (x.stack_hash == y.stack_hash));
 }
 
-// workgroup (x, L): the anchors' keys of level L.  They are few, and every anchor would go for the same few slots: the
-// first of each key within the workgroup (found through a table in LDS) goes, the others take over its slot.
-__global__ __launch_bounds__(256) void ss_keys_kernel(AnchorArgs g, KeyLists q) {
+__device__ __forceinline__ unsigned long long level_hash(const ss_op_t &o, int L) {
+  unsigned long long x = o.op_token;
+  if (L < 2) x |= (unsigned long long)o.sig << 32;
+  if (L < 1) x ^= (unsigned long long)o.stack_hash << 18;
+  return x * 0x9E3779B97F4A7C15ull;
+}
+
+// workgroup (x, L): the anchors' keys of level L.  They are few, and every anchor would go for the same few slots: only the
+// first of each key within the workgroup (found through a table in LDS) goes.
+__global__ __launch_bounds__(256) void ss_keys_kernel(AnchorArgs g, KeyTable q) {
   constexpr uint32_t kSlots = 512, kShift = 64 - 9;
-  __shared__ uint32_t first[kSlots], slot_of[kSlots];
+  __shared__ uint32_t first[kSlots];
   __shared__ ss_op_t ops[256];
   const uint32_t a = blockIdx.x * 256 + threadIdx.x;
   const int L = blockIdx.y;
@@ -410,10 +432,7 @@ __global__ __launch_bounds__(256) void ss_keys_kernel(AnchorArgs g, KeyLists q) 
   ops[threadIdx.x] = R;
   for (uint32_t i = threadIdx.x; i < kSlots; i += 256) first[i] = 0;
   __syncthreads();
-  unsigned long long x = R.op_token;
-  if (L < 2) x |= (unsigned long long)R.sig << 32;
-  if (L < 1) x ^= (unsigned long long)R.stack_hash << 18;
-  x *= 0x9E3779B97F4A7C15ull;
+  const unsigned long long x = level_hash(R, L);
   uint32_t l = (uint32_t)(x >> kShift);
   bool goes = false;
   for (uint32_t probe = 0; live && probe < kSlots; ++probe) {  // at most 256 keys in 512 slots
@@ -425,139 +444,143 @@ __global__ __launch_bounds__(256) void ss_keys_kernel(AnchorArgs g, KeyLists q) 
     if (same_at(ops[seen - 1], R, L)) break;
     l = (l + 1) % kSlots;
   }
-  if (goes) {
-    uint32_t h = (uint32_t)(x >> q.shift);
-    for (uint32_t probe = 0; probe <= q.mask; ++probe) {       // at most k keys in more than 2k slots
-      uint32_t seen = __hip_atomic_load(q.rep[L] + h, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-      if (!seen) {
-        seen = atomicCAS(q.rep[L] + h, 0u, a + 1);
-        if (!seen) {
-          q.used[L][atomicAdd(q.n_used + L, 1u)] = h;
-          break;
-        }
-      }
-      if (same_at(g.ref[g.anchors[seen - 1].ref_op], R, L)) break;
-      h = (h + 1) & q.mask;
+  // a slot holds 1 + the anchor and seven more bits of the hash: another key's anchor is rarely looked at (two dependent loads)
+  constexpr uint32_t kTagShift = 25;
+  uint32_t h = (uint32_t)(x >> q.shift);
+  const uint32_t tag = (uint32_t)(x >> (q.shift - 7)) & 127u, entry = tag << kTagShift | (a + 1);
+  bool won = false;
+  for (uint32_t probe = 0; goes && probe <= q.mask; ++probe) { // at most k keys in more than 2k slots
+    uint32_t seen = __hip_atomic_load(q.rep[L] + h, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if (!seen) {
+      seen = atomicCAS(q.rep[L] + h, 0u, entry);
+      if (!seen) { won = true; break; }
     }
-    slot_of[l] = h;
+    if (seen >> kTagShift == tag && same_at(g.ref[g.anchors[(seen & ((1u << kTagShift) - 1)) - 1].ref_op], R, L)) break;
+    h = (h + 1) & q.mask;
   }
-  __syncthreads();
-  if (live) q.key_of[L][a] = slot_of[l];
+  // numbers for a wavefront's new keys at once: additions to one word are served one after the other
+  const uint64_t winners = __ballot(won);
+  if (!winners) return;
+  const int lane = threadIdx.x & 63;
+  uint32_t number = 0;
+  if (lane == __builtin_ctzll(winners)) number = atomicAdd(q.n_used + L, (uint32_t)__popcll(winners));
+  number = (uint32_t)__builtin_amdgcn_readlane((int)number, __builtin_ctzll(winners));
+  number += (uint32_t)__popcll(winners & (lane ? (~0ull >> (64 - lane)) : 0ull));
+  if (won) q.key[L][h] = uint4{number + 1, R.op_token, L < 1 ? R.stack_hash : 0, L < 2 ? R.sig : 0};
 }
 
-constexpr uint32_t kHitWords = 4096;                   // groups of 64 operators of cur whose hits are kept in LDS
+// Where the counts of a level's chunks are.
+__device__ __forceinline__ uint32_t *counts_of(const KeyTable &q, int which, int L) {
+  uint32_t before = 0;
+  for (int l = 0; l < L; ++l) before += q.n_used[l];
+  return q.count[which] + (size_t)before * q.chunks[which];
+}
 
-// One workgroup per key: ordinals of its occurrences in ref, and the list of those in cur.  Both sequences are gone through
-// together, a wavefront taking 256 consecutive operators of each a turn, all loads in flight, one barrier a turn (the
-// counts alternate between two sets).  The list's place is known only after that, so the hits in cur are kept and
-// the list is written from them, where cur has more than kHitWords * 64 operators by going through it again.
-__global__ __launch_bounds__(1024) void ss_lists_kernel(AnchorArgs g, KeyLists q) {
-  constexpr uint32_t kTurn = 4096;
-  __shared__ uint32_t wave_cnt[2][2][16], s_start, at[kHitWords];
-  __shared__ uint64_t hits[kHitWords];
-  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+// Workgroup (x, L): the operators of a chunk of ref or cur at level L, 512 at a time.  Equal numbers within a wavefront are
+// found by a ballot for each of their bits, and wavefronts tell each other their counts.
+__global__ __launch_bounds__(kChunkThreads) void ss_chunks_kernel(AnchorArgs g, KeyTable q) {
+  constexpr uint32_t W = kChunkThreads / 64;
+  __shared__ uint8_t mine[W][kMaxKeys];
+  __shared__ uint32_t seen[kMaxKeys];
+  const int L = blockIdx.y;
+  const uint32_t keys = q.n_used[L], tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
+  if (q.n_used[0] + q.n_used[1] + q.n_used[2] > q.max_keys) return;
+  const uint32_t which = blockIdx.x >= q.chunks[0], chunk = blockIdx.x - (which ? q.chunks[0] : 0);
+  const ss_op_t *const seq = which ? g.cur : g.ref;
+  const uint32_t len = which ? g.m : g.n, size = 1u << q.chunk_bits[which], lo = chunk * size;
+  const uint32_t bits = keys > 1 ? 32 - __builtin_clz(keys - 1) : 0;
   const uint64_t below = lane ? (~0ull >> (64 - lane)) : 0ull;
-  const uint32_t n0 = q.n_used[0], n1 = q.n_used[1], n2 = q.n_used[2];
-  if (n0 + n1 + n2 > q.max_lists) return;
-  for (uint32_t it = blockIdx.x; it < n0 + n1 + n2; it += gridDim.x) {
-    const int L = it < n0 ? 0 : it < n0 + n1 ? 1 : 2;
-    const uint32_t h = q.used[L][it - (L == 0 ? 0 : L == 1 ? n0 : n0 + n1)];
-    const ss_op_t R = g.ref[g.anchors[q.rep[L][h] - 1].ref_op];
-    struct Turn { uint64_t hit[4]; uint32_t ord, all; };
-    auto load = [&](const ss_op_t *seq, uint32_t len, uint32_t j0, ss_op_t *o) {
+  for (uint32_t u = tid; u < keys; u += kChunkThreads) seen[u] = 0;
+  for (uint32_t at = 0; at < size; at += kChunkThreads) {
+    const uint32_t i = lo + at + tid;
+    ss_op_t o = {0, 0, 0, 0};
+    if (i < len) o = seq[i];
+    for (uint32_t u = tid; u < keys; u += kChunkThreads)
 #pragma unroll
-      for (int u = 0; u < 4; ++u) {
-        o[u].op_token = 0;
-        if (j0 + 64 * u < len) o[u] = seq[j0 + 64 * u];
+      for (uint32_t v = 0; v < W; ++v) mine[v][u] = 0;
+    uint32_t id = kNoKey;
+    if (o.op_token) {
+      uint32_t h = (uint32_t)(level_hash(o, L) >> q.shift);
+      for (uint32_t probe = 0; probe <= q.mask; ++probe) {     // half of the slots are free at least
+        const uint4 k = q.key[L][h];
+        if (!k.x) break;
+        if ((k.y == o.op_token) & ((L == 2) | (k.w == o.sig)) & ((L != 0) | (k.z == o.stack_hash))) { id = k.x - 1; break; }
+        h = (h + 1) & q.mask;
       }
-    };
-    auto test = [&](const ss_op_t *o, Turn &t, uint32_t *cnt) {
-      uint32_t mine = 0;
-#pragma unroll
-      for (int u = 0; u < 4; ++u) {
-        t.hit[u] = __ballot(same_at(o[u], R, L));
-        mine += __popcll(t.hit[u]);
-      }
-      if (lane == 0) cnt[w] = mine;
-    };
-    auto count = [&](Turn &t, const uint32_t *cnt) {           // hits before this wavefront's, and of all of them
-      t.ord = t.all = 0;
-      for (int v = 0; v < 16; ++v) {
-        const uint32_t x = cnt[v];
-        if (v < w) t.ord += x;
-        t.all += x;
-      }
-    };
-    uint32_t seen_r = 0, seen_c = 0;
-    int set = 0;
-    for (uint32_t base = 0; base < max(g.n, g.m); base += kTurn, set ^= 1) {
-      const uint32_t j0 = base + w * 256 + lane;
-      ss_op_t r[4], c[4];
-      load(g.ref, g.n, j0, r);
-      load(g.cur, g.m, j0, c);
-      Turn tr, tc;
-      test(r, tr, wave_cnt[set][0]);
-      test(c, tc, wave_cnt[set][1]);
-      __syncthreads();
-      count(tr, wave_cnt[set][0]);
-      count(tc, wave_cnt[set][1]);
-      uint32_t ord_r = seen_r + tr.ord, ord_c = seen_c + tc.ord;
-#pragma unroll
-      for (int u = 0; u < 4; ++u) {
-        if ((tr.hit[u] >> lane) & 1ull) q.rank[L][j0 + 64 * u] = ord_r + (uint32_t)__popcll(tr.hit[u] & below);
-        const uint32_t word = base / 64 + w * 4 + u;
-        if (lane == 0 && word < kHitWords) { hits[word] = tc.hit[u]; at[word] = ord_c; }
-        ord_r += __popcll(tr.hit[u]);
-        ord_c += __popcll(tc.hit[u]);
-      }
-      seen_r += tr.all;
-      seen_c += tc.all;
     }
-    if (threadIdx.x == 0) {
-      s_start = atomicAdd(q.n_used + 3 + L, seen_c);         // the keys of a level share no place: m entries suffice
-      q.start[L][h] = s_start;
-      q.count[L][h] = seen_c;
+    const bool live = id != kNoKey;
+    uint64_t same = __ballot(live);
+    for (uint32_t b = 0; b < bits; ++b) {
+      const bool set = (id >> b) & 1u;
+      const uint64_t with = __ballot(set);
+      same &= set ? with : ~with;
     }
+    const uint32_t rank = (uint32_t)__popcll(same & below);
     __syncthreads();
-    uint32_t *const out = q.place[L] + s_start;
-    const uint32_t words = min((g.m + 63) / 64, kHitWords);
-    for (uint32_t word = w; word < words; word += 16) {
-      const uint64_t hit = hits[word];
-      if ((hit >> lane) & 1ull) out[at[word] + (uint32_t)__popcll(hit & below)] = word * 64 + lane;
-    }
-    if (g.m > kHitWords * 64) {
-      uint32_t seen = at[kHitWords - 1] + (uint32_t)__popcll(hits[kHitWords - 1]);
-      for (uint32_t base = kHitWords * 64; base < g.m; base += kTurn, set ^= 1) {
-        const uint32_t j0 = base + w * 256 + lane;
-        ss_op_t c[4];
-        load(g.cur, g.m, j0, c);
-        Turn t;
-        test(c, t, wave_cnt[set][0]);
-        __syncthreads();
-        count(t, wave_cnt[set][0]);
-        uint32_t ord = seen + t.ord;
+    if (live && !rank) mine[w][id] = (uint8_t)__popcll(same);
+    __syncthreads();
+    uint32_t before = 0;
+    if (live) {
+      before = seen[id] + rank;
 #pragma unroll
-        for (int u = 0; u < 4; ++u) {
-          if ((t.hit[u] >> lane) & 1ull) out[ord + (uint32_t)__popcll(t.hit[u] & below)] = j0 + 64 * u;
-          ord += __popcll(t.hit[u]);
-        }
-        seen += t.all;
-      }
+      for (uint32_t v = 0; v < W; ++v) before += v < w ? mine[v][id] : 0;
     }
-    __syncthreads();                                         // the next key's counts and hits
+    q.info[which][L][i] = live ? id << kRankBits | before : kNoKey;
+    __syncthreads();
+    for (uint32_t u = tid; u < keys; u += kChunkThreads) {
+      uint32_t all = 0;
+#pragma unroll
+      for (uint32_t v = 0; v < W; ++v) all += mine[v][u];
+      seen[u] += all;                                          // each thread its own keys: zeroed and read by others behind barriers
+    }
   }
+  uint32_t *const out = counts_of(q, which, L) + (size_t)chunk * keys;
+  for (uint32_t u = tid; u < keys; u += kChunkThreads) out[u] = seen[u];
+}
+
+// The operator of cur with the number and ordinal of operator i of ref at level L, or -1; by one wavefront.
+__device__ __forceinline__ int32_t look_up(const KeyTable &q, uint32_t i, int L) {
+  const uint32_t lane = threadIdx.x & 63, keys = q.n_used[L], info = q.info[0][L][i], id = info >> kRankBits;
+  const uint32_t *const in_ref = counts_of(q, 0, L), *const in_cur = counts_of(q, 1, L);
+  const uint32_t c = i >> q.chunk_bits[0];
+  uint32_t ordinal = 0;
+  for (uint32_t c0 = 0; c0 < c; c0 += 64) ordinal += c0 + lane < c ? in_ref[(size_t)(c0 + lane) * keys + id] : 0;
+  ordinal = (uint32_t)__builtin_amdgcn_readlane((int)wave_scan_u32(ordinal), 63) + (info & ((1u << kRankBits) - 1));
+  for (uint32_t c0 = 0, before = 0; c0 < q.chunks[1]; c0 += 64) {
+    const uint32_t v = c0 + lane < q.chunks[1] ? in_cur[(size_t)(c0 + lane) * keys + id] : 0, upto = before + wave_scan_u32(v);
+    const uint64_t there = __ballot(upto > ordinal);
+    if (there) {
+      const int l = __builtin_ctzll(there);
+      const uint32_t want = id << kRankBits | (ordinal - (uint32_t)__builtin_amdgcn_readlane((int)(upto - v), l));
+      const uint32_t lo = (c0 + (uint32_t)l) << q.chunk_bits[1];
+      const uint4 *const infos = reinterpret_cast<const uint4 *>(q.info[1][L] + lo);
+      for (uint32_t o = 0; o < 1u << q.chunk_bits[1]; o += 512) {
+        const uint4 a = infos[o / 4 + lane], b = infos[o / 4 + 64 + lane];
+        const uint32_t at = a.x == want ? 0 : a.y == want ? 1 : a.z == want ? 2 : a.w == want ? 3 : b.x == want ? 256
+                          : b.y == want ? 257 : b.z == want ? 258 : b.w == want ? 259 : kNoKey;
+        const uint64_t hit = __ballot(at != kNoKey);
+        if (hit) {
+          const int x = __builtin_ctzll(hit);
+          return (int32_t)(lo + o + 4 * (uint32_t)x + (uint32_t)__builtin_amdgcn_readlane((int)at, x));
+        }
+      }
+      return -1;
+    }
+    before = (uint32_t)__builtin_amdgcn_readlane((int)upto, 63);
+  }
+  return -1;
 }
 
 // A wavefront per anchor looks its ordinal up, four to a workgroup or, up to kOneEach anchors, one.  With too many distinct
-// keys for lists an anchor is searched for by itself: by its workgroup where that has no other, else by its wavefront.
+// keys for numbers an anchor is searched for by itself: by its workgroup where that has no other, else by its wavefront.
 // 1,000 anchors over 65,536 operators 302 us a call with a workgroup each, 711 with a wavefront each; 4,000 over 18,464
-// operators 180 and 255, 8,001 260 and 296, 20,000 488 and 478.  Where there are lists a workgroup each costs its launch:
+// operators 180 and 255, 8,001 260 and 296, 20,000 488 and 478.  Where there are numbers a workgroup each costs its launch:
 // 8,001 anchors 227 us against 222, 2,048 nothing to be seen.
 constexpr uint32_t kOneEach = 4096;
 
-__global__ __launch_bounds__(256) void ss_lookup_kernel(AnchorArgs g, KeyLists q, uint32_t per) {
+__global__ __launch_bounds__(256) void ss_lookup_kernel(AnchorArgs g, KeyTable q, uint32_t per) {
   __shared__ AnchorShared sh;
-  const bool listed = q.n_used[0] + q.n_used[1] + q.n_used[2] <= q.max_lists;
+  const bool listed = q.n_used[0] + q.n_used[1] + q.n_used[2] <= q.max_keys;
   if (!listed && per == 1) {
     search_anchor(g, blockIdx.x, sh);
     return;
@@ -565,17 +588,19 @@ __global__ __launch_bounds__(256) void ss_lookup_kernel(AnchorArgs g, KeyLists q
   const uint32_t w = threadIdx.x >> 6, a = blockIdx.x * per + w;
   if (w >= per || a >= g.k) return;                          // uniform per wavefront
   const uint32_t i = g.anchors[a].ref_op, slot = g.anchors[a].out_slot;
-  int32_t f[3] = {-1, -1, -1}, result = -1;
+  int32_t result = -1;
   uint8_t level = 255;
   if (i < g.n && g.ref[i].op_token != 0) {
     const ss_op_t R = g.ref[i];
     if (listed) {
-#pragma unroll
-      for (int L = 0; L < 3; ++L) {
-        const uint32_t h = q.key_of[L][a], ord = q.rank[L][i];
-        if (ord < q.count[L][h]) f[L] = (int32_t)q.place[L][q.start[L][h] + ord];
+      // a landing at the first level is the rule: the others are looked at only without one
+      for (int L = 0; L < 3 && result < 0; ++L) {
+        int32_t f[3] = {-1, -1, -1};
+        f[0] = look_up(q, i, L);
+        uint8_t unused;
+        result = choose_landing(g.cur, R, slot, f, unused);
+        if (result >= 0) level = (uint8_t)L;
       }
-      result = choose_landing(g.cur, R, slot, f, level);
     } else {
       result = search_alone(g, R, i, slot, level);
     }
@@ -702,7 +727,7 @@ extern "C" int ss_match_sequence(ss_ctx *ctx, const ss_op_t *ref, uint32_t n, co
     // nothing that large is kept pinned.
     const bool mapped = in_bytes <= (4u << 20);
     const uint64_t pairs = (uint64_t)k * ((uint64_t)n + m);
-    const bool listed = search && pairs > (1ull << 24);        // 10 us of comparing; the lists take 20 us
+    const bool listed = search && (pairs > kManyPairs || (uint64_t)n + m >= kLongSearch);
     const uint32_t len = n > m ? n : m, wgs = std::min(256u, std::max(1u, (len + 255) / 256));
     const uint32_t out_wgs = (k + 255) / 256;
     // table of the injectivity pass: a power of two of at least 2k slots
@@ -719,15 +744,17 @@ extern "C" int ss_match_sequence(ss_ctx *ctx, const ss_op_t *ref, uint32_t n, co
     const size_t o_hist = take(hist ? 2 * (size_t)kTokenLimit * 4 + 256 : 0);
     size_t o_rep[3];
     for (size_t &o : o_rep) o = take(listed ? slots * 4 : 0);
-    const size_t o_n_used = take(listed ? 6 * 4 : 0), zeros_end = off;
-    size_t o_used[3], o_start[3], o_count[3], o_key[3], o_rank[3], o_place[3];
-    for (int L = 0; L < 3; ++L) {
-      o_used[L] = take(listed ? (size_t)k * 4 : 0);
-      o_start[L] = take(listed ? slots * 4 : 0);
-      o_count[L] = take(listed ? slots * 4 : 0);
-      o_key[L] = take(listed ? (size_t)k * 4 : 0);
-      o_rank[L] = take(listed ? (size_t)n * 4 : 0);
-      o_place[L] = take(listed ? (size_t)m * 4 : 0);
+    size_t o_key[3], o_info[2][3], o_count[2];
+    for (size_t &o : o_key) o = take(listed ? slots * 16 : 0);
+    const size_t o_n_used = take(listed ? 3 * 4 : 0), zeros_end = off;
+    const uint32_t max_keys = (uint32_t)std::min<uint64_t>(kMaxKeys, 3ull * k), lens[2] = {n, m};
+    uint32_t chunk_bits[2], chunks[2];
+    for (int x = 0; x < 2; ++x) {
+      chunk_bits[x] = 9;                                     // as many operators as a workgroup has threads
+      while (lens[x] > (uint64_t)kMaxChunks << chunk_bits[x]) ++chunk_bits[x];
+      chunks[x] = (uint32_t)(((uint64_t)lens[x] + (1u << chunk_bits[x]) - 1) >> chunk_bits[x]);
+      for (int L = 0; L < 3; ++L) o_info[x][L] = take(listed ? ((size_t)chunks[x] << chunk_bits[x]) * 4 : 0);
+      o_count[x] = take(listed ? (size_t)chunks[x] * max_keys * 4 : 0);
     }
     const size_t ho_ref = htake(mapped ? (size_t)n * op_bytes : 0), ho_cur = htake(mapped ? (size_t)m * op_bytes : 0);
     const size_t ho_anc = htake(mapped ? (size_t)k * sizeof(ss_anchor_t) : 0);
@@ -740,6 +767,7 @@ extern "C" int ss_match_sequence(ss_ctx *ctx, const ss_op_t *ref, uint32_t n, co
     hipStream_t s = ctx->s_aux;
     CosinePart *dpart = (CosinePart *)(hd + ho_part);
     PrepArgs p = {};
+    bool split = false;
     p.n = n; p.m = m; p.k = search ? k : 0;
     p.cosine = !hist;
     p.ones = (uint4 *)(d + o_ones);
@@ -747,14 +775,38 @@ extern "C" int ss_match_sequence(ss_ctx *ctx, const ss_op_t *ref, uint32_t n, co
     p.zeros = (uint4 *)(d + o_hist);
     p.n_zeros = (uint32_t)((zeros_end - o_hist) / 16);
     p.part = dpart;
+    // the call's last kernel tells the host, unless copies follow it
+    ss_done done = search && !mapped ? ss_done{} : ss_next_done(ctx);
+    auto launch_prep = [&](const PrepArgs &a) -> uint32_t {
+      const uint32_t longest = std::max(a.n, a.m), clears = std::max(a.n_ones, a.n_zeros);
+      const uint32_t for_ops = std::min(256u, std::max(1u, (longest + 255) / 256));
+      const uint32_t grid = std::max(for_ops, std::min(kMaxParts, clears / 2048));
+      PrepArgs x = a;
+      if (x.done.flag) x.done.wgs = grid;
+      if (mapped && longest > kTogetherMapped) hipLaunchKernelGGL(ss_prep_kernel<false>, dim3(grid), dim3(256), 0, s, x);
+      else hipLaunchKernelGGL(ss_prep_kernel<true>, dim3(grid), dim3(256), 0, s, x);
+      return grid;
+    };
     if (mapped) {
       if (n) std::memcpy(h + ho_ref, ref, (size_t)n * op_bytes);
-      if (m) std::memcpy(h + ho_cur, cur, (size_t)m * op_bytes);
       if (k) std::memcpy(h + ho_anc, anchors, (size_t)k * sizeof(ss_anchor_t));
+      if (!hist && (size_t)std::min(n, m) * op_bytes >= kSplitBytes) {
+        PrepArgs q = p;                                      // the reference comes while the host copies the other sequence
+        q.ref = (const ss_op_t *)(hd + ho_ref); q.dref = (ss_op_t *)(d + o_ref);
+        q.anchors = (const ss_anchor_t *)(hd + ho_anc);
+        if (search) q.danc = (ss_anchor_t *)(d + o_anc);
+        q.m = q.cosine = 0;
+        launch_prep(q);
+        SS_HIP(hipGetLastError());
+        p.k = p.n_ones = p.n_zeros = 0;
+        split = true;
+      }
+      if (m) std::memcpy(h + ho_cur, cur, (size_t)m * op_bytes);
       p.ref = (const ss_op_t *)(hd + ho_ref); p.dref = (ss_op_t *)(d + o_ref);
       p.cur = (const ss_op_t *)(hd + ho_cur); p.dcur = (ss_op_t *)(d + o_cur);
       p.anchors = (const ss_anchor_t *)(hd + ho_anc);
-      if (search) p.danc = (ss_anchor_t *)(d + o_anc);
+      if (search && !split) p.danc = (ss_anchor_t *)(d + o_anc);
+      if (split) { p.ref = (const ss_op_t *)(d + o_ref); p.dref = nullptr; }
     } else {
       if (n) SS_HIP(hipMemcpyAsync(d + o_ref, ref, (size_t)n * op_bytes, hipMemcpyHostToDevice, s));
       if (m) SS_HIP(hipMemcpyAsync(d + o_cur, cur, (size_t)m * op_bytes, hipMemcpyHostToDevice, s));
@@ -763,15 +815,9 @@ extern "C" int ss_match_sequence(ss_ctx *ctx, const ss_op_t *ref, uint32_t n, co
       p.cur = (const ss_op_t *)(d + o_cur);
       if (hist) p.n = p.m = 0;                               // nothing to read them for
     }
-    const uint32_t clears = std::max(p.n_ones, p.n_zeros);
-    const uint32_t prep_wgs = std::max(wgs, std::min(kMaxParts, clears / 2048));
-    // the call's last kernel tells the host, unless copies follow it
-    ss_done done = search && !mapped ? ss_done{} : ss_next_done(ctx);
-    done.wgs = search ? out_wgs : hist ? 256 : prep_wgs;
+    done.wgs = search ? out_wgs : 256;                       // launch_prep sets its own
     if (!search && !hist) p.done = done;
-    if (mapped && len > kTogetherMapped) hipLaunchKernelGGL(ss_prep_kernel<false>, dim3(prep_wgs), dim3(256), 0, s, p);
-    else hipLaunchKernelGGL(ss_prep_kernel<true>, dim3(prep_wgs), dim3(256), 0, s, p);
-    const uint32_t parts = hist ? 256 : prep_wgs;
+    const uint32_t prep_wgs = launch_prep(p), parts = hist ? 256 : prep_wgs;
     const ss_op_t *dref = (const ss_op_t *)(d + o_ref), *dcur = (const ss_op_t *)(d + o_cur);
     if (hist) {
       uint32_t *h_ref = (uint32_t *)(d + o_hist), *h_cur = h_ref + kTokenLimit, *bad = h_cur + kTokenLimit;
@@ -785,22 +831,24 @@ extern "C" int ss_match_sequence(ss_ctx *ctx, const ss_op_t *ref, uint32_t n, co
                       (uint32_t *)(d + o_slot),
                       {(unsigned long long *)(d + o_ones), (uint32_t *)(d + o_owner), (uint32_t)(slots - 1), 64u - bits}};
       if (listed) {
-        KeyLists q = {};
+        KeyTable q = {};
         for (int L = 0; L < 3; ++L) {
           q.rep[L] = (uint32_t *)(d + o_rep[L]);
-          q.used[L] = (uint32_t *)(d + o_used[L]);
-          q.start[L] = (uint32_t *)(d + o_start[L]);
-          q.count[L] = (uint32_t *)(d + o_count[L]);
-          q.key_of[L] = (uint32_t *)(d + o_key[L]);
-          q.rank[L] = (uint32_t *)(d + o_rank[L]);
-          q.place[L] = (uint32_t *)(d + o_place[L]);
+          q.key[L] = (uint4 *)(d + o_key[L]);
+          for (int x = 0; x < 2; ++x) q.info[x][L] = (uint32_t *)(d + o_info[x][L]);
+        }
+        for (int x = 0; x < 2; ++x) {
+          q.chunk_bits[x] = chunk_bits[x];
+          q.chunks[x] = chunks[x];
+          q.count[x] = (uint32_t *)(d + o_count[x]);
         }
         q.n_used = (uint32_t *)(d + o_n_used);
         q.mask = (uint32_t)(slots - 1);
         q.shift = 64u - bits;
-        q.max_lists = std::min(kMaxLists, k / 2);
+        q.max_keys = max_keys;
         hipLaunchKernelGGL(ss_keys_kernel, dim3((k + 255) / 256, 3), dim3(256), 0, s, g, q);
-        hipLaunchKernelGGL(ss_lists_kernel, dim3(512), dim3(1024), 0, s, g, q);
+        if (chunks[0] + chunks[1])
+          hipLaunchKernelGGL(ss_chunks_kernel, dim3(chunks[0] + chunks[1], 3), dim3(kChunkThreads), 0, s, g, q);
         const uint32_t per = k <= kOneEach ? 1 : 4;
         hipLaunchKernelGGL(ss_lookup_kernel, dim3((k + per - 1) / per), dim3(256), 0, s, g, q, per);
       } else {

@@ -83,23 +83,7 @@ __device__ __forceinline__ int64_t dpp_i64(int64_t v) {
   return (int64_t)(((uint64_t)(uint32_t)hi << 32) | (uint32_t)lo);
 }
 
-// the same over 32 bits, `none` where there is no such lane
-template <int kCtrl, int kRows>
-__device__ __forceinline__ uint32_t dpp_u32(uint32_t v, uint32_t none) {
-  return (uint32_t)__builtin_amdgcn_update_dpp((int)none, (int)v, kCtrl, kRows, 0xF, false);
-}
-
 // inclusive prefix sum over the 64 lanes: within rows of 16, then the rows' last lanes handed on
-__device__ __forceinline__ uint32_t wave_scan_u32(uint32_t v) {
-  v += dpp_u32<0x111, 0xF>(v, 0);
-  v += dpp_u32<0x112, 0xF>(v, 0);
-  v += dpp_u32<0x114, 0xF>(v, 0);
-  v += dpp_u32<0x118, 0xF>(v, 0);
-  v += dpp_u32<0x142, 0xA>(v, 0);
-  v += dpp_u32<0x143, 0xC>(v, 0);
-  return v;
-}
-
 __device__ __forceinline__ int64_t wave_scan(int64_t v) {
   v += dpp_i64<0x111, 0xF>(v);
   v += dpp_i64<0x112, 0xF>(v);

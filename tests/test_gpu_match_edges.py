@@ -1,5 +1,5 @@
-"""GPU parity of the sequence matcher where its kernels change form: a workgroup per anchor, lists per distinct key, too
-many distinct keys for lists, inputs through pinned memory or by copy, histograms with tokens in and beyond LDS.  Exact
+"""GPU parity of the sequence matcher where its kernels change form: a workgroup per anchor, numbered keys, too
+many distinct keys for that, inputs through pinned memory or by copy, histograms with tokens in and beyond LDS.  Exact
 comparison with the definition in plain Python, itself checked against the oracle."""
 import numpy as np
 import pytest
@@ -108,6 +108,20 @@ def test_forms(P, ctx, n, k, tokens, stacks):                     # noqa: F811
     check(P, ctx, ref, perturbed(rng, ref), anchors(rng, n, k))
     check(P, ctx, ref, ref[:0], anchors(rng, n, k))
     check(P, ctx, perturbed(rng, ref), ref, anchors(rng, n, 7))
+
+
+@pytest.mark.parametrize("n,k,tokens,stacks", [
+    (1535, 12000, 1, 1), (1536, 12000, 2, 1), (1537, 12000, 30, 60),       # whole chunks of 512, one key and many
+    (8191, 2100, 3, 2), (8192, 2100, 33, 1), (8193, 4000, 9, 30),           # two passes or one over the sequences, keys' bits
+    (33000, 600, 25, 4), (131073, 300, 9, 1), (270000, 300, 9, 1),          # more than 64 chunks, chunks of 1,024 and 2,048
+])
+def test_numbered_chunks(P, ctx, n, k, tokens, stacks):           # noqa: F811
+    rng = np.random.default_rng([n, k, tokens, 1])
+    ref = sequence(rng, n, tokens, stacks)
+    cur = perturbed(rng, ref)
+    cur = np.concatenate([cur, ref[:n - len(cur)]])                 # of the same length
+    check(P, ctx, ref, cur, anchors(rng, n, k))
+    check(P, ctx, ref, cur[:n // 3], anchors(rng, n, k))
 
 
 @pytest.mark.parametrize("m", [0, 1])
