@@ -167,6 +167,7 @@ struct ss_ctx {
   void *d_board = nullptr;          // what the workgroups of a long scan tell each other (ss_scan.hip)
   uint32_t *h_done = nullptr, *d_done = nullptr;            // pinned word (behind ops) and its device address (ss_done)
   uint32_t *d_told = nullptr;       // device (in front of d_board)
+  int pool_board = -1;              // which of the pool's boards, -1: its own
   uint32_t done_count = 0;
   uint32_t scan_wait_ticks = 0;     // limit of their waits, 0 = the usual one
   // scratch for scan / match (device + pinned mirrors), grown on demand
@@ -251,7 +252,8 @@ int ss_scratch_reserve(ss_ctx *ctx, size_t dev_bytes, size_t host_bytes);
 // address of the static scratch array of ss_timeline_scan_static on the context's device; the context's own board, once s_aux
 // is there (ss_scan.hip)
 int ss_scan_static_init(ss_ctx *ctx);
-int ss_scan_board_init(ss_ctx *ctx);
+int ss_scan_board_take(ss_ctx *ctx);
+void ss_scan_board_give(ss_ctx *ctx);
 
 // internal entry used by the greedy generator: timing + schedule without loading it
 struct ss_applied {

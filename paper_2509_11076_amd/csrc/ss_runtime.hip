@@ -464,7 +464,7 @@ extern "C" int ss_create(ss_ctx **out, const ss_config_t *cfg_in) {
     // queues (4 per process here) with another - a stream that shares its queue with the stream of the
     // copy-engine transfers stands still for the length of every transfer.
     ctx->s_aux = ctx->s_in[0];
-    if (rc == SS_OK) rc = ss_scan_board_init(ctx);
+    if (rc == SS_OK) rc = ss_scan_board_take(ctx);
     if (rc == SS_OK && (cfg.copy_path == SS_PATH_STAGED || cfg.copy_path_in == SS_PATH_STAGED)) {
       // gathers / scatters and direct batches of a direction share that direction's one stream; the copy-engine
       // transfers out of and into the rings share a third
@@ -580,7 +580,7 @@ extern "C" int ss_destroy(ss_ctx *ctx) {
   if (ctx->staging) (void)hipHostFree(ctx->staging);
   if (ctx->ops) (void)hipHostFree(ctx->ops);
   if (ctx->events) (void)hipHostFree(ctx->events);
-  if (ctx->d_told) (void)hipFree(ctx->d_told);
+  ss_scan_board_give(ctx);
   if (ctx->d_scratch) (void)hipFree(ctx->d_scratch);
   if (ctx->h_scratch) (void)hipHostFree(ctx->h_scratch);
   delete ctx;

@@ -22,6 +22,7 @@
 // and timeline left to one workgroup 1,084 us; 1,048,574 + 20,014 events, 65,536 operators: 44 us, was 221).
 #include <algorithm>
 #include <cstring>
+#include <mutex>
 
 #include "ss_internal.h"
 
@@ -1108,7 +1109,11 @@ constexpr uint64_t kStaticMaxEvents = 262144;
 constexpr size_t kBoardBytes = (sizeof(TileBoard) + 255) / 256 * 256;
 constexpr size_t kStaticBytes = kBoardBytes + 2 * (kStaticMaxOps + 1) * sizeof(OpAt) + 2 * kStaticMaxOps * 8 +
                                 kStaticMaxEvents * 12 + 8 * 256;
-static __device__ __align__(256) uint8_t scratch[kStaticBytes];          // starts as zeros: so does the board at its front
+// Contexts take their boards from a pool behind it (one more than it holds allocates its own): an allocation and a clear for
+// each made preparing a 7B alignment 853 -> 977 us.
+constexpr int kPoolBoards = 32;
+constexpr size_t kToldBytes = 256, kOwnBoard = kToldBytes + kBoardBytes, kPoolAt = (kStaticBytes + 255) / 256 * 256;
+static __device__ __align__(256) uint8_t scratch[kPoolAt + kPoolBoards * kOwnBoard];          // starts as zeros: so do the boards
 
 // Address of `scratch` on each device (the name itself is only a host-side handle): resolved once
 // per device, with that device current.
@@ -1139,13 +1144,46 @@ int ss_scan_static_init(ss_ctx *ctx) {
   return rc;
 }
 
-int ss_scan_board_init(ss_ctx *ctx) {
-  constexpr size_t kBoardAt = 256;
-  SS_HIP(hipMalloc((void **)&ctx->d_told, kBoardAt + sizeof(TileBoard)));
-  ctx->d_board = (uint8_t *)ctx->d_told + kBoardAt;
-  ss_launch_fill(ctx->s_aux, (uint8_t *)ctx->d_told, kBoardAt + sizeof(TileBoard), 0);     // their kernels run there too
-  SS_HIP(hipGetLastError());
+static std::mutex g_boards_mu;
+static uint32_t g_boards_taken[kMaxDevices];
+static_assert(kPoolBoards <= 32, "a bit for each");
+
+int ss_scan_board_take(ss_ctx *ctx) {
+  uint8_t *base = nullptr;
+  hipError_t e;
+  const int rc = static_scratch_ptr(ctx->device, &base, &e);
+  if (rc == SS_E_HIP) SS_HIP(e);
+  if (rc != SS_OK) return rc;
+  {
+    std::lock_guard<std::mutex> lock(g_boards_mu);
+    uint32_t &taken = g_boards_taken[ctx->device];
+    for (int i = 0; i < kPoolBoards && ctx->pool_board < 0; ++i)
+      if (!(taken >> i & 1u)) {
+        taken |= 1u << i;
+        ctx->pool_board = i;
+      }
+  }
+  if (ctx->pool_board >= 0) {
+    ctx->d_told = (uint32_t *)(base + kPoolAt + (size_t)ctx->pool_board * kOwnBoard);
+  } else {
+    SS_HIP(hipMalloc((void **)&ctx->d_told, kOwnBoard));
+    ss_launch_fill(ctx->s_aux, (uint8_t *)ctx->d_told, kOwnBoard, 0);       // their kernels run there too
+    SS_HIP(hipGetLastError());
+  }
+  ctx->d_board = (uint8_t *)ctx->d_told + kToldBytes;
   return SS_OK;
+}
+
+// Once nothing of the context runs any more.  The next one takes the board as it is (see TileBoard).
+void ss_scan_board_give(ss_ctx *ctx) {
+  if (ctx->pool_board >= 0) {
+    std::lock_guard<std::mutex> lock(g_boards_mu);
+    g_boards_taken[ctx->device] &= ~(1u << ctx->pool_board);
+  } else if (ctx->d_told) {
+    (void)hipFree(ctx->d_told);
+  }
+  ctx->pool_board = -1;
+  ctx->d_told = nullptr;
 }
 
 extern "C" int ss_timeline_scan_static(ss_ctx *ctx, void *stream, const ss_event_t *d_ev, uint64_t n_ev,
