@@ -233,6 +233,7 @@ struct AnchorArgs {
 struct AnchorShared {
   uint32_t in_ref[4][3], in_cur[4][3];
   int32_t found[3];
+  uint32_t lands[3];           // ss_anchor_kernel in registers: the found operator has the slot and the data type
 };
 
 // The landing of anchor a, found by the whole workgroup.  Each wavefront counts, over its quarter of the reference up to
@@ -316,11 +317,89 @@ __device__ __forceinline__ void search_anchor(const AnchorArgs &g, uint32_t a, A
   }
 }
 
-// One workgroup per anchor.  Bound by the latency of the walks: 480 anchors of 1,154 operators 8.3 us, claims included; a
-// wavefront per anchor, all of both sequences in one walk, took 13.0 us and the claims 3.1 us in a launch of their own.
+// The same for sequences of up to kRegOps operators, which the workgroup holds in registers: they are loaded while the anchor
+// and its operator are, counted, walked and landed on without another load.
+constexpr uint32_t kPerLane = 8, kRegOps = 256 * kPerLane;
+
+__device__ __forceinline__ void search_in_registers(const AnchorArgs &g, uint32_t a, AnchorShared &sh) {
+  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+  const uint32_t rq = (g.n + 255) / 256 * 64, cq = (g.m + 255) / 256 * 64;     // quarters, whole strips of 64
+  const uint32_t r_lo = w * rq, c_lo = w * cq;
+  ss_op_t r[kPerLane], c[kPerLane];
+#pragma unroll
+  for (uint32_t u = 0; u < kPerLane; ++u) {
+    r[u] = c[u] = ss_op_t{0, 0, 0, 0};                   // padding: never the anchor's token
+    const uint32_t i = r_lo + 64 * u + lane, j = c_lo + 64 * u + lane;
+    if (64 * u < rq && i < g.n) r[u] = g.ref[i];
+    if (64 * u < cq && j < g.m) c[u] = g.cur[j];
+  }
+  const uint32_t i = g.anchors[a].ref_op, slot = g.anchors[a].out_slot;
+  ss_op_t R = {0, 0, 0, 0};
+  if (i < g.n) R = g.ref[i];
+  if (R.op_token == 0) {                                 // uniform
+    if (threadIdx.x == 0) { g.land[a] = -1; g.lvl[a] = 255; }
+    return;
+  }
+  uint32_t rn[3] = {0, 0, 0}, cn[3] = {0, 0, 0};
+#pragma unroll
+  for (uint32_t u = 0; u < kPerLane; ++u) {
+    bool e[3], f[3];
+    same_key(r[u], R, e[0], e[1], e[2]);
+    same_key(c[u], R, f[0], f[1], f[2]);
+    const bool before = r_lo + 64 * u + lane < i;
+#pragma unroll
+    for (int L = 0; L < 3; ++L) {
+      rn[L] += __popcll(__ballot(e[L] & before));
+      cn[L] += __popcll(__ballot(f[L]));
+    }
+  }
+  if (lane < 3) {
+    sh.in_ref[w][lane] = lane == 0 ? rn[0] : lane == 1 ? rn[1] : rn[2];
+    sh.in_cur[w][lane] = lane == 0 ? cn[0] : lane == 1 ? cn[1] : cn[2];
+  }
+  if (threadIdx.x < 3) { sh.found[threadIdx.x] = -1; sh.lands[threadIdx.x] = 0; }
+  __syncthreads();
+#pragma unroll
+  for (int L = 0; L < 3; ++L) {
+    uint32_t ord = sh.in_ref[0][L] + sh.in_ref[1][L] + sh.in_ref[2][L] + sh.in_ref[3][L], before = 0;
+    for (int v = 0; v < w; ++v) before += sh.in_cur[v][L];
+    if (ord < before || ord >= before + cn[L]) continue; // uniform: another wavefront's, or nowhere
+    uint32_t need = ord - before;
+#pragma unroll
+    for (uint32_t u = 0; u < kPerLane; ++u) {
+      bool f[3];
+      same_key(c[u], R, f[0], f[1], f[2]);
+      const uint64_t b = __ballot(f[L]);
+      const uint32_t pc = __popcll(b);
+      if (need < pc) {
+        if (lane == nth_set_bit(b, need, lane)) {
+          sh.found[L] = (int32_t)(c_lo + 64 * u + lane);
+          sh.lands[L] = slot < c[u].n_out && (c[u].sig & 0xFFu) == (R.sig & 0xFFu);
+        }
+        break;
+      }
+      need -= pc;
+    }
+  }
+  __syncthreads();
+  if (threadIdx.x) return;
+  int32_t j = -1;
+  uint8_t level = 255;
+#pragma unroll
+  for (int L = 2; L >= 0; --L)
+    if (sh.lands[L]) { j = sh.found[L]; level = (uint8_t)L; }
+  g.land[a] = j;
+  g.lvl[a] = level;
+  if (j >= 0) g.slot_of[a] = claim(g.table, j, slot, a);
+}
+
+// One workgroup per anchor.  Bound by the latency of the loads and walks: 480 anchors of 1,154 operators 6.1 us in registers,
+// claims included, 8.3 reading them as they are counted and walked; a wavefront per anchor, all of both sequences in one walk,
+// took 13.0 us and the claims 3.1 us in a launch of their own.
 __global__ __launch_bounds__(256) void ss_anchor_kernel(AnchorArgs g) {
   __shared__ AnchorShared sh;
-  search_anchor(g, blockIdx.x, sh);
+  if (g.n <= kRegOps && g.m <= kRegOps) search_in_registers(g, blockIdx.x, sh);
+  else search_anchor(g, blockIdx.x, sh);
 }
 
 // The landing of anchor a, found by one wavefront: all of both sequences in one walk.
