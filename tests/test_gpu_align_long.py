@@ -115,3 +115,22 @@ def test_strips_that_give_up_waiting_are_started_one_by_one(P, ctx, n, m, alpha)
     assert np.array_equal(got["new_idx"], again["new_idx"]) and np.array_equal(got["level"], again["level"])
     assert np.array_equal(P.ss_align_sequence(ctx, x, y)["ref_to_cur"], want)
     assert lib.ss_align_wait_limit(ctx, usual) == after
+
+
+@pytest.mark.parametrize("n,m,alpha", [
+    (1, 1, 1), (4095, 1, 3), (4064, 32, 4), (1, 33, 2), (31, 64, 5), (2048, 2048, 40), (2047, 2049, 40), (2049, 2048, 40),
+    (2080, 2016, 30), (2048, 2017, 30), (1000, 1100, 254), (1000, 1100, 255), (1000, 1100, 256), (1500, 2000, 1500),
+])
+def test_short_sequences_in_one_workgroup(P, n, m, alpha):           # noqa: F811
+    """one strip and both sequences' keys in one workgroup, or just not; lanes with and without a word; ids of 16 and of 32
+    bits, also where a new context's scratch turns out too small for the masks"""
+    rng = np.random.default_rng([n, m, alpha, 2])
+    ref, cur = rng.integers(0, alpha, n), rng.integers(0, alpha, m)
+    cur[:min(m, alpha)] = np.arange(min(m, alpha))                   # every key is there
+    want = pairing(ref.tolist(), cur.tolist())
+    c = P.ss_create(P.ss_config_default())
+    for _ in range(3):
+        lib = P.ss_align_sequence(c, ops_arr(ref), ops_arr(cur))
+        assert np.array_equal(lib["ref_to_cur"], want)
+        assert lib["n_keys"] == min(m, alpha)
+    P.ss_destroy(c)
