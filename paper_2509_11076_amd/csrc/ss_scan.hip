@@ -510,7 +510,7 @@ __device__ __forceinline__ void scan_wg(const ScanArgs &a, OpAt *at, int64_t *po
 // and 3 for 1,734).  An operator's OpAt entry is written by the event that starts it; those of operators without events
 // are copied from the next operator that has some, found in a bit map (each gap filled by the wavefront that met it: 1.6
 // and 2.5 us, 7 with 90 events over 700 operators).  The timeline is put together in LDS, so that it leaves in whole lines.
-// 124 + 24 events over 66 operators: 4.3 us, before 6.0; 1,398 + 336 over 700 from and to pinned memory 8.7, before 12.1.
+// 124 + 24 events over 66 operators: 3.9 us, before 6.0; 1,398 + 336 over 700 from and to pinned memory 9.4, before 12.1.
 
 constexpr uint32_t kLdsOps = 2900;                       // OpAt tables of more don't fit LDS
 constexpr uint32_t kHeadWords = (kLdsOps + 1 + 31) / 32;
@@ -652,13 +652,30 @@ __device__ __forceinline__ void scan_short(const ScanArgs &a, uint8_t *lds, uint
     __syncthreads();
     final_total += n ? sh.sums.tot_sp : 0;
   } else {
+    // the words of a map that hold a bit, for where a search leaves its word (words looked through one by one: 1,000 events
+    // of the trace and none of the policy over 2,900 operators 37 us, so 9.7)
+    static_assert(kHeadWords <= 128, "two masks a map");
+    uint64_t some[2][2];
+#pragma unroll
+    for (int l = 0; l < 2; ++l)
+#pragma unroll
+      for (uint32_t h = 0; h < 2; ++h) some[l][h] = __ballot(h * 64 + lane < kHeadWords && sh.head[l][min(h * 64 + lane, kHeadWords - 1)]);
     for (uint32_t i = tid; i < 2 * n; i += T) {
       const uint32_t l = i >= n, t = i - (l ? n : 0);
       uint32_t word = t / 32, bits = sh.head[l][word] >> (t % 32);
       if (bits & 1u) continue;
       uint32_t next = t;
-      if (!bits) {
-        do bits = sh.head[l][++word]; while (!bits);     // the entry of n is always there
+      if (!bits) {                                       // the entry of n is always there
+        const uint64_t lo = l ? some[1][0] : some[0][0], hi = l ? some[1][1] : some[0][1];
+        ++word;
+        const uint64_t here = word < 64 ? lo >> word : 0;
+        if (here) {
+          word += (uint32_t)__builtin_ctzll(here);
+        } else {
+          word = max(word, 64u);
+          word += (uint32_t)__builtin_ctzll(hi >> (word - 64));
+        }
+        bits = sh.head[l][word];
         next = word * 32;
       }
       next += (uint32_t)__builtin_ctz(bits);
@@ -703,8 +720,12 @@ __global__ __launch_bounds__(T) void ss_scan_short_batch_kernel(const ScanArgs *
 // lanes and events to a lane for two lists of that many
 struct ShortForm { int T, K; };
 
-static ShortForm short_form(uint64_t n_ev, uint64_t n_pe) {
-  auto fits = [&](uint64_t T, uint64_t K) { return ss_align_up(n_ev, 64 * K) + ss_align_up(n_pe, 64 * K) <= T * K; };
+// Where operators outnumber the lanes that the events need by much, filling the gaps is the work, and more lanes do it sooner: 4
+// events over 2,900 operators 9.3 us with 1,024 lanes (with 256, which looked through the map word by word, 40).
+static ShortForm short_form(uint64_t n_ev, uint64_t n_pe, uint32_t n_ops) {
+  auto fits = [&](uint64_t T, uint64_t K) {
+    return n_ops <= 4 * T && ss_align_up(n_ev, 64 * K) + ss_align_up(n_pe, 64 * K) <= T * K;
+  };
   if (fits(256, 1)) return {256, 1};
   if (fits(256, 4)) return {256, 4};
   if (fits(512, 4)) return {512, 4};
@@ -1042,7 +1063,7 @@ uint32_t tile_events(uint64_t n, uint32_t n_ops, int per_lane) {
 // call for 3,500 + 500 events over 2,500 operators 9.3 us, with a timeline 11.0, the two launches of the other 11 at least.
 bool is_short(uint64_t n_ev, uint64_t n_pe, uint32_t n_ops, bool timeline) {
   if (n_ev + n_pe > kSmallEvents || n_ops > kLdsOps) return false;
-  const ShortForm f = short_form(n_ev, n_pe);
+  const ShortForm f = short_form(n_ev, n_pe, n_ops);
   return f.T && short_lds(f.T, f.K, n_ops, n_ev + n_pe, timeline) <= kShortLds;
 }
 
@@ -1070,7 +1091,7 @@ size_t scan_scratch(ScanArgs *a, uint8_t *d, uint64_t n_ev, uint64_t n_pe, uint6
 
 void launch_scan(hipStream_t s, ScanArgs &a) {
   if (is_short(a.n_ev, a.n_pe, a.n_ops, a.want_timeline)) {
-    const ShortForm f = short_form(a.n_ev, a.n_pe);
+    const ShortForm f = short_form(a.n_ev, a.n_pe, a.n_ops);
     const size_t bytes = short_lds(f.T, f.K, a.n_ops, a.n_ev + a.n_pe, a.want_timeline);
     const uint32_t tl_at = (uint32_t)short_tables(f.T, f.K, a.n_ops);
 #define SS_LAUNCH(T, K) hipLaunchKernelGGL((ss_scan_short_kernel<T, K>), dim3(1), dim3(T), bytes, s, a, tl_at)
@@ -1275,7 +1296,7 @@ extern "C" int ss_timeline_scan_batch(ss_ctx *ctx, const ss_event_t *ev, uint64_
     ShortForm f = {0, 0};                               // one for all
     bool all_short = lds;
     for (uint32_t c = 0; c < k && all_short; ++c) {
-      const ShortForm g = short_form(n_ev, ha[c].n_pe);
+      const ShortForm g = short_form(n_ev, ha[c].n_pe, n_ops);
       all_short = g.T && n_ev + ha[c].n_pe <= kSmallEvents && short_lds(g.T, g.K, n_ops, 0, false) <= kShortLds;
       if (g.T * g.K > f.T * f.K) f = g;
     }

@@ -158,3 +158,16 @@ def test_tiles_take_up_the_sums_before_them(P, ctx, n_ev, n_pe, n_ops):         
     ora = both_ways(P, ctx, ev, pe, n_ops, 5, 1 << 41)
     lib.ss_scan_wait_limit(ctx, 1)
     assert_scan_equal(P.ss_timeline_scan(ctx, ev, pe, n_ops, 5, 1 << 41, want_timeline=True), ora)
+
+
+@pytest.mark.parametrize("n_ops", [32, 1024, 1025, 2046, 2047, 2048, 2049, 2900])
+@pytest.mark.parametrize("at", [(0,), (0.5,), (1,), (0, 1), (0.3, 0.7)])
+def test_wide_gaps_in_one_workgroup(P, ctx, n_ops, at):           # noqa: F811
+    """a few events of a few operators, far apart, at the ends, beside an empty list and beside one another"""
+    rng = np.random.default_rng([n_ops, len(at)])
+    places = np.asarray([int(x * (n_ops - 1)) for x in at])
+    ev = events(rng, 2 * len(at), len(at))
+    ev["op_idx"] = np.sort(places[ev["op_idx"]])
+    other = events(rng, 3, n_ops)
+    for a, b in ((ev, other[:0]), (other[:0], ev), (ev, other)):
+        both_ways(P, ctx, a, b, n_ops, 3, 1 << 40)
