@@ -171,3 +171,13 @@ def test_wide_gaps_in_one_workgroup(P, ctx, n_ops, at):           # noqa: F811
     other = events(rng, 3, n_ops)
     for a, b in ((ev, other[:0]), (other[:0], ev), (ev, other)):
         both_ways(P, ctx, a, b, n_ops, 3, 1 << 40)
+
+
+@pytest.mark.parametrize("n_ev,n_pe,n_ops", [(1000, 1, 65536), (9000, 8, 40000), (8, 9000, 40000)])
+def test_one_list_out_of_order_beside_a_sparse_one(P, ctx, n_ev, n_pe, n_ops):       # noqa: F811
+    """gaps needn't be filled then, and whether they are the operators' sums are those of the lists in order"""
+    rng = np.random.default_rng([n_ev, n_pe, n_ops, 2])
+    ev, pe = events(rng, n_ev, n_ops), events(rng, n_pe, n_ops)
+    ora = oracle.timeline_scan(ev, pe, n_ops, 0, 1 << 40)
+    for a, b in ((ev[::-1].copy(), pe), (ev, pe[::-1].copy())):
+        assert_scan_equal(P.ss_timeline_scan(ctx, a, b, n_ops, 0, 1 << 40), ora, timeline=False)
