@@ -894,7 +894,7 @@ extern "C" int ss_match_sequence(ss_ctx *ctx, const ss_op_t *ref, uint32_t n, co
       p.cur = (const ss_op_t *)(d + o_cur);
       if (hist) p.n = p.m = 0;                               // nothing to read them for
     }
-    done.wgs = search ? out_wgs : 256;                       // launch_prep sets its own
+    ss_told_by(done, search ? out_wgs : 256);                // launch_prep sets its own
     if (!search && !hist) p.done = done;
     const uint32_t prep_wgs = launch_prep(p), parts = hist ? 256 : prep_wgs;
     const ss_op_t *dref = (const ss_op_t *)(d + o_ref), *dcur = (const ss_op_t *)(d + o_cur);

@@ -607,7 +607,7 @@ ss_done ss_next_done(ss_ctx *ctx) {
 // A look takes a few ns; after a millisecond, with the GPU busy with other work, the thread leaves the core to others.
 int ss_wait_done(ss_ctx *ctx, const ss_done &d) {
   const auto until = std::chrono::steady_clock::now() + std::chrono::milliseconds(1);
-  do {
+  if (d.flag) do {
     for (int i = 0; i < 64; ++i) {
       if (__atomic_load_n(ctx->h_done, __ATOMIC_ACQUIRE) == d.value) return SS_OK;
       __builtin_ia32_pause();

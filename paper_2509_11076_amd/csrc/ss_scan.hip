@@ -1128,7 +1128,7 @@ void launch_scan(hipStream_t s, ScanArgs &a) {
   if (per_lane == 2) hipLaunchKernelGGL((ss_scan_running_kernel<2, true>), dim3(tiles), dim3(kTileThreads), 0, s, a);
   else if (per_lane == 4) hipLaunchKernelGGL((ss_scan_running_kernel<4, true>), dim3(tiles), dim3(kTileThreads), 0, s, a);
   else hipLaunchKernelGGL((ss_scan_running_kernel<8, false>), dim3(tiles), dim3(kTileThreads), 0, s, a);
-  a.done.wgs = op_wgs + ev_wgs;
+  ss_told_by(a.done, op_wgs + ev_wgs);
   hipLaunchKernelGGL(ss_scan_finish_kernel, dim3(op_wgs + ev_wgs), dim3(kThreads), 0, s, a, op_wgs);
 }
 
@@ -1288,7 +1288,7 @@ extern "C" int ss_timeline_scan_batch(ss_ctx *ctx, const ss_event_t *ev, uint64_
     }
     const uint8_t *const in = mapped ? hd : d;
     ss_done done = ss_next_done(ctx);
-    done.wgs = k;
+    ss_told_by(done, k);
     ScanArgs *ha = (ScanArgs *)h;                       // pinned, read and written by the kernel: arguments, results
     for (uint32_t c = 0; c < k; ++c) {
       uint8_t *w = d + o_work + (size_t)c * per_scan;
