@@ -1064,14 +1064,34 @@ __global__ __launch_bounds__(kThreads) void ss_scan_finish_kernel(ScanArgs a, ui
 // Where operators outnumber the events, filling the gaps between them is the work (a wavefront fills gaps above kAlone one
 // after the other), and few events to a tile spread it: 60,000 operators with 40,000 events and 2,000 of the policy
 // 82 -> 40 us, with 6,000 and 200 66 -> 41.
+// A lane that gets two or four loads them once, so there a tile is at most one pass.
 int events_per_lane(uint64_t n) {
   return n <= kMaxTiles * kTileThreads * 2 ? 2 : n <= kMaxTiles * kTileThreads * 4 ? 4 : 8;
 }
 
 uint32_t tile_events(uint64_t n, uint32_t n_ops, int per_lane) {
-  if (n_ops > 2 * n) return (uint32_t)std::max<uint64_t>(8, ss_align_up((n + 255) / 256, 8));
   const uint64_t pass = (uint64_t)kTileThreads * per_lane;
+  if (n_ops > 2 * n) {
+    const uint64_t spread = std::max<uint64_t>(8, ss_align_up((n + 255) / 256, 8));
+    return (uint32_t)(per_lane == 8 ? spread : std::min(spread, pass));
+  }
   return (uint32_t)std::max(pass, ss_align_up((n + kMaxTiles - 1) / kMaxTiles, pass));
+}
+
+struct Tiling {
+  int per_lane;
+  uint32_t tile[2], tiles[2];        // events of a tile, tiles: of the trace's events, of the policy's
+};
+
+Tiling tiling_of(uint64_t n_ev, uint64_t n_pe, uint32_t n_ops) {
+  Tiling t;
+  t.per_lane = events_per_lane(std::max(n_ev, n_pe));
+  for (int l = 0; l < 2; ++l) {
+    const uint64_t n = l ? n_pe : n_ev;
+    t.tile[l] = tile_events(n, n_ops, t.per_lane);
+    t.tiles[l] = (uint32_t)std::max<uint64_t>(1, (n + t.tile[l] - 1) / t.tile[l]);
+  }
+  return t;
 }
 
 // One workgroup takes a trace whose events fit its registers and whose tables fit LDS.  Up to there it is the faster form: a
@@ -1114,12 +1134,13 @@ void launch_scan(hipStream_t s, ScanArgs &a) {
 #undef SS_LAUNCH
     return;
   }
-  const int per_lane = events_per_lane(std::max(a.n_ev, a.n_pe));
-  a.tile[0] = tile_events(a.n_ev, a.n_ops, per_lane);
-  a.tile[1] = tile_events(a.n_pe, a.n_ops, per_lane);
+  const Tiling t = tiling_of(a.n_ev, a.n_pe, a.n_ops);
+  const int per_lane = t.per_lane;
+  a.tile[0] = t.tile[0];
+  a.tile[1] = t.tile[1];
   if (!a.wait_ticks) a.wait_ticks = kTileWaitTicks;
-  a.tiles0 = (uint32_t)std::max<uint64_t>(1, (a.n_ev + a.tile[0] - 1) / a.tile[0]);
-  a.tiles1 = (uint32_t)std::max<uint64_t>(1, (a.n_pe + a.tile[1] - 1) / a.tile[1]);
+  a.tiles0 = t.tiles[0];
+  a.tiles1 = t.tiles[1];
   const uint32_t tiles = a.tiles0 + a.tiles1;
   const uint32_t op_wgs = (uint32_t)std::min<uint64_t>(kMaxOpWgs, std::max<uint64_t>(1, ((uint64_t)a.n_ops + kThreads - 1) / kThreads));
   // without a timeline these are there for lists out of order only, and end at once where there are none
@@ -1422,4 +1443,14 @@ extern "C" int ss_timeline_scan(ss_ctx *ctx, const ss_event_t *ev, uint64_t n_ev
 // For tests: how long a workgroup of the context's long scans waits for a tile's sums (10 ns each; 0 = the usual time).
 extern "C" void ss_scan_wait_limit(ss_ctx *ctx, uint32_t ticks) {
   if (ctx) ctx->scan_wait_ticks = ticks;
+}
+
+// For tests: how a long trace is cut. out: events to a lane, then for each list the events of a tile and the tiles.
+extern "C" void ss_scan_tiling(uint64_t n_ev, uint64_t n_pe, uint32_t n_ops, uint32_t *out) {
+  const Tiling t = tiling_of(n_ev, n_pe, n_ops);
+  out[0] = (uint32_t)t.per_lane;
+  for (int l = 0; l < 2; ++l) {
+    out[1 + 2 * l] = t.tile[l];
+    out[2 + 2 * l] = t.tiles[l];
+  }
 }

@@ -160,6 +160,36 @@ def test_tiles_take_up_the_sums_before_them(P, ctx, n_ev, n_pe, n_ops):         
     assert_scan_equal(P.ss_timeline_scan(ctx, ev, pe, n_ops, 5, 1 << 41, want_timeline=True), ora)
 
 
+@pytest.mark.parametrize("n_ev,n_pe,n_ops", [
+    (131072, 0, 262145), (131073, 0, 262147), (0, 131073, 262147), (140000, 140000, 300000), (400000, 9, 1000000),   # two a lane
+    (600000, 3, 1300000), (524289, 140000, 300000), (3, 1048577, 2200000),                                          # four | passes
+])
+def test_more_operators_than_events_and_many_of_both(P, ctx, n_ev, n_pe, n_ops):     # noqa: F811
+    """tiles of gaps to be filled that would take more events than a workgroup loads at once; what is wrong with a tile's
+    last event is found too"""
+    rng = np.random.default_rng([n_ev, n_pe, n_ops, 5])
+    ev, pe = events(rng, n_ev, n_ops), events(rng, n_pe, n_ops, runs=True)
+    ora = both_ways(P, ctx, ev, pe, n_ops, 5, 1 << 41)
+    assert_scan_equal(P.ss_timeline_scan(ctx, ev, pe, n_ops, 5, 1 << 41), ora, timeline=False)
+    lists = [ev, pe]
+    which = int(n_pe > n_ev)
+    for at in (511, 513, 551, 1023, 1025):                   # with the one before it out of order, or out of range
+        swapped = lists[which].copy()
+        swapped[[at, at - 1]] = swapped[[at - 1, at]]
+        if swapped["op_idx"][at] != swapped["op_idx"][at - 1]:
+            one = list(lists)
+            one[which] = swapped
+            lib = P.ss_timeline_scan(ctx, one[0], one[1], n_ops, 5, 1 << 41)
+            assert lib["sorted"] == 0
+            assert_scan_equal(lib, ora, timeline=False)
+        one = list(lists)
+        one[which] = lists[which].copy()
+        one[which]["op_idx"][at] = n_ops
+        with pytest.raises(P.SsError) as e:
+            P.ss_timeline_scan(ctx, one[0], one[1], n_ops, 5, 1 << 41)
+        assert e.value.code == P.SS_E_INVAL
+
+
 @pytest.mark.parametrize("n_ops", [32, 1024, 1025, 2046, 2047, 2048, 2049, 2900])
 @pytest.mark.parametrize("at", [(0,), (0.5,), (1,), (0, 1), (0.3, 0.7)])
 def test_wide_gaps_in_one_workgroup(P, ctx, n_ops, at):           # noqa: F811
