@@ -39,7 +39,8 @@ struct ss_sched {
   std::vector<uint8_t> out_inline, in_inline;                           // per batch, this iteration: copied on the compute stream
   hipEvent_t last_inline = nullptr;               // done-event of the latest of these since the streams were last joined
   bool any_inline = false;                        // this iteration has some
-  uint32_t unsettled = 0;                         // batches on streams of their own that the compute stream doesn't wait for yet
+  std::vector<uint8_t> out_unsettled, in_unsettled;   // per batch, this iteration: on a stream of its own, the compute stream doesn't wait for it yet
+  uint32_t unsettled = 0;                         // how many of these there are
   // Per-batch events exist twice: iterations alternate between the two sets (`phase`, switched by the
   // drain), so that the timing of the iteration drained last stays readable while the next one runs.
   std::vector<hipEvent_t> ev_out_done[2], ev_in_done[2], ev_out_start[2], ev_in_start[2];
@@ -151,6 +152,7 @@ struct ss_ctx {
   hipEvent_t ev_iter[2][kIterEvents] = {};
   bool iter_pending[2] = {false, false};
   uint64_t iter_last_seq[2] = {0, 0};
+  uint32_t iter_unsettled[2] = {0, 0};   // batches of the iteration that the compute stream never waited for
   int iter_set = 0;
   std::vector<hipEvent_t> ev_ring;  // compute-stream markers, used round-robin
   size_t ev_next = 0;

@@ -511,6 +511,25 @@ static void free_events(std::vector<hipEvent_t> &v) {
   v.clear();
 }
 
+// Batches on streams of their own that the compute stream doesn't wait for yet.  Each is counted by itself: a release may
+// come after the streams were joined otherwise.
+static void unsettle(ss_sched &s, std::vector<uint8_t> &of, uint32_t batch) {
+  of[batch] = 1;
+  s.unsettled++;
+}
+
+static void settle(ss_sched &s, std::vector<uint8_t> &of, uint32_t batch) {
+  if (!of[batch]) return;
+  of[batch] = 0;
+  s.unsettled--;
+}
+
+static void settle_all(ss_sched &s) {
+  std::fill(s.out_unsettled.begin(), s.out_unsettled.end(), 0);
+  std::fill(s.in_unsettled.begin(), s.in_unsettled.end(), 0);
+  s.unsettled = 0;
+}
+
 // host joins every swap stream of both directions
 static int sync_swap_streams(ss_ctx *ctx) {
   eq_wait_idle(ctx);                  // the ring transfers pushed so far are on their stream
@@ -527,7 +546,8 @@ static int sync_swap_streams(ss_ctx *ctx) {
   for (uint32_t i = 0; i < ctx->n_s_in; ++i)
     if (ctx->s_in[i]) SS_HIP(hipStreamSynchronize(ctx->s_in[i]));
   if (ctx->s_flush) SS_HIP(hipStreamSynchronize(ctx->s_flush));
-  ctx->sched.unsettled = 0;
+  settle_all(ctx->sched);
+  ctx->iter_unsettled[0] = ctx->iter_unsettled[1] = 0;
   return SS_OK;
 }
 
@@ -830,9 +850,11 @@ extern "C" int ss_load_schedule(ss_ctx *ctx, const ss_desc_t *descs_out, uint32_
       }
     s.out_waited.assign(n_out_batches, 0);
     s.out_inline.assign(n_out_batches, 0);
+    s.out_unsettled.assign(n_out_batches, 0);
     s.out_issued.assign(n_out_batches, 0);
     s.in_waited.assign(n_in_batches, 0);
     s.in_inline.assign(n_in_batches, 0);
+    s.in_unsettled.assign(n_in_batches, 0);
     s.in_issued.assign(n_in_batches, 0);
     s.last_engine_out = -1;
     // staged swap-out: group consecutive batches whose staging slots form one gap-free range (every size
@@ -1328,9 +1350,13 @@ extern "C" int ss_swap_in_to(ss_ctx *ctx, uint32_t batch, void *const *dev_dst) 
 // staging slot written again) follow from the compute stream's own.
 constexpr uint64_t kInlineBytes = 256u << 10;
 
+static uint32_t swap_unsettled(const ss_ctx *ctx) {
+  return ctx->sched.unsettled + ctx->iter_unsettled[0] + ctx->iter_unsettled[1];
+}
+
 static bool copies_inline(const ss_ctx *ctx, bool engine, uint64_t bytes) {
   const ss_sched &s = ctx->sched;
-  return !engine && bytes <= kInlineBytes && s.unsettled == 0 && !s.flat_next && !ctx->d_mark && !ctx->cfg.copy_cus &&
+  return !engine && bytes <= kInlineBytes && !swap_unsettled(ctx) && !s.flat_next && !ctx->d_mark && !ctx->cfg.copy_cus &&
          !ctx->ring && !ctx->ring_in;
 }
 
@@ -1432,7 +1458,7 @@ static int swap_out_batch(ss_ctx *ctx, uint32_t batch) {
     s.last_inline = s.ev_out_done[s.phase][batch];
   } else {
     s.last_out_on[engine ? 0 : batch % ctx->n_s_out] = batch;
-    s.unsettled++;
+    if (hi > lo) unsettle(s, s.out_unsettled, batch);
   }
   ctx->stats.bytes_out += bytes;
   return SS_OK;
@@ -1633,8 +1659,8 @@ static int swap_in_batch(ss_ctx *ctx, uint32_t batch) {
     s.in_inline[batch] = 1;
     s.any_inline = true;
     s.last_inline = s.ev_in_done[s.phase][batch];
-  } else {
-    s.unsettled++;
+  } else if (hi > lo) {
+    unsettle(s, s.in_unsettled, batch);
   }
   ctx->stats.bytes_in += bytes;
   return SS_OK;
@@ -1695,7 +1721,7 @@ extern "C" int ss_sync(ss_ctx *ctx, uint32_t what, uint32_t id) {
         if (!s.out_inline[b]) {
           if (ctx->cfg.flags & SS_CFG_STALL_TIMING) SS_HIP(hipEventRecord(s.ev_free_at[b], ctx->compute));
           SS_HIP(hipStreamWaitEvent(ctx->compute, s.out_staged[b] ? s.ev_gathered[s.phase][b] : s.ev_out_done[s.phase][b], 0));
-          if (s.unsettled) s.unsettled--;
+          settle(s, s.out_unsettled, b);
         }
         s.out_waited[b] = 1;
         ctx->stats.free_waits++;
@@ -1717,7 +1743,7 @@ extern "C" int ss_sync(ss_ctx *ctx, uint32_t what, uint32_t id) {
         if (!s.in_inline[b]) {
           if (ctx->cfg.flags & SS_CFG_STALL_TIMING) SS_HIP(hipEventRecord(s.ev_wait_at[b], ctx->compute));
           SS_HIP(hipStreamWaitEvent(ctx->compute, s.ev_in_done[s.phase][b], 0));
-          if (s.unsettled) s.unsettled--;
+          settle(s, s.in_unsettled, b);
         }
         s.in_waited[b] = 1;
         ctx->stats.in_waits++;
@@ -1737,6 +1763,7 @@ extern "C" int ss_sync(ss_ctx *ctx, uint32_t what, uint32_t id) {
           if (ctx->ev_iter[prev][k]) SS_HIP(hipEventSynchronize(ctx->ev_iter[prev][k]));
         eq_wait_enqueued(ctx, ctx->iter_last_seq[prev]);
         ctx->iter_pending[prev] = false;
+        ctx->iter_unsettled[prev] = 0;
       }
       if (ctx->eq) {
         const int he = ctx->eq->hip_error.exchange(0);
@@ -1781,6 +1808,8 @@ extern "C" int ss_sync(ss_ctx *ctx, uint32_t what, uint32_t id) {
         for (uint32_t j = 0; j < ctx->n_s_in; ++j) SS_HIP(hipStreamWaitEvent(ctx->s_flush, ctx->ev_iter[cur][4 + j], 0));
       }
       ctx->iter_pending[cur] = true;
+      ctx->iter_unsettled[cur] = s.unsettled;                  // until the host has waited for the events above
+      settle_all(s);
       ctx->iter_set ^= 1;
       std::fill(s.out_waited.begin(), s.out_waited.end(), 0);
       std::fill(s.in_waited.begin(), s.in_waited.end(), 0);
@@ -2176,3 +2205,6 @@ extern "C" int ss_bw_probe(ss_ctx *ctx, uint64_t bytes, uint32_t reps, ss_bw_t *
     return rc;
   });
 }
+
+// For tests: batches on streams of their own that the compute stream isn't known to be behind.
+extern "C" uint32_t ss_swap_unsettled(ss_ctx *ctx) { return ctx ? swap_unsettled(ctx) : 0; }

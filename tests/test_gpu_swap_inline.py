@@ -125,3 +125,100 @@ def test_a_batch_is_done_before_what_follows_it_on_the_compute_stream(P):
         torch.cuda.synchronize()
     finally:
         P.ss_destroy(ctx)
+
+
+def two_copies(P, torch, groups):
+    """context, arena (random bytes, then as many zeros), start, sizes: `groups` of tensors leave from the first half and come
+    back to the second"""
+    sizes = [n for g in groups for n in g]
+    start = np.cumsum([0] + [len(g) for g in groups]).astype(np.uint32)
+    slot = [(n + 255) // 256 * 256 for n in sizes]
+    span, at = sum(slot), np.cumsum([0] + slot)
+    arena = torch.zeros(2 * span, dtype=torch.uint8, device="cuda")
+    arena[:span] = torch.randint(0, 256, (span,), dtype=torch.uint8, device="cuda")
+    cfg = P.ss_config_default()
+    cfg.staging_bytes = span
+    cfg.copy_path = cfg.copy_path_in = P.SS_PATH_KERNEL
+    ctx = P.ss_create(cfg)
+    P.ss_bind(ctx, arena.data_ptr(), 2 * span, torch.cuda.current_stream().cuda_stream)
+    d_out, d_in = np.zeros(len(sizes), dtype=W.DESC_DT), np.zeros(len(sizes), dtype=W.DESC_DT)
+    for i, n in enumerate(sizes):
+        d_out[i], d_in[i] = (at[i], at[i], n, i, 0), (span + at[i], at[i], n, i, 0)
+    torch.cuda.synchronize()
+    return ctx, arena, d_out, d_in, start, at
+
+
+def unsettled(P, ctx):
+    import ctypes
+    f = P._lib.ss_swap_unsettled
+    f.argtypes, f.restype = [ctypes.c_void_p], ctypes.c_uint32
+    return f(ctx)
+
+
+def test_a_late_release_counts_for_its_own_batch(P):
+    """the streams are joined between a batch and its release; a larger batch issued in between is still on its way then, and a
+    small swap-in of one of its tensors must not be copied ahead of it"""
+    import torch
+    ctx, arena, d_out, d_in, start, at = two_copies(P, torch, [[1024 * K], [96 << 20, 64 * K], [64 * K]])
+    try:
+        ins = np.array([0, 1], dtype=np.uint32)              # the second tensor of the large batch, by itself
+        P.ss_load_schedule(ctx, d_out, start, d_in[2:3], ins, in_dep=[1])
+        for late in (False, True):
+            P.ss_swap_out(ctx, 0)
+            assert unsettled(P, ctx) == 1
+            P.ss_staging_fill(ctx, 0x77)                     # joins the swap streams
+            assert unsettled(P, ctx) == 0
+            P.ss_swap_out(ctx, 1)
+            if late:
+                P.ss_swap_out(ctx, 2)
+            P.ss_sync(ctx, P.SS_SYNC_FREE, 0)
+            assert unsettled(P, ctx) == 1 + late
+            P.ss_swap_in(ctx, 0)
+            P.ss_sync(ctx, P.SS_SYNC_WAIT_IN, 2)
+            back = arena.clone()
+            assert unsettled(P, ctx) == 1 + late
+            P.ss_sync(ctx, P.SS_SYNC_FREE, 1)
+            P.ss_sync(ctx, P.SS_SYNC_FREE, 2)                # the same batch again
+            assert unsettled(P, ctx) == late
+            P.ss_sync(ctx, P.SS_SYNC_DRAIN)
+            assert unsettled(P, ctx) == 0
+            half = len(back) // 2
+            assert torch.equal(back[half + at[2]:half + at[3]], back[at[2]:at[3]])
+            arena[half:].zero_()
+    finally:
+        P.ss_destroy(ctx)
+
+
+def test_batches_that_are_never_released_or_empty(P):
+    """an empty batch holds nothing up; one that is never released does until the host has waited for its iteration"""
+    import torch
+    ctx, arena, d_out, d_in, start, at = two_copies(P, torch, [[1024 * K], [], [64 * K], [512 * K]])
+    try:
+        P.ss_load_schedule(ctx, d_out, start, d_in, start)
+        left_over = 0
+        for it in range(6):
+            leave = it in (1, 2)
+            P.ss_swap_out(ctx, 0)
+            P.ss_swap_out(ctx, 1)
+            assert unsettled(P, ctx) == 1 + left_over
+            P.ss_sync(ctx, P.SS_SYNC_FREE, 0)
+            P.ss_swap_out(ctx, 2)                            # on the compute stream where nothing is left over
+            assert unsettled(P, ctx) == (2 if left_over else 0)
+            P.ss_sync(ctx, P.SS_SYNC_FREE, 1)
+            P.ss_swap_out(ctx, 3)
+            if not leave:
+                P.ss_sync(ctx, P.SS_SYNC_FREE, 2)
+            for b in range(4):
+                P.ss_swap_in(ctx, b)
+            for t in range(3):
+                P.ss_sync(ctx, P.SS_SYNC_WAIT_IN, t)
+            back = arena.clone()
+            P.ss_sync(ctx, P.SS_SYNC_ITERATION_END)
+            left_over = int(leave)
+            assert unsettled(P, ctx) == left_over
+            torch.cuda.synchronize()
+            half = len(back) // 2
+            assert torch.equal(back[half:], back[:half])
+            arena[half:].zero_()
+    finally:
+        P.ss_destroy(ctx)
