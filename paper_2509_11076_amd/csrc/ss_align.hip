@@ -345,9 +345,14 @@ struct RowsShared {
   uint32_t out[kFeeds][kStripWords];     // V after a block; lane 63's is what the strip hands on
 };
 
-// The wavefronts of a strip meet after every block of steps.  Those that write LDS have done so by then; the first one
-// only reads, what it reads is not written again before it has used it (kFeeds), and it waits for none of its reads here.
+// The wavefronts of a strip meet after every block of steps.  Those that write LDS have done so by then; what the first one
+// reads is not written again before it has used it (kFeeds), and it waits for none of its reads here.  In several strips it
+// also leaves its words, one store a block; the store of the block before has been done by then: the eight reads for the next
+// block were issued after it, and LDS operations of a wavefront end in order.  (They were issued a block of steps ago: the
+// wait takes no time.)
 __device__ __forceinline__ void meet() { asm volatile("s_barrier" ::: "memory"); }
+static_assert(kBlock / 4 == 8, "reads of a block of steps");
+__device__ __forceinline__ void meet_written_before() { asm volatile("s_waitcnt lgkmcnt(8)\n\ts_barrier" ::: "memory"); }
 __device__ __forceinline__ void meet_written() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
 
 // Masks for the first wavefront: two feeders take the blocks in turn.  Block c lies in LDS when the first one enters block
@@ -463,7 +468,7 @@ __device__ __forceinline__ void take_carries(RowsShared &sh, const RowsArgs &a, 
 }
 
 // The first wavefront leaves its words in LDS (a store of its own, by one lane, took it 70 cycles a block) and doesn't wait
-// for that: they are there a block later.  Taking and giving are two wavefronts' work: behind its own stores the one that
+// for that: they are there a block later (meet_written_before).  Taking and giving are two wavefronts' work: behind its own stores the one that
 // looks at the other strip's words waits for them too (32,312 x 32,297 operators 623 us against 500).
 __device__ __forceinline__ void give_carries(const RowsShared &sh, const RowsArgs &a, bool gives) {
   const uint32_t lane = threadIdx.x & 63, strip = a.strip0 + blockIdx.x, n_blocks = a.n_steps / kBlock;
@@ -525,8 +530,12 @@ __device__ __forceinline__ void strip_rows(RowsShared &sh, const RowsArgs &a, bo
       __builtin_amdgcn_sched_barrier(0);
     }
     at += kBlock * kStripWords * 4;
-    if constexpr (kMany) sh.out[b % kFeeds][lane] = V;
-    meet();
+    if constexpr (kMany) {
+      sh.out[b % kFeeds][lane] = V;
+      meet_written_before();
+    } else {
+      meet();
+    }
   }
   meet_written();
 }
