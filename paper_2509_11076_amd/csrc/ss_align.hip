@@ -339,7 +339,7 @@ struct Masks<uint16_t> {
   }
 };
 
-struct RowsShared {
+struct alignas(16) RowsShared {             // read and written 16 bytes at a time
   uint32_t feed[kFeeds][kFeedWords];     // masks of a block of steps, four steps of a lane together
   uint32_t in[kFeeds];                   // what lane 0 hands on during a block
   uint32_t out[kFeeds][kStripWords];     // V after a block; lane 63's is what the strip hands on
@@ -562,7 +562,8 @@ __global__ __launch_bounds__(kRowsThreads) void ss_align_rows_kernel(const Id *_
                                                                      const uint32_t *__restrict__ n_keys) {
   constexpr bool kLds = sizeof(Id) == 2;
   __shared__ RowsShared sh;
-  extern __shared__ uint32_t lds[];
+  extern __shared__ uint4 lds4[];                            // written 16 bytes at a time
+  uint32_t *const lds = reinterpret_cast<uint32_t *>(lds4);
   const uint32_t tid = threadIdx.x, lane = tid & 63, role = __builtin_amdgcn_readfirstlane(tid >> 6), strip = a.strip0 + blockIdx.x;
   const bool many = a.strips > 1;
   const uint32_t first = many ? 1 : 0;                       // lane of the strip's first word
@@ -576,10 +577,9 @@ __global__ __launch_bounds__(kRowsThreads) void ss_align_rows_kernel(const Id *_
   }
   Masks<Id> masks;
   if constexpr (kLds) {
-    uint4 *const table4 = reinterpret_cast<uint4 *>(lds);
     for (uint32_t i = tid; i < n_mask_rows * (kStripWords / 4); i += kRowsThreads) {
       const uint32_t part = i % (kStripWords / 4);
-      table4[i] = uint4{many && part == 0 ? ~0u : 0, 0, 0, many && part == kStripWords / 4 - 1 ? ~0u : 0};
+      lds4[i] = uint4{many && part == 0 ? ~0u : 0, 0, 0, many && part == kStripWords / 4 - 1 ? ~0u : 0};
     }
     // ten words' columns at a time, all of them in flight
     constexpr uint32_t kPer = (kStripWords * 32 + kRowsThreads - 1) / kRowsThreads;
