@@ -552,9 +552,10 @@ int ss_generate_policy_best(ss_ctx *ctx, const ss_op_t *ops, uint32_t n_ops, con
 /* Enqueue swap-out batch `batch`: the swap-out stream waits (on the device) for
  * everything enqueued so far on the compute stream, copies each tensor of the
  * batch to its staging slot and records the batch's done-event.  Returns at
- * once.  A copy-kernel batch of at most 256 KiB is copied on the compute stream itself, by both calls, while
- * no batch on a swap stream is outstanding (issued, and neither released / waited for nor drained; one that its
- * iteration never released or waited for, until the next iteration has ended): that delays the compute stream
+ * once.  A copy-kernel batch of at most 64 KiB, or of at most 256 KiB that the schedule of ss_apply_policy
+ * releases or waits for within an operator of its issue, is copied on the compute stream itself, by both calls,
+ * while no batch on a swap stream is outstanding (issued, and neither released / waited for nor drained; one that
+ * its iteration never released or waited for, until the next iteration has ended): that delays the compute stream
  * by less than the events between two streams.  Not with SS_CFG_MEMORY_MARKERS, copy_cus, an HBM ring, or
  * addresses given with the call. */
 int ss_swap_out(ss_ctx *ctx, uint32_t batch);

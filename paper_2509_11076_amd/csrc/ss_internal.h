@@ -36,6 +36,8 @@ struct ss_sched {
   std::unordered_map<uint32_t, uint32_t> out_of_tensor, in_of_tensor;  // tensor id -> descriptor index
   std::vector<uint32_t> out_batch_of, in_batch_of;                      // descriptor index -> batch
   std::vector<uint8_t> out_waited, in_waited, out_issued, in_issued;    // per batch, this iteration
+  // per batch, by the loaded actions: released / waited for at most one operator after its issue (0 without actions)
+  std::vector<uint8_t> out_soon, in_soon;
   std::vector<uint8_t> out_inline, in_inline;                           // per batch, this iteration: copied on the compute stream
   hipEvent_t last_inline = nullptr;               // done-event of the latest of these since the streams were last joined
   bool any_inline = false;                        // this iteration has some

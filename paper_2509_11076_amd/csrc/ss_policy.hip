@@ -381,6 +381,19 @@ extern "C" int ss_apply_policy(ss_ctx *ctx, const ss_policy_item_t *policy, uint
     for (const ss_action_t &a : s.actions) s.act_start[2ull * a.op_idx + (a.kind >= SS_ACT_OUT ? 1 : 0) + 1]++;
     for (uint64_t g = 0; g < groups; ++g) s.act_start[g + 1] += s.act_start[g];
     s.have_actions = true;
+    // Batches whose first release or wait comes at most one operator after their issue.  The actions are in order, so the first
+    // of either kind is the earliest; -1: none yet, -2: released or waited for.
+    std::vector<int64_t> out_at(s.out_soon.size(), -1), in_at(s.in_soon.size(), -1);
+    for (const ss_action_t &a : s.actions) {
+      const bool out = a.kind >= SS_ACT_OUT;
+      int64_t &at = (out ? out_at : in_at)[a.batch];
+      if (a.kind == SS_ACT_OUT || a.kind == SS_ACT_IN) {
+        if (at == -1) at = a.op_idx;
+      } else {
+        if (at >= 0 && a.op_idx - at <= 1) (out ? s.out_soon : s.in_soon)[a.batch] = 1;
+        at = -2;
+      }
+    }
     // reuse interval of every kept item (Sec. 6.4): operators between issuing the swap-out and the release
     std::memset(ctx->stats.reuse_hist, 0, sizeof(ctx->stats.reuse_hist));
     ctx->stats.reuse_sum = ctx->stats.reuse_count = 0;

@@ -782,6 +782,8 @@ extern "C" int ss_load_schedule(ss_ctx *ctx, const ss_desc_t *descs_out, uint32_
       if (n_out_batches == 0 || in_dep[b] >= n_out_batches) return SS_E_INVAL;
     ss_sched &s = ctx->sched;
     s.have_actions = false;       // a schedule loaded here carries no actions; ss_apply_policy adds them
+    std::fill(s.out_soon.begin(), s.out_soon.end(), 0);
+    std::fill(s.in_soon.begin(), s.in_soon.end(), 0);
     // the same schedule as the one already loaded (a fixed operator sequence in the Stable stage): it was
     // validated against this arena and staging area when it was loaded; device tables, chunk tables and
     // events stay, only the per-iteration state starts over
@@ -850,10 +852,12 @@ extern "C" int ss_load_schedule(ss_ctx *ctx, const ss_desc_t *descs_out, uint32_
       }
     s.out_waited.assign(n_out_batches, 0);
     s.out_inline.assign(n_out_batches, 0);
+    s.out_soon.assign(n_out_batches, 0);
     s.out_unsettled.assign(n_out_batches, 0);
     s.out_issued.assign(n_out_batches, 0);
     s.in_waited.assign(n_in_batches, 0);
     s.in_inline.assign(n_in_batches, 0);
+    s.in_soon.assign(n_in_batches, 0);
     s.in_unsettled.assign(n_in_batches, 0);
     s.in_issued.assign(n_in_batches, 0);
     s.last_engine_out = -1;
@@ -1340,23 +1344,30 @@ extern "C" int ss_swap_in_to(ss_ctx *ctx, uint32_t batch, void *const *dev_dst) 
 
 // Small batches are copied by a kernel on the compute stream itself.  On a stream of its own a batch takes an event in each
 // direction between the two streams, which costs the host five calls instead of two and the compute stream more than the copy
-// does.  24 batches of one tensor beside compute kernels of 30 us each, waited for three operators later (us for all):
-// 16 KiB 888 on a stream of their own and 849 on the compute stream, 64 KiB 890 and 868, 128 KiB 891 and 897, 256 KiB 886
-// and 960; beside kernels of 6 us 580 and 237, 589 and 249, 642 and 277, 635 and 333; of 63 us 1,720 and 1,634 ... 1,724 and
-// 1,748; waited for at once 1,236 and 849 ... 1,315 and 960.  (Without any copy 767, 137 and 1,554.)  So up to 256 KiB it is
-// the faster form or 2 to 8 % of such a step slower, and beyond it a copy that may overlap should.
+// does; but there it may overlap with operators that run before its release.  12 batches out and 12 in, beside operators of
+// 15, 30 and 63 us (us for all, on streams of their own and on the compute stream):
+//   released or waited for 0 operators later, 256 KiB    883 and 582, 1,265 and 950, 2,090 and 1,723
+//   1 later,                                  64 KiB     692 and 503,   948 and 894, 1,824 and 1,761
+//                                            192 KiB     708 and 565,   950 and 953, 1,833 and 1,819
+//                                            256 KiB     711 and 601,   963 and 985, 1,846 and 1,853
+//   3 later,                                  64 KiB     722 and 559, 1,019 and 1,014, 2,065 and 2,014
+//                                            128 KiB     718 and 591, 1,023 and 1,040, 2,066 and 2,041
+//                                            256 KiB     727 and 656, 1,042 and 1,108, 2,086 and 2,104
+// Without operators to overlap with it is 360 to 570 and 155 to 225.  So up to 64 KiB it is never the slower form; up to
+// 256 KiB it is where the schedule has the release or wait follow within an operator (within 2.3 %); beyond, or where the
+// library doesn't know the schedule, the copy gets its chance to overlap.
 // Only while no batch on a stream of its own is on its way as far as the compute stream knows: beside one the copy would
 // queue for the link with the compute stream behind it, and the orders below (a swap-in after the swap-outs of its tensors, a
 // staging slot written again) follow from the compute stream's own.
-constexpr uint64_t kInlineBytes = 256u << 10;
+constexpr uint64_t kInlineBytes = 64u << 10, kInlineBytesSoon = 256u << 10;
 
 static uint32_t swap_unsettled(const ss_ctx *ctx) {
   return ctx->sched.unsettled + ctx->iter_unsettled[0] + ctx->iter_unsettled[1];
 }
 
-static bool copies_inline(const ss_ctx *ctx, bool engine, uint64_t bytes) {
+static bool copies_inline(const ss_ctx *ctx, bool engine, uint64_t bytes, bool soon) {
   const ss_sched &s = ctx->sched;
-  return !engine && bytes <= kInlineBytes && !swap_unsettled(ctx) && !s.flat_next && !ctx->d_mark && !ctx->cfg.copy_cus &&
+  return !engine && bytes <= (soon ? kInlineBytesSoon : kInlineBytes) && !swap_unsettled(ctx) && !s.flat_next && !ctx->d_mark && !ctx->cfg.copy_cus &&
          !ctx->ring && !ctx->ring_in;
 }
 
@@ -1395,7 +1406,7 @@ static int swap_out_batch(ss_ctx *ctx, uint32_t batch) {
                     : s.flat_next ? ctx->cfg.copy_path != SS_PATH_KERNEL
                                   : use_engine(ctx, ctx->cfg.copy_path, true, s.out, lo, hi);
   const uint64_t bytes = batch_bytes(s.out, lo, hi);
-  const bool in_line = copies_inline(ctx, engine, bytes);
+  const bool in_line = copies_inline(ctx, engine, bytes, s.out_soon[batch]);
   const hipEvent_t done = with_kernel(ctx, in_line, s.ev_out_done[s.phase][batch]);
   bool recorded = false;
   // copy-kernel batches take the swap-out streams in turn; copy-engine batches stay on the first
@@ -1568,7 +1579,7 @@ static int swap_in_batch(ss_ctx *ctx, uint32_t batch) {
                     : s.flat_next ? ctx->cfg.copy_path_in != SS_PATH_KERNEL
                                   : use_engine(ctx, ctx->cfg.copy_path_in, false, s.in, lo, hi);
   const uint64_t bytes = batch_bytes(s.in, lo, hi);
-  const bool in_line = copies_inline(ctx, engine, bytes);
+  const bool in_line = copies_inline(ctx, engine, bytes, s.in_soon[batch]);
   const hipEvent_t done = with_kernel(ctx, in_line, s.ev_in_done[s.phase][batch]);
   bool recorded = false;
   hipStream_t si = in_line ? ctx->compute : engine ? ctx->s_in[0] : ctx->s_in[batch % ctx->n_s_in];

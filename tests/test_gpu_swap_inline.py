@@ -1,6 +1,7 @@
-"""Copy-kernel batches of at most 256 KiB are copied on the compute stream while no other batch is outstanding: batches at
-and beyond that size mixed, released at once or late, swap-outs in either order, several iterations that end with and without
-a host wait, the compute stream lagging behind the calls; bytes exact in staging and arena."""
+"""Small copy-kernel batches (64 KiB, or 256 KiB where the schedule releases them soon) are copied on the compute stream while
+no other batch is outstanding: batches at and beyond these sizes mixed, released at once or late, swap-outs in either order,
+one or several swap streams a direction, several iterations that end with and without a host wait, the compute stream lagging
+behind the calls; bytes exact in staging and arena."""
 import numpy as np
 import pytest
 
@@ -23,7 +24,7 @@ def P():
 def test_small_and_large_batches_mixed(P, flags_name, release, end):
     import torch
     groups = [[1], [256 * K], [256 * K + 1], [16], [64 * K, 100 * K + 3], [1024 * K], [], [255 * K, K], [128 * K, 128 * K + 1],
-              [300 * K], [5] * 9]
+              [300 * K], [5] * 9, [64 * K], [64 * K + 1], [32 * K, 32 * K], [3]]
     sizes = [n for g in groups for n in g]
     start = np.cumsum([0] + [len(g) for g in groups]).astype(np.uint32)
     slot = [(n + 255) // 256 * 256 for n in sizes]
@@ -220,5 +221,100 @@ def test_batches_that_are_never_released_or_empty(P):
             half = len(back) // 2
             assert torch.equal(back[half:], back[:half])
             arena[half:].zero_()
+    finally:
+        P.ss_destroy(ctx)
+
+
+def scheduled(P, torch, sizes_of_op, bpo, streams=1, flags=0):
+    """context with a schedule of ss_apply_policy: the tensors of each operator leave after it and come back before its mirror
+    image, from the first half of the arena to the second; the link moves bpo bytes during an operator"""
+    flat = [(op, n) for op, sizes in enumerate(sizes_of_op) for n in sizes]
+    n_ops, n = 3 * len(sizes_of_op) + 40, len(flat)
+    slot = [(x + 255) // 256 * 256 for _, x in flat]
+    span = sum(slot)
+    tab, pol = np.zeros(n, dtype=P.TENSOR_DT), np.zeros(n, dtype=P.POLICY_DT)
+    order = np.random.default_rng(4).permutation(n)
+    at = np.zeros(n, dtype=np.int64)
+    at[order] = np.cumsum(np.array(slot)[order]) - np.array(slot)[order]
+    for i, (op, size) in enumerate(flat):
+        tab["tensor_id"][i], tab["dtype"][i], tab["nbytes"][i] = i, 1, size
+        tab["producer_op"][i] = tab["alloc_op"][i] = tab["last_fwd_use"][i] = op
+        tab["out_slot"][i] = pol["out_slot"][i] = sum(1 for o, _ in flat[:i] if o == op)
+        tab["first_bwd_use"][i] = tab["free_op"][i] = n_ops - 1 - op
+        pol["ref_op"][i], pol["tensor_id"][i], pol["nbytes"][i] = op, i, size
+    tab["dev_off"], tab["dev_off_in"] = at, span + at
+    cfg = P.ss_config_default()
+    cfg.staging_bytes, cfg.link_bytes_per_op, cfg.flags = span, bpo, flags
+    cfg.copy_path = cfg.copy_path_in = P.SS_PATH_KERNEL
+    cfg.out_streams = cfg.in_streams = streams
+    arena = torch.zeros(2 * span, dtype=torch.uint8, device="cuda")
+    ctx = P.ss_create(cfg)
+    P.ss_bind(ctx, arena.data_ptr(), 2 * span, torch.cuda.current_stream().cuda_stream)
+    ap = P.ss_apply_policy(ctx, pol, pol["ref_op"].astype(np.int32), tab)
+    assert ap["n_kept"] == n
+    return ctx, arena, ap["actions"], n_ops, at, [x for _, x in flat]
+
+
+@pytest.mark.parametrize("size,bpo,soon", [
+    (64 * K, 1 << 40, True), (64 * K, 8 * K, False), (64 * K + 1, 1 << 40, True), (64 * K + 1, 16 * K, False),
+    (256 * K, 256 * K, True), (256 * K, 255 * K, False), (256 * K + 1, 1 << 40, True)])
+def test_which_batches_are_copied_on_the_compute_stream(P, size, bpo, soon):
+    """at most 64 KiB, or 256 KiB where at most one operator runs between the batch and its release or wait"""
+    import torch
+    ctx, arena, actions, n_ops, at, sizes = scheduled(P, torch, [[size]], bpo)
+    try:
+        op = {k: int(actions["op_idx"][actions["kind"] == k][0]) for k in range(4)}
+        gaps = (op[P.SS_ACT_FREE] - op[P.SS_ACT_OUT], op[P.SS_ACT_WAIT_IN] - op[P.SS_ACT_IN])
+        assert all((g <= 1) == soon for g in gaps)
+        inline = size <= (256 * K if soon else 64 * K)
+        for loaded in (False, True):                         # the same schedule without its actions: when it ends isn't known
+            if loaded:
+                start = np.array([0, 1], dtype=np.uint32)
+                d_out, d_in = np.zeros(1, dtype=W.DESC_DT), np.zeros(1, dtype=W.DESC_DT)
+                d_out[0], d_in[0] = (at[0], 0, size, 0, 0), (len(arena) // 2 + at[0], 0, size, 0, 0)
+                P.ss_load_schedule(ctx, d_out, start, d_in, start)
+                inline = size <= 64 * K
+            P.ss_swap_out(ctx, 0)
+            assert unsettled(P, ctx) == (0 if inline else 1)
+            P.ss_sync(ctx, P.SS_SYNC_FREE, 0)
+            P.ss_swap_in(ctx, 0)
+            assert unsettled(P, ctx) == (0 if inline else 1)
+            P.ss_sync(ctx, P.SS_SYNC_WAIT_IN, 0)
+            P.ss_sync(ctx, P.SS_SYNC_DRAIN)
+    finally:
+        P.ss_destroy(ctx)
+
+
+@pytest.mark.parametrize("flags_name", [None, "SS_CFG_TIMING", "SS_CFG_STALL_TIMING"])
+@pytest.mark.parametrize("streams", [1, 3])
+@pytest.mark.parametrize("bpo", [1 << 40, 200 * K])
+def test_scheduled_batches(P, flags_name, streams, bpo):
+    """whole iterations by their actions, most batches released soon or none of the larger ones"""
+    import torch
+    from paper_2509_11076_amd.executor import dispatch_points, run_iteration_dispatch
+    groups = [[1], [256 * K], [16], [256 * K + 1], [200 * K], [64 * K, 100 * K + 3], [255 * K, K], [1024 * K], [128 * K, 128 * K],
+              [300 * K], [5] * 9, [64 * K], [64 * K + 1], [130 * K], [3]]
+    ctx, arena, actions, n_ops, at, sizes = scheduled(P, torch, groups, bpo, streams, getattr(P, flags_name) if flags_name else 0)
+    try:
+        points, half = dispatch_points(actions), len(arena) // 2
+        last_out = int(actions["op_idx"][actions["kind"] >= P.SS_ACT_OUT].max())
+        gen = torch.Generator(device="cuda")
+        gen.manual_seed(5)
+        for it in range(5):
+            src = torch.randint(0, 256, (half,), dtype=torch.uint8, device="cuda", generator=gen)
+            arena[:half].copy_(src)
+            arena[half:].zero_()
+            torch.cuda.synchronize()
+
+            def run_op(i):
+                torch.cuda._sleep(60000 if i % 3 else 3000)
+                if i == last_out + 1:
+                    arena[:half].fill_(0x3C)                 # every block has been released
+            run_iteration_dispatch(ctx, n_ops, run_op, points,
+                                   end=P.SS_SYNC_ITERATION_END if it % 2 else P.SS_SYNC_DRAIN)
+            back, want = arena[half:].clone().cpu().numpy(), src.cpu().numpy()
+            for a, n in zip(at, sizes):
+                assert np.array_equal(back[a:a + n], want[a:a + n])
+        P.ss_sync(ctx, P.SS_SYNC_DRAIN)
     finally:
         P.ss_destroy(ctx)
