@@ -49,18 +49,10 @@ def test_results_beside_work_on_the_compute_stream(P, ctx):                     
             assert all(same(f(), want) for _ in range(5))
 
 
-@pytest.mark.parametrize("n_ev,n_ops", [(60000, 9000), (20000, 3000)])
-def test_the_word_comes_after_every_result(P, ctx, n_ev, n_ops):                     # noqa: F811
+def in_turn(call, want):
     """two inputs in turn, so that a result that is late is the other input's; beside short products and beside kernels that
     keep the caches full of their own stores (a word that did not wait for other dies' results: 2 to 4 % of the calls)"""
     import torch
-    rng = np.random.default_rng([n_ev, n_ops])
-    inputs = [(events(rng, n_ev, n_ops), events(rng, n_ev // 4, n_ops), 5 + 1000003 * i) for i in (1, 2)]
-
-    def call(i):
-        ev, pe, base = inputs[i]
-        return P.ss_timeline_scan(ctx, ev, pe, n_ops, base, 1 << 40, want_timeline=True)
-    want = [call(0), call(1)]
     m = torch.ones(4096, 4096, dtype=torch.bfloat16, device="cuda")
     full = torch.zeros(1 << 28, dtype=torch.uint8, device="cuda")
     for work in (lambda: m @ m, lambda: full.add_(1)):
@@ -71,3 +63,49 @@ def test_the_word_comes_after_every_result(P, ctx, n_ev, n_ops):                
                 got = call(i)
                 assert all(np.array_equal(got[k], want[i][k]) for k in got)
         torch.cuda.synchronize()
+
+
+@pytest.mark.parametrize("n_ev,n_ops", [(60000, 9000), (20000, 3000)])
+def test_the_word_comes_after_every_result(P, ctx, n_ev, n_ops):                     # noqa: F811
+    rng = np.random.default_rng([n_ev, n_ops])
+    inputs = [(events(rng, n_ev, n_ops), events(rng, n_ev // 4, n_ops), 5 + 1000003 * i) for i in (1, 2)]
+
+    def call(i):
+        ev, pe, base = inputs[i]
+        return P.ss_timeline_scan(ctx, ev, pe, n_ops, base, 1 << 40, want_timeline=True)
+    in_turn(call, [call(0), call(1)])
+
+
+@pytest.mark.parametrize("what,n,k", [
+    ("match", 1500, 400), ("match", 7000, 5000), ("match", 40000, 300),      # searches in registers, by numbers; sums of many workgroups
+    ("match", 60000, 0), ("histogram", 9000, 0), ("histogram", 9000, 900),   # the sums alone
+    ("align", 1500, 40), ("align", 3000, 40), ("align", 7000, 40),           # one launch; rows walked by the host; pairs from the GPU
+])
+def test_the_word_comes_after_every_result_of_earlier_kernels(P, ctx, what, n, k):   # noqa: F811
+    """the sums of the cosine are written by the first kernel of a call, an aligner's pairs partly by the one before the last;
+    expected values from the oracle"""
+    import oracle
+    rng = np.random.default_rng([n, k])
+    inputs = []
+    for extra in (3, 11):
+        ref, cur = operators(P, rng, n), operators(P, rng, n + extra)
+        anchors = np.zeros(k, dtype=P.ANCHOR_DT)
+        anchors["ref_op"] = np.sort(rng.choice(n, k, replace=False))
+        inputs.append((ref, cur, anchors))
+
+    def call(i):
+        if what == "align":
+            return P.ss_align_sequence(ctx, *inputs[i])
+        return P.ss_match_sequence(ctx, *inputs[i], flags=P.SS_MATCH_HISTOGRAM if what == "histogram" else 0)
+    want = [call(0), call(1)]
+    for (ref, cur, _), got in zip(inputs, want):
+        if what != "align":
+            a, b = cur["op_token"].astype(np.int64), ref["op_token"].astype(np.int64)
+            if what == "histogram":
+                a, b = np.bincount(a, minlength=64), np.bincount(b, minlength=64)
+            b = np.pad(b, (0, len(a) - len(b)))
+            assert (got["dot"], got["na"], got["nb"]) == ((a * b).sum(), (a * a).sum(), (b * b).sum())
+        elif n <= 1500:
+            ora = oracle.align_anchors(oracle.ops_tuples(ref), oracle.ops_tuples(cur), [])
+            assert np.array_equal(got["ref_to_cur"], ora["ref_to_cur"])
+    in_turn(call, want)

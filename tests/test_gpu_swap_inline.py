@@ -318,3 +318,48 @@ def test_scheduled_batches(P, flags_name, streams, bpo):
         P.ss_sync(ctx, P.SS_SYNC_DRAIN)
     finally:
         P.ss_destroy(ctx)
+
+
+@pytest.mark.parametrize("sizes", [[64 * K, 16, 1000], [1024 * K, 300 * K], [64 * K, 1024 * K, 16, 300 * K]])
+def test_an_iteration_captured_into_a_graph(P, sizes):
+    """batches on the compute stream and on streams of their own, captured with the step; what the capture recorded is no event
+    that a drain could wait for.  Replays with new bytes, eager iterations and drains in between"""
+    import torch
+    stream = torch.cuda.Stream()
+    with torch.cuda.stream(stream):
+        ctx, arena, d_out, d_in, start, at = two_copies(P, torch, [[n] for n in sizes])
+        half = len(arena) // 2
+        try:
+            P.ss_load_schedule(ctx, d_out, start, d_in, start)
+
+            def iteration():
+                for b in range(len(sizes)):
+                    P.ss_swap_out(ctx, b)
+                for t in range(len(sizes)):
+                    P.ss_sync(ctx, P.SS_SYNC_FREE, t)
+                arena[:half].fill_(0x3C)
+                for b in range(len(sizes)):
+                    P.ss_swap_in(ctx, b)
+                for t in range(len(sizes)):
+                    P.ss_sync(ctx, P.SS_SYNC_WAIT_IN, t)
+
+            def check(step):
+                src = torch.randint(0, 256, (half,), dtype=torch.uint8, device="cuda")
+                arena[:half].copy_(src)
+                arena[half:].zero_()
+                step()
+                torch.cuda.synchronize()
+                for a, n in zip(at, sizes):
+                    assert torch.equal(arena[half + a:half + a + n], src[a:a + n])
+                    assert np.array_equal(P.ss_host_peek(ctx, int(a), n), src[a:a + n].cpu().numpy())
+            graph = torch.cuda.CUDAGraph()
+            with torch.cuda.graph(graph, stream=stream):
+                iteration()
+            P.ss_sync(ctx, P.SS_SYNC_DRAIN)
+            for _ in range(3):
+                check(graph.replay)
+                check(iteration)
+                P.ss_sync(ctx, P.SS_SYNC_DRAIN)
+                check(graph.replay)
+        finally:
+            P.ss_destroy(ctx)
