@@ -458,9 +458,9 @@ __global__ __launch_bounds__(256) void ss_anchor_short_kernel(AnchorArgs g) {
 // their occurrences and 8.8 for the anchors.  (A workgroup per key that went through both sequences and listed its places took
 // 16.5 us, bound by the turns of one workgroup, and the anchors 7.8.)
 
-// Per level: an open-addressing table of at least 2k slots holding the anchor that stands for a key, and beside it the
-// key itself with its number; and for every operator of both sequences the number of its key and how many with that key come
-// before it in its chunk.
+// Per level: an open-addressing table of at least 2k slots, up to 2^kKeyBits, holding the anchor that stands for a key, and
+// beside it the key itself with its number; and for every operator of both sequences the number of its key and how many with
+// that key come before it in its chunk.
 struct KeyTable {
   uint32_t *rep[3];
   uint4 *key[3];               // {1 + number, token, stack, sig}; zeros: no key
@@ -468,6 +468,7 @@ struct KeyTable {
   uint32_t *info[2][3];        // [0] ref, [1] cur: number << kRankBits | rank in the chunk, or kNoKey; whole chunks
   uint32_t *count[2];          // [level][chunk][number]: occurrences in the chunk, n_used of the level to a chunk
   uint32_t mask, shift, max_keys;
+  uint32_t probes;             // slots that are looked at for a key at most
   uint32_t chunk_bits[2], chunks[2];         // operators of a chunk (a power of two), chunks
 };
 // They take the calls of that many comparisons of an anchor with an operator (10 us of comparing), and those where a single
@@ -482,6 +483,13 @@ static_assert((1u << 23) / kMaxChunks < 1u << kRankBits, "a rank fits its bits")
 // More distinct keys (of all levels) than this, and an anchor is searched for by itself.
 constexpr uint32_t kMaxKeys = 4096;
 static_assert(kMaxKeys <= 1u << (32 - kRankBits), "a key's number fits its bits");
+
+// The tables are cleared by every call, 60 bytes a slot, and no more than kMaxKeys of their keys are made use of: 2^16 slots
+// do for any number of anchors (2^24 over 2^23 operators: 1.5 GiB of scratch, with 2k slots 3.8, the call 190 ms; 2^20 over
+// 2^20 0.14 and 0.28 GiB, 5.1 and 5.2 ms).  Keys may outnumber these slots.  At most one slot in sixteen is taken while the
+// keys can be made use of, so a key that finds no place in kProbes of them says that there are too many.
+constexpr uint32_t kKeyBits = 16, kProbes = 32, kTooMany = 1u << 30;
+static_assert(3 * ((uint64_t)kTooMany + (1u << kKeyBits)) < 1ull << 32, "the levels' numbers are added");
 
 __device__ __forceinline__ bool same_at(const ss_op_t &x, const ss_op_t &y, int L) {
   return (x.op_token == y.op_token) & ((L == 2) | (x.sig == y.sig)) & ((L != 0) | (x.stack_hash == y.stack_hash));
@@ -527,16 +535,17 @@ __global__ __launch_bounds__(256) void ss_keys_kernel(AnchorArgs g, KeyTable q) 
   constexpr uint32_t kTagShift = 25;
   uint32_t h = (uint32_t)(x >> q.shift);
   const uint32_t tag = (uint32_t)(x >> (q.shift - 7)) & 127u, entry = tag << kTagShift | (a + 1);
-  bool won = false;
-  for (uint32_t probe = 0; goes && probe <= q.mask; ++probe) { // at most k keys in more than 2k slots
+  bool won = false, placed = !goes;
+  for (uint32_t probe = 0; !placed && probe < q.probes; ++probe) {
     uint32_t seen = __hip_atomic_load(q.rep[L] + h, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     if (!seen) {
       seen = atomicCAS(q.rep[L] + h, 0u, entry);
-      if (!seen) { won = true; break; }
+      if (!seen) { won = placed = true; break; }
     }
-    if (seen >> kTagShift == tag && same_at(g.ref[g.anchors[(seen & ((1u << kTagShift) - 1)) - 1].ref_op], R, L)) break;
-    h = (h + 1) & q.mask;
+    placed = seen >> kTagShift == tag && same_at(g.ref[g.anchors[(seen & ((1u << kTagShift) - 1)) - 1].ref_op], R, L);
+    if (!placed) h = (h + 1) & q.mask;
   }
+  if (!placed) atomicMax(q.n_used + L, kTooMany);
   // numbers for a wavefront's new keys at once: additions to one word are served one after the other
   const uint64_t winners = __ballot(won);
   if (!winners) return;
@@ -813,6 +822,8 @@ extern "C" int ss_match_sequence(ss_ctx *ctx, const ss_op_t *ref, uint32_t n, co
     uint32_t bits = 6;
     while ((1ull << bits) < 2ull * k) ++bits;
     const size_t slots = (size_t)1 << bits;
+    const uint32_t key_bits = std::min(bits, kKeyBits);       // of the anchors' distinct keys
+    const size_t key_slots = (size_t)1 << key_bits;
     size_t off = 0, hoff = 0;
     auto take = [&](size_t bytes) { size_t o = off; off += ss_align_up(bytes, 256); return o; };
     auto htake = [&](size_t bytes) { size_t o = hoff; hoff += ss_align_up(bytes, 256); return o; };
@@ -822,9 +833,9 @@ extern "C" int ss_match_sequence(ss_ctx *ctx, const ss_op_t *ref, uint32_t n, co
     const size_t o_ones = take(search ? slots * 8 : 0), o_owner = take(search ? slots * 4 : 0), ones_end = off;
     const size_t o_hist = take(hist ? 2 * (size_t)kTokenLimit * 4 + 256 : 0);
     size_t o_rep[3];
-    for (size_t &o : o_rep) o = take(listed ? slots * 4 : 0);
+    for (size_t &o : o_rep) o = take(listed ? key_slots * 4 : 0);
     size_t o_key[3], o_info[2][3], o_count[2];
-    for (size_t &o : o_key) o = take(listed ? slots * 16 : 0);
+    for (size_t &o : o_key) o = take(listed ? key_slots * 16 : 0);
     const size_t o_n_used = take(listed ? 3 * 4 : 0), zeros_end = off;
     const uint32_t max_keys = (uint32_t)std::min<uint64_t>(kMaxKeys, 3ull * k), lens[2] = {n, m};
     uint32_t chunk_bits[2], chunks[2];
@@ -922,8 +933,9 @@ extern "C" int ss_match_sequence(ss_ctx *ctx, const ss_op_t *ref, uint32_t n, co
           q.count[x] = (uint32_t *)(d + o_count[x]);
         }
         q.n_used = (uint32_t *)(d + o_n_used);
-        q.mask = (uint32_t)(slots - 1);
-        q.shift = 64u - bits;
+        q.mask = (uint32_t)(key_slots - 1);
+        q.shift = 64u - key_bits;
+        q.probes = key_bits < bits ? kProbes : (uint32_t)key_slots;        // else every key has a place
         q.max_keys = max_keys;
         hipLaunchKernelGGL(ss_keys_kernel, dim3((k + 255) / 256, 3), dim3(256), 0, s, g, q);
         if (chunks[0] + chunks[1])
