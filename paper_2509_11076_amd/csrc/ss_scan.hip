@@ -393,7 +393,7 @@ __device__ __forceinline__ Best wg_best(Best b, Best *part) {
   return wave_best(threadIdx.x < T / 64 ? part[threadIdx.x] : no_best());
 }
 
-// at: 2 * (n_ops + 1) entries; pos, net: n_ops entries, may lie in `at`.  A timeline only if the trace fits one pass.
+// at: 2 * (n_ops + 1) entries; pos, net: n_ops entries, may lie in `at`.  No timeline.
 template <int T, int K>
 __device__ __forceinline__ void scan_wg(const ScanArgs &a, OpAt *at, int64_t *pos, int64_t *net, WgShared &sh) {
   const uint32_t n = a.n_ops, tid = threadIdx.x;
@@ -485,18 +485,6 @@ __device__ __forceinline__ void scan_wg(const ScanArgs &a, OpAt *at, int64_t *po
     for (uint32_t t = tid; t < n; t += T)
       put_op(a, t, a.base + at_ev[t + 1].sp + at_pe[t + 1].sp + at_ev[t].sn + at_pe[t].sn, b);
     final_total += at_ev[n].sp + at_ev[n].sn + at_pe[n].sp + at_pe[n].sn;
-    if (a.want_timeline) {
-#pragma unroll
-      for (int k = 0; k < K; ++k) {
-        const Elem &y = x[k];
-        const uint64_t i = (uint64_t)k * T + tid;
-        if (i >= total || !y.live) continue;
-        const bool policy = i >= a.n_ev;
-        const uint32_t e = (uint32_t)(policy ? i - a.n_ev : i);
-        put_event(a, a.timeline, policy, y.pos, (y.pos ? sp[k] : sn[k]) + y.delta, y.pos ? cp[k] : e - cp[k], at_ev[y.op],
-                  at_ev[y.op + 1], at_pe[y.op], at_pe[y.op + 1]);
-      }
-    }
   }
   b = wg_best<T>(b, sh.best);
   if (tid == 0) write_result(a, b, final_total, flags);
@@ -837,9 +825,9 @@ __device__ __forceinline__ TileSum wg_total(int64_t sp, int64_t sn, uint32_t cp,
   return s;
 }
 
-// Sums over events [lo, hi) of the workgroup's list; `copy`: also to where the second launch reads them.
+// Sums over events [lo, hi) of the workgroup's list.
 template <int K>
-__device__ __forceinline__ TileSum sum_events(const ScanArgs &a, const Tile &tl, uint64_t lo, uint64_t hi, bool copy, TileSum *part) {
+__device__ __forceinline__ TileSum sum_events(const ScanArgs &a, const Tile &tl, uint64_t lo, uint64_t hi, TileSum *part) {
   int64_t sp = 0, sn = 0;
   uint32_t cp = 0, flags = 0;
   for (; lo < hi; lo += (uint64_t)kTileThreads * K) {
@@ -847,8 +835,6 @@ __device__ __forceinline__ TileSum sum_events(const ScanArgs &a, const Tile &tl,
     flags |= load_events<kTileThreads, K>(tl.src ? tl.src : tl.L, tl.cnt, nullptr, 0, lo, hi, a.n_ops, x);
 #pragma unroll
     for (int k = 0; k < K; ++k) {
-      if (copy && x[k].live)
-        const_cast<ss_event_t *>(tl.L)[lo + (uint64_t)k * kTileThreads + threadIdx.x] = ss_event_t{x[k].op, 0, x[k].delta};
       sp += x[k].pos ? x[k].delta : 0;
       sn += x[k].pos ? 0 : x[k].delta;
       cp += x[k].pos;
@@ -892,7 +878,7 @@ __global__ __launch_bounds__(kTileThreads) void ss_scan_running_kernel(ScanArgs 
     mine = TileSum{sh.tot_sp, sh.tot_sn, sh.tot_cp, 0};
     for (int i = 0; i < kTileThreads / 64; ++i) mine.flags |= part[i].flags;
   } else {
-    mine = sum_events<K>(a, tl, tl.lo, tl.hi, tl.src != nullptr, part);
+    mine = sum_events<K>(a, tl, tl.lo, tl.hi, part);
   }
   if (tid == 0) put_tile(a.board, tl.index, scan, mine);
   if (blockIdx.x == 0 && tid == 0) a.board->done = 0;
@@ -918,7 +904,7 @@ __global__ __launch_bounds__(kTileThreads) void ss_scan_running_kernel(ScanArgs 
     }
     __syncthreads();                                         // everyone has read its part
     before = wg_total(before.sp, before.sn, before.cp, before.flags, part);
-    if (__syncthreads_or(!there)) before = sum_events<K>(a, tl, 0, tl.lo, false, part);
+    if (__syncthreads_or(!there)) before = sum_events<K>(a, tl, 0, tl.lo, part);
   }
   if (before.flags) return;
   // Where filling gaps is the work it is not done for nothing if the other list is out of order: the policy's tiles wait for
@@ -1106,6 +1092,7 @@ bool is_short(uint64_t n_ev, uint64_t n_pe, uint32_t n_ops, bool timeline) {
 // kernels themselves; a copy call for pageable memory costs 19 to 33 us at 16 to 64 KiB and a copy from pinned memory a
 // launch, the link's time is the same.  Beyond it the copy engine keeps up with the link and the call's cost is small.
 constexpr size_t kMappedBytes = 768 * 1024;
+static_assert(kMappedBytes / sizeof(ss_event_t) <= kMaxTiles * kTileThreads * 2, "only tiles of one pass copy their events");
 
 // Scratch of a long trace from `d` on; returns its size (nothing is assigned where `a` is null).
 size_t scan_scratch(ScanArgs *a, uint8_t *d, uint64_t n_ev, uint64_t n_pe, uint64_t n_ops, bool timeline) {
@@ -1375,7 +1362,7 @@ extern "C" int ss_timeline_scan(ss_ctx *ctx, const ss_event_t *ev, uint64_t n_ev
     const size_t ev_bytes = n_ev * sizeof(ss_event_t), pe_bytes = n_pe * sizeof(ss_event_t);
     const size_t out_bytes = (per_op ? n * 8 : 0) + (mre ? n * 8 : 0) + (timeline ? E * 8 : 0);
     // Short traces: the one kernel reads the events out of pinned memory.  Longer ones: the first kernel does, and copies
-    // them on the way for the other two.  Results are written to pinned memory in both cases.
+    // them on the way for the second.  Results are written to pinned memory in both cases.
     const bool is_small = is_short(n_ev, n_pe, n_ops, timeline != nullptr);
     const bool in_mapped = is_small || ev_bytes + pe_bytes <= kMappedBytes;
     const bool out_mapped = is_small || (in_mapped ? ev_bytes + pe_bytes : 0) + out_bytes <= kMappedBytes;
