@@ -42,7 +42,7 @@ constexpr uint32_t kMaxOpWgs = 256;
 // What the workgroups of a long trace tell each other.  A tile's sums are five words and a maximum is four, each with the
 // number of the scan in its upper half, so that a reader knows each word by itself for this scan's and neither side needs a
 // fence.  `scan` is the last one's number (the second launch sets it); nothing is ever cleared, and what an earlier
-// scan left, finished or not, is not taken for this one's.
+// scan left is not taken for this one's.  Words that no scan has written hold number 0, which none has.
 struct TileBoard {
   uint32_t scan;
   uint32_t done;              // workgroups of the second launch that have ended; the first sets it to 0
@@ -858,7 +858,7 @@ __global__ __launch_bounds__(kTileThreads) void ss_scan_running_kernel(ScanArgs 
   __shared__ SumShared sh;
   __shared__ TileSum part[kTileThreads / 64];
   const Tile tl(a);
-  const uint32_t scan = a.board->scan + 1, tid = threadIdx.x;
+  const uint32_t scan = max(a.board->scan + 1, 1u), tid = threadIdx.x;
   OpAt *const at = a.at + (tl.policy ? (size_t)a.n_ops + 1 : 0);
   Elem x[K];
   int64_t delta[K], xsp[K], xsn[K];
@@ -1440,4 +1440,12 @@ extern "C" void ss_scan_tiling(uint64_t n_ev, uint64_t n_pe, uint32_t n_ops, uin
     out[1 + 2 * l] = t.tile[l];
     out[2 + 2 * l] = t.tiles[l];
   }
+}
+
+// For tests: the number of the scan that the context's last long one had.
+extern "C" int ss_scan_number(ss_ctx *ctx, uint32_t number) {
+  if (!ctx) return SS_E_INVAL;
+  SS_HIP(hipStreamSynchronize(ctx->s_aux));
+  SS_HIP(hipMemcpy(&((TileBoard *)ctx->d_board)->scan, &number, sizeof(number), hipMemcpyHostToDevice));
+  return SS_OK;
 }

@@ -211,3 +211,16 @@ def test_one_list_out_of_order_beside_a_sparse_one(P, ctx, n_ev, n_pe, n_ops):  
     ora = oracle.timeline_scan(ev, pe, n_ops, 0, 1 << 40)
     for a, b in ((ev[::-1].copy(), pe), (ev, pe[::-1].copy())):
         assert_scan_equal(P.ss_timeline_scan(ctx, a, b, n_ops, 0, 1 << 40), ora, timeline=False)
+
+
+def test_the_numbers_of_scans_start_over(P, ctx):                 # noqa: F811
+    """words of the board that no scan has written yet hold 0, so no scan has that number"""
+    import ctypes
+    lib = P._lib
+    lib.ss_scan_number.argtypes, lib.ss_scan_number.restype = [ctypes.c_void_p, ctypes.c_uint32], ctypes.c_int
+    rng = np.random.default_rng(12)
+    assert lib.ss_scan_number(ctx, 0xFFFFFFFE) == 0
+    for n_ev in (5000, 40000, 524288, 9000):                 # more tiles from scan to scan
+        ev, pe = events(rng, n_ev, 3000), events(rng, 2000, 3000)
+        assert_scan_equal(P.ss_timeline_scan(ctx, ev, pe, 3000, 5, 1 << 41, want_timeline=True),
+                          oracle.timeline_scan(ev, pe, 3000, 5, 1 << 41))
