@@ -1003,7 +1003,7 @@ int launch_rows(ss_ctx *ctx, const Layout &y, uint8_t *d, uint8_t *hd, uint32_t 
   const uint32_t *n_keys = (const uint32_t *)(d + y.n_keys);
   const uint32_t per_launch = one_by_one ? 1 : y.strips;
   done = ss_next_done(ctx);
-  done.wgs = y.short_rows ? y.strips : y.walk_blocks;
+  ss_told_by(done, y.short_rows ? y.strips : y.walk_blocks);
   if (y.short_rows) args.done = done;
   for (; args.strip0 < y.strips; args.strip0 += per_launch)
     hipLaunchKernelGGL(ss_align_rows_kernel<Id>, dim3(per_launch), dim3(kRowsThreads), kLds ? lds_need(keys) : 0, s, ref_id,
@@ -1084,9 +1084,10 @@ int ss_align_core(ss_ctx *ctx, const ss_op_t *ref, uint32_t n, const ss_op_t *cu
       const uint32_t wgs = std::min(256u, (std::max(n, m) + 255) / 256), len = std::max(m, id_length(y.n_steps));
       hipLaunchKernelGGL(ss_align_fetch_kernel, dim3(wgs), dim3(256), 0, s, mref, dref, n, mcur, dcur, m, a.rep, y.slots, a.n_keys);
       hipLaunchKernelGGL(ss_align_insert_kernel, dim3((m + 255) / 256), dim3(256), 0, s, a);
-      keys_known = a.done = ss_next_done(ctx);
-      a.done.wgs = (len + 255) / 256;
-      hipLaunchKernelGGL(ss_align_ids_kernel, dim3(a.done.wgs), dim3(256), 0, s, a);
+      a.done = ss_next_done(ctx);
+      ss_told_by(a.done, (len + 255) / 256);
+      keys_known = a.done;
+      hipLaunchKernelGGL(ss_align_ids_kernel, dim3((len + 255) / 256), dim3(256), 0, s, a);
     }
     SS_HIP(hipGetLastError());
     return SS_OK;

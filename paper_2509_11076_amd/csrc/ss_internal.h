@@ -213,8 +213,17 @@ struct ss_done {
 };
 
 // More workgroups than this don't tell, the host waits for the stream: each one's release has its die's second-level cache
-// written back (1,048,574 + 20,014 events, 2,112 workgroups in the scan's second launch: 22.5 us, 5.7 without).
-constexpr uint32_t kTellingWgs = 1024;
+// written back.  us a call that waits for the stream and one that is told: matcher, 125 workgroups in the last kernel 91.5 and
+// 88.5, 313 158.0 and 156.9, 450 208.3 and 208.5, 512 244.1 and 244.8, 1,024 445 and 450; aligner, 250 388 and 379, 344 755.8
+// and 750.4, 407 1,375 and 1,387, 1,016 1,411 and 1,432; scan, 68 68.1 and 66.7, 390 221.3 and 221.9, 615 320.5 and 323.1, 986
+// 481 and 486.
+constexpr uint32_t kTellingWgs = 384;
+
+// Nor does a kernel whose results are then copied to the caller's memory, if the first copy is of more than this (up to there
+// the runtime's copy has a way of its own): behind a wait for the stream such a copy starts sooner than behind a kernel that
+// is still on its way to its end.  Batches of 6 scans with 16 KiB of sums 59.9 us told by the stream and 55.3 by the word, with
+// 24 KiB 53.9 and 57.3; a scan of 28,000 events with a timeline over 9,000 operators 78.8 and 84.
+constexpr size_t kToldCopyBytes = 16u << 10;
 
 static inline void ss_told_by(ss_done &d, uint32_t wgs) {
   if (wgs > kTellingWgs) d = ss_done{};

@@ -1295,8 +1295,11 @@ extern "C" int ss_timeline_scan_batch(ss_ctx *ctx, const ss_event_t *ev, uint64_
       if (n_pe) SS_HIP(hipMemcpyAsync(d + o_pev, pev, pe_bytes, hipMemcpyHostToDevice, s));
     }
     const uint8_t *const in = mapped ? hd : d;
-    ss_done done = ss_next_done(ctx);
-    ss_told_by(done, k);
+    ss_done done = {};
+    if (!per_op || (size_t)k * n * 8 <= kToldCopyBytes) {
+      done = ss_next_done(ctx);
+      ss_told_by(done, k);
+    }
     ScanArgs *ha = (ScanArgs *)h;                       // pinned, read and written by the kernel: arguments, results
     for (uint32_t c = 0; c < k; ++c) {
       uint8_t *w = d + o_work + (size_t)c * per_scan;
@@ -1401,7 +1404,7 @@ extern "C" int ss_timeline_scan(ss_ctx *ctx, const ss_event_t *ev, uint64_t n_ev
     a.mre = mre ? (int64_t *)(out + o_mre) : nullptr;
     a.timeline = timeline ? (int64_t *)(out + o_tl) : nullptr;
     a.res = (ss_scan_result_t *)(hd + o_res);
-    a.done = ss_next_done(ctx);
+    if (out_mapped || (per_op || mre ? n : E) * 8 <= kToldCopyBytes) a.done = ss_next_done(ctx);
     launch_scan(s, a);
     SS_HIP(hipGetLastError());
     if ((rc = ss_wait_done(ctx, a.done)) != SS_OK) return rc;

@@ -102,6 +102,7 @@ def test_the_definition_here_is_the_oracles(P):                   # noqa: F811
     (500, 2047, 12, 9), (500, 2048, 12, 9), (600, 2048, 12, 9), (63, 70000, 9, 3),           # short, many anchors: a wavefront each
     (9001, 32768, 30, 40), (9001, 32769, 30, 40), (40000, 32769, 200, 1 << 30),              # keys' tables of all anchors | of some
     (3000, 40000, 500, 1 << 30), (150000, 150000, 200, 1 << 30),                             # nearly too many keys | more than slots
+    (3000, 98304, 9, 4), (3000, 98305, 9, 4),                                                # results told by the word | by the stream
     (16385, 5, 3, 2), (65537, 5, 3, 2), (262145, 5, 3, 2),                                   # turns of the first pass
 ])
 def test_forms(P, ctx, n, k, tokens, stacks):                     # noqa: F811
