@@ -946,17 +946,24 @@ __global__ __launch_bounds__(kTileThreads) void ss_scan_running_kernel(ScanArgs 
 
 constexpr int kGatherK = 1;
 
-// true in the workgroup that ends last of `wgs` that call this; what the others wrote before is visible to it
+// Up to this many events one workgroup gathers them all and goes on with the operators: 290 events out of order over 8,045
+// operators 26.9 us, gathered by all workgroups 29.5; 1,000 + 500 over 4,000 19.6 and 21.4; but 2,000 in random order over
+// 8,000 31.2 and 29.6, and 4,000 over 3,000 26.0 and 19.4.
+constexpr uint64_t kGatherAlone = 1536;
+
+// true in the workgroup that ends last of `wgs` that call this; what the others wrote before is visible to it.  One release a
+// workgroup, and an acquire in the last one (fences both ways in all its wavefronts: 8,000 + 100 events out of order over 5,000
+// operators 23.3 us, so 21.7).
 __device__ __forceinline__ bool ends_last(TileBoard *b, uint32_t wgs, uint32_t *s_last) {
   asm volatile("s_waitcnt vmcnt(0)" ::: "memory");           // this wavefront's stores and atomics are complete
   __syncthreads();
   if (threadIdx.x == 0) {
-    __threadfence();                                         // for the workgroup (one fence each: 64 workgroups' 1,024 took 14 us)
-    *s_last = atomicAdd(&b->done, 1u) + 1 == wgs;
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");       // for the workgroup (one fence each: 64 workgroups' 1,024 took 14 us)
+    *s_last = __hip_atomic_fetch_add(&b->done, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) + 1 == wgs;
   }
   __syncthreads();
   if (!*s_last) return false;
-  __threadfence();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
   return true;
 }
 
@@ -988,13 +995,22 @@ __device__ __forceinline__ void scan_finish(const ScanArgs &a, uint32_t op_wgs, 
     return;
   }
   if (flags) {
-    for (uint64_t first = (uint64_t)blockIdx.x * kThreads * kGatherK; first < total; first += (uint64_t)gridDim.x * kThreads * kGatherK) {
+    const bool alone = total <= kGatherAlone;
+    if (alone && blockIdx.x) return;
+    const uint32_t wgs = alone ? 1 : gridDim.x;
+    for (uint64_t first = (uint64_t)blockIdx.x * kThreads * kGatherK; first < total; first += (uint64_t)wgs * kThreads * kGatherK) {
       Elem x[kGatherK];
       load_events<kThreads, kGatherK>(a.ev, a.n_ev, a.pev, a.n_pe, first, total, n, x);
 #pragma unroll
       for (int k = 0; k < kGatherK; ++k) gather_run(a.pos, a.net, x[k], n);
     }
-    if (!ends_last(a.board, gridDim.x, &sh.last)) return;
+    if (alone) {
+      __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
+      __syncthreads();
+      __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
+    } else if (!ends_last(a.board, wgs, &sh.last)) {
+      return;
+    }
     Best b = ops_of_sums<kThreads>(a, a.pos, a.net, sh.sums);
     b = wg_best<kThreads>(b, sh.part);
     if (tid == 0) write_result(a, b, a.base + (n ? sh.sums.tot_sp : 0), flags);

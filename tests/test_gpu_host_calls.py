@@ -109,3 +109,22 @@ def test_the_word_comes_after_every_result_of_earlier_kernels(P, ctx, what, n, k
             ora = oracle.align_anchors(oracle.ops_tuples(ref), oracle.ops_tuples(cur), [])
             assert np.array_equal(got["ref_to_cur"], ora["ref_to_cur"])
     in_turn(call, want)
+
+
+@pytest.mark.parametrize("n_ev,n_pe,n_ops", [(1000, 400, 9000), (9000, 3000, 6000), (60000, 20, 30000)])
+def test_lists_out_of_order_in_turn(P, ctx, n_ev, n_pe, n_ops):                      # noqa: F811
+    """the sums that other workgroups gathered are there for the one that does the operators"""
+    import oracle
+    rng = np.random.default_rng([n_ev, n_ops, 9])
+    inputs, want = [], []
+    for base in (5, 1 << 50):
+        ev, pe = events(rng, n_ev, n_ops), events(rng, n_pe, n_ops)
+        ora = oracle.timeline_scan(ev, pe, n_ops, base, 1 << 40)
+        inputs.append((ev[rng.permutation(n_ev)], pe[::-1].copy(), base))
+        want.append(dict(per_op=ora["per_op"], mre=ora["mre"], peak=ora["peak"], argpeak_op=ora["argpeak_op"], final=ora["final"]))
+
+    def call(i):
+        ev, pe, base = inputs[i]
+        r = P.ss_timeline_scan(ctx, ev, pe, n_ops, base, 1 << 40)
+        return {k: r[k] for k in want[i]}
+    in_turn(call, want)

@@ -59,7 +59,8 @@ def test_operators_without_events_and_events_of_one_operator(P, ctx):       # no
         both_ways(P, ctx, ev, pe, n_ops, 1 << 45, 0)
 
 
-@pytest.mark.parametrize("n_ev,n_pe,n_ops", [(700, 200, 66), (3000, 100, 700), (300, 20, 5000), (9000, 4000, 700), (70000, 50, 9000)])
+@pytest.mark.parametrize("n_ev,n_pe,n_ops", [(700, 200, 66), (3000, 100, 700), (300, 20, 5000), (9000, 4000, 700), (70000, 50, 9000),
+                                             (1500, 36, 4000), (1500, 37, 4000)])      # gathered by one workgroup | by all
 def test_lists_out_of_order_give_the_same_operators(P, ctx, n_ev, n_pe, n_ops):      # noqa: F811
     import torch
     rng = np.random.default_rng([n_ev, n_pe, n_ops, 1])
