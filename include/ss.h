@@ -386,10 +386,11 @@ int ss_timeline_scan_batch(ss_ctx *ctx, const ss_event_t *ev, uint64_t n_ev, con
 /* For callers that cannot allocate (code under HIP graph capture, tight serving loops, harnesses
  * that forbid hipMalloc): the scan of ss_timeline_scan with nothing allocated, copied or waited
  * for.  Inputs and outputs are the caller's DEVICE arrays (same meaning, sizes and nullability as
- * above; d_res is required); the kernel's scratch is a static device array of 7.1 MiB that every GPU
- * the library runs on holds until the process ends.  The call enqueues one kernel (three beyond 4,096
- * events or 2,900 operators) on `stream` (a hipStream_t of the context's device, which must be
- * current; NULL = the null stream) and returns; results are valid once that stream has reached the kernel's end.
+ * above; d_res is required); the kernels' scratch is 7.1 MiB of a static device array (9.9 MiB) that every GPU
+ * the library runs on holds until the process ends.  The call enqueues one kernel (two for a long trace: beyond
+ * 4,096 events, with each list rounded up to whole wavefronts, or 2,900 operators) on `stream` (a hipStream_t of
+ * the context's device, which must be current; NULL = the null stream) and returns; results are valid once that
+ * stream has reached the kernel's end.
  * Limits: n_ops <= 65,536 and n_ev + n_pe <= 262,144, else SS_E_CAPACITY (nothing is enqueued).
  * Errors the kernel finds are reported in d_res->reserved: bit 0 = an event names an operator
  * >= n_ops (no other output is meaningful), bit 1 = a list is not in operator order (d_res->sorted
