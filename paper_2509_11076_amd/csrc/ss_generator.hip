@@ -14,6 +14,7 @@ namespace {
 struct Layer {
   uint32_t first, end;     // operators [first, end)
   uint32_t type;           // 0 forward, 1 backward, 2 optimizer
+  uint32_t lo, hi;         // its operators among its phase's: [lo, hi)
   int64_t remaining;       // link bytes still free in this layer
   uint64_t bpo;            // link bytes one operator of this layer is worth (Eq. 1)
 };
@@ -25,178 +26,236 @@ struct Chosen {
 
 typedef unsigned __int128 u128;
 
-// Cut the operators of each phase, in execution order, into groups of (almost) equal count.
-void build_layers(const std::vector<uint32_t> &phase, uint32_t g_fwd, uint32_t g_bwd, const uint64_t bpo[3],
-                  std::vector<Layer> &layers, std::vector<uint32_t> &layer_of) {
-  const uint32_t n = (uint32_t)phase.size();
-  struct Raw { Layer L; std::vector<uint32_t> ops; };
-  std::vector<Raw> raw;
-  const uint32_t groups[3] = {g_fwd, g_bwd, 1};
-  for (uint32_t ph = 0; ph < 3; ++ph) {
-    std::vector<uint32_t> idx;
-    for (uint32_t i = 0; i < n; ++i)
-      if (phase[i] == ph) idx.push_back(i);
-    if (idx.empty()) continue;
-    const uint64_t G = std::max<uint64_t>(1, std::min<uint64_t>(groups[ph], idx.size()));
-    for (uint64_t g = 0; g < G; ++g) {
-      const size_t lo = (size_t)(g * idx.size() / G), hi = (size_t)((g + 1) * idx.size() / G);
-      if (hi <= lo) continue;
-      Raw r;
-      r.L = Layer{idx[lo], idx[hi - 1] + 1, ph, (int64_t)(bpo[ph] * (hi - lo)), bpo[ph]};
-      r.ops.assign(idx.begin() + lo, idx.begin() + hi);
-      raw.push_back(std::move(r));
+// What the parameter sets of a call share.  Entries are the operators over the limit (the memory reduction list of Sec. 4.2);
+// there are far fewer of them than operators (67 of 700 at 90 % of the peak), and all that is asked of the list is asked for
+// a stretch of it.
+struct Shared {
+  std::vector<uint32_t> ops_of[3];     // operators of each phase, in execution order
+  std::vector<uint32_t> entry_op;      // operators of the entries
+  std::vector<uint32_t> before;        // [n_ops + 1]: entries before the operator
+  std::vector<int64_t> excess;         // of the entries
+  // tensors that can be away from some entry: operators t with last_fwd_use + 1 < t < first_bwd_use
+  struct Away { uint32_t row, lo, hi, id, last_fwd, first_bwd; uint64_t size; };
+  std::vector<Away> away;
+};
+
+void share(const ss_op_t *ops, uint32_t n_ops, const ss_tensor_t *tensors, uint32_t n_tensors, const std::vector<int64_t> &per_op,
+           int64_t limit, Shared &s) {
+  s.before.resize(n_ops + 1);
+  s.ops_of[0].reserve(n_ops);
+  s.away.reserve(n_tensors);
+  for (uint32_t i = 0; i < n_ops; ++i) {
+    s.ops_of[std::min<uint32_t>(ops[i].sig >> 16, 2u)].push_back(i);
+    s.before[i] = (uint32_t)s.entry_op.size();
+    if (per_op[i] > limit) {
+      s.entry_op.push_back(i);
+      s.excess.push_back(per_op[i] - limit);
     }
   }
-  std::sort(raw.begin(), raw.end(), [](const Raw &a, const Raw &b) { return a.L.first < b.L.first; });
-  layers.clear();
-  layer_of.assign(n, 0);
-  for (size_t li = 0; li < raw.size(); ++li) {
-    layers.push_back(raw[li].L);
-    for (uint32_t i : raw[li].ops) layer_of[i] = (uint32_t)li;
+  s.before[n_ops] = (uint32_t)s.entry_op.size();
+  for (uint32_t r = 0; r < n_tensors; ++r) {
+    const ss_tensor_t &t = tensors[r];
+    if (t.last_fwd_use == SS_NONE_OP || t.first_bwd_use == SS_NONE_OP || t.last_fwd_use >= t.first_bwd_use || t.first_bwd_use >= n_ops ||
+        t.last_fwd_use + 2 >= t.first_bwd_use)
+      continue;
+    const uint32_t lo = s.before[t.last_fwd_use + 2], hi = s.before[t.first_bwd_use];
+    if (lo < hi) s.away.push_back({r, lo, hi, t.tensor_id, t.last_fwd_use, t.first_bwd_use, t.nbytes});
   }
 }
 
+// The entries that are left, as a bit map with a second one over its words.
+struct Entries {
+  std::vector<uint64_t> word, some;
+  std::vector<uint32_t> upto;          // entries left before each (before each word, if there are many), as of the last count()
+  uint32_t left = 0, shift = 0;
+  void all(uint32_t n, bool many) {
+    left = n;
+    shift = many ? 6 : 0;
+    word.assign(n / 64 + 1, ~0ull);
+    word[n / 64] = (1ull << n % 64) - 1;
+    some.assign(word.size() / 64 + 1, 0);
+    for (size_t w = 0; w < word.size(); ++w) some[w / 64] |= (uint64_t)(word[w] != 0) << w % 64;
+    upto.resize((n >> shift) + 1);
+  }
+  bool has(uint32_t e) const { return word[e / 64] >> e % 64 & 1u; }
+  void take(uint32_t w, uint64_t gone) {
+    left -= (uint32_t)__builtin_popcountll(gone);
+    if (!(word[w] &= ~gone)) some[w / 64] &= ~(1ull << w % 64);
+  }
+  void count() {
+    uint32_t c = 0;
+    for (size_t i = 0; i < upto.size(); ++i) {
+      upto[i] = c;
+      c += shift ? (uint32_t)__builtin_popcountll(word[i]) : has((uint32_t)i);
+    }
+  }
+  uint32_t rank(uint32_t e) const {
+    return shift ? upto[e / 64] + (uint32_t)__builtin_popcountll(word[e / 64] & ((1ull << e % 64) - 1)) : upto[e];
+  }
+  // the last one in [lo, hi), or -1
+  int64_t last(uint32_t lo, uint32_t hi) const {
+    uint64_t x = word[hi / 64] & ((1ull << hi % 64) - 1);
+    uint32_t w = hi / 64;
+    if (!x) {
+      uint64_t y = some[w / 64] & ((1ull << w % 64) - 1);
+      uint32_t v = w / 64;
+      while (!y && v) y = some[--v];
+      if (!y) return -1;
+      w = v * 64 + 63 - (uint32_t)__builtin_clzll(y);
+      x = word[w];
+    }
+    const uint32_t e = w * 64 + 63 - (uint32_t)__builtin_clzll(x);
+    return e >= lo ? (int64_t)e : -1;
+  }
+};
+
+// Cut the operators of each phase, in execution order, into groups of (almost) equal count.
+void build_layers(const Shared &s, uint32_t n_ops, uint32_t g_fwd, uint32_t g_bwd, const uint64_t bpo[3], std::vector<Layer> &layers,
+                  std::vector<uint32_t> &layer_of) {
+  const uint32_t groups[3] = {g_fwd, g_bwd, 1};
+  layers.clear();
+  for (uint32_t ph = 0; ph < 3; ++ph) {
+    const std::vector<uint32_t> &idx = s.ops_of[ph];
+    const uint64_t G = std::min<uint64_t>(groups[ph], idx.size());
+    for (uint64_t g = 0; g < G; ++g) {
+      const uint32_t lo = (uint32_t)(g * idx.size() / G), hi = (uint32_t)((g + 1) * idx.size() / G);
+      layers.push_back(Layer{idx[lo], idx[hi - 1] + 1, ph, lo, hi, (int64_t)(bpo[ph] * (hi - lo)), bpo[ph]});
+    }
+  }
+  std::sort(layers.begin(), layers.end(), [](const Layer &a, const Layer &b) { return a.first < b.first; });
+  layer_of.resize(n_ops);
+  for (uint32_t li = 0; li < layers.size(); ++li)
+    for (uint32_t i = layers[li].lo; i < layers[li].hi; ++i) layer_of[s.ops_of[layers[li].type][i]] = li;
+}
+
+// What generate_core works with; kept from one set to the next.
+struct Work {
+  std::vector<Layer> layers;
+  std::vector<uint32_t> layer_of, order;
+  std::vector<int64_t> excess;
+  Entries entries;
+  std::vector<uint8_t> taken;
+  std::vector<Chosen> chosen;
+  struct Cand { uint32_t at, n_mre; u128 key; };
+  std::vector<Cand> list;
+};
+
 }  // namespace
 
-// The generator proper: per_op is the memory without swaps (n_ops entries).  Fills `items` in commit
-// order and the counters of `res` that do not need a scan.
-static int generate_core(uint64_t bpo, const ss_op_t *ops, uint32_t n_ops, const ss_tensor_t *tensors,
-                         uint32_t n_tensors, const std::vector<int64_t> &per_op, int64_t limit,
-                         const ss_gen_params_t *params, std::vector<ss_policy_item_t> &items,
-                         std::vector<ss_event_t> &pe, ss_gen_result_t *res) {
-  if (params->c_den == 0 || params->g_fwd == 0 || params->g_bwd == 0) return SS_E_INVAL;
-  std::vector<int64_t> excess(n_ops, 0);
-  uint32_t n_entries = 0;
-  for (uint32_t t = 0; t < n_ops; ++t)
-    if (per_op[t] > limit) { excess[t] = per_op[t] - limit; ++n_entries; }
-  std::vector<uint32_t> phase(n_ops);
-  for (uint32_t i = 0; i < n_ops; ++i) phase[i] = std::min<uint32_t>(ops[i].sig >> 16, 2u);
-  std::vector<Layer> layers;
-  std::vector<uint32_t> layer_of;
+// The generator proper.  Fills `items` in commit order and the counters of `res` that do not need a scan.
+// Bound by the host's work on lists of some hundred elements.  Entries over the limit are kept as a bit map, so that how many a
+// tensor can be away from, the last of them and their reduction cost what is left of the list and not the length of the trace; the
+// tensors' stretches of it are found once for all sets.  A round ranks little more than the candidates that it commits, and in one
+// that can commit none (it then accepts a late tensor) only the best is looked for.  Six sets, on one core: 700 operators, 67
+// entries, 60 items 30 us (spans counted over all operators, candidates sorted whole: 105); 265 operators, 24 entries, with sets
+// that run out of candidates 198 (647); one of 65,536 operators with 4,000 long spans 7.4 ms (12.6).  The call of the first with
+// its scans 56 us (98).
+static int generate_core(uint64_t bpo, const Shared &s, Work &k, uint32_t n_ops, const ss_tensor_t *tensors, const ss_gen_params_t *params,
+                         std::vector<ss_policy_item_t> &items, std::vector<ss_event_t> &pe, ss_gen_result_t *res) {
   uint64_t bpo3[3];
   for (int ph = 0; ph < 3; ++ph) bpo3[ph] = params->phase_bytes_per_op[ph] ? params->phase_bytes_per_op[ph] : bpo;
-  build_layers(phase, params->g_fwd, params->g_bwd, bpo3, layers, layer_of);
+  std::vector<Layer> &layers = k.layers;
+  std::vector<uint32_t> &layer_of = k.layer_of;
+  build_layers(s, n_ops, params->g_fwd, params->g_bwd, bpo3, layers, layer_of);
+  k.excess = s.excess;
+  const uint32_t n_entries = (uint32_t)s.entry_op.size();
+  k.entries.all(n_entries, n_entries > 4 * s.away.size());
+  k.taken.assign(s.away.size(), 0);
+  std::vector<Chosen> &chosen = k.chosen;
+  chosen.clear();
 
-  // Entries the tensor can be away from: operators t with last_fwd_use + 1 < t < first_bwd_use.  How many there are is
-  // asked for every tensor once a round, with no commit in between: a prefix count.  The last of them is asked for one
-  // tensor at a time while entries go: up[t + 1] leads to the last entry at or before t (0 = none; entries only ever go,
-  // so paths are shortened as they are walked).  Walking the spans instead was most of the generator's time (336 tensors
-  // over 700 operators: 80 of 83 us a parameter set).  Only where the spans that are left are shorter, together, than the
-  // trace are they walked: 500 of up to 10 operators in a trace of 65,536, 250 rounds, 6.0 ms against 13.2.
-  auto usable = [&](const ss_tensor_t &t) {
-    return t.last_fwd_use != SS_NONE_OP && t.first_bwd_use != SS_NONE_OP && t.last_fwd_use < t.first_bwd_use &&
-           t.first_bwd_use < n_ops && t.nbytes >= params->min_bytes;
-  };
-  auto span = [&](const ss_tensor_t &t, uint32_t &lo, uint32_t &hi) {
-    lo = (uint32_t)std::min<uint64_t>((uint64_t)t.last_fwd_use + 2, n_ops);
-    hi = std::min(t.first_bwd_use, n_ops);
-    return lo < hi;
-  };
-  uint64_t walk = 0;                                    // spans of those that can be taken, as far as it matters here
-  for (uint32_t r = 0; walk <= n_ops && r < n_tensors; ++r) {
-    uint32_t lo, hi;
-    if (usable(tensors[r]) && span(tensors[r], lo, hi)) walk += hi - lo;
-  }
-  std::vector<uint32_t> before, up;
-  if (walk > n_ops) {
-    before.assign(n_ops + 1, 0);
-    up.assign(n_ops + 1, 0);
-    for (uint32_t t = 0; t < n_ops; ++t) up[t + 1] = excess[t] > 0 ? t + 1 : up[t];
-  }
-  auto last_entry = [&](const ss_tensor_t &t) -> int64_t {
-    uint32_t lo, hi;
-    if (!span(t, lo, hi)) return -1;
-    uint32_t x = hi;                                    // up[hi]: at or before operator hi - 1
-    if (up.empty()) {
-      while (x > lo && !(excess[x - 1] > 0)) --x;
-      return x > lo ? (int64_t)x - 1 : -1;
+  auto commit = [&](uint32_t at, uint32_t L_in, bool late) {
+    const Shared::Away &a = s.away[at];
+    const uint32_t t_in = layers[L_in].first, hi = s.before[t_in];
+    layers[L_in].remaining -= (int64_t)a.size;
+    for (uint32_t w = a.lo / 64; w * 64 < hi; ++w) {
+      uint64_t here = k.entries.word[w], gone = 0;
+      if (w == a.lo / 64) here &= ~0ull << a.lo % 64;
+      if (hi - w * 64 < 64) here &= (1ull << hi % 64) - 1;
+      int64_t *const excess = k.excess.data() + (size_t)w * 64;
+      if (here == ~0ull)
+        for (uint32_t b = 0; b < 64; ++b) gone |= (uint64_t)((excess[b] -= (int64_t)a.size) <= 0) << b;
+      else
+        for (uint64_t x = here; x; x &= x - 1) {
+          const uint32_t b = (uint32_t)__builtin_ctzll(x);
+          gone |= (uint64_t)((excess[b] -= (int64_t)a.size) <= 0) << b;
+        }
+      if (gone) k.entries.take(w, gone);
     }
-    while (x && !(excess[x - 1] > 0)) {
-      const uint32_t y = up[x] == x ? x - 1 : up[x];
-      up[x] = y && up[y] != y ? up[y] : y;
-      x = y;
-    }
-    return x > lo ? (int64_t)x - 1 : -1;
+    k.taken[at] = 1;
+    chosen.push_back(Chosen{a.row, L_in, t_in, 0, late});
   };
-
-  std::vector<uint8_t> taken(n_tensors, 0);
-  std::vector<Chosen> chosen;
-  auto commit = [&](uint32_t row, uint32_t L_in, bool late) {
-    const ss_tensor_t &t = tensors[row];
-    const uint32_t t_in = layers[L_in].first;
-    layers[L_in].remaining -= (int64_t)t.nbytes;
-    for (uint64_t op = (uint64_t)t.last_fwd_use + 2; op < t_in; ++op)
-      if (excess[op] > 0) {
-        excess[op] -= (int64_t)t.nbytes;
-        if (excess[op] <= 0) { excess[op] = 0; --n_entries; }
-      }
-    taken[row] = 1;
-    chosen.push_back(Chosen{row, L_in, t_in, 0, late});
+  // pre-trigger swap-in (Sec. 4.3.1): the latest layer between the last entry and the use that has the time, or -1
+  auto layer_in = [&](uint32_t at) -> int64_t {
+    const Shared::Away &a = s.away[at];
+    const int64_t last = k.entries.last(a.lo, a.hi);
+    if (last < 0) return -1;
+    const uint32_t L_use = layer_of[a.first_bwd], L_peak = layer_of[s.entry_op[(size_t)last]];
+    for (int64_t L = (int64_t)L_use - 1; L > (int64_t)L_peak; --L)
+      if (layers[(size_t)L].remaining > (int64_t)a.size) return L;
+    return -1;
   };
-
-  struct Cand { uint32_t row, n_mre; uint64_t size; u128 key; };
-  while (n_entries) {                                   // Algo. 2
-    std::vector<Cand> cl;
-    const bool counted = walk > n_ops;                  // never again once it is not
-    if (counted)
-      for (uint32_t t = 0; t < n_ops; ++t) before[t + 1] = before[t] + (excess[t] > 0);
-    walk = 0;                                           // for the next round: what is left now
+  using Cand = Work::Cand;
+  std::vector<Cand> &cl = k.list;
+  auto above = [&](const Cand &x, const Cand &y) {
+    if (x.key != y.key) return x.key > y.key;
+    const Shared::Away &a = s.away[x.at], &b = s.away[y.at];
+    if (a.size != b.size) return a.size > b.size;
+    return a.id != b.id ? a.id < b.id : x.at < y.at;
+  };
+  while (k.entries.left) {                              // Algo. 2
+    cl.clear();
+    const bool whole = k.entries.left == n_entries;
+    if (!whole) k.entries.count();
     uint32_t max_n = 0;
     uint64_t max_s = 0;
-    for (uint32_t r = 0; r < n_tensors; ++r) {
-      if (taken[r] || !usable(tensors[r])) continue;
-      uint32_t lo, hi, c = 0;
-      if (!span(tensors[r], lo, hi)) continue;
-      walk += hi - lo;
-      if (counted) c = before[hi] - before[lo];
-      else
-        for (uint32_t op = lo; op < hi; ++op) c += excess[op] > 0;
+    for (uint32_t at = 0; at < s.away.size(); ++at) {
+      const Shared::Away &a = s.away[at];
+      if (k.taken[at] || a.size < params->min_bytes) continue;
+      const uint32_t c = whole ? a.hi - a.lo : k.entries.rank(a.hi) - k.entries.rank(a.lo);
       if (!c) continue;
-      cl.push_back(Cand{r, c, tensors[r].nbytes, 0});
+      cl.push_back(Cand{at, c, 0});
       max_n = std::max(max_n, c);
-      max_s = std::max(max_s, tensors[r].nbytes);
+      max_s = std::max(max_s, a.size);
     }
     if (cl.empty()) return SS_E_INFEASIBLE;             // "Raise Error"
     for (Cand &c : cl)                                  // Eq. 2, scaled to integers
-      c.key = (u128)c.n_mre * max_s * params->c_den + (u128)params->c_num * c.size * max_n;
-    std::sort(cl.begin(), cl.end(), [&](const Cand &a, const Cand &b) {
-      if (a.key != b.key) return a.key > b.key;
-      if (a.size != b.size) return a.size > b.size;
-      return tensors[a.row].tensor_id < tensors[b.row].tensor_id;
-    });
+      c.key = (u128)c.n_mre * max_s * params->c_den + (u128)params->c_num * s.away[c.at].size * max_n;
     res->n_rounds++;
 
-    uint32_t committed = 0;
-    for (const Cand &c : cl) {                          // pre-trigger swap-in (Sec. 4.3.1)
-      if (!n_entries) break;
-      const ss_tensor_t &t = tensors[c.row];
-      const int64_t last = last_entry(t);
-      if (last < 0) continue;
-      const uint32_t L_use = layer_of[t.first_bwd_use], L_peak = layer_of[(uint32_t)last];
-      for (int64_t L = (int64_t)L_use - 1; L > (int64_t)L_peak; --L)
-        if (layers[(size_t)L].remaining > (int64_t)t.nbytes) {
-          commit(c.row, (uint32_t)L, false);
-          ++committed;
-          break;
+    size_t some = 0;                                    // until something is committed nothing changes: can anything be?
+    while (some < cl.size() && layer_in(cl[some].at) < 0) ++some;
+    if (some < cl.size()) {
+      size_t ranked = 0;
+      for (size_t i = 0; i < cl.size() && k.entries.left; ++i) {
+        if (i == ranked) {                              // the next ones in order, as many again
+          const size_t end = std::min(cl.size(), std::max<size_t>(16, 2 * ranked));
+          if (end < cl.size()) std::nth_element(cl.begin() + ranked, cl.begin() + end, cl.end(), above);
+          std::sort(cl.begin() + ranked, cl.begin() + end, above);
+          ranked = end;
         }
-    }
-    if (!committed && n_entries) {                      // accept latency rather than stop
-      for (const Cand &c : cl) {
-        const ss_tensor_t &t = tensors[c.row];
-        if (last_entry(t) < 0) continue;
-        const uint32_t L_use = layer_of[t.first_bwd_use];
-        const uint32_t L_in = std::max<uint32_t>(L_use ? L_use - 1 : 0, layer_of[t.last_fwd_use] + 1);
-        if (L_in > L_use) continue;
-        commit(c.row, L_in, true);
-        ++committed;
-        break;
+        const int64_t L = layer_in(cl[i].at);
+        if (L >= 0) commit(cl[i].at, (uint32_t)L, false);
       }
-      if (!committed) return SS_E_INFEASIBLE;
+      continue;
     }
+    const Cand *best = nullptr;                         // accept latency rather than stop
+    uint32_t best_in = 0;
+    for (const Cand &c : cl) {
+      const Shared::Away &a = s.away[c.at];
+      const uint32_t L_use = layer_of[a.first_bwd];
+      const uint32_t L_in = std::max<uint32_t>(L_use ? L_use - 1 : 0, layer_of[a.last_fwd] + 1);
+      if (L_in > L_use || (best && !above(c, *best))) continue;
+      best = &c;
+      best_in = L_in;
+    }
+    if (!best) return SS_E_INFEASIBLE;
+    commit(best->at, best_in, true);
   }
 
   // SetFreeTime: swap-out completion in swap-out order (Sec. 4.3.2)
-  std::vector<uint32_t> order(chosen.size());
+  std::vector<uint32_t> &order = k.order;
+  order.resize(chosen.size());
   for (uint32_t i = 0; i < order.size(); ++i) order[i] = i;
   std::sort(order.begin(), order.end(), [&](uint32_t x, uint32_t y) {
     const ss_tensor_t &a = tensors[chosen[x].row], &b = tensors[chosen[y].row];
@@ -293,10 +352,12 @@ extern "C" int ss_generate_policy_best(ss_ctx *ctx, const ss_op_t *ops, uint32_t
     std::vector<ss_event_t> all_pe;
     std::vector<uint64_t> pe_start(n_params + 1, 0);
     bool any = false;
+    Shared shared;
+    Work work;
+    share(ops, n_ops, tensors, n_tensors, per_op, limit, shared);
     for (uint32_t c = 0; c < n_params; ++c) {
       std::memset(&cands[c].r, 0, sizeof(ss_gen_result_t));
-      cands[c].rc = generate_core(bpo, ops, n_ops, tensors, n_tensors, per_op, limit, &params[c], cands[c].items,
-                                  cands[c].pe, &cands[c].r);
+      cands[c].rc = generate_core(bpo, shared, work, n_ops, tensors, &params[c], cands[c].items, cands[c].pe, &cands[c].r);
       if (cands[c].rc != SS_OK && cands[c].rc != SS_E_INFEASIBLE) return cands[c].rc;
       if (cands[c].rc != SS_OK) cands[c].pe.clear();
       any = any || cands[c].rc == SS_OK;
