@@ -663,15 +663,18 @@ __global__ __launch_bounds__(kWgThreads) void ss_align_short_kernel(KeyArgs k, R
 // group's entry known the blocks are walked again side by side to write the pairs (ss_align_pairs_kernel).  Where a group's
 // table has no entry the chain follows its blocks' own, and a block whose entry lies outside its window, or whose path
 // leaves the tile to the left, is walked in place by a wavefront of the chain.
-// 32,312 rows: 64 us for the tables, 5 us for the groups' and 17 us for the chain (an LDS read and its way through the
-// scalar unit per group; 90 us block by block), 30 us for the pairs; single steps in one wavefront took 97 ns a row (3.1
+// 32,312 rows: 48 us for the tables, 5 us for the groups' and 17 us for the chain (an LDS read and its way through the
+// scalar unit per group; 90 us block by block), 14 us for the pairs; single steps in one wavefront took 97 ns a row (3.1
 // ms), the rows over the host link (130 MB) 2.3 ms and a walk there.
 constexpr uint32_t kWalkRows = 64;
 constexpr uint32_t kWindow = 2048;                     // entry columns tabulated per block of rows
 constexpr uint32_t kEntries = 256;                     // of these, per workgroup
 constexpr uint32_t kMargin = 256;                      // columns a tile reaches to the left of its first entry
 constexpr uint32_t kTileWords = (kEntries + kMargin) / 32;
-constexpr uint32_t kTileStride = kTileWords + 1;
+// A word of a tile: columns that are equal, and those where the walk stops (equal, or it steps up).  In front of a row's first is
+// one without a stop.
+struct TileWord { uint32_t stops, equal; };
+typedef TileWord Tile[kWalkRows][kTileWords + 1];
 constexpr uint16_t kNoEntry = 0xFFFF;
 
 // rows of block k (counted from the end): [lo, hi)
@@ -686,48 +689,83 @@ __device__ __forceinline__ uint32_t window_start(uint32_t k, uint32_t n, uint32_
   return (mid > kWindow / 2 ? mid - kWindow / 2 : 0) / kEntries * kEntries;
 }
 
-// M and X = M | ~V of rows [lo, hi) and kTileWords words from word w0 on (w0 may be negative: empty); a step of the
-// row buffer holds consecutive words of consecutive rows, so threads run along it
+// 0 to 31, or all ones for 0
+__device__ __forceinline__ uint32_t leading_zeros(uint32_t x) {
+  uint32_t n;
+  asm("v_ffbh_u32_e32 %0, %1" : "=v"(n) : "v"(x));
+  return n;
+}
+
+// Rows [lo, hi) and kTileWords words from word w0 on (w0 may be negative: empty); stops = M | ~V.  A step of the row buffer holds
+// consecutive words of consecutive rows, so threads run along it there, and along a mask row for the masks; each thread's loads are
+// all on their way before the first is waited for.
+constexpr uint32_t kTileThreads = 256;
+
 template <class Id>
 __device__ __forceinline__ void load_tile(const Id *ref_id, const uint32_t *masks, const uint32_t *rows, uint32_t W,
-                                          uint32_t n_steps, RowBlock blk, int w0, uint32_t (*M)[kTileStride],
-                                          uint32_t (*X)[kTileStride]) {
-  const uint32_t n_rows = blk.hi - blk.lo;
-  for (uint32_t i = threadIdx.x; i < (kWalkRows + kSkew * kTileWords) * kTileWords; i += blockDim.x) {
-    const uint32_t l = i % kTileWords, t = i / kTileWords, back = kSkew * l;       // row lo + t - back
+                                          uint32_t n_steps, RowBlock blk, int w0, Tile &tile) {
+  constexpr uint32_t kMasks = kWalkRows * kTileWords / kTileThreads, kRows = (kWalkRows + kSkew * kTileWords) * kTileWords / kTileThreads;
+  static_assert(kMasks * kTileThreads == kWalkRows * kTileWords && kRows * kTileThreads == (kWalkRows + kSkew * kTileWords) * kTileWords, "");
+  const uint32_t n_rows = blk.hi - blk.lo, l = threadIdx.x % kTileWords;
+  const int w = w0 + (int)l;
+  const bool there = w >= 0 && (uint32_t)w < W;
+  Id id[kMasks];
+#pragma unroll
+  for (uint32_t u = 0; u < kMasks; ++u) {                    // q: how far from the block's last row
+    const uint32_t q = (u * kTileThreads + threadIdx.x) / kTileWords;
+    id[u] = q < n_rows ? ref_id[kIdPad + blk.hi - 1 - q] : Id(0);
+  }
+  uint32_t V[kRows], M[kMasks];
+#pragma unroll
+  for (uint32_t u = 0; u < kRows; ++u) {                     // row lo + t - back
+    const uint32_t t = (u * kTileThreads + threadIdx.x) / kTileWords, back = kSkew * l;
+    V[u] = there && t >= back && t - back < n_rows ? rows[row_word(blk.lo + t - back, (uint32_t)w, W, n_steps)] : ~0u;
+  }
+#pragma unroll
+  for (uint32_t u = 0; u < kMasks; ++u) M[u] = there ? masks[(size_t)key_of(id[u]) * W + w] : 0;
+  if (threadIdx.x < kWalkRows) tile[threadIdx.x][0] = TileWord{0, 1};
+#pragma unroll
+  for (uint32_t u = 0; u < kMasks; ++u) tile[(u * kTileThreads + threadIdx.x) / kTileWords][l + 1].equal = M[u];
+  __syncthreads();
+#pragma unroll
+  for (uint32_t u = 0; u < kRows; ++u) {
+    const uint32_t t = (u * kTileThreads + threadIdx.x) / kTileWords, back = kSkew * l;
     if (t < back || t - back >= n_rows) continue;
-    const uint32_t r = blk.lo + t - back, q = blk.hi - 1 - r;          // q: how far from the block's last row
-    const int w = w0 + (int)l;
-    uint32_t mm = 0, x = 0;
-    if (w >= 0 && (uint32_t)w < W) {
-      mm = masks[(size_t)key_of(ref_id[kIdPad + r]) * W + w];
-      x = mm | ~rows[row_word(r, (uint32_t)w, W, n_steps)];
-    }
-    M[q][l] = mm;
-    X[q][l] = x;
+    TileWord &x = tile[n_rows - 1 - (t - back)][l + 1];
+    x.stops = x.equal | ~V[u];
   }
 }
 
+// Lane q: which words of the block's row q hold a stop (bit l + 1: word l).
+__device__ __forceinline__ uint32_t words_that_stop(uint32_t n_rows, const Tile &tile) {
+  const uint32_t q = threadIdx.x & 63;
+  uint32_t some = 0;
+  if (q < n_rows)
+#pragma unroll
+    for (uint32_t l = 0; l < kTileWords; ++l) some |= tile[q][l + 1].stops ? 2u << l : 0;
+  return some;
+}
+
 // The walk through a block with j columns left on entry; returns the columns left after it, or -1 if it leaves the
-// tile.  Per row: the highest column below j that is equal or steps up.  `pair` is told of every pair.
-template <class Pair>
-__device__ __forceinline__ int walk_tile(uint32_t n_rows, int w0, int j, const uint32_t (*M)[kTileStride],
-                                         const uint32_t (*X)[kTileStride], Pair pair) {
-  for (uint32_t q = 0; q < n_rows && j > 0; ++q) {
-    int w = ((j - 1) >> 5) - w0;
-    if (w < 0) return -1;
-    uint32_t bits = X[q][w] & (~0u >> (31 - ((j - 1) & 31)));
-    while (!bits && --w >= 0) bits = X[q][w];
-    if (!bits) {
-      if (w0 > 0) return -1;
-      return 0;                                              // nothing left in this row: all the columns are used up
-    }
-    const int b = 31 - __builtin_clz(bits);
-    j = (w + w0) * 32 + b;
-    if ((M[q][w] >> b) & 1u) pair(q, j);
-    else ++j;
+// tile.  Per row: the highest column below j where it stops, in the word of column j - 1 or else in the highest one below with a
+// stop (beside the path hundreds of columns in a row may hold none).  Both words are read at once and there is no branch: bound
+// by the instructions of a row, some 25 for a wavefront's 64 entries; with a search from word to word and early ends 65.
+// at: the column, counted from 32 before the tile's first; 31 (nothing left in the tile) leads to the empty word in front of the
+// row, which leads back to 31.
+__device__ __forceinline__ int walk_tile(uint32_t n_rows, int w0, int j, const Tile &tile) {
+  const uint32_t rows_some = words_that_stop(n_rows, tile);
+  uint32_t at = (uint32_t)(j - 1 - w0 * 32 + 32);
+  for (uint32_t q = 0; q < n_rows; ++q) {
+    const uint32_t some = (uint32_t)__builtin_amdgcn_readlane((int)rows_some, q);
+    const uint32_t word = at >> 5;
+    const uint32_t other = ~(uint32_t)leading_zeros(__builtin_amdgcn_ubfe(some, 0, word)) & 31u;
+    const TileWord here = tile[q][word], below = tile[q][other];
+    const uint32_t upto = here.stops & (~0u >> (~at & 31u));
+    const uint32_t stops = upto ? upto : below.stops, equal = upto ? here.equal : below.equal;
+    const uint32_t lead = leading_zeros(stops);
+    at = ((upto ? word : other) << 5) + (31 - lead) - (equal >> (~lead & 31u) & 1u);
   }
-  return j;
+  return at == 31 && w0 > 0 ? -1 : max(0, (int)at - 31 + w0 * 32);
 }
 
 template <class Id>
@@ -736,16 +774,16 @@ __global__ __launch_bounds__(kEntries) void ss_align_tab_kernel(const Id *__rest
                                                                 uint32_t W, uint32_t n_steps,
                                                                 const uint32_t *__restrict__ rows,
                                                                 uint16_t *__restrict__ table) {
-  __shared__ uint32_t M[kWalkRows][kTileStride], X[kWalkRows][kTileStride];
+  __shared__ Tile tile;
   const uint32_t k = blockIdx.x, e0 = window_start(k, n, m) + blockIdx.y * kEntries;
   if (e0 > m) return;
   const RowBlock blk(k, n);
   const int w0 = (int)(e0 / 32) - (int)(kMargin / 32);
-  load_tile(ref_id, masks, rows, W, n_steps, blk, w0, M, X);
+  load_tile(ref_id, masks, rows, W, n_steps, blk, w0, tile);
   __syncthreads();
   const int j = (int)(e0 + threadIdx.x);
-  const int out = j <= (int)m ? walk_tile(blk.hi - blk.lo, w0, j, M, X, [](uint32_t, int) {}) : -1;
-  table[(size_t)k * kWindow + blockIdx.y * kEntries + threadIdx.x] = out < 0 ? kNoEntry : (uint16_t)(j - out);
+  const int out = walk_tile(blk.hi - blk.lo, w0, min(j, (int)m), tile);
+  table[(size_t)k * kWindow + blockIdx.y * kEntries + threadIdx.x] = out < 0 || j > (int)m ? kNoEntry : (uint16_t)(j - out);
 }
 
 // One wavefront walks a block in place and writes its pairs: lane q holds one 64-bit word of row hi - 1 - q.  A run of
@@ -813,16 +851,19 @@ __device__ __forceinline__ uint32_t taken(const uint16_t *table, uint32_t k, uin
   return at < kWindow ? table[(size_t)k * kWindow + at] : kNoEntry;
 }
 
-// the table of a group of blocks, for the window of its first: at most 8 * (kEntries + kMargin) columns
+// The table of a group of blocks, for the window of its first: at most 8 * (kEntries + kMargin) columns.  upto: what the group's
+// blocks take up to each of them, so that a block finds its entry from its group's with one read (block by block 4 us).
 __global__ __launch_bounds__(256) void ss_align_compose_kernel(const uint16_t *__restrict__ table, uint32_t n, uint32_t m,
-                                                               uint32_t K, uint16_t *__restrict__ groups) {
+                                                               uint32_t K, uint16_t *__restrict__ upto, uint16_t *__restrict__ groups) {
   const uint32_t k0 = blockIdx.x * kGroupBlocks, i = blockIdx.y * 256 + threadIdx.x, entry = window_start(k0, n, m) + i;
   uint32_t j = entry;
   bool known = j <= m;
-  for (uint32_t k = k0; known && k < min(k0 + kGroupBlocks, K); ++k) {
-    const uint32_t d = taken(table, k, n, m, j);
+  const uint32_t end = min(k0 + kGroupBlocks, K);
+  for (uint32_t k = k0; k < end; ++k) {
+    const uint32_t d = known ? taken(table, k, n, m, j) : kNoEntry;
     known = d != kNoEntry;
     if (known) j -= d;
+    upto[(size_t)k * kWindow + i] = known ? (uint16_t)(entry - j) : kNoEntry;
   }
   groups[(size_t)blockIdx.x * kWindow + i] = known ? (uint16_t)(entry - j) : kNoEntry;
 }
@@ -890,23 +931,54 @@ __global__ __launch_bounds__(kChainThreads) void ss_align_chain_kernel(const Id 
   }
 }
 
-// One thread walks, all of them load its tile.  32,312 rows: 25 us; with 64 threads, which load it in 24 turns, 36.
-constexpr uint32_t kPairThreads = 256;
+// The walk through a block from j columns left by one wavefront, lane q the block's row q; returns the column that the row pairs
+// with, or -1.  Equal operators run along the diagonal: each lane tests its own row's bit there and a ballot tells how long the
+// run is; in the row that it ends in, sixteen lanes look for the highest column below that is equal or steps up.
+__device__ __forceinline__ int32_t walk_runs(uint32_t n_rows, int w0, int j, const Tile &tile) {
+  const int lane = threadIdx.x & 63, l = lane % (int)kTileWords;
+  int32_t mine = -1;
+  uint32_t q = 0;
+  while (q < n_rows && j > 0) {
+    const int c = j - 1 - (lane - (int)q), w = (c >> 5) - w0;
+    const bool hit = lane >= (int)q && lane < (int)n_rows && c >= 0 && w >= 0 && (tile[lane][w + 1].equal >> (c & 31) & 1u);
+    const u64 missed = ~(__builtin_amdgcn_ballot_w64(hit) >> q);       // the shift brings in zeros
+    const uint32_t run = missed ? (uint32_t)__builtin_ctzll(missed) : 64;
+    if (lane >= (int)q && lane < (int)(q + run)) mine = c;
+    q += run;
+    j -= (int)run;
+    if (q >= n_rows || j <= 0) break;
+    const int at = ((j - 1) >> 5) - w0;
+    if (at < 0) break;                                       // left of the tile: the table had no entry
+    const uint32_t bits = l <= at ? tile[q][l + 1].stops & (l == at ? ~0u >> (31 - ((j - 1) & 31)) : ~0u) : 0;
+    const uint32_t there = (uint32_t)__builtin_amdgcn_ballot_w64(bits != 0) & ((1u << kTileWords) - 1);
+    if (!there) break;                                       // all the columns are used up
+    const int word = 31 - __builtin_clz(there);
+    const int b = 31 - __builtin_clz((uint32_t)__builtin_amdgcn_readlane((int)bits, word));
+    j = (word + w0) * 32 + b + 1;
+    if (!(__builtin_amdgcn_readfirstlane(tile[q][word + 1].equal) >> b & 1u)) ++q;            // up; else the next run begins there
+  }
+  return mine;
+}
+
+// One wavefront walks, all of them load its tile.  Bound by the latency of loads that need each other (the group's entry, the
+// block's, the tile's ids and masks) and of the walk's LDS reads: 32,312 rows 14.0 us; with one thread that walks row by row, the
+// block's entry by up to seven reads one after the other and the tile's loads one after the other 20.1.
+constexpr uint32_t kPairThreads = kTileThreads;
+static_assert(kEntries == kTileThreads, "a table's workgroup loads its tile");
 
 template <class Id>
 __global__ __launch_bounds__(kPairThreads) void ss_align_pairs_kernel(const Id *__restrict__ ref_id, uint32_t n,
                                                             const uint32_t *__restrict__ masks, uint32_t m, uint32_t W,
                                                             uint32_t n_steps, const uint32_t *__restrict__ rows,
-                                                            const uint16_t *__restrict__ table,
+                                                            const uint16_t *__restrict__ upto,
                                                             const int32_t *__restrict__ entry,
                                                             const int32_t *__restrict__ group_entry,
                                                             int32_t *__restrict__ ref_to_cur, ss_done done) {
-  __shared__ uint32_t M[kWalkRows][kTileStride], X[kWalkRows][kTileStride];
-  __shared__ int32_t paired[kWalkRows];
+  __shared__ Tile tile;
   const uint32_t k = blockIdx.x, k0 = k / kGroupBlocks * kGroupBlocks;
   int j = group_entry[k / kGroupBlocks];
-  if (j >= 0) {
-    for (uint32_t b = k0; b < k; ++b) j -= (int)taken(table, b, n, m, (uint32_t)j);       // known: the group's table is
+  if (j >= 0) {                                              // known: the group's table is
+    if (k > k0) j -= (int)upto[(size_t)(k - 1) * kWindow + (uint32_t)j - window_start(k0, n, m)];
   } else {
     j = entry[k];
   }
@@ -916,12 +988,12 @@ __global__ __launch_bounds__(kPairThreads) void ss_align_pairs_kernel(const Id *
   }
   const RowBlock blk(k, n);
   const int w0 = j / (int)kEntries * (int)(kEntries / 32) - (int)(kMargin / 32);     // the tile the table came from
-  if (threadIdx.x < kWalkRows) paired[threadIdx.x] = -1;
-  load_tile(ref_id, masks, rows, W, n_steps, blk, w0, M, X);
+  load_tile(ref_id, masks, rows, W, n_steps, blk, w0, tile);
   __syncthreads();
-  if (threadIdx.x == 0) walk_tile(blk.hi - blk.lo, w0, j, M, X, [&](uint32_t q, int c) { paired[q] = c; });
-  __syncthreads();
-  if (threadIdx.x < blk.hi - blk.lo) ref_to_cur[blk.hi - 1 - threadIdx.x] = paired[threadIdx.x];
+  if (threadIdx.x < 64) {
+    const int32_t mine = walk_runs(blk.hi - blk.lo, w0, __builtin_amdgcn_readfirstlane(j), tile);
+    if (threadIdx.x < blk.hi - blk.lo) ref_to_cur[blk.hi - 1 - threadIdx.x] = mine;
+  }
   ss_tell_host(done);
 }
 
@@ -931,7 +1003,7 @@ size_t lds_need(uint32_t n_keys) { return (size_t)(n_keys + 1) * kStripWords * 4
 // Where everything lies.  `d` device scratch, `h` pinned scratch.
 struct Layout {
   size_t h_ref, h_cur, h_flag, h_n_keys, h_out, h_end;
-  size_t ref, cur, ref_id, cur_id, n_keys, rep, id, slot, carry, gave_up, rows, table, entry, groups, group_entry, masks, end;
+  size_t ref, cur, ref_id, cur_id, n_keys, rep, id, slot, carry, gave_up, rows, table, entry, upto, groups, group_entry, masks, end;
   uint32_t n, m, W, strips, n_steps, n_blocks, walk_blocks, walk_groups, slots, bits;
   bool one_wg, short_rows;
 
@@ -970,6 +1042,7 @@ struct Layout {
     rows = take(short_rows ? 0 : row_bytes);
     table = take(short_rows ? 0 : (size_t)walk_blocks * kWindow * 2);
     entry = take(short_rows ? 0 : (size_t)walk_blocks * 4);
+    upto = take(short_rows ? 0 : (size_t)walk_blocks * kWindow * 2);
     groups = take(short_rows ? 0 : (size_t)walk_groups * kWindow * 2);
     group_entry = take(short_rows ? 0 : (size_t)walk_groups * 4);
     carry = take((size_t)(strips - 1) * (n_blocks + kCarryPad) * 8);
@@ -1010,16 +1083,16 @@ int launch_rows(ss_ctx *ctx, const Layout &y, uint8_t *d, uint8_t *hd, uint32_t 
                        cur_id, y.m, args, n_keys);
   if (!y.short_rows) {
     const uint32_t *cmasks = masks, *crows = rows;
-    uint16_t *table = (uint16_t *)(d + y.table), *groups = (uint16_t *)(d + y.groups);
+    uint16_t *table = (uint16_t *)(d + y.table), *upto = (uint16_t *)(d + y.upto), *groups = (uint16_t *)(d + y.groups);
     int32_t *entry = (int32_t *)(d + y.entry), *group_entry = (int32_t *)(d + y.group_entry), *pair = (int32_t *)(hd + y.h_out);
     hipLaunchKernelGGL(ss_align_tab_kernel<Id>, dim3(y.walk_blocks, kWindow / kEntries), dim3(kEntries), 0, s, ref_id, y.n,
                        cmasks, y.m, y.W, y.n_steps, crows, table);
     hipLaunchKernelGGL(ss_align_compose_kernel, dim3(y.walk_groups, kWindow / 256), dim3(256), 0, s, table, y.n, y.m,
-                       y.walk_blocks, groups);
+                       y.walk_blocks, upto, groups);
     hipLaunchKernelGGL(ss_align_chain_kernel<Id>, dim3(1), dim3(kChainThreads), 0, s, ref_id, y.n, cmasks, y.m, y.W,
                        y.n_steps, crows, table, groups, entry, group_entry, pair);
     hipLaunchKernelGGL(ss_align_pairs_kernel<Id>, dim3(y.walk_blocks), dim3(kPairThreads), 0, s, ref_id, y.n, cmasks, y.m, y.W,
-                       y.n_steps, crows, table, entry, group_entry, pair, done);
+                       y.n_steps, crows, upto, entry, group_entry, pair, done);
   }
   SS_HIP(hipGetLastError());
   return SS_OK;
