@@ -663,11 +663,14 @@ __global__ __launch_bounds__(kWgThreads) void ss_align_short_kernel(KeyArgs k, R
 // group's entry known the blocks are walked again side by side to write the pairs (ss_align_pairs_kernel).  Where a group's
 // table has no entry the chain follows its blocks' own, and a block whose entry lies outside its window, or whose path
 // leaves the tile to the left, is walked in place by a wavefront of the chain.
-// 32,312 rows: 48 us for the tables, 5 us for the groups' and 17 us for the chain (an LDS read and its way through the
+// 32,312 rows: 28 us for the tables, 5 us for the groups' and 17 us for the chain (an LDS read and its way through the
 // scalar unit per group; 90 us block by block), 14 us for the pairs; single steps in one wavefront took 97 ns a row (3.1
 // ms), the rows over the host link (130 MB) 2.3 ms and a walk there.
 constexpr uint32_t kWalkRows = 64;
-constexpr uint32_t kWindow = 2048;                     // entry columns tabulated per block of rows
+// Entry columns tabulated per block of rows.  A path strays from the diagonal by some hundred columns where operators come and go
+// all along the sequences, so half as many are tried first where their lengths differ by no more than that; if it turns out to
+// leave them the walk is made again with all (32,312 rows: tables 48 us, half as many 27.6).
+constexpr uint32_t kWindow = 2048, kNarrowWindow = 1024, kNearlyEqual = 512;
 constexpr uint32_t kEntries = 256;                     // of these, per workgroup
 constexpr uint32_t kMargin = 256;                      // columns a tile reaches to the left of its first entry
 constexpr uint32_t kTileWords = (kEntries + kMargin) / 32;
@@ -683,11 +686,21 @@ struct RowBlock {
   __device__ RowBlock(uint32_t k, uint32_t n) : lo(n > (k + 1) * kWalkRows ? n - (k + 1) * kWalkRows : 0), hi(n - k * kWalkRows) {}
 };
 
-// first entry (columns left) of the block's window: a multiple of kEntries, the scaled diagonal in the middle
-__device__ __forceinline__ uint32_t window_start(uint32_t k, uint32_t n, uint32_t m) {
-  const uint32_t mid = (uint32_t)((uint64_t)(n - k * kWalkRows) * m / n);
-  return (mid > kWindow / 2 ? mid - kWindow / 2 : 0) / kEntries * kEntries;
-}
+// The windows' size, and where a block's starts (columns left): a multiple of kEntries, the scaled diagonal in the middle.
+struct Windows {
+  uint64_t slope;                      // m / n, 32 bits of it behind the point
+  uint32_t n, m, size;
+  Windows(uint32_t n_, uint32_t m_, uint32_t size_) : slope(((uint64_t)m_ << 32) / n_), n(n_), m(m_), size(size_) {}
+  __device__ __forceinline__ uint32_t start(uint32_t k) const {
+    const uint32_t mid = (uint32_t)((n - k * kWalkRows) * slope >> 32);
+    return (mid > size / 2 ? mid - size / 2 + kEntries / 2 : 0) / kEntries * kEntries;
+  }
+  // columns that block k takes off j, or kNoEntry
+  __device__ __forceinline__ uint32_t taken(const uint16_t *table, uint32_t k, uint32_t j) const {
+    const uint32_t at = j - start(k);                        // before the window: wraps to a large number
+    return at < size ? table[(size_t)k * size + at] : kNoEntry;
+  }
+};
 
 // 0 to 31, or all ones for 0
 __device__ __forceinline__ uint32_t leading_zeros(uint32_t x) {
@@ -769,21 +782,21 @@ __device__ __forceinline__ int walk_tile(uint32_t n_rows, int w0, int j, const T
 }
 
 template <class Id>
-__global__ __launch_bounds__(kEntries) void ss_align_tab_kernel(const Id *__restrict__ ref_id, uint32_t n,
-                                                                const uint32_t *__restrict__ masks, uint32_t m,
+__global__ __launch_bounds__(kEntries) void ss_align_tab_kernel(const Id *__restrict__ ref_id, Windows win,
+                                                                const uint32_t *__restrict__ masks,
                                                                 uint32_t W, uint32_t n_steps,
                                                                 const uint32_t *__restrict__ rows,
                                                                 uint16_t *__restrict__ table) {
   __shared__ Tile tile;
-  const uint32_t k = blockIdx.x, e0 = window_start(k, n, m) + blockIdx.y * kEntries;
-  if (e0 > m) return;
-  const RowBlock blk(k, n);
+  const uint32_t k = blockIdx.x, e0 = win.start(k) + blockIdx.y * kEntries;
+  if (e0 > win.m) return;
+  const RowBlock blk(k, win.n);
   const int w0 = (int)(e0 / 32) - (int)(kMargin / 32);
   load_tile(ref_id, masks, rows, W, n_steps, blk, w0, tile);
   __syncthreads();
   const int j = (int)(e0 + threadIdx.x);
-  const int out = walk_tile(blk.hi - blk.lo, w0, min(j, (int)m), tile);
-  table[(size_t)k * kWindow + blockIdx.y * kEntries + threadIdx.x] = out < 0 || j > (int)m ? kNoEntry : (uint16_t)(j - out);
+  const int out = walk_tile(blk.hi - blk.lo, w0, min(j, (int)win.m), tile);
+  table[(size_t)k * win.size + blockIdx.y * kEntries + threadIdx.x] = out < 0 || j > (int)win.m ? kNoEntry : (uint16_t)(j - out);
 }
 
 // One wavefront walks a block in place and writes its pairs: lane q holds one 64-bit word of row hi - 1 - q.  A run of
@@ -845,56 +858,56 @@ constexpr uint32_t kGroupBlocks = 8;                   // blocks whose tables ar
 constexpr uint32_t kChainGroups = 16;                  // tables in LDS at a time
 constexpr uint32_t kChainThreads = 256;
 
-// columns that block k takes off j, or kNoEntry
-__device__ __forceinline__ uint32_t taken(const uint16_t *table, uint32_t k, uint32_t n, uint32_t m, uint32_t j) {
-  const uint32_t at = j - window_start(k, n, m);             // before the window: wraps to a large number
-  return at < kWindow ? table[(size_t)k * kWindow + at] : kNoEntry;
-}
-
 // The table of a group of blocks, for the window of its first: at most 8 * (kEntries + kMargin) columns.  upto: what the group's
 // blocks take up to each of them, so that a block finds its entry from its group's with one read (block by block 4 us).
-__global__ __launch_bounds__(256) void ss_align_compose_kernel(const uint16_t *__restrict__ table, uint32_t n, uint32_t m,
-                                                               uint32_t K, uint16_t *__restrict__ upto, uint16_t *__restrict__ groups) {
-  const uint32_t k0 = blockIdx.x * kGroupBlocks, i = blockIdx.y * 256 + threadIdx.x, entry = window_start(k0, n, m) + i;
+__global__ __launch_bounds__(256) void ss_align_compose_kernel(const uint16_t *__restrict__ table, Windows win, uint32_t K,
+                                                               uint16_t *__restrict__ upto, uint16_t *__restrict__ groups) {
+  const uint32_t k0 = blockIdx.x * kGroupBlocks, i = blockIdx.y * 256 + threadIdx.x, entry = win.start(k0) + i;
   uint32_t j = entry;
-  bool known = j <= m;
+  bool known = j <= win.m;
   const uint32_t end = min(k0 + kGroupBlocks, K);
   for (uint32_t k = k0; k < end; ++k) {
-    const uint32_t d = known ? taken(table, k, n, m, j) : kNoEntry;
+    const uint32_t d = known ? win.taken(table, k, j) : kNoEntry;
     known = d != kNoEntry;
     if (known) j -= d;
-    upto[(size_t)k * kWindow + i] = known ? (uint16_t)(entry - j) : kNoEntry;
+    upto[(size_t)k * win.size + i] = known ? (uint16_t)(entry - j) : kNoEntry;
   }
-  groups[(size_t)blockIdx.x * kWindow + i] = known ? (uint16_t)(entry - j) : kNoEntry;
+  groups[(size_t)blockIdx.x * win.size + i] = known ? (uint16_t)(entry - j) : kNoEntry;
 }
 
 // group_entry[g]: columns left when the walk enters group g, or -1 if its blocks have been followed one by one here;
-// then entry[k] is that of block k, or -1 if the block has been walked here
+// then entry[k] is that of block k, or -1 if the block has been walked here.  strayed (narrow windows): the path has left them,
+// nothing else is meaningful.
+struct Strayed { uint32_t *device, *host; };
+
 template <class Id>
-__global__ __launch_bounds__(kChainThreads) void ss_align_chain_kernel(const Id *__restrict__ ref_id, uint32_t n,
-                                                                       const uint32_t *__restrict__ masks, uint32_t m,
+__global__ __launch_bounds__(kChainThreads) void ss_align_chain_kernel(const Id *__restrict__ ref_id, Windows win,
+                                                                       const uint32_t *__restrict__ masks,
                                                                        uint32_t W, uint32_t n_steps,
                                                                        const uint32_t *__restrict__ rows,
                                                                        const uint16_t *__restrict__ table,
                                                                        const uint16_t *__restrict__ groups,
                                                                        int32_t *__restrict__ entry,
                                                                        int32_t *__restrict__ group_entry,
-                                                                       int32_t *__restrict__ ref_to_cur) {
+                                                                       int32_t *__restrict__ ref_to_cur, Strayed strayed) {
   __shared__ uint4 tabs[kChainGroups * kWindow / 8];
+  __shared__ uint32_t left;
+  const uint32_t n = win.n, size = win.size;
+  if (threadIdx.x == 0) left = 0;
   constexpr uint32_t kPer = kChainGroups * kWindow / 8 / kChainThreads;
   const uint32_t K = (n + kWalkRows - 1) / kWalkRows, G = (K + kGroupBlocks - 1) / kGroupBlocks;
   const uint4 *src = reinterpret_cast<const uint4 *>(groups);
-  const size_t total = (size_t)G * kWindow / 8;
+  const uint32_t total = G * (size / 8), turn = kChainGroups * (size / 8);        // at most 2^10 tables of 2^11 entries
   uint4 next[kPer];
   auto fetch = [&](uint32_t g0) {
 #pragma unroll
     for (uint32_t i = 0; i < kPer; ++i) {
-      const size_t at = (size_t)g0 * kWindow / 8 + i * kChainThreads + threadIdx.x;
-      next[i] = at < total ? src[at] : uint4{0, 0, 0, 0};
+      const uint32_t of_turn = i * kChainThreads + threadIdx.x, at = g0 * (size / 8) + of_turn;
+      next[i] = of_turn < turn && at < total ? src[at] : uint4{0, 0, 0, 0};
     }
   };
   fetch(0);
-  uint32_t j = m;                                            // wavefront 0's own
+  uint32_t j = win.m;                                        // wavefront 0's own
   for (uint32_t g0 = 0; g0 < G; g0 += kChainGroups) {
 #pragma unroll
     for (uint32_t i = 0; i < kPer; ++i) tabs[i * kChainThreads + threadIdx.x] = next[i];
@@ -903,12 +916,12 @@ __global__ __launch_bounds__(kChainThreads) void ss_align_chain_kernel(const Id 
     if (threadIdx.x < 64) {
       const uint16_t *t = reinterpret_cast<const uint16_t *>(tabs);
       const uint32_t mine = min(g0 + (threadIdx.x & (kChainGroups - 1)), G - 1);
-      const uint32_t starts = window_start(mine * kGroupBlocks, n, m);      // lane u: group g0 + u's
+      const uint32_t starts = win.start(mine * kGroupBlocks);               // lane u: group g0 + u's
       int32_t entries = 0;                                   // likewise
 #pragma unroll 1
       for (uint32_t u = 0; u < kChainGroups && g0 + u < G; ++u) {
         const uint32_t at = j - (uint32_t)__builtin_amdgcn_readlane((int)starts, u);       // before the window: wraps to a large number
-        const uint32_t d = at < kWindow ? __builtin_amdgcn_readfirstlane((uint32_t)t[u * kWindow + at]) : kNoEntry;
+        const uint32_t d = at < size ? __builtin_amdgcn_readfirstlane((uint32_t)t[u * size + at]) : kNoEntry;
         if (threadIdx.x == u) entries = d != kNoEntry ? (int32_t)j : -1;
         if (__builtin_expect(d != kNoEntry, 1)) {
           j -= d;
@@ -916,7 +929,16 @@ __global__ __launch_bounds__(kChainThreads) void ss_align_chain_kernel(const Id 
         }
         const uint32_t k0 = (g0 + u) * kGroupBlocks;
         for (uint32_t k = k0; k < min(k0 + kGroupBlocks, K); ++k) {
-          const uint32_t e = __builtin_amdgcn_readfirstlane(taken(table, k, n, m, j));
+          if (strayed.device && j - win.start(k) >= size) {
+            if (threadIdx.x == 0) {
+              left = 1;
+              *strayed.device = 1;
+              __hip_atomic_store(strayed.host, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+            }
+            u = kChainGroups;                                // no more groups, and no more turns
+            break;
+          }
+          const uint32_t e = __builtin_amdgcn_readfirstlane(win.taken(table, k, j));
           if (threadIdx.x == 0) entry[k] = e != kNoEntry ? (int32_t)j : -1;
           if (e != kNoEntry)
             j -= e;
@@ -928,6 +950,7 @@ __global__ __launch_bounds__(kChainThreads) void ss_align_chain_kernel(const Id 
       if (threadIdx.x < kChainGroups && g0 + threadIdx.x < G) group_entry[g0 + threadIdx.x] = entries;
     }
     __syncthreads();
+    if (left) return;
   }
 }
 
@@ -967,18 +990,22 @@ constexpr uint32_t kPairThreads = kTileThreads;
 static_assert(kEntries == kTileThreads, "a table's workgroup loads its tile");
 
 template <class Id>
-__global__ __launch_bounds__(kPairThreads) void ss_align_pairs_kernel(const Id *__restrict__ ref_id, uint32_t n,
-                                                            const uint32_t *__restrict__ masks, uint32_t m, uint32_t W,
+__global__ __launch_bounds__(kPairThreads) void ss_align_pairs_kernel(const Id *__restrict__ ref_id, Windows win,
+                                                            const uint32_t *__restrict__ masks, uint32_t W,
                                                             uint32_t n_steps, const uint32_t *__restrict__ rows,
                                                             const uint16_t *__restrict__ upto,
                                                             const int32_t *__restrict__ entry,
                                                             const int32_t *__restrict__ group_entry,
-                                                            int32_t *__restrict__ ref_to_cur, ss_done done) {
+                                                            int32_t *__restrict__ ref_to_cur, const uint32_t *strayed, ss_done done) {
   __shared__ Tile tile;
   const uint32_t k = blockIdx.x, k0 = k / kGroupBlocks * kGroupBlocks;
+  if (strayed && *strayed) {                                 // the chain has ended early
+    ss_tell_host(done);
+    return;
+  }
   int j = group_entry[k / kGroupBlocks];
   if (j >= 0) {                                              // known: the group's table is
-    if (k > k0) j -= (int)upto[(size_t)(k - 1) * kWindow + (uint32_t)j - window_start(k0, n, m)];
+    if (k > k0) j -= (int)upto[(size_t)(k - 1) * win.size + (uint32_t)j - win.start(k0)];
   } else {
     j = entry[k];
   }
@@ -986,7 +1013,7 @@ __global__ __launch_bounds__(kPairThreads) void ss_align_pairs_kernel(const Id *
     ss_tell_host(done);
     return;
   }
-  const RowBlock blk(k, n);
+  const RowBlock blk(k, win.n);
   const int w0 = j / (int)kEntries * (int)(kEntries / 32) - (int)(kMargin / 32);     // the tile the table came from
   load_tile(ref_id, masks, rows, W, n_steps, blk, w0, tile);
   __syncthreads();
@@ -1026,7 +1053,7 @@ struct Layout {
     auto take = [&](size_t bytes) { size_t at = o; o += ss_align_up(bytes, 256); return at; };
     h_ref = take((size_t)n * sizeof(ss_op_t));
     h_cur = take((size_t)m * sizeof(ss_op_t));
-    h_flag = take(4);
+    h_flag = take(8);                                      // the same
     h_n_keys = take(4);
     h_out = take(short_rows ? row_bytes : (size_t)n * 4);
     h_end = o;
@@ -1046,7 +1073,7 @@ struct Layout {
     groups = take(short_rows ? 0 : (size_t)walk_groups * kWindow * 2);
     group_entry = take(short_rows ? 0 : (size_t)walk_groups * 4);
     carry = take((size_t)(strips - 1) * (n_blocks + kCarryPad) * 8);
-    gave_up = take(strips > 1 ? 4 : 0);
+    gave_up = take(8);                                     // by a strip; by the walk (strayed)
     masks = o;                                             // last: its size needs the number of keys
     end = o;
   }
@@ -1057,6 +1084,30 @@ struct Layout {
 static_assert((uint64_t)steps_of(kAlignLenLimit) * kStripWords * 4 * strips_of(kAlignLenLimit / 32) <= 1ull << 30, "rows");
 static_assert((uint64_t)steps_of(kAlignLenLimit) * kStripWords * 4 < 1ull << 31, "a strip's rows");
 static_assert(((uint64_t)kAlignLenLimit + 1) * (kAlignLenLimit / 32) * 4 <= 1ull << 30, "masks");
+
+// The walk over rows in device memory.
+template <class Id>
+int launch_walk(ss_ctx *ctx, const Layout &y, uint8_t *d, uint8_t *hd, bool narrow, ss_done &done) {
+  hipStream_t s = ctx->s_aux;
+  const Id *ref_id = (const Id *)(d + y.ref_id);
+  const uint32_t *masks = (const uint32_t *)(d + y.masks), *rows = (const uint32_t *)(d + y.rows);
+  uint16_t *table = (uint16_t *)(d + y.table), *upto = (uint16_t *)(d + y.upto), *groups = (uint16_t *)(d + y.groups);
+  int32_t *entry = (int32_t *)(d + y.entry), *group_entry = (int32_t *)(d + y.group_entry), *pair = (int32_t *)(hd + y.h_out);
+  const Windows win(y.n, y.m, narrow ? kNarrowWindow : kWindow);
+  const Strayed strayed = narrow ? Strayed{(uint32_t *)(d + y.gave_up) + 1, (uint32_t *)(hd + y.h_flag) + 1} : Strayed{nullptr, nullptr};
+  done = ss_next_done(ctx);
+  ss_told_by(done, y.walk_blocks);
+  hipLaunchKernelGGL(ss_align_tab_kernel<Id>, dim3(y.walk_blocks, win.size / kEntries), dim3(kEntries), 0, s, ref_id, win, masks,
+                     y.W, y.n_steps, rows, table);
+  hipLaunchKernelGGL(ss_align_compose_kernel, dim3(y.walk_groups, win.size / 256), dim3(256), 0, s, table, win, y.walk_blocks, upto,
+                     groups);
+  hipLaunchKernelGGL(ss_align_chain_kernel<Id>, dim3(1), dim3(kChainThreads), 0, s, ref_id, win, masks, y.W, y.n_steps, rows, table,
+                     groups, entry, group_entry, pair, strayed);
+  hipLaunchKernelGGL(ss_align_pairs_kernel<Id>, dim3(y.walk_blocks), dim3(kPairThreads), 0, s, ref_id, win, masks, y.W, y.n_steps,
+                     rows, upto, entry, group_entry, pair, strayed.device, done);
+  SS_HIP(hipGetLastError());
+  return SS_OK;
+}
 
 // Rows (and, long ones, the walk) for ids of the given form.  The masks are needed where the rows kernel does not keep its
 // own in LDS, and by the walk.
@@ -1075,27 +1126,16 @@ int launch_rows(ss_ctx *ctx, const Layout &y, uint8_t *d, uint8_t *hd, uint32_t 
                    y.W, y.n_steps, y.strips, 0, ctx->align_wait_looks, {}};
   const uint32_t *n_keys = (const uint32_t *)(d + y.n_keys);
   const uint32_t per_launch = one_by_one ? 1 : y.strips;
-  done = ss_next_done(ctx);
-  ss_told_by(done, y.short_rows ? y.strips : y.walk_blocks);
-  if (y.short_rows) args.done = done;
+  if (y.short_rows) {
+    done = ss_next_done(ctx);
+    ss_told_by(done, y.strips);
+    args.done = done;
+  }
   for (; args.strip0 < y.strips; args.strip0 += per_launch)
     hipLaunchKernelGGL(ss_align_rows_kernel<Id>, dim3(per_launch), dim3(kRowsThreads), kLds ? lds_need(keys) : 0, s, ref_id,
                        cur_id, y.m, args, n_keys);
-  if (!y.short_rows) {
-    const uint32_t *cmasks = masks, *crows = rows;
-    uint16_t *table = (uint16_t *)(d + y.table), *upto = (uint16_t *)(d + y.upto), *groups = (uint16_t *)(d + y.groups);
-    int32_t *entry = (int32_t *)(d + y.entry), *group_entry = (int32_t *)(d + y.group_entry), *pair = (int32_t *)(hd + y.h_out);
-    hipLaunchKernelGGL(ss_align_tab_kernel<Id>, dim3(y.walk_blocks, kWindow / kEntries), dim3(kEntries), 0, s, ref_id, y.n,
-                       cmasks, y.m, y.W, y.n_steps, crows, table);
-    hipLaunchKernelGGL(ss_align_compose_kernel, dim3(y.walk_groups, kWindow / 256), dim3(256), 0, s, table, y.n, y.m,
-                       y.walk_blocks, upto, groups);
-    hipLaunchKernelGGL(ss_align_chain_kernel<Id>, dim3(1), dim3(kChainThreads), 0, s, ref_id, y.n, cmasks, y.m, y.W,
-                       y.n_steps, crows, table, groups, entry, group_entry, pair);
-    hipLaunchKernelGGL(ss_align_pairs_kernel<Id>, dim3(y.walk_blocks), dim3(kPairThreads), 0, s, ref_id, y.n, cmasks, y.m, y.W,
-                       y.n_steps, crows, upto, entry, group_entry, pair, done);
-  }
   SS_HIP(hipGetLastError());
-  return SS_OK;
+  return y.short_rows ? SS_OK : launch_walk<Id>(ctx, y, d, hd, std::max(y.n, y.m) - std::min(y.n, y.m) <= kNearlyEqual, done);
 }
 
 }  // namespace
@@ -1126,7 +1166,7 @@ int ss_align_core(ss_ctx *ctx, const ss_op_t *ref, uint32_t n, const ss_op_t *cu
     std::memcpy(h + y.h_cur, cur, (size_t)m * sizeof(ss_op_t));
     h_flag = (volatile uint32_t *)(h + y.h_flag);
     h_n_keys = (volatile uint32_t *)(h + y.h_n_keys);
-    *h_flag = 0;
+    h_flag[0] = h_flag[1] = 0;
     KeyArgs a = {};
     a.n = n; a.m = m; a.n_steps = y.n_steps;
     a.few = few;
@@ -1191,7 +1231,12 @@ int ss_align_core(ss_ctx *ctx, const ss_op_t *ref, uint32_t n, const ss_op_t *cu
   }
   if (*h_flag) {                        // a strip gave up: each after the one before it, then every word is there and none waits
     ctx->align_one_by_one += 1;
+    h_flag[1] = 0;                      // what the walk made of these rows
     if ((rc = rows(true)) != SS_OK) return rc;
+  }
+  if (h_flag[1]) {                      // the path has left the narrow windows
+    rc = keys <= few ? launch_walk<uint16_t>(ctx, y, d, hd, false, done) : launch_walk<uint32_t>(ctx, y, d, hd, false, done);
+    if (rc != SS_OK || (rc = ss_wait_done(ctx, done)) != SS_OK) return rc;
   }
   if (n_keys_out) *n_keys_out = keys;
   uint32_t pairs = 0;

@@ -1,4 +1,6 @@
-"""GPU parity of the walk back over long sequences where its tables change: rows without a column to stop in."""
+"""GPU parity of the walk back over long sequences where its windows, blocks and tables change: paths that stay inside the narrow
+windows, leave them on either side or only just, lengths about the limit for trying them, remainders of blocks and groups, rows
+without a column to stop in, 16-bit and wide ids."""
 import numpy as np
 import pytest
 
@@ -12,6 +14,30 @@ pytestmark = pytest.mark.gpu
 def same(P, ctx, ref, cur):
     lib = P.ss_align_sequence(ctx, ops_arr(ref), ops_arr(cur))
     assert np.array_equal(lib["ref_to_cur"], pairing(ref.tolist(), cur.tolist()))
+
+
+@pytest.mark.parametrize("keys", [40, 900])
+@pytest.mark.parametrize("shift", [120, 383, 384, 400, 511, 512, 640, 641, 900, 1024, 1300])
+def test_paths_beside_the_diagonal(P, ctx, keys, shift):           # noqa: F811
+    """a piece of foreign operators before the middle and as many missing after it, and the other way round"""
+    rng = np.random.default_rng([keys, shift])
+    n = 9100
+    ref = perturbed(rng, np.tile(rng.integers(0, keys, 700), 14)[:n], keys)
+    n = len(ref)
+    a, b = n // 5, 4 * n // 5
+    foreign = keys + 5 + rng.integers(0, 4, shift)
+    same(P, ctx, ref, perturbed(rng, np.concatenate([ref[:a], foreign, ref[a:b], ref[b + shift:]]), keys))
+    same(P, ctx, ref, np.concatenate([ref[:a], ref[a + shift:b], foreign, ref[b:]]))
+
+
+@pytest.mark.parametrize("n", [8705, 8703, 9216, 9217, 16384, 16385])
+@pytest.mark.parametrize("more", [-513, -512, 0, 1, 512, 513])
+def test_lengths_about_the_limit_and_remainders(P, ctx, n, more):  # noqa: F811
+    rng = np.random.default_rng([n, more + 1000])
+    ref = rng.integers(0, 25, n)
+    cur = np.concatenate([ref, 60 + rng.integers(0, 5, max(0, more))])[:n + min(0, more)]
+    same(P, ctx, ref, cur)
+    same(P, ctx, ref, perturbed(rng, ref, 25)[:n])
 
 
 def test_stretches_that_have_nothing_in_common(P, ctx):            # noqa: F811
