@@ -663,8 +663,8 @@ __global__ __launch_bounds__(kWgThreads) void ss_align_short_kernel(KeyArgs k, R
 // group's entry known the blocks are walked again side by side to write the pairs (ss_align_pairs_kernel).  Where a group's
 // table has no entry the chain follows its blocks' own, and a block whose entry lies outside its window, or whose path
 // leaves the tile to the left, is walked in place by a wavefront of the chain.
-// 32,312 rows: 28 us for the tables, 5 us for the groups' and 17 us for the chain (an LDS read and its way through the
-// scalar unit per group; 90 us block by block), 14 us for the pairs; single steps in one wavefront took 97 ns a row (3.1
+// 32,312 rows: 28 us for the tables, 5 us for the groups' and 11 us for the chain (an LDS read and a few vector operations
+// per group; 17 where each group's went through the scalar unit, 90 block by block), 14 us for the pairs; single steps in one wavefront took 97 ns a row (3.1
 // ms), the rows over the host link (130 MB) 2.3 ms and a walk there.
 constexpr uint32_t kWalkRows = 64;
 // Entry columns tabulated per block of rows.  A path strays from the diagonal by some hundred columns where operators come and go
@@ -918,8 +918,21 @@ __global__ __launch_bounds__(kChainThreads) void ss_align_chain_kernel(const Id 
       const uint32_t mine = min(g0 + (threadIdx.x & (kChainGroups - 1)), G - 1);
       const uint32_t starts = win.start(mine * kGroupBlocks);               // lane u: group g0 + u's
       int32_t entries = 0;                                   // likewise
+      // where every table has its entry: nothing goes through the scalar unit between two of them
+      uint32_t v = j;
+      bool known = true;
+#pragma unroll
+      for (uint32_t u = 0; u < kChainGroups; ++u) {
+        const uint32_t at = v - (uint32_t)__builtin_amdgcn_readlane((int)starts, u);       // before the window: wraps to a large number
+        const uint32_t d = g0 + u < G ? at < size ? t[u * size + min(at, size - 1)] : kNoEntry : 0;
+        entries = threadIdx.x == u ? (int32_t)v : entries;
+        known &= d != kNoEntry;
+        v -= d;
+      }
+      const bool all = __builtin_amdgcn_ballot_w64(known) == ~0ull;
+      if (all) j = (uint32_t)__builtin_amdgcn_readfirstlane((int)v);
 #pragma unroll 1
-      for (uint32_t u = 0; u < kChainGroups && g0 + u < G; ++u) {
+      for (uint32_t u = 0; !all && u < kChainGroups && g0 + u < G; ++u) {
         const uint32_t at = j - (uint32_t)__builtin_amdgcn_readlane((int)starts, u);       // before the window: wraps to a large number
         const uint32_t d = at < size ? __builtin_amdgcn_readfirstlane((uint32_t)t[u * size + at]) : kNoEntry;
         if (threadIdx.x == u) entries = d != kNoEntry ? (int32_t)j : -1;
