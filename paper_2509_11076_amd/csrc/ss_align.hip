@@ -35,8 +35,12 @@ constexpr uint32_t kRowsThreads = 320;
 constexpr uint32_t kSkew = 2;                          // steps that a lane is behind the one before it
 constexpr uint32_t kIdPad = 64 * kSkew;                // entries before the first id (lanes whose row has not begun)
 // Rows up to this many bytes go straight to host memory and are walked there: beside the kernel's pace they cost the
-// link nothing up to about 13 GB/s, and the walk on the GPU takes four more launches and two copies.
-constexpr size_t kHostRowBytes = 4u << 20;
+// link nothing up to about 13 GB/s, and the walk on the GPU takes four more launches.  us a call, walked on the host and on the
+// GPU: 2,694 x 2,704 operators (1.4 MiB) 104 and 113, 3,100 x 3,100 (1.6) 105 and 111, 3,300 x 3,300 (1.7) 119 and 113, 3,882 x 3,880
+// 148 and 132, 5,192 x 5,196 201 and 154, 16,000 x 1,000 337 and 302.  Where cur is more than four times as long, a block's path
+// leaves the columns that are tabulated for it: 2,000 x 8,000 (2.6) 137 and 124, but 1,800 x 9,000 136 and 244, 500 x 30,000 184
+// and 386.
+constexpr size_t kHostRowBytes = 1700u << 10, kHostRowBytesSteep = 4u << 20;
 constexpr uint32_t kCarryPad = 8;                      // carry words beyond a strip's last (the first of them is looked at)
 
 // steps a strip takes for n rows, whole blocks of them: the last lane with a word is that far behind the first
@@ -1058,7 +1062,7 @@ struct Layout {
     one_wg = n + m <= kWgOps;
     // the kernel writes the rows to pinned host memory and the host walks them; else they stay in device memory and
     // are walked there
-    short_rows = row_bytes <= kHostRowBytes;
+    short_rows = row_bytes <= (m > 4 * (uint64_t)n ? kHostRowBytesSteep : kHostRowBytes);
     bits = 13;
     while ((1u << bits) < 2 * m) ++bits;
     slots = 1u << bits;

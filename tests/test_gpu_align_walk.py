@@ -40,6 +40,15 @@ def test_lengths_about_the_limit_and_remainders(P, ctx, n, more):  # noqa: F811
     same(P, ctx, ref, perturbed(rng, ref, 25)[:n])
 
 
+@pytest.mark.parametrize("n,m", [(3263, 3250), (3264, 3264), (3265, 3265), (3270, 3270), (6598, 2000), (6800, 1900),     # rows of 1,700 KiB
+                                 (2000, 8000), (2000, 8001), (1500, 6001), (1300, 11000), (1400, 5600)])               # four times as long
+def test_walked_on_the_host_or_on_the_gpu(P, ctx, n, m):           # noqa: F811
+    rng = np.random.default_rng([n, m])
+    base = rng.integers(0, 30, max(n, m))
+    cut = [base[np.sort(rng.choice(len(base), k, replace=False))] for k in (n, m)]
+    same(P, ctx, *cut)
+
+
 def test_stretches_that_have_nothing_in_common(P, ctx):            # noqa: F811
     """rows in which no column of a tile is equal or steps up, and a current sequence that ends or begins with them"""
     rng = np.random.default_rng(7)
