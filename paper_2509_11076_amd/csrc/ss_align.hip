@@ -301,7 +301,7 @@ struct RowsArgs {
   u64 *carry;
   uint32_t *rows;
   uint32_t *gave_up;         // device, cleared before the launch (several strips only): a strip has given up
-  uint32_t *gave_up_host;    // pinned: the same
+  uint32_t *gave_up_host;    // pinned: the same; two words on, the number of keys, as a kernel that the host waits for has to say it
   uint32_t W, n_steps, strips, strip0;       // strips of a row; the one of workgroup 0
   uint32_t wait_looks;       // looks at a carry word before a strip gives up
   ss_done done;              // where the host walks the rows
@@ -575,6 +575,7 @@ __global__ __launch_bounds__(kRowsThreads) void ss_align_rows_kernel(const Id *_
   const uint32_t words = min(many ? kInnerWords : kStripWords, a.W - w0);
   const bool stored = lane >= first && lane < first + words;
   const uint32_t n_mask_rows = *n_keys + 1, n_blocks = a.n_steps / kBlock;
+  if (blockIdx.x == 0 && tid == 0) a.gave_up_host[2] = n_mask_rows - 1;
   if (kLds && n_mask_rows > kLdsKeys) {                      // launched before the number was known, and the ids are wide
     ss_tell_host(a.done);
     return;
@@ -893,10 +894,12 @@ __global__ __launch_bounds__(kChainThreads) void ss_align_chain_kernel(const Id 
                                                                        const uint16_t *__restrict__ groups,
                                                                        int32_t *__restrict__ entry,
                                                                        int32_t *__restrict__ group_entry,
-                                                                       int32_t *__restrict__ ref_to_cur, Strayed strayed) {
+                                                                       int32_t *__restrict__ ref_to_cur, Strayed strayed,
+                                                                       const uint32_t *__restrict__ n_keys) {
   __shared__ uint4 tabs[kChainGroups * kWindow / 8];
   __shared__ uint32_t left;
   const uint32_t n = win.n, size = win.size;
+  if (sizeof(Id) == 2 && *n_keys >= kLdsKeys) return;        // launched before the number was known, and there are no rows
   if (threadIdx.x == 0) left = 0;
   constexpr uint32_t kPer = kChainGroups * kWindow / 8 / kChainThreads;
   const uint32_t K = (n + kWalkRows - 1) / kWalkRows, G = (K + kGroupBlocks - 1) / kGroupBlocks;
@@ -1013,10 +1016,13 @@ __global__ __launch_bounds__(kPairThreads) void ss_align_pairs_kernel(const Id *
                                                             const uint16_t *__restrict__ upto,
                                                             const int32_t *__restrict__ entry,
                                                             const int32_t *__restrict__ group_entry,
-                                                            int32_t *__restrict__ ref_to_cur, const uint32_t *strayed, ss_done done) {
+                                                            int32_t *__restrict__ ref_to_cur, const uint32_t *strayed, const uint32_t *n_keys,
+                                                            uint32_t *n_keys_out, ss_done done) {
   __shared__ Tile tile;
   const uint32_t k = blockIdx.x, k0 = k / kGroupBlocks * kGroupBlocks;
-  if (strayed && *strayed) {                                 // the chain has ended early
+  const uint32_t keys = *n_keys;
+  if (k == 0 && threadIdx.x == 0) *n_keys_out = keys;        // as a kernel that the host waits for has to say it
+  if ((strayed && *strayed) || (sizeof(Id) == 2 && keys >= kLdsKeys)) {      // the chain has ended early
     ss_tell_host(done);
     return;
   }
@@ -1070,8 +1076,8 @@ struct Layout {
     auto take = [&](size_t bytes) { size_t at = o; o += ss_align_up(bytes, 256); return at; };
     h_ref = take((size_t)n * sizeof(ss_op_t));
     h_cur = take((size_t)m * sizeof(ss_op_t));
-    h_flag = take(8);                                      // the same
-    h_n_keys = take(4);
+    h_flag = take(12);                                     // the same; the number of keys
+    h_n_keys = h_flag + 8;
     h_out = take(short_rows ? row_bytes : (size_t)n * 4);
     h_end = o;
     o = 0;
@@ -1110,6 +1116,7 @@ int launch_walk(ss_ctx *ctx, const Layout &y, uint8_t *d, uint8_t *hd, bool narr
   const uint32_t *masks = (const uint32_t *)(d + y.masks), *rows = (const uint32_t *)(d + y.rows);
   uint16_t *table = (uint16_t *)(d + y.table), *upto = (uint16_t *)(d + y.upto), *groups = (uint16_t *)(d + y.groups);
   int32_t *entry = (int32_t *)(d + y.entry), *group_entry = (int32_t *)(d + y.group_entry), *pair = (int32_t *)(hd + y.h_out);
+  const uint32_t *n_keys = (const uint32_t *)(d + y.n_keys);
   const Windows win(y.n, y.m, narrow ? kNarrowWindow : kWindow);
   const Strayed strayed = narrow ? Strayed{(uint32_t *)(d + y.gave_up) + 1, (uint32_t *)(hd + y.h_flag) + 1} : Strayed{nullptr, nullptr};
   done = ss_next_done(ctx);
@@ -1119,9 +1126,9 @@ int launch_walk(ss_ctx *ctx, const Layout &y, uint8_t *d, uint8_t *hd, bool narr
   hipLaunchKernelGGL(ss_align_compose_kernel, dim3(y.walk_groups, win.size / 256), dim3(256), 0, s, table, win, y.walk_blocks, upto,
                      groups);
   hipLaunchKernelGGL(ss_align_chain_kernel<Id>, dim3(1), dim3(kChainThreads), 0, s, ref_id, win, masks, y.W, y.n_steps, rows, table,
-                     groups, entry, group_entry, pair, strayed);
+                     groups, entry, group_entry, pair, strayed, n_keys);
   hipLaunchKernelGGL(ss_align_pairs_kernel<Id>, dim3(y.walk_blocks), dim3(kPairThreads), 0, s, ref_id, win, masks, y.W, y.n_steps,
-                     rows, upto, entry, group_entry, pair, strayed.device, done);
+                     rows, upto, entry, group_entry, pair, strayed.device, n_keys, (uint32_t *)(hd + y.h_n_keys), done);
   SS_HIP(hipGetLastError());
   return SS_OK;
 }
@@ -1214,9 +1221,11 @@ int ss_align_core(ss_ctx *ctx, const ss_op_t *ref, uint32_t n, const ss_op_t *cu
       const uint32_t wgs = std::min(256u, (std::max(n, m) + 255) / 256), len = std::max(m, id_length(y.n_steps));
       hipLaunchKernelGGL(ss_align_fetch_kernel, dim3(wgs), dim3(256), 0, s, mref, dref, n, mcur, dcur, m, a.rep, y.slots, a.n_keys);
       hipLaunchKernelGGL(ss_align_insert_kernel, dim3((m + 255) / 256), dim3(256), 0, s, a);
-      a.done = ss_next_done(ctx);
-      ss_told_by(a.done, (len + 255) / 256);
-      keys_known = a.done;
+      if (ctx->align_many_keys) {
+        a.done = ss_next_done(ctx);
+        ss_told_by(a.done, (len + 255) / 256);
+        keys_known = a.done;
+      }
       hipLaunchKernelGGL(ss_align_ids_kernel, dim3((len + 255) / 256), dim3(256), 0, s, a);
     }
     SS_HIP(hipGetLastError());
@@ -1231,8 +1240,11 @@ int ss_align_core(ss_ctx *ctx, const ss_op_t *ref, uint32_t n, const ss_op_t *cu
                         : launch_rows<uint32_t>(ctx, y, d, hd, keys, done, one_by_one);
     return r != SS_OK ? r : ss_wait_done(ctx, done);
   };
-  if (y.one_wg) {                       // rows at once, as if there were few keys (the kernel looks again): one wait less
-    if (y.strips > 1 && (rc = launch_rows<uint16_t>(ctx, y, d, hd, keys, done)) != SS_OK) return rc;
+  // Rows and walk at once, as if there were few keys (the kernels of the rows look again): one wait less, some 8 us.  If there are
+  // more it is all for nothing, so a context whose last call had more waits for their number before.  The tables that are then made
+  // of ids of another form take them for keys below kLdsKeys, so nothing out of range is read, and nothing looks at them.
+  if (y.one_wg || !ctx->align_many_keys) {
+    if (!(y.one_wg && y.strips == 1) && (rc = launch_rows<uint16_t>(ctx, y, d, hd, keys, done)) != SS_OK) return rc;
     if ((rc = ss_wait_done(ctx, done)) != SS_OK) return rc;
     keys = *h_n_keys;
     done_rows = keys <= few;
@@ -1240,7 +1252,9 @@ int ss_align_core(ss_ctx *ctx, const ss_op_t *ref, uint32_t n, const ss_op_t *cu
     if ((rc = ss_wait_done(ctx, keys_known)) != SS_OK) return rc;
     keys = *h_n_keys;
   }
+  ctx->align_many_keys = keys > few;
   if (!done_rows) {
+    h_flag[0] = h_flag[1] = 0;
     if (y.with_masks(keys) > ctx->d_scratch_bytes) {
       if ((rc = make_ids(y.with_masks(keys), true)) != SS_OK) return rc;
     }

@@ -183,6 +183,7 @@ struct ss_ctx {
   // strip after strip
   uint32_t align_wait_looks = 1u << 20;
   uint32_t align_one_by_one = 0;
+  bool align_many_keys = false;     // the last call's ids had 32 bits: the next one of long sequences waits for the number of keys
   ss_sched sched;
   ss_stats_t stats;
 };

@@ -57,3 +57,21 @@ def test_stretches_that_have_nothing_in_common(P, ctx):            # noqa: F811
     for cur in (np.concatenate([other[:4000], ref[4000:]]), np.concatenate([ref[:6000], other[6000:]]),
                 np.concatenate([ref[:3000], other[3000:7000], ref[7000:]]), other, np.where(np.arange(10000) // 700 % 2, ref, other)):
         same(P, ctx, ref, cur)
+
+
+@pytest.mark.parametrize("n,m", [(2600, 2700), (700, 4000), (9000, 9001)])
+def test_few_keys_and_many_in_turn(P, n, m):                       # noqa: F811
+    """rows are launched before the number of keys is known, unless the call before had many: 255 and 256 keys, each after either,
+    the first ones on a new context whose scratch is small"""
+    rng = np.random.default_rng([n, m, 3])
+    c = P.ss_create(P.ss_config_default())
+    try:
+        for keys in (256, 255, 256, 1500, 40, 255, 900, 256, 30, 30):
+            ref = rng.integers(0, keys, n)
+            cur = perturbed(rng, np.tile(ref, 1 + m // n), keys - 5)[:m] if m > n and keys > 300 else rng.integers(0, keys, m)
+            cur[:keys] = np.arange(keys)
+            lib = P.ss_align_sequence(c, ops_arr(ref), ops_arr(cur))
+            assert np.array_equal(lib["ref_to_cur"], pairing(ref.tolist(), cur.tolist())), keys
+            assert lib["n_keys"] == len(set(cur.tolist()))
+    finally:
+        P.ss_destroy(c)
