@@ -87,6 +87,7 @@ struct KeyArgs {
   uint32_t *rep, *id;          // per slot
   uint32_t *slot;              // per operator of cur
   uint32_t mask, shift;
+  uint32_t *masks, W;          // if given, cleared: mask rows of W words, made with the ids where there are few keys
 };
 
 __device__ __forceinline__ uint32_t key_hash(uint32_t token, uint32_t stack, uint32_t sig, uint32_t shift) {
@@ -176,15 +177,17 @@ __global__ __launch_bounds__(kWgThreads) void ss_align_keys_kernel(KeyArgs a) {
   keys_of_wg(a, lds, mine);
 }
 
-// Long sequences: ops copied from pinned host memory and the table cleared; keys of cur inserted; ids of both.
+// Long sequences: ops copied from pinned host memory, the table cleared and what the rows need clear; keys of cur inserted; ids of
+// both, and the masks (the clearing and the masks in launches of their own: 32,312 operators 663 us a call, so 654).
 __global__ __launch_bounds__(256) void ss_align_fetch_kernel(const ss_op_t *__restrict__ ref, ss_op_t *__restrict__ dref,
                                                              uint32_t n, const ss_op_t *__restrict__ cur,
                                                              ss_op_t *__restrict__ dcur, uint32_t m, uint32_t *rep,
-                                                             uint32_t slots, uint32_t *n_keys) {
+                                                             uint32_t slots, uint32_t *n_keys, uint4 *zeros, uint32_t n_zeros) {
   const uint32_t first = blockIdx.x * 256 + threadIdx.x, stride = gridDim.x * 256;
   for (uint32_t i = first; i < n; i += stride) dref[i] = ref[i];
   for (uint32_t i = first; i < m; i += stride) dcur[i] = cur[i];
   for (uint32_t i = first; i < slots; i += stride) rep[i] = 0;
+  for (uint32_t i = first; i < n_zeros; i += stride) zeros[i] = uint4{0, 0, 0, 0};
   if (first == 0) *n_keys = 0;
 }
 
@@ -240,7 +243,11 @@ __device__ __forceinline__ void operator_ids(const KeyArgs &a) {
   const uint32_t i = blockIdx.x * 256 + threadIdx.x, keys = *a.n_keys;
   const bool few = keys <= a.few;
   if (i == 0) *a.n_keys_out = keys;
-  if (i < a.m) put_id(a.cur_id, i, a.id[a.slot[i]], few);
+  if (i < a.m) {
+    const uint32_t key = a.id[a.slot[i]];
+    put_id(a.cur_id, i, key, few);
+    if (few && a.masks) atomicOr(&a.masks[(size_t)key * a.W + (i >> 5)], 1u << (i & 31));
+  }
   if (i >= id_length(a.n_steps)) return;
   uint32_t key = keys;
   if (i >= kIdPad && i < kIdPad + a.n) {
@@ -1101,6 +1108,7 @@ struct Layout {
     end = o;
   }
   size_t with_masks(uint32_t keys) const { return end + (size_t)(keys + 1) * W * 4; }
+  size_t to_clear(bool with, uint32_t keys) const { return (with ? with_masks(keys) : end) - carry; }          // carry words, then masks
 };
 // With both lengths at their limit the rows take 545 MiB, a strip 16 MiB (the kernel's buffer offsets have 31 bits), and the
 // masks, with every key distinct, 512 MiB.
@@ -1133,18 +1141,19 @@ int launch_walk(ss_ctx *ctx, const Layout &y, uint8_t *d, uint8_t *hd, bool narr
   return SS_OK;
 }
 
+// cleared: with what the rows need clear, and the masks made, by the kernels of the ids.
 // Rows (and, long ones, the walk) for ids of the given form.  The masks are needed where the rows kernel does not keep its
 // own in LDS, and by the walk.
 template <class Id>
-int launch_rows(ss_ctx *ctx, const Layout &y, uint8_t *d, uint8_t *hd, uint32_t keys, ss_done &done, bool one_by_one = false) {
+int launch_rows(ss_ctx *ctx, const Layout &y, uint8_t *d, uint8_t *hd, uint32_t keys, ss_done &done, bool one_by_one = false,
+                bool cleared = false) {
   constexpr bool kLds = sizeof(Id) == 2;
   hipStream_t s = ctx->s_aux;
   const Id *ref_id = (const Id *)(d + y.ref_id), *cur_id = (const Id *)(d + y.cur_id);
   uint32_t *masks = (uint32_t *)(d + y.masks), *rows = (uint32_t *)(y.short_rows ? hd + y.h_out : d + y.rows);
   const bool masks_needed = !kLds || !y.short_rows;
-  const size_t clear = (masks_needed ? y.with_masks(keys) : y.end) - y.carry;          // carry words, then masks
-  if (clear) ss_launch_fill(s, d + y.carry, clear, 0);
-  if (masks_needed)
+  if (!cleared) ss_launch_fill(s, d + y.carry, y.to_clear(masks_needed, keys), 0);
+  if (!cleared && masks_needed)
     hipLaunchKernelGGL(ss_align_masks_kernel<Id>, dim3((y.m + 255) / 256), dim3(256), 0, s, cur_id, y.m, masks, y.W);
   RowsArgs args = {masks, (u64 *)(d + y.carry), rows, (uint32_t *)(d + y.gave_up), (uint32_t *)(hd + y.h_flag),
                    y.W, y.n_steps, y.strips, 0, ctx->align_wait_looks, {}};
@@ -1219,7 +1228,13 @@ int ss_align_core(ss_ctx *ctx, const ss_op_t *ref, uint32_t n, const ss_op_t *cu
       a.mask = y.slots - 1;
       a.shift = 64 - y.bits;
       const uint32_t wgs = std::min(256u, (std::max(n, m) + 255) / 256), len = std::max(m, id_length(y.n_steps));
-      hipLaunchKernelGGL(ss_align_fetch_kernel, dim3(wgs), dim3(256), 0, s, mref, dref, n, mcur, dcur, m, a.rep, y.slots, a.n_keys);
+      const bool for_rows = !ctx->align_many_keys;
+      if (for_rows && !y.short_rows) {
+        a.masks = (uint32_t *)(d + y.masks);
+        a.W = y.W;
+      }
+      hipLaunchKernelGGL(ss_align_fetch_kernel, dim3(wgs), dim3(256), 0, s, mref, dref, n, mcur, dcur, m, a.rep, y.slots, a.n_keys,
+                         (uint4 *)(d + y.carry), for_rows ? (uint32_t)((y.to_clear(a.masks, few) + 15) / 16) : 0);
       hipLaunchKernelGGL(ss_align_insert_kernel, dim3((m + 255) / 256), dim3(256), 0, s, a);
       if (ctx->align_many_keys) {
         a.done = ss_next_done(ctx);
@@ -1244,7 +1259,7 @@ int ss_align_core(ss_ctx *ctx, const ss_op_t *ref, uint32_t n, const ss_op_t *cu
   // more it is all for nothing, so a context whose last call had more waits for their number before.  The tables that are then made
   // of ids of another form take them for keys below kLdsKeys, so nothing out of range is read, and nothing looks at them.
   if (y.one_wg || !ctx->align_many_keys) {
-    if (!(y.one_wg && y.strips == 1) && (rc = launch_rows<uint16_t>(ctx, y, d, hd, keys, done)) != SS_OK) return rc;
+    if (!(y.one_wg && y.strips == 1) && (rc = launch_rows<uint16_t>(ctx, y, d, hd, keys, done, false, !y.one_wg)) != SS_OK) return rc;
     if ((rc = ss_wait_done(ctx, done)) != SS_OK) return rc;
     keys = *h_n_keys;
     done_rows = keys <= few;
