@@ -24,7 +24,7 @@ namespace {
 typedef unsigned long long u64;
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 
-constexpr uint32_t kAlignLenLimit = 1u << 16;          // at most 34 strips
+constexpr uint32_t kAlignLenLimit = SS_ALIGN_LEN_LIMIT;       // at most 34 strips
 constexpr uint32_t kBlock = 32;                        // steps between two looks at the neighbouring strip
 constexpr uint32_t kStripWords = 64;                   // 32-bit words of a row, one per lane, in a single strip
 constexpr uint32_t kInnerWords = 62;                   // the same where there are several strips: lanes 1 to 62
@@ -88,6 +88,7 @@ struct KeyArgs {
   uint32_t *slot;              // per operator of cur
   uint32_t mask, shift;
   uint32_t *masks, W;          // if given, cleared: mask rows of W words, made with the ids where there are few keys
+  ss_cosine_part *part;        // pinned, if wanted: of each workgroup that reads the operators
 };
 
 __device__ __forceinline__ uint32_t key_hash(uint32_t token, uint32_t stack, uint32_t sig, uint32_t shift) {
@@ -127,6 +128,16 @@ __device__ __forceinline__ uint32_t keys_of_wg(const KeyArgs &a, uint32_t *lds, 
     if (i < total) { tok[i] = o[u].op_token; stk[i] = o[u].stack_hash; sig[i] = o[u].sig; }
   }
   __syncthreads();
+  if (a.part) {
+    uint64_t dot = 0, na = 0, nb = 0;
+    uint32_t bad = 0;
+    for (uint32_t i = tid; i < max(a.n, a.m); i += kWgThreads) {               // the shorter sequence is padded with token 0
+      const uint32_t x = i < a.m ? tok[i] : 0, y = i < a.n ? tok[a.m + i] : 0;
+      bad |= x >= SS_TOKEN_LIMIT || y >= SS_TOKEN_LIMIT;
+      dot += (uint64_t)x * y; na += (uint64_t)x * x; nb += (uint64_t)y * y;
+    }
+    ss_put_part<kWgThreads>(a.part, dot, na, nb, bad);
+  }
   // at most m <= kWgSlots / 2 keys: a free or matching slot is met
   auto find = [&](uint32_t u, bool insert) -> uint32_t {
     const uint32_t i = u * kWgThreads + tid;
@@ -177,15 +188,33 @@ __global__ __launch_bounds__(kWgThreads) void ss_align_keys_kernel(KeyArgs a) {
   keys_of_wg(a, lds, mine);
 }
 
+constexpr uint32_t kFetchWgs = 256;
+
 // Long sequences: ops copied from pinned host memory, the table cleared and what the rows need clear; keys of cur inserted; ids of
 // both, and the masks (the clearing and the masks in launches of their own: 32,312 operators 663 us a call, so 654).
 __global__ __launch_bounds__(256) void ss_align_fetch_kernel(const ss_op_t *__restrict__ ref, ss_op_t *__restrict__ dref,
                                                              uint32_t n, const ss_op_t *__restrict__ cur,
                                                              ss_op_t *__restrict__ dcur, uint32_t m, uint32_t *rep,
-                                                             uint32_t slots, uint32_t *n_keys, uint4 *zeros, uint32_t n_zeros) {
+                                                             uint32_t slots, uint32_t *n_keys, uint4 *zeros, uint32_t n_zeros,
+                                                             ss_cosine_part *part) {
   const uint32_t first = blockIdx.x * 256 + threadIdx.x, stride = gridDim.x * 256;
-  for (uint32_t i = first; i < n; i += stride) dref[i] = ref[i];
-  for (uint32_t i = first; i < m; i += stride) dcur[i] = cur[i];
+  if (part) {
+    uint64_t dot = 0, na = 0, nb = 0;
+    uint32_t bad = 0;
+    for (uint32_t i = first; i < max(n, m); i += stride) {
+      ss_op_t c = {0, 0, 0, 0}, r = {0, 0, 0, 0};              // the shorter sequence is padded with token 0
+      if (i < m) c = cur[i];
+      if (i < n) r = ref[i];
+      if (i < m) dcur[i] = c;
+      if (i < n) dref[i] = r;
+      bad |= c.op_token >= SS_TOKEN_LIMIT || r.op_token >= SS_TOKEN_LIMIT;
+      dot += (uint64_t)c.op_token * r.op_token; na += (uint64_t)c.op_token * c.op_token; nb += (uint64_t)r.op_token * r.op_token;
+    }
+    ss_put_part<256>(part, dot, na, nb, bad);
+  } else {
+    for (uint32_t i = first; i < n; i += stride) dref[i] = ref[i];
+    for (uint32_t i = first; i < m; i += stride) dcur[i] = cur[i];
+  }
   for (uint32_t i = first; i < slots; i += stride) rep[i] = 0;
   for (uint32_t i = first; i < n_zeros; i += stride) zeros[i] = uint4{0, 0, 0, 0};
   if (first == 0) *n_keys = 0;
@@ -1059,7 +1088,7 @@ size_t lds_need(uint32_t n_keys) { return (size_t)(n_keys + 1) * kStripWords * 4
 
 // Where everything lies.  `d` device scratch, `h` pinned scratch.
 struct Layout {
-  size_t h_ref, h_cur, h_flag, h_n_keys, h_out, h_end;
+  size_t h_ref, h_cur, h_flag, h_n_keys, h_part, h_out, h_end;
   size_t ref, cur, ref_id, cur_id, n_keys, rep, id, slot, carry, gave_up, rows, table, entry, upto, groups, group_entry, masks, end;
   uint32_t n, m, W, strips, n_steps, n_blocks, walk_blocks, walk_groups, slots, bits;
   bool one_wg, short_rows;
@@ -1085,6 +1114,7 @@ struct Layout {
     h_cur = take((size_t)m * sizeof(ss_op_t));
     h_flag = take(12);                                     // the same; the number of keys
     h_n_keys = h_flag + 8;
+    h_part = take(kFetchWgs * sizeof(ss_cosine_part));
     h_out = take(short_rows ? row_bytes : (size_t)n * 4);
     h_end = o;
     o = 0;
@@ -1176,7 +1206,7 @@ int launch_rows(ss_ctx *ctx, const Layout &y, uint8_t *d, uint8_t *hd, uint32_t 
 // ref_to_cur: n entries (host), filled; *lcs out.  Shared by ss_align_sequence and the SS_MATCH_ALIGN
 // branch of ss_match_sequence.
 int ss_align_core(ss_ctx *ctx, const ss_op_t *ref, uint32_t n, const ss_op_t *cur, uint32_t m,
-                  int32_t *ref_to_cur, uint32_t *lcs, uint32_t *n_keys_out) {
+                  int32_t *ref_to_cur, uint32_t *lcs, uint32_t *n_keys_out, ss_cosine_part *sums) {
   if (n > kAlignLenLimit || m > kAlignLenLimit) return SS_E_CAPACITY;
   for (uint32_t i = 0; i < n; ++i) ref_to_cur[i] = -1;
   *lcs = 0;
@@ -1188,6 +1218,7 @@ int ss_align_core(ss_ctx *ctx, const ss_op_t *ref, uint32_t n, const ss_op_t *cu
   uint8_t *d = nullptr, *h = nullptr, *hd = nullptr;
   volatile uint32_t *h_flag = nullptr, *h_n_keys = nullptr;
   ss_done keys_known = {}, done = {};
+  uint32_t parts = 1;
   // key ids; again if the mask table then turns out not to fit (the first call with that many keys)
   auto make_ids = [&](size_t dev_bytes, bool again) -> int {
     const int rc = ss_scratch_reserve(ctx, dev_bytes, y.h_end);
@@ -1207,6 +1238,7 @@ int ss_align_core(ss_ctx *ctx, const ss_op_t *ref, uint32_t n, const ss_op_t *cu
     a.cur_id = d + y.cur_id;
     a.n_keys = (uint32_t *)(d + y.n_keys);
     a.n_keys_out = (uint32_t *)(hd + y.h_n_keys);
+    if (sums) a.part = (ss_cosine_part *)(hd + y.h_part);
     const ss_op_t *mref = (const ss_op_t *)(hd + y.h_ref), *mcur = (const ss_op_t *)(hd + y.h_cur);
     if (y.one_wg) {
       a.ref = mref;
@@ -1227,14 +1259,14 @@ int ss_align_core(ss_ctx *ctx, const ss_op_t *ref, uint32_t n, const ss_op_t *cu
       a.slot = (uint32_t *)(d + y.slot);
       a.mask = y.slots - 1;
       a.shift = 64 - y.bits;
-      const uint32_t wgs = std::min(256u, (std::max(n, m) + 255) / 256), len = std::max(m, id_length(y.n_steps));
+      const uint32_t wgs = parts = std::min(kFetchWgs, (std::max(n, m) + 255) / 256), len = std::max(m, id_length(y.n_steps));
       const bool for_rows = !ctx->align_many_keys;
       if (for_rows && !y.short_rows) {
         a.masks = (uint32_t *)(d + y.masks);
         a.W = y.W;
       }
       hipLaunchKernelGGL(ss_align_fetch_kernel, dim3(wgs), dim3(256), 0, s, mref, dref, n, mcur, dcur, m, a.rep, y.slots, a.n_keys,
-                         (uint4 *)(d + y.carry), for_rows ? (uint32_t)((y.to_clear(a.masks, few) + 15) / 16) : 0);
+                         (uint4 *)(d + y.carry), for_rows ? (uint32_t)((y.to_clear(a.masks, few) + 15) / 16) : 0, a.part);
       hipLaunchKernelGGL(ss_align_insert_kernel, dim3((m + 255) / 256), dim3(256), 0, s, a);
       if (ctx->align_many_keys) {
         a.done = ss_next_done(ctx);
@@ -1285,6 +1317,13 @@ int ss_align_core(ss_ctx *ctx, const ss_op_t *ref, uint32_t n, const ss_op_t *cu
     if (rc != SS_OK || (rc = ss_wait_done(ctx, done)) != SS_OK) return rc;
   }
   if (n_keys_out) *n_keys_out = keys;
+  if (sums) {
+    const ss_cosine_part *const part = (const ss_cosine_part *)(h + y.h_part);
+    *sums = ss_cosine_part{0, 0, 0, 0};
+    for (uint32_t w = 0; w < parts; ++w) {
+      sums->dot += part[w].dot; sums->na += part[w].na; sums->nb += part[w].nb; sums->bad |= part[w].bad;
+    }
+  }
   uint32_t pairs = 0;
   if (!y.short_rows) {
     std::memcpy(ref_to_cur, h + y.h_out, (size_t)n * 4);

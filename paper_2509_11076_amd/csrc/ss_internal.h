@@ -234,6 +234,10 @@ static inline void ss_told_by(ss_done &d, uint32_t wgs) {
 ss_done ss_next_done(ss_ctx *ctx);                 // for the next kernel on s_aux; its launcher fills in wgs
 int ss_wait_done(ss_ctx *ctx, const ss_done &d);   // the stream itself is waited for where the word doesn't come soon
 
+// What one workgroup adds to the cosine's three sums (na: current, nb: reference); bad: a token is too large.
+struct ss_cosine_part { uint64_t dot, na, nb, bad; };
+constexpr uint32_t SS_TOKEN_LIMIT = 1u << 18;
+
 #ifdef __HIPCC__
 // v of another lane by one data-parallel move, `none` where there is no such lane
 template <int kCtrl, int kRows>
@@ -250,6 +254,29 @@ __device__ __forceinline__ uint32_t wave_scan_u32(uint32_t v) {
   v += dpp_u32<0x142, 0xA>(v, 0);
   v += dpp_u32<0x143, 0xC>(v, 0);
   return v;
+}
+
+__device__ __forceinline__ uint64_t ss_wave_sum(uint64_t v) {
+#pragma unroll
+  for (int d = 32; d >= 1; d >>= 1) {
+    const uint32_t lo = (uint32_t)__shfl_xor((int)(uint32_t)v, d, 64), hi = (uint32_t)__shfl_xor((int)(uint32_t)(v >> 32), d, 64);
+    v += ((uint64_t)hi << 32) | lo;
+  }
+  return v;
+}
+
+// A workgroup's part of the cosine's sums, from each of its T threads'.
+template <uint32_t T>
+__device__ __forceinline__ void ss_put_part(ss_cosine_part *out, uint64_t dot, uint64_t na, uint64_t nb, uint32_t bad) {
+  __shared__ ss_cosine_part part[T / 64];
+  dot = ss_wave_sum(dot); na = ss_wave_sum(na); nb = ss_wave_sum(nb);
+  const uint64_t any = __ballot(bad != 0);
+  if ((threadIdx.x & 63) == 0) part[threadIdx.x >> 6] = ss_cosine_part{dot, na, nb, any ? 1ull : 0ull};
+  __syncthreads();
+  if (threadIdx.x) return;
+  ss_cosine_part s = part[0];
+  for (uint32_t w = 1; w < T / 64; ++w) { s.dot += part[w].dot; s.na += part[w].na; s.nb += part[w].nb; s.bad |= part[w].bad; }
+  out[blockIdx.x] = s;
 }
 
 // The last thing that every thread of each of the workgroups calls.  Results written to pinned memory may still be in the
@@ -308,9 +335,10 @@ void ss_launch_mark(hipStream_t s, uint64_t *flag, uint64_t value);
 void ss_launch_wait_flag(hipStream_t s, const uint64_t *flag, uint64_t want, uint64_t limit_ticks, uint32_t *gave_up,
                          uint32_t *timeouts);
 
-// sequence aligner (ss_align.hip): ref_to_cur has n entries
+// sequence aligner (ss_align.hip): ref_to_cur has n entries; sums: the matcher's cosine of the two sequences, neither empty
+constexpr uint32_t SS_ALIGN_LEN_LIMIT = 1u << 16;
 int ss_align_core(ss_ctx *ctx, const ss_op_t *ref, uint32_t n, const ss_op_t *cur, uint32_t m,
-                  int32_t *ref_to_cur, uint32_t *lcs, uint32_t *n_keys_out);
+                  int32_t *ref_to_cur, uint32_t *lcs, uint32_t *n_keys_out, ss_cosine_part *sums = nullptr);
 void ss_align_anchors(const ss_op_t *ref, uint32_t n, const ss_op_t *cur, const int32_t *ref_to_cur,
                       const ss_anchor_t *anchors, uint32_t k, int32_t *new_idx, uint8_t *level,
                       uint32_t *n_unmatched);

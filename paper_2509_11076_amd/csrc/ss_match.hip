@@ -18,35 +18,10 @@
 
 namespace {
 
-constexpr uint32_t kTokenLimit = 1u << 18;
+constexpr uint32_t kTokenLimit = SS_TOKEN_LIMIT;
 constexpr uint32_t kLenLimit = 1u << 23;
 
-__device__ inline uint64_t wave_sum_u64(uint64_t v) {
-#pragma unroll
-  for (int d = 32; d >= 1; d >>= 1) {
-    uint32_t lo = (uint32_t)__shfl_xor((int)(uint32_t)v, d, 64);
-    uint32_t hi = (uint32_t)__shfl_xor((int)(uint32_t)(v >> 32), d, 64);
-    v += ((uint64_t)hi << 32) | lo;
-  }
-  return v;
-}
-
-// What one workgroup adds to the cosine's three sums (na: current, nb: reference); bad: a token is too large.
-struct CosinePart { uint64_t dot, na, nb, bad; };
-
 constexpr uint32_t kMaxParts = 1024;
-
-__device__ __forceinline__ void put_part(CosinePart *out, uint64_t dot, uint64_t na, uint64_t nb, uint32_t bad) {
-  __shared__ CosinePart part[4];
-  dot = wave_sum_u64(dot); na = wave_sum_u64(na); nb = wave_sum_u64(nb);
-  const uint64_t any = __ballot(bad != 0);
-  if ((threadIdx.x & 63) == 0) part[threadIdx.x >> 6] = CosinePart{dot, na, nb, any ? 1ull : 0ull};
-  __syncthreads();
-  if (threadIdx.x) return;
-  CosinePart s = part[0];
-  for (int w = 1; w < 4; ++w) { s.dot += part[w].dot; s.na += part[w].na; s.nb += part[w].nb; s.bad |= part[w].bad; }
-  out[blockIdx.x] = s;
-}
 
 // Everything that has to be done before anchors can be looked for, in one pass: the sequences (and anchors) are copied
 // from pinned host memory to device memory if dref / dcur / danc are given, the sums of the cosine taken on the way
@@ -56,7 +31,7 @@ struct PrepArgs {
   ss_op_t *dref, *dcur;      ss_anchor_t *danc;
   uint32_t n, m, k, cosine;
   uint4 *ones, *zeros;       uint32_t n_ones, n_zeros;       // in 16-byte words
-  CosinePart *part;          // one per workgroup
+  ss_cosine_part *part;          // one per workgroup
   ss_done done;              // if this is the call's last kernel
 };
 
@@ -111,7 +86,7 @@ __global__ __launch_bounds__(256) void ss_prep_kernel(PrepArgs a) {
     for (uint32_t i = first; i < a.k; i += stride) a.danc[i] = a.anchors[i];
   for (uint32_t i = first; i < a.n_ones; i += stride) a.ones[i] = uint4{~0u, ~0u, ~0u, ~0u};
   for (uint32_t i = first; i < a.n_zeros; i += stride) a.zeros[i] = uint4{0, 0, 0, 0};
-  if (a.cosine) put_part(a.part, dot, na, nb, bad);
+  if (a.cosine) ss_put_part<256>(a.part, dot, na, nb, bad);
   ss_tell_host(a.done);
 }
 
@@ -144,13 +119,13 @@ __global__ __launch_bounds__(256) void ss_histogram_kernel(const ss_op_t *__rest
 
 __global__ __launch_bounds__(256) void ss_histdot_kernel(const uint32_t *__restrict__ h_ref,
                                                          const uint32_t *__restrict__ h_cur, uint32_t vocab,
-                                                         const uint32_t *__restrict__ flags, CosinePart *part, ss_done done) {
+                                                         const uint32_t *__restrict__ flags, ss_cosine_part *part, ss_done done) {
   uint64_t dot = 0, na = 0, nb = 0;
   for (uint32_t i = blockIdx.x * blockDim.x + threadIdx.x; i < vocab; i += gridDim.x * blockDim.x) {
     const uint64_t a = h_cur[i], b = h_ref[i];
     dot += a * b; na += a * a; nb += b * b;
   }
-  put_part(part, dot, na, nb, *flags);
+  ss_put_part<256>(part, dot, na, nb, *flags);
   ss_tell_host(done);
 }
 
@@ -808,6 +783,20 @@ extern "C" int ss_match_sequence(ss_ctx *ctx, const ss_op_t *ref, uint32_t n, co
       finish(sm, unm);
       return SS_OK;
     }
+    // Aligned: the sums are taken by the aligner's first kernel, which reads both sequences anyway (a pass of their own before it,
+    // with a wait: some 560 operators each 36.1 us a call, so 28.3; 1,240 52.4 and 44.0).
+    if (k && aligned && !hist && n && m && n <= SS_ALIGN_LEN_LIMIT && m <= SS_ALIGN_LEN_LIMIT) {
+      std::vector<int32_t> ref_to_cur(n);
+      ss_cosine_part sums;
+      uint32_t lcs = 0, n_unm = 0;
+      const int rc = ss_align_core(ctx, ref, n, cur, m, ref_to_cur.data(), &lcs, nullptr, &sums);
+      if (rc != SS_OK) return rc;
+      if (sums.bad) return SS_E_INVAL;                       // a token beyond 2^18
+      ss_align_anchors(ref, n, cur, ref_to_cur.data(), anchors, k, new_idx, level, &n_unm);
+      const uint64_t sm[3] = {sums.dot, sums.na, sums.nb};
+      finish(sm, n_unm);
+      return SS_OK;
+    }
     const bool search = k && !aligned;
     const size_t op_bytes = sizeof(ss_op_t), in_bytes = ((size_t)n + m) * op_bytes + (size_t)k * sizeof(ss_anchor_t);
     // Inputs up to this size go through pinned memory that the first kernel reads (and copies on the way) and the last
@@ -849,13 +838,13 @@ extern "C" int ss_match_sequence(ss_ctx *ctx, const ss_op_t *ref, uint32_t n, co
     const size_t ho_ref = htake(mapped ? (size_t)n * op_bytes : 0), ho_cur = htake(mapped ? (size_t)m * op_bytes : 0);
     const size_t ho_anc = htake(mapped ? (size_t)k * sizeof(ss_anchor_t) : 0);
     const size_t ho_idx = htake(mapped ? (size_t)k * 4 : 0), ho_level = htake(mapped ? k : 0);
-    const size_t ho_part = htake(kMaxParts * sizeof(CosinePart)), ho_lost = htake((size_t)out_wgs * 4);
+    const size_t ho_part = htake(kMaxParts * sizeof(ss_cosine_part)), ho_lost = htake((size_t)out_wgs * 4);
     int rc = ss_scratch_reserve(ctx, off, hoff);
     if (rc != SS_OK) return rc;
     uint8_t *d = (uint8_t *)ctx->d_scratch, *h = (uint8_t *)ctx->h_scratch, *hd = nullptr;
     SS_HIP(hipHostGetDevicePointer((void **)&hd, h, 0));
     hipStream_t s = ctx->s_aux;
-    CosinePart *dpart = (CosinePart *)(hd + ho_part);
+    ss_cosine_part *dpart = (ss_cosine_part *)(hd + ho_part);
     PrepArgs p = {};
     bool split = false;
     p.n = n; p.m = m; p.k = search ? k : 0;
@@ -958,7 +947,7 @@ extern "C" int ss_match_sequence(ss_ctx *ctx, const ss_op_t *ref, uint32_t n, co
     if (!done.flag) SS_HIP(hipStreamSynchronize(s));
     else if ((rc = ss_wait_done(ctx, done)) != SS_OK) return rc;
     uint64_t sm[3] = {0, 0, 0}, too_large = 0;
-    const CosinePart *part = (const CosinePart *)(h + ho_part);
+    const ss_cosine_part *part = (const ss_cosine_part *)(h + ho_part);
     for (uint32_t w = 0; w < parts; ++w) {
       sm[0] += part[w].dot;
       sm[1] += part[w].na;
