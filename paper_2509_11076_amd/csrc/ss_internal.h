@@ -183,6 +183,7 @@ struct ss_ctx {
   // strip after strip
   uint32_t align_wait_looks = 1u << 20;
   uint32_t align_one_by_one = 0;
+  uint32_t match_many_keys = 0;     // calls of short sequences to come that don't try the form for few keys (ss_match.hip)
   bool align_many_keys = false;     // the last call's ids had 32 bits: the next one of long sequences waits for the number of keys
   ss_sched sched;
   ss_stats_t stats;
@@ -256,12 +257,19 @@ __device__ __forceinline__ uint32_t wave_scan_u32(uint32_t v) {
   return v;
 }
 
+template <int kCtrl, int kRows>
+__device__ __forceinline__ uint64_t dpp_u64(uint64_t v) {
+  return (uint64_t)dpp_u32<kCtrl, kRows>((uint32_t)(v >> 32), 0) << 32 | dpp_u32<kCtrl, kRows>((uint32_t)v, 0);
+}
+
+// sum over the 64 lanes, in the last one
 __device__ __forceinline__ uint64_t ss_wave_sum(uint64_t v) {
-#pragma unroll
-  for (int d = 32; d >= 1; d >>= 1) {
-    const uint32_t lo = (uint32_t)__shfl_xor((int)(uint32_t)v, d, 64), hi = (uint32_t)__shfl_xor((int)(uint32_t)(v >> 32), d, 64);
-    v += ((uint64_t)hi << 32) | lo;
-  }
+  v += dpp_u64<0x111, 0xF>(v);
+  v += dpp_u64<0x112, 0xF>(v);
+  v += dpp_u64<0x114, 0xF>(v);
+  v += dpp_u64<0x118, 0xF>(v);
+  v += dpp_u64<0x142, 0xA>(v);
+  v += dpp_u64<0x143, 0xC>(v);
   return v;
 }
 
@@ -269,14 +277,17 @@ __device__ __forceinline__ uint64_t ss_wave_sum(uint64_t v) {
 template <uint32_t T>
 __device__ __forceinline__ void ss_put_part(ss_cosine_part *out, uint64_t dot, uint64_t na, uint64_t nb, uint32_t bad) {
   __shared__ ss_cosine_part part[T / 64];
+  const uint32_t lane = threadIdx.x & 63;
   dot = ss_wave_sum(dot); na = ss_wave_sum(na); nb = ss_wave_sum(nb);
   const uint64_t any = __ballot(bad != 0);
-  if ((threadIdx.x & 63) == 0) part[threadIdx.x >> 6] = ss_cosine_part{dot, na, nb, any ? 1ull : 0ull};
+  if (lane == 63) part[threadIdx.x >> 6] = ss_cosine_part{dot, na, nb, any ? 1ull : 0ull};
   __syncthreads();
-  if (threadIdx.x) return;
-  ss_cosine_part s = part[0];
-  for (uint32_t w = 1; w < T / 64; ++w) { s.dot += part[w].dot; s.na += part[w].na; s.nb += part[w].nb; s.bad |= part[w].bad; }
-  out[blockIdx.x] = s;
+  if (threadIdx.x >= 64) return;
+  ss_cosine_part s = {0, 0, 0, 0};
+  if (lane < T / 64) s = part[lane];
+  dot = ss_wave_sum(s.dot); na = ss_wave_sum(s.na); nb = ss_wave_sum(s.nb);
+  const uint64_t worse = __ballot(s.bad != 0);
+  if (lane == 63) out[blockIdx.x] = ss_cosine_part{dot, na, nb, worse ? 1ull : 0ull};
 }
 
 // The last thing that every thread of each of the workgroups calls.  Results written to pinned memory may still be in the

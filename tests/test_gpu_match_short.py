@@ -1,0 +1,57 @@
+"""GPU parity of the matcher where one workgroup takes short sequences: words of the bit maps, the longest sequences and most
+anchors, as many keys as fit and one more, the calls after one that didn't fit, anchors of all levels.  Exact comparison."""
+import numpy as np
+import pytest
+
+import workloads as W
+from test_gpu_match_edges import anchors, check, landings, perturbed, sequence
+from test_gpu_trace_scan_match import P, ctx          # noqa: F401  (fixtures)
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("n,k,tokens,stacks", [
+    (1, 1, 1, 1), (31, 40, 2, 1), (32, 40, 2, 2), (33, 40, 2, 2), (129, 300, 3, 2), (600, 1023, 4, 2), (1100, 1024, 4, 1), (1100, 1025, 4, 1),
+    (2047, 2047, 2, 2), (2048, 2048, 2, 2), (2048, 2049, 2, 2), (2049, 2048, 2, 2),
+])
+def test_sizes(P, ctx, n, k, tokens, stacks):                     # noqa: F811
+    rng = np.random.default_rng([n, k])
+    ref = sequence(rng, n, tokens, stacks)
+    cur, anc = perturbed(rng, ref), anchors(rng, n, k)
+    if n >= 129:
+        assert set(landings(ref, cur, anc)[1]) == {0, 1, 2, 255}
+    check(P, ctx, ref, cur, anc)
+    if 1 < n <= 2048:
+        check(P, ctx, cur, ref, anc)                              # the longer one second
+
+
+@pytest.mark.parametrize("n,keys", [(160, 255), (160, 256), (160, 257), (2048, 48), (2048, 49)])
+def test_as_many_keys_as_fit(P, ctx, n, keys):                    # noqa: F811
+    rng = np.random.default_rng([n, keys])
+    few, many = (np.concatenate([np.arange(c), rng.integers(0, c, 2 * n - c)]) for c in (5, keys))
+    anc = anchors(rng, n, 100)
+    for key in (many, few, many):                                 # after one that doesn't fit the next calls don't try
+        ops = np.zeros(2 * n, dtype=W.OP_DT)
+        ops["op_token"] = 1 + key % 7
+        ops["stack_hash"] = key // 14
+        ops["sig"] = 0x101 + (key // 7 % 2 << 16)
+        ops["n_out"] = 2
+        check(P, ctx, ops[:n], ops[n:], anc)
+        for _ in range(40):
+            r = P.ss_match_sequence(ctx, ops[:n], ops[n:], anc)
+        idx, lvl = landings(ops[:n], ops[n:], anc)
+        assert np.array_equal(r["new_idx"], idx) and np.array_equal(r["level"], lvl)
+
+
+def test_tokens_out_of_range(P, ctx):                             # noqa: F811
+    ops = np.zeros(70, dtype=W.OP_DT)
+    ops["op_token"], ops["n_out"] = (1 << 18) - 1, 1
+    anc = np.zeros(3, dtype=W.ANCHOR_DT)
+    anc["ref_op"] = [0, 69, 70]
+    check(P, ctx, ops, ops[:69], anc)
+    for at in (0, 69):
+        bad = ops.copy()
+        bad["op_token"][at] = 1 << 18
+        for pair in ((bad, ops), (ops, bad)):
+            with pytest.raises(P.SsError):
+                P.ss_match_sequence(ctx, *pair, anc)
