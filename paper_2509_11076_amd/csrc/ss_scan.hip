@@ -843,6 +843,53 @@ __device__ __forceinline__ TileSum sum_events(const ScanArgs &a, const Tile &tl,
   return wg_total(sp, sn, cp, flags, part);
 }
 
+// Gaps of a tile of few events, each filled by the whole workgroup, 8 bytes a lane side by side: bound by how many stores a workgroup
+// has under way.  Both launches of 460 + 28 events over 58,299 operators 21 us, of 2,000 + 4 over 65,536 23; one by one by the first
+// wavefront, 64 entries of 24 bytes in 0.1 us (fill_gap), 29 and 56.  Where there are fewer operators to an event than kLongGaps that is as
+// fast (5 to one: 14.9 us, so 15.3; 7 to one: 16.4 and 14.7).
+constexpr uint32_t kFewInTile = 8, kLongGaps = 8;
+
+__host__ __device__ inline bool few_in_tile(uint32_t tile, uint64_t events, uint32_t n_ops) {
+  return tile <= kFewInTile && n_ops > kLongGaps * events;
+}
+
+struct FewGaps {
+  uint32_t lo[kFewInTile + 1], hi[kFewInTile + 1];           // the last one's: after the list's last event
+  OpAt x[kFewInTile + 1];
+};
+
+// `e`: the event of this thread, in its tile's order, from thread 0 on
+__device__ __forceinline__ void fill_together(OpAt *at, FewGaps &gaps, const Elem &y, uint32_t e, int64_t sp, int64_t sn, uint32_t cp,
+                                              uint32_t n_ops) {
+  static_assert(sizeof(OpAt) == 24 && kTileThreads % 3 == 1, "whose word a thread's next one is");
+  const uint32_t tid = threadIdx.x;
+  if (tid <= kFewInTile) gaps.lo[tid] = gaps.hi[tid] = 0;
+  __syncthreads();
+  if (y.live && y.op < n_ops && y.prev <= y.op) {
+    if (y.first || y.prev != y.op) {
+      gaps.lo[tid] = y.first ? 0 : y.prev + 1;
+      gaps.hi[tid] = y.op + 1;
+      gaps.x[tid] = OpAt{sp, sn, e, cp};
+    }
+    if (y.last) {
+      gaps.lo[kFewInTile] = y.op + 1;
+      gaps.hi[kFewInTile] = n_ops + 1;
+      gaps.x[kFewInTile] = OpAt{sp + (y.pos ? y.delta : 0), sn + (y.pos ? 0 : y.delta), e + 1, cp + (y.pos ? 1 : 0)};
+    }
+  }
+  __syncthreads();
+  uint64_t *const words = reinterpret_cast<uint64_t *>(at);
+  for (uint32_t g = 0; g <= kFewInTile; ++g) {
+    const uint64_t *const x = reinterpret_cast<const uint64_t *>(gaps.x + g);
+    const uint32_t end = gaps.hi[g] * 3;
+    const uint64_t v[3] = {x[tid % 3], x[(tid + 1) % 3], x[(tid + 2) % 3]};
+    for (uint32_t w = gaps.lo[g] * 3 + tid; w < end; w += 3 * kTileThreads)
+#pragma unroll
+      for (uint32_t u = 0; u < 3; ++u)
+        if (w + u * kTileThreads < end) words[w + u * kTileThreads] = v[u];
+  }
+}
+
 // How long a workgroup waits for the sums of the tiles before its own (10 ns each).  They belong to workgroups that are
 // started before it and wait for no later one, so it sees them within a few us; should one of them not run all the same,
 // it adds up their events itself, and no wait depends on another workgroup's progress.
@@ -853,7 +900,8 @@ constexpr uint32_t kTileWaitTicks = 10000;
 // one pass over the events where the sums had a launch of their own (100,000 + 40,000 events with a timeline 7.6 us in
 // place of 4.1 + 9.1, a launch of about 2.5 and the second loading of the events; 1,048,574 + 20,014 events 30.4 in place of
 // 7.4 + 25.5, the filling of gaps being the most of it).
-template <int K, bool kOnce>
+// kFew: a list has few events to a tile and long gaps (its code in the others' kernel cost 100,000 + 40,000 events 0.2 us of 10.9).
+template <int K, bool kOnce, bool kFew>
 __global__ __launch_bounds__(kTileThreads) void ss_scan_running_kernel(ScanArgs a) {
   __shared__ SumShared sh;
   __shared__ TileSum part[kTileThreads / 64];
@@ -922,6 +970,7 @@ __global__ __launch_bounds__(kTileThreads) void ss_scan_running_kernel(ScanArgs 
     }
     if (__syncthreads_or(over)) return;
   }
+  const bool few = kFew && few_in_tile(a.tile[tl.policy], tl.cnt, a.n_ops);
   for (uint64_t lo = tl.lo; lo < tl.hi; lo += (uint64_t)kTileThreads * K) {
     if constexpr (kOnce) {
 #pragma unroll
@@ -938,7 +987,11 @@ __global__ __launch_bounds__(kTileThreads) void ss_scan_running_kernel(ScanArgs 
         a.sumx[tl.out0 + e] = (pos[k] ? xsp[k] : xsn[k]) + delta[k];
         a.cntx[tl.out0 + e] = pos[k] ? xcp[k] : (uint32_t)e - xcp[k];
       }
-      fill_from<16>(at, x[k], (uint32_t)e, xsp[k], xsn[k], xcp[k], a.n_ops);
+      if (!few) fill_from<16>(at, x[k], (uint32_t)e, xsp[k], xsn[k], xcp[k], a.n_ops);
+    }
+    if constexpr (kFew) {
+      __shared__ FewGaps gaps;
+      if (few) fill_together(at, gaps, x[0], (uint32_t)(lo + tid), xsp[0], xsn[0], xcp[0], a.n_ops);
     }
     __syncthreads();                                         // sh is written again in the next pass
   }
@@ -1065,7 +1118,8 @@ __global__ __launch_bounds__(kThreads) void ss_scan_finish_kernel(ScanArgs a, ui
 // passes, 30.4 us, four 32.1, eight 42.9), so a lane gets two, or four, and beyond that a tile takes several passes of eight.
 // Where operators outnumber the events, filling the gaps between them is the work (a wavefront fills gaps above kAlone one
 // after the other), and few events to a tile spread it: 60,000 operators with 40,000 events and 2,000 of the policy
-// 82 -> 40 us, with 6,000 and 200 66 -> 41.
+// 82 -> 40 us, with 6,000 and 200 66 -> 41.  Of few events a tile takes so many that it fills about 1,024 operators (one each always:
+// 3,500 operators with 124 events 15.6 us, so 13.7).
 // A lane that gets two or four loads them once, so there a tile is at most one pass.
 int events_per_lane(uint64_t n) {
   return n <= kMaxTiles * kTileThreads * 2 ? 2 : n <= kMaxTiles * kTileThreads * 4 ? 4 : 8;
@@ -1074,7 +1128,8 @@ int events_per_lane(uint64_t n) {
 uint32_t tile_events(uint64_t n, uint32_t n_ops, int per_lane) {
   const uint64_t pass = (uint64_t)kTileThreads * per_lane;
   if (n_ops > 2 * n) {
-    const uint64_t spread = std::max<uint64_t>(8, ss_align_up((n + 255) / 256, 8));
+    const uint64_t some = std::min<uint64_t>(kFewInTile, std::max<uint64_t>({1, (n + 255) / 256, n * 1024 / n_ops}));
+    const uint64_t spread = n <= 2048 ? some : ss_align_up((n + 255) / 256, 8);
     return (uint32_t)(per_lane == 8 ? spread : std::min(spread, pass));
   }
   return (uint32_t)std::max(pass, ss_align_up((n + kMaxTiles - 1) / kMaxTiles, pass));
@@ -1149,9 +1204,14 @@ void launch_scan(hipStream_t s, ScanArgs &a) {
   // without a timeline these are there for lists out of order only, and end at once where there are none
   const uint64_t per_wg = a.want_timeline ? kThreads : kGatherK * kThreads;
   const uint32_t ev_wgs = (uint32_t)std::min<uint64_t>(2048, (a.n_ev + a.n_pe + per_wg - 1) / per_wg);
-  if (per_lane == 2) hipLaunchKernelGGL((ss_scan_running_kernel<2, true>), dim3(tiles), dim3(kTileThreads), 0, s, a);
-  else if (per_lane == 4) hipLaunchKernelGGL((ss_scan_running_kernel<4, true>), dim3(tiles), dim3(kTileThreads), 0, s, a);
-  else hipLaunchKernelGGL((ss_scan_running_kernel<8, false>), dim3(tiles), dim3(kTileThreads), 0, s, a);
+  const bool few = few_in_tile(a.tile[0], a.n_ev, a.n_ops) || few_in_tile(a.tile[1], a.n_pe, a.n_ops);
+#define SS_LAUNCH(K, ONCE)                                                                                                     \
+  if (few) hipLaunchKernelGGL((ss_scan_running_kernel<K, ONCE, true>), dim3(tiles), dim3(kTileThreads), 0, s, a);              \
+  else hipLaunchKernelGGL((ss_scan_running_kernel<K, ONCE, false>), dim3(tiles), dim3(kTileThreads), 0, s, a)
+  if (per_lane == 2) { SS_LAUNCH(2, true); }
+  else if (per_lane == 4) { SS_LAUNCH(4, true); }
+  else { SS_LAUNCH(8, false); }
+#undef SS_LAUNCH
   ss_told_by(a.done, op_wgs + ev_wgs);
   hipLaunchKernelGGL(ss_scan_finish_kernel, dim3(op_wgs + ev_wgs), dim3(kThreads), 0, s, a, op_wgs);
 }

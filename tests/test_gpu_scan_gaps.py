@@ -1,0 +1,25 @@
+"""GPU parity of the timeline scan where the gaps between few events are the work and a workgroup fills each together: one event to a
+tile and as many as there may be, gaps before the first and after the last, several events of one operator, one list without any."""
+import numpy as np
+import pytest
+
+from test_gpu_scan_edges import both_ways, events
+from test_gpu_trace_scan_match import P, ctx          # noqa: F401  (fixtures)
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("n_ev,n_pe,n_ops", [
+    (1, 0, 3000), (0, 1, 3000), (1, 1, 65536), (2, 3, 4097), (8, 9, 2901), (9, 65, 65536), (360, 12, 2901), (500, 13, 26112),
+    (257, 512, 65536), (2047, 1, 16377), (2048, 2049, 65536), (4096, 3, 60000), (2047, 300, 1 << 21),
+])
+def test_few_events_over_many_operators(P, ctx, n_ev, n_pe, n_ops):           # noqa: F811
+    rng = np.random.default_rng([n_ev, n_pe, n_ops, 9])
+    for end in (False, True):
+        ev, pe = events(rng, n_ev, n_ops), events(rng, n_pe, n_ops, runs=True)
+        for x in (ev, pe):
+            if len(x):
+                x["op_idx"][0 if end else -1] = 0 if end else n_ops - 1
+        if not end:
+            ev["op_idx"][:len(ev) // 2] = ev["op_idx"][len(ev) // 2:][:1]      # in front nothing, then many of one operator
+        both_ways(P, ctx, ev, pe, n_ops, 5, 1 << 41)
