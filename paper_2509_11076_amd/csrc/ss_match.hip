@@ -432,11 +432,11 @@ __global__ __launch_bounds__(256) void ss_anchor_short_kernel(AnchorArgs g) {
 // The operators of both sequences get the number of their key through a table in LDS.  Each key has a bit map of its places in
 // either sequence for each level: at the second and the third that of the lowest key equal to it there, where those of all of
 // them are put together.  With the places before each word counted, an anchor's thread finds its ordinal in one map and its landing by
-// search in the other, level after level.  Bound by the latency of the link (7,200 of the kernel's 27,400 cycles are the
-// wait for the operators), of LDS and of the barriers between nine short phases: 480 anchors of 1,154 + 1,156 operators are 11.4 us
-// (a wavefront per anchor that the first level doesn't land, over the maps of its equals: 15.6 where 37 don't, and without a
-// bound; every operator into all three levels' maps at once: 12.8, atomics on shared words take turns).  Fetched, searched for by a
-// workgroup each and made injective in three launches they took 15.3 and two gaps.
+// search in the other, level after level.  Bound by the latency of the link (7,200 of 27,400 cycles are the wait for the operators),
+// of LDS and of the barriers between nine short phases: 480 anchors of 1,154 + 1,156 operators 12.3 us.  A wavefront for each
+// anchor that the first level doesn't land, over the maps of its equals, took 33,600 cycles where 37 don't, and without a bound;
+// every operator into all three levels' maps at once 30,800 (atomics on shared words take turns).  Fetched, searched for by a
+// workgroup each and made injective in three launches they took 15.3 us and two gaps.
 struct ShortArgs {
   const ss_op_t *ref, *cur;            // pinned
   const ss_anchor_t *anchors;

@@ -196,7 +196,7 @@ __device__ __forceinline__ void put_event(const ScanArgs &a, int64_t *timeline, 
 
 // OpAt entries of operators (prev, op] take the values before the event that starts op.  A lane fills a short gap by
 // itself; the wavefront fills a long one (more than kAlone operators) together, 64 entries a turn of about 0.1 us (one gap of
-// 65,536 operators 0.1 ms: spreading it over the grid is not done, few such events are the rare case).  A workgroup that
+// 65,536 operators 0.1 ms; tiles of few events do it with the whole workgroup, fill_together).  A workgroup that
 // does the whole scan has few long gaps in a wavefront: 4.  A tile may have many: 16 (the running sums of 20,014 events
 // over 65,536 operators 30 us, with 4 37).
 template <uint32_t kAlone>
