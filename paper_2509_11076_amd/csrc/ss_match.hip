@@ -628,9 +628,9 @@ __global__ __launch_bounds__(kShortThreads) void ss_match_short_kernel(ShortArgs
       bad |= x >= kTokenLimit || y >= kTokenLimit;
       dot += (uint64_t)x * y; na += (uint64_t)x * x; nb += (uint64_t)y * y;
     }
-    if (__ballot(na + nb != 0)) {
+    const uint64_t any = __ballot(bad != 0);                   // of tokens that are too large the sums may wrap to 0
+    if (any | __ballot((na | nb) != 0)) {
       dot = ss_wave_sum(dot); na = ss_wave_sum(na); nb = ss_wave_sum(nb);
-      const uint64_t any = __ballot(bad != 0);
       if (lane == 63) {
         atomicAdd(&sh.dot, (unsigned long long)dot);
         atomicAdd(&sh.na, (unsigned long long)na);

@@ -55,3 +55,19 @@ def test_tokens_out_of_range(P, ctx):                             # noqa: F811
         for pair in ((bad, ops), (ops, bad)):
             with pytest.raises(P.SsError):
                 P.ss_match_sequence(ctx, *pair, anc)
+
+
+@pytest.mark.parametrize("n,wrong", [(2048, slice(0, 64)), (2048, slice(64, 128)), (2048, slice(960, 1024)), (2048, slice(0, 1024))])
+def test_tokens_out_of_range_whose_squares_wrap_to_zero(P, ctx, n, wrong):         # noqa: F811
+    """2^31 four times, at places i and i + 1,024 of both sequences, has squares that add up to 2^64: for one wavefront or all"""
+    ref = np.zeros(n, dtype=W.OP_DT)
+    ref["op_token"], ref["n_out"] = 1 + np.arange(n) % 7, 1
+    cur = ref.copy()
+    cur["stack_hash"][5] = 9                                      # the same sequence twice is another path
+    anc = np.zeros(3, dtype=W.ANCHOR_DT)
+    check(P, ctx, ref, cur, anc)
+    for ops in (ref, cur):
+        ops["op_token"][:1024][wrong] = ops["op_token"][1024:][wrong] = 1 << 31
+    with pytest.raises(P.SsError) as e:
+        P.ss_match_sequence(ctx, ref, cur, anc)
+    assert e.value.code == P.SS_E_INVAL
