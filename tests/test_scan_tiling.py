@@ -27,3 +27,14 @@ def test_tiles(n, other):
             for events, tile, tiles in zip(lists, rest[::2], rest[1::2]):
                 assert tiles == max(1, -(-events // tile)) <= MAX_TILES
                 assert per_lane == 8 or tile <= THREADS * per_lane
+
+
+@pytest.mark.parametrize("n_ev,n_pe,n_ops,few", [
+    (100000, 0, 40000, 0), (0, 100000, 40000, 0), (5000, 0, 9000, 0), (0, 0, 9000, 0), (0, 0, 1, 0),         # a list without events has no gaps
+    (10, 0, 9000, 1), (0, 10, 9000, 1), (100000, 10, 9000, 1),
+])
+def test_whose_gaps_are_filled_together(n_ev, n_pe, n_ops, few):
+    import paper_2509_11076_amd.binding as B
+    f = ctypes.CDLL(B.LIB_PATH).ss_scan_few_events
+    f.argtypes, f.restype = [ctypes.c_uint64, ctypes.c_uint64, ctypes.c_uint32], ctypes.c_int
+    assert f(n_ev, n_pe, n_ops) == few
