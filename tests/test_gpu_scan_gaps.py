@@ -3,6 +3,7 @@ tile and as many as there may be, gaps before the first and after the last, seve
 import numpy as np
 import pytest
 
+import oracle
 from test_gpu_scan_edges import both_ways, events
 from test_gpu_trace_scan_match import P, ctx          # noqa: F401  (fixtures)
 
@@ -23,3 +24,18 @@ def test_few_events_over_many_operators(P, ctx, n_ev, n_pe, n_ops):           # 
         if not end:
             ev["op_idx"][:len(ev) // 2] = ev["op_idx"][len(ev) // 2:][:1]      # in front nothing, then many of one operator
         both_ways(P, ctx, ev, pe, n_ops, 5, 1 << 41)
+
+
+@pytest.mark.parametrize("n_ev,n_pe,n_ops", [(2, 0, 3000), (10, 12, 65536), (100, 3, 65536), (300, 40, 30000), (9, 2000, 9000)])
+def test_few_events_out_of_order(P, ctx, n_ev, n_pe, n_ops):                 # noqa: F811
+    """an inversion in the first tiles, in the last one, everywhere, in the other list; then a scan in order, which finds no traces of it"""
+    rng = np.random.default_rng([n_ev, n_pe, n_ops, 10])
+    ev, pe = events(rng, n_ev, n_ops), events(rng, n_pe, n_ops)
+    ev["op_idx"][0], ev["op_idx"][-1] = 3, n_ops - 2
+    first, last = ev.copy(), ev.copy()
+    first["op_idx"][0] = n_ops - 1
+    last["op_idx"][-1] = 1
+    for x, y in ((first, pe), (last, pe), (ev[rng.permutation(n_ev)], pe), (ev, pe[::-1].copy()), (ev, pe)):
+        ora, got = oracle.timeline_scan(x, y, n_ops, 5, 1 << 41), P.ss_timeline_scan(ctx, x, y, n_ops, 5, 1 << 41)
+        for what in ("per_op", "mre", "peak", "argpeak_op", "n_over", "final"):
+            assert np.array_equal(got[what], ora[what]), what
