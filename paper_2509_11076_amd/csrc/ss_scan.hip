@@ -883,10 +883,12 @@ __device__ __forceinline__ void fill_together(OpAt *at, FewGaps &gaps, const Ele
     const uint64_t *const x = reinterpret_cast<const uint64_t *>(gaps.x + g);
     const uint32_t end = gaps.hi[g] * 3;
     const uint64_t v[3] = {x[tid % 3], x[(tid + 1) % 3], x[(tid + 2) % 3]};
-    for (uint32_t w = gaps.lo[g] * 3 + tid; w < end; w += 3 * kTileThreads)
+    uint32_t w = gaps.lo[g] * 3 + tid;
+    for (; w + 2 * kTileThreads < end; w += 3 * kTileThreads)
 #pragma unroll
-      for (uint32_t u = 0; u < 3; ++u)
-        if (w + u * kTileThreads < end) words[w + u * kTileThreads] = v[u];
+      for (uint32_t u = 0; u < 3; ++u) words[w + u * kTileThreads] = v[u];
+    if (w < end) words[w] = v[0];
+    if (w + kTileThreads < end) words[w + kTileThreads] = v[1];
   }
 }
 
