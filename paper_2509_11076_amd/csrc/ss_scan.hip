@@ -845,9 +845,11 @@ __device__ __forceinline__ TileSum sum_events(const ScanArgs &a, const Tile &tl,
 
 // Gaps of a tile of few events, each filled by the whole workgroup, 8 bytes a lane side by side: bound by how many stores a workgroup
 // has under way.  Both launches of 460 + 28 events over 58,299 operators 21 us, of 2,000 + 4 over 65,536 23; one by one by the first
-// wavefront, 64 entries of 24 bytes in 0.1 us (fill_gap), 29 and 56.  Where there are fewer operators to an event than kLongGaps that is as
-// fast (5 to one: 14.9 us, so 15.3; 7 to one: 16.4 and 14.7).
-constexpr uint32_t kFewInTile = 8, kLongGaps = 8;
+// wavefront, 64 entries of 24 bytes in 0.1 us (fill_gap), 29 and 56.  Up to kLongGaps operators to an event lanes and wavefronts that
+// each fill their own gaps are as fast or faster (both launches, filled each by its own and together; the list beside 2,000 events:
+// 9 operators to an event, 1,000 over 9,000: 13.9 us and 14.3; 40, 400 over 16,000: 14.1 and 14.3; 75, 400 over 30,000: 14.5 and 14.8;
+// 160, 100 over 16,000: 14.5 and 14.2; 300, 30 over 9,000: 14.0 and 13.7; 1,000, 16 over 16,000: 20 and 13.7).
+constexpr uint32_t kFewInTile = 8, kLongGaps = 128;
 
 __host__ __device__ inline bool few_in_tile(uint32_t tile, uint64_t events, uint32_t n_ops) {
   return events && tile <= kFewInTile && n_ops > kLongGaps * events;
@@ -1126,8 +1128,8 @@ __global__ __launch_bounds__(kThreads) void ss_scan_finish_kernel(ScanArgs a, ui
 // passes, 30.4 us, four 32.1, eight 42.9), so a lane gets two, or four, and beyond that a tile takes several passes of eight.
 // Where operators outnumber the events, filling the gaps between them is the work (a wavefront fills gaps above kAlone one
 // after the other), and few events to a tile spread it: 60,000 operators with 40,000 events and 2,000 of the policy
-// 82 -> 40 us, with 6,000 and 200 66 -> 41.  Of few events a tile takes so many that it fills about 1,024 operators (one each always:
-// 3,500 operators with 124 events 15.6 us, so 13.7).
+// 82 -> 40 us, with 6,000 and 200 66 -> 41.  Of at most 2,048 events a tile takes as many as fill about 1,024 operators, but no more
+// than 8 and no fewer than make 256 tiles (one each always: 3,500 operators with 124 events, which take 8, 15.6 us, so 13.7).
 // A lane that gets two or four loads them once, so there a tile is at most one pass.
 int events_per_lane(uint64_t n) {
   return n <= kMaxTiles * kTileThreads * 2 ? 2 : n <= kMaxTiles * kTileThreads * 4 ? 4 : 8;
