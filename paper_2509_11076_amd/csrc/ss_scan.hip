@@ -962,13 +962,14 @@ __global__ __launch_bounds__(kTileThreads) void ss_scan_running_kernel(ScanArgs 
   // Where filling gaps is the work it is not done for nothing if the other list is out of order: the policy's tiles wait for
   // those of the events, which were started before them (a reversed trace of 1,000 events over 65,536 operators beside 8 of
   // the policy: the call 269 us without and 217 with it), the events' own only look.  Of few events to a tile the tiles before
-  // the one where the order breaks look at the later ones of their list as well (10 events in random order, a tile each, beside 12 of
-  // the policy over 65,536 operators 151 us without and 127 with it; 100 events 144 and 126).
+  // the one where the order breaks look at a line of words of their list's next ones as well (10 events in random order, a tile each,
+  // beside 12 of the policy over 65,536 operators 151 us without and 127 with it; 100 events 144 and 126).
   if (a.n_ops > 2 * tl.cnt) {
     bool over = false;
     const uint32_t own_end = tl.policy ? a.tiles0 + a.tiles1 : a.tiles0;
+    constexpr uint32_t kLooks = 16;
     uint64_t later = 0;
-    if (kFew && tl.index + 1 + tid < own_end) later = __hip_atomic_load(&a.board->tile[4][tl.index + 1 + tid], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if (kFew && tid < kLooks && tl.index + 1 + tid < own_end) later = __hip_atomic_load(&a.board->tile[4][tl.index + 1 + tid], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     const uint64_t since = wall_clock64();
     const uint32_t first = tl.policy ? 0 : a.tiles0, end = tl.policy ? a.tiles0 : a.tiles0 + a.tiles1;
     for (uint32_t i = first + tid; i < end; i += kTileThreads) {
