@@ -831,8 +831,9 @@ __global__ __launch_bounds__(kEntries) void ss_align_tab_kernel(const Id *__rest
                                                                 const uint32_t *__restrict__ masks,
                                                                 uint32_t W, uint32_t n_steps,
                                                                 const uint32_t *__restrict__ rows,
-                                                                uint16_t *__restrict__ table) {
+                                                                uint16_t *__restrict__ table, const uint32_t *__restrict__ n_keys) {
   __shared__ Tile tile;
+  if (sizeof(Id) == 2 && *n_keys >= kLdsKeys) return;        // launched before the number was known, and there are no rows
   const uint32_t k = blockIdx.x, e0 = win.start(k) + blockIdx.y * kEntries;
   if (e0 > win.m) return;
   const RowBlock blk(k, win.n);
@@ -905,8 +906,11 @@ constexpr uint32_t kChainThreads = 256;
 
 // The table of a group of blocks, for the window of its first: at most 8 * (kEntries + kMargin) columns.  upto: what the group's
 // blocks take up to each of them, so that a block finds its entry from its group's with one read (block by block 4 us).
+template <class Id>
 __global__ __launch_bounds__(256) void ss_align_compose_kernel(const uint16_t *__restrict__ table, Windows win, uint32_t K,
-                                                               uint16_t *__restrict__ upto, uint16_t *__restrict__ groups) {
+                                                               uint16_t *__restrict__ upto, uint16_t *__restrict__ groups,
+                                                               const uint32_t *__restrict__ n_keys) {
+  if (sizeof(Id) == 2 && *n_keys >= kLdsKeys) return;        // nor tables
   const uint32_t k0 = blockIdx.x * kGroupBlocks, i = blockIdx.y * 256 + threadIdx.x, entry = win.start(k0) + i;
   uint32_t j = entry;
   bool known = j <= win.m;
@@ -939,7 +943,7 @@ __global__ __launch_bounds__(kChainThreads) void ss_align_chain_kernel(const Id 
   __shared__ uint4 tabs[kChainGroups * kWindow / 8];
   __shared__ uint32_t left;
   const uint32_t n = win.n, size = win.size;
-  if (sizeof(Id) == 2 && *n_keys >= kLdsKeys) return;        // launched before the number was known, and there are no rows
+  if (sizeof(Id) == 2 && *n_keys >= kLdsKeys) return;
   if (threadIdx.x == 0) left = 0;
   constexpr uint32_t kPer = kChainGroups * kWindow / 8 / kChainThreads;
   const uint32_t K = (n + kWalkRows - 1) / kWalkRows, G = (K + kGroupBlocks - 1) / kGroupBlocks;
@@ -1164,9 +1168,9 @@ int launch_walk(ss_ctx *ctx, const Layout &y, uint8_t *d, uint8_t *hd, bool narr
   done = ss_next_done(ctx);
   ss_told_by(done, y.walk_blocks);
   hipLaunchKernelGGL(ss_align_tab_kernel<Id>, dim3(y.walk_blocks, win.size / kEntries), dim3(kEntries), 0, s, ref_id, win, masks,
-                     y.W, y.n_steps, rows, table);
-  hipLaunchKernelGGL(ss_align_compose_kernel, dim3(y.walk_groups, win.size / 256), dim3(256), 0, s, table, win, y.walk_blocks, upto,
-                     groups);
+                     y.W, y.n_steps, rows, table, n_keys);
+  hipLaunchKernelGGL(ss_align_compose_kernel<Id>, dim3(y.walk_groups, win.size / 256), dim3(256), 0, s, table, win, y.walk_blocks, upto,
+                     groups, n_keys);
   hipLaunchKernelGGL(ss_align_chain_kernel<Id>, dim3(1), dim3(kChainThreads), 0, s, ref_id, win, masks, y.W, y.n_steps, rows, table,
                      groups, entry, group_entry, pair, strayed, n_keys);
   hipLaunchKernelGGL(ss_align_pairs_kernel<Id>, dim3(y.walk_blocks), dim3(kPairThreads), 0, s, ref_id, win, masks, y.W, y.n_steps,
@@ -1291,9 +1295,8 @@ int ss_align_core(ss_ctx *ctx, const ss_op_t *ref, uint32_t n, const ss_op_t *cu
                         : launch_rows<uint32_t>(ctx, y, d, hd, keys, done, one_by_one);
     return r != SS_OK ? r : ss_wait_done(ctx, done);
   };
-  // Rows and walk at once, as if there were few keys (the kernels of the rows look again): one wait less, some 8 us.  If there are
-  // more it is all for nothing, so a context whose last call had more waits for their number before.  The tables that are then made
-  // of ids of another form take them for keys below kLdsKeys, so nothing out of range is read, and nothing looks at them.
+  // Rows and walk at once, as if there were few keys (every kernel looks again): one wait less, some 8 us.  If there are more the
+  // launches are for nothing, so a context whose last call had more waits for their number before.
   if (y.one_wg || !ctx->align_many_keys) {
     if (!(y.one_wg && y.strips == 1) && (rc = launch_rows<uint16_t>(ctx, y, d, hd, keys, done, false, !y.one_wg)) != SS_OK) return rc;
     if ((rc = ss_wait_done(ctx, done)) != SS_OK) return rc;
