@@ -810,19 +810,23 @@ __device__ __forceinline__ uint32_t words_that_stop(uint32_t n_rows, const Tile 
 // by the instructions of a row, some 25 for a wavefront's 64 entries; with a search from word to word and early ends 65.
 // at: the column, counted from 32 before the tile's first; 31 (nothing left in the tile) leads to the empty word in front of the
 // row, which leads back to 31.
+struct TileStep { uint32_t stops, equal; };                  // whether there is a stop; whether the row's operator is equal there
+
+__device__ __forceinline__ TileStep step_row(const Tile &tile, uint32_t q, uint32_t some, uint32_t &at) {
+  const uint32_t word = at >> 5;
+  const uint32_t other = ~(uint32_t)leading_zeros(__builtin_amdgcn_ubfe(some, 0, word)) & 31u;
+  const TileWord here = tile[q][word], below = tile[q][other];
+  const uint32_t upto = here.stops & (~0u >> (~at & 31u));
+  const uint32_t stops = upto ? upto : below.stops, equal = upto ? here.equal : below.equal;
+  const uint32_t lead = leading_zeros(stops), there = equal >> (~lead & 31u) & 1u;
+  at = ((upto ? word : other) << 5) + (31 - lead) - there;
+  return TileStep{stops, there};
+}
+
 __device__ __forceinline__ int walk_tile(uint32_t n_rows, int w0, int j, const Tile &tile) {
   const uint32_t rows_some = words_that_stop(n_rows, tile);
   uint32_t at = (uint32_t)(j - 1 - w0 * 32 + 32);
-  for (uint32_t q = 0; q < n_rows; ++q) {
-    const uint32_t some = (uint32_t)__builtin_amdgcn_readlane((int)rows_some, q);
-    const uint32_t word = at >> 5;
-    const uint32_t other = ~(uint32_t)leading_zeros(__builtin_amdgcn_ubfe(some, 0, word)) & 31u;
-    const TileWord here = tile[q][word], below = tile[q][other];
-    const uint32_t upto = here.stops & (~0u >> (~at & 31u));
-    const uint32_t stops = upto ? upto : below.stops, equal = upto ? here.equal : below.equal;
-    const uint32_t lead = leading_zeros(stops);
-    at = ((upto ? word : other) << 5) + (31 - lead) - (equal >> (~lead & 31u) & 1u);
-  }
+  for (uint32_t q = 0; q < n_rows; ++q) step_row(tile, q, (uint32_t)__builtin_amdgcn_readlane((int)rows_some, q), at);
   return at == 31 && w0 > 0 ? -1 : max(0, (int)at - 31 + w0 * 32);
 }
 
@@ -1020,12 +1024,16 @@ __global__ __launch_bounds__(kChainThreads) void ss_align_chain_kernel(const Id 
 
 // The walk through a block from j columns left by one wavefront, lane q the block's row q; returns the column that the row pairs
 // with, or -1.  Equal operators run along the diagonal: each lane tests its own row's bit there and a ballot tells how long the
-// run is; in the row that it ends in, sixteen lanes look for the highest column below that is equal or steps up.
+// run is; in the row that it ends in, sixteen lanes look for the highest column below that is equal or steps up.  A block of many
+// short runs is gone through row by row as by walk_tile: 0.1 us a row, a run's end takes 0.2.
+constexpr uint32_t kManyRuns = 16;
+
 __device__ __forceinline__ int32_t walk_runs(uint32_t n_rows, int w0, int j, const Tile &tile) {
   const int lane = threadIdx.x & 63, l = lane % (int)kTileWords;
   int32_t mine = -1;
   uint32_t q = 0;
-  while (q < n_rows && j > 0) {
+  for (uint32_t runs = 0; runs < kManyRuns; ++runs) {
+    if (q >= n_rows || j <= 0) return mine;
     const int c = j - 1 - (lane - (int)q), w = (c >> 5) - w0;
     const bool hit = lane >= (int)q && lane < (int)n_rows && c >= 0 && w >= 0 && (tile[lane][w + 1].equal >> (c & 31) & 1u);
     const u64 missed = ~(__builtin_amdgcn_ballot_w64(hit) >> q);       // the shift brings in zeros
@@ -1033,16 +1041,23 @@ __device__ __forceinline__ int32_t walk_runs(uint32_t n_rows, int w0, int j, con
     if (lane >= (int)q && lane < (int)(q + run)) mine = c;
     q += run;
     j -= (int)run;
-    if (q >= n_rows || j <= 0) break;
+    if (q >= n_rows || j <= 0) return mine;
     const int at = ((j - 1) >> 5) - w0;
-    if (at < 0) break;                                       // left of the tile: the table had no entry
-    const uint32_t bits = l <= at ? tile[q][l + 1].stops & (l == at ? ~0u >> (31 - ((j - 1) & 31)) : ~0u) : 0;
+    if (at < 0) return mine;                                 // left of the tile: the table had no entry
+    const TileWord x = tile[q][l + 1];
+    const uint32_t bits = l <= at ? x.stops & (l == at ? ~0u >> (31 - ((j - 1) & 31)) : ~0u) : 0;
     const uint32_t there = (uint32_t)__builtin_amdgcn_ballot_w64(bits != 0) & ((1u << kTileWords) - 1);
-    if (!there) break;                                       // all the columns are used up
+    if (!there) return mine;                                 // all the columns are used up
     const int word = 31 - __builtin_clz(there);
     const int b = 31 - __builtin_clz((uint32_t)__builtin_amdgcn_readlane((int)bits, word));
     j = (word + w0) * 32 + b + 1;
-    if (!(__builtin_amdgcn_readfirstlane(tile[q][word + 1].equal) >> b & 1u)) ++q;            // up; else the next run begins there
+    if (!((uint32_t)__builtin_amdgcn_readlane((int)x.equal, word) >> b & 1u)) ++q;            // up; else the next run begins there
+  }
+  const uint32_t rows_some = words_that_stop(n_rows, tile);
+  uint32_t at = (uint32_t)(j - 1 - w0 * 32 + 32);
+  for (; q < n_rows; ++q) {
+    const TileStep x = step_row(tile, q, (uint32_t)__builtin_amdgcn_readlane((int)rows_some, q), at);
+    if (x.stops && x.equal && lane == (int)q) mine = (int32_t)(at - 32) + w0 * 32 + 1;
   }
   return mine;
 }
