@@ -849,58 +849,88 @@ __global__ __launch_bounds__(kEntries) void ss_align_tab_kernel(const Id *__rest
   table[(size_t)k * win.size + blockIdx.y * kEntries + threadIdx.x] = out < 0 || j > (int)win.m ? kNoEntry : (uint16_t)(j - out);
 }
 
-// One wavefront walks a block in place and writes its pairs: lane q holds one 64-bit word of row hi - 1 - q.  A run of
-// equal operators steps one row and one column at a time, so each lane tests the bit of its own row on the diagonal
+// One wavefront walks a block in place and writes its pairs: lane q holds 64-bit words of row hi - 1 - q, id is the row's key.  A run
+// of equal operators steps one row and one column at a time, so each lane tests the bit of its own row on the diagonal
 // and the run's length is the number of leading ones; then one find-first in the row the run ended in.
-template <class Id>
-__device__ uint32_t walk_in_place(const Id *ref_id, const uint32_t *masks, const uint32_t *rows, uint32_t W,
-                                  uint32_t n_steps, RowBlock blk, uint32_t j, int32_t *ref_to_cur) {
-  const int lane = threadIdx.x & 63, n_rows = (int)(blk.hi - blk.lo), r = (int)blk.hi - 1 - lane;
-  const bool mine_is_row = lane < n_rows;
-  const uint32_t id = mine_is_row ? key_of(ref_id[kIdPad + r]) : 0;
+// Bound by the latency of the words' loads: four words to the left are loaded at a time, by every lane, also beside the rows and
+// the words, whose bits nobody looks at (one word ahead at a time, handed on from word to word, is copied behind its load, which is
+// waited for: 15,000 operators and the first 5,000 of them, most of whose path lies outside the windows, 2,044 us a call, so up to
+// 2,500).  Through columns without a stop it goes 4,096 at a time (word by word 16,000 operators with nothing in common 743 us
+// a call, so 361).
+__device__ uint32_t walk_in_place(uint32_t id, const uint32_t *masks, const uint32_t *rows, uint32_t W, uint32_t n_steps, RowBlock blk,
+                                  uint32_t j, int32_t *ref_to_cur) {
+  const int lane = threadIdx.x & 63, n_rows = (int)(blk.hi - blk.lo), r = max((int)blk.hi - 1 - lane, (int)blk.lo);
+  const int row = lane < n_rows ? lane : -1;
   struct Word { u64 M, V; };
+  // Every lane loads, also beside the rows and the words, whose bits nobody looks at: no value is put together behind a load, which
+  // would be waited for.
   auto load = [&](int w) -> Word {
-    Word x = {0ull, ~0ull};
-    if (w >= 0 && mine_is_row) {
-      const uint32_t a = 2 * (uint32_t)w, b = min(a + 1, W - 1);       // an odd last word: its upper half is never reached
-      x.M = ((u64)masks[(size_t)id * W + b] << 32) | masks[(size_t)id * W + a];
-      x.V = ((u64)rows[row_word((uint32_t)r, b, W, n_steps)] << 32) | rows[row_word((uint32_t)r, a, W, n_steps)];
-    }
-    return x;
+    const uint32_t a = 2 * (uint32_t)max(w, 0), b = min(a + 1, W - 1);     // an odd last word: its upper half is never reached
+    return Word{((u64)masks[(size_t)id * W + b] << 32) | masks[(size_t)id * W + a],
+                ((u64)rows[row_word((uint32_t)r, b, W, n_steps)] << 32) | rows[row_word((uint32_t)r, a, W, n_steps)]};
   };
-  int w = (int)(j - 1) >> 6, p = (int)(j - 1) & 63, q = 0;
-  Word here = load(w), left = load(w - 1);
+  // the highest word below w with a stop in the block's row q, 64 words at a time; -1: there is none
+  auto jump = [&](int w, int q) -> int {
+    const uint32_t row = blk.hi - 1 - (uint32_t)q, mask_row = (uint32_t)__builtin_amdgcn_readlane((int)id, q);
+    for (int at = w - 1; at >= 0; at -= 64) {
+      u64 stops = 0;
+      if (at >= lane) {
+        const uint32_t a = 2 * (uint32_t)(at - lane);
+        stops = ((u64)masks[(size_t)mask_row * W + a + 1] << 32) | masks[(size_t)mask_row * W + a];
+        stops |= ~(((u64)rows[row_word(row, a + 1, W, n_steps)] << 32) | rows[row_word(row, a, W, n_steps)]);
+      }
+      const u64 there = __builtin_amdgcn_ballot_w64(stops != 0);
+      if (there) return at - __builtin_ctzll(there);
+    }
+    return -1;
+  };
+  int w = (int)(j - 1) >> 6, p = (int)(j - 1) & 63, q = 0, empty = 0, empty_row = -1;
   int32_t mine = -1;
   while (w >= 0 && q < n_rows) {
-    const int sh = p - (lane - q);
-    const bool hit = lane >= q && sh >= 0 && ((here.M >> (sh & 63)) & 1ull);
-    const u64 diag = __builtin_amdgcn_ballot_w64(hit) >> q;
-    const int run = ~diag ? __builtin_ctzll(~diag) : 64;     // the shift brings in zeros: at most 64 - q
-    if (lane >= q && lane < q + run) mine = w * 64 + sh;
-    q += run;
-    p -= run;
-    if (q < n_rows && p >= 0) {
-      const u64 x = here.M | ~here.V;
-      const u64 xq = ((u64)(uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(x >> 32), q) << 32) |
-                     (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)x, q);
-      const u64 cand = xq & (~0ull >> (63 - p));
-      if (cand) {
+    constexpr int kAhead = 4, kStepped = 2;                  // words loaded at a time; without a stop gone through one by one
+    Word words[kAhead];
+#pragma unroll
+    for (int i = 0; i < kAhead; ++i) words[i] = load(w - i);
+#pragma unroll
+    for (int i = 0; i < kAhead; ++i) {
+      const Word here = words[i];
+      if (w < 0) break;
+      while (p >= 0 && q < n_rows) {
+        const int sh = p - (lane - q);
+        const bool hit = row >= q && sh >= 0 && ((here.M >> (sh & 63)) & 1ull);
+        const u64 diag = __builtin_amdgcn_ballot_w64(hit) >> q;
+        const int run = ~diag ? __builtin_ctzll(~diag) : 64; // the shift brings in zeros: at most 64 - q
+        if (lane >= q && lane < q + run) mine = w * 64 + sh;
+        q += run;
+        p -= run;
+        if (q >= n_rows || p < 0) break;
+        const u64 x = here.M | ~here.V;
+        const u64 xq = ((u64)(uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(x >> 32), q) << 32) |
+                       (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)x, q);
+        const u64 cand = xq & (~0ull >> (63 - p));
+        if (!cand) {
+          p = -1;
+          empty = q == empty_row ? empty + 1 : 1;
+          empty_row = q;
+          break;
+        }
         p = 63 - __builtin_clzll(cand);
         const u64 mq = ((u64)(uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(here.M >> 32), q) << 32) |
                        (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)here.M, q);
         if (!((mq >> p) & 1ull)) ++q;                        // not equal there: up
-      } else {
-        p = -1;
       }
+      if (p < 0) {                                           // on to the word to the left
+        p = 63;
+        --w;
+      }
+      if (q >= n_rows) break;
     }
-    if (p < 0) {                                             // on to the word to the left
-      p = 63;
-      --w;
-      here = left;
-      left = load(w - 1);
+    if (empty > kStepped && q == empty_row) {                // or to the next that holds a stop
+      w = jump(w + 1, q);
+      empty = 0;
     }
   }
-  if (mine_is_row) ref_to_cur[r] = mine;
+  if (row >= 0) ref_to_cur[r] = mine;
   return w < 0 ? 0 : (uint32_t)(64 * w + p + 1);
 }
 
@@ -1011,8 +1041,11 @@ __global__ __launch_bounds__(kChainThreads) void ss_align_chain_kernel(const Id 
           if (e != kNoEntry)
             j -= e;
           else
-            j = __builtin_amdgcn_readfirstlane(
-                walk_in_place(ref_id, masks, rows, W, n_steps, RowBlock(k, n), j, ref_to_cur));
+          {
+            const RowBlock blk(k, n);
+            const Id id = threadIdx.x < blk.hi - blk.lo ? ref_id[kIdPad + blk.hi - 1 - threadIdx.x] : Id(0);
+            j = __builtin_amdgcn_readfirstlane(walk_in_place(key_of(id), masks, rows, W, n_steps, blk, j, ref_to_cur));
+          }
         }
       }
       if (threadIdx.x < kChainGroups && g0 + threadIdx.x < G) group_entry[g0 + threadIdx.x] = entries;

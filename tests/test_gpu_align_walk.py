@@ -86,3 +86,16 @@ def test_blocks_of_short_runs(P, ctx, period):                     # noqa: F811
     cur = np.where(np.arange(len(ref)) % period == 0, 50, ref)
     same(P, ctx, ref, cur)
     same(P, ctx, ref, np.where(np.arange(len(ref)) // 640 % 2, rng.integers(0, 20, len(ref)), cur))
+
+
+@pytest.mark.parametrize("keys", [40, 900])
+@pytest.mark.parametrize("gap", [130, 192, 256, 300, 4032, 4096, 4170, 8400])
+def test_far_to_the_left_in_one_row(P, ctx, keys, gap):            # noqa: F811
+    """columns without a stop: some words of them, as many as are looked at together and more, at the end, between equal stretches
+    and at the front of cur"""
+    rng = np.random.default_rng([keys, gap])
+    ref = rng.integers(0, keys, 9050)
+    foreign = np.full(gap, keys + 7)
+    for at in (len(ref), 5003, 4992, 64, 0):
+        same(P, ctx, ref, np.concatenate([ref[:at], foreign, ref[at:]]))
+    same(P, ctx, ref, np.concatenate([foreign, ref[200:300], foreign, ref[4000:4001], foreign]))
