@@ -709,12 +709,16 @@ __global__ __launch_bounds__(kWgThreads) void ss_align_short_kernel(KeyArgs k, R
 // table has no entry the chain follows its blocks' own, and a block whose entry lies outside its window, or whose path
 // leaves the tile to the left, is walked in place by a wavefront of the chain.
 // 32,312 rows: 28 us for the tables, 5 us for the groups' and 11 us for the chain (an LDS read and a few vector operations
-// per group; 17 where each group's went through the scalar unit, 90 block by block), 14 us for the pairs; single steps in one wavefront took 97 ns a row (3.1
-// ms), the rows over the host link (130 MB) 2.3 ms and a walk there.
+// per group; 17 where each group's went through the scalar unit, 90 block by block), 14 us for the pairs; single steps in one
+// wavefront took 97 ns a row (3.1 ms), the rows over the host link (130 MB) 2.3 ms and a walk there.
 constexpr uint32_t kWalkRows = 64;
-// Entry columns tabulated per block of rows.  A path strays from the diagonal by some hundred columns where operators come and go
-// all along the sequences, so half as many are tried first where their lengths differ by no more than that; if it turns out to
-// leave them the walk is made again with all (32,312 rows: tables 48 us, half as many 27.6).
+// Entry columns tabulated per block of rows (windows): kWindow; or, where the lengths differ by at most kNearlyEqual, kNarrowWindow
+// first, since a path of operators that come and go all along the sequences strays from the diagonal by some hundred columns (32,312
+// rows: tables 48 us, half as many 28).  If it leaves them after all, the walk goes on from there with kWindow columns around the
+// diagonal of what is left, which finds a path that has come to lie beside the first one.
+// us a call, sequences of 9,000 with 700 foreign operators in a quarter of one and as many missing in the last of it: 247, by a second
+// walk of all blocks 272, with kWindow alone 254; with 1,500 foreign ones 266, 392 and 351; without any 208, 207 and 243 (the last
+// with the tables' older kernel).
 constexpr uint32_t kWindow = 2048, kNarrowWindow = 1024, kNearlyEqual = 512;
 constexpr uint32_t kEntries = 256;                     // of these, per workgroup
 constexpr uint32_t kMargin = 256;                      // columns a tile reaches to the left of its first entry
@@ -731,11 +735,14 @@ struct RowBlock {
   __device__ RowBlock(uint32_t k, uint32_t n) : lo(n > (k + 1) * kWalkRows ? n - (k + 1) * kWalkRows : 0), hi(n - k * kWalkRows) {}
 };
 
-// The windows' size, and where a block's starts (columns left): a multiple of kEntries, the scaled diagonal in the middle.
+// The windows' size, and where a block's starts (columns left): a multiple of kEntries, the scaled diagonal in the middle, or, of
+// windows of all columns, 0.
 struct Windows {
-  uint64_t slope;                      // m / n, 32 bits of it behind the point
+  uint64_t slope;                      // columns to a row, 32 bits of them behind the point
   uint32_t n, m, size;
-  Windows(uint32_t n_, uint32_t m_, uint32_t size_) : slope(((uint64_t)m_ << 32) / n_), n(n_), m(m_), size(size_) {}
+  // of a walk that begins with `rows` rows and `columns` columns left
+  Windows(uint32_t n_, uint32_t m_, uint32_t size_, uint32_t rows, uint32_t columns)
+      : slope(size_ > m_ ? 0 : ((uint64_t)columns << 32) / rows), n(n_), m(m_), size(size_) {}
   __device__ __forceinline__ uint32_t start(uint32_t k) const {
     const uint32_t mid = (uint32_t)((n - k * kWalkRows) * slope >> 32);
     return (mid > size / 2 ? mid - size / 2 + kEntries / 2 : 0) / kEntries * kEntries;
@@ -835,10 +842,10 @@ __global__ __launch_bounds__(kEntries) void ss_align_tab_kernel(const Id *__rest
                                                                 const uint32_t *__restrict__ masks,
                                                                 uint32_t W, uint32_t n_steps,
                                                                 const uint32_t *__restrict__ rows,
-                                                                uint16_t *__restrict__ table, const uint32_t *__restrict__ n_keys) {
+                                                                uint16_t *__restrict__ table, const uint32_t *__restrict__ n_keys, uint32_t k_first) {
   __shared__ Tile tile;
   if (sizeof(Id) == 2 && *n_keys >= kLdsKeys) return;        // launched before the number was known, and there are no rows
-  const uint32_t k = blockIdx.x, e0 = win.start(k) + blockIdx.y * kEntries;
+  const uint32_t k = k_first + blockIdx.x, e0 = win.start(k) + blockIdx.y * kEntries;
   if (e0 > win.m) return;
   const RowBlock blk(k, win.n);
   const int w0 = (int)(e0 / 32) - (int)(kMargin / 32);
@@ -942,10 +949,10 @@ constexpr uint32_t kChainThreads = 256;
 // blocks take up to each of them, so that a block finds its entry from its group's with one read (block by block 4 us).
 template <class Id>
 __global__ __launch_bounds__(256) void ss_align_compose_kernel(const uint16_t *__restrict__ table, Windows win, uint32_t K,
-                                                               uint16_t *__restrict__ upto, uint16_t *__restrict__ groups,
-                                                               const uint32_t *__restrict__ n_keys) {
+                                                               uint16_t *__restrict__ upto, uint32_t upto_stride, uint16_t *__restrict__ groups,
+                                                               const uint32_t *__restrict__ n_keys, uint32_t g_first) {
   if (sizeof(Id) == 2 && *n_keys >= kLdsKeys) return;        // nor tables
-  const uint32_t k0 = blockIdx.x * kGroupBlocks, i = blockIdx.y * 256 + threadIdx.x, entry = win.start(k0) + i;
+  const uint32_t g = g_first + blockIdx.x, k0 = g * kGroupBlocks, i = blockIdx.y * 256 + threadIdx.x, entry = win.start(k0) + i;
   uint32_t j = entry;
   bool known = j <= win.m;
   const uint32_t end = min(k0 + kGroupBlocks, K);
@@ -953,54 +960,93 @@ __global__ __launch_bounds__(256) void ss_align_compose_kernel(const uint16_t *_
     const uint32_t d = known ? win.taken(table, k, j) : kNoEntry;
     known = d != kNoEntry;
     if (known) j -= d;
-    upto[(size_t)k * win.size + i] = known ? (uint16_t)(entry - j) : kNoEntry;
+    upto[(size_t)k * upto_stride + i] = known ? (uint16_t)(entry - j) : kNoEntry;
   }
-  groups[(size_t)blockIdx.x * win.size + i] = known ? (uint16_t)(entry - j) : kNoEntry;
+  groups[(size_t)g * win.size + i] = known ? (uint16_t)(entry - j) : kNoEntry;
 }
 
-// group_entry[g]: columns left when the walk enters group g, or -1 if its blocks have been followed one by one here;
-// then entry[k] is that of block k, or -1 if the block has been walked here.  strayed (narrow windows): the path has left them,
-// nothing else is meaningful.
-struct Strayed { uint32_t *device, *host; };
+// Where a walk with narrow windows ends because the path has left them: the block's number and 1, and the columns left there.  The
+// host is told at once; the pairs are left to the walk that goes on from there.
+struct Strayed { uint32_t *device, *host_block, *host_columns; ss_done done; };
 
+// group_entry[g]: columns left when the walk enters group g, or -1 if its blocks have been followed one by one here;
+// then entry[k] is that of block k, or -1 if the block has been walked here.  The walk begins at block k_first with j_first columns
+// left and ends with the last block, or at the one it strays at: what lies before that is as it would have been.
 template <class Id>
 __global__ __launch_bounds__(kChainThreads) void ss_align_chain_kernel(const Id *__restrict__ ref_id, Windows win,
                                                                        const uint32_t *__restrict__ masks,
                                                                        uint32_t W, uint32_t n_steps,
                                                                        const uint32_t *__restrict__ rows,
                                                                        const uint16_t *__restrict__ table,
+                                                                       const uint16_t *__restrict__ upto, uint32_t upto_stride,
                                                                        const uint16_t *__restrict__ groups,
                                                                        int32_t *__restrict__ entry,
                                                                        int32_t *__restrict__ group_entry,
                                                                        int32_t *__restrict__ ref_to_cur, Strayed strayed,
-                                                                       const uint32_t *__restrict__ n_keys) {
-  __shared__ uint4 tabs[kChainGroups * kWindow / 8];
+                                                                       const uint32_t *__restrict__ n_keys, uint32_t k_first, uint32_t j_first) {
+  constexpr uint32_t kTabs = kChainGroups * kWindow / 8, kPer = kTabs / kChainThreads;
+  __shared__ uint4 tabs[kTabs];
   __shared__ uint32_t left;
   const uint32_t n = win.n, size = win.size;
   if (sizeof(Id) == 2 && *n_keys >= kLdsKeys) return;
   if (threadIdx.x == 0) left = 0;
-  constexpr uint32_t kPer = kChainGroups * kWindow / 8 / kChainThreads;
   const uint32_t K = (n + kWalkRows - 1) / kWalkRows, G = (K + kGroupBlocks - 1) / kGroupBlocks;
   const uint4 *src = reinterpret_cast<const uint4 *>(groups);
-  const uint32_t total = G * (size / 8), turn = kChainGroups * (size / 8);        // at most 2^10 tables of 2^11 entries
+  const uint32_t of_turn = min(kChainGroups, kTabs * 8 / size);
+  const uint32_t total = G * (size / 8), turn = of_turn * (size / 8);      // at most 2^10 tables of 2^13 entries
   uint4 next[kPer];
   auto fetch = [&](uint32_t g0) {
 #pragma unroll
     for (uint32_t i = 0; i < kPer; ++i) {
-      const uint32_t of_turn = i * kChainThreads + threadIdx.x, at = g0 * (size / 8) + of_turn;
-      next[i] = of_turn < turn && at < total ? src[at] : uint4{0, 0, 0, 0};
+      const uint32_t x = i * kChainThreads + threadIdx.x, at = g0 * (size / 8) + x;
+      next[i] = x < turn && at < total ? src[at] : uint4{0, 0, 0, 0};
     }
   };
-  fetch(0);
-  uint32_t j = win.m;                                        // wavefront 0's own
-  for (uint32_t g0 = 0; g0 < G; g0 += kChainGroups) {
+  uint32_t j = j_first;                                      // wavefront 0's own
+  // block by block, up to block `end`; false: the path has left the windows
+  auto row_id = [&](uint32_t k) {
+    const RowBlock blk(k, n);
+    const uint32_t q = threadIdx.x & 63;
+    return q < blk.hi - blk.lo ? ref_id[kIdPad + blk.hi - 1 - q] : Id(0);
+  };
+  auto follow = [&](uint32_t k, uint32_t end) {
+    Id ahead = row_id(k);
+    for (; k < end; ++k) {
+      const Id id = ahead;
+      if (k + 1 < end) ahead = row_id(k + 1);
+      if (strayed.device && j - win.start(k) >= size) {
+        if (threadIdx.x == 0) {
+          left = 1;
+          *strayed.device = k + 1;
+          __hip_atomic_store(strayed.host_block, k + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+          __hip_atomic_store(strayed.host_columns, j, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+          if (strayed.done.flag) {
+            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "");
+            __hip_atomic_store(strayed.done.flag, strayed.done.value, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+          }
+        }
+        return false;
+      }
+      const uint32_t e = __builtin_amdgcn_readfirstlane(win.taken(table, k, j));
+      if (threadIdx.x == 0) entry[k] = e != kNoEntry ? (int32_t)j : -1;
+      if (e != kNoEntry)
+        j -= e;
+      else
+        j = __builtin_amdgcn_readfirstlane(walk_in_place(key_of(id), masks, rows, W, n_steps, RowBlock(k, n), j, ref_to_cur));
+    }
+    return true;
+  };
+  const uint32_t g_first = (k_first + kGroupBlocks - 1) / kGroupBlocks;    // the walk may begin within the group before
+  fetch(g_first);
+  if (k_first % kGroupBlocks && threadIdx.x < 64) follow(k_first, min(g_first * kGroupBlocks, K));
+  for (uint32_t g0 = g_first; g0 < G; g0 += of_turn) {
 #pragma unroll
     for (uint32_t i = 0; i < kPer; ++i) tabs[i * kChainThreads + threadIdx.x] = next[i];
     __syncthreads();
-    fetch(g0 + kChainGroups);
+    fetch(g0 + of_turn);
     if (threadIdx.x < 64) {
       const uint16_t *t = reinterpret_cast<const uint16_t *>(tabs);
-      const uint32_t mine = min(g0 + (threadIdx.x & (kChainGroups - 1)), G - 1);
+      const uint32_t here = min(of_turn, G - g0), mine = min(g0 + (threadIdx.x & (kChainGroups - 1)), G - 1);
       const uint32_t starts = win.start(mine * kGroupBlocks);               // lane u: group g0 + u's
       int32_t entries = 0;                                   // likewise
       // where every table has its entry: nothing goes through the scalar unit between two of them
@@ -1009,7 +1055,7 @@ __global__ __launch_bounds__(kChainThreads) void ss_align_chain_kernel(const Id 
 #pragma unroll
       for (uint32_t u = 0; u < kChainGroups; ++u) {
         const uint32_t at = v - (uint32_t)__builtin_amdgcn_readlane((int)starts, u);       // before the window: wraps to a large number
-        const uint32_t d = g0 + u < G ? at < size ? t[u * size + min(at, size - 1)] : kNoEntry : 0;
+        const uint32_t d = u < here ? at < size ? t[u * size + min(at, size - 1)] : kNoEntry : 0;
         entries = threadIdx.x == u ? (int32_t)v : entries;
         known &= d != kNoEntry;
         v -= d;
@@ -1017,7 +1063,7 @@ __global__ __launch_bounds__(kChainThreads) void ss_align_chain_kernel(const Id 
       const bool all = __builtin_amdgcn_ballot_w64(known) == ~0ull;
       if (all) j = (uint32_t)__builtin_amdgcn_readfirstlane((int)v);
 #pragma unroll 1
-      for (uint32_t u = 0; !all && u < kChainGroups && g0 + u < G; ++u) {
+      for (uint32_t u = 0; !all && u < here; ++u) {
         const uint32_t at = j - (uint32_t)__builtin_amdgcn_readlane((int)starts, u);       // before the window: wraps to a large number
         const uint32_t d = at < size ? __builtin_amdgcn_readfirstlane((uint32_t)t[u * size + at]) : kNoEntry;
         if (threadIdx.x == u) entries = d != kNoEntry ? (int32_t)j : -1;
@@ -1026,29 +1072,18 @@ __global__ __launch_bounds__(kChainThreads) void ss_align_chain_kernel(const Id 
           continue;
         }
         const uint32_t k0 = (g0 + u) * kGroupBlocks;
-        for (uint32_t k = k0; k < min(k0 + kGroupBlocks, K); ++k) {
-          if (strayed.device && j - win.start(k) >= size) {
-            if (threadIdx.x == 0) {
-              left = 1;
-              *strayed.device = 1;
-              __hip_atomic_store(strayed.host, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
-            }
-            u = kChainGroups;                                // no more groups, and no more turns
-            break;
-          }
-          const uint32_t e = __builtin_amdgcn_readfirstlane(win.taken(table, k, j));
-          if (threadIdx.x == 0) entry[k] = e != kNoEntry ? (int32_t)j : -1;
-          if (e != kNoEntry)
-            j -= e;
-          else
-          {
-            const RowBlock blk(k, n);
-            const Id id = threadIdx.x < blk.hi - blk.lo ? ref_id[kIdPad + blk.hi - 1 - threadIdx.x] : Id(0);
-            j = __builtin_amdgcn_readfirstlane(walk_in_place(key_of(id), masks, rows, W, n_steps, blk, j, ref_to_cur));
-          }
+        uint32_t known_blocks = 0;                           // whose way through the group's first blocks is tabulated
+        if (at < size) {
+          const uint32_t b = threadIdx.x & 63;
+          const uint32_t c = b < kGroupBlocks && k0 + b < K ? upto[(size_t)(k0 + b) * upto_stride + at] : kNoEntry;
+          known_blocks = (uint32_t)__builtin_ctzll(__builtin_amdgcn_ballot_w64(c == kNoEntry));
+          const uint32_t before = dpp_u32<0x111, 0xF>(c, 0);               // of the block before
+          if (b < known_blocks) entry[k0 + b] = (int32_t)(j - before);
+          if (known_blocks) j -= (uint32_t)__builtin_amdgcn_readlane((int)c, known_blocks - 1);
         }
+        if (!follow(k0 + known_blocks, min(k0 + kGroupBlocks, K))) break;
       }
-      if (threadIdx.x < kChainGroups && g0 + threadIdx.x < G) group_entry[g0 + threadIdx.x] = entries;
+      if (threadIdx.x < here) group_entry[g0 + threadIdx.x] = entries;
     }
     __syncthreads();
     if (left) return;
@@ -1095,6 +1130,7 @@ __device__ __forceinline__ int32_t walk_runs(uint32_t n_rows, int w0, int j, con
   return mine;
 }
 
+// Blocks from k_win on were walked by the chain with windows `win`, those before with `first`.
 // One wavefront walks, all of them load its tile.  Bound by the latency of loads that need each other (the group's entry, the
 // block's, the tile's ids and masks) and of the walk's LDS reads: 32,312 rows 14.0 us; with one thread that walks row by row, the
 // block's entry by up to seven reads one after the other and the tile's loads one after the other 20.1.
@@ -1102,10 +1138,10 @@ constexpr uint32_t kPairThreads = kTileThreads;
 static_assert(kEntries == kTileThreads, "a table's workgroup loads its tile");
 
 template <class Id>
-__global__ __launch_bounds__(kPairThreads) void ss_align_pairs_kernel(const Id *__restrict__ ref_id, Windows win,
+__global__ __launch_bounds__(kPairThreads) void ss_align_pairs_kernel(const Id *__restrict__ ref_id, Windows first, Windows win, uint32_t k_win,
                                                             const uint32_t *__restrict__ masks, uint32_t W,
                                                             uint32_t n_steps, const uint32_t *__restrict__ rows,
-                                                            const uint16_t *__restrict__ upto,
+                                                            const uint16_t *__restrict__ upto, uint32_t upto_stride,
                                                             const int32_t *__restrict__ entry,
                                                             const int32_t *__restrict__ group_entry,
                                                             int32_t *__restrict__ ref_to_cur, const uint32_t *strayed, const uint32_t *n_keys,
@@ -1113,14 +1149,15 @@ __global__ __launch_bounds__(kPairThreads) void ss_align_pairs_kernel(const Id *
   __shared__ Tile tile;
   const uint32_t k = blockIdx.x, k0 = k / kGroupBlocks * kGroupBlocks;
   const uint32_t keys = *n_keys;
-  if (k == 0 && threadIdx.x == 0) *n_keys_out = keys;        // as a kernel that the host waits for has to say it
-  if ((strayed && *strayed) || (sizeof(Id) == 2 && keys >= kLdsKeys)) {      // the chain has ended early
+  if (blockIdx.x == 0 && threadIdx.x == 0) *n_keys_out = keys;        // as a kernel that the host waits for has to say it
+  if (strayed && *strayed) return;                           // the chain has ended early, and has told the host
+  if (sizeof(Id) == 2 && keys >= kLdsKeys) {
     ss_tell_host(done);
     return;
   }
   int j = group_entry[k / kGroupBlocks];
   if (j >= 0) {                                              // known: the group's table is
-    if (k > k0) j -= (int)upto[(size_t)(k - 1) * win.size + (uint32_t)j - win.start(k0)];
+    if (k > k0) j -= (int)upto[(size_t)(k - 1) * upto_stride + (uint32_t)j - (k < k_win ? first.start(k0) : win.start(k0))];
   } else {
     j = entry[k];
   }
@@ -1146,7 +1183,7 @@ size_t lds_need(uint32_t n_keys) { return (size_t)(n_keys + 1) * kStripWords * 4
 struct Layout {
   size_t h_ref, h_cur, h_flag, h_n_keys, h_part, h_out, h_end;
   size_t ref, cur, ref_id, cur_id, n_keys, rep, id, slot, carry, gave_up, rows, table, entry, upto, groups, group_entry, masks, end;
-  uint32_t n, m, W, strips, n_steps, n_blocks, walk_blocks, walk_groups, slots, bits;
+  uint32_t n, m, W, strips, n_steps, n_blocks, walk_blocks, walk_groups, window, upto_stride, slots, bits;
   bool one_wg, short_rows;
 
   Layout(uint32_t n_, uint32_t m_) : n(n_), m(m_) {
@@ -1161,6 +1198,9 @@ struct Layout {
     // the kernel writes the rows to pinned host memory and the host walks them; else they stay in device memory and
     // are walked there
     short_rows = row_bytes <= (m > 4 * (uint64_t)n ? kHostRowBytesSteep : kHostRowBytes);
+    window = std::max(n, m) - std::min(n, m) <= kNearlyEqual ? kNarrowWindow : kWindow;            // that the walk begins with
+    upto_stride = std::max(window, kWindow);               // the same for a second walk, of whose blocks it leaves the others'
+    const size_t entries = upto_stride;
     bits = 13;
     while ((1u << bits) < 2 * m) ++bits;
     slots = 1u << bits;
@@ -1168,7 +1208,7 @@ struct Layout {
     auto take = [&](size_t bytes) { size_t at = o; o += ss_align_up(bytes, 256); return at; };
     h_ref = take((size_t)n * sizeof(ss_op_t));
     h_cur = take((size_t)m * sizeof(ss_op_t));
-    h_flag = take(12);                                     // the same; the number of keys
+    h_flag = take(16);                                     // the same; the number of keys; columns left where the walk strays
     h_n_keys = h_flag + 8;
     h_part = take(kFetchWgs * sizeof(ss_cosine_part));
     h_out = take(short_rows ? row_bytes : (size_t)n * 4);
@@ -1183,10 +1223,10 @@ struct Layout {
     id = take(one_wg ? 0 : (size_t)slots * 4);
     slot = take(one_wg ? 0 : (size_t)m * 4);
     rows = take(short_rows ? 0 : row_bytes);
-    table = take(short_rows ? 0 : (size_t)walk_blocks * kWindow * 2);
+    table = take(short_rows ? 0 : walk_blocks * entries * 2);
     entry = take(short_rows ? 0 : (size_t)walk_blocks * 4);
-    upto = take(short_rows ? 0 : (size_t)walk_blocks * kWindow * 2);
-    groups = take(short_rows ? 0 : (size_t)walk_groups * kWindow * 2);
+    upto = take(short_rows ? 0 : walk_blocks * entries * 2);
+    groups = take(short_rows ? 0 : walk_groups * entries * 2);
     group_entry = take(short_rows ? 0 : (size_t)walk_groups * 4);
     carry = take((size_t)(strips - 1) * (n_blocks + kCarryPad) * 8);
     gave_up = take(8);                                     // by a strip; by the walk (strayed)
@@ -1202,27 +1242,29 @@ static_assert((uint64_t)steps_of(kAlignLenLimit) * kStripWords * 4 * strips_of(k
 static_assert((uint64_t)steps_of(kAlignLenLimit) * kStripWords * 4 < 1ull << 31, "a strip's rows");
 static_assert(((uint64_t)kAlignLenLimit + 1) * (kAlignLenLimit / 32) * 4 <= 1ull << 30, "masks");
 
-// The walk over rows in device memory.
+// The walk over rows in device memory, with windows of that size, from block k on with j columns left.
 template <class Id>
-int launch_walk(ss_ctx *ctx, const Layout &y, uint8_t *d, uint8_t *hd, bool narrow, ss_done &done) {
+int launch_walk(ss_ctx *ctx, const Layout &y, uint8_t *d, uint8_t *hd, uint32_t size, uint32_t k, uint32_t j, ss_done &done) {
   hipStream_t s = ctx->s_aux;
   const Id *ref_id = (const Id *)(d + y.ref_id);
   const uint32_t *masks = (const uint32_t *)(d + y.masks), *rows = (const uint32_t *)(d + y.rows);
   uint16_t *table = (uint16_t *)(d + y.table), *upto = (uint16_t *)(d + y.upto), *groups = (uint16_t *)(d + y.groups);
   int32_t *entry = (int32_t *)(d + y.entry), *group_entry = (int32_t *)(d + y.group_entry), *pair = (int32_t *)(hd + y.h_out);
   const uint32_t *n_keys = (const uint32_t *)(d + y.n_keys);
-  const Windows win(y.n, y.m, narrow ? kNarrowWindow : kWindow);
-  const Strayed strayed = narrow ? Strayed{(uint32_t *)(d + y.gave_up) + 1, (uint32_t *)(hd + y.h_flag) + 1} : Strayed{nullptr, nullptr};
+  uint32_t *const h_flag = (uint32_t *)(hd + y.h_flag);
+  const Windows win(y.n, y.m, size, y.n - k * kWalkRows, j), first(y.n, y.m, y.window, y.n, y.m);
+  const uint32_t g = k / kGroupBlocks, k0 = g * kGroupBlocks;              // the tables' first group and block
   done = ss_next_done(ctx);
   ss_told_by(done, y.walk_blocks);
-  hipLaunchKernelGGL(ss_align_tab_kernel<Id>, dim3(y.walk_blocks, win.size / kEntries), dim3(kEntries), 0, s, ref_id, win, masks,
-                     y.W, y.n_steps, rows, table, n_keys);
-  hipLaunchKernelGGL(ss_align_compose_kernel<Id>, dim3(y.walk_groups, win.size / 256), dim3(256), 0, s, table, win, y.walk_blocks, upto,
-                     groups, n_keys);
+  const Strayed strayed = size == kNarrowWindow && size <= y.m ? Strayed{(uint32_t *)(d + y.gave_up) + 1, h_flag + 1, h_flag + 3, done} : Strayed{};
+  hipLaunchKernelGGL(ss_align_tab_kernel<Id>, dim3(y.walk_blocks - k0, size / kEntries), dim3(kEntries), 0, s, ref_id, win, masks,
+                     y.W, y.n_steps, rows, table, n_keys, k0);
+  hipLaunchKernelGGL(ss_align_compose_kernel<Id>, dim3(y.walk_groups - g, size / 256), dim3(256), 0, s, table, win, y.walk_blocks, upto,
+                     y.upto_stride, groups, n_keys, g);
   hipLaunchKernelGGL(ss_align_chain_kernel<Id>, dim3(1), dim3(kChainThreads), 0, s, ref_id, win, masks, y.W, y.n_steps, rows, table,
-                     groups, entry, group_entry, pair, strayed, n_keys);
-  hipLaunchKernelGGL(ss_align_pairs_kernel<Id>, dim3(y.walk_blocks), dim3(kPairThreads), 0, s, ref_id, win, masks, y.W, y.n_steps,
-                     rows, upto, entry, group_entry, pair, strayed.device, n_keys, (uint32_t *)(hd + y.h_n_keys), done);
+                     upto, y.upto_stride, groups, entry, group_entry, pair, strayed, n_keys, k, j);
+  hipLaunchKernelGGL(ss_align_pairs_kernel<Id>, dim3(y.walk_blocks), dim3(kPairThreads), 0, s, ref_id, first, win, k, masks, y.W,
+                     y.n_steps, rows, upto, y.upto_stride, entry, group_entry, pair, strayed.device, n_keys, (uint32_t *)(hd + y.h_n_keys), done);
   SS_HIP(hipGetLastError());
   return SS_OK;
 }
@@ -1254,7 +1296,7 @@ int launch_rows(ss_ctx *ctx, const Layout &y, uint8_t *d, uint8_t *hd, uint32_t 
     hipLaunchKernelGGL(ss_align_rows_kernel<Id>, dim3(per_launch), dim3(kRowsThreads), kLds ? lds_need(keys) : 0, s, ref_id,
                        cur_id, y.m, args, n_keys);
   SS_HIP(hipGetLastError());
-  return y.short_rows ? SS_OK : launch_walk<Id>(ctx, y, d, hd, std::max(y.n, y.m) - std::min(y.n, y.m) <= kNearlyEqual, done);
+  return y.short_rows ? SS_OK : launch_walk<Id>(ctx, y, d, hd, y.window, 0, y.m, done);
 }
 
 }  // namespace
@@ -1367,8 +1409,9 @@ int ss_align_core(ss_ctx *ctx, const ss_op_t *ref, uint32_t n, const ss_op_t *cu
     h_flag[1] = 0;                      // what the walk made of these rows
     if ((rc = rows(true)) != SS_OK) return rc;
   }
-  if (h_flag[1]) {                      // the path has left the narrow windows
-    rc = keys <= few ? launch_walk<uint16_t>(ctx, y, d, hd, false, done) : launch_walk<uint32_t>(ctx, y, d, hd, false, done);
+  if (h_flag[1]) {                      // the path has left the narrow windows: on from there with wide ones
+    const uint32_t k = h_flag[1] - 1, j = h_flag[3];
+    rc = keys <= few ? launch_walk<uint16_t>(ctx, y, d, hd, kWindow, k, j, done) : launch_walk<uint32_t>(ctx, y, d, hd, kWindow, k, j, done);
     if (rc != SS_OK || (rc = ss_wait_done(ctx, done)) != SS_OK) return rc;
   }
   if (n_keys_out) *n_keys_out = keys;

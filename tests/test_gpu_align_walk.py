@@ -99,3 +99,21 @@ def test_far_to_the_left_in_one_row(P, ctx, keys, gap):            # noqa: F811
     for at in (len(ref), 5003, 4992, 64, 0):
         same(P, ctx, ref, np.concatenate([ref[:at], foreign, ref[at:]]))
     same(P, ctx, ref, np.concatenate([foreign, ref[200:300], foreign, ref[4000:4001], foreign]))
+
+
+@pytest.mark.parametrize("keys", [40, 900])
+@pytest.mark.parametrize("at", [2, 7, 8, 9, 15, 16, 17, 60, 135])
+def test_walks_that_go_on_where_the_path_has_left_the_windows(P, ctx, keys, at):         # noqa: F811
+    """the path leaves the narrow windows about block `at` from the end: within a group of eight blocks and at its first and last one,
+    in the last blocks of the walk, to either side; it stays beside the diagonal, comes back or leaves the second windows too"""
+    rng = np.random.default_rng([keys, at])
+    n = 9100
+    ref = rng.integers(0, keys, n)
+    x = max(0, n - 64 * at)
+    foreign = keys + 5 + rng.integers(0, 4, 3000)
+    for shift in (650, 1700):
+        same(P, ctx, ref, np.concatenate([foreign[:shift], ref[:max(0, x - shift)], ref[x:]]))
+        same(P, ctx, ref, np.concatenate([ref[shift:x], foreign[:min(shift, x)], ref[x:]]))
+        same(P, ctx, ref, np.concatenate([ref[:x // 2], foreign[:shift], ref[x // 2:max(x // 2, x - shift)], ref[x:]]))
+    y = max(0, x - 2500)
+    same(P, ctx, ref, np.concatenate([ref[:y // 2], foreign[:1600], ref[y // 2:max(y // 2, y - 800)], ref[y:max(y, x - 800)], ref[x:]]))
