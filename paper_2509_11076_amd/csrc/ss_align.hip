@@ -37,9 +37,9 @@ constexpr uint32_t kIdPad = 64 * kSkew;                // entries before the fir
 // Rows up to this many bytes go straight to host memory and are walked there: beside the kernel's pace they cost the
 // link nothing up to about 13 GB/s, and the walk on the GPU takes four more launches.  us a call, walked on the host and on the
 // GPU: 2,694 x 2,704 operators (1.4 MiB) 104 and 113, 3,100 x 3,100 (1.6) 105 and 111, 3,300 x 3,300 (1.7) 119 and 113, 3,882 x 3,880
-// 148 and 132, 5,192 x 5,196 201 and 154, 16,000 x 1,000 337 and 302.  Where cur is more than four times as long, a block's path
-// leaves the columns that are tabulated for it: 2,000 x 8,000 (2.6) 137 and 124, but 1,800 x 9,000 136 and 244, 500 x 30,000 184
-// and 386.
+// 148 and 132, 5,192 x 5,196 201 and 154, 16,000 x 1,000 337 and 302; paths beside the diagonal: kAllTables.  Where cur is more than
+// twice as long, a block's path leaves the tile of columns that is looked at for it: 2,200 x 6,000 (2.3), all of ref at the front of
+// cur, 124 and 186, spread over cur 123 and 116; 1,800 x 9,000 136 and 244, 500 x 30,000 184 and 386.
 constexpr size_t kHostRowBytes = 1700u << 10, kHostRowBytesSteep = 4u << 20;
 constexpr uint32_t kCarryPad = 8;                      // carry words beyond a strip's last (the first of them is looked at)
 
@@ -712,14 +712,20 @@ __global__ __launch_bounds__(kWgThreads) void ss_align_short_kernel(KeyArgs k, R
 // per group; 17 where each group's went through the scalar unit, 90 block by block), 14 us for the pairs; single steps in one
 // wavefront took 97 ns a row (3.1 ms), the rows over the host link (130 MB) 2.3 ms and a walk there.
 constexpr uint32_t kWalkRows = 64;
-// Entry columns tabulated per block of rows (windows): kWindow; or, where the lengths differ by at most kNearlyEqual, kNarrowWindow
-// first, since a path of operators that come and go all along the sequences strays from the diagonal by some hundred columns (32,312
-// rows: tables 48 us, half as many 28).  If it leaves them after all, the walk goes on from there with kWindow columns around the
-// diagonal of what is left, which finds a path that has come to lie beside the first one.
+// Entry columns tabulated per block of rows (windows).  Where that takes no more than kAllTables workgroups, all columns: no path leaves
+// them.  Otherwise kWindow; or, where the lengths differ by at most kNearlyEqual, kNarrowWindow first, since a path of operators that
+// come and go all along the sequences strays from the diagonal by some hundred columns (32,312 rows: tables 48 us, half as many 28).
+// If it leaves them after all, the walk goes on from there with kWindow columns around the diagonal of what is left, which finds a
+// path that has come to lie beside the first one.
 // us a call, sequences of 9,000 with 700 foreign operators in a quarter of one and as many missing in the last of it: 247, by a second
 // walk of all blocks 272, with kWindow alone 254; with 1,500 foreign ones 266, 392 and 351; without any 208, 207 and 243 (the last
 // with the tables' older kernel).
-constexpr uint32_t kWindow = 2048, kNarrowWindow = 1024, kNearlyEqual = 512;
+// All columns, or few of them at first (kAllTablesNear): 3,300 x 3,300 111 us where the path stays near the diagonal (few at first
+// 107), 126 where it lies 700 or 1,500 beside it (150 and 163; walked on the host 125); 4,400 x 4,400 137 and 129, beside it 145 to
+// 160 and 166 to 175 (host 163); 5,100 x 5,100 150 and 138, beside it 158 to 180 and 160 to 199 (host 190).  Where lengths differ
+// by more the path is seldom near the diagonal: 8,000 operators and the first 3,000 of them 192 us, with kWindow 709, on the host 235.
+constexpr uint32_t kWindow = 2048, kNarrowWindow = 1024, kNearlyEqual = 512, kMostColumns = 8192;
+constexpr uint32_t kAllTables = 2600, kAllTablesNear = 1200;
 constexpr uint32_t kEntries = 256;                     // of these, per workgroup
 constexpr uint32_t kMargin = 256;                      // columns a tile reaches to the left of its first entry
 constexpr uint32_t kTileWords = (kEntries + kMargin) / 32;
@@ -1197,8 +1203,11 @@ struct Layout {
     one_wg = n + m <= kWgOps;
     // the kernel writes the rows to pinned host memory and the host walks them; else they stay in device memory and
     // are walked there
-    short_rows = row_bytes <= (m > 4 * (uint64_t)n ? kHostRowBytesSteep : kHostRowBytes);
-    window = std::max(n, m) - std::min(n, m) <= kNearlyEqual ? kNarrowWindow : kWindow;            // that the walk begins with
+    short_rows = row_bytes <= (m > 2 * (uint64_t)n ? kHostRowBytesSteep : kHostRowBytes);
+    // The windows that the walk begins with (kWindow)
+    const uint32_t all = (uint32_t)ss_align_up(m + 1, kEntries);
+    const bool near = std::max(n, m) - std::min(n, m) <= kNearlyEqual;
+    window = all <= kWindow || (all <= kMostColumns && walk_blocks * (all / kEntries) <= (near ? kAllTablesNear : kAllTables)) ? all : near ? kNarrowWindow : kWindow;
     upto_stride = std::max(window, kWindow);               // the same for a second walk, of whose blocks it leaves the others'
     const size_t entries = upto_stride;
     bits = 13;

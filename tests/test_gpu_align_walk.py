@@ -117,3 +117,19 @@ def test_walks_that_go_on_where_the_path_has_left_the_windows(P, ctx, keys, at):
         same(P, ctx, ref, np.concatenate([ref[:x // 2], foreign[:shift], ref[x // 2:max(x // 2, x - shift)], ref[x:]]))
     y = max(0, x - 2500)
     same(P, ctx, ref, np.concatenate([ref[:y // 2], foreign[:1600], ref[y // 2:max(y // 2, y - 800)], ref[y:max(y, x - 800)], ref[x:]]))
+
+
+@pytest.mark.parametrize("n,m", [(3300, 3300), (4000, 4500), (4288, 4288), (4289, 4350), (4800, 4300), (8000, 3000), (2200, 4400), (2200, 4401),
+                                 (5100, 8191), (5100, 8192), (12000, 2047), (12000, 2048), (20000, 900)])
+def test_tables_of_all_columns(P, ctx, n, m):                      # noqa: F811
+    """paths near the diagonal, far beside it and along the edges, where all columns are tabulated and where they just aren't"""
+    rng = np.random.default_rng([n, m, 8])
+    base = rng.integers(0, 35, max(n, m))
+    ref, cur = base[:n], base[:m]
+    same(P, ctx, ref, cur)
+    same(P, ctx, base[-n:], base[-m:])
+    same(P, ctx, ref, perturbed(rng, np.resize(ref, m), 35)[:m])
+    k = min(n, m) // 2
+    same(P, ctx, ref, np.concatenate([np.full(m - k, 70), ref[:k]]))
+    same(P, ctx, ref, np.concatenate([ref[-k:], 70 + rng.integers(0, 3, m - k)]))
+    same(P, ctx, ref, 100 + rng.integers(0, 30, m))
