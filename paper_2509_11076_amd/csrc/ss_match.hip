@@ -440,10 +440,10 @@ __global__ __launch_bounds__(256) void ss_anchor_short_kernel(AnchorArgs g) {
 struct ShortArgs {
   const ss_op_t *ref, *cur;            // pinned
   const ss_anchor_t *anchors;
-  uint32_t n, m, k;
+  uint32_t n, m, k, most_keys;         // short_keys
   int32_t *new_idx;                    // pinned
   uint8_t *level;
-  uint32_t *lost, *too_many;           // pinned: anchors without a place; keys, if their maps don't fit (nothing else is written)
+  uint32_t *lost, *too_many;           // pinned: anchors without a place; keys, if there are more than that (nothing else is written)
   ss_cosine_part *part;
   ss_done done;
 };
@@ -482,7 +482,21 @@ __device__ __forceinline__ uint2 counts_before(uint4 b) {
   return uint2{first | (first + x) << 16, (first + y) | (first + z) << 16};
 }
 
-static __device__ __forceinline__ uint32_t up_to_four(uint32_t x) { return (x + 3) / 4 * 4; }
+static __host__ __device__ __forceinline__ uint32_t up_to_four(uint32_t x) { return (x + 3) / 4 * 4; }
+
+// Words of a key's maps at a level: an odd number of 16 bytes, so that the maps' starts lie in different banks.
+static __host__ __device__ __forceinline__ uint32_t map_stride(uint32_t n, uint32_t m) {
+  return (up_to_four((n + 31) / 32) + up_to_four((m + 31) / 32)) | 4;
+}
+
+// How many keys one workgroup matches: as many as the maps of three levels, with 16 bits more a word, fit LDS for, and no more than are
+// as fast as three launches.  Each key is compared with all and its maps are put together, which few anchors don't make up for
+// (three launches | one; 100 anchors of 200 operators, 115 keys 21.0 | 20.9 us, 145 21.4 | 22.4, 200 21.0 | 25.6; 1,000 anchors, 160 keys
+// 27.8 | 25.0, 200 27.7 | 27.6, of 300 operators 26.3 | 27.9; 1,500 anchors, 200 keys 33.6 | 29.7).
+static uint32_t short_keys(uint32_t n, uint32_t m, uint32_t k) {
+  const uint32_t fit = 2 * kShortMap / (9 * map_stride(n, m)), fast = k < 768 ? 120 : k < 1280 ? 180 : kShortKeys;
+  return fit < fast ? fit : fast;
+}
 
 // the bit of `word` with `need` set bits below it
 __device__ __forceinline__ uint32_t select_bit(uint32_t word, uint32_t need) {
@@ -561,9 +575,9 @@ __global__ __launch_bounds__(kShortThreads) void ss_match_short_kernel(ShortArgs
   }
   __syncthreads();
   const uint32_t keys = sh.n_keys, ref_words = (a.n + 31) / 32, cur_words = (a.m + 31) / 32, cur_at = up_to_four(ref_words),
-                 stride = (cur_at + up_to_four(cur_words)) | 4;              // an odd number of 16 bytes: the maps' starts lie in different banks
+                 stride = map_stride(a.n, a.m);
   const uint32_t level_words = keys * stride;
-  if (keys > kShortKeys || 3 * level_words + (3 * level_words + 1) / 2 > kShortMap) {
+  if (keys > a.most_keys) {
     if (tid == 0) *a.too_many = keys;
     ss_tell_host(a.done);
     return;
@@ -1149,7 +1163,7 @@ extern "C" int ss_match_sequence(ss_ctx *ctx, const ss_op_t *ref, uint32_t n, co
         ss_done told = ss_next_done(ctx);
         told.wgs = 1;
         const ShortArgs a = {(const ss_op_t *)(hd + ho_ref), (const ss_op_t *)(hd + ho_cur), (const ss_anchor_t *)(hd + ho_anc), n, m, k,
-                             (int32_t *)(hd + ho_idx), hd + ho_level, (uint32_t *)(hd + ho_lost), (uint32_t *)(hd + ho_lost) + 1, dpart, told};
+                             short_keys(n, m, k), (int32_t *)(hd + ho_idx), hd + ho_level, (uint32_t *)(hd + ho_lost), (uint32_t *)(hd + ho_lost) + 1, dpart, told};
         hipLaunchKernelGGL(ss_match_short_kernel, dim3(1), dim3(kShortThreads), sizeof(ShortLds), s, a);
         SS_HIP(hipGetLastError());
         if ((rc = ss_wait_done(ctx, told)) != SS_OK) return rc;

@@ -71,3 +71,24 @@ def test_tokens_out_of_range_whose_squares_wrap_to_zero(P, ctx, n, wrong):      
     with pytest.raises(P.SsError) as e:
         P.ss_match_sequence(ctx, ref, cur, anc)
     assert e.value.code == P.SS_E_INVAL
+
+
+@pytest.mark.parametrize("n,k,limit", [(160, 767, 120), (300, 4, 120), (160, 768, 180), (300, 1279, 180), (160, 1280, 256), (300, 2048, 227),
+                                       (1156, 480, 75), (1156, 2048, 75), (2048, 100, 48)])
+def test_keys_about_what_one_workgroup_takes(P, n, k, limit):              # noqa: F811
+    """as many keys as fit LDS and are as fast there, one less and one more, on a context of their own each"""
+    rng = np.random.default_rng([n, k])
+    anc = anchors(rng, n, k)
+    for keys in (limit - 1, limit, limit + 1):
+        key = np.concatenate([np.arange(keys), rng.integers(0, keys, 2 * n - keys)])
+        rng.shuffle(key)
+        ops = np.zeros(2 * n, dtype=W.OP_DT)
+        ops["op_token"], ops["stack_hash"], ops["sig"], ops["n_out"] = 1 + key % 7, key // 14, 0x101 + (key // 7 % 2 << 16), 2
+        c = P.ss_create(P.ss_config_default())
+        try:
+            idx, lvl = landings(ops[:n], ops[n:], anc)
+            for _ in range(3):
+                r = P.ss_match_sequence(c, ops[:n], ops[n:], anc)
+                assert np.array_equal(r["new_idx"], idx) and np.array_equal(r["level"], lvl)
+        finally:
+            P.ss_destroy(c)
