@@ -91,11 +91,6 @@ struct KeyArgs {
   ss_cosine_part *part;        // pinned, if wanted: of each workgroup that reads the operators
 };
 
-__device__ __forceinline__ uint32_t key_hash(uint32_t token, uint32_t stack, uint32_t sig, uint32_t shift) {
-  const u64 x = (((u64)token << 32) | stack) * 0x9E3779B97F4A7C15ull ^ (u64)sig * 0xC2B2AE3D27D4EB4Full;
-  return (uint32_t)((x ^ (x >> 29)) * 0x9E3779B97F4A7C15ull >> shift);
-}
-
 __device__ __forceinline__ void put_id(void *ids, size_t at, uint32_t key, bool few) {
   if (few) static_cast<uint16_t *>(ids)[at] = (uint16_t)(key << 8);
   else static_cast<uint32_t *>(ids)[at] = key;
@@ -143,7 +138,7 @@ __device__ __forceinline__ uint32_t keys_of_wg(const KeyArgs &a, uint32_t *lds, 
   // at most m <= kWgSlots / 2 keys: a free or matching slot is met
   auto find = [&](uint32_t u, bool insert) -> uint32_t {
     const uint32_t i = u * kWgThreads + tid;
-    uint32_t h = key_hash(o[u].op_token, o[u].stack_hash, o[u].sig, kShift);
+    uint32_t h = ss_key_hash(o[u].op_token, o[u].stack_hash, o[u].sig, kShift);
     for (uint32_t probe = 0; probe < kWgSlots; ++probe) {
       uint32_t seen = *(volatile uint32_t *)(rep + h);
       if (!seen) {
@@ -240,7 +235,7 @@ __global__ __launch_bounds__(256) void ss_align_insert_kernel(KeyArgs a) {
   ops[threadIdx.x] = o;
   for (uint32_t i = threadIdx.x; i < kSlots; i += 256) first[i] = 0;
   __syncthreads();
-  uint32_t l = key_hash(o.op_token, o.stack_hash, o.sig, kShift);
+  uint32_t l = ss_key_hash(o.op_token, o.stack_hash, o.sig, kShift);
   bool goes = false;
   for (uint32_t probe = 0; live && probe < kSlots; ++probe) {  // at most 256 keys in 512 slots
     uint32_t seen = *(volatile uint32_t *)(first + l);
@@ -252,7 +247,7 @@ __global__ __launch_bounds__(256) void ss_align_insert_kernel(KeyArgs a) {
     l = (l + 1) % kSlots;
   }
   if (goes) {
-    uint32_t h = key_hash(o.op_token, o.stack_hash, o.sig, a.shift);
+    uint32_t h = ss_key_hash(o.op_token, o.stack_hash, o.sig, a.shift);
     for (uint32_t probe = 0; probe <= a.mask; ++probe) {       // at most m keys in at least 2m slots
       uint32_t seen = __hip_atomic_load(a.rep + h, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
       if (!seen) {
@@ -284,7 +279,7 @@ __device__ __forceinline__ void operator_ids(const KeyArgs &a) {
   uint32_t key = keys;
   if (i >= kIdPad && i < kIdPad + a.n) {
     const ss_op_t o = a.ref[i - kIdPad];
-    uint32_t h = key_hash(o.op_token, o.stack_hash, o.sig, a.shift);
+    uint32_t h = ss_key_hash(o.op_token, o.stack_hash, o.sig, a.shift);
     for (uint32_t probe = 0; probe <= a.mask; ++probe) {
       const uint32_t seen = a.rep[h];
       if (!seen) break;

@@ -240,18 +240,29 @@ struct ss_cosine_part { uint64_t dot, na, nb, bad; };
 constexpr uint32_t SS_TOKEN_LIMIT = 1u << 18;
 
 #ifdef __HIPCC__
+// `64 - shift` bits of hash for an operator's key
+static __host__ __device__ __forceinline__ uint32_t ss_key_hash(uint32_t token, uint32_t stack, uint32_t sig, uint32_t shift) {
+  const uint64_t x = (((uint64_t)token << 32) | stack) * 0x9E3779B97F4A7C15ull ^ (uint64_t)sig * 0xC2B2AE3D27D4EB4Full;
+  return (uint32_t)((x ^ (x >> 29)) * 0x9E3779B97F4A7C15ull >> shift);
+}
+
 // v of another lane by one data-parallel move, `none` where there is no such lane
 template <int kCtrl, int kRows>
 __device__ __forceinline__ uint32_t dpp_u32(uint32_t v, uint32_t none) {
   return (uint32_t)__builtin_amdgcn_update_dpp((int)none, (int)v, kCtrl, kRows, 0xF, false);
 }
 
-// inclusive prefix sum over the 64 lanes: within rows of 16, then the rows' last lanes handed on
-__device__ __forceinline__ uint32_t wave_scan_u32(uint32_t v) {
+// inclusive prefix sum over the lanes of a row of 16
+__device__ __forceinline__ uint32_t row_scan_u32(uint32_t v) {
   v += dpp_u32<0x111, 0xF>(v, 0);
   v += dpp_u32<0x112, 0xF>(v, 0);
   v += dpp_u32<0x114, 0xF>(v, 0);
-  v += dpp_u32<0x118, 0xF>(v, 0);
+  return v + dpp_u32<0x118, 0xF>(v, 0);
+}
+
+// over the 64 lanes: within rows, then the rows' last lanes handed on
+__device__ __forceinline__ uint32_t wave_scan_u32(uint32_t v) {
+  v = row_scan_u32(v);
   v += dpp_u32<0x142, 0xA>(v, 0);
   v += dpp_u32<0x143, 0xC>(v, 0);
   return v;
