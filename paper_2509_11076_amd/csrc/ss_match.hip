@@ -22,7 +22,9 @@ constexpr uint32_t kTokenLimit = SS_TOKEN_LIMIT;
 constexpr uint32_t kLenLimit = 1u << 23;
 
 constexpr uint32_t kMaxParts = 1024;
-constexpr uint32_t kTryAgain = 64;     // calls until short sequences are given to one workgroup again after one with too many keys (a try costs 9 us)
+// Calls until short sequences are given to one workgroup again after one with too many keys.  A try for nothing costs 9 us, a context's
+// first 14; so where none has been worth it yet, or the last one wasn't, some operators are looked at first (more_keys, 1 us).
+constexpr uint32_t kTryAgain = 64;
 
 // Everything that has to be done before anchors can be looked for, in one pass: the sequences (and anchors) are copied
 // from pinned host memory to device memory if dref / dcur / danc are given, the sums of the cosine taken on the way
@@ -501,6 +503,26 @@ __device__ __forceinline__ uint32_t select_bit(uint32_t word, uint32_t need) {
     else word &= (1u << half) - 1;
   }
   return at;
+}
+
+// Whether operators spread over a sequence have more than that many keys.
+static bool more_keys(const ss_op_t *ops, uint32_t n, uint32_t most) {
+  constexpr uint32_t kLooks = 256, kSlots = 4 * kLooks;
+  uint16_t slots[kSlots] = {};                               // 1 + the look that a key was met at
+  uint32_t keys = 0;
+  for (uint32_t x = 0; x < std::min(n, kLooks); ++x) {
+    const ss_op_t &o = ops[(uint64_t)x * n / std::min(n, kLooks)];
+    uint32_t h = ss_key_hash(o.op_token, o.stack_hash, o.sig, 64 - 10);
+    static_assert(kSlots == 1u << 10, "hash bits");
+    for (; slots[h]; h = (h + 1) % kSlots) {
+      const ss_op_t &r = ops[(uint64_t)(slots[h] - 1) * n / std::min(n, kLooks)];
+      if (r.op_token == o.op_token && r.stack_hash == o.stack_hash && r.sig == o.sig) break;
+    }
+    if (slots[h]) continue;
+    slots[h] = (uint16_t)(x + 1);
+    if (++keys > most) return true;
+  }
+  return false;
 }
 
 __global__ __launch_bounds__(kShortThreads) void ss_match_short_kernel(ShortArgs a) {
@@ -1144,8 +1166,11 @@ extern "C" int ss_match_sequence(ss_ctx *ctx, const ss_op_t *ref, uint32_t n, co
     // calls.  Three launches | one: 4 anchors of 60 operators 20.2 | 15.8 us, of 2,048 21.8 | 21.1; 1,024 of 60 27.8 | 19.0, of 2,048
     // 26.5 | 25.6; 2,048 of 2,048 33.1 | 30.8.  From there on three passes over the chip are the faster.
     if (mapped && search && !hist && n && m && n <= kShortOps && m <= kShortOps && k <= kShortAnchors) {
+      const uint32_t most_keys = short_keys(n, m, k);
       if (ctx->match_many_keys) {
         ctx->match_many_keys--;
+      } else if (!ctx->match_few_keys && more_keys(ref, n, most_keys)) {
+        ctx->match_many_keys = kTryAgain;
       } else {
         std::memcpy(h + ho_ref, ref, (size_t)n * op_bytes);
         std::memcpy(h + ho_cur, cur, (size_t)m * op_bytes);
@@ -1155,10 +1180,11 @@ extern "C" int ss_match_sequence(ss_ctx *ctx, const ss_op_t *ref, uint32_t n, co
         ss_done told = ss_next_done(ctx);
         told.wgs = 1;
         const ShortArgs a = {(const ss_op_t *)(hd + ho_ref), (const ss_op_t *)(hd + ho_cur), (const ss_anchor_t *)(hd + ho_anc), n, m, k,
-                             short_keys(n, m, k), (int32_t *)(hd + ho_idx), hd + ho_level, (uint32_t *)(hd + ho_lost), (uint32_t *)(hd + ho_lost) + 1, dpart, told};
+                             most_keys, (int32_t *)(hd + ho_idx), hd + ho_level, (uint32_t *)(hd + ho_lost), (uint32_t *)(hd + ho_lost) + 1, dpart, told};
         hipLaunchKernelGGL(ss_match_short_kernel, dim3(1), dim3(kShortThreads), sizeof(ShortLds), s, a);
         SS_HIP(hipGetLastError());
         if ((rc = ss_wait_done(ctx, told)) != SS_OK) return rc;
+        ctx->match_few_keys = !said[1];
         if (!said[1]) {
           const ss_cosine_part &sums = *(const ss_cosine_part *)(h + ho_part);
           if (sums.bad) return SS_E_INVAL;                   // a token beyond 2^18

@@ -92,3 +92,29 @@ def test_keys_about_what_one_workgroup_takes(P, n, k, limit):              # noq
                 assert np.array_equal(r["new_idx"], idx) and np.array_equal(r["level"], lvl)
         finally:
             P.ss_destroy(c)
+
+
+def test_contexts_that_begin_with_many_keys(P):                            # noqa: F811
+    """some operators are looked at before one workgroup is tried: few keys in those and many in all, many in both, few in both, in any
+    order on one context, past the number of calls that aren't tried"""
+    rng = np.random.default_rng(41)
+    n = 2000
+
+    def ops(key):
+        o = np.zeros(len(key), dtype=W.OP_DT)
+        o["op_token"], o["stack_hash"], o["sig"], o["n_out"] = 1 + key % 50, key // 100, 0x101 + (key // 50 % 2 << 16), 1
+        return o
+    anc = anchors(rng, n, 300)
+    hidden = np.zeros(n, dtype=np.int64)
+    hidden[1::8] = 1 + np.arange(len(hidden[1::8]))                # not among every eighth operator
+    forms = [hidden, rng.integers(0, 900, n), rng.integers(0, 30, n), np.arange(n)]
+    pairs = [(ops(f), ops(np.roll(f, 5))) for f in forms]
+    want = [landings(ref, cur, anc) for ref, cur in pairs]
+    for first in range(4):
+        c = P.ss_create(P.ss_config_default())
+        try:
+            for i in [first] + [x for x in (0, 2, 1, 2, 3, 0) for _ in range(1 if x != 1 else 70)]:
+                r = P.ss_match_sequence(c, *pairs[i], anc)
+                assert np.array_equal(r["new_idx"], want[i][0]) and np.array_equal(r["level"], want[i][1])
+        finally:
+            P.ss_destroy(c)
