@@ -335,7 +335,7 @@ struct RowsArgs {
   u64 *carry;
   uint32_t *rows;
   uint32_t *gave_up;         // device, cleared before the launch (several strips only): a strip has given up
-  uint32_t *gave_up_host;    // pinned: the same; two words on, the number of keys, as a kernel that the host waits for has to say it
+  uint32_t *gave_up_host;    // pinned: the same
   uint32_t W, n_steps, strips, strip0;       // strips of a row; the one of workgroup 0
   uint32_t wait_looks;       // looks at a carry word before a strip gives up
   ss_done done;              // where the host walks the rows
@@ -609,7 +609,6 @@ __global__ __launch_bounds__(kRowsThreads) void ss_align_rows_kernel(const Id *_
   const uint32_t words = min(many ? kInnerWords : kStripWords, a.W - w0);
   const bool stored = lane >= first && lane < first + words;
   const uint32_t n_mask_rows = *n_keys + 1, n_blocks = a.n_steps / kBlock;
-  if (blockIdx.x == 0 && tid == 0) a.gave_up_host[2] = n_mask_rows - 1;
   if (kLds && n_mask_rows > kLdsKeys) {                      // launched before the number was known, and the ids are wide
     ss_tell_host(a.done);
     return;
@@ -1146,13 +1145,11 @@ __global__ __launch_bounds__(kPairThreads) void ss_align_pairs_kernel(const Id *
                                                             const int32_t *__restrict__ entry,
                                                             const int32_t *__restrict__ group_entry,
                                                             int32_t *__restrict__ ref_to_cur, const uint32_t *strayed, const uint32_t *n_keys,
-                                                            uint32_t *n_keys_out, ss_done done) {
+                                                            ss_done done) {
   __shared__ Tile tile;
   const uint32_t k = blockIdx.x, k0 = k / kGroupBlocks * kGroupBlocks;
-  const uint32_t keys = *n_keys;
-  if (blockIdx.x == 0 && threadIdx.x == 0) *n_keys_out = keys;        // as a kernel that the host waits for has to say it
   if (strayed && *strayed) return;                           // the chain has ended early, and has told the host
-  if (sizeof(Id) == 2 && keys >= kLdsKeys) {
+  if (sizeof(Id) == 2 && *n_keys >= kLdsKeys) {
     ss_tell_host(done);
     return;
   }
@@ -1268,7 +1265,7 @@ int launch_walk(ss_ctx *ctx, const Layout &y, uint8_t *d, uint8_t *hd, uint32_t 
   hipLaunchKernelGGL(ss_align_chain_kernel<Id>, dim3(1), dim3(kChainThreads), 0, s, ref_id, win, masks, y.W, y.n_steps, rows, table,
                      upto, y.upto_stride, groups, entry, group_entry, pair, strayed, n_keys, k, j);
   hipLaunchKernelGGL(ss_align_pairs_kernel<Id>, dim3(y.walk_blocks), dim3(kPairThreads), 0, s, ref_id, first, win, k, masks, y.W,
-                     y.n_steps, rows, upto, y.upto_stride, entry, group_entry, pair, strayed.device, n_keys, (uint32_t *)(hd + y.h_n_keys), done);
+                     y.n_steps, rows, upto, y.upto_stride, entry, group_entry, pair, strayed.device, n_keys, done);
   SS_HIP(hipGetLastError());
   return SS_OK;
 }

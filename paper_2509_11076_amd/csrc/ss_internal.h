@@ -305,7 +305,10 @@ __device__ __forceinline__ void ss_put_part(ss_cosine_part *out, uint64_t dot, u
 // The last thing that every thread of each of the workgroups calls.  Results written to pinned memory may still be in the
 // L2 of the workgroup's die when its stores have completed: every workgroup releases its own to the system before it counts
 // (the last one's release writes back its own die's only; beside products on the compute stream the host then saw the word
-// before other dies' results).
+// before other dies' results).  What earlier kernels of the call wrote there needs nothing: where a kernel ends, before the next one of
+// the stream begins, every die writes back what it holds, or workgroups of the next one on other dies would not see it (the
+// cosine's sums, the number of keys, pairs of blocks that the aligner's chain has walked: none stale in the calls that are checked
+// beside such products).
 __device__ __forceinline__ void ss_tell_host(const ss_done &d) {
   if (!d.flag) return;
   asm volatile("s_waitcnt vmcnt(0)" ::: "memory");

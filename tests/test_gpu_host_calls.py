@@ -111,6 +111,36 @@ def test_the_word_comes_after_every_result_of_earlier_kernels(P, ctx, what, n, k
     in_turn(call, want)
 
 
+@pytest.mark.parametrize("n", [1500, 2500, 3000, 7000, 20000])
+def test_words_of_an_aligners_first_kernels(P, ctx, n):                              # noqa: F811
+    """the number of keys and, in aligned matching, the cosine's sums are pinned by the first kernels, of up to 80 workgroups, and the
+    host waits for the last one, of one to 313: inputs of different keys and tokens in turn"""
+    rng = np.random.default_rng([n, 5])
+    inputs, want = [], [[], []]
+    for stacks, token in ((3, 0), (7, 900)):
+        ref, cur = operators(P, rng, n), operators(P, rng, n + 30)
+        for ops in (ref, cur):
+            ops["op_token"] += token
+            ops["stack_hash"] = rng.integers(0, stacks, len(ops))
+        anchors = np.zeros(40, dtype=P.ANCHOR_DT)
+        anchors["ref_op"] = np.sort(rng.choice(n, 40, replace=False))
+        inputs.append((ref, cur, anchors))
+
+    def aligned(i):
+        r = P.ss_align_sequence(ctx, *inputs[i])
+        return {k: r[k] for k in ("n_keys", "lcs", "ref_to_cur", "new_idx")}
+
+    def matched(i):
+        r = P.ss_match_sequence(ctx, *inputs[i], flags=P.SS_MATCH_ALIGN)
+        return {k: r[k] for k in ("dot", "na", "nb", "new_idx", "level")}
+    for i, (ref, cur, _) in enumerate(inputs):
+        a, b = cur["op_token"].astype(np.int64), np.pad(ref["op_token"].astype(np.int64), (0, 30))
+        want[0].append(dict(aligned(i), n_keys=len(np.unique(cur[["op_token", "stack_hash", "sig"]]))))
+        want[1].append(dict(matched(i), dot=(a * b).sum(), na=(a * a).sum(), nb=(b * b).sum()))
+    in_turn(aligned, want[0])
+    in_turn(matched, want[1])
+
+
 @pytest.mark.parametrize("n_ev,n_pe,n_ops", [(1000, 400, 9000), (9000, 3000, 6000), (60000, 20, 30000)])
 def test_lists_out_of_order_in_turn(P, ctx, n_ev, n_pe, n_ops):                      # noqa: F811
     """the sums that other workgroups gathered are there for the one that does the operators"""
