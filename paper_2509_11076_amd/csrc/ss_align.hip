@@ -763,12 +763,13 @@ __device__ __forceinline__ uint32_t leading_zeros(uint32_t x) {
 
 // Rows [lo, hi) and kTileWords words from word w0 on (w0 may be negative: empty); stops = M | ~V.  A step of the row buffer holds
 // consecutive words of consecutive rows, so threads run along it there, and along a mask row for the masks; each thread's loads are
-// all on their way before the first is waited for.
+// all on their way before the first is waited for.  n_keys, if given: false, and nothing read but ids, where there are too many for
+// ids of this form (looked at while the ids are on their way; in front of them it takes 0.4 us).
 constexpr uint32_t kTileThreads = 256;
 
 template <class Id>
-__device__ __forceinline__ void load_tile(const Id *ref_id, const uint32_t *masks, const uint32_t *rows, uint32_t W,
-                                          uint32_t n_steps, RowBlock blk, int w0, Tile &tile) {
+__device__ __forceinline__ bool load_tile(const Id *ref_id, const uint32_t *masks, const uint32_t *rows, uint32_t W,
+                                          uint32_t n_steps, RowBlock blk, int w0, Tile &tile, const uint32_t *n_keys = nullptr) {
   constexpr uint32_t kMasks = kWalkRows * kTileWords / kTileThreads, kRows = (kWalkRows + kSkew * kTileWords) * kTileWords / kTileThreads;
   static_assert(kMasks * kTileThreads == kWalkRows * kTileWords && kRows * kTileThreads == (kWalkRows + kSkew * kTileWords) * kTileWords, "");
   const uint32_t n_rows = blk.hi - blk.lo, l = threadIdx.x % kTileWords;
@@ -780,6 +781,7 @@ __device__ __forceinline__ void load_tile(const Id *ref_id, const uint32_t *mask
     const uint32_t q = (u * kTileThreads + threadIdx.x) / kTileWords;
     id[u] = q < n_rows ? ref_id[kIdPad + blk.hi - 1 - q] : Id(0);
   }
+  if (sizeof(Id) == 2 && n_keys && *n_keys >= kLdsKeys) return false;
   uint32_t V[kRows], M[kMasks];
 #pragma unroll
   for (uint32_t u = 0; u < kRows; ++u) {                     // row lo + t - back
@@ -799,6 +801,7 @@ __device__ __forceinline__ void load_tile(const Id *ref_id, const uint32_t *mask
     TileWord &x = tile[n_rows - 1 - (t - back)][l + 1];
     x.stops = x.equal | ~V[u];
   }
+  return true;
 }
 
 // Lane q: which words of the block's row q hold a stop (bit l + 1: word l).
@@ -844,12 +847,11 @@ __global__ __launch_bounds__(kEntries) void ss_align_tab_kernel(const Id *__rest
                                                                 const uint32_t *__restrict__ rows,
                                                                 uint16_t *__restrict__ table, const uint32_t *__restrict__ n_keys, uint32_t k_first) {
   __shared__ Tile tile;
-  if (sizeof(Id) == 2 && *n_keys >= kLdsKeys) return;        // launched before the number was known, and there are no rows
   const uint32_t k = k_first + blockIdx.x, e0 = win.start(k) + blockIdx.y * kEntries;
   if (e0 > win.m) return;
   const RowBlock blk(k, win.n);
   const int w0 = (int)(e0 / 32) - (int)(kMargin / 32);
-  load_tile(ref_id, masks, rows, W, n_steps, blk, w0, tile);
+  if (!load_tile(ref_id, masks, rows, W, n_steps, blk, w0, tile, n_keys)) return;        // launched before the number was known: no rows
   __syncthreads();
   const int j = (int)(e0 + threadIdx.x);
   const int out = walk_tile(blk.hi - blk.lo, w0, min(j, (int)win.m), tile);
