@@ -73,7 +73,8 @@ static __device__ __forceinline__ uint32_t key_of(uint32_t id) { return id; }
 // 1 + the operator that stands for a key; which key gets which id does not matter.  Operators of ref whose key cur does
 // not hold share the id n_keys, whose mask row is empty.  Ids are written in the form the rows kernel reads (key_of):
 // 16 bits if there are few enough keys, 32 bits otherwise.  2,310 operators: one workgroup, 6.4 us; 64,609: three
-// launches, 33 us, of which 23 bring the operators over the link.  An unordered map on the host took about 23 and 260 us.
+// launches, 36 us, of which 24 bring the operators over the link and clear what the rows need clear; the third one makes the masks
+// as well.  An unordered map on the host took about 23 and 260 us.
 
 struct KeyArgs {
   const ss_op_t *ref, *cur;

@@ -184,7 +184,7 @@ struct ss_ctx {
   uint32_t align_wait_looks = 1u << 20;
   uint32_t align_one_by_one = 0;
   uint32_t match_many_keys = 0;     // calls of short sequences to come that don't try the form for few keys (ss_match.hip)
-  bool match_few_keys = false;      // the last try was worth it
+  uint32_t match_few_ops = 0;       // of the reference sequence when the last try was worth it; 0: it wasn't
   bool align_many_keys = false;     // the last call's ids had 32 bits: the next one of long sequences waits for the number of keys
   ss_sched sched;
   ss_stats_t stats;

@@ -23,7 +23,8 @@ constexpr uint32_t kLenLimit = 1u << 23;
 
 constexpr uint32_t kMaxParts = 1024;
 // Calls until short sequences are given to one workgroup again after one with too many keys.  A try for nothing costs 9 us, a context's
-// first 14; so where none has been worth it yet, or the last one wasn't, some operators are looked at first (more_keys, 1 us).
+// first 14; so where none has been worth it yet, the last one wasn't or was of sequences half as long, some operators are looked at
+// first (more_keys, 1 us).
 constexpr uint32_t kTryAgain = 64;
 
 // Everything that has to be done before anchors can be looked for, in one pass: the sequences (and anchors) are copied
@@ -1169,7 +1170,7 @@ extern "C" int ss_match_sequence(ss_ctx *ctx, const ss_op_t *ref, uint32_t n, co
       const uint32_t most_keys = short_keys(n, m, k);
       if (ctx->match_many_keys) {
         ctx->match_many_keys--;
-      } else if (!ctx->match_few_keys && more_keys(ref, n, most_keys)) {
+      } else if (n > 2 * ctx->match_few_ops && more_keys(ref, n, most_keys)) {
         ctx->match_many_keys = kTryAgain;
       } else {
         std::memcpy(h + ho_ref, ref, (size_t)n * op_bytes);
@@ -1184,7 +1185,7 @@ extern "C" int ss_match_sequence(ss_ctx *ctx, const ss_op_t *ref, uint32_t n, co
         hipLaunchKernelGGL(ss_match_short_kernel, dim3(1), dim3(kShortThreads), sizeof(ShortLds), s, a);
         SS_HIP(hipGetLastError());
         if ((rc = ss_wait_done(ctx, told)) != SS_OK) return rc;
-        ctx->match_few_keys = !said[1];
+        ctx->match_few_ops = said[1] ? 0 : n;
         if (!said[1]) {
           const ss_cosine_part &sums = *(const ss_cosine_part *)(h + ho_part);
           if (sums.bad) return SS_E_INVAL;                   // a token beyond 2^18

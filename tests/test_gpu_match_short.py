@@ -110,11 +110,16 @@ def test_contexts_that_begin_with_many_keys(P):                            # noq
     forms = [hidden, rng.integers(0, 900, n), rng.integers(0, 30, n), np.arange(n)]
     pairs = [(ops(f), ops(np.roll(f, 5))) for f in forms]
     want = [landings(ref, cur, anc) for ref, cur in pairs]
+    small = tuple(x[:40].copy() for x in pairs[2])
+    small_want = landings(*small, anc[:9])
     for first in range(4):
         c = P.ss_create(P.ss_config_default())
         try:
             for i in [first] + [x for x in (0, 2, 1, 2, 3, 0) for _ in range(1 if x != 1 else 70)]:
                 r = P.ss_match_sequence(c, *pairs[i], anc)
                 assert np.array_equal(r["new_idx"], want[i][0]) and np.array_equal(r["level"], want[i][1])
+                if i in (1, 2):                                    # sequences much shorter in between
+                    r = P.ss_match_sequence(c, *small, anc[:9])
+                    assert np.array_equal(r["new_idx"], small_want[0])
         finally:
             P.ss_destroy(c)
