@@ -36,10 +36,10 @@ constexpr uint32_t kSkew = 2;                          // steps that a lane is b
 constexpr uint32_t kIdPad = 64 * kSkew;                // entries before the first id (lanes whose row has not begun)
 // Rows up to this many bytes go straight to host memory and are walked there: beside the kernel's pace they cost the
 // link nothing up to about 13 GB/s, and the walk on the GPU takes four more launches.  us a call, walked on the host and on the
-// GPU: 2,694 x 2,704 operators (1.4 MiB) 104 and 113, 3,100 x 3,100 (1.6) 105 and 111, 3,300 x 3,300 (1.7) 119 and 113, 3,882 x 3,880
-// 148 and 132, 5,192 x 5,196 201 and 154, 16,000 x 1,000 337 and 302; paths beside the diagonal: kAllTables.  Where cur is more than
+// GPU: 2,694 x 2,704 operators (1.4 MiB) 93 and 101, 3,100 x 3,100 (1.6) 109 and 108, 3,300 x 3,300 (1.7) 124 and 111, 3,882 x 3,880
+// 143 and 123, 5,192 x 5,196 195 and 140, 16,000 x 1,000 332 and 280; paths beside the diagonal: kAllTables.  Where cur is more than
 // twice as long, a block's path leaves the tile of columns that is looked at for it: 2,200 x 6,000 (2.3), all of ref at the front of
-// cur, 124 and 186, spread over cur 123 and 116; 1,800 x 9,000 136 and 244, 500 x 30,000 184 and 386.
+// cur, 124 and 186, spread over cur 112 and 113; 1,800 x 9,000 126 and 228, 500 x 30,000 192 and 384.
 constexpr size_t kHostRowBytes = 1700u << 10, kHostRowBytesSteep = 4u << 20;
 constexpr uint32_t kCarryPad = 8;                      // carry words beyond a strip's last (the first of them is looked at)
 
@@ -703,8 +703,8 @@ __global__ __launch_bounds__(kWgThreads) void ss_align_short_kernel(KeyArgs k, R
 // group's entry known the blocks are walked again side by side to write the pairs (ss_align_pairs_kernel).  Where a group's
 // table has no entry the chain follows its blocks' own, and a block whose entry lies outside its window, or whose path
 // leaves the tile to the left, is walked in place by a wavefront of the chain.
-// 32,312 rows: 28 us for the tables, 5 us for the groups' and 11 us for the chain (an LDS read and a few vector operations
-// per group; 17 where each group's went through the scalar unit, 90 block by block), 14 us for the pairs; single steps in one
+// 32,312 rows: 28 us for the tables, 5 us for the groups' and 12 us for the chain (an LDS read and a few vector operations
+// per group; 17 where each group's went through the scalar unit, 90 block by block), 15 us for the pairs; single steps in one
 // wavefront took 97 ns a row (3.1 ms), the rows over the host link (130 MB) 2.3 ms and a walk there.
 constexpr uint32_t kWalkRows = 64;
 // Entry columns tabulated per block of rows (windows).  Where that takes no more than kAllTables workgroups, all columns: no path leaves
@@ -712,13 +712,14 @@ constexpr uint32_t kWalkRows = 64;
 // come and go all along the sequences strays from the diagonal by some hundred columns (32,312 rows: tables 48 us, half as many 28).
 // If it leaves them after all, the walk goes on from there with kWindow columns around the diagonal of what is left, which finds a
 // path that has come to lie beside the first one.
-// us a call, sequences of 9,000 with 700 foreign operators in a quarter of one and as many missing in the last of it: 247, by a second
-// walk of all blocks 272, with kWindow alone 254; with 1,500 foreign ones 266, 392 and 351; without any 208, 207 and 243 (the last
-// with the tables' older kernel).
-// All columns, or few of them at first (kAllTablesNear): 3,300 x 3,300 111 us where the path stays near the diagonal (few at first
-// 107), 126 where it lies 700 or 1,500 beside it (150 and 163; walked on the host 125); 4,400 x 4,400 137 and 129, beside it 145 to
-// 160 and 166 to 175 (host 163); 5,100 x 5,100 150 and 138, beside it 158 to 180 and 160 to 199 (host 190).  Where lengths differ
-// by more the path is seldom near the diagonal: 8,000 operators and the first 3,000 of them 192 us, with kWindow 709, on the host 235.
+// us a call, sequences of 9,000 with 700 foreign operators in a quarter of one and as many missing in the last of it: 244, by a second
+// walk of all blocks 275, with kWindow alone and the kernels of that time 254; with 1,500 foreign ones 251, 392 and 351; without any
+// 209, 207 and 243.
+// All columns, or few of them at first (kAllTablesNear), or the host's walk: 3,300 x 3,300 112 us, 109 and 125 where the path stays
+// near the diagonal, 120 to 133, 134 to 150 and 124 to 134 where it lies 700 or 1,500 beside it; 4,400 x 4,400 138, 130 and 162, beside
+// it 147 to 156, 165 to 175 and 162 to 169; 5,100 x 5,100 151, 139 and 190, beside it 160 to 169, 154 to 183 and 190 to 196.  Where
+// lengths differ by more the path is seldom near the diagonal: 8,000 operators and the first 3,000 of them 191 us, with kWindow 709, on
+// the host 235.
 constexpr uint32_t kWindow = 2048, kNarrowWindow = 1024, kNearlyEqual = 512, kMostColumns = 8192;
 constexpr uint32_t kAllTables = 2600, kAllTablesNear = 1200;
 constexpr uint32_t kEntries = 256;                     // of these, per workgroup
@@ -864,9 +865,9 @@ __global__ __launch_bounds__(kEntries) void ss_align_tab_kernel(const Id *__rest
 // and the run's length is the number of leading ones; then one find-first in the row the run ended in.
 // Bound by the latency of the words' loads: four words to the left are loaded at a time, by every lane, also beside the rows and
 // the words, whose bits nobody looks at (one word ahead at a time, handed on from word to word, is copied behind its load, which is
-// waited for: 15,000 operators and the first 5,000 of them, most of whose path lies outside the windows, 2,044 us a call, so up to
-// 2,500).  Through columns without a stop it goes 4,096 at a time (word by word 16,000 operators with nothing in common 743 us
-// a call, so 361).
+// waited for: 15,000 operators and the first 5,000 of them, most of whose path lies outside the windows, 2,050 us a call, so up to
+// 2,500).  Through columns without a stop it goes 4,096 at a time (word by word 16,000 operators with nothing in common 587 us
+// a call, so 378).
 __device__ uint32_t walk_in_place(uint32_t id, const uint32_t *masks, const uint32_t *rows, uint32_t W, uint32_t n_steps, RowBlock blk,
                                   uint32_t j, int32_t *ref_to_cur) {
   const int lane = threadIdx.x & 63, n_rows = (int)(blk.hi - blk.lo), r = max((int)blk.hi - 1 - lane, (int)blk.lo);
@@ -1135,7 +1136,7 @@ __device__ __forceinline__ int32_t walk_runs(uint32_t n_rows, int w0, int j, con
 
 // Blocks from k_win on were walked by the chain with windows `win`, those before with `first`.
 // One wavefront walks, all of them load its tile.  Bound by the latency of loads that need each other (the group's entry, the
-// block's, the tile's ids and masks) and of the walk's LDS reads: 32,312 rows 14.0 us; with one thread that walks row by row, the
+// block's, the tile's ids and masks) and of the walk's LDS reads: 32,312 rows 15.3 us; with one thread that walks row by row, the
 // block's entry by up to seven reads one after the other and the tile's loads one after the other 20.1.
 constexpr uint32_t kPairThreads = kTileThreads;
 static_assert(kEntries == kTileThreads, "a table's workgroup loads its tile");
@@ -1202,7 +1203,8 @@ struct Layout {
     // The windows that the walk begins with (kWindow)
     const uint32_t all = (uint32_t)ss_align_up(m + 1, kEntries);
     const bool near = std::max(n, m) - std::min(n, m) <= kNearlyEqual;
-    window = all <= kWindow || (all <= kMostColumns && walk_blocks * (all / kEntries) <= (near ? kAllTablesNear : kAllTables)) ? all : near ? kNarrowWindow : kWindow;
+    const uint32_t most = near ? kAllTablesNear : kAllTables;
+    window = all <= kWindow || (all <= kMostColumns && walk_blocks * (all / kEntries) <= most) ? all : near ? kNarrowWindow : kWindow;
     upto_stride = std::max(window, kWindow);               // the same for a second walk, of whose blocks it leaves the others'
     const size_t entries = upto_stride;
     bits = 13;

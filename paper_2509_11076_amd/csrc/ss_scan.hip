@@ -969,7 +969,8 @@ __global__ __launch_bounds__(kTileThreads) void ss_scan_running_kernel(ScanArgs 
     const uint32_t own_end = tl.policy ? a.tiles0 + a.tiles1 : a.tiles0;
     constexpr uint32_t kLooks = 16;
     uint64_t later = 0;
-    if (kFew && tid < kLooks && tl.index + 1 + tid < own_end) later = __hip_atomic_load(&a.board->tile[4][tl.index + 1 + tid], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if (kFew && tid < kLooks && tl.index + 1 + tid < own_end)
+      later = __hip_atomic_load(&a.board->tile[4][tl.index + 1 + tid], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     const uint64_t since = wall_clock64();
     const uint32_t first = tl.policy ? 0 : a.tiles0, end = tl.policy ? a.tiles0 : a.tiles0 + a.tiles1;
     for (uint32_t i = first + tid; i < end; i += kTileThreads) {
