@@ -707,21 +707,22 @@ __global__ __launch_bounds__(kWgThreads) void ss_align_short_kernel(KeyArgs k, R
 // per group; 17 where each group's went through the scalar unit, 90 block by block), 15 us for the pairs; single steps in one
 // wavefront took 97 ns a row (3.1 ms), the rows over the host link (130 MB) 2.3 ms and a walk there.
 constexpr uint32_t kWalkRows = 64;
-// Entry columns tabulated per block of rows (windows).  Where that takes no more than kAllTables workgroups, all columns: no path leaves
-// them.  Otherwise kWindow; or, where the lengths differ by at most kNearlyEqual, kNarrowWindow first, since a path of operators that
+// Entry columns tabulated per block of rows (windows).  Where lengths differ by more than half of kWindow and that takes no more than
+// kAllTables workgroups, all columns: no path leaves them.  Otherwise kWindow; or, where the lengths differ by at most kNearlyEqual, kNarrowWindow first, since a path of operators that
 // come and go all along the sequences strays from the diagonal by some hundred columns (32,312 rows: tables 48 us, half as many 28).
 // If it leaves them after all, the walk goes on from there with kWindow columns around the diagonal of what is left, which finds a
 // path that has come to lie beside the first one.
 // us a call, sequences of 9,000 with 700 foreign operators in a quarter of one and as many missing in the last of it: 244, by a second
 // walk of all blocks 275, with kWindow alone and the kernels of that time 254; with 1,500 foreign ones 251, 392 and 351; without any
 // 209, 207 and 243.
-// All columns, or few of them at first (kAllTablesNear), or the host's walk: 3,300 x 3,300 112 us, 109 and 125 where the path stays
-// near the diagonal, 120 to 133, 134 to 150 and 124 to 134 where it lies 700 or 1,500 beside it; 4,400 x 4,400 138, 130 and 162, beside
-// it 147 to 156, 165 to 175 and 162 to 169; 5,100 x 5,100 151, 139 and 190, beside it 160 to 169, 154 to 183 and 190 to 196.  Where
-// lengths differ by more the path is seldom near the diagonal: 8,000 operators and the first 3,000 of them 191 us, with kWindow 709, on
-// the host 235.
+// All columns, kWindow or kNarrowWindow first: lengths that are nearly equal, the path near the diagonal, 3,300 operators 110 us and
+// 107, 3,600 117 and 112, 4,000 126 and 120; 700 or 1,500 beside it 119 to 148 and 126 to 165 (the host 124 to 169, a second walk of all
+// blocks 136 to 188), but sequences that are that far apart are the rarer.  Operators missing all along one of them, 4,000 and 3,400 of
+// them 125 and 120, 6,000 and 5,100 171 and 157; 5,000 and 4,100 of them from one end on 145 and 136.  Lengths that differ by more are
+// seldom those of a path near the diagonal: 8,000 operators and the first 3,000 of them 192 us, with kWindow 704, on the host 235;
+// 5,000 and the first 3,500 149 and 158, with operators missing all along 142 and 139.
 constexpr uint32_t kWindow = 2048, kNarrowWindow = 1024, kNearlyEqual = 512, kMostColumns = 8192;
-constexpr uint32_t kAllTables = 2600, kAllTablesNear = 1200;
+constexpr uint32_t kAllTables = 2600;
 constexpr uint32_t kEntries = 256;                     // of these, per workgroup
 constexpr uint32_t kMargin = 256;                      // columns a tile reaches to the left of its first entry
 constexpr uint32_t kTileWords = (kEntries + kMargin) / 32;
@@ -1202,9 +1203,9 @@ struct Layout {
     short_rows = row_bytes <= (m > 2 * (uint64_t)n ? kHostRowBytesSteep : kHostRowBytes);
     // The windows that the walk begins with (kWindow)
     const uint32_t all = (uint32_t)ss_align_up(m + 1, kEntries);
-    const bool near = std::max(n, m) - std::min(n, m) <= kNearlyEqual;
-    const uint32_t most = near ? kAllTablesNear : kAllTables;
-    window = all <= kWindow || (all <= kMostColumns && walk_blocks * (all / kEntries) <= most) ? all : near ? kNarrowWindow : kWindow;
+    const uint32_t differ = std::max(n, m) - std::min(n, m);
+    const bool few_tables = all <= kMostColumns && walk_blocks * (all / kEntries) <= kAllTables;
+    window = all <= kWindow || (few_tables && differ > kWindow / 2) ? all : differ <= kNearlyEqual ? kNarrowWindow : kWindow;
     upto_stride = std::max(window, kWindow);               // the same for a second walk, of whose blocks it leaves the others'
     const size_t entries = upto_stride;
     bits = 13;

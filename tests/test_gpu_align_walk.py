@@ -120,7 +120,8 @@ def test_walks_that_go_on_where_the_path_has_left_the_windows(P, ctx, keys, at):
 
 
 @pytest.mark.parametrize("n,m", [(3300, 3300), (4000, 4500), (4288, 4288), (4289, 4350), (4800, 4300), (8000, 3000), (2200, 4400), (2200, 4401),
-                                 (5100, 8191), (5100, 8192), (12000, 2047), (12000, 2048), (20000, 900)])
+                                 (5100, 8191), (5100, 8192), (12000, 2047), (12000, 2048), (20000, 900),
+                                 (4000, 5024), (4000, 5025), (5025, 4000)])
 def test_tables_of_all_columns(P, ctx, n, m):                      # noqa: F811
     """paths near the diagonal, far beside it and along the edges, where all columns are tabulated and where they just aren't"""
     rng = np.random.default_rng([n, m, 8])
