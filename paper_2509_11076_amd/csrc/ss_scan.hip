@@ -845,11 +845,12 @@ __device__ __forceinline__ TileSum sum_events(const ScanArgs &a, const Tile &tl,
 
 // Gaps of a tile of few events, each filled by the whole workgroup, 8 bytes a lane side by side: bound by how many stores a workgroup
 // has under way.  Both launches of 460 + 28 events over 58,299 operators 21 us, of 2,000 + 4 over 65,536 23; one by one by the first
-// wavefront, 64 entries of 24 bytes in 0.1 us (fill_gap), 29 and 56.  Up to kLongGaps operators to an event lanes and wavefronts that
-// each fill their own gaps are as fast or faster (both launches, filled each by its own and together; the list beside 2,000 events:
-// 9 operators to an event, 1,000 over 9,000: 13.9 us and 14.3; 40, 400 over 16,000: 14.1 and 14.3; 75, 400 over 30,000: 14.5 and 14.8;
-// 160, 100 over 16,000: 14.5 and 14.2; 300, 30 over 9,000: 14.0 and 13.7; 1,000, 16 over 16,000: 20 and 13.7).
-constexpr uint32_t kFewInTile = 8, kLongGaps = 128;
+// wavefront, 64 entries of 24 bytes in 0.1 us (fill_gap), 29 and 56.  Where an event stands for few
+// operators on average, but not everywhere, a tile of short gaps loses 0.3 and one with a long gap gains 2 us (both launches, filled each
+// by its own and together; evenly spread 1,000 over 9,000: 13.9 and 14.3, 400 over 30,000: 14.5 and 14.8; the policy of 939 tensors that
+// live from one half of 29,449 operators into the other, 1,878 events: 21.1 and 18.8).  Up to kLongGaps operators to an event it is as
+// fast (7 to one: 16.4 and 14.7; 5 to one: 14.9 and 15.3).
+constexpr uint32_t kFewInTile = 8, kLongGaps = 8;
 
 __host__ __device__ inline bool few_in_tile(uint32_t tile, uint64_t events, uint32_t n_ops) {
   return events && tile <= kFewInTile && n_ops > kLongGaps * events;

@@ -13,7 +13,8 @@ pytestmark = pytest.mark.gpu
 @pytest.mark.parametrize("n_ev,n_pe,n_ops", [
     (1, 0, 3000), (0, 1, 3000), (1, 1, 65536), (2, 3, 4097), (8, 9, 2901), (9, 65, 65536), (360, 12, 2901), (500, 13, 26112),
     (257, 512, 65536), (2047, 1, 16377), (2048, 2049, 65536), (4096, 3, 60000), (2047, 300, 1 << 21),
-    (128, 40, 16384), (127, 40, 16385), (40, 2048, 65536), (700, 512, 65537),          # about 128 operators to an event
+    (128, 40, 16384), (127, 40, 16385), (40, 2048, 65536), (700, 512, 65537), (300, 1878, 29449),
+    (1000, 40, 8000), (1000, 40, 8001),                                                # about eight operators to an event
 ])
 def test_few_events_over_many_operators(P, ctx, n_ev, n_pe, n_ops):           # noqa: F811
     rng = np.random.default_rng([n_ev, n_pe, n_ops, 9])

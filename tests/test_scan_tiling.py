@@ -31,8 +31,8 @@ def test_tiles(n, other):
 
 @pytest.mark.parametrize("n_ev,n_pe,n_ops,few", [
     (100000, 0, 40000, 0), (0, 100000, 40000, 0), (5000, 0, 9000, 0), (0, 0, 9000, 0), (0, 0, 1, 0),         # a list without events has no gaps
-    (10, 0, 9000, 1), (0, 10, 9000, 1), (100000, 10, 9000, 1), (1000, 0, 128000, 0), (1000, 0, 128001, 1), (0, 70, 8961, 1),
-    (100000, 70, 8961, 1), (100000, 70, 8960, 0), (1000, 0, 9000, 0), (2049, 0, 1 << 23, 0),      # 128 operators to an event; 8 events to a tile
+    (10, 0, 9000, 1), (0, 10, 9000, 1), (100000, 10, 9000, 1), (1000, 0, 8000, 0), (1000, 0, 8001, 1), (0, 70, 561, 1),
+    (100000, 70, 561, 1), (100000, 70, 560, 0), (2049, 0, 1 << 23, 0),      # 8 operators to an event; 8 events to a tile
 ])
 def test_whose_gaps_are_filled_together(n_ev, n_pe, n_ops, few):
     import paper_2509_11076_amd.binding as B
