@@ -79,8 +79,8 @@ def test_few_keys_and_many_in_turn(P, n, m):                       # noqa: F811
 
 @pytest.mark.parametrize("period", [1, 2, 3, 4, 5, 7, 64])
 def test_blocks_of_short_runs(P, ctx, period):                     # noqa: F811
-    """a foreign operator in every `period`-th place: 64 to 0 ends of runs to a block, 16 and 13 on either side of where it is gone
-    through row by row; the others equal all along, or drawn anew"""
+    """a foreign operator in every `period`-th place: 64 to 0 ends of runs to a block, 32 and 48 rows to the first
+    sixteen on either side of where it is gone through row by row; the others equal all along, or drawn anew"""
     rng = np.random.default_rng(period)
     ref = rng.integers(0, 20, 9300)
     cur = np.where(np.arange(len(ref)) % period == 0, 50, ref)
